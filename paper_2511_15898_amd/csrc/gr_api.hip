@@ -1,4 +1,5 @@
 // C ABI of the Global Resolution verifier: handle, argument checks, kernel launches.
+#include <algorithm>
 #include <new>
 #include <vector>
 
@@ -367,8 +368,10 @@ extern "C" int gr_accept_sweep(gr_handle h, const float* p, const float* q, cons
             for (int i = 0; i < kSweepMaxK; ++i) fs.ks[i] = i < nk ? ((ks[i] <= 0 || ks[i] >= V) ? V : ks[i]) : 0;
             for (int i = 0; i < kSweepMaxN; ++i) {
                 if (i < nn && (ns[i] < 1 || ns[i] > kSweepMaxDrafts)) return GR_EINVAL;
-                fs.ns[i] = i < nn ? ns[i] : 1;
+                fs.npos[i] = i;
             }
+            std::stable_sort(fs.npos, fs.npos + nn, [ns](int x, int y) { return ns[x] < ns[y]; });
+            for (int i = 0; i < kSweepMaxN; ++i) fs.ns[i] = i < nn ? ns[fs.npos[i]] : 1;
             h->solved = false;
             const int rc = prepare_full(h, B, V);
             if (rc != GR_OK) return rc;

@@ -131,7 +131,8 @@ hipError_t launch_sweep(const SweepParams& sw, int B, hipStream_t stream);
 // The grid of a sweep whose largest support lives in the HBM workspace.
 struct FullSweep {
     int nk, nn;
-    int ks[kSweepMaxK]; int ns[kSweepMaxN];   // ks: V for "no top-k"
+    int ks[kSweepMaxK]; int ns[kSweepMaxN];   // ks: V for "no top-k"; ns in rising order
+    int npos[kSweepMaxN];         // place of ns[i] in the caller's list
     double* mass;                 // [B, kSweepMaxK] q mass of each top-k support
     float* accept_prob;           // [B, nk, nn]
     int* status;                  // [B]

@@ -172,3 +172,14 @@ def test_top_k_sizes_up_to_the_whole_vocabulary_at_full_width():
     acc, st = _sweep(wl.p, wl.q, ks, ns, max_k=0)
     assert np.all(st == 0)
     _check(wl.p, wl.q, ks, ns, range(wl.B), acc)
+
+
+@pytest.mark.parametrize("V,ns", [(8192, [7, 1, 64, 7, 2]), (8193, [16, 16, 3]), (12289, list(range(16, 0, -1)))])
+def test_draft_counts_in_any_order_on_both_workgroup_sizes(V, ns):
+    """Draft counts unsorted and repeated come back in the caller's order; vocabularies on both sides of the large
+    workgroup's threshold, top-k sizes that leave whole waves without a token of the support.  Same bound as above."""
+    wl = W.llm_shaped(B=3, V=V, n=4, k=0, temperature=(0.5, 1.5), near_identical_frac=0.3, seed_sub=V)
+    ks = [0, 3, 257, V - 1]
+    acc, st = _sweep(wl.p, wl.q, ks, ns, max_k=0)
+    assert np.all(st == 0)
+    _check(wl.p, wl.q, ks, ns, range(wl.B), acc)
