@@ -138,22 +138,165 @@ __device__ int block_radix_sort(unsigned long long* k0, int* v0, unsigned long l
     return cur;
 }
 
+// The sort of the large supports: elements of 8 bytes, a 32-bit key in the high word and the token id in the low one.
+template <int NT>
+struct Sort32Lds {
+    static constexpr int kWavesNT = NT / 64;
+    static constexpr int kTile = NT * kSortItems;
+    unsigned long long tile[kTile];                // the tile in digit order
+    unsigned long long wcnt[kWavesNT][64];         // per wave: 256 counters of 16 bits, four to a word
+    int hist[4][256];
+    int start[256];                                // first place of each digit in the tile
+    int dest[256];                                 // output slot of the tile's place 0, per digit
+    int skip[4];
+};
+
+// Stable least-significant-digit radix sort of one row's `count` elements by their high words, 8 bits per pass, between
+// a and b; returns the buffer that holds the result.  A pass moves tiles of 4 NT elements: every wave ranks 256
+// consecutive ones among themselves (ballots, and counters that are its own, so no barrier lies between its four
+// rounds), wave 0 turns the counters into places, and the tile goes through LDS into digit order, so that the
+// elements of one digit leave as one run (128 bytes on average for NT = 1024) and not one by one.  Three barriers per tile.
+// Bound: the memory system, 16 bytes per element and pass.  All threads call.
+template <int NT>
+__device__ unsigned long long* block_sort32(unsigned long long* a, unsigned long long* b, int count, Sort32Lds<NT>& S) {
+    constexpr int kTile = Sort32Lds<NT>::kTile;
+    constexpr int NW = NT / 64;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    for (int c = tid; c < 4 * 256; c += NT) (&S.hist[0][0])[c] = 0;
+    if (tid < 4) S.skip[tid] = 0;
+    __syncthreads();
+    for (int i0 = 0; i0 < count; i0 += NT) {
+        const int i = i0 + tid;
+        const bool valid = i < count;
+        const unsigned key = valid ? static_cast<unsigned>(a[i] >> 32) : 0u;
+        const unsigned long long vm = __ballot(valid);
+        if (vm == 0ull) continue;                               // wave-uniform; lane 0 is valid otherwise
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int d = static_cast<int>((key >> (8 * j)) & 255u);
+            const int d0 = __builtin_amdgcn_readfirstlane(d);
+            if (__ballot(valid && d == d0) == vm) {             // one digit in the whole wave: one update
+                if (lane == 0) atomicAdd(&S.hist[j][d0], __popcll(vm));
+            } else if (valid) {
+                atomicAdd(&S.hist[j][d], 1);
+            }
+        }
+    }
+    __syncthreads();
+    for (int c = tid; c < 4 * 256; c += NT) if ((&S.hist[0][0])[c] == count) S.skip[c >> 8] = 1;
+    __syncthreads();
+
+    for (int pass = 0; pass < 4; ++pass) {
+        if (S.skip[pass]) continue;
+        const int shift = 32 + 8 * pass;
+        int next[4] = {0, 0, 0, 0};                             // wave 0: next output slot of digits 4 lane .. 4 lane + 3
+        if (wv == 0) {
+            int tot = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) { next[j] = tot; tot += S.hist[pass][4 * lane + j]; }
+            int incl = tot;
+            for (int o = 1; o < 64; o <<= 1) { const int up = __shfl_up(incl, o); if (lane >= o) incl += up; }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) next[j] += incl - tot;
+        }
+        unsigned short* mycnt = reinterpret_cast<unsigned short*>(&S.wcnt[wv][0]);
+        unsigned long long en[kSortItems];
+#pragma unroll
+        for (int j = 0; j < kSortItems; ++j) {
+            const int i = wv * 64 * kSortItems + j * 64 + lane;
+            en[j] = i < count ? a[i] : 0ull;
+        }
+        for (int t0 = 0; t0 < count; t0 += kTile) {
+            unsigned long long e[kSortItems]; int rank[kSortItems];
+            const int first = t0 + wv * 64 * kSortItems + lane;
+#pragma unroll
+            for (int j = 0; j < kSortItems; ++j) {
+                e[j] = en[j];
+                const int i = first + kTile + j * 64;
+                en[j] = i < count ? a[i] : 0ull;
+            }
+            S.wcnt[wv][lane] = 0ull;                            // read last before the barrier that ended the previous tile's second phase
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int j = 0; j < kSortItems; ++j) {
+                const bool valid = first + j * 64 < count;
+                const int d = static_cast<int>((e[j] >> shift) & 255ull);
+                unsigned long long peers = __ballot(valid);     // lanes of this wave that hold the same digit
+#pragma unroll
+                for (int bb = 0; bb < 8; ++bb) {
+                    const bool bit = (d >> bb) & 1;
+                    const unsigned long long m = __ballot(valid && bit);
+                    peers &= bit ? m : ~m;
+                }
+                const int before = mycnt[d];
+                const int below = __popcll(peers & ((1ull << lane) - 1ull));
+                rank[j] = before + below;
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); __builtin_amdgcn_wave_barrier();
+                if (valid && below == 0) mycnt[d] = static_cast<unsigned short>(before + __popcll(peers));
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); __builtin_amdgcn_wave_barrier();
+            }
+            __syncthreads();
+            if (wv == 0) {
+                // four digits per lane: the waves' counts become offsets (16-bit fields: a tile holds at most 4096)
+                unsigned long long run = 0ull;
+#pragma unroll 4
+                for (int w = 0; w < NW; ++w) { const unsigned long long c = S.wcnt[w][lane]; S.wcnt[w][lane] = run; run += c; }
+                int c[4]; int tot = 0;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) { c[j] = static_cast<int>((run >> (16 * j)) & 0xFFFFull); tot += c[j]; }
+                int incl = tot;
+                for (int o = 1; o < 64; o <<= 1) { const int up = __shfl_up(incl, o); if (lane >= o) incl += up; }
+                int at = incl - tot;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    S.start[4 * lane + j] = at; S.dest[4 * lane + j] = next[j] - at;
+                    at += c[j]; next[j] += c[j];
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < kSortItems; ++j) {
+                if (first + j * 64 < count) {
+                    const int d = static_cast<int>((e[j] >> shift) & 255ull);
+                    S.tile[S.start[d] + mycnt[d] + rank[j]] = e[j];
+                }
+            }
+            __syncthreads();
+            const int cnt = min(kTile, count - t0);
+#pragma unroll
+            for (int j = 0; j < kSortItems; ++j) {
+                const int i = j * NT + tid;
+                if (i < cnt) { const unsigned long long x = S.tile[i]; b[S.dest[static_cast<int>((x >> shift) & 255ull)] + i] = x; }
+            }
+        }
+        __syncthreads();
+        unsigned long long* t = a; a = b; b = t;
+    }
+    return a;
+}
+__device__ __forceinline__ unsigned long long pack32(unsigned key, int id) {
+    return (static_cast<unsigned long long>(key) << 32) | static_cast<unsigned>(id);
+}
+__device__ __forceinline__ int packed_id(unsigned long long e) { return static_cast<int>(static_cast<unsigned>(e)); }
+
 #pragma clang fp contract(off)
 // The running sums of wave_sequential_scan for operands in LDS: every lane reads x[j] (one address
 // for the whole wave: a broadcast read) and adds it, so all lanes hold the same sums, in the order of
 // a sequential loop; lane 0 stores them.  x must be readable and zero, out writable, up to the next
 // multiple of 64 beyond `count`.  out[0] = start, out[i + 1] = start + x[0] + ... + x[i].
+// U sums are held in registers between two rounds of stores.
+template <int U = 64>
 __device__ __forceinline__ void wave_sequential_scan_padded(const double* x, double* out, int count, double start) {
     const int lane = threadIdx.x & 63;
     double acc = start;
     if (lane == 0) out[0] = start;
-    for (int base = 0; base < count; base += 64) {
-        double a[64];
+    for (int base = 0; base < count; base += U) {
+        double a[U];
 #pragma unroll
-        for (int j = 0; j < 64; ++j) { acc = acc + x[base + j]; a[j] = acc; }
+        for (int j = 0; j < U; ++j) { acc = acc + x[base + j]; a[j] = acc; }
         if (lane == 0) {
 #pragma unroll
-            for (int j = 0; j < 64; ++j) out[base + j + 1] = a[j];
+            for (int j = 0; j < U; ++j) out[base + j + 1] = a[j];
         }
     }
 }
@@ -197,19 +340,22 @@ __device__ int block_prefix_sum_excl(int v, int* buf0, int* buf1, int* total) {
 // chist[4096]: members per magnitude class of a positive float (its bit pattern >> 19: exponent and four mantissa
 // bits; every member lies below the class's upper edge, so count x edge bounds the class's mass).  Classes are
 // dropped from the bottom while that bound stays within `budget`; returns the lowest class that stays (0 when every
-// class would fit: nothing is dropped then).  dscan: LDS double[kThreads], bsel: LDS int.  All threads call.
+// class would fit: nothing is dropped then).  dscan: LDS double[kThreads], bsel: LDS int.  All threads
+// call; the first kThreads of them own the classes.
 __device__ int class_threshold(const int* chist, double budget, double* dscan, int* bsel) {
     const int tid = threadIdx.x;
     // thread t owns classes 16 t .. 16 t + 15; prefix of the bounds over the threads, serially by thread 0
     double local = 0.0;
-    for (int c = 16 * tid; c < 16 * tid + 16; ++c)
-        local += static_cast<double>(chist[c]) * static_cast<double>(__uint_as_float((static_cast<unsigned>(c) + 1u) << 19));
-    dscan[tid] = local;
+    if (tid < kThreads) {
+        for (int c = 16 * tid; c < 16 * tid + 16; ++c)
+            local += static_cast<double>(chist[c]) * static_cast<double>(__uint_as_float((static_cast<unsigned>(c) + 1u) << 19));
+        dscan[tid] = local;
+    }
     if (tid == 0) *bsel = 4096;
     __syncthreads();
     if (tid == 0) { double run = 0.0; for (int t = 0; t < kThreads; ++t) { const double v = dscan[t]; dscan[t] = run; run += v; } }
     __syncthreads();
-    {
+    if (tid < kThreads) {
         double run = dscan[tid];                                 // bound on the mass of all classes below 16 tid
         for (int c = 16 * tid; c < 16 * tid + 16; ++c) {
             run += static_cast<double>(chist[c]) * static_cast<double>(__uint_as_float((static_cast<unsigned>(c) + 1u) << 19));
@@ -239,24 +385,46 @@ __device__ void mark_bad(const FullParams& fp, int row, double ptot, double qtot
 // The sort key is the correctly rounded float64 quotient q/p: for float32 inputs two different
 // ratios differ by at least 2^-48 relative, so their quotients differ and keep their order, and equal
 // ratios give equal quotients -- the same order as the exact cross-product comparison (Sec. 5.1).
-__global__ __launch_bounds__(kThreads) void full_order_kernel(FullParams fp) {
-    __shared__ SortLds S;
+//
+// The quotient's 64-bit pattern is not sorted as a whole: the row's largest and smallest pattern are known from the
+// first pass, and the 32 leading bits of what lies between them order all but the few neighbours that share them
+// (about 22 bits of mantissa at the widest range).  Those are put in order afterwards by the whole pattern, each run of equal
+// leading bits by one thread; a row with more than kMaxRun tokens in such a run is sorted by the low 32 bits and then
+// again by the high ones.
+// Bound: the memory system.  One workgroup of 256 threads per row and eight passes over 12 bytes took 15.27 ms for 1024
+// rows of 128256 tokens and 4.42 ms for 256 of them; four passes over 8 bytes and 1024 threads
+// 8.55 and 1.44 ms.  (Two workgroups per compute unit, at half the registers, spill: 8.94 and 1.72 ms.)
+template <int NT>
+__global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
+    constexpr int kWaves = NT / 64;                              // this workgroup's waves
+    constexpr int kThreads = NT;
+    constexpr int kMaxRun = 32;
+    __shared__ Sort32Lds<NT> S;
     __shared__ double red[kWaves];
+    __shared__ unsigned long long kred[2][kWaves];
     __shared__ int wtot[4 * kWaves];
-    __shared__ double dscan[kThreads];
-    __shared__ double xin[kThreads];
-    __shared__ double xout[kThreads + 1];
-    __shared__ int bsel;
+    __shared__ double dscan[gr::kThreads];
+    __shared__ int bsel, nruns, again;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, row = blockIdx.x;
     const int V = fp.V;
     const size_t vs = static_cast<size_t>(V) + 2;
     const float* pr = fp.p + static_cast<size_t>(row) * V;
     const float* qr = fp.q + static_cast<size_t>(row) * V;
     unsigned long long* k0 = fp.key0 + row * vs; unsigned long long* k1 = fp.key1 + row * vs;
-    int* v0 = fp.val0 + row * vs; int* v1 = fp.val1 + row * vs;
+    int* runs = fp.val0 + row * vs;
+    const bool lg = fp.logits != 0;
 
     double ptot, qtot;
     double p_ref = 0.0, q_ref = 0.0, inv_temp = 0.0, inv_temp_q = 0.0;
+    // the sort key of a token: ascending patterns are descending ratios.
+    // Rows given as logits: q/p is proportional to exp((d - t) / T), so the order is that of d - t (exact in
+    // float64 for float32 logits; a masked target gives +inf: first)
+    auto full_key = [&](float qv, float pv) -> unsigned long long {
+        const double ratio = lg ? logit_ratio_key(static_cast<double>(qv), static_cast<double>(pv), inv_temp_q, inv_temp)
+                                : static_cast<double>(qv) / static_cast<double>(pv);   // p = 0 gives +inf: first
+        return lg ? ~mono64(ratio) : ~static_cast<unsigned long long>(__double_as_longlong(ratio));
+    };
+    unsigned long long kmin = ~0ull, kmax = 0ull;               // over all tokens that the draft can give
     if (fp.logits) {
         // rows given as logits: the largest target and draft logit, then the target's softmax sum relative to it;
         // q needs no sum (it is renormalised over the support).  A NaN or +inf anywhere, or a temperature that is not
@@ -269,15 +437,19 @@ __global__ __launch_bounds__(kThreads) void full_order_kernel(FullParams fp) {
             bad |= !(pv + qv < 3.0e38f);
             tm = fmaxf(tm, pv); dm = fmaxf(dm, qv);
         }
-        p_ref = block_max(static_cast<double>(tm), red);
-        q_ref = block_max(static_cast<double>(dm), red);
-        const int anybad = block_sum_i(bad, red);
+        p_ref = block_max<kWaves>(static_cast<double>(tm), red);
+        q_ref = block_max<kWaves>(static_cast<double>(dm), red);
+        const int anybad = block_sum_i<kWaves>(bad, red);
         inv_temp = anybad ? 0.0 : 1.0 / static_cast<double>(T);
         inv_temp_q = anybad ? 0.0 : 1.0 / static_cast<double>(Td);
         double ps = 0.0;
         if (!anybad && p_ref > -3.0e38 && q_ref > -3.0e38)
-            for (int i = tid; i < V; i += kThreads) ps += exp((static_cast<double>(pr[i]) - p_ref) * inv_temp);
-        ptot = block_sum(ps, red); qtot = 1.0;
+            for (int i = tid; i < V; i += kThreads) {
+                const float pv = pr[i], qv = qr[i];
+                ps += exp((static_cast<double>(pv) - p_ref) * inv_temp);
+                if (qv > -3.0e38f) { const unsigned long long key = full_key(qv, pv); kmin = min(kmin, key); kmax = max(kmax, key); }
+            }
+        ptot = block_sum<kWaves>(ps, red); qtot = 1.0;
         if (anybad || !(ptot >= 1.0) || !(ptot < 1e300)) {
             if (tid == 0) mark_bad(fp, row, ptot, qtot);
             return;
@@ -288,16 +460,28 @@ __global__ __launch_bounds__(kThreads) void full_order_kernel(FullParams fp) {
             const float pv = pr[i], qv = qr[i];
             bad |= !(qv >= 0.f) | !(pv >= 0.f);
             ps += static_cast<double>(pv); qs += static_cast<double>(qv);
+            if (qv > 0.f) { const unsigned long long key = full_key(qv, pv); kmin = min(kmin, key); kmax = max(kmax, key); }
         }
-        ptot = block_sum(ps, red);
-        qtot = block_sum(qs, red);
-        const int anybad = block_sum_i(bad, red);
+        ptot = block_sum<kWaves>(ps, red);
+        qtot = block_sum<kWaves>(qs, red);
+        const int anybad = block_sum_i<kWaves>(bad, red);
         if (anybad || !(fabs(ptot - 1.0) <= 1e-3) || !(fabs(qtot - 1.0) <= 1e-3)) {
             if (tid == 0) mark_bad(fp, row, ptot, qtot);
             return;
         }
     }
-    const bool lg = fp.logits != 0;
+    int shift;                                                   // the patterns' range >> shift fits 32 bits
+    {
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            kmin = min(kmin, static_cast<unsigned long long>(__shfl_xor(kmin, o)));
+            kmax = max(kmax, static_cast<unsigned long long>(__shfl_xor(kmax, o)));
+        }
+        if (lane == 0) { kred[0][wv] = kmin; kred[1][wv] = kmax; }
+        __syncthreads();
+        for (int w = 0; w < kWaves; ++w) { kmin = min(kmin, kred[0][w]); kmax = max(kmax, kred[1][w]); }
+        shift = kmax > kmin ? max(0, 32 - __clzll(static_cast<long long>(kmax - kmin))) : 0;
+    }
     // With a top-k below the number of positive entries, or a nucleus cut (tail_mass > 0; Sec. 5.1: top-p/k
     // sampling of the draft restricts the domain): order the candidates by decreasing q (ties by token id)
     // and flag the first k' of them; the support is then the flagged tokens.
@@ -313,8 +497,8 @@ __global__ __launch_bounds__(kThreads) void full_order_kernel(FullParams fp) {
         // tail that the exact walk below would leave out anyway.
         double qmin = 0.0; int bstar = 0;
         if (cut) {
-            int* chist = reinterpret_cast<int*>(&S.wcnt[0][0][0]);          // 4096 classes = the sort's 16 KB of counters
-            static_assert(sizeof(S.wcnt) >= 4096 * sizeof(int), "the class histogram borrows the sort's counters");
+            int* chist = reinterpret_cast<int*>(&S);             // 4096 classes = 16 KB of the sort's LDS
+            static_assert(sizeof(S) >= 4096 * sizeof(int), "the class histogram borrows the sort's LDS");
             for (int c = tid; c < 4096; c += kThreads) chist[c] = 0;
             __syncthreads();
             const double budget = fp.tail_mass * qtot;
@@ -339,7 +523,7 @@ __global__ __launch_bounds__(kThreads) void full_order_kernel(FullParams fp) {
             }
             __syncthreads();
             int run = 0, offs[4] = {0, 0, 0, 0};
-#pragma unroll
+#pragma unroll 16
             for (int g = 0; g < 4 * kWaves; ++g) {
 #pragma unroll
                 for (int j = 0; j < 4; ++j) if (g == j * kWaves + wv) offs[j] = run;
@@ -350,8 +534,7 @@ __global__ __launch_bounds__(kThreads) void full_order_kernel(FullParams fp) {
                 const int i = t0 + j * kThreads + tid;
                 if (take[j]) {
                     const int off = cnt + offs[j] + __popcll(mask[j] & ((1ull << lane) - 1ull));
-                    k0[off] = static_cast<unsigned long long>(lg ? ~mono32(qv[j]) : ~__float_as_uint(qv[j]));   // ties: the sort is stable and this is token order
-                    v0[off] = i;
+                    k0[off] = pack32(lg ? ~mono32(qv[j]) : ~__float_as_uint(qv[j]), i);   // ties: the sort is stable and this is token order
                 }
                 if (i < V) member[i] = 0;
             }
@@ -359,21 +542,22 @@ __global__ __launch_bounds__(kThreads) void full_order_kernel(FullParams fp) {
             __syncthreads();
         }
         if (cnt > fp.k || (cut && cnt > 0)) {
-            const int res = block_radix_sort(k0, v0, k1, v1, cnt, S);
-            const int* sorted = res ? v1 : v0;
+            const unsigned long long* sorted = block_sort32<NT>(k0, k1, cnt, S);
             int keep = cnt;
             if (cut) {
                 // the exact walk: running sums of q in the sorted order, added one after the other (wave 0), until
                 // they reach (1 - tail_mass) qtot; the first rank that does is the last token of the support
                 const double need = (1.0 - fp.tail_mass) * qtot;
                 double carry = 0.0;
+                double* xin = reinterpret_cast<double*>(&S.tile[0]); double* xout = xin + NT;   // the sort is done with its tile
+                static_assert(sizeof(S.tile) >= (2 * NT + 1) * sizeof(double), "the walk borrows the sort's tile");
                 if (tid == 0) bsel = cnt;                                // rank of the last kept token; cnt: never reached
                 __syncthreads();
                 for (int t0 = 0; t0 < cnt; t0 += kThreads) {
                     const int r = t0 + tid;
-                    xin[tid] = r < cnt ? static_cast<double>(qr[sorted[r]]) : 0.0;
+                    xin[tid] = r < cnt ? static_cast<double>(qr[packed_id(sorted[r])]) : 0.0;
                     __syncthreads();
-                    if (wv == 0) wave_sequential_scan_padded(xin, xout, kThreads, carry);
+                    if (wv == 0) wave_sequential_scan_padded<16>(xin, xout, kThreads, carry);   // 16: few registers, the others need theirs
                     __syncthreads();
                     if (r < cnt && xout[tid + 1] >= need) atomicMin(&bsel, r);
                     carry = xout[kThreads];
@@ -384,7 +568,7 @@ __global__ __launch_bounds__(kThreads) void full_order_kernel(FullParams fp) {
                 __syncthreads();
             }
             if (fp.k < keep) keep = fp.k;
-            for (int r = tid; r < keep; r += kThreads) member[sorted[r]] = 1;
+            for (int r = tid; r < keep; r += kThreads) member[packed_id(sorted[r])] = 1;
             by_flag = true;
         }
         __syncthreads();
@@ -406,7 +590,7 @@ __global__ __launch_bounds__(kThreads) void full_order_kernel(FullParams fp) {
         }
         __syncthreads();
         int run = 0, offs[4] = {0, 0, 0, 0};
-#pragma unroll
+#pragma unroll 16
         for (int g = 0; g < 4 * kWaves; ++g) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) if (g == j * kWaves + wv) offs[j] = run;
@@ -416,12 +600,7 @@ __global__ __launch_bounds__(kThreads) void full_order_kernel(FullParams fp) {
         for (int j = 0; j < 4; ++j) {
             if (in[j]) {
                 const int off = kk + offs[j] + __popcll(mask[j] & ((1ull << lane) - 1ull));
-                // rows given as logits: q/p is proportional to exp((d - t) / T), so the order is that of d - t (exact in
-                // float64 for float32 logits; a masked target gives +inf: first)
-                const double ratio = lg ? logit_ratio_key(static_cast<double>(qv[j]), static_cast<double>(pv[j]), inv_temp_q, inv_temp)
-                                        : static_cast<double>(qv[j]) / static_cast<double>(pv[j]);   // p = 0 gives +inf: first
-                k0[off] = lg ? ~mono64(ratio) : ~static_cast<unsigned long long>(__double_as_longlong(ratio));
-                v0[off] = t0 + j * kThreads + tid;
+                k0[off] = pack32(static_cast<unsigned>((full_key(qv[j], pv[j]) - kmin) >> shift), t0 + j * kThreads + tid);
             }
         }
         kk += run;
@@ -432,10 +611,53 @@ __global__ __launch_bounds__(kThreads) void full_order_kernel(FullParams fp) {
         return;
     }
     __syncthreads();
-    const int res = block_radix_sort(k0, v0, k1, v1, kk, S);
-    const int* sorted = res ? v1 : v0;
     int* order = fp.order + row * vs;
-    for (int r = tid; r < kk; r += kThreads) order[r] = sorted[r];
+    unsigned long long* elems = k0;
+    // round 0: the leading bits; rounds 1 and 2, for a row that needs them: the low 32 bits, then the high ones, both stable
+    for (int round = 0;; ++round) {
+        elems = block_sort32<NT>(elems, elems == k0 ? k1 : k0, kk, S);
+        auto key_at = [&](int r) { const int id = packed_id(elems[r]); return full_key(qr[id], pr[id]); };
+        if (round == 1) {
+            for (int r = tid; r < kk; r += NT) elems[r] = pack32(static_cast<unsigned>(key_at(r) >> 32), packed_id(elems[r]));
+            __syncthreads();
+            continue;
+        }
+        for (int r = tid; r < kk; r += NT) order[r] = packed_id(elems[r]);
+        if (round == 2 || shift == 0) break;
+        // Neighbours with equal leading bits.  The sort was stable, so equal patterns already are in token order, and a
+        // run without a descent is in order.  The first descent of a run lists it (its first rank and its length).
+        if (tid == 0) { nruns = 0; again = 0; }
+        __syncthreads();
+        for (int r = tid + 1; r < kk; r += NT) {
+            const unsigned lead = static_cast<unsigned>(elems[r] >> 32);
+            if (static_cast<unsigned>(elems[r - 1] >> 32) != lead || key_at(r - 1) <= key_at(r)) continue;
+            int lo = r - 1, hi = r + 1;
+            bool first = true;
+            while (lo > 0 && r - lo <= kMaxRun && static_cast<unsigned>(elems[lo - 1] >> 32) == lead) {
+                first = first && key_at(lo - 1) <= key_at(lo);
+                --lo;
+            }
+            while (hi < kk && hi - lo <= kMaxRun && static_cast<unsigned>(elems[hi] >> 32) == lead) ++hi;
+            if (hi - lo > kMaxRun) { again = 1; break; }
+            if (first) runs[atomicAdd(&nruns, 1)] = lo | ((hi - lo - 1) << 24);          // V < 2^24; fewer runs than tokens
+        }
+        __syncthreads();
+        if (again == 0) {
+            for (int i = tid; i < nruns; i += NT) {
+                const int lo = runs[i] & 0xFFFFFF, hi = lo + (runs[i] >> 24) + 1;
+                for (int r = lo + 1; r < hi; ++r) {              // insertion, stable
+                    const int id = order[r];
+                    const unsigned long long key = full_key(qr[id], pr[id]);
+                    int at = r;
+                    while (at > lo && full_key(qr[order[at - 1]], pr[order[at - 1]]) > key) { order[at] = order[at - 1]; --at; }
+                    order[at] = id;
+                }
+            }
+            break;
+        }
+        for (int r = tid; r < kk; r += NT) elems[r] = pack32(static_cast<unsigned>(key_at(r)), packed_id(elems[r]));
+        __syncthreads();
+    }
     if (tid == 0) {
         RowInfo info;
         info.support = kk; info.h = 0; info.status = GR_ROW_OK; info.iterations = 0;
@@ -792,8 +1014,13 @@ __global__ __launch_bounds__(kThreads) void full_trunc_kernel(FullParams fp) {
 // q mass of each top-k support of the grid; kernel B takes the masked prefix sums along the ratio order and
 // the minimum of F(m) = P_m - Q_m^n for every cell (Thm 3.1, Sec. 5.1).  Only min F is reported, to 1e-5, so these
 // sums are parallel float64 scans like those of the LDS-resident sweep.
-__global__ __launch_bounds__(kThreads) void full_sweep_rank_kernel(FullParams fp, FullSweep fs) {
-    __shared__ SortLds S;
+//
+// The whole vocabulary is ranked by one sort of the tokens in token order (their order is the tie-break: 32-bit keys, four
+// passes); a support below half of it by its own tokens alone, first by id and then by q.
+template <int NT>
+__global__ __launch_bounds__(NT) void full_sweep_rank_kernel(FullParams fp, FullSweep fs) {
+    constexpr int kThreads = NT, kWaves = NT / 64;
+    __shared__ Sort32Lds<NT> S;
     __shared__ double red[kWaves];
     const int tid = threadIdx.x, row = blockIdx.x;
     const int V = fp.V;
@@ -805,7 +1032,6 @@ __global__ __launch_bounds__(kThreads) void full_sweep_rank_kernel(FullParams fp
     const float* qr = fp.q + static_cast<size_t>(row) * V;
     const int* order = fp.order + row * vs;
     unsigned long long* k0 = fp.key0 + row * vs; unsigned long long* k1 = fp.key1 + row * vs;
-    int* v0 = fp.val0 + row * vs; int* v1 = fp.val1 + row * vs;
     double* pn = fp.pn + row * vs; double* qn = fp.qn + row * vs;
     int* qrank = fp.blk + row * vs;                              // by ratio rank: the token's rank by decreasing q
     for (int r0 = tid; r0 < kk; r0 += 4 * kThreads) {
@@ -818,31 +1044,49 @@ __global__ __launch_bounds__(kThreads) void full_sweep_rank_kernel(FullParams fp
         for (int j = 0; j < 4; ++j) {
             const int r = r0 + j * kThreads;
             if (r < kk) {
-                const unsigned long long qb = static_cast<unsigned long long>(~__float_as_uint(qv[j]) & 0x7FFFFFFFu);
-                k0[r] = (qb << 24) | static_cast<unsigned long long>(id[j]);
-                v0[r] = r;
                 pn[r] = static_cast<double>(pv[j]) / info.p_total;
                 qn[r] = static_cast<double>(qv[j]);
             }
         }
     }
-    __syncthreads();
-    const int res = block_radix_sort(k0, v0, k1, v1, kk, S);
-    const int* sorted = res ? v1 : v0;
-    // sorted[j] = ratio rank of the token of q rank j; the q mass of the first k of them for every k of the grid
+    // the ranks by decreasing q, ties by id, and the q mass of the first k of them for every k of the grid
     double part[kSweepMaxK];
 #pragma unroll
     for (int a = 0; a < kSweepMaxK; ++a) part[a] = 0.0;
-    for (int j = tid; j < kk; j += kThreads) {
-        const int r = sorted[j];
-        qrank[r] = j;
-        const double qv = qn[r];
+    const bool whole = kk > V / 2;
+    const int count = whole ? V : kk;
+    for (int i = tid; i < count; i += NT) {
+        if (whole) { const float qv = qr[i]; k0[i] = pack32(qv > 0.f ? ~__float_as_uint(qv) : ~0u, i); }
+        else k0[i] = pack32(static_cast<unsigned>(order[i]), i);
+    }
+    __syncthreads();
+    unsigned long long* sorted = k0;
+    for (int round = whole ? 1 : 0; round < 2; ++round) {
+        sorted = block_sort32<NT>(sorted, sorted == k0 ? k1 : k0, count, S);
+        if (round == 0) {                                        // by token id so far: now by decreasing q
+            for (int j = tid; j < kk; j += NT) {
+                const int r = packed_id(sorted[j]);
+                sorted[j] = pack32(~__float_as_uint(qr[order[r]]), r);
+            }
+            __syncthreads();
+        }
+    }
+    int* by_id = fp.blo + row * vs;                              // whole: q rank of every token id
+    for (int j = tid; j < kk; j += NT) {                         // the support is the first kk of the vocabulary by q
+        const int x = packed_id(sorted[j]);
+        double qv;
+        if (whole) { by_id[x] = j; qv = static_cast<double>(qr[x]); }
+        else { qrank[x] = j; qv = qn[x]; }
 #pragma unroll
         for (int a = 0; a < kSweepMaxK; ++a) if (a < fs.nk && j < fs.ks[a]) part[a] += qv;
     }
+    if (whole) {
+        __syncthreads();
+        for (int r = tid; r < kk; r += NT) qrank[r] = by_id[order[r]];
+    }
 #pragma unroll
     for (int a = 0; a < kSweepMaxK; ++a) {
-        const double t = block_sum(part[a], red);
+        const double t = block_sum<kWaves>(part[a], red);
         if (tid == 0 && a < fs.nk) fs.mass[row * kSweepMaxK + a] = t;
     }
 }
@@ -937,16 +1181,23 @@ __global__ __launch_bounds__(NT) void full_sweep_scan_kernel(FullParams fp, Full
     if (tid == 0 && a == 0) fs.status[row] = GR_ROW_OK;
 }
 
+// Workgroups of 1024 threads take rows of more than two of their tiles of 4096 tokens; shorter rows would leave most of one idle.
+static void launch_full_order(const FullParams& fp, hipStream_t stream) {
+    if (fp.V > 8192) hipLaunchKernelGGL(full_order_kernel<1024>, dim3(fp.B), dim3(1024), 0, stream, fp);
+    else hipLaunchKernelGGL(full_order_kernel<kThreads>, dim3(fp.B), dim3(kThreads), 0, stream, fp);
+}
+
 void launch_full_sweep(const FullParams& fp, const FullSweep& fs, hipStream_t stream) {
-    hipLaunchKernelGGL(full_order_kernel, dim3(fp.B), dim3(kThreads), 0, stream, fp);
-    hipLaunchKernelGGL(full_sweep_rank_kernel, dim3(fp.B), dim3(kThreads), 0, stream, fp, fs);
+    launch_full_order(fp, stream);
+    if (fp.V > 8192) hipLaunchKernelGGL(full_sweep_rank_kernel<1024>, dim3(fp.B), dim3(1024), 0, stream, fp, fs);
+    else hipLaunchKernelGGL(full_sweep_rank_kernel<kThreads>, dim3(fp.B), dim3(kThreads), 0, stream, fp, fs);
     // a round of a 1024-thread workgroup is 4096 ranks: rows that fill fewer than two rounds take the small workgroup
     if (fp.V > 8192) hipLaunchKernelGGL(full_sweep_scan_kernel<1024>, dim3(fp.B, fs.nk), dim3(1024), 0, stream, fp, fs);
     else hipLaunchKernelGGL(full_sweep_scan_kernel<kThreads>, dim3(fp.B, fs.nk), dim3(kThreads), 0, stream, fp, fs);
 }
 
 void launch_full_prologue(const FullParams& fp, hipStream_t stream) {
-    hipLaunchKernelGGL(full_order_kernel, dim3(fp.B), dim3(kThreads), 0, stream, fp);
+    launch_full_order(fp, stream);
     hipLaunchKernelGGL(full_scan_kernel, dim3(fp.B), dim3(kThreads), 0, stream, fp);
     hipLaunchKernelGGL(full_trunc_kernel, dim3(fp.B), dim3(kThreads), 0, stream, fp);
 }

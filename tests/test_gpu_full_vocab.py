@@ -204,3 +204,33 @@ def test_nucleus_cut_on_the_stress_cell_at_full_batch():
         pt = float(np.sum(wl.p[b], dtype=np.float64))
         _, _, F = G.prefix_psi(wl.p[b][order].astype(np.float64) / pt, wl.q[b][order], wl.n)
         assert abs(out["accept_prob"][b] - (1.0 + F.min())) <= wl.n * tm + 2e-6
+
+
+@pytest.mark.parametrize("V", [257, 1024, 1025, 4097, 8192, 8193, 12289, 40001])
+def test_ratio_order_of_rows_with_close_and_equal_ratios(V):
+    """The exported order against a stable argsort of the float64 quotient, on vocabularies around the sort's tiles and
+    workgroup sizes.  Row 0: ratios spread wide.  Row 1: all equal.  Rows 2-4: draft = target up to a relative 2^-10,
+    2^-15 and 2^-22, with one target of zero (ratio +inf: the patterns' range is the widest, so that the leading bits of
+    many neighbours are equal, from a few at a time to the whole row).  Row 5: few distinct ratios, zeros in both."""
+    rng = np.random.default_rng(V)
+    p = rng.dirichlet(np.full(V, 0.5), size=6).astype(np.float32) + np.float32(1e-9)
+    q = p.copy()
+    q[0] = rng.dirichlet(np.full(V, 0.3)).astype(np.float32)
+    for row, bits in ((2, 10), (3, 15), (4, 22)):
+        q[row] = (p[row].astype(np.float64) * (1.0 + rng.uniform(-1, 1, V) * 2.0 ** -bits)).astype(np.float32)
+        p[row, V // 3] = 0.0
+    q[5] = (p[5] * rng.choice([0.0, 0.5, 1.0, 2.0], V)).astype(np.float32)
+    p[5, ::7] = 0.0
+    p = (p.astype(np.float64) / p.sum(1, keepdims=True, dtype=np.float64)).astype(np.float32)
+    q[[0, 5]] = (q[[0, 5]].astype(np.float64) / q[[0, 5]].sum(1, keepdims=True, dtype=np.float64)).astype(np.float32)
+    q[1] = p[1]
+    wl = dataclasses.replace(W.llm_shaped(B=6, V=V, n=2, k=0, seed_sub=V), p=p, q=q,
+                             drafts=np.argsort(-q, axis=1)[:, :2].astype(np.int32))
+    out = run_gpu(wl, 1e-3, want_slice=False, export_rows=range(6))
+    for b in range(6):
+        ids = np.flatnonzero(q[b] > 0)
+        with np.errstate(divide="ignore"):
+            ratio = q[b, ids].astype(np.float64) / p[b, ids].astype(np.float64)
+        want = ids[np.argsort(-ratio, kind="stable")]
+        assert out["support"][b] == len(ids)
+        assert np.array_equal(out["rows"][b]["order"], want), b
