@@ -79,7 +79,7 @@ struct FullParams {
     double* pn; double* qn; double* P; double* Q; double* F; double* rho; double* tgt; double* weight;
     int* flag; int* blk; int* blo; int* inT; int* bcount;
     int* rank_of;      // [B, V + 2] rank of each token id, -1 outside the support
-    double* rho_id;    // [B, V + 2] residual p(i) - p_i by token id (0 inside H*)
+    double* rho_id;    // [B, V + 2] residual p(i) - p_i by token id (0 inside H*); before the programs kernel: the pair (p, q) of every token of the support
     int* nblk;         // [B] number of outer blocks
     int* tcount;       // [B, 2] sizes of the two truncation sets
     RowInfo* info; float* accept_prob; int* status;
