@@ -575,7 +575,7 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
     }
     // the support in token order, with its keys; p and q of a token side by side for the kernels behind this one, which
     // read them in the order of the ratios: one line of memory per token and not two (full_scan_kernel, 1024 rows of
-    // 128256 tokens: 10.68 -> 9.51 ms, at 71 instead of 171 registers; full_sweep_rank_kernel, 256 rows: 3.54 -> 3.12 ms;
+    // 128256 tokens: 10.92 -> 9.57 ms, 256 rows: 3.45 -> 3.06 ms; full_sweep_rank_kernel, 256 rows: 3.54 -> 3.12 ms;
     // writing the pairs: 0.03-0.24 ms)
     float2* pq = reinterpret_cast<float2*>(fp.rho_id + row * vs);   // the programs kernel writes the residuals there later
     int kk = 0;
@@ -740,8 +740,11 @@ __global__ __launch_bounds__(kThreads) void full_scan_kernel(FullParams fp) {
             const int i = t0 + kTile + j * kThreads + tid;
             np_[j] = i < kk ? pn[i] : 0.0; nq_[j] = i < kk ? qn[i] : 0.0;
         }
-        if (wv == 0) wave_sequential_scan_padded<16>(xin[0], xout[0], cnt, carry_p);
-        if (wv == 1) wave_sequential_scan_padded<16>(xin[1], xout[1], cnt, carry_q);
+        // 64 sums in registers: the chain of additions bounds this, and 16 at a time (71 registers for 171) lengthened it more
+        // than the further workgroups per compute unit gave: one row of 8192 tokens 143 -> 159 us, 256 of 128256 3.06 -> 3.33
+        // ms, 1024 9.57 -> 9.68 ms
+        if (wv == 0) wave_sequential_scan_padded(xin[0], xout[0], cnt, carry_p);
+        if (wv == 1) wave_sequential_scan_padded(xin[1], xout[1], cnt, carry_q);
         __syncthreads();
         for (int i = tid; i < cnt; i += kThreads) { P[t0 + i + 1] = xout[0][i + 1]; Q[t0 + i + 1] = xout[1][i + 1]; }
         carry_p = xout[0][cnt]; carry_q = xout[1][cnt];
