@@ -3,7 +3,8 @@
 // without top-k or with a top-k above GR_MAX_SUPPORT, where the support (up to V tokens) does not fit LDS.
 //
 // Every per-token array lives in a per-handle HBM workspace, row-major with stride V + 2; one
-// 256-thread workgroup works through a row.  The arithmetic that decides integers (prefix sums, F,
+// workgroup works through a row (256 threads; 1024 in the kernels that order and rank long rows; one
+// workgroup per row and top-k size in the acceptance grid's scan).  The arithmetic that decides integers (prefix sums, F,
 // the running masses of the truncation sets) is the same sequential fp64 arithmetic as on the
 // LDS-resident path.
 #include "gr_internal.h"
@@ -138,7 +139,7 @@ __device__ int block_radix_sort(unsigned long long* k0, int* v0, unsigned long l
     return cur;
 }
 
-// The sort of the large supports: elements of 8 bytes, a 32-bit key in the high word and the token id in the low one.
+// The sort of the large supports: elements of 8 bytes, the key in the high bits and the token id in the low ones.
 template <int NT>
 struct Sort32Lds {
     static constexpr int kWavesNT = NT / 64;
@@ -151,14 +152,15 @@ struct Sort32Lds {
     int skip[4];
 };
 
-// Stable least-significant-digit radix sort of one row's `count` elements by their high words, 8 bits per pass, between
-// a and b; returns the buffer that holds the result.  A pass moves tiles of 4 NT elements: every wave ranks 256
+// Stable least-significant-digit radix sort of one row's `count` elements by their bits from `lo` on, 8 bits per pass and
+// at most four passes, between a and b; returns the buffer that holds the result.  A pass moves tiles of 4 NT elements: every wave ranks 256
 // consecutive ones among themselves (ballots, and counters that are its own, so no barrier lies between its four
 // rounds), wave 0 turns the counters into places, and the tile goes through LDS into digit order, so that the
 // elements of one digit leave as one run (128 bytes on average for NT = 1024) and not one by one.  Three barriers per tile.
 // Bound: the memory system, 16 bytes per element and pass.  All threads call.
 template <int NT>
-__device__ unsigned long long* block_sort32(unsigned long long* a, unsigned long long* b, int count, Sort32Lds<NT>& S) {
+__device__ unsigned long long* block_sort32(unsigned long long* a, unsigned long long* b, int count, Sort32Lds<NT>& S, int lo = 32,
+                                           int passes = 4) {
     constexpr int kTile = Sort32Lds<NT>::kTile;
     constexpr int NW = NT / 64;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -168,7 +170,7 @@ __device__ unsigned long long* block_sort32(unsigned long long* a, unsigned long
     for (int i0 = 0; i0 < count; i0 += NT) {
         const int i = i0 + tid;
         const bool valid = i < count;
-        const unsigned key = valid ? static_cast<unsigned>(a[i] >> 32) : 0u;
+        const unsigned key = valid ? static_cast<unsigned>(a[i] >> lo) : 0u;
         const unsigned long long vm = __ballot(valid);
         if (vm == 0ull) continue;                               // wave-uniform; lane 0 is valid otherwise
 #pragma unroll
@@ -186,9 +188,9 @@ __device__ unsigned long long* block_sort32(unsigned long long* a, unsigned long
     for (int c = tid; c < 4 * 256; c += NT) if ((&S.hist[0][0])[c] == count) S.skip[c >> 8] = 1;
     __syncthreads();
 
-    for (int pass = 0; pass < 4; ++pass) {
+    for (int pass = 0; pass < passes; ++pass) {
         if (S.skip[pass]) continue;
-        const int shift = 32 + 8 * pass;
+        const int shift = lo + 8 * pass;
         int next[4] = {0, 0, 0, 0};                             // wave 0: next output slot of digits 4 lane .. 4 lane + 3
         if (wv == 0) {
             int tot = 0;
@@ -386,19 +388,30 @@ __device__ void mark_bad(const FullParams& fp, int row, double ptot, double qtot
 // ratios differ by at least 2^-48 relative, so their quotients differ and keep their order, and equal
 // ratios give equal quotients -- the same order as the exact cross-product comparison (Sec. 5.1).
 //
-// The quotient's 64-bit pattern is not sorted as a whole: the row's largest and smallest pattern are known from the
-// first pass, and the 32 leading bits of what lies between them order all but the few neighbours that share them
-// (about 22 bits of mantissa at the widest range).  Those are put in order afterwards by the whole pattern, each run of equal
-// leading bits by one thread; a row with more than kMaxRun tokens in such a run is sorted by the low 32 bits and then
-// again by the high ones.
-// Bound: the memory system.  One workgroup of 256 threads per row and eight passes over 12 bytes took 15.27 ms for 1024
-// rows of 128256 tokens and 4.42 ms for 256 of them; four passes over 8 bytes and 1024 threads
-// 8.55 and 1.44 ms.  (Two workgroups per compute unit, at half the registers, spill: 8.94 and 1.72 ms.)
+// An element of the sort is 64 bits: the token id in as many low bits as V needs, the token's code above it.  The code is
+// the quotient's pattern relative to the row's first one, without the low bits that there is no room for (15 at most for
+// V = 128256 and probabilities, whose patterns span at most 2^61).  A sort by the 32 leading bits of the codes orders all
+// but the few neighbours that share them; one thread per run of such neighbours puts those in order by the rest of their
+// codes, or by the whole pattern where the codes are equal.
+// A row of tight ratios beside one far away has many such neighbours: a draft that is the target up to rounding, beside a
+// token that the target all but excludes.  The pack loop compares a sample of pairs, nine partners of every token; from
+// two near pairs on the codes are sorted whole (6 passes at V = 128256, 7 at 8192), which costs what it costs to put about
+// one near neighbour per token in order.  Ordinary rows show two such pairs less than once in a million.  A run of more
+// than kMaxRun tokens, which one thread would work on for longer than the workgroup sorts, takes the row to the next sort:
+// by the whole codes, then by the low and the high half of the whole patterns.
+// Ratios that are not finite have codes of their own and don't widen the range.
+// 256 rows of 8192 and of 128256 tokens, us, with eight passes over 12 bytes; with one sort of 32 bits and two more
+// for every row with a long run; and now: ratios within 2^-13 and one masked target 258 and 4230; 633 and 5414; 168 and 1439.
+// Ratios within 2^-18 beside ratios 2^20 and 2^-20: 251 and 4134; 648 and 5378; 249 and 2114 (within 2^-15, 8192 tokens: 283
+// against 255 with eight passes).
+// Bound: the memory system and the latency of a workgroup's passes.  One workgroup of 256 threads per row and eight passes
+// over 12 bytes took 15.45 ms for 1024 rows of 128256 tokens and 4.47 ms for 256 of them; four passes over 8 bytes and
+// 1024 threads 5.9 and 1.45 ms.  (Two workgroups per compute unit, at half the registers, spilled and were slower.)
 template <int NT>
 __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
     constexpr int kWaves = NT / 64;                              // this workgroup's waves
     constexpr int kThreads = NT;
-    constexpr int kMaxRun = 32;
+    constexpr int kMaxRun = 16, kClose = 4;                      // kClose: twice the near pairs that the sample may hold
     __shared__ Sort32Lds<NT> S;
     __shared__ double red[kWaves];
     __shared__ unsigned long long kred[2][kWaves];
@@ -413,6 +426,7 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
     unsigned long long* k0 = fp.key0 + row * vs; unsigned long long* k1 = fp.key1 + row * vs;
     int* runs = fp.val0 + row * vs;
     const bool lg = fp.logits != 0;
+    const bool cut = fp.tail_mass > 0.0;
 
     double ptot, qtot;
     double p_ref = 0.0, q_ref = 0.0, inv_temp = 0.0, inv_temp_q = 0.0;
@@ -424,7 +438,10 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
                                 : static_cast<double>(qv) / static_cast<double>(pv);   // p = 0 gives +inf: first
         return lg ? ~mono64(ratio) : ~static_cast<unsigned long long>(__double_as_longlong(ratio));
     };
-    unsigned long long kmin = ~0ull, kmax = 0ull;               // over all tokens that the draft can give
+    unsigned long long kmin = ~0ull, kmax = 0ull;               // of all tokens that the draft can give, where the ratio is finite
+    auto bounds = [&](float qv, float pv) {
+        if (pv > (lg ? -__builtin_inff() : 0.f)) { const unsigned long long key = full_key(qv, pv); kmin = min(kmin, key); kmax = max(kmax, key); }
+    };
     if (fp.logits) {
         // rows given as logits: the largest target and draft logit, then the target's softmax sum relative to it;
         // q needs no sum (it is renormalised over the support).  A NaN or +inf anywhere, or a temperature that is not
@@ -447,7 +464,7 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
             for (int i = tid; i < V; i += kThreads) {
                 const float pv = pr[i], qv = qr[i];
                 ps += exp((static_cast<double>(pv) - p_ref) * inv_temp);
-                if (qv > -3.0e38f) { const unsigned long long key = full_key(qv, pv); kmin = min(kmin, key); kmax = max(kmax, key); }
+                if (qv > -3.0e38f) bounds(qv, pv);
             }
         ptot = block_sum<kWaves>(ps, red); qtot = 1.0;
         if (anybad || !(ptot >= 1.0) || !(ptot < 1e300)) {
@@ -460,7 +477,7 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
             const float pv = pr[i], qv = qr[i];
             bad |= !(qv >= 0.f) | !(pv >= 0.f);
             ps += static_cast<double>(pv); qs += static_cast<double>(qv);
-            if (qv > 0.f) { const unsigned long long key = full_key(qv, pv); kmin = min(kmin, key); kmax = max(kmax, key); }
+            if (qv > 0.f) bounds(qv, pv);
         }
         ptot = block_sum<kWaves>(ps, red);
         qtot = block_sum<kWaves>(qs, red);
@@ -470,24 +487,11 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
             return;
         }
     }
-    int shift;                                                   // the patterns' range >> shift fits 32 bits
-    {
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            kmin = min(kmin, static_cast<unsigned long long>(__shfl_xor(kmin, o)));
-            kmax = max(kmax, static_cast<unsigned long long>(__shfl_xor(kmax, o)));
-        }
-        if (lane == 0) { kred[0][wv] = kmin; kred[1][wv] = kmax; }
-        __syncthreads();
-        for (int w = 0; w < kWaves; ++w) { kmin = min(kmin, kred[0][w]); kmax = max(kmax, kred[1][w]); }
-        shift = kmax > kmin ? max(0, 32 - __clzll(static_cast<long long>(kmax - kmin))) : 0;
-    }
     // With a top-k below the number of positive entries, or a nucleus cut (tail_mass > 0; Sec. 5.1: top-p/k
     // sampling of the draft restricts the domain): order the candidates by decreasing q (ties by token id)
     // and flag the first k' of them; the support is then the flagged tokens.
     int* member = fp.flag + row * vs;                       // by token id here; reused by rank later
     bool by_flag = false;
-    const bool cut = fp.tail_mass > 0.0;
     if (fp.k < V || cut) {
         // Nucleus cut: tokens are taken by decreasing q until their running sum reaches (1 - tail_mass) qtot.
         // Candidates first, so that only they are sorted: half of the budget tail_mass qtot goes to the tokens
@@ -511,7 +515,7 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
             bstar = class_threshold(chist, 0.5 * budget, dscan, &bsel);
         }
         int cnt = 0;
-        for (int t0 = 0; t0 < V; t0 += 4 * kThreads) {           // 1024 tokens per round
+        for (int t0 = 0; t0 < V; t0 += 4 * kThreads) {           // 4 NT tokens per round
             float qv[4]; unsigned long long mask[4]; bool take[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) { const int i = t0 + j * kThreads + tid; qv[j] = i < V ? qr[i] : (lg ? -__builtin_inff() : 0.f); }
@@ -541,9 +545,10 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
             cnt += run;
             __syncthreads();
         }
+        const unsigned long long* sorted = k0;
+        int keep = cnt;
         if (cnt > fp.k || (cut && cnt > 0)) {
-            const unsigned long long* sorted = block_sort32<NT>(k0, k1, cnt, S);
-            int keep = cnt;
+            sorted = block_sort32<NT>(k0, k1, cnt, S);
             if (cut) {
                 // the exact walk: running sums of q in the sorted order, added one after the other (wave 0), until
                 // they reach (1 - tail_mass) qtot; the first rank that does is the last token of the support
@@ -573,14 +578,40 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
         }
         __syncthreads();
     }
-    // the support in token order, with its keys; p and q of a token side by side for the kernels behind this one, which
+    // A token's code: its finite ratio's pattern, relative to the row's first and without the `shift` bits that the element
+    // has no room for, behind the codes of the ratios that are not finite (a target of -0 gives -inf, which comes first,
+    // one of +0 or a masked target logit +inf).  `lo`: where the 32 leading bits of the row's codes begin; each kind of
+    // ratio that is not finite has leading bits of its own.
+    const int id_bits = V > 2 ? 32 - __clz(V - 1) : 1;
+    const unsigned id_mask = (1u << id_bits) - 1u;
+    int shift, under, lo;
+    unsigned long long base;
+    {
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            kmin = min(kmin, static_cast<unsigned long long>(__shfl_xor(kmin, o)));
+            kmax = max(kmax, static_cast<unsigned long long>(__shfl_xor(kmax, o)));
+        }
+        if (lane == 0) { kred[0][wv] = kmin; kred[1][wv] = kmax; }
+        __syncthreads();
+        for (int w = 0; w < kWaves; ++w) { kmin = min(kmin, kred[0][w]); kmax = max(kmax, kred[1][w]); }
+        auto bits = [](unsigned long long x) { return x ? 64 - __clzll(static_cast<long long>(x)) : 0; };
+        const unsigned long long range = kmax > kmin ? kmax - kmin : 0ull;
+        shift = max(0, bits(range) - (64 - id_bits) + 1);        // one bit less than there is room for: `base` may carry into it
+        under = max(0, bits(range >> shift) - 31);
+        base = 2ull << under;
+        lo = id_bits + max(0, bits((range >> shift) + base) - 32);
+    }
+    auto code = [&](unsigned long long key) -> unsigned long long { return key >= kmin ? ((key - kmin) >> shift) + base : (key >> 63) << under; };
+    // the support in token order, with its codes; p and q of a token side by side for the kernels behind this one, which
     // read them in the order of the ratios: one line of memory per token and not two (full_scan_kernel, 1024 rows of
     // 128256 tokens: 10.92 -> 9.57 ms, 256 rows: 3.45 -> 3.06 ms; full_sweep_rank_kernel, 256 rows: 3.54 -> 3.12 ms;
     // writing the pairs: 0.03-0.24 ms)
     float2* pq = reinterpret_cast<float2*>(fp.rho_id + row * vs);   // the programs kernel writes the residuals there later
-    int kk = 0;
-    for (int t0 = 0; t0 < V; t0 += 4 * kThreads) {               // 1024 tokens per round
-        float qv[4], pv[4]; bool in[4]; unsigned long long mask[4];
+    int kk = 0, close = 0;                                       // close: twice the sampled pairs of tokens that are near
+    auto near = [&](unsigned long long x, unsigned long long y) { return (x >> lo) == (y >> lo) && (x >> id_bits) != (y >> id_bits); };
+    for (int t0 = 0; t0 < V; t0 += 4 * kThreads) {               // 4 NT tokens per round
+        float qv[4], pv[4]; bool in[4]; unsigned long long mask[4], e[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int i = t0 + j * kThreads + tid;
@@ -591,6 +622,15 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
         for (int j = 0; j < 4; ++j) {
             mask[j] = __ballot(in[j]);
             if (lane == 0) wtot[j * kWaves + wv] = __popcll(mask[j]);
+            e[j] = 0ull;
+            if (in[j]) e[j] = (code(full_key(qv[j], pv[j])) << id_bits) | static_cast<unsigned>(t0 + j * kThreads + tid);
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const unsigned long long x = __shfl_xor(e[j], o);
+                close += in[j] && (mask[j] >> (lane ^ o) & 1ull) && near(x, e[j]);
+            }
+#pragma unroll
+            for (int i = 0; i < j; ++i) close += in[j] && in[i] && near(e[i], e[j]) ? 2 : 0;
         }
         __syncthreads();
         int run = 0, offs[4] = {0, 0, 0, 0};
@@ -604,7 +644,7 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
         for (int j = 0; j < 4; ++j) {
             if (in[j]) {
                 const int off = kk + offs[j] + __popcll(mask[j] & ((1ull << lane) - 1ull));
-                k0[off] = pack32(static_cast<unsigned>((full_key(qv[j], pv[j]) - kmin) >> shift), t0 + j * kThreads + tid);
+                k0[off] = e[j];
                 pq[t0 + j * kThreads + tid] = make_float2(pv[j], qv[j]);
             }
         }
@@ -618,50 +658,72 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
     __syncthreads();
     int* order = fp.order + row * vs;
     unsigned long long* elems = k0;
-    // round 0: the leading bits; rounds 1 and 2, for a row that needs them: the low 32 bits, then the high ones, both stable
-    for (int round = 0;; ++round) {
-        elems = block_sort32<NT>(elems, elems == k0 ? k1 : k0, kk, S);
-        auto key_at = [&](int r) { const int id = packed_id(elems[r]); return full_key(qr[id], pr[id]); };
-        if (round == 1) {
-            for (int r = tid; r < kk; r += NT) elems[r] = pack32(static_cast<unsigned>(key_at(r) >> 32), packed_id(elems[r]));
-            __syncthreads();
-            continue;
-        }
-        for (int r = tid; r < kk; r += NT) order[r] = packed_id(elems[r]);
-        if (round == 2 || shift == 0) break;
-        // Neighbours with equal leading bits.  The sort was stable, so equal patterns already are in token order, and a
-        // run without a descent is in order.  The first descent of a run lists it (its first rank and its length).
-        if (tid == 0) { nruns = 0; again = 0; }
-        __syncthreads();
-        for (int r = tid + 1; r < kk; r += NT) {
-            const unsigned lead = static_cast<unsigned>(elems[r] >> 32);
-            if (static_cast<unsigned>(elems[r - 1] >> 32) != lead || key_at(r - 1) <= key_at(r)) continue;
-            int lo = r - 1, hi = r + 1;
-            bool first = true;
-            while (lo > 0 && r - lo <= kMaxRun && static_cast<unsigned>(elems[lo - 1] >> 32) == lead) {
-                first = first && key_at(lo - 1) <= key_at(lo);
-                --lo;
-            }
-            while (hi < kk && hi - lo <= kMaxRun && static_cast<unsigned>(elems[hi] >> 32) == lead) ++hi;
-            if (hi - lo > kMaxRun) { again = 1; break; }
-            if (first) runs[atomicAdd(&nruns, 1)] = lo | ((hi - lo - 1) << 24);          // V < 2^24; fewer runs than tokens
-        }
-        __syncthreads();
-        if (again == 0) {
-            for (int i = tid; i < nruns; i += NT) {
-                const int lo = runs[i] & 0xFFFFFF, hi = lo + (runs[i] >> 24) + 1;
-                for (int r = lo + 1; r < hi; ++r) {              // insertion, stable
-                    const int id = order[r];
-                    const unsigned long long key = full_key(qr[id], pr[id]);
-                    int at = r;
-                    while (at > lo && full_key(qr[order[at - 1]], pr[order[at - 1]]) > key) { order[at] = order[at - 1]; --at; }
-                    order[at] = id;
+    auto id_of = [&](unsigned long long e) { return static_cast<int>(static_cast<unsigned>(e) & id_mask); };
+    auto key_of = [&](unsigned long long e) { const float2 x = pq[id_of(e)]; return full_key(x.y, x.x); };
+    auto behind = [&](unsigned long long x, unsigned long long y) {   // the token of x comes after that of y (ids decide between equals)
+        if ((x >> id_bits) != (y >> id_bits) || shift == 0) return x > y;
+        const unsigned long long kx = key_of(x), ky = key_of(y);
+        return kx != ky ? kx > ky : x > y;
+    };
+    if (tid == 0) { again = 0; nruns = 0; }
+    // The sorts of a row, all stable: 0 by the codes' leading bits; 1 and 2 by the bits below them, then by the leading
+    // ones again; 3 and 4 by the low, then the high half of the whole patterns.
+    int step = block_sum_i<kWaves>(close, red) >= kClose && lo > id_bits ? 1 : 0;
+    for (;;) {
+        const int from = step == 1 ? id_bits : (step >= 3 ? 32 : lo);
+        elems = block_sort32<NT>(elems, elems == k0 ? k1 : k0, kk, S, from, step == 1 ? (lo - id_bits + 7) >> 3 : 4);
+        if (step == 1) { step = 2; continue; }
+        if (step == 0 || step == 2) {
+            const int same = step == 0 ? lo : id_bits;           // tokens equal from this bit on may still be out of order
+            for (int r = tid; r < kk; r += NT) order[r] = id_of(elems[r]);
+            if (shift == 0 && same == id_bits) break;
+            // The sorts were stable, so tokens of equal ratios already are in token order, and a run without a descent
+            // is in order.  The first descent of a run lists it (its first rank and its length).
+            for (int r = tid + 1; r < kk; r += NT) {
+                const unsigned long long e = elems[r], before = elems[r - 1];
+                if ((before >> same) != (e >> same) || !behind(before, e)) continue;
+                int first = r - 1, end = r + 1;
+                bool lists = true;
+                while (first > 0 && r - first <= kMaxRun && (elems[first - 1] >> same) == (e >> same)) {
+                    lists = lists && !behind(elems[first - 1], elems[first]);
+                    --first;
                 }
+                while (end < kk && end - first <= kMaxRun && (elems[end] >> same) == (e >> same)) ++end;
+                if (end - first > kMaxRun) { again = 1; break; }
+                if (lists) runs[atomicAdd(&nruns, 1)] = first | ((end - first - 1) << 24);     // V < 2^24; fewer runs than tokens
             }
+            __syncthreads();
+            if (again == 0) {
+                // one thread per run: a token's place is the number of tokens that it comes after
+                for (int i = tid; i < nruns; i += NT) {
+                    const int first = runs[i] & 0xFFFFFF, end = first + (runs[i] >> 24) + 1;
+                    for (int r = first; r < end; ++r) {
+                        const unsigned long long e = elems[r];
+                        int at = first;
+                        for (int o = first; o < end; ++o) at += behind(e, elems[o]);
+                        order[at] = id_of(e);
+                    }
+                }
+                break;
+            }
+            __syncthreads();
+            if (tid == 0) { again = 0; nruns = 0; }
+            step = same > id_bits ? 1 : 3;
+        } else {
+            ++step;
+        }
+        if (step == 5) {
+            for (int r = tid; r < kk; r += NT) order[r] = packed_id(elems[r]);
             break;
         }
-        for (int r = tid; r < kk; r += NT) elems[r] = pack32(static_cast<unsigned>(key_at(r)), packed_id(elems[r]));
-        __syncthreads();
+        if (step >= 3) {
+            for (int r = tid; r < kk; r += NT) {
+                const int id = step == 3 ? id_of(elems[r]) : packed_id(elems[r]);
+                const unsigned long long key = full_key(pq[id].y, pq[id].x);
+                elems[r] = pack32(static_cast<unsigned>(step == 3 ? key : key >> 32), id);
+            }
+            __syncthreads();
+        }
     }
     if (tid == 0) {
         RowInfo info;
@@ -1105,8 +1167,8 @@ __global__ __launch_bounds__(NT) void full_sweep_rank_kernel(FullParams fp, Full
     }
 }
 
-// One workgroup per (row, top-k size): the draft counts of the grid are then few enough for their running minima to
-// stay in registers, and every size of the grid has its own compute unit.  The draft counts come in rising order
+// One workgroup per (row, top-k size): the running minima of its draft counts stay in registers, and the sizes of a grid
+// are spread over the chip.  The draft counts come in rising order
 // (fs.ns; fs.npos is each one's place in the grid), so their powers are one chain of products, the same products that
 // ipow takes for each of them apart.  A wave none of whose 256 tokens belongs to the support repeats the prefix
 // before it: it computes nothing.  Bound: arithmetic, 2 float64 operations per token, size and draft count plus the
