@@ -339,6 +339,22 @@ __device__ int block_prefix_sum_excl(int v, int* buf0, int* buf1, int* total) {
     return excl;
 }
 
+// wtot: LDS, the counts of the workgroup's 4 NW groups of 64 tokens in token order (NW <= 16: one per lane).  offs[j] = the
+// count before this wave's group of round j; returns the count of all groups.  (A loop over the groups in every thread
+// cost a row of 8193 tokens cut to 9 36 of its 100 us in a workgroup of 16 waves.)
+template <int NW>
+__device__ __forceinline__ int group_offsets(const int* wtot, int (&offs)[4]) {
+    static_assert(4 * NW <= 64, "one group per lane");
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int v = lane < 4 * NW ? wtot[lane] : 0;
+    int incl = v;
+#pragma unroll
+    for (int o = 1; o < 4 * NW; o <<= 1) { const int up = __shfl_up(incl, o); if (lane >= o) incl += up; }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) offs[j] = __shfl(incl - v, j * NW + wv);
+    return __shfl(incl, 4 * NW - 1);
+}
+
 // chist[4096]: members per magnitude class of a positive float (its bit pattern >> 19: exponent and four mantissa
 // bits; every member lies below the class's upper edge, so count x edge bounds the class's mass).  Classes are
 // dropped from the bottom while that bound stays within `budget`; returns the lowest class that stays (0 when every
@@ -355,7 +371,11 @@ __device__ int class_threshold(const int* chist, double budget, double* dscan, i
     }
     if (tid == 0) *bsel = 4096;
     __syncthreads();
-    if (tid == 0) { double run = 0.0; for (int t = 0; t < kThreads; ++t) { const double v = dscan[t]; dscan[t] = run; run += v; } }
+    if (tid == 0) {
+        double run = 0.0;
+#pragma unroll 32
+        for (int t = 0; t < kThreads; ++t) { const double v = dscan[t]; dscan[t] = run; run += v; }
+    }
     __syncthreads();
     if (tid < kThreads) {
         double run = dscan[tid];                                 // bound on the mass of all classes below 16 tid
@@ -427,6 +447,10 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
     int* runs = fp.val0 + row * vs;
     const bool lg = fp.logits != 0;
     const bool cut = fp.tail_mass > 0.0;
+    // Where the support may be small, its first and last pattern are found when it is known: a division per token of the
+    // vocabulary is much of what such a row costs (one row of 128256 tokens cut to 9: 531 -> 459 us, with the pack loop
+    // leaving out the waves that hold none).  A top-k above V / 8 takes those of all tokens from the pass over the sums.
+    const bool early = !cut && fp.k > V / 8;
 
     double ptot, qtot;
     double p_ref = 0.0, q_ref = 0.0, inv_temp = 0.0, inv_temp_q = 0.0;
@@ -438,7 +462,7 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
                                 : static_cast<double>(qv) / static_cast<double>(pv);   // p = 0 gives +inf: first
         return lg ? ~mono64(ratio) : ~static_cast<unsigned long long>(__double_as_longlong(ratio));
     };
-    unsigned long long kmin = ~0ull, kmax = 0ull;               // of all tokens that the draft can give, where the ratio is finite
+    unsigned long long kmin = ~0ull, kmax = 0ull;               // of the support (early: of all tokens), where the ratio is finite
     auto bounds = [&](float qv, float pv) {
         if (pv > (lg ? -__builtin_inff() : 0.f)) { const unsigned long long key = full_key(qv, pv); kmin = min(kmin, key); kmax = max(kmax, key); }
     };
@@ -464,7 +488,7 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
             for (int i = tid; i < V; i += kThreads) {
                 const float pv = pr[i], qv = qr[i];
                 ps += exp((static_cast<double>(pv) - p_ref) * inv_temp);
-                if (qv > -3.0e38f) bounds(qv, pv);
+                if (early && qv > -3.0e38f) bounds(qv, pv);
             }
         ptot = block_sum<kWaves>(ps, red); qtot = 1.0;
         if (anybad || !(ptot >= 1.0) || !(ptot < 1e300)) {
@@ -477,7 +501,7 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
             const float pv = pr[i], qv = qr[i];
             bad |= !(qv >= 0.f) | !(pv >= 0.f);
             ps += static_cast<double>(pv); qs += static_cast<double>(qv);
-            if (qv > 0.f) bounds(qv, pv);
+            if (early && qv > 0.f) bounds(qv, pv);
         }
         ptot = block_sum<kWaves>(ps, red);
         qtot = block_sum<kWaves>(qs, red);
@@ -526,13 +550,8 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
                 if (lane == 0) wtot[j * kWaves + wv] = __popcll(mask[j]);
             }
             __syncthreads();
-            int run = 0, offs[4] = {0, 0, 0, 0};
-#pragma unroll 16
-            for (int g = 0; g < 4 * kWaves; ++g) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) if (g == j * kWaves + wv) offs[j] = run;
-                run += wtot[g];
-            }
+            int offs[4];
+            const int run = group_offsets<kWaves>(wtot, offs);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int i = t0 + j * kThreads + tid;
@@ -562,10 +581,11 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
                     const int r = t0 + tid;
                     xin[tid] = r < cnt ? static_cast<double>(qr[packed_id(sorted[r])]) : 0.0;
                     __syncthreads();
-                    if (wv == 0) wave_sequential_scan_padded<16>(xin, xout, kThreads, carry);   // 16: few registers, the others need theirs
+                    const int todo = min(kThreads, (cnt - t0 + 15) & ~15);
+                    if (wv == 0) wave_sequential_scan_padded<16>(xin, xout, todo, carry);       // 16: few registers, the others need theirs
                     __syncthreads();
                     if (r < cnt && xout[tid + 1] >= need) atomicMin(&bsel, r);
-                    carry = xout[kThreads];
+                    carry = xout[todo];
                     __syncthreads();
                     if (bsel < cnt) break;                               // uniform: read behind the barrier
                 }
@@ -577,6 +597,15 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
             by_flag = true;
         }
         __syncthreads();
+        if (!early) {
+            // a small support by its list (a gather costs whole lines), a large one in token order
+            const bool few = keep <= V / 8;
+            for (int r = tid; r < (few ? keep : V); r += kThreads) {
+                const int i = few ? packed_id(sorted[r]) : r;
+                if (few || (by_flag ? member[i] != 0 : (lg ? qr[i] > -3.0e38f : qr[i] > 0.f))) bounds(qr[i], pr[i]);
+            }
+            __syncthreads();
+        }
     }
     // A token's code: its finite ratio's pattern, relative to the row's first and without the `shift` bits that the element
     // has no room for, behind the codes of the ratios that are not finite (a target of -0 gives -inf, which comes first,
@@ -623,6 +652,7 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
             mask[j] = __ballot(in[j]);
             if (lane == 0) wtot[j * kWaves + wv] = __popcll(mask[j]);
             e[j] = 0ull;
+            if (mask[j] == 0ull) continue;                       // uniform over the wave
             if (in[j]) e[j] = (code(full_key(qv[j], pv[j])) << id_bits) | static_cast<unsigned>(t0 + j * kThreads + tid);
 #pragma unroll
             for (int o = 1; o < 64; o <<= 1) {
@@ -633,13 +663,8 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
             for (int i = 0; i < j; ++i) close += in[j] && in[i] && near(e[i], e[j]) ? 2 : 0;
         }
         __syncthreads();
-        int run = 0, offs[4] = {0, 0, 0, 0};
-#pragma unroll 16
-        for (int g = 0; g < 4 * kWaves; ++g) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) if (g == j * kWaves + wv) offs[j] = run;
-            run += wtot[g];
-        }
+        int offs[4];
+        const int run = group_offsets<kWaves>(wtot, offs);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             if (in[j]) {
@@ -1257,9 +1282,13 @@ __global__ __launch_bounds__(NT) void full_sweep_scan_kernel(FullParams fp, Full
     if (tid == 0 && a == 0) fs.status[row] = GR_ROW_OK;
 }
 
-// Workgroups of 1024 threads take rows of more than two of their tiles of 4096 tokens; shorter rows would leave most of one idle.
+// Workgroups of 1024 threads take rows of more than two of their tiles of 4096 tokens; shorter rows would leave most of one
+// idle.  One of them fills a compute unit, so where rows wait for one (more of them than compute units) and a nucleus cut
+// leaves little to sort, the row must be longer (cut of 1e-3; 1024 against 256 threads, the call): 1024 rows of
+// 8193 tokens 795 and 707 us, of 12289 840 and 779, of 16384 959 and 950, of 24000 968 and 1010, of 50021 1504 and 1725.
 static void launch_full_order(const FullParams& fp, hipStream_t stream) {
-    if (fp.V > 8192) hipLaunchKernelGGL(full_order_kernel<1024>, dim3(fp.B), dim3(1024), 0, stream, fp);
+    const bool crowded = fp.tail_mass > 0.0 && fp.B > 256 && fp.V <= 16384;
+    if (fp.V > 8192 && !crowded) hipLaunchKernelGGL(full_order_kernel<1024>, dim3(fp.B), dim3(1024), 0, stream, fp);
     else hipLaunchKernelGGL(full_order_kernel<kThreads>, dim3(fp.B), dim3(kThreads), 0, stream, fp);
 }
 

@@ -357,3 +357,44 @@ def test_a_masked_target_does_not_slow_a_row_of_tight_ratios():
     q = (p.astype(np.float64) * (1.0 + rng.uniform(-1, 1, p.shape) * 2.0 ** -13)).astype(np.float32)
     masked = p.copy(); masked[:, 2730] = 0.0
     assert _solve_us(masked, q) < 1.25 * _solve_us(p, q)
+
+
+@pytest.mark.parametrize("B,V", [(6, 1025), (6, 8193), (6, 20000), (300, 8193), (257, 16385)])
+@pytest.mark.parametrize("k,tail_mass", [(300, 0.0), (0.5, 0.0), (0, 1.03e-3), (0, 1e-8), (300, 1e-6)])
+def test_ratio_order_of_restricted_supports(B, V, k, tail_mass):
+    """A top-k on both sides of V / 8 (0.5: half the vocabulary), nucleus cuts that leave little and much, and both: the support by a
+    stable argsort of q and its float64 running sums, the order by a stable argsort of its quotients.  Masked targets
+    inside the support, a row with fewer positive q than the top-k, a row of equal q.  Batches on both sides of the
+    number of compute units."""
+    k = V // 2 if k == 0.5 else k
+    wl = W.llm_shaped(B=6, V=V, n=2, k=0, temperature=(0.5, 1.5), seed_sub=V)
+    p, q = wl.p.astype(np.float64), wl.q.astype(np.float64)
+    p[:, 3::7] = 0.0
+    q[2, np.random.default_rng(V).permutation(V)[200:]] = 0.0
+    q[3] = 1.0
+    p = (p / p.sum(1, keepdims=True)).astype(np.float32)
+    q = (q / q.sum(1, keepdims=True)).astype(np.float32)
+    rows = [B - 6 + b for b in range(6)]                              # the last ones
+    at = (np.arange(B) - (B - 6)) % 6
+    got = _orders(p[at], q[at], k=k, tail_mass=tail_mass, rows=rows)
+    for b in range(6):
+        ids = np.argsort(-q[b], kind="stable")[: int((q[b] > 0).sum())]
+        if tail_mass:
+            mass = np.cumsum(q[b, ids].astype(np.float64))
+            need = (1.0 - tail_mass) * q[b].sum(dtype=np.float64)
+            assert np.abs(mass - need).min() > 1e-13                  # far from the row sum's rounding, so the end is certain
+            ids = ids[: int(np.searchsorted(mass, need)) + 1]
+        ids = np.sort(ids[:k] if k else ids)
+        with np.errstate(divide="ignore"):
+            want = ids[np.argsort(-(q[b, ids].astype(np.float64) / p[b, ids].astype(np.float64)), kind="stable")]
+        assert np.array_equal(got[b], want), b
+
+
+def test_nucleus_rows_across_the_workgroup_sizes():
+    """One token more takes a short nucleus row past the vocabulary at which workgroups grow: 1024 such rows took 1.25 to 1.3 times as
+    long for it.  The bound leaves the clock a seventh."""
+    wl = W.llm_shaped(B=64, V=8193, n=2, k=0, seed_sub=5)
+    at = np.arange(1024) % 64
+    p, q = wl.p[at], wl.q[at]
+    fewer = [(x[:, :8192].astype(np.float64) / x[:, :8192].sum(1, keepdims=True, dtype=np.float64)).astype(np.float32) for x in (p, q)]
+    assert _solve_us(p, q, 1e-3) < 1.15 * _solve_us(*fewer, 1e-3)
