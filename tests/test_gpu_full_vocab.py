@@ -349,7 +349,7 @@ def _solve_us(p, q, tail_mass=0.0):
 
 
 def test_a_masked_target_does_not_slow_a_row_of_tight_ratios():
-    """One target of zero beside ratios within 2^-13.  Three sorts instead of one made the call 1.9 times as long; the two
+    """One target of zero beside ratios within 2^-13.  Three sorts instead of one made the call 1.58 times as long; the two
     calls differ by at most 3 % now, the bound leaves the clock a quarter."""
     rng = np.random.default_rng(13)
     p = (rng.dirichlet(np.full(8192, 0.5), size=64) + 1e-9).astype(np.float32)
@@ -391,7 +391,7 @@ def test_ratio_order_of_restricted_supports(B, V, k, tail_mass):
 
 
 def test_nucleus_rows_across_the_workgroup_sizes():
-    """One token more takes a short nucleus row past the vocabulary at which workgroups grow: 1024 such rows took 1.25 to 1.3 times as
+    """One token more takes a short nucleus row past the vocabulary at which workgroups grow: 1024 such rows took 1.37 times as
     long for it.  The bound leaves the clock a seventh."""
     wl = W.llm_shaped(B=64, V=8193, n=2, k=0, seed_sub=5)
     at = np.arange(1024) % 64

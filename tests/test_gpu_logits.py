@@ -194,3 +194,17 @@ def test_a_cooled_target_with_the_draft_left_at_its_own_temperature(V, n, k, tol
     out = _run_logits(wl, tol, drafts, export_rows=range(wl.B))
     st = _compare(wl, out, range(wl.B), tol, drafts)
     assert st["rows"] == wl.B and st["fragile"] < wl.B and np.any(out["status"] == 0)
+
+
+@pytest.mark.parametrize("V,n,k,tol", [(8192, 2, 0, 1e-3), (8193, 2, 0, 1e-3), (8193, 3, 300, 1e-4), (12289, 2, 300, 1e-3)])
+def test_logits_on_both_workgroup_sizes_of_the_order_kernel(V, n, k, tol):
+    """Vocabularies on both sides of the order kernel's large workgroups, without top-k and with one, every other row's
+    draft at a temperature of its own."""
+    import dataclasses
+    wl = W.llm_shaped(B=4, V=V, n=n, k=k, temperature=1.0, near_identical_frac=0.25, seed_sub=V + k, keep_logits=True)
+    meta = dict(wl.meta); meta["temps"] = np.array([0.6, 0.8, 1.0, 1.3]); meta["draft_temps"] = np.array([0.6, 1.0, 1.0, 1.0])
+    wl = dataclasses.replace(wl, meta=meta)
+    drafts = _drafts_from_logits(wl, set(range(wl.B)), 19)
+    out = _run_logits(wl, tol, drafts, export_rows=range(wl.B))
+    st = _compare(wl, out, range(wl.B), tol, drafts)
+    assert st["rows"] == wl.B and st["fragile"] < wl.B

@@ -183,3 +183,22 @@ def test_draft_counts_in_any_order_on_both_workgroup_sizes(V, ns):
     acc, st = _sweep(wl.p, wl.q, ks, ns, max_k=0)
     assert np.all(st == 0)
     _check(wl.p, wl.q, ks, ns, range(wl.B), acc)
+
+
+@pytest.mark.parametrize("V", [1001, 5000, 8192, 8193, 12289])
+def test_grids_that_end_below_half_the_vocabulary(V):
+    """The ranks by q of a support of at most half the vocabulary come from its own tokens: a largest top-k size on both
+    sides of V / 2, many equal q across the sizes' ends (ties by token id), and rows of which most q are zero."""
+    wl = W.llm_shaped(B=4, V=V, n=2, k=0, temperature=(0.5, 1.5), seed_sub=V)
+    p, q = wl.p.copy(), wl.q.copy()
+    q[1] = np.round(q[1] * (4.0 * V)) + 1.0                          # few distinct values
+    q[2, np.random.default_rng(V).random(V) < 0.6] = 0.0
+    q[3] = 1.0
+    q = (q / q.sum(1, keepdims=True, dtype=np.float64)).astype(np.float32)
+    for ks in ([10, 300], [300, V // 2 - 1, 64], [V // 2, 17], [V // 2 + 1, 257]):
+        acc, st = _sweep(p, q, ks, [1, 2, 8], max_k=0)
+        assert np.all(st == 0)
+        _check(p, q, ks, [1, 2, 8], range(4), acc)
+    acc, st = _sweep(p[2:3], q[2:3], [0, 300], [1, 2, 8], max_k=0)     # no top-k: the zeros leave a support below V / 2
+    assert np.all(st == 0)
+    _check(p[2:3], q[2:3], [0, 300], [1, 2, 8], [0], acc)
