@@ -157,7 +157,8 @@ struct Sort32Lds {
 // consecutive ones among themselves (ballots, and counters that are its own, so no barrier lies between its four
 // rounds), wave 0 turns the counters into places, and the tile goes through LDS into digit order, so that the
 // elements of one digit leave as one run (128 bytes on average for NT = 1024) and not one by one.  Three barriers per tile.
-// Bound: the memory system, 16 bytes per element and pass.  All threads call.
+// Bound: 16 bytes of traffic per element and pass, and the latency of a tile's three barriers (order kernel, 1024 rows of 128256
+// tokens: 18 GB in 6.0 ms, 3.0 TB/s where a device copy reaches 5.1).  All threads call.
 template <int NT>
 __device__ unsigned long long* block_sort32(unsigned long long* a, unsigned long long* b, int count, Sort32Lds<NT>& S, int lo = 32,
                                            int passes = 4) {
@@ -424,9 +425,9 @@ __device__ void mark_bad(const FullParams& fp, int row, double ptot, double qtot
 // for every row with a long run; and now: ratios within 2^-13 and one masked target 258 and 4230; 633 and 5414; 168 and 1439.
 // Ratios within 2^-18 beside ratios 2^20 and 2^-20: 251 and 4134; 648 and 5378; 249 and 2114 (within 2^-15, 8192 tokens: 283
 // against 255 with eight passes).
-// Bound: the memory system and the latency of a workgroup's passes.  One workgroup of 256 threads per row and eight passes
+// Bound: as the sort.  One workgroup of 256 threads per row and eight passes
 // over 12 bytes took 15.45 ms for 1024 rows of 128256 tokens and 4.47 ms for 256 of them; four passes over 8 bytes and
-// 1024 threads 5.9 and 1.45 ms.  (Two workgroups per compute unit, at half the registers, spilled and were slower.)
+// 1024 threads 6.03 and 1.42 ms.  (Two workgroups per compute unit, at half the registers, spilled and were slower.)
 template <int NT>
 __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
     constexpr int kWaves = NT / 64;                              // this workgroup's waves
@@ -1198,7 +1199,7 @@ __global__ __launch_bounds__(NT) void full_sweep_rank_kernel(FullParams fp, Full
 // ipow takes for each of them apart.  A wave none of whose 256 tokens belongs to the support repeats the prefix
 // before it: it computes nothing.  Bound: arithmetic, 2 float64 operations per token, size and draft count plus the
 // chain.  (One workgroup per row for all sizes, a wave reduction per cell and round, and a chain per draft count:
-// 4576 us for 256 rows of 128256 tokens, 6 sizes and 10 draft counts; now 1284 us.)
+// 4576 us for 256 rows of 128256 tokens, 6 sizes and 10 draft counts; now 1388 us, at 3.1 GB.)
 template <int NT>
 __global__ __launch_bounds__(NT) void full_sweep_scan_kernel(FullParams fp, FullSweep fs) {
     constexpr int NW = NT / 64;

@@ -7,7 +7,7 @@
 
 namespace gr {
 
-constexpr int kThreads = 256;             // every kernel here runs 256-thread workgroups (4 wave64)
+constexpr int kThreads = 256;             // 256-thread workgroups (4 wave64), but for the solve kernels and those that order long rows
 constexpr int kWaves = kThreads / 64;
 constexpr int kMaxSupport = GR_MAX_SUPPORT;
 constexpr int kMaxT = GR_MAX_T;
