@@ -5,7 +5,7 @@
 //   order by decreasing q/p, prefix psi, H*, alpha*         (Sec. 5.1, Thm 3.1)
 //   suffix minima -> outer targets p_i and block boundaries (Thm 6.2, Lemma 6.3)
 //   truncation sets T                                       (Alg. 1, Sec. 6.3)
-//   softmax weights of Theta_T / Phi_T by iterative scaling (Thm 6.5 / Thm 6.4)
+//   softmax weights of Theta_T / Phi_T by Newton's iteration (Thm 6.5 / Thm 6.4)
 //
 // A second kernel (full_programs_kernel) runs the same programs for rows whose steps 1-2 were done in
 // HBM because the support is the whole vocabulary.
@@ -18,6 +18,8 @@
 // through its logarithm: log(1 + x (e^u - 1)) = sum_k kappa_k(x) u^k / k! with the cumulants of a
 // Bernoulli(x) variable, and only k <= n can reach the z^n coefficient, so n cumulant sums per
 // quadrature node describe all tokens exactly; the series exponential is taken once per node.
+#include <type_traits>
+
 #include "gr_internal.h"
 #include "gr_verify_row.h"
 
@@ -46,15 +48,19 @@ constexpr int KS = kMaxSupport;
 #endif
 template <int D> constexpr int kThreadsOf = D > 8 ? 256 : GR_THREADS_UP_TO_8;
 constexpr double kQuadStep = 0.45;   // trapezoid step in log t (discretisation error ~1e-9 relative)
+constexpr double kQuadGrow = 1.5683121854901688;   // e^0.45
 constexpr double kQuadLo = 1e-4;     // t_lo * (slack + sum w): the part below t_lo is added in closed form
 constexpr double kQuadHi = 25.0;     // t_hi * (slowest decay rate)
-constexpr double kStretch = 4.0;     // first cap on the per-coordinate stretch of the fixed-point step
-constexpr int kStall = 3;            // iterations without a better point before the cap is halved
-constexpr double kOddsFrom = 0.9, kOddsTo = 0.999;    // targets within these shares of Pr[token drawn] ...
-constexpr double kOddsFirst = 0.5;                    // ... that start further than this from their routed mass (in log) step on the log odds ...
-constexpr double kOddsUntil = 1e-6;                   // ... while the stopping measure is above this
-constexpr int kMixBudget = 60;       // the mixed fixed-point iteration gets kMixBudget + m evaluations before Newton takes over
-constexpr int kCols = kHist - 1;                       // Anderson columns
+constexpr int kStar = 8;             // tokens of a program whose couplings to every token are computed (the others meet in a hub)
+constexpr double kClip = 3.0;        // longest step in log weight
+constexpr double kOddsFrom = 0.5;    // a target above this share of Pr[token drawn] aims at its log odds while its mass falls short
+constexpr double kSecantBelow = 1e-2;   // stopping measure from which on a step is combined with the one before it
+constexpr double kKeepBelow = 1e-3;  // stopping measure from which on the couplings stay as they are
+constexpr int kStall = 4;            // steps without a better point before fixed-point steps are mixed in
+constexpr int kRetreats = 30;        // returns to the best point, each with half the step, before the program is left to the fallback
+constexpr int kStarBudget = 60;      // the iteration gets kStarBudget + m evaluations before the fallback takes over
+constexpr int kRowW = 12;            // floats of a token's row of couplings: kStar couplings, slack, hub, right-hand side, 1 / sum
+constexpr int kNodes = kStar + 2;    // the reduced system's vertices: kStar tokens, slack, hub
 constexpr int kMaxHeavy = 3;         // tokens that keep their exact factor (only with more than 8 drafts)
 constexpr double kHeavyShare = 0.3;  // ... those above this share of the program's draw mass
 
@@ -72,15 +78,16 @@ struct Lds {
     static constexpr int kST = kThreadsOf<D>;
     static constexpr int kSW = kST / 64;
     static constexpr int kNPW = 64 / kSW;   // quadrature nodes a wave owns within a chunk of 64
+    static constexpr int kSer = D < 4 ? 4 : D;                // floats of one series of hser ...
+    static constexpr int kSerStride = kStar * kSer + 4;      // ... and of a node's kStar of them (padded: neighbouring nodes start four banks apart)
     // support, in ratio order
     int tok[KS]; int blk[KS]; int inT[KS]; int ordq[KS]; int apos[kMaxT];
-    int flag[KS + 2]; int blo[KS + 2];
+    int flag[KS + 2]; int blo[KS + 2]; int star[kStar];
     double qn[KS]; double pn[KS]; double rho[KS]; double tgt[KS]; double wgt[KS];
     double Q[KS + 1]; double F[KS + 2];
-    // one convex program (tokens by decreasing q)
+    // one convex program (the kStar tokens of largest target first, then by decreasing q)
     double aq[kMaxT]; double at[kMaxT]; double aal[kMaxT]; double aR[kMaxT];
-    double aS[kMaxT]; double ag[kMaxT];   // with aR: what one evaluation hands to the mixing step (see solve_program)
-    int aodds[kMaxT];                     // tokens that step on their log odds (chosen at a program's first evaluation)
+    double aS[kMaxT]; double ag[kMaxT];   // with aR: what one evaluation hands to the step (see solve_program)
     double aR0, alc;                      // ... the slack mass and, with slack, log(slack mass / its target)
     double ared[2][3];                    // ... and the first two waves' sum of R, max and min of log(target / R)
     double apd[kMaxT];              // Pr[token drawn within the program] = atot^n - (atot - q)^n
@@ -95,17 +102,22 @@ struct Lds {
             double qd[KS]; double accb[KS];
             double dlt[KS]; double dval[KS];   // rows given as logits: draft minus target logit, draft logit
             double P[KS + 1]; double S[KS + 1]; double G0[KS + 2]; double G1[KS + 2];
+            unsigned long long keys[kSelCap];   // unsorted candidates (select merge)
         };
         struct {
+            double hpair[kSW][4];       // per wave: the couplings of the heavy tokens 0-1, 0-2, 1-2 (only with more than 8 drafts)
             double rpart[kSW][kMaxT];   // per wave: sum over its nodes of the integrand of each token
             double spart[kSW][kMaxT];   // the same weighted by t
-            NodeRec<D> nrec[kSW][kNPW];
+            float cpart[kSW][kMaxT * kStar];   // per wave: the couplings of each token to the first kStar
+            float hser[kSW][kNPW / 2 * kSerStride];   // per wave: the series of the first kStar tokens at every other node
+            NodeRec<D> nrec[D > 8 ? kSW : 1][D > 8 ? kNPW : 1];
             TokRec<D> trec[kMaxT + 4];  // active tokens; every record beyond the last has aw = 1e300 (x = 0), e = 0
         };
     };
-    double Ha[kHist][kMaxT]; double Hf[kHist][kMaxT]; double aBest[kMaxT]; double fBest[kMaxT]; double rBest[kMaxT];
-    double pm[kHist][kHist];        // inner products of the stored residual vectors of the mixing, by history slot
-    Grid ctl_grid; int ctl_go, ctl_result, ctl_bestok;   // handed from the mixing wave to all waves
+    double aBest[kMaxT]; double fBest[kMaxT]; double aPrev[kMaxT]; double fPrev[kMaxT];
+    alignas(16) float W[kMaxT][kRowW];   // the tokens' rows of the reduced system
+    alignas(16) float Am[16][20];        // the light tokens' share of it, as the matrix cores leave it
+    Grid ctl_grid; int ctl_go, ctl_result, ctl_bestok, ctl_couple;   // handed from the stepping wave to all waves
     double e2tab[32];               // 2^(-j/32)
     int nheavy;                     // leading tokens that keep their exact factor
     int nfull;                      // leading tokens (the heavy ones included) that need all D cumulants; the rest need four
@@ -114,7 +126,6 @@ struct Lds {
     long long clk[24]; long long clk_last; double errlog[24];
 #endif
     double red[2][kSW][8]; double redn[kSW]; double r0part[kSW]; int pick[4]; int count; int hist[256];
-    unsigned long long keys[kSelCap];   // unsorted candidates (select merge)
 };
 
 // ---- workgroup reductions with one barrier: the waves' partial results alternate between two LDS
@@ -172,6 +183,16 @@ template <class LdsT> __device__ __forceinline__ double wg_max(LdsT& L, int& par
     double a[1] = {wave_max(v)};
     wg_reduce<1>(L, par, a, {kOpMax});
     return a[0];
+}
+
+__device__ __forceinline__ unsigned wave_max_u(unsigned x) {
+    int v = static_cast<int>(x);
+    v = static_cast<int>(max(static_cast<unsigned>(v), static_cast<unsigned>(dpp_move<kDppXor1>(v))));
+    v = static_cast<int>(max(static_cast<unsigned>(v), static_cast<unsigned>(dpp_move<kDppXor2>(v))));
+    v = static_cast<int>(max(static_cast<unsigned>(v), static_cast<unsigned>(dpp_move<kDppHalfMirror>(v))));
+    v = static_cast<int>(max(static_cast<unsigned>(v), static_cast<unsigned>(dpp_move<kDppMirror>(v))));
+    return max(max(static_cast<unsigned>(__builtin_amdgcn_readlane(v, 0)), static_cast<unsigned>(__builtin_amdgcn_readlane(v, 16))),
+               max(static_cast<unsigned>(__builtin_amdgcn_readlane(v, 32)), static_cast<unsigned>(__builtin_amdgcn_readlane(v, 48))));
 }
 
 // 1/x from the hardware estimate and two Newton steps (about 1e-16 relative; x = 0, infinite or NaN gives NaN or 0).
@@ -240,13 +261,13 @@ __device__ constexpr double kCumA[17][8] = {
 };
 
 // g[k-1] = g_k(x) for k = 1..C.
-template <int K, int C>
-__device__ __forceinline__ void cum_g_from(double v, double s, double (&g)[C]) {
+template <int K, int C, class T>
+__device__ __forceinline__ void cum_g_from(T v, T s, T (&g)[C]) {
     if constexpr (K <= C) {
         constexpr int deg = (K - 1) / 2;
-        double r = kCumA[K][deg];
+        T r = static_cast<T>(kCumA[K][deg]);
 #pragma unroll
-        for (int j = deg - 1; j >= 0; --j) r = fma(r, v, kCumA[K][j]);
+        for (int j = deg - 1; j >= 0; --j) r = fma(r, v, static_cast<T>(kCumA[K][j]));
         g[K - 1] = (K % 2 == 0) ? r * s : r;
         cum_g_from<K + 1, C>(v, s, g);
     }
@@ -433,10 +454,181 @@ __device__ __forceinline__ Grid make_grid(int slack, double ctx, double wsum, do
     if (N < 1) N = 1;
     if (N > 4096) N = 4096;
     g.N = N;
-    const double estep = g.step == kQuadStep ? 1.5683121854901688 : exp(g.step);      // e^0.45
-    g.tail = g.step * g.t_lo * fast_rcp(estep - 1.0);
-    g.tail2 = g.step * g.t_lo * g.t_lo * fast_rcp(estep * estep - 1.0);
+    double geo = kQuadStep / (kQuadGrow - 1.0), geo2 = kQuadStep / (kQuadGrow * kQuadGrow - 1.0);
+    if (g.step != kQuadStep) { const double estep = exp(g.step); geo = g.step * fast_rcp(estep - 1.0); geo2 = g.step * fast_rcp(estep * estep - 1.0); }
+    g.tail = geo * g.t_lo;
+    g.tail2 = geo2 * g.t_lo * g.t_lo;
     return g;
+}
+
+// The couplings C_ij = E[s_i s_j] (s_i = w_i / (slack + sum of the drawn tokens' w) for a drawn token, 0 otherwise) are
+// the off-diagonal entries of -dR_i / dalpha_j; with phi_i(z) = x_i (e^{zq_i} - 1) / (1 + x_i (e^{zq_i} - 1)),
+//     C_ij = w_i w_j n! int t e^{-slack t} [z^n] T phi_i phi_j dt.
+// They only steer the step, so they are taken in float32 and at every other node of the grid (the trapezoid rule with twice
+// the step is good to 1e-4), for the first kStar tokens j and every token i.  Two lanes share a node: lane k of the wave's
+// even nodes takes the tokens 0..3 of the kStar, its mirror lane (that of the odd neighbour) the tokens 4..7.
+// star_series: u[k-1] = weight * t w_j [z^{n-k}] (T phi_j) / k!, k = 1 .. D - 1, of one of the kStar tokens at one node; the
+// row of token i is then w_i n! sum over the nodes and k of x_i g_k(x_i) q_i^k u[k-1].  Tr[k-1] = T_{n-k}; e: the token's series.
+template <int D>
+__device__ __forceinline__ void star_series(const float (&Tr)[D], const double* e, double tw, double qw2, float x, float* out) {
+    constexpr int M = D - 1;
+    float g[M], phi[M];
+    cum_g_from<1, M>(fmaf(-x, x, x), fmaf(-2.f, x, 1.f), g);
+#pragma unroll
+    for (int b = 1; b <= M; ++b) phi[b - 1] = x * g[b - 1] * static_cast<float>(e[b - 1]);
+    float cw = static_cast<float>(qw2 * fmin(tw, 1000.0));    // beyond that x = 0
+    float u[Lds<D>::kSer];
+#pragma unroll
+    for (int k = 1; k <= Lds<D>::kSer; ++k) {
+        float acc = 0.f;
+#pragma unroll
+        for (int b = 1; b <= D - k; ++b) acc = fmaf(phi[b - 1], Tr[k + b - 1], acc);
+        cw *= 1.f / static_cast<float>(k);
+        u[k - 1] = acc * cw;
+    }
+#pragma unroll
+    for (int k = 0; k < Lds<D>::kSer; k += 4) *reinterpret_cast<float4*>(out + k) = make_float4(u[k], u[k + 1], u[k + 2], u[k + 3]);
+}
+// This lane's four series of a node (half = 0: tokens 0..3, 1: tokens 4..7).
+template <int D>
+__device__ __forceinline__ void star_load(float (&U)[4][Lds<D>::kSer], const float* node, int half) {
+#pragma unroll
+    for (int h = 0; h < 4; ++h)
+#pragma unroll
+        for (int k = 0; k < Lds<D>::kSer; k += 4) {
+            const float4 v = *reinterpret_cast<const float4*>(node + (4 * half + h) * Lds<D>::kSer + k);
+            U[h][k] = v.x; U[h][k + 1] = v.y; U[h][k + 2] = v.z; U[h][k + 3] = v.w;
+        }
+}
+// One token's terms at one node for four of the kStar tokens, its orders up to C.
+template <int D, int C>
+__device__ __forceinline__ void star_row(const float (&U)[4][Lds<D>::kSer], float q, float x, float (&acc)[4]) {
+    float y[C];
+    y[0] = x * q;
+    if constexpr (C >= 2) {
+        float g[C], xq = y[0];
+        cum_g_from<1, C>(fmaf(-x, x, x), fmaf(-2.f, x, 1.f), g);
+#pragma unroll
+        for (int k = 2; k <= C; ++k) { xq *= q; y[k - 1] = xq * g[k - 1]; }
+    }
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+        acc[h] = y[0] * U[h][0];
+#pragma unroll
+        for (int k = 2; k <= C; ++k) acc[h] = fmaf(y[k - 1], U[h][k - 1], acc[h]);
+    }
+}
+template <int CTRL> __device__ __forceinline__ float dpp_f(float v) { return __int_as_float(dpp_move<CTRL>(__float_as_int(v))); }
+// Keeps one of two values and adds the partner lane's copy of it: the first step of a sum that also parts the values.
+template <int CTRL> __device__ __forceinline__ float part_add(float a, float b, bool second) {
+    const float keep = second ? b : a, send = second ? a : b;
+    return keep + dpp_f<CTRL>(send);
+}
+
+// The same for a token that keeps its exact factor (more than 8 drafts): its cumulants cancel, so T phi = (T / (1 + x (e^u - 1)))
+// x (e^u - 1) is taken by series division in float64.
+template <int D, int NN>
+__device__ __forceinline__ void pick_star(float (&u)[D], const double (&V)[D], int n) {
+    if constexpr (NN >= 1) {
+        if (n == NN) {
+#pragma unroll
+            for (int k = 1; k <= D; ++k) u[k - 1] = (NN - k >= 1) ? static_cast<float>(V[(NN - k >= 1) ? NN - k : 0]) : 0.f;
+            return;
+        }
+        pick_star<D, NN - 1>(u, V, n);
+    }
+}
+// B = T / (1 + x (e^u - 1)) up to degree D - 1.
+template <int D>
+__device__ __forceinline__ void divide_factor(double (&B)[D], double x, const double* e) {
+#pragma unroll
+    for (int d = 1; d < D; ++d) {
+        double conv = 0.0;
+#pragma unroll
+        for (int a = 1; a <= d; ++a) conv = fma(e[a - 1], B[d - a], conv);
+        B[d] = fma(-x, conv, B[d]);
+    }
+}
+template <int D>
+__device__ __forceinline__ void star_series_exact(const double (&T)[D + 1], const double* e, double tw, double qw2, double x, int n, float* out) {
+    double B[D], V[D];
+#pragma unroll
+    for (int d = 0; d < D; ++d) B[d] = T[d];
+    divide_factor<D>(B, x, e);
+    const double cx = qw2 * fmin(tw, 1000.0) * x;
+    V[0] = 0.0;
+#pragma unroll
+    for (int d = 1; d < D; ++d) {
+        double conv = 0.0;
+#pragma unroll
+        for (int a = 1; a <= d; ++a) conv = fma(e[a - 1], B[d - a], conv);
+        V[d] = cx * conv;
+    }
+    float u[D], inv = 1.f;
+    pick_star<D, D>(u, V, n);
+#pragma unroll
+    for (int k = 1; k <= D; ++k) { inv *= 1.f / static_cast<float>(k); u[k - 1] *= inv; }
+#pragma unroll
+    for (int k = 0; k < D; k += 4) *reinterpret_cast<float4*>(out + k) = make_float4(u[k], u[k + 1], u[k + 2], u[k + 3]);
+}
+// [z^n] T phi_a phi_b of two such tokens.
+template <int D>
+__device__ __forceinline__ double heavy_pair(const double (&T)[D + 1], const double* ea, const double* eb, double xa, double xb, int n) {
+    double B[D];
+#pragma unroll
+    for (int d = 0; d < D; ++d) B[d] = T[d];
+    divide_factor<D>(B, xa, ea);
+    divide_factor<D>(B, xb, eb);
+    double V[D];
+    V[0] = 0.0;
+#pragma unroll
+    for (int d = 1; d < D; ++d) {
+        double conv = 0.0;
+#pragma unroll
+        for (int a = 1; a <= d; ++a) conv = fma(ea[a - 1], B[d - a], conv);
+        V[d] = conv;
+    }
+    double out = 0.0;
+#pragma unroll
+    for (int d = 1; d < D; ++d) out = fma(d < n ? V[d] : 0.0, eb[n - d > 0 ? n - d - 1 : 0], out);
+    return xa * xb * out;
+}
+// Phase 4 of an evaluation: the rows of all tokens from the series that the wave has left in hser.  t: abscissa of the
+// lane's node.  The sixteen tokens that come first (the kStar, then the largest q) take all orders, the others the first (the first
+// two with more than 8 drafts): with all orders for all of them the step is no better, as their q is small.
+// `more`: the wave has been through a chunk of nodes before.
+template <int D>
+__device__ __forceinline__ void star_phase(Lds<D>& L, int lane, int wv, int m, double t, bool more) {
+    constexpr int NPW = Lds<D>::kNPW, NS = 64 / NPW, CC = D > 8 ? 2 : 1;
+    const int j = lane & (NPW - 1), tsub = lane / NPW;
+    const bool upper = j >= NPW / 2, b0 = j & 1, b1 = j & 2, b2 = j & 4;
+    const double tm = dpp_move<NPW == 8 ? kDppHalfMirror : kDppMirror>(t);
+    const double te = upper ? tm : t;                          // the pair's even node
+    wave_lds_sync();
+    float U[4][Lds<D>::kSer];
+    star_load<D>(U, &L.hser[wv][(upper ? NPW - 1 - j : j) * Lds<D>::kSerStride], upper);
+    float* out = &L.cpart[wv][tsub * kStar + (NPW == 8 ? j : (upper ? 4 : 0) + (b2 ? 2 : 0) + (b0 ? 1 : 0))];
+    auto row = [&](int i, auto all) {
+        const TokRec<D>& rec = L.trec[NS * i + tsub];          // records beyond the last token: x = 0
+        const float x = __expf(-static_cast<float>(fmin(te * rec.aw, 1000.0))), q = static_cast<float>(rec.e[0]);
+        float acc[4], c;
+        star_row<D, decltype(all)::value>(U, q, x, acc);
+        if constexpr (NPW == 8) {
+            const float r0 = part_add<kDppXor1>(acc[0], acc[1], b0), r1 = part_add<kDppXor1>(acc[2], acc[3], b0);
+            c = part_add<kDppXor2>(r0, r1, b1);
+        } else {
+            const float r0 = part_add<kDppHalfMirror>(acc[0], acc[2], b2), r1 = part_add<kDppHalfMirror>(acc[1], acc[3], b2);
+            c = part_add<kDppXor1>(r0, r1, b0);
+            c += dpp_f<kDppXor2>(c);
+        }
+        float* const at = out + i * NS * kStar;
+        if (NPW == 8 || !b1) *at = more ? *at + c : c;
+    };
+    const int rows = (m + NS - 1) / NS;
+    int i = 0;
+    for (; i < min(rows, 16 / NS); ++i) row(i, std::integral_constant<int, D - 1>());
+#pragma unroll 2
+    for (; i < rows; ++i) row(i, std::integral_constant<int, CC>());
 }
 
 // Routed mass of every active token, and the mass left to the slack term.
@@ -450,16 +642,13 @@ __device__ __forceinline__ Grid make_grid(int slack, double ctx, double wsum, do
 //   phase 2  per node: T = exp(z ctx + cumulant series) (times the exact factors of the heavy tokens), the
 //            slack integrand, and the node record {t, weight, T_{n-1..n-D}} -> LDS;
 //   phase 3  lane = (token, node subset): the leave-one-out coefficient of its token at each of the wave's
-//            nodes; the waves' partial sums meet in LDS at the end.
+//            nodes; the waves' partial sums meet in LDS at the end;
+//   phase 4  lane = (node pair and half of the first kStar tokens, token subset): the couplings (star_phase).
 // In: L.trec[] (weights and series terms), L.apd / L.nheavy / L.nfull (set up by solve_program), the grid.
-// Out: every wave's partial sums in L.rpart / L.spart / L.r0part.  All waves call it behind a barrier that made
-// the weights visible; it contains no workgroup barrier itself.
+// Out: every wave's partial sums in L.rpart / L.spart / L.r0part, and in L.cpart where `couple` is set.  All waves call it
+// behind a barrier that made the weights visible; it contains no workgroup barrier itself.
 template <int D>
-__device__ __forceinline__ void eval_core_rows(Lds<D>& L, const Grid& gr, int m, int n, double ctx, int slack);
-
-template <int D>
-__device__ __forceinline__ void eval_core(Lds<D>& L, const Grid& gr, int m, int n, double ctx, int slack) {
-    if constexpr (D <= 8) { eval_core_rows<D>(L, gr, m, n, ctx, slack); return; }
+__device__ __forceinline__ void eval_core_nodes(Lds<D>& L, const Grid& gr, int m, int n, double ctx, int slack, bool couple) {
     constexpr int kSW = Lds<D>::kSW, NPW = Lds<D>::kNPW, NS = 64 / NPW;
     constexpr int CL = D < 4 ? D : 4;                          // cumulants of a light token
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -467,6 +656,7 @@ __device__ __forceinline__ void eval_core(Lds<D>& L, const Grid& gr, int m, int 
     const int nfull = (D > 4) ? L.nfull : nheavy;              // up to four drafts four cumulants are all there are
     const double t_lo = gr.t_lo, step = gr.step;
     const int N = gr.N;
+    static_assert(NPW == 16 && NS == 4, "phase 4 pairs the sixteen node lanes of a subset by a row mirror");
     for (int i = lane; i < m; i += 64) { L.rpart[wv][i] = 0.0; L.spart[wv][i] = 0.0; }
     double r0 = 0.0;                                       // slack integrand, lanes of token subset 0
     double hacc[kMaxHeavy] = {0.0, 0.0, 0.0}, hacct[kMaxHeavy] = {0.0, 0.0, 0.0};
@@ -475,9 +665,12 @@ __device__ __forceinline__ void eval_core(Lds<D>& L, const Grid& gr, int m, int 
 
     for (int c0 = 0; c0 < N; c0 += 64) {
         const int nn = min(64, N - c0);
-        const int npw = (nn - wv + kSW - 1) / kSW;          // nodes of this wave in the chunk: c0 + wv + kSW j
-        const double t = t_lo * exp(step * static_cast<double>(c0 + wv + kSW * j));
-        const double qw = j < npw ? step * t * exp_neg(slack * t, L.e2tab) : 0.0;
+        // pairs of neighbouring nodes are dealt to the waves; the wave's node j sits at place `at` of its nodes in rising order
+        const int pairs = (nn + 1) >> 1, mine = (pairs - wv + kSW - 1) / kSW;
+        const int npw = 2 * mine - ((nn & 1) && (pairs - 1) % kSW == wv ? 1 : 0);
+        const int at = j < 8 ? 2 * j : 2 * (15 - j) + 1;
+        const double t = t_lo * exp(step * static_cast<double>(c0 + 2 * wv + 2 * kSW * (at >> 1) + (at & 1)));
+        const double qw = at < npw ? step * t * exp_neg(slack * t, L.e2tab) : 0.0;
         // ---- phase 1: cumulant sums at node j of the tokens of subset tsub
         double K[D];
 #pragma unroll
@@ -532,13 +725,42 @@ __device__ __forceinline__ void eval_core(Lds<D>& L, const Grid& gr, int m, int 
             NodeRec<D> rec;
             rec.t = t; rec.qw = qw;
             const double tn = pick_series<D, D>(rec, T, n);
-            if (tsub == 0) { r0 = fma(qw, tn, r0); L.nrec[wv][j] = rec; }
+            if (tsub == 0) { r0 = fma(qw, tn, r0); L.nrec[wv][at] = rec; }
+            if (couple) {
+            // the even nodes' series of the first kStar tokens: lane (k, tsub) takes token tsub at the k-th of them, its
+            // mirror token 4 + tsub
+            const bool upper = j >= 8;
+            const int k = upper ? 15 - j : j, a = tsub + (upper ? 4 : 0);
+            float Tr[D];
+#pragma unroll
+            for (int b = 0; b < D; ++b) {
+                const float v = static_cast<float>(rec.Tr[b]), w = dpp_f<kDppMirror>(v);
+                Tr[b] = upper ? w : v;
+            }
+            const double tm = dpp_move<kDppMirror>(t), qm = dpp_move<kDppMirror>(qw);       // not inside the selection: every lane must be active
+            const double te = upper ? tm : t, qe = upper ? qm : qw;
+            const double tw = te * L.trec[a].aw;
+            float* const out = &L.hser[wv][k * Lds<D>::kSerStride + a * Lds<D>::kSer];
+            if (a >= nheavy) star_series<D>(Tr, L.trec[a].e, tw, 2.0 * qe, __expf(-static_cast<float>(fmin(tw, 1000.0))), out);
+            else star_series_exact<D>(T, L.trec[a].e, tw, 2.0 * qe, exp_neg(tw, L.e2tab), n, out);
+            // the heavy tokens' couplings among themselves: one pair per token subset
+            if (nheavy >= 2) {
+                const int pa = tsub == 2 ? 1 : 0, pb = tsub == 0 ? 1 : 2;
+                double c = 0.0;
+                if (tsub < 3 && pb < nheavy)
+                    c = qw * t * heavy_pair<D>(T, L.trec[pa].e, L.trec[pb].e, exp_neg(t * L.trec[pa].aw, L.e2tab), exp_neg(t * L.trec[pb].aw, L.e2tab), n);
+                c += dpp_move<kDppXor1>(c); c += dpp_move<kDppXor2>(c); c += dpp_move<kDppHalfMirror>(c); c += dpp_move<kDppMirror>(c);
+                if (j == 0 && tsub < 3) L.hpair[wv][tsub] = c0 > 0 ? L.hpair[wv][tsub] + c : c;
+            }
+            }
         }
         wave_lds_sync();
         GR_CLK(L, 8);
         // ---- phase 3
         if constexpr (D > 4) phase3_range<D, D>(L, nheavy, nfull, m, npw, wv, lane);
         phase3_range<D, CL>(L, nfull, m, m, npw, wv, lane);
+        // ---- phase 4
+        if (couple) star_phase<D>(L, lane, wv, m, t, c0 > 0);
         wave_lds_sync();                                   // this wave's node records are rewritten by its next chunk
         GR_CLK(L, 9);
     }
@@ -562,8 +784,11 @@ __device__ __forceinline__ void eval_core(Lds<D>& L, const Grid& gr, int m, int 
 // series, which this lane already holds, and the token's q; it ends with a sum over the NPW neighbouring lanes that
 // hold the nodes of a subset.  No node records in LDS and no exchange between the phases.
 // Rows whose first token is below L.nfull take all D cumulants, the others four.
+// A wave owns eight neighbouring nodes, so that a grid of few nodes leaves whole waves (and their share of the SIMDs) out;
+// lanes 0..3 hold its even nodes in order, lanes 7..4 the odd ones, so that a half-row mirror pairs neighbours (star_series).
+// The first row's lanes hold the factors of the first kStar tokens: lane (node, tsub) takes the series of token tsub.
 template <int D>
-__device__ __forceinline__ void eval_core_rows(Lds<D>& L, const Grid& gr, int m_, int n_, double ctx, int slack_) {
+__device__ __forceinline__ void eval_core_rows(Lds<D>& L, const Grid& gr, int m_, int n_, double ctx, int slack_, bool couple) {
     constexpr int kSW = Lds<D>::kSW, NPW = Lds<D>::kNPW, NS = 64 / NPW, NT = kMaxT / NS;
     constexpr int CL = D < 4 ? D : 4;
     static_assert(D <= 8 && NPW == 8 && NT % 2 == 0, "rows are taken two at a time; eight node lanes per subset");
@@ -575,15 +800,20 @@ __device__ __forceinline__ void eval_core_rows(Lds<D>& L, const Grid& gr, int m_
     const double t_lo = gr.t_lo, step = gr.step;
     const int N = __builtin_amdgcn_readfirstlane(gr.N);
     const int j = lane & (NPW - 1), tsub = lane / NPW;
-    for (int i = lane; i < kMaxT; i += 64) { L.rpart[wv][i] = 0.0; L.spart[wv][i] = 0.0; }
+    const bool upper = j >= 4;                             // the odd nodes
+    static_assert(NS == kStar, "the first row of tokens are the kStar");
     double r0 = 0.0;                                       // slack integrand, lanes of token subset 0
     GR_CLK(L, 6);
 
-    for (int c0 = 0; c0 < N; c0 += 64) {
-        const int nn = min(64, N - c0);
-        const int npw = (nn - wv + kSW - 1) / kSW;          // nodes of this wave in the chunk: c0 + wv + kSW j
-        const double t = t_lo * exp(step * static_cast<double>(c0 + wv + kSW * j));
-        const double qw = j < npw ? step * t * exp_neg(slack * t, L.e2tab) : 0.0;
+    if (NPW * wv >= N) {                                   // no node for this wave: its sums are 0
+        for (int i = lane; i < m; i += 64) { L.rpart[wv][i] = 0.0; L.spart[wv][i] = 0.0; }
+        if (couple) for (int i = lane; i < m * (kStar / 4); i += 64) *reinterpret_cast<float4*>(&L.cpart[wv][4 * i]) = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    for (int c0 = NPW * wv; c0 < N; c0 += 64) {             // this wave's first node of the chunk
+        const bool more = c0 >= 64;                         // its sums go on
+        const int node = c0 + (upper ? 15 - 2 * j : 2 * j);
+        const double t = t_lo * exp(step * static_cast<double>(node));
+        const double qw = node < N ? step * t * exp_neg(slack * t, L.e2tab) : 0.0;
         // ---- phase 1: cumulant sums at this lane's node over the tokens of its subset
         double K[D], xs[NT];
 #pragma unroll
@@ -637,6 +867,12 @@ __device__ __forceinline__ void eval_core_rows(Lds<D>& L, const Grid& gr, int m_
             NodeRec<D> rec;
             const double tn = pick_series<D, D>(rec, T, n);
             if (tsub == 0) r0 = fma(qw, tn, r0);
+            float Tr[D];
+#pragma unroll
+            for (int k = 0; k < D; ++k) Tr[k] = static_cast<float>(rec.Tr[k]);
+            if (couple && !upper)
+                star_series<D>(Tr, L.trec[tsub].e, t * L.trec[tsub].aw, 2.0 * qw, static_cast<float>(xs[0]),
+                               &L.hser[wv][j * Lds<D>::kSerStride + tsub * Lds<D>::kSer]);
             double invf = qw;
 #pragma unroll
             for (int k = 1; k <= D; ++k) { invf *= 1.0 / k; Tp[k - 1] = rec.Tr[k - 1] * invf; }
@@ -646,14 +882,13 @@ __device__ __forceinline__ void eval_core_rows(Lds<D>& L, const Grid& gr, int m_
         // the eight node lanes of a subset: the first step (lane k with lane 7 - k) also parts the two sums, R to
         // lanes 0-3 and its t-weighted companion S to lanes 4-7, so that the other two steps move one value, not two.
         double qna = L.trec[tsub].e[0], qnb = L.trec[tsub + NS].e[0];
-        const bool upper = (NPW == 8) && j >= 4;
         double* const part = upper ? &L.spart[wv][0] : &L.rpart[wv][0];
 #pragma unroll
         for (int i = 0; i < NT; i += 2) {
             if (NS * i < m) {
                 const int a = NS * i + tsub, b = a + NS;            // b <= kMaxT - 1: sums of rows past the last token are 0
                 double olda = 0.0, oldb = 0.0;
-                if ((j & 3) == 0) { olda = part[a]; oldb = part[b]; }
+                if (more && (j & 3) == 0) { olda = part[a]; oldb = part[b]; }
                 const double qa = qna, qb = qnb;
                 if (i + 2 < NT) {
                     qna = L.trec[b + NS].e[0];
@@ -674,6 +909,9 @@ __device__ __forceinline__ void eval_core_rows(Lds<D>& L, const Grid& gr, int m_
                 if ((j & 3) == 0) { part[a] = olda + ka; part[b] = oldb + kb; }
             }
         }
+        // ---- phase 4
+        if (couple) star_phase<D>(L, lane, wv, m, t, more);
+        wave_lds_sync();                                   // the series are rewritten by the wave's next chunk
         GR_CLK(L, 9);
     }
     {
@@ -683,18 +921,29 @@ __device__ __forceinline__ void eval_core_rows(Lds<D>& L, const Grid& gr, int m_
     if (tid == 0) L.work += static_cast<double>(N) * m;
 }
 
-// The routed mass R and its t-weighted companion S of token `tok` from the waves' partial sums (behind the
-// barrier that follows eval_core), and the slack mass.
 template <int D>
-__device__ __forceinline__ void token_sums(const Lds<D>& L, const Grid& gr, int tok, double fact, double& R, double& S) {
+__device__ __forceinline__ void eval_core(Lds<D>& L, const Grid& gr, int m, int n, double ctx, int slack, bool couple) {
+    if constexpr (D <= 8) eval_core_rows<D>(L, gr, m, n, ctx, slack, couple); else eval_core_nodes<D>(L, gr, m, n, ctx, slack, couple);
+}
+
+// The routed mass R of token `tok`, its t-weighted companion S (the share that the token loses to itself) and, with slack,
+// its coupling to the slack vertex, from the waves' partial sums (behind the barrier that follows eval_core).
+struct TokenSums { double R, S, b; };
+template <int D>
+__device__ __forceinline__ TokenSums token_sums(const Lds<D>& L, const Grid& gr, int tok, double fact) {
     constexpr int kSW = Lds<D>::kSW;
     const double rfact = fast_rcp(fact);
     double r = L.apd[tok] * gr.tail * rfact, sq = L.apd[tok] * gr.tail2 * rfact;
 #pragma unroll
-    for (int w2 = 0; w2 < kSW; ++w2) { r += L.rpart[w2][tok]; sq += L.spart[w2][tok]; }
+    for (int w2 = 0; w2 < kSW; ++w2) {
+        r += L.rpart[w2][tok]; sq += L.spart[w2][tok];
+    }
     const double w = L.trec[tok].aw;
-    R = r * w * fact;
-    S = sq * w * w * fact;
+    TokenSums o;
+    o.R = r * w * fact;
+    o.b = sq * w * fact;
+    o.S = o.b * w;
+    return o;
 }
 template <int D>
 __device__ __forceinline__ double slack_mass(const Lds<D>& L, const Grid& gr, int n, double atot, double fact, int slack) {
@@ -703,6 +952,33 @@ __device__ __forceinline__ double slack_mass(const Lds<D>& L, const Grid& gr, in
 #pragma unroll
     for (int w2 = 0; w2 < kSW; ++w2) r0all += L.r0part[w2];
     return (r0all * fact + ipow(atot, n) * gr.tail) * slack;
+}
+// The couplings of token `tok` to four of the kStar tokens (half: 0 or 1), times `scale`, into its row; none to itself.
+template <int D>
+__device__ __forceinline__ void token_couplings(Lds<D>& L, const Grid& gr, int tok, int half, double scale) {
+    constexpr int kSW = Lds<D>::kSW;
+    float c[4] = {0.f, 0.f, 0.f, 0.f};
+    if (D > 8 && tok < L.nheavy) {
+        // the other token's row, or the heavy pair's own sum
+        for (int h = 0; h < 4; ++h) {
+            const int o = 4 * half + h;
+            double v = 0.0;
+            if (o < L.nheavy) { if (o != tok) for (int w2 = 0; w2 < kSW; ++w2) v += L.hpair[w2][o + tok - 1]; }
+            else for (int w2 = 0; w2 < kSW; ++w2) v += static_cast<double>(L.cpart[w2][o * kStar + tok]);
+            v = o < L.nheavy ? v * L.trec[tok].aw * L.trec[o].aw * scale : v * L.trec[o].aw * scale;
+            L.W[tok][o] = L.trec[o].aw < 1e300 && v > 0.0 ? static_cast<float>(v) : 0.f;
+        }
+        return;
+    }
+#pragma unroll
+    for (int w2 = 0; w2 < kSW; ++w2) {
+        const float4 v = *reinterpret_cast<const float4*>(&L.cpart[w2][tok * kStar + 4 * half]);
+        c[0] += v.x; c[1] += v.y; c[2] += v.z; c[3] += v.w;
+    }
+    const double f = L.trec[tok].aw * scale;
+#pragma unroll
+    for (int h = 0; h < 4; ++h) c[h] = tok == 4 * half + h ? 0.f : fmaxf(static_cast<float>(static_cast<double>(c[h]) * f), 0.f);
+    *reinterpret_cast<float4*>(&L.W[tok][4 * half]) = make_float4(c[0], c[1], c[2], c[3]);
 }
 
 // Workgroup-wide evaluation (the Newton fallback's): every thread passes the log weight of its own token and gets
@@ -716,11 +992,11 @@ __device__ __forceinline__ Routed routed_eval(Lds<D>& L, int& par, int m, int n,
     double a[2] = {wave_sum(tid < m ? w : 0.0), wave_min(tid < m ? w : 1e300)};
     wg_reduce<2>(L, par, a, {kOpSum, kOpMin});              // its barrier also publishes the weights
     const Grid gr = make_grid(slack, ctx, a[0], a[1], kQuadStep);
-    eval_core<D>(L, gr, m, n, ctx, slack);
+    eval_core<D>(L, gr, m, n, ctx, slack, false);
     __syncthreads();
     Routed out;
     out.R = 0.0; out.S = 0.0;
-    if (tid < m) { token_sums<D>(L, gr, tid, fact, out.R, out.S); L.aR[tid] = out.R; }
+    if (tid < m) { const TokenSums ts = token_sums<D>(L, gr, tid, fact); out.R = ts.R; out.S = ts.S; L.aR[tid] = out.R; }
     out.R0 = slack_mass<D>(L, gr, n, ctx + qsum, fact, slack);
     GR_CLK(L, 10);
     return out;
@@ -759,7 +1035,7 @@ __device__ __forceinline__ Defect defect_eval(Lds<D>& L, int& par, int m, int n,
 // Damped Newton iteration on routed(alpha) = target with a finite-difference Jacobian (the Hessian of
 // Theta_T / Phi_T in alpha), for programs on which the fixed-point iteration is slow (a target that
 // nearly exhausts the tuples containing its token).  One step costs one evaluation per variable, so
-// it only takes over when the mixed iteration has used up its budget.  Without slack the last weight
+// it only takes over when the iteration of newton_step has used up its budget.  Without slack the last weight
 // is pinned (the system is singular along the common shift).  Starts from L.aal.
 // J: this row's scratch in HBM, kMaxT rows of kMaxT + 1 doubles (the last column is the right-hand side).
 // The cap counts the evaluations of this program only (`evals0` = the row's count when the program began).
@@ -853,20 +1129,34 @@ __device__ int newton_program(Lds<D>& L, int& par, double* J, int m, int n, doub
     return err <= rel_tol ? 0 : 1;
 }
 
-// The mixing step of one iteration, by wave 0 alone behind the barrier that follows the evaluation.  Compiled as a
-// function of its own (not inlined) so that its values do not compete for registers with the evaluator's series.
-// The uniform solver state travels in MixState; per-token values live in LDS (see solve_program).
-struct MixState { int hcount, plain, since, odds; double best_err, cap; };
+// One step of the iteration, by wave 0 alone behind the barrier that follows the evaluation: Newton's step on the program
+// with a reduced Hessian.  The Hessian of Theta_T / Phi_T in the log weights, -dR_i / dalpha_j, is the Laplacian of the
+// graph whose edges are the couplings C_ij (star_series), with the slack term as one more vertex (its edges S_i / w_i come
+// with the masses): R_i is the sum of row i, S_i included.  The edges of the kStar tokens of largest target are known, and so is
+// what is left of every other row; the light tokens' edges among themselves are taken to be in proportion to what is left of
+// both rows, which is a star around one more vertex, the hub.  Light tokens then touch only the kStar, the slack and the hub: they
+// are eliminated one by one, sum over i of W_i W_i^T / d_i on the matrix cores, and ten vertices remain.  Those are eliminated
+// with every diagonal taken as the sum of its row's edges, so nothing is subtracted and float32 gives the step to 1e-5
+// relative whatever the edges' sizes; the token of largest target is held, so its equation, the one whose rounding would
+// hide the slack's, is the one left out.  In the solver's emulation (1134 programs, n = 2..16) this takes 5.2, 4.5, 4.3 and 4.2
+// evaluations for n = 2, 3-4, 5-8 and 9-16, 17 at most; the fixed-point iteration with Anderson mixing that stood here took
+// 8.9, 7.4, 6.4 and 5.7, and 33 at most.
+// Bound: the serial chain of the stepping wave (about 9 k cycles for up to 64 tokens) between two evaluations.  A call of 256 rows of
+// 32000 tokens, n = 4, k = 64: 242 -> 126 us (and 2424 -> 132 where a row of the batch had reached the finite differences); 64 rows
+// of 1024, n = 4, k = 32: 122 -> 80; 256 rows of 128256, n = 8, k = 128: 272 -> 217.
+// Compiled as a function of its own (not inlined) so that its values do not compete for registers with the evaluator's series.
+// The uniform solver state travels in StepState; per-token values live in LDS (see solve_program).
+struct StepState { int since, retreats, havePrev; double best_err; };
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 template <int D>
-__device__ __attribute__((noinline)) MixState mix_step(MixState st, Grid gr, int it, int m, int n, int slack, double ctx, double slack_target,
-                                                      double tsum, double atot, double fact, double rel_tol, int evals) {
+__device__ __attribute__((noinline)) StepState newton_step(StepState st, int m, int n, int slack, double ctx, double slack_target, double tsum,
+                                                           double rel_tol, int evals) {
     Lds<D>& L = *reinterpret_cast<Lds<D>*>(gr_lds_raw);
     const int tid = threadIdx.x, lane = tid & 63;
-    int hcount = st.hcount, plain = st.plain, since = st.since;
-    double best_err = st.best_err, cap = st.cap;
+    const bool two = m > 64;                               // uniform: lane l holds tokens l and l + 64
     const int tk[2] = {lane, lane + 64};
     const bool on[2] = {tk[0] < m, tk[1] < m};
-    double R[2] = {0.0, 0.0}, S[2] = {0.0, 0.0}, g[2] = {0.0, 0.0}, al[2] = {0.0, 0.0};
+    double R[2] = {0.0, 0.0}, S[2] = {0.0, 0.0}, g[2] = {0.0, 0.0}, al[2] = {0.0, 0.0}, f[2] = {0.0, 0.0};
 #pragma unroll
     for (int u = 0; u < 2; ++u) if (on[u]) {
         R[u] = L.aR[tk[u]]; S[u] = L.aS[tk[u]]; g[u] = L.ag[tk[u]];
@@ -876,191 +1166,183 @@ __device__ __attribute__((noinline)) MixState mix_step(MixState st, Grid gr, int
     // stopping measure: max_i | log(target_i / routed_i) - common term |, the common term log(slack_target / slack
     // mass) with slack, log(sum target / sum routed) without (zero in exact arithmetic: it removes the common
     // quadrature error)
-    const double rd[3] = {L.ared[0][0] + L.ared[1][0], fmax(L.ared[0][1], L.ared[1][1]), fmin(L.ared[0][2], L.ared[1][2])};
-    GR_CLK(L, 19);
-    const double lc = slack ? L.alc : fast_log(rd[0] * fast_rcp(tsum));
-    double err = fmax(fabs(rd[1] + lc), fabs(rd[2] + lc));
-    if (!(err == err) || !(rd[1] < 1e300) || !(rd[2] > -1e300)) err = 1e301;      // NaN or infinite: "no finite point"
+    const double rsum = L.ared[0][0] + L.ared[1][0], gmax = fmax(L.ared[0][1], L.ared[1][1]), gmin = fmin(L.ared[0][2], L.ared[1][2]);
+    const double lc = slack ? L.alc : fast_log(rsum * fast_rcp(tsum));
+    double err = fmax(fabs(gmax + lc), fabs(gmin + lc));
+    if (!(err == err) || !(gmax < 1e300) || !(gmin > -1e300)) err = 1e301;      // NaN or infinite: "no finite point"
 #ifdef GR_PHASE_CLOCKS
     if (tid == 0 && evals <= 24) L.errlog[evals - 1] = err;
 #endif
     GR_CLK(L, 11);
-    // The fixed-point step log(target / routed) treats the routed mass as proportional to the
-    // weight; its true logarithmic derivative is (R - S) / R with S = w^2 int t ... (the share a
-    // token loses to itself), so the step of each coordinate is stretched by R / (R - S), at most
-    // `cap`.  The stretched iteration is no longer monotone: when kStall iterations bring no
-    // better point it returns to the best one with half the cap; at cap 1 (the plain step, whose
-    // stopping measure need not fall at every step) it is left alone.
-    double f[2], ratio[2];
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        f[u] = on[u] ? g[u] + lc : 0.0;
-        const double d = R[u] - S[u];
-        ratio[u] = (on[u] && d > 0.0) ? fmin(R[u] * fast_rcp(d), 1e30) : (on[u] ? 1e30 : 1.0);
-    }
-    // A token whose target nearly exhausts P = Pr[token drawn] (in the targets' units) can saturate: its routed mass
-    // hardly answers to its weight, log(target / R) flattens out and the stretched step crawls (the start weights
-    // leave such a token at log 2 from its target, and every other token has settled long before it has).  What is
-    // linear in its log weight there is the log odds R / (P - R) (the single-draft rule is their fixed point), so
-    // while the iteration is far from its end such a token steps by the difference of the log odds instead, the
-    // stretch changing with it: d log(R / (P - R)) = (R - S) / R * P / (P - R) d log w.  The tokens are chosen once,
-    // at the program's first evaluation (a token that starts near its target is better off with the plain form,
-    // and a form that changes from one iteration to the next spoils the mixing); below kOddsUntil the plain form
-    // takes over for good: the factor P / (P - R) would amplify the error of the quadrature.
-    int odds = st.odds;                                // 0: off, 1: on, 2: on and some token of this program steps on its odds
-    if (odds && err < kOddsUntil) odds = 0;
-    if (odds) {
-        bool sel[2]; double P[2] = {1.0, 1.0}, tg[2] = {0.0, 0.0};
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            if (on[u]) { P[u] = L.apd[tk[u]]; tg[u] = L.at[tk[u]]; }
-            if (it == 1 && on[u]) L.aodds[tk[u]] = (tg[u] > kOddsFrom * P[u] && tg[u] < kOddsTo * P[u] && fabs(f[u]) > kOddsFirst) ? 1 : 0;
-            sel[u] = on[u] && L.aodds[on[u] ? tk[u] : 0] != 0 && R[u] < P[u];
-        }
-        const bool some = __any(sel[0] || sel[1]);
-        if (it == 1) odds = some ? 2 : 0;              // a program without such a token never looks again
-        if (some) {
-#pragma unroll
-            for (int u = 0; u < 2; ++u) if (sel[u]) {
-                const double room = P[u] - R[u];
-                f[u] += fast_log(room * fast_rcp(P[u] - tg[u]));
-                ratio[u] = fmax(ratio[u] * room * fast_rcp(P[u]), 1.0);
-            }
-        }
-    }
-    bool stop = false;
-    if (err <= rel_tol) {
-        if (lane == 0) L.ctl_result = 0;
-        stop = true;
-    } else if (!(err < 1e300) || err > 100.0 * best_err) {
-        // a mixed step went astray: back to the best point, unmixed steps for a while
-        if (!(best_err < 1e300)) stop = true;          // no finite point seen: give up on this program
-#pragma unroll
-        for (int u = 0; u < 2; ++u) if (on[u]) { al[u] = L.aBest[tk[u]]; f[u] = L.fBest[tk[u]]; ratio[u] = L.rBest[tk[u]]; }
-        hcount = 0; plain = 20; since = 0;
-    } else if (err < best_err) {
-        best_err = err; since = 0;
-#pragma unroll
-        for (int u = 0; u < 2; ++u) if (on[u]) { L.aBest[tk[u]] = al[u]; L.fBest[tk[u]] = f[u]; L.rBest[tk[u]] = ratio[u]; }
-    } else if (cap > 1.0 && ++since >= kStall) {
-#pragma unroll
-        for (int u = 0; u < 2; ++u) if (on[u]) { al[u] = L.aBest[tk[u]]; f[u] = L.fBest[tk[u]]; ratio[u] = L.rBest[tk[u]]; }
-        hcount = 0; since = 0;
-        cap = fmax(1.0, 0.5 * cap);
-    }
-    if (stop) {
-        if (lane == 0) { L.ctl_go = 0; L.ctl_bestok = best_err < 1e300 ? 1 : 0; }
+    const bool astray = !(err < 1e300) || err > 100.0 * st.best_err;
+    if (err <= rel_tol || (astray && (!(st.best_err < 1e300) || st.retreats >= kRetreats))) {
+        if (lane == 0) { L.ctl_go = 0; L.ctl_bestok = st.best_err < 1e300 ? 1 : 0; if (err <= rel_tol) L.ctl_result = 0; }
         return st;
     }
+    const bool better = err < st.best_err;
+    if (astray) {
+        // back to the best point, with half the step that was last taken from it
+        ++st.retreats; st.havePrev = 0;
 #pragma unroll
-    for (int u = 0; u < 2; ++u) f[u] *= fmin(ratio[u], cap);
-    GR_CLK(L, 16);
-    const int cur = it % kHist;
-    const int navail = min(hcount, kCols);             // stored vectors since the history was last dropped
-    const int ncol = plain > 0 ? 0 : navail;
-    if (plain > 0) --plain;
-    // inner products of the new residual vector with itself and the stored ones, and the longest plain step
-    double hf[kCols][2], ha[kCols][2];
-    double ex[kHist + 1];
-    ex[0] = f[0] * f[0] + f[1] * f[1];
-    ex[kHist] = fmax(fabs(f[0]), fabs(f[1]));
+        for (int u = 0; u < 2; ++u) if (on[u]) { al[u] = L.aBest[tk[u]]; f[u] = 0.5 * L.fBest[tk[u]]; L.fBest[tk[u]] = f[u]; }
+    } else {
+        st.since = better ? 0 : st.since + 1;
+        const double R0 = L.aR0, total = rsum + R0, mass = tsum + slack_target;
+        const double inv = fast_rcp(mass), over = (total - mass) * inv, rho = 1.0 + over, share = fast_rcp(total);
+        const double lrho = over * (1.0 - 0.5 * over);         // the masses sum to the tuples' mass, up to the quadrature's error
+        // What a token's mass lacks, in a form that is nearly linear in its log weight: target - R below the target (there R
+        // grows at most in proportion to the weight), R log(target / R) above it.  A target that takes more than half of
+        // P = Pr[token drawn] saturates: R / (P - R) is what its weight moves (the single-draft rule), so its log odds set the
+        // aim while that is the longer way.
+        double rhs[2] = {0.0, 0.0};
 #pragma unroll
-    for (int c = 0; c < kCols; ++c) {
-        const int slot = (cur - 1 - c + 2 * kHist) % kHist;
+        for (int u = 0; u < 2; ++u) if (on[u]) {
+            const double tr = L.at[tk[u]] * rho, lg = g[u] + lrho, P = L.apd[tk[u]];
+            rhs[u] = lg > 0.0 ? tr - R[u] : R[u] * lg;
+            const double room = P - R[u];
+            if (u == 0 && lg > 0.0 && tr > kOddsFrom * P && room > 0.0)      // such a token is among the first
+                rhs[u] = fmax(rhs[u], R[u] * room * fast_rcp(P) * (lg + fast_log(room * fast_rcp(fmax(P - tr, 1e-5 * P)))));
+        }
+        double rhs0 = 0.0;
+        if (slack) { const double t0 = slack_target * rho, l0 = lrho - L.alc; rhs0 = l0 > 0.0 ? t0 - R0 : R0 * l0; }
+        const double lack = (wave_sum(rhs[0] + rhs[1]) + rhs0) * share;       // the sum of a Laplacian's right-hand side is 0
+        rhs0 = (rhs0 - lack * R0) * inv;
+        // the tokens' rows: couplings to the kStar (in place), to the slack, what is left (light tokens), right-hand side, 1 / sum
+        float wr[2][kRowW];
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            hf[c][u] = (on[u] && c < navail) ? L.Hf[slot][tk[u]] : 0.0;
-            ha[c][u] = (on[u] && c < navail) ? L.Ha[slot][tk[u]] : 0.0;
-        }
-        ex[1 + c] = f[0] * hf[c][0] + f[1] * hf[c][1];
-    }
-    wave_reduce_many<kHist + 1>(ex, {kOpSum, kOpSum, kOpSum, kOpSum, kOpSum, kOpMax});
-    GR_CLK(L, 17);
-    double stepv[2] = {f[0], f[1]};
-    if (ncol >= 1) {
-        // normal equations of  min || f - dF gamma ||  with dF_c = f - f_c:  <dF_a, dF_b> and <dF_a, f> from the
-        // inner products (the new vector's are in ex, the older ones in L.pm: lane 4a + b fetches entry (a, b));
-        // Gaussian elimination without pivoting (symmetric positive definite after the ridge), in registers
-        double old;
-        {
-            const int la = (lane >> 2) & 3, lb = lane & 3;
-            old = L.pm[(cur - 1 - la + 2 * kHist) % kHist][(cur - 1 - lb + 2 * kHist) % kHist];
-        }
-        double Gm[kCols][kCols + 1];
+            if (u == 1 && !two) continue;
 #pragma unroll
-        for (int a2 = 0; a2 < kCols; ++a2) {
-#pragma unroll
-            for (int b2 = 0; b2 < kCols; ++b2) Gm[a2][b2] = (ex[0] - ex[1 + a2]) - (ex[1 + b2] - read_lane(old, 4 * a2 + b2));
-            Gm[a2][kCols] = ex[0] - ex[1 + a2];
-        }
-        bool good = true;
-        double pivinv[kCols];
-#pragma unroll
-        for (int c = 0; c < kCols; ++c) pivinv[c] = 0.0;
-#pragma unroll
-        for (int c = 0; c < kCols; ++c) {
-            if (c < ncol) {
-                // a ridge relative to the column itself: recent columns are far shorter than old ones
-                Gm[c][c] = Gm[c][c] * (1.0 + 1e-10) + 1e-300;
-                good = good && (Gm[c][c] > 0.0);
-                double inv = __builtin_amdgcn_rcp(Gm[c][c]);          // reciprocal: two Newton steps from the hardware estimate
-                inv = inv * fma(-Gm[c][c], inv, 2.0);
-                inv = inv * fma(-Gm[c][c], inv, 2.0);
-                pivinv[c] = inv;
-#pragma unroll
-                for (int r = c + 1; r < kCols; ++r) {
-                    if (r < ncol) {
-                        const double fct = Gm[r][c] * inv;
-#pragma unroll
-                        for (int jc = c + 1; jc <= kCols; ++jc) Gm[r][jc] = fma(-fct, Gm[c][jc], Gm[r][jc]);
-                    }
+            for (int c = 0; c < kRowW; ++c) wr[u][c] = 0.f;
+            if (on[u]) {
+                rhs[u] = (rhs[u] - lack * R[u]) * inv;
+                const float4 c0 = *reinterpret_cast<const float4*>(&L.W[tk[u]][0]), c1 = *reinterpret_cast<const float4*>(&L.W[tk[u]][4]);
+                wr[u][0] = c0.x; wr[u][1] = c0.y; wr[u][2] = c0.z; wr[u][3] = c0.w;
+                wr[u][4] = c1.x; wr[u][5] = c1.y; wr[u][6] = c1.z; wr[u][7] = c1.w;
+                wr[u][8] = L.W[tk[u]][8];
+                const float known = ((c0.x + c0.y) + (c0.z + c0.w)) + ((c1.x + c1.y) + (c1.z + c1.w)) + wr[u][8];
+                wr[u][10] = static_cast<float>(rhs[u]);
+                if (tk[u] >= kStar) {
+                    wr[u][9] = fmaxf(static_cast<float>((R[u] - S[u]) * inv) - known, 0.f);
+                    const float d = known + wr[u][9];
+                    wr[u][11] = d > 0.f ? __builtin_amdgcn_rcpf(d) : 0.f;
                 }
             }
+            if (tk[u] < max(m, kStar)) {
+#pragma unroll
+                for (int c = 0; c < kRowW; c += 4) *reinterpret_cast<float4*>(&L.W[tk[u]][c]) = make_float4(wr[u][c], wr[u][c + 1], wr[u][c + 2], wr[u][c + 3]);
+            }
         }
-        double gam[kCols];
+        wave_lds_sync();
+        GR_CLK(L, 16);
+        // sum over the light tokens of W_i W_i^T / d_i, and of W_i rhs_i / d_i in column 10: lane = (vertex, token of a group of four)
+        {
+            const int c = lane & 15, g4 = lane >> 4, cc = c < kRowW ? c : kRowW - 1;
+            f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+            for (int t0 = kStar; t0 < m; t0 += 32) {            // eight groups of four: their loads first, they are all that takes time
+                float w[8], d[8];
 #pragma unroll
-        for (int c = kCols - 1; c >= 0; --c) {
-            double sacc = Gm[c][kCols];
+                for (int r = 0; r < 8; ++r) {
+                    const int t = min(t0 + 4 * r + g4, kMaxT - 1);
+                    w[r] = L.W[t][cc]; d[r] = L.W[t][kRowW - 1];
+                }
 #pragma unroll
-            for (int jc = c + 1; jc < kCols; ++jc) if (jc < ncol) sacc = fma(-Gm[c][jc], gam[jc], sacc);
-            gam[c] = (c < ncol) ? sacc * pivinv[c] : 0.0;
+                for (int r = 0; r < 8; ++r) {
+                    const bool in = t0 + 4 * r + g4 < m;
+                    acc[r & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(in && c < kNodes ? w[r] : 0.f, in && c <= kNodes ? w[r] * d[r] : 0.f, acc[r & 1], 0, 0, 0);
+                }
+            }
+            *reinterpret_cast<float4*>(&L.Am[c][4 * g4]) = make_float4(acc[0][0] + acc[1][0], acc[0][1] + acc[1][1], acc[0][2] + acc[1][2], acc[0][3] + acc[1][3]);
         }
-        double gnorm = 0.0;
+        wave_lds_sync();
+        GR_CLK(L, 17);
+        // lane i < 10 holds row i of the remaining vertices: their own edges and what the light tokens left
+        float dl[kNodes];
+        {
+            const int i = min(lane, kNodes - 1);
+            float a[kNodes], r1 = L.Am[kNodes][i];
 #pragma unroll
-        for (int c = 0; c < kCols; ++c) gnorm += fabs(gam[c]);
-        const bool solved = good && gnorm < 1e300;
-        double cand[2] = {f[0], f[1]};
+            for (int k = 0; k < kNodes; ++k) a[k] = L.Am[i][k];
+            if (lane < kStar) {
 #pragma unroll
-        for (int c = 0; c < kCols; ++c)
+                for (int k = 0; k <= kStar; ++k) a[k] += wr[0][k];
+                r1 += wr[0][10];
+            } else if (lane == kStar) {
 #pragma unroll
-            for (int u = 0; u < 2; ++u) if (c < ncol) cand[u] -= ((al[u] - ha[c][u]) + (f[u] - hf[c][u])) * gam[c];
-        const double cmax = wave_max(fmax(on[0] ? fabs(cand[0]) : 0.0, on[1] ? fabs(cand[1]) : 0.0));
-        // a mixed step longer than 3 in log weight is cut to that length (the same cap as the
-        // Newton fallback); a failed solve drops the history
-        if (solved && cmax < 1e300) {
-            const double cut = cmax > 3.0 ? 3.0 * fast_rcp(cmax) : 1.0;
-            stepv[0] = cand[0] * cut; stepv[1] = cand[1] * cut;
-        } else hcount = 0;
-    } else {                                           // a plain step: the same cap on its length
-        const double fmx = ex[kHist];
-        if (fmx > 3.0) { const double cut = 3.0 * fast_rcp(fmx); stepv[0] = f[0] * cut; stepv[1] = f[1] * cut; }
-    }
-    GR_CLK(L, 20);
-    // the new vector takes slot `cur` of the history (its inner products are read again next iteration)
-    if (lane <= kCols) {
-        const int slot = lane == 0 ? cur : (cur - lane + 2 * kHist) % kHist;
-        double val = ex[0];                             // ex[lane] without indexing registers by a variable
+                for (int k = 0; k < kStar; ++k) a[k] += L.W[k][kStar];
+                r1 += static_cast<float>(rhs0);
+            }
+            float e[kNodes][kNodes], c[kNodes];
 #pragma unroll
-        for (int c = 1; c <= kCols; ++c) if (lane == c) val = c - 1 < navail ? ex[c] : 0.0;
-        L.pm[cur][slot] = val; L.pm[slot][cur] = val;
+            for (int k = kNodes - 1; k >= 1; --k) {
+                float ak[kNodes], s = 0.f;
+#pragma unroll
+                for (int x = 0; x < k; ++x) { ak[x] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(a[x]), k)); s += ak[x]; }
+                const float rk = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(r1), k));
+                const float is = s > 0.f ? __builtin_amdgcn_rcpf(s) : 0.f, fac = a[k] * is;
+                c[k] = rk * is;
+                r1 = fmaf(fac, rk, r1);
+#pragma unroll
+                for (int x = 0; x < k; ++x) { e[k][x] = ak[x] * is; a[x] = fmaf(fac, ak[x], a[x]); }
+            }
+            dl[0] = 0.f;
+#pragma unroll
+            for (int k = 1; k < kNodes; ++k) {
+                float v = c[k];
+#pragma unroll
+                for (int x = 1; x < k; ++x) v = fmaf(e[k][x], dl[x], v);
+                dl[k] = v;
+            }
+        }
+        GR_CLK(L, 20);
+        const float base = slack ? dl[kStar] : 0.f;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) if (on[u]) {
+            float v = wr[u][10];
+#pragma unroll
+            for (int c = 0; c < kNodes; ++c) v = fmaf(wr[u][c], dl[c], v);
+            v *= wr[u][11];
+            if (u == 0) {
+#pragma unroll
+                for (int c = 0; c < kStar; ++c) v = lane == c ? dl[c] : v;
+            }
+            f[u] = static_cast<double>(v - base);
+        }
+        // A few programs are left with a linear rate by what the hub stands for: near the end a step is combined with the one
+        // before it (one secant pair).
+        if (err < kSecantBelow) {
+            if (st.havePrev) {
+                double df[2] = {0.0, 0.0}, da[2] = {0.0, 0.0};
+#pragma unroll
+                for (int u = 0; u < 2; ++u) if (on[u]) { df[u] = f[u] - L.fPrev[tk[u]]; da[u] = al[u] - L.aPrev[tk[u]]; }
+                double v[2] = {df[0] * f[0] + df[1] * f[1], df[0] * df[0] + df[1] * df[1]};
+                wave_reduce_many<2>(v, {kOpSum, kOpSum});
+                const double gam = v[1] > 0.0 ? v[0] * fast_rcp(v[1]) : 0.0;
+#pragma unroll
+                for (int u = 0; u < 2; ++u) if (on[u]) { L.aPrev[tk[u]] = al[u]; L.fPrev[tk[u]] = f[u]; f[u] -= (da[u] + df[u]) * gam; }
+            } else {
+#pragma unroll
+                for (int u = 0; u < 2; ++u) if (on[u]) { L.aPrev[tk[u]] = al[u]; L.fPrev[tk[u]] = f[u]; }
+                st.havePrev = 1;
+            }
+        }
+        double longest = wave_max(fmax(fabs(f[0]), fabs(f[1])));
+        if (st.since >= kStall || !(longest < 1e300)) {     // the fixed-point step, which lowers the objective whatever the point
+#pragma unroll
+            for (int u = 0; u < 2; ++u) f[u] = on[u] ? g[u] + lc : 0.0;
+            longest = err; st.since = 0; st.havePrev = 0;
+        }
+        const double cut = longest > kClip ? kClip * fast_rcp(longest) : 1.0;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            f[u] *= cut;
+            if (better && on[u]) { L.aBest[tk[u]] = al[u]; L.fBest[tk[u]] = f[u]; }
+        }
+        if (better) st.best_err = err;
     }
     double ws = 0.0, wm = 1e300, amax = -1e300;
 #pragma unroll
-    for (int u = 0; u < 2; ++u) if (on[u]) {
-        L.Ha[cur][tk[u]] = al[u]; L.Hf[cur][tk[u]] = f[u];
-        al[u] += stepv[u];
-        amax = fmax(amax, al[u]);
-    }
+    for (int u = 0; u < 2; ++u) if (on[u]) { al[u] += f[u]; amax = fmax(amax, al[u]); }
     if (!slack) amax = wave_max(amax); else amax = 0.0;   // without slack only differences of log weights matter
 #pragma unroll
     for (int u = 0; u < 2; ++u) if (on[u]) {
@@ -1070,22 +1352,22 @@ __device__ __attribute__((noinline)) MixState mix_step(MixState st, Grid gr, int
     }
     ws = wave_sum(ws); wm = wave_min(wm);
     if (lane == 0) {
-        L.ctl_grid = make_grid(slack, ctx, ws, wm, kQuadStep); L.ctl_bestok = best_err < 1e300 ? 1 : 0;
+        L.ctl_grid = make_grid(slack, ctx, ws, wm, kQuadStep); L.ctl_bestok = st.best_err < 1e300 ? 1 : 0;
+        L.ctl_couple = err < kKeepBelow ? 0 : 1;
     }
-    ++hcount;
-    st.hcount = hcount; st.plain = plain; st.since = since; st.odds = odds; st.best_err = best_err; st.cap = cap;
     GR_CLK(L, 12);
     return st;
 }
 
-// Solve one program by iterative scaling with Anderson mixing.  Returns 0 when converged.
-// In: L.aq, L.at (targets, already scaled to the tuple mass), L.aal (start log weights), each written by the
-// thread of its token; qsum = sum aq, tsum = sum at.
-// Out: L.aal.  `evals` counts evaluator calls (summed over the row's programs; max_iter caps this program's).
+// Solve one program by Newton's iteration with a reduced Hessian (newton_step).  Returns 0 when converged.
+// In: L.aq (decreasing), L.at (targets, already scaled to the tuple mass), L.aal (start log weights) and L.apos, the first three
+// written by the thread of their token; qsum = sum aq, tsum = sum at.
+// Out: L.aal, L.apos, in the program's own order of tokens.  `evals` counts evaluator calls (summed over the row's programs;
+// max_iter caps this program's).
 template <int D>
 __device__ __forceinline__ int solve_program(Lds<D>& L, int& par, double* newton_ws, int m, int n, double ctx, int slack, double slack_target,
                              double qsum, double tsum, double rel_tol, int max_iter, int* evals) {
-    constexpr int kSW = Lds<D>::kSW;
+    constexpr int kST = Lds<D>::kST;
     const int tid = threadIdx.x;
     const int evals0 = *evals;
     if (n == 1) {
@@ -1103,21 +1385,53 @@ __device__ __forceinline__ int solve_program(Lds<D>& L, int& par, double* newton
         return wg_sum(L, par, static_cast<double>(stuck)) > 0.0 ? 1 : 0;
     }
     const double atot = ctx + qsum;
-    int heavy = 0, full = 0;
+    const int wvi = tid >> 6, lane = tid & 63;
+    double q = 0.0;
+    int me = tid, heavy = 0;
+    if (tid < m) {
+        q = L.aq[tid];
+        // With more than 8 drafts the cumulant series of a token that dominates the draw mass loses digits to
+        // cancellation: the (at most three) tokens above kHeavyShare keep their exact factor instead.
+        heavy = (D > 8 && q > kHeavyShare * atot) ? 1 : 0;
+    }
+    if (m > kStar) {
+        // the heavy tokens, then those of largest target, to the front: the kStar tokens whose couplings the steps know
+        double t = 0.0, al = 0.0;
+        int pos = 0;
+        if (tid < m) { t = L.at[tid]; al = L.aal[tid]; pos = L.apos[tid]; L.nused[tid] = static_cast<int>(heavy ? 0x7F800000u - tid : (__float_as_uint(static_cast<float>(t)) & ~127u) | (127u - tid)); }
+        __syncthreads();
+        if (wvi == 0) {
+            unsigned k0 = lane < m ? static_cast<unsigned>(L.nused[lane]) : 0u, k1 = lane + 64 < m ? static_cast<unsigned>(L.nused[lane + 64]) : 0u;
+#pragma unroll
+            for (int r = 0; r < kStar; ++r) {
+                const unsigned top = wave_max_u(max(k0, k1));
+                const unsigned long long h0 = __ballot(k0 == top), h1 = __ballot(k1 == top);
+                const int at = h0 ? __ffsll(static_cast<long long>(h0)) - 1 : 63 + __ffsll(static_cast<long long>(h1));
+                if (lane == 0) L.star[r] = at;
+                if (at == lane) k0 = 0u;
+                if (at == lane + 64) k1 = 0u;
+            }
+        }
+        __syncthreads();
+        if (tid < m) {
+            int before = 0, place = -1;
+#pragma unroll
+            for (int r = 0; r < kStar; ++r) { const int x = L.star[r]; before += x < tid; if (x == tid) place = r; }
+            me = place >= 0 ? place : tid + kStar - before;
+            L.aq[me] = q; L.at[me] = t; L.aal[me] = al; L.apos[me] = pos;
+        }
+    }
+    int full = 0;
     if (tid < m) {
         // per-token series of e^{zq}: q^k / k! for k <= n (terms beyond z^n never reach the z^n coefficient)
-        const double q = L.aq[tid];
         double e = 1.0;
 #pragma unroll
         for (int a = 1; a <= D; ++a) {
             e = e * q * (1.0 / a);
-            L.trec[tid].e[a - 1] = a <= n ? e : 0.0;
+            L.trec[me].e[a - 1] = a <= n ? e : 0.0;
         }
-        L.trec[tid].pad = 0.0;
-        L.apd[tid] = pow_diff(atot, q, n);
-        // With more than 8 drafts the cumulant series of a token that dominates the draw mass loses digits to
-        // cancellation: the (at most three) tokens above kHeavyShare keep their exact factor instead.
-        heavy = (D > 8 && q > kHeavyShare * atot) ? 1 : 0;
+        L.trec[me].pad = 0.0;
+        L.apd[me] = pow_diff(atot, q, n);
         // A token needs only four cumulants when the u^5 and later terms of its factor cannot change the z^n
         // coefficient by more than 1e-11 relative: C(n-1, 4) (q/atot)^4 / 5 < 1e-11 (always, up to four drafts).
         const double r = q / atot;
@@ -1133,29 +1447,28 @@ __device__ __forceinline__ int solve_program(Lds<D>& L, int& par, double* newton
         for (int a = 0; a < D; ++a) z.e[a] = 0.0;
     }
     if (D > 4) {
-        // tokens are in decreasing q: the heavy ones are the first nh, those with all cumulants the first nf
-        double a[2] = {wave_sum(static_cast<double>(heavy)), wave_sum(static_cast<double>(full))};
-        wg_reduce<2>(L, par, a, {kOpSum, kOpSum});
-        const int nh = static_cast<int>(a[0]), nf = static_cast<int>(a[1]);
-        if (tid == 0) { L.nheavy = nh < kMaxHeavy ? nh : kMaxHeavy; L.nfull = nf > L.nheavy ? nf : L.nheavy; }
+        // the heavy tokens are the first nh; behind the kStar tokens come the others in decreasing q, those with all cumulants first
+        double a[3] = {wave_sum(static_cast<double>(heavy)), wave_sum(static_cast<double>(full)), wave_sum(static_cast<double>(full && me >= kStar))};
+        wg_reduce<3>(L, par, a, {kOpSum, kOpSum, kOpSum});
+        const int nh = static_cast<int>(a[0]), nf = static_cast<int>(a[1]), rest = static_cast<int>(a[2]);
+        if (tid == 0) { L.nheavy = nh < kMaxHeavy ? nh : kMaxHeavy; L.nfull = nf == 0 ? L.nheavy : min(m, kStar) + rest; }
     }
     __syncthreads();
     GR_CLK(L, 5);
     double fact = 1.0;
     for (int i = 2; i <= n; ++i) fact *= i;
-    const int mix_iters = (max_iter > kMixBudget + m) ? kMixBudget + m : max_iter;
-    const int wvi = tid >> 6, lane = tid & 63;
+    const int step_iters = (max_iter > kStarBudget + m) ? kStarBudget + m : max_iter;
     // The iteration is steered by wave 0 alone (lane l holds tokens l and l + 64, so every reduction over the
-    // tokens is a wave reduction and the mixing needs no workgroup exchange); all waves evaluate.  Per
-    // iteration: barrier, evaluation by all waves, barrier, mixing step by wave 0 (the others wait at the next
+    // tokens is a wave reduction and the step needs no workgroup exchange); all waves evaluate.  Per
+    // iteration: barrier, evaluation by all waves, barrier, the waves' sums, barrier, the step by wave 0 (the others wait at the next
     // barrier).  Wave 0 hands over through L.ctl_*: whether to go on, and the quadrature grid of the new weights.
-    // Wave-0 state: uniform scalars in registers, per-token values in LDS (L.aal, L.at, the best point, the last
-    // kHist iterates and stretched residuals by slot, L.pm = inner products of the stored residual vectors).
-    MixState st;
-    st.hcount = 0; st.plain = 0; st.since = 0; st.odds = 1; st.best_err = 1e300; st.cap = kStretch;
-    const int tk[2] = {lane, lane + 64};
-    const bool on[2] = {wvi == 0 && tk[0] < m, wvi == 0 && tk[1] < m};
+    // Wave-0 state: uniform scalars in registers, per-token values in LDS (L.aal, L.at, the best point and the last one, each with
+    // its step).
+    StepState st;
+    st.since = 0; st.retreats = 0; st.havePrev = 0; st.best_err = 1e300;
     if (wvi == 0) {
+        const int tk[2] = {lane, lane + 64};
+        const bool on[2] = {tk[0] < m, tk[1] < m};
         double ws = 0.0, wm = 1e300, amax = -1e300;
         if (!slack) {
 #pragma unroll
@@ -1169,43 +1482,54 @@ __device__ __forceinline__ int solve_program(Lds<D>& L, int& par, double* newton
             L.aal[tk[u]] = al; L.trec[tk[u]].aw = w; ws += w; wm = fmin(wm, w);
         }
         ws = wave_sum(ws); wm = wave_min(wm);
-        if (lane == 0) { L.ctl_go = 1; L.ctl_result = 1; L.ctl_bestok = 0; L.ctl_grid = make_grid(slack, ctx, ws, wm, kQuadStep); }
+        if (lane == 0) { L.ctl_go = 1; L.ctl_result = 1; L.ctl_bestok = 0; L.ctl_couple = 1; L.ctl_grid = make_grid(slack, ctx, ws, wm, kQuadStep); }
     }
-    for (int it = 1; it <= mix_iters; ++it) {
+    const double inv_mass = fast_rcp(tsum + slack_target);
+    for (int it = 1; it <= step_iters; ++it) {
         __syncthreads();                                   // the weights and L.ctl of this iteration are in place
         if (!L.ctl_go) break;
         const Grid gr = L.ctl_grid;
-        eval_core<D>(L, gr, m, n, ctx, slack);
+        const bool couple = L.ctl_couple != 0;
+        eval_core<D>(L, gr, m, n, ctx, slack, couple);
         *evals += 1;
         __syncthreads();                                   // every wave's partial sums are in place
         GR_CLK(L, 10);
-        // one token per thread: its routed mass R, the companion S and log(target / R); one thread the slack mass.
-        // Done here by the first waves side by side, not by the mixing wave for two tokens per lane.
+        // one token per thread: the first two waves its routed mass R, the companion S and log(target / R), the next ones its
+        // couplings, one thread the slack mass.  Done here side by side, not by the stepping wave for two tokens per lane.
         if (tid < kMaxT) {                                 // the first two waves, whole
-            double R = 0.0, S = 0.0, g = 0.0;
+            double R = 0.0, g = 0.0;
             if (tid < m) {
-                token_sums<D>(L, gr, tid, fact, R, S);
+                const TokenSums ts = token_sums<D>(L, gr, tid, fact);
+                R = ts.R;
                 g = fast_log(L.at[tid] * fast_rcp(R));
                 if (!(g == g)) g = 1e301;
-                L.aR[tid] = R; L.aS[tid] = S; L.ag[tid] = g;
+                L.aR[tid] = R; L.aS[tid] = ts.S; L.ag[tid] = g;
+                L.W[tid][kStar] = slack ? static_cast<float>(ts.b * inv_mass) : 0.f;
             }
             double a3[3] = {tid < m ? R : 0.0, tid < m ? g : -1e300, tid < m ? g : 1e300};
             wave_reduce_many<3>(a3, {kOpSum, kOpMax, kOpMin});
             if (lane == 0) { L.ared[wvi][0] = a3[0]; L.ared[wvi][1] = a3[1]; L.ared[wvi][2] = a3[2]; }
-        } else if (tid == kMaxT) {
-            const double R0 = slack_mass<D>(L, gr, n, atot, fact, slack);
-            L.aR0 = R0;
-            if (slack) L.alc = fast_log(R0 * fast_rcp(slack_target));
+        } else {
+            const int tok = tid & (kMaxT - 1), part = tid / kMaxT - 1;   // 256 threads: both halves by one of them
+            if (couple && tok < m && part < 2) {
+                token_couplings<D>(L, gr, tok, part, fact * inv_mass);
+                if (kST == 2 * kMaxT) token_couplings<D>(L, gr, tok, 1, fact * inv_mass);
+            }
+            if (tid == kST - 1) {
+                const double R0 = slack_mass<D>(L, gr, n, atot, fact, slack);
+                L.aR0 = R0;
+                if (slack) L.alc = fast_log(R0 * fast_rcp(slack_target));
+            }
         }
         __syncthreads();
         if (wvi != 0) continue;
-        st = mix_step<D>(st, gr, it, m, n, slack, ctx, slack_target, tsum, atot, fact, rel_tol, *evals);
+        st = newton_step<D>(st, m, n, slack, ctx, slack_target, tsum, rel_tol, *evals);
     }
     __syncthreads();
     int result = L.ctl_result;
     const bool bestok = L.ctl_bestok != 0;
     GR_CLK(L, 12);
-    if (result != 0 && mix_iters < max_iter && bestok) {
+    if (result != 0 && step_iters < max_iter && bestok) {
         if (tid < m) L.aal[tid] = L.aBest[tid];
         __syncthreads();
         result = newton_program<D>(L, par, newton_ws, m, n, ctx, slack, slack_target, qsum, tsum, fact, rel_tol, max_iter, evals, evals0);
