@@ -43,13 +43,17 @@ constexpr int KS = kMaxSupport;
 // Threads of the solve workgroup: eight waves (two per SIMD, 256 registers each) up to 8 drafts, so that one
 // wave's dependent float64 chains and LDS waits are filled by the other; four waves (one per SIMD, all 512
 // registers) for the longer series of 9 to 16 drafts.
-#ifndef GR_THREADS_UP_TO_8
-#define GR_THREADS_UP_TO_8 512
-#endif
-template <int D> constexpr int kThreadsOf = D > 8 ? 256 : GR_THREADS_UP_TO_8;
-constexpr double kQuadStep = 0.45;   // trapezoid step in log t (discretisation error ~1e-9 relative)
-constexpr double kQuadGrow = 1.5683121854901688;   // e^0.45
-constexpr double kQuadLo = 1e-4;     // t_lo * (slack + sum w): the part below t_lo is added in closed form
+template <int D> constexpr int kThreadsOf = D > 8 ? 256 : 512;
+constexpr double kQuadStep = 0.45;   // trapezoid step in log t (discretisation error 5.6e-9 relative at most)
+constexpr double kQuadLo = 0.1;      // t_lo * (slack + sum w)
+// The nodes below t_lo, t_lo e^{-step k}, are not evaluated: the integrand over t, a sum of e^{-s t} with s (slack + sum w)^-1
+// at most 1, is extrapolated from its value at 0 (kQuadZero) and at the first nodes (kQuadEnd, added to their weights in units of
+// t_lo): the sums over k >= 1 of step e^{-step k} times the Lagrange polynomials on 0, 1, e^step .. e^{4 step}.  Largest relative
+// error of 1/s over s: 6.1e-9, of which the trapezoid rule's own 5.6e-9; taking the integrand's value at 0 for all nodes below
+// t_lo = 1e-4, as was done before, 7.1e-9 with 16 nodes more.
+constexpr double kQuadZero = 0.307605450234338265;
+constexpr double kQuadEnd[5] = {1.01966774875832561, -0.714299827412849101, 0.202748276556553684, -0.0250005611332631344, 0.00109723308425186904};
+constexpr double kQuadPair = 1.198;  // weight of the first node of every other one for t^2: 1 + 1 / (e^{4 step} - 1)
 constexpr double kQuadHi = 25.0;     // t_hi * (slowest decay rate)
 constexpr int kStar = 8;             // tokens of a program whose couplings to every token are computed (the others meet in a hub)
 constexpr double kClip = 3.0;        // longest step in log weight
@@ -68,16 +72,16 @@ constexpr double kHeavyShare = 0.3;  // ... those above this share of the progra
 template <int D> struct alignas(16) TokRec { double aw; double e[D]; double pad; };     // weight; e[k-1] = q^k / k! (0 for k > n)
 template <int D> struct alignas(16) NodeRec { double t, qw; double Tr[D]; };            // abscissa, quadrature weight; Tr[k-1] = T_{n-k}
 
-// The quadrature grid of one evaluation: nodes t_lo e^{step j}, j = 0..N-1, and the closed-form sums over the
-// nodes below t_lo (x = 1 there) of the integral of 1 (tail) and of t (tail2).
-struct Grid { double t_lo, step, tail, tail2; int N; };
+// The quadrature grid of one evaluation: nodes t_lo e^{kQuadStep j}, j = 0..N-1, and the weight of the integrand's value at 0.
+struct Grid { double t_lo, tail; int N; };
 
 // D: the series degree of the kernel (>= n).
 template <int D>
 struct Lds {
     static constexpr int kST = kThreadsOf<D>;
     static constexpr int kSW = kST / 64;
-    static constexpr int kNPW = 64 / kSW;   // quadrature nodes a wave owns within a chunk of 64
+    static constexpr int kNPW = D > 8 ? 16 : 4;               // quadrature nodes a wave owns within a chunk
+    static constexpr int kChunk = kSW * kNPW;
     static constexpr int kSer = D < 4 ? 4 : D;                // floats of one series of hser ...
     static constexpr int kSerStride = kStar * kSer + 4;      // ... and of a node's kStar of them (padded: neighbouring nodes start four banks apart)
     // support, in ratio order
@@ -152,12 +156,13 @@ __device__ __forceinline__ void wave_reduce_many(double (&v)[NV], const int (&op
 }
 
 // v[j] holds this wave's partial result of operation op[j]; on return it holds the workgroup's.  After the
-// barrier lane l reads the partial of wave l mod NW (one LDS instruction per value and wave, not NW), and a
-// butterfly over NW neighbouring lanes combines them: every lane ends with the same bits.
+// barrier lane l reads the partial of wave l mod 4 or 16 (one LDS instruction per value and wave, not NW), and a
+// butterfly over that many neighbouring lanes combines them: every lane ends with the same bits.
 template <int NV, class LdsT>
 __device__ __forceinline__ void wg_reduce(LdsT& L, int& par, double (&v)[NV], const int (&op)[NV]) {
     constexpr int NW = LdsT::kSW;
-    static_assert(NW == 4 || NW == 8, "the butterfly below covers four or eight waves");
+    static_assert(NW <= 16, "the butterfly below covers up to sixteen waves");
+    constexpr int G = NW <= 4 ? 4 : 16;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     if (lane == 0) {
 #pragma unroll
@@ -166,10 +171,12 @@ __device__ __forceinline__ void wg_reduce(LdsT& L, int& par, double (&v)[NV], co
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
-        double r = L.red[par][lane & (NW - 1)][j];
+        const int w = lane & (G - 1);
+        double r = L.red[par][min(w, NW - 1)][j];
+        if (G != NW) r = w < NW ? r : (op[j] == kOpSum ? 0.0 : (op[j] == kOpMax ? -1e301 : 1e301));
         r = combine(r, dpp_move<kDppXor1>(r), op[j]);
         r = combine(r, dpp_move<kDppXor2>(r), op[j]);
-        if (NW == 8) r = combine(r, dpp_move<kDppHalfMirror>(r), op[j]);
+        if (G == 16) { r = combine(r, dpp_move<kDppHalfMirror>(r), op[j]); r = combine(r, dpp_move<kDppMirror>(r), op[j]); }
         v[j] = r;
     }
     par ^= 1;
@@ -443,30 +450,29 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_wave_barrier();
 }
 
-__device__ __forceinline__ Grid make_grid(int slack, double ctx, double wsum, double wmin, double step0) {
+__device__ __forceinline__ Grid make_grid(int slack, double ctx, double wsum, double wmin) {
     Grid g;
     g.t_lo = kQuadLo * fast_rcp(slack + wsum);
     const double lowest = slack + ((slack == 0 || ctx == 0.0) ? wmin : 0.0);
     const double range = fast_log((kQuadHi / kQuadLo) * (slack + wsum) * fast_rcp(lowest));
-    g.step = step0;
-    int N = static_cast<int>(ceil(range / g.step)) + 1;
-    if (step0 == kQuadStep && N > 64 && range <= 0.5 * 63.0) { g.step = range / 63.0; N = 64; }
-    if (N < 1) N = 1;
-    if (N > 4096) N = 4096;
-    g.N = N;
-    double geo = kQuadStep / (kQuadGrow - 1.0), geo2 = kQuadStep / (kQuadGrow * kQuadGrow - 1.0);
-    if (g.step != kQuadStep) { const double estep = exp(g.step); geo = g.step * fast_rcp(estep - 1.0); geo2 = g.step * fast_rcp(estep * estep - 1.0); }
-    g.tail = geo * g.t_lo;
-    g.tail2 = geo2 * g.t_lo * g.t_lo;
+    g.N = min(max(static_cast<int>(ceil(range / kQuadStep)) + 1, 1), 4096);
+    g.tail = kQuadZero * g.t_lo;
     return g;
+}
+// The weight of node j, at t, without the slack's e^{-slack t}.
+__device__ __forceinline__ double node_weight(int j, double t, double t_lo) {
+    double e = 0.0;
+#pragma unroll
+    for (int k = 0; k < 5; ++k) e = j == k ? kQuadEnd[k] : e;
+    return fma(e, t_lo, kQuadStep * t);
 }
 
 // The couplings C_ij = E[s_i s_j] (s_i = w_i / (slack + sum of the drawn tokens' w) for a drawn token, 0 otherwise) are
 // the off-diagonal entries of -dR_i / dalpha_j; with phi_i(z) = x_i (e^{zq_i} - 1) / (1 + x_i (e^{zq_i} - 1)),
 //     C_ij = w_i w_j n! int t e^{-slack t} [z^n] T phi_i phi_j dt.
 // They only steer the step, so they are taken in float32 and at every other node of the grid (the trapezoid rule with twice
-// the step is good to 1e-4), for the first kStar tokens j and every token i.  Two lanes share a node: lane k of the wave's
-// even nodes takes the tokens 0..3 of the kStar, its mirror lane (that of the odd neighbour) the tokens 4..7.
+// the step is good to 1e-4), for the first kStar tokens j and every token i.  Two lanes share a node: that of the
+// wave's even node takes the tokens 0..3 of the kStar, its partner (that of the odd neighbour) the tokens 4..7.
 // star_series: u[k-1] = weight * t w_j [z^{n-k}] (T phi_j) / k!, k = 1 .. D - 1, of one of the kStar tokens at one node; the
 // row of token i is then w_i n! sum over the nodes and k of x_i g_k(x_i) q_i^k u[k-1].  Tr[k-1] = T_{n-k}; e: the token's series.
 template <int D>
@@ -600,29 +606,33 @@ __device__ __forceinline__ double heavy_pair(const double (&T)[D + 1], const dou
 template <int D>
 __device__ __forceinline__ void star_phase(Lds<D>& L, int lane, int wv, int m, double t, bool more) {
     constexpr int NPW = Lds<D>::kNPW, NS = 64 / NPW, CC = D > 8 ? 2 : 1;
+    static_assert(NPW == 4 || NPW == 16, "the sums over a subset's node lanes below");
     const int j = lane & (NPW - 1), tsub = lane / NPW;
-    const bool upper = j >= NPW / 2, b0 = j & 1, b1 = j & 2, b2 = j & 4;
-    const double tm = dpp_move<NPW == 8 ? kDppHalfMirror : kDppMirror>(t);
+    const bool b0 = j & 1, b1 = j & 2, b2 = j & 4;
+    const bool upper = NPW == 4 ? b0 : j >= 8;
+    const double tm = dpp_move<NPW == 4 ? kDppXor1 : kDppMirror>(t);
     const double te = upper ? tm : t;                          // the pair's even node
     wave_lds_sync();
     float U[4][Lds<D>::kSer];
-    star_load<D>(U, &L.hser[wv][(upper ? NPW - 1 - j : j) * Lds<D>::kSerStride], upper);
-    float* out = &L.cpart[wv][tsub * kStar + (NPW == 8 ? j : (upper ? 4 : 0) + (b2 ? 2 : 0) + (b0 ? 1 : 0))];
+    star_load<D>(U, &L.hser[wv][(NPW == 4 ? j >> 1 : (upper ? 15 - j : j)) * Lds<D>::kSerStride], upper);
+    float* out = &L.cpart[wv][tsub * kStar + (upper ? 4 : 0) + (NPW == 4 ? (b1 ? 2 : 0) : (b2 ? 2 : 0) + (b0 ? 1 : 0))];
     auto row = [&](int i, auto all) {
         const TokRec<D>& rec = L.trec[NS * i + tsub];          // records beyond the last token: x = 0
         const float x = __expf(-static_cast<float>(fmin(te * rec.aw, 1000.0))), q = static_cast<float>(rec.e[0]);
-        float acc[4], c;
+        float acc[4];
         star_row<D, decltype(all)::value>(U, q, x, acc);
-        if constexpr (NPW == 8) {
-            const float r0 = part_add<kDppXor1>(acc[0], acc[1], b0), r1 = part_add<kDppXor1>(acc[2], acc[3], b0);
-            c = part_add<kDppXor2>(r0, r1, b1);
+        float* const at = out + i * NS * kStar;
+        if constexpr (NPW == 4) {
+            const float c0 = part_add<kDppXor2>(acc[0], acc[2], b1), c1 = part_add<kDppXor2>(acc[1], acc[3], b1);
+            float2* const p = reinterpret_cast<float2*>(at);
+            const float2 old = more ? *p : make_float2(0.f, 0.f);
+            *p = make_float2(old.x + c0, old.y + c1);
         } else {
             const float r0 = part_add<kDppHalfMirror>(acc[0], acc[2], b2), r1 = part_add<kDppHalfMirror>(acc[1], acc[3], b2);
-            c = part_add<kDppXor1>(r0, r1, b0);
+            float c = part_add<kDppXor1>(r0, r1, b0);
             c += dpp_f<kDppXor2>(c);
+            if (!b1) *at = more ? *at + c : c;
         }
-        float* const at = out + i * NS * kStar;
-        if (NPW == 8 || !b1) *at = more ? *at + c : c;
     };
     const int rows = (m + NS - 1) / NS;
     int i = 0;
@@ -654,7 +664,7 @@ __device__ __forceinline__ void eval_core_nodes(Lds<D>& L, const Grid& gr, int m
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int nheavy = (D > 8) ? L.nheavy : 0;
     const int nfull = (D > 4) ? L.nfull : nheavy;              // up to four drafts four cumulants are all there are
-    const double t_lo = gr.t_lo, step = gr.step;
+    const double t_lo = gr.t_lo;
     const int N = gr.N;
     static_assert(NPW == 16 && NS == 4, "phase 4 pairs the sixteen node lanes of a subset by a row mirror");
     for (int i = lane; i < m; i += 64) { L.rpart[wv][i] = 0.0; L.spart[wv][i] = 0.0; }
@@ -669,8 +679,9 @@ __device__ __forceinline__ void eval_core_nodes(Lds<D>& L, const Grid& gr, int m
         const int pairs = (nn + 1) >> 1, mine = (pairs - wv + kSW - 1) / kSW;
         const int npw = 2 * mine - ((nn & 1) && (pairs - 1) % kSW == wv ? 1 : 0);
         const int at = j < 8 ? 2 * j : 2 * (15 - j) + 1;
-        const double t = t_lo * exp(step * static_cast<double>(c0 + 2 * wv + 2 * kSW * (at >> 1) + (at & 1)));
-        const double qw = at < npw ? step * t * exp_neg(slack * t, L.e2tab) : 0.0;
+        const int node = c0 + 2 * wv + 2 * kSW * (at >> 1) + (at & 1);
+        const double t = t_lo * exp(kQuadStep * static_cast<double>(node));
+        const double es = at < npw ? exp_neg(slack * t, L.e2tab) : 0.0, qw = node_weight(node, t, t_lo) * es;
         // ---- phase 1: cumulant sums at node j of the tokens of subset tsub
         double K[D];
 #pragma unroll
@@ -737,12 +748,13 @@ __device__ __forceinline__ void eval_core_nodes(Lds<D>& L, const Grid& gr, int m
                 const float v = static_cast<float>(rec.Tr[b]), w = dpp_f<kDppMirror>(v);
                 Tr[b] = upper ? w : v;
             }
-            const double tm = dpp_move<kDppMirror>(t), qm = dpp_move<kDppMirror>(qw);       // not inside the selection: every lane must be active
-            const double te = upper ? tm : t, qe = upper ? qm : qw;
+            const double tq = 2.0 * kQuadStep * (node == 0 ? kQuadPair : 1.0) * t * es;
+            const double tm = dpp_move<kDppMirror>(t), qm = dpp_move<kDppMirror>(tq);       // not inside the selection: every lane must be active
+            const double te = upper ? tm : t, qe = upper ? qm : tq;
             const double tw = te * L.trec[a].aw;
             float* const out = &L.hser[wv][k * Lds<D>::kSerStride + a * Lds<D>::kSer];
-            if (a >= nheavy) star_series<D>(Tr, L.trec[a].e, tw, 2.0 * qe, __expf(-static_cast<float>(fmin(tw, 1000.0))), out);
-            else star_series_exact<D>(T, L.trec[a].e, tw, 2.0 * qe, exp_neg(tw, L.e2tab), n, out);
+            if (a >= nheavy) star_series<D>(Tr, L.trec[a].e, tw, qe, __expf(-static_cast<float>(fmin(tw, 1000.0))), out);
+            else star_series_exact<D>(T, L.trec[a].e, tw, qe, exp_neg(tw, L.e2tab), n, out);
             // the heavy tokens' couplings among themselves: one pair per token subset
             if (nheavy >= 2) {
                 const int pa = tsub == 2 ? 1 : 0, pb = tsub == 0 ? 1 : 2;
@@ -784,24 +796,24 @@ __device__ __forceinline__ void eval_core_nodes(Lds<D>& L, const Grid& gr, int m
 // series, which this lane already holds, and the token's q; it ends with a sum over the NPW neighbouring lanes that
 // hold the nodes of a subset.  No node records in LDS and no exchange between the phases.
 // Rows whose first token is below L.nfull take all D cumulants, the others four.
-// A wave owns eight neighbouring nodes, so that a grid of few nodes leaves whole waves (and their share of the SIMDs) out;
-// lanes 0..3 hold its even nodes in order, lanes 7..4 the odd ones, so that a half-row mirror pairs neighbours (star_series).
+// A wave owns four neighbouring nodes of a chunk of 32: most grids have 27 to 50 nodes, and the chunk behind the first is taken
+// by as many waves as it has nodes for.  Eight nodes a wave and chunks of 64 left no wave out and took 217 us where this takes 210
+// for a call of 256 rows of 128256 tokens (n = 8, k = 128), 660 and 634 for 1024 of them; 77 and 78 for 64 rows of 1024 (n = 4).
 // The first row's lanes hold the factors of the first kStar tokens: lane (node, tsub) takes the series of token tsub.
 template <int D>
 __device__ __forceinline__ void eval_core_rows(Lds<D>& L, const Grid& gr, int m_, int n_, double ctx, int slack_, bool couple) {
-    constexpr int kSW = Lds<D>::kSW, NPW = Lds<D>::kNPW, NS = 64 / NPW, NT = kMaxT / NS;
+    constexpr int NPW = Lds<D>::kNPW, NS = 64 / NPW, NT = kMaxT / NS;
     constexpr int CL = D < 4 ? D : 4;
-    static_assert(D <= 8 && NPW == 8 && NT % 2 == 0, "rows are taken two at a time; eight node lanes per subset");
+    static_assert(D <= 8 && NPW == 4 && NS >= kStar, "four node lanes per subset; the first row holds the kStar");
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     // the sizes are the same in every lane; said so, the row guards below are scalar branches, not lane masks
     const int m = __builtin_amdgcn_readfirstlane(m_), n = __builtin_amdgcn_readfirstlane(n_);
     const int slack = __builtin_amdgcn_readfirstlane(slack_);
     const int nfull = (D > 4) ? __builtin_amdgcn_readfirstlane(L.nfull) : 0;
-    const double t_lo = gr.t_lo, step = gr.step;
+    const double t_lo = gr.t_lo;
     const int N = __builtin_amdgcn_readfirstlane(gr.N);
     const int j = lane & (NPW - 1), tsub = lane / NPW;
-    const bool upper = j >= 4;                             // the odd nodes
-    static_assert(NS == kStar, "the first row of tokens are the kStar");
+    const bool odd = j & 1;
     double r0 = 0.0;                                       // slack integrand, lanes of token subset 0
     GR_CLK(L, 6);
 
@@ -809,39 +821,35 @@ __device__ __forceinline__ void eval_core_rows(Lds<D>& L, const Grid& gr, int m_
         for (int i = lane; i < m; i += 64) { L.rpart[wv][i] = 0.0; L.spart[wv][i] = 0.0; }
         if (couple) for (int i = lane; i < m * (kStar / 4); i += 64) *reinterpret_cast<float4*>(&L.cpart[wv][4 * i]) = make_float4(0.f, 0.f, 0.f, 0.f);
     }
-    for (int c0 = NPW * wv; c0 < N; c0 += 64) {             // this wave's first node of the chunk
-        const bool more = c0 >= 64;                         // its sums go on
-        const int node = c0 + (upper ? 15 - 2 * j : 2 * j);
-        const double t = t_lo * exp(step * static_cast<double>(node));
-        const double qw = node < N ? step * t * exp_neg(slack * t, L.e2tab) : 0.0;
+    for (int c0 = NPW * wv; c0 < N; c0 += Lds<D>::kChunk) {  // this wave's first node of the chunk
+        const bool more = c0 >= Lds<D>::kChunk;             // its sums go on
+        const int node = c0 + j;
+        const double t = t_lo * exp(kQuadStep * static_cast<double>(node));
+        const double es = node < N ? exp_neg(slack * t, L.e2tab) : 0.0, qw = node_weight(node, t, t_lo) * es;
         // ---- phase 1: cumulant sums at this lane's node over the tokens of its subset
         double K[D], xs[NT];
 #pragma unroll
         for (int k = 0; k < D; ++k) K[k] = 0.0;
-        // the weights of a pair of rows are requested one pair ahead: they head the longest chain (the exponential)
-        double awa = L.trec[tsub].aw, awb = L.trec[tsub + NS].aw;
+        // the weight of a row is requested one row ahead: it heads the longest chain (the exponential)
+        double aw = L.trec[tsub].aw;
 #pragma unroll
-        for (int i = 0; i < NT; i += 2) {
-            xs[i] = 0.0; xs[i + 1] = 0.0;
+        for (int i = 0; i < NT; ++i) {
+            xs[i] = 0.0;
             if (NS * i < m) {
-                const int a = NS * i + tsub, b = a + NS;
-                const TokRec<D>& ra = L.trec[a];               // the records behind the last token have x = 0
-                const TokRec<D>& rb = L.trec[b];
-                const double ya = t * awa, yb = t * awb;
-                if (i + 2 < NT) {
-                    awa = L.trec[b + NS].aw;
-                    awb = L.trec[b + 2 * NS].aw;
-                }
-                double x0, x1;
-                exp_neg2(ya, yb, L.e2tab, x0, x1);
-                if (D > 4 && NS * i < nfull) { phase1_token<D, D>(K, ra, x0); phase1_token<D, D>(K, rb, x1); }
-                else { phase1_token<D, CL>(K, ra, x0); phase1_token<D, CL>(K, rb, x1); }
-                xs[i] = x0; xs[i + 1] = x1;
+                const TokRec<D>& rec = L.trec[NS * i + tsub];  // the records behind the last token have x = 0
+                const double y = t * aw;
+                if (i + 1 < NT) aw = L.trec[NS * (i + 1) + tsub].aw;
+                const double x = exp_neg(y, L.e2tab);
+                if (D > 4 && NS * i < nfull) phase1_token<D, D>(K, rec, x);
+                else phase1_token<D, CL>(K, rec, x);
+                xs[i] = x;
             }
         }
+        // over the subsets: rotations within a row of sixteen lanes, then the four rows
 #pragma unroll
         for (int k = 0; k < D; ++k) {
-            if (NS >= 8) K[k] += __shfl_xor(K[k], 8);
+            K[k] += dpp_move<kDppRor8>(K[k]);
+            K[k] += dpp_move<kDppRor4>(K[k]);
             K[k] += __shfl_xor(K[k], 16);
             K[k] += __shfl_xor(K[k], 32);
         }
@@ -867,46 +875,40 @@ __device__ __forceinline__ void eval_core_rows(Lds<D>& L, const Grid& gr, int m_
             NodeRec<D> rec;
             const double tn = pick_series<D, D>(rec, T, n);
             if (tsub == 0) r0 = fma(qw, tn, r0);
-            float Tr[D];
+            if (couple) {
+                float Tr[D];
 #pragma unroll
-            for (int k = 0; k < D; ++k) Tr[k] = static_cast<float>(rec.Tr[k]);
-            if (couple && !upper)
-                star_series<D>(Tr, L.trec[tsub].e, t * L.trec[tsub].aw, 2.0 * qw, static_cast<float>(xs[0]),
-                               &L.hser[wv][j * Lds<D>::kSerStride + tsub * Lds<D>::kSer]);
+                for (int k = 0; k < D; ++k) Tr[k] = static_cast<float>(rec.Tr[k]);
+                if (!odd && tsub < kStar)
+                    star_series<D>(Tr, L.trec[tsub].e, t * L.trec[tsub].aw, 2.0 * kQuadStep * (node == 0 ? kQuadPair : 1.0) * t * es,
+                                   static_cast<float>(xs[0]), &L.hser[wv][(j >> 1) * Lds<D>::kSerStride + tsub * Lds<D>::kSer]);
+            }
             double invf = qw;
 #pragma unroll
             for (int k = 1; k <= D; ++k) { invf *= 1.0 / k; Tp[k - 1] = rec.Tr[k - 1] * invf; }
         }
         GR_CLK(L, 8);
         // ---- phase 3: the leave-one-out coefficient of every pair, summed over the nodes of the wave.  The sums over
-        // the eight node lanes of a subset: the first step (lane k with lane 7 - k) also parts the two sums, R to
-        // lanes 0-3 and its t-weighted companion S to lanes 4-7, so that the other two steps move one value, not two.
-        double qna = L.trec[tsub].e[0], qnb = L.trec[tsub + NS].e[0];
-        double* const part = upper ? &L.spart[wv][0] : &L.rpart[wv][0];
+        // the four node lanes of a subset: the first step (lane k with lane k ^ 1) also parts the two sums, R to
+        // the even lanes and its t-weighted companion S to the odd ones, so that the other step moves one value, not two.
+        double qn = L.trec[tsub].e[0];
+        double* const part = odd ? &L.spart[wv][0] : &L.rpart[wv][0];
 #pragma unroll
-        for (int i = 0; i < NT; i += 2) {
+        for (int i = 0; i < NT; ++i) {
             if (NS * i < m) {
-                const int a = NS * i + tsub, b = a + NS;            // b <= kMaxT - 1: sums of rows past the last token are 0
-                double olda = 0.0, oldb = 0.0;
-                if (more && (j & 3) == 0) { olda = part[a]; oldb = part[b]; }
-                const double qa = qna, qb = qnb;
-                if (i + 2 < NT) {
-                    qna = L.trec[b + NS].e[0];
-                    qnb = L.trec[b + 2 * NS].e[0];
-                }
-                const double x0 = xs[i], x1 = xs[i + 1];
-                const double v0 = fma(-x0, x0, x0), s0 = fma(-2.0, x0, 1.0), v1 = fma(-x1, x1, x1), s1 = fma(-2.0, x1, 1.0);
-                double ta = 0.0, tb = 0.0;
-                if (D > CL && NS * i < nfull) { ta = loo_top<D, CL>(Tp, qa, v0, s0); tb = loo_top<D, CL>(Tp, qb, v1, s1); }
-                const double ca = loo_low<D, CL>(Tp, qa, v0, s0, ta), cb = loo_low<D, CL>(Tp, qb, v1, s1, tb);
-                const double ra_ = xs[i] * ca, rb_ = xs[i + 1] * cb;
-                const double sa_ = ra_ * t, sb_ = rb_ * t;
-                double ka = upper ? sa_ : ra_, kb = upper ? sb_ : rb_;
-                ka += dpp_move<kDppHalfMirror>(upper ? ra_ : sa_);
-                kb += dpp_move<kDppHalfMirror>(upper ? rb_ : sb_);
-                ka += dpp_move<kDppXor1>(ka); kb += dpp_move<kDppXor1>(kb);
-                ka += dpp_move<kDppXor2>(ka); kb += dpp_move<kDppXor2>(kb);
-                if ((j & 3) == 0) { part[a] = olda + ka; part[b] = oldb + kb; }
+                const int a = NS * i + tsub;                        // a <= kMaxT - 1: the sums of places past the last token are 0
+                double old = 0.0;
+                if (more && j < 2) old = part[a];
+                const double q = qn;
+                if (i + 1 < NT) qn = L.trec[a + NS].e[0];
+                const double x = xs[i], v = fma(-x, x, x), s = fma(-2.0, x, 1.0);
+                double top = 0.0;
+                if (D > CL && NS * i < nfull) top = loo_top<D, CL>(Tp, q, v, s);
+                const double r_ = x * loo_low<D, CL>(Tp, q, v, s, top), s_ = r_ * t;
+                double k = odd ? s_ : r_;
+                k += dpp_move<kDppXor1>(odd ? r_ : s_);
+                k += dpp_move<kDppXor2>(k);
+                if (j < 2) part[a] = old + k;
             }
         }
         // ---- phase 4
@@ -933,7 +935,7 @@ template <int D>
 __device__ __forceinline__ TokenSums token_sums(const Lds<D>& L, const Grid& gr, int tok, double fact) {
     constexpr int kSW = Lds<D>::kSW;
     const double rfact = fast_rcp(fact);
-    double r = L.apd[tok] * gr.tail * rfact, sq = L.apd[tok] * gr.tail2 * rfact;
+    double r = L.apd[tok] * gr.tail * rfact, sq = 0.0;           // the integrand of S is 0 at t = 0
 #pragma unroll
     for (int w2 = 0; w2 < kSW; ++w2) {
         r += L.rpart[w2][tok]; sq += L.spart[w2][tok];
@@ -991,7 +993,7 @@ __device__ __forceinline__ Routed routed_eval(Lds<D>& L, int& par, int m, int n,
     if (tid < m) { w = exp(alpha); L.trec[tid].aw = w; }
     double a[2] = {wave_sum(tid < m ? w : 0.0), wave_min(tid < m ? w : 1e300)};
     wg_reduce<2>(L, par, a, {kOpSum, kOpMin});              // its barrier also publishes the weights
-    const Grid gr = make_grid(slack, ctx, a[0], a[1], kQuadStep);
+    const Grid gr = make_grid(slack, ctx, a[0], a[1]);
     eval_core<D>(L, gr, m, n, ctx, slack, false);
     __syncthreads();
     Routed out;
@@ -1352,7 +1354,7 @@ __device__ __attribute__((noinline)) StepState newton_step(StepState st, int m, 
     }
     ws = wave_sum(ws); wm = wave_min(wm);
     if (lane == 0) {
-        L.ctl_grid = make_grid(slack, ctx, ws, wm, kQuadStep); L.ctl_bestok = st.best_err < 1e300 ? 1 : 0;
+        L.ctl_grid = make_grid(slack, ctx, ws, wm); L.ctl_bestok = st.best_err < 1e300 ? 1 : 0;
         L.ctl_couple = err < kKeepBelow ? 0 : 1;
     }
     GR_CLK(L, 12);
@@ -1482,7 +1484,7 @@ __device__ __forceinline__ int solve_program(Lds<D>& L, int& par, double* newton
             L.aal[tk[u]] = al; L.trec[tk[u]].aw = w; ws += w; wm = fmin(wm, w);
         }
         ws = wave_sum(ws); wm = wave_min(wm);
-        if (lane == 0) { L.ctl_go = 1; L.ctl_result = 1; L.ctl_bestok = 0; L.ctl_couple = 1; L.ctl_grid = make_grid(slack, ctx, ws, wm, kQuadStep); }
+        if (lane == 0) { L.ctl_go = 1; L.ctl_result = 1; L.ctl_bestok = 0; L.ctl_couple = 1; L.ctl_grid = make_grid(slack, ctx, ws, wm); }
     }
     const double inv_mass = fast_rcp(tsum + slack_target);
     for (int it = 1; it <= step_iters; ++it) {
