@@ -282,29 +282,6 @@ __device__ __forceinline__ unsigned long long pack32(unsigned key, int id) {
 }
 __device__ __forceinline__ int packed_id(unsigned long long e) { return static_cast<int>(static_cast<unsigned>(e)); }
 
-#pragma clang fp contract(off)
-// The running sums of wave_sequential_scan for operands in LDS: every lane reads x[j] (one address
-// for the whole wave: a broadcast read) and adds it, so all lanes hold the same sums, in the order of
-// a sequential loop; lane 0 stores them.  x must be readable and zero, out writable, up to the next
-// multiple of 64 beyond `count`.  out[0] = start, out[i + 1] = start + x[0] + ... + x[i].
-// U sums are held in registers between two rounds of stores.
-template <int U = 64>
-__device__ __forceinline__ void wave_sequential_scan_padded(const double* x, double* out, int count, double start) {
-    const int lane = threadIdx.x & 63;
-    double acc = start;
-    if (lane == 0) out[0] = start;
-    for (int base = 0; base < count; base += U) {
-        double a[U];
-#pragma unroll
-        for (int j = 0; j < U; ++j) { acc = acc + x[base + j]; a[j] = acc; }
-        if (lane == 0) {
-#pragma unroll
-            for (int j = 0; j < U; ++j) out[base + j + 1] = a[j];
-        }
-    }
-}
-#pragma clang fp contract(fast)
-
 // Exclusive suffix minimum over the 256 threads: min of v over the threads after this one (1e300 for
 // the last); *total = min over all.  buf0, buf1: LDS double[256].
 __device__ double block_suffix_min_excl(double v, double* buf0, double* buf1, double* total) {

@@ -202,6 +202,34 @@ __device__ __forceinline__ int wave_sum_i(int v) {
            (__builtin_amdgcn_readlane(v, 32) + __builtin_amdgcn_readlane(v, 48));
 }
 
+// Inclusive scans over the lanes of a wave on the same path: shifts within the rows of sixteen lanes, then the rows' last lanes
+// are broadcast to the rows behind them.  A lane without a source takes `none`.  All 64 lanes must be active.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_shift(int v, int none) { return __builtin_amdgcn_update_dpp(none, v, CTRL, ROWS, 0xF, false); }
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_shift(double v, double none) {
+    const int lo = dpp_shift<CTRL, ROWS>(__double2loint(v), __double2loint(none)), hi = dpp_shift<CTRL, ROWS>(__double2hiint(v), __double2hiint(none));
+    return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ int wave_scan_i(int v) {
+    v += dpp_shift<0x111, 0xF>(v, 0);
+    v += dpp_shift<0x112, 0xF>(v, 0);
+    v += dpp_shift<0x114, 0xF>(v, 0);
+    v += dpp_shift<0x118, 0xF>(v, 0);
+    v += dpp_shift<0x142, 0xA>(v, 0);
+    v += dpp_shift<0x143, 0xC>(v, 0);
+    return v;
+}
+__device__ __forceinline__ double wave_scan_min(double v) {
+    v = fmin(v, dpp_shift<0x111, 0xF>(v, 1e300));
+    v = fmin(v, dpp_shift<0x112, 0xF>(v, 1e300));
+    v = fmin(v, dpp_shift<0x114, 0xF>(v, 1e300));
+    v = fmin(v, dpp_shift<0x118, 0xF>(v, 1e300));
+    v = fmin(v, dpp_shift<0x142, 0xA>(v, 1e300));
+    v = fmin(v, dpp_shift<0x143, 0xC>(v, 1e300));
+    return v;
+}
+
 // Workgroup reductions over NW waves.  `red` is an LDS array of at least NW doubles; both barriers are inside, so `red` may be reused right after the call.
 template <int NW = kWaves>
 __device__ __forceinline__ double block_sum(double v, double* red) {
@@ -263,22 +291,23 @@ __device__ __forceinline__ double pow_diff(double a, double d, int n) {
 }
 
 // Inclusive prefix sums of x[0..count) in index order, added one after the other exactly as a
-// sequential loop would (so the rounding does not depend on the machine), but held in the
-// registers of one wave: lane j of round r owns element 64 r + j, the running sum travels through
-// v_readlane.  Called by one whole wave; out[0] = start, out[i + 1] = start + x[0] + ... + x[i].
-__device__ __forceinline__ void wave_sequential_scan(const double* x, double* out, int count, double start) {
+// sequential loop would (so the rounding does not depend on the machine), x and out in LDS: every lane of the one wave that
+// calls reads x[j] (one address for the whole wave: a broadcast read) and adds it, so all lanes hold the same sums, and lane 0
+// stores them.  x must be readable and zero, out writable, up to the next multiple of U beyond `count`.  out[0] = start,
+// out[i + 1] = start + x[0] + ... + x[i].  U sums are held in registers between two rounds of stores.
+template <int U = 64>
+__device__ __forceinline__ void wave_sequential_scan_padded(const double* x, double* out, int count, double start) {
     const int lane = threadIdx.x & 63;
     double acc = start;
     if (lane == 0) out[0] = start;
-    for (int base = 0; base < count; base += 64) {
-        const double mine = (base + lane < count) ? x[base + lane] : 0.0;
-        double res = 0.0;
+    for (int base = 0; base < count; base += U) {
+        double a[U];
 #pragma unroll
-        for (int j = 0; j < 64; ++j) {
-            acc = acc + __shfl(mine, j);
-            if (lane == j) res = acc;
+        for (int j = 0; j < U; ++j) { acc = acc + x[base + j]; a[j] = acc; }
+        if (lane == 0) {
+#pragma unroll
+            for (int j = 0; j < U; ++j) out[base + j + 1] = a[j];
         }
-        if (base + lane < count) out[base + lane + 1] = res;
     }
 }
 #pragma clang fp contract(fast)
@@ -381,11 +410,7 @@ __device__ inline unsigned long long block_kth_largest(const unsigned long long*
             // lane l owns digits 255-4l .. 252-4l (largest digits in lane 0)
             int c[4]; int tot = 0;
             for (int j = 0; j < 4; ++j) { c[j] = hist[255 - 4 * tid - j]; tot += c[j]; }
-            int incl = tot;
-            for (int o = 1; o < 64; o <<= 1) {
-                int up = __shfl_up(incl, o);
-                if (tid >= o) incl += up;
-            }
+            const int incl = wave_scan_i(tot);
             int excl = incl - tot;
             if (excl < need && need <= incl) {
                 int above = excl;

@@ -40,6 +40,8 @@ namespace {
 #endif
 
 constexpr int KS = kMaxSupport;
+constexpr int kScan = 32;            // operands that a sequential sum takes from LDS between two rounds of stores
+__device__ __forceinline__ int padded(int count) { return (count + kScan - 1) / kScan * kScan; }
 // Threads of the solve workgroup: eight waves (two per SIMD, 256 registers each) up to 8 drafts, so that one
 // wave's dependent float64 chains and LDS waits are filled by the other; four waves (one per SIMD, all 512
 // registers) for the longer series of 9 to 16 drafts.
@@ -105,7 +107,7 @@ struct Lds {
             int cnt0[KS + 2]; int cnt1[KS + 2]; int ids[KS]; int byq[KS];
             double qd[KS]; double accb[KS];
             double dlt[KS]; double dval[KS];   // rows given as logits: draft minus target logit, draft logit
-            double P[KS + 1]; double S[KS + 1]; double G0[KS + 2]; double G1[KS + 2];
+            double P[KS + 2]; double S[KS + 2]; double G0[KS]; double G1[KS + 2]; double O0[KS]; double O1[KS + 2];
             unsigned long long keys[kSelCap];   // unsorted candidates (select merge)
         };
         struct {
@@ -1550,8 +1552,7 @@ __device__ int compact_active(LdsT& L, int lo, int hi, int kk) {
     const int j = tid < kk ? L.ordq[tid] : -1;           // kk <= KS <= kST
     const int on = (j >= lo && j < hi && L.inT[j] && L.tgt[j] > 0.0) ? 1 : 0;
     // inclusive scan of `on` over the workgroup
-    int incl = on;
-    for (int o = 1; o < 64; o <<= 1) { const int up = __shfl_up(incl, o); if ((tid & 63) >= o) incl += up; }
+    const int incl = wave_scan_i(on);
     int* wtot = reinterpret_cast<int*>(L.redn);
     if ((tid & 63) == 63) wtot[tid >> 6] = incl;
     __syncthreads();
@@ -1654,11 +1655,11 @@ __global__ __launch_bounds__(kThreadsOf<D>) void solve_kernel(SolveParams sp) {
             const double qa = L.accb[tid]; const int ta = L.ids[tid];
             for (int j = 0; j < kk; ++j) { const double qj = L.accb[j]; qr_ += static_cast<int>(qj > qa) | (static_cast<int>(qj == qa) & static_cast<int>(L.ids[j] < ta)); }
             L.qd[qr_] = qa;
-        }
+        } else if (tid < padded(kk)) L.qd[tid] = 0.0;
         __syncthreads();
         {
 #pragma clang fp contract(off)
-            if ((tid >> 6) == 0) wave_sequential_scan(L.qd, L.S, kk, 0.0);
+            if ((tid >> 6) == 0) wave_sequential_scan_padded<kScan>(L.qd, L.S, kk, 0.0);
         }
         __syncthreads();
         const double need = (1.0 - sp.tail_mass) * qtot;
@@ -1727,15 +1728,15 @@ __global__ __launch_bounds__(kThreadsOf<D>) void solve_kernel(SolveParams sp) {
             const int rank = L.cnt0[tid];
             L.tok[rank] = L.ids[tid]; L.qd[rank] = L.accb[tid]; L.pn[rank] = L.G0[tid] / ptot;
             L.byq[L.cnt1[tid]] = rank;                    // the token of q rank j sits at ratio rank byq[j]
-        }
+        } else if (tid < padded(kk)) { L.pn[tid] = 0.0; L.qd[tid] = 0.0; }
         __syncthreads();
     }
     GR_CLK(L, 1);
     // ---- prefix sums in the order, sequentially (bit-reproducible), then F(m) = P_m - Q_m^n
     {
 #pragma clang fp contract(off)
-        if ((tid >> 6) == 0) wave_sequential_scan(L.pn, L.P, kk, 0.0);
-        if ((tid >> 6) == 1) wave_sequential_scan(L.qd, L.S, kk, 0.0);
+        if ((tid >> 6) == 0) wave_sequential_scan_padded<kScan>(L.pn, L.P, kk, 0.0);
+        if ((tid >> 6) == 1) wave_sequential_scan_padded<kScan>(L.qd, L.S, kk, 0.0);
         __syncthreads();
         const double stot = L.S[kk];
         for (int m = tid; m <= kk; m += kST) {
@@ -1748,10 +1749,11 @@ __global__ __launch_bounds__(kThreadsOf<D>) void solve_kernel(SolveParams sp) {
     }
     // ---- one wave, no barriers: H* (the smallest minimising prefix), the suffix minima G of F, residuals,
     // targets and records (F(m) <= G(m+1) for m >= h; m = kk always), the block of every token, and the
-    // order by decreasing q split into H* and the rest.  Lane l holds ranks 5l .. 5l+4 (kk + 1 <= 257).
+    // order by decreasing q split into H* and the rest.  Lane l holds ranks 5 (63 - l) .. + 4 (kk + 1 <= 257): the suffix minima
+    // are then a scan over the lanes.
     if ((tid >> 6) == 0) {
         constexpr int E = (KS + 1 + 63) / 64;
-        const int lane = tid, m0 = lane * E;
+        const int lane = tid, m0 = (63 - lane) * E;
         double Fv[E];
 #pragma unroll
         for (int e = 0; e < E; ++e) Fv[e] = (m0 + e <= kk) ? L.F[m0 + e] : 1e300;
@@ -1767,10 +1769,9 @@ __global__ __launch_bounds__(kThreadsOf<D>) void solve_kernel(SolveParams sp) {
         sfx[E - 1] = Fv[E - 1];
 #pragma unroll
         for (int e = E - 2; e >= 0; --e) sfx[e] = fmin(Fv[e], sfx[e + 1]);
-        double later = sfx[0];                             // min of F over this lane's ranks and all later ones
-        for (int o = 1; o < 64; o <<= 1) { const double x = __shfl_down(later, o); if (lane + o < 64) later = fmin(later, x); }
-        double after = __shfl_down(later, 1);              // ... over the later lanes only
-        if (lane == 63) after = 1e300;
+        const double later = wave_scan_min(sfx[0]);        // min of F over this lane's ranks and all later ones
+        double after = __shfl_up(later, 1);                // ... over the later ranks' lanes only
+        if (lane == 0) after = 1e300;
         int fl[E], run = 0, cl[E];
 #pragma unroll
         for (int e = 0; e < E; ++e) {
@@ -1788,9 +1789,9 @@ __global__ __launch_bounds__(kThreadsOf<D>) void solve_kernel(SolveParams sp) {
             }
             run += fl[e]; cl[e] = run;
         }
-        int incl = run;
-        for (int o = 1; o < 64; o <<= 1) { const int up = __shfl_up(incl, o); if (lane >= o) incl += up; }
-        const int base = incl - run;
+        const int from_here = wave_scan_i(run);            // records of this lane's ranks and all later ones
+        const int nrec_ = __builtin_amdgcn_readlane(from_here, 63);
+        const int base = nrec_ - from_here;
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             const int m = m0 + e;
@@ -1800,7 +1801,6 @@ __global__ __launch_bounds__(kThreadsOf<D>) void solve_kernel(SolveParams sp) {
                 if (m < kk) L.blk[m] = (m >= hh) ? c : 0;    // token m (rank m+1) lies after record c
             }
         }
-        const int nrec_ = __shfl(incl, 63);
         // ordq: ratio ranks listed by decreasing q, the tokens of H* first (a stable split of the q order)
         constexpr int E4 = KS / 64;
         const int j0 = lane * E4;
@@ -1813,9 +1813,7 @@ __global__ __launch_bounds__(kThreadsOf<D>) void solve_kernel(SolveParams sp) {
             ci[e] = cin;                                   // members of H* among this lane's earlier entries
             cin += in[e];
         }
-        int incl_in = cin;
-        for (int o = 1; o < 64; o <<= 1) { const int up = __shfl_up(incl_in, o); if (lane >= o) incl_in += up; }
-        const int base_in = incl_in - cin;
+        const int base_in = wave_scan_i(cin) - cin;
 #pragma unroll
         for (int e = 0; e < E4; ++e) {
             const int j = j0 + e;
@@ -1835,16 +1833,18 @@ __global__ __launch_bounds__(kThreadsOf<D>) void solve_kernel(SolveParams sp) {
     const double Qh = L.Q[h];
     {
 #pragma clang fp contract(off)
-        // running q mass in decreasing-q order: G0 <- q in that order, G1 <- its sequential prefix sums
-        if (tid < kk) L.G0[tid] = L.qn[L.ordq[tid]];
+        // running q mass in decreasing-q order: G0 <- q of H* in that order, G1 <- its sequential prefix sums; O0, O1: of the rest
+        if (tid < kk) { const double q = L.qn[L.ordq[tid]]; if (tid < h) L.G0[tid] = q; else L.O0[tid - h] = q; }
+        if (tid >= h && tid < padded(h)) L.G0[tid] = 0.0;
+        if (tid >= kk - h && tid < padded(kk - h)) L.O0[tid] = 0.0;
         __syncthreads();
-        if ((tid >> 6) == 0) wave_sequential_scan(L.G0, L.G1, h, 0.0);
-        if ((tid >> 6) == 1) wave_sequential_scan(L.G0 + h, L.G1 + h + 1, kk - h, Qh);
+        if ((tid >> 6) == 0) wave_sequential_scan_padded<kScan>(L.G0, L.G1, h, 0.0);
+        if ((tid >> 6) == 1) wave_sequential_scan_padded<kScan>(L.O0, L.O1, kk - h, Qh);
         __syncthreads();
-        // the token at position t of that order has the mass G1[...] before it
+        // the token at position t of that order has the mass G1[t] or O1[t - h] before it
         if (tid < kk) {
             const int j = L.ordq[tid];
-            const double a = L.G1[tid < h ? tid : tid + 1];
+            const double a = tid < h ? L.G1[tid] : L.O1[tid - h];
             const double an = (a > 0.0) ? ipow(a, n) : 0.0;
             L.inT[j] = (j < h) ? ((ipow(Qh, n) - an) > sp.tau) : ((1.0 - an) > sp.tau);
         }
