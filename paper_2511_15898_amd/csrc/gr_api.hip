@@ -38,9 +38,10 @@ struct gr_handle_s {
     double* sweep_mass = nullptr;  // [max_B, kSweepMaxK] q mass of each top-k support of a sweep that runs in the workspace
     FullParams full = {};
     bool full_mode = false;
-    // staging of gr_tree_walk (allocated by its first call): gathered rows, drafts, uniforms, results, row offsets
-    float* tw_p = nullptr; float* tw_q = nullptr; int* tw_drafts = nullptr; float* tw_u = nullptr; float* tw_temp = nullptr; int* tw_tok = nullptr;
-    unsigned char* tw_ok = nullptr; long long* tw_idx = nullptr; float* tw_acc = nullptr; int* tw_status = nullptr;
+    // staging of gr_tree_walk (allocated by its first call): what a batch takes and gives, packed, on both sides; rows gathered for the
+    // HBM-resident path
+    unsigned char* tw_in = nullptr; unsigned char* tw_out = nullptr; unsigned char* tw_host = nullptr;
+    float* tw_p = nullptr; float* tw_q = nullptr;
     // last solve
     bool solved = false;
     const float* p = nullptr;
@@ -54,16 +55,25 @@ void mark(gr_handle h, int which, hipStream_t stream) {
     if (h->prof_now && h->prof_count < kProfSlots) (void)hipEventRecord(h->ev[h->prof_count][which], stream);
 }
 
+// A call that verified its rows in the solve launch: an empty interval where the profile has the verify launch.
+void mark_no_verify(gr_handle h, hipStream_t stream) {
+    mark(h, 3, stream);
+    mark(h, 4, stream);
+    if (h->prof_now && h->prof_count < kProfSlots) ++h->prof_count;
+    h->prof_now = false;
+}
+
 template <typename T>
 bool dev_alloc(T** ptr, size_t count) {
     return hipMalloc(reinterpret_cast<void**>(ptr), count * sizeof(T)) == hipSuccess;
 }
 
 void free_all(gr_handle h) {
-    void* ptrs[] = {h->cand, h->cand_count, h->part_psum, h->part_qsum, h->part_bad, h->piece_psum, h->piece_pref, h->part_pref, h->tw_p, h->tw_q, h->tw_drafts, h->tw_u, h->tw_temp, h->tw_tok, h->tw_ok, h->tw_idx, h->tw_acc, h->tw_status, h->sweep_mass, h->newton_ws, h->order, h->block,
+    void* ptrs[] = {h->cand, h->cand_count, h->part_psum, h->part_qsum, h->part_bad, h->piece_psum, h->piece_pref, h->part_pref, h->tw_p, h->tw_q, h->tw_in, h->tw_out, h->sweep_mass, h->newton_ws, h->order, h->block,
                     h->weight, h->rho, h->pnorm, h->info};
     for (void* ptr : ptrs) (void)hipFree(ptr);
     (void)hipFree(h->full_ws);
+    if (h->tw_host) (void)hipHostFree(h->tw_host);
     if (h->profile)
         for (auto& slot : h->ev)
             for (auto& e : slot)
@@ -194,9 +204,10 @@ int solve_in_hbm(gr_handle h, const float* p, const float* q, const float* tempe
 
 // The LDS-resident path of gr_solve (temperature == nullptr: p and q are probabilities) and of gr_solve_logits.
 // With drafts (and uniforms, token, accepted) the solve kernel also verifies every row; otherwise all four are nullptr.
+// row_at, row_n: rows picked from p and q, each with its own draft count (at most n; drafts [B, n]).
 int solve_in_lds(gr_handle h, const float* p, const float* q, const float* temperature, const float* draft_temperature, int n, int k_eff, float tol, int B, int V,
                  float* accept_prob, int* status, hipStream_t stream, const int* drafts = nullptr, const float* uniforms = nullptr,
-                 int* token = nullptr, unsigned char* accepted = nullptr) {
+                 int* token = nullptr, unsigned char* accepted = nullptr, const long long* row_at = nullptr, const int* row_n = nullptr) {
     h->full_mode = false;
     const int splits = choose_splits(B, V);
     int slice_len = (V + splits - 1) / splits;
@@ -205,10 +216,10 @@ int solve_in_lds(gr_handle h, const float* p, const float* q, const float* tempe
     mark(h, 0, stream);
     if (temperature)
         launch_select_logits(p, q, temperature, B, V, k_eff, splits, slice_len, h->cand, h->cand_count, h->part_psum, h->part_qsum,
-                             h->part_bad, h->part_pref, h->piece_psum, h->piece_pref, h->piece_stride, stream);
+                             h->part_bad, h->part_pref, h->piece_psum, h->piece_pref, h->piece_stride, row_at, stream);
     else
         launch_select(p, q, B, V, k_eff, splits, slice_len, h->cand, h->cand_count, h->part_psum, h->part_qsum,
-                      h->part_bad, h->piece_psum, h->piece_stride, stream);
+                      h->part_bad, h->piece_psum, h->piece_stride, row_at, stream);
     if (hipGetLastError() != hipSuccess) return GR_EHIP;
     mark(h, 1, stream);
     SolveParams sp;
@@ -222,6 +233,7 @@ int solve_in_lds(gr_handle h, const float* p, const float* q, const float* tempe
     sp.info = h->info; sp.accept_prob = accept_prob; sp.status = status; sp.newton_ws = h->newton_ws;
     sp.v_drafts = drafts; sp.v_uniforms = uniforms; sp.v_token = token; sp.v_accepted = accepted;
     sp.piece_psum = h->piece_psum; sp.piece_stride = h->piece_stride; sp.piece_pref = h->piece_pref;
+    sp.v_stride = n; sp.row_at = row_at; sp.row_n = row_n;
     if (launch_solve(sp, stream) != hipSuccess) return GR_EHIP;
     mark(h, 2, stream);
     h->solved = true; h->p = p; h->B = B; h->V = V; h->n = n;
@@ -306,10 +318,7 @@ int solve_entry(gr_handle h, const float* p, const float* q, const float* temper
     const int rc = solve_in_lds(h, p, q, temperature, draft_temperature, n, k_eff, tol, B, V, accept_prob, status, stream, drafts, uniforms,
                                 token, accepted);
     if (rc != GR_OK || !drafts) return rc;
-    mark(h, 3, stream);                              // no verify launch of its own: an empty interval in the profile
-    mark(h, 4, stream);
-    if (h->prof_now && h->prof_count < kProfSlots) ++h->prof_count;
-    h->prof_now = false;
+    mark_no_verify(h, stream);
     return GR_OK;
 }
 
@@ -393,7 +402,7 @@ extern "C" int gr_accept_sweep(gr_handle h, const float* p, const float* q, cons
     slice_len = (slice_len + kSelTile - 1) / kSelTile * kSelTile;
     h->solved = false;                                   // the selection scratch of the handle is overwritten
     launch_select(p, q, B, V, sw.kmax, splits, slice_len, h->cand, h->cand_count, h->part_psum, h->part_qsum,
-                  h->part_bad, h->piece_psum, h->piece_stride, stream);
+                  h->part_bad, h->piece_psum, h->piece_stride, nullptr, stream);
     if (hipGetLastError() != hipSuccess) return GR_EHIP;
     sw.p = p; sw.splits = splits;
     sw.cand = h->cand; sw.cand_count = h->cand_count; sw.part_psum = h->part_psum; sw.part_qsum = h->part_qsum;
@@ -421,7 +430,7 @@ extern "C" int gr_accept_sweep_noalloc(const float* p, const float* q, const int
     const int splits = choose_splits(B, V);
     int slice_len = (V + splits - 1) / splits;
     slice_len = (slice_len + kSelTile - 1) / kSelTile * kSelTile;
-    launch_select(p, q, B, V, sw.kmax, splits, slice_len, cand, count, psum, qsum, bad, nullptr, 0, stream);
+    launch_select(p, q, B, V, sw.kmax, splits, slice_len, cand, count, psum, qsum, bad, nullptr, 0, nullptr, stream);
     if (hipGetLastError() != hipSuccess) return GR_EHIP;
     sw.p = p; sw.splits = splits;
     sw.cand = cand; sw.cand_count = count; sw.part_psum = psum; sw.part_qsum = qsum; sw.part_bad = bad;
@@ -465,56 +474,75 @@ extern "C" int gr_tree_walk(gr_handle h, const float* p, const float* q, const f
     if (S <= 0 || K < 1 || L < 1 || V <= 0 || S > h->max_B || V > h->max_V || K > h->max_n) return GR_EINVAL;
     if (!(tol >= 0.f) || !(tol < 1.f)) return GR_EINVAL;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    if (!h->tw_p) {
-        const size_t rows = static_cast<size_t>(h->max_B), cols = static_cast<size_t>(h->max_V);
-        const bool ok = dev_alloc(&h->tw_p, rows * cols) && dev_alloc(&h->tw_q, rows * cols) && dev_alloc(&h->tw_drafts, rows * GR_MAX_N) &&
-                        dev_alloc(&h->tw_u, rows) && dev_alloc(&h->tw_temp, rows) && dev_alloc(&h->tw_tok, rows) && dev_alloc(&h->tw_ok, rows) && dev_alloc(&h->tw_idx, rows) &&
-                        dev_alloc(&h->tw_acc, rows) && dev_alloc(&h->tw_status, rows);
-        if (!ok) {
-            void* ptrs[] = {h->tw_p, h->tw_q, h->tw_drafts, h->tw_u, h->tw_temp, h->tw_tok, h->tw_ok, h->tw_idx, h->tw_acc, h->tw_status};
-            for (void* ptr : ptrs) (void)hipFree(ptr);
-            h->tw_p = h->tw_q = h->tw_u = h->tw_temp = h->tw_acc = nullptr; h->tw_drafts = h->tw_tok = h->tw_status = nullptr; h->tw_ok = nullptr; h->tw_idx = nullptr;
-            (void)hipGetLastError();
-            return GR_ENOMEM;
-        }
-    }
+    const int k_eff = (k <= 0 || k >= V) ? V : k;
+    const bool in_lds = k_eff <= kMaxSupport;
+    // Per row in: where it begins, its draft count, its drafts, uniform, temperature; out: token, status, acceptance, flag.
+    constexpr size_t kIn = sizeof(long long) + sizeof(int) * (1 + GR_MAX_N) + 2 * sizeof(float), kOut = 2 * sizeof(int) + sizeof(float) + 1;
+    const size_t rows = static_cast<size_t>(h->max_B), cols = static_cast<size_t>(h->max_V);
+    const bool staged = (h->tw_in || dev_alloc(&h->tw_in, rows * kIn)) && (h->tw_out || dev_alloc(&h->tw_out, rows * kOut)) &&
+                        (h->tw_host || hipHostMalloc(reinterpret_cast<void**>(&h->tw_host), rows * (kIn + kOut), hipHostMallocDefault) == hipSuccess) &&
+                        (in_lds || ((h->tw_p || dev_alloc(&h->tw_p, rows * cols)) && (h->tw_q || dev_alloc(&h->tw_q, rows * cols))));
+    if (!staged) { (void)hipGetLastError(); return GR_ENOMEM; }          // what was allocated stays for the next call
     try {
     // the state of every sequence lives on the host: the paths that still agree with the tokens emitted so far
     std::vector<unsigned> active(S, K >= 32 ? 0xFFFFFFFFu : ((1u << K) - 1u));
     std::vector<char> alive(S, 1);
     for (int s = 0; s < S; ++s) { out_len[s] = 0; out_accepted[s] = 0; if (out_fallbacks) out_fallbacks[s] = 0; }
     for (int i = 0; i < S * L; ++i) out_tokens[i] = -1;
-    std::vector<int> seqs, drafts, tok, st; std::vector<long long> idx; std::vector<float> us, ts; std::vector<unsigned char> okv;
+    std::vector<int> seqs;
     for (int l = 0; l < L; ++l) {
-        for (int n = 1; n <= K; ++n) {
-            seqs.clear(); drafts.clear(); idx.clear(); us.clear(); ts.clear();
+        // Every sequence still alive, whatever its draft count, in one batch: a level then takes as long as its slowest row, and
+        // not as the slowest row of every count in turn (32 sequences of 4 paths, 5 levels, V = 32000: 17 batches took 3060 us).
+        // The HBM-resident kernels take one count per batch and rows one after the other.
+        for (int group = in_lds ? K : 1; group <= K; ++group) {
+            seqs.clear();
+            int most = 0;
             for (int s = 0; s < S; ++s) {
-                if (!alive[s] || __builtin_popcount(active[s]) != n) continue;
-                const int a0 = __builtin_ctz(active[s]);
+                const int n = __builtin_popcount(active[s]);
+                if (!alive[s] || (!in_lds && n != group)) continue;
                 seqs.push_back(s);
-                idx.push_back(((static_cast<long long>(s) * K + a0) * L + l) * V);
-                for (int a = 0; a < K; ++a) if (active[s] >> a & 1u) drafts.push_back(paths[(static_cast<size_t>(s) * K + a) * L + l]);
-                us.push_back(uniforms[static_cast<size_t>(s) * L + l]);
-                if (temperature) ts.push_back(temperature[s]);
+                most = std::max(most, n);
             }
             const int cnt = static_cast<int>(seqs.size());
             if (cnt == 0) continue;
-            if (hipMemcpyAsync(h->tw_idx, idx.data(), sizeof(long long) * cnt, hipMemcpyHostToDevice, stream) != hipSuccess ||
-                hipMemcpyAsync(h->tw_drafts, drafts.data(), sizeof(int) * cnt * n, hipMemcpyHostToDevice, stream) != hipSuccess ||
-                hipMemcpyAsync(h->tw_u, us.data(), sizeof(float) * cnt, hipMemcpyHostToDevice, stream) != hipSuccess ||
-                (temperature && hipMemcpyAsync(h->tw_temp, ts.data(), sizeof(float) * cnt, hipMemcpyHostToDevice, stream) != hipSuccess)) return GR_EHIP;
-            hipLaunchKernelGGL(gather_rows_kernel, dim3(cnt), dim3(kThreads), 0, stream, p, q, h->tw_idx, h->tw_p, h->tw_q, V);
-            if (hipGetLastError() != hipSuccess) return GR_EHIP;
-            const int rc = temperature
-                ? gr_solve_logits_verify(h, h->tw_p, h->tw_q, h->tw_temp, nullptr, n, k, tol, cnt, V, h->tw_drafts, h->tw_u, h->tw_acc, h->tw_status,
-                                         h->tw_tok, h->tw_ok, stream)
-                : gr_solve_verify(h, h->tw_p, h->tw_q, n, k, tol, cnt, V, h->tw_drafts, h->tw_u, h->tw_acc, h->tw_status, h->tw_tok, h->tw_ok, stream);
-            if (rc != GR_OK) return rc;
-            tok.resize(cnt); st.resize(cnt); okv.resize(cnt);
-            if (hipMemcpyAsync(tok.data(), h->tw_tok, sizeof(int) * cnt, hipMemcpyDeviceToHost, stream) != hipSuccess ||
-                hipMemcpyAsync(okv.data(), h->tw_ok, cnt, hipMemcpyDeviceToHost, stream) != hipSuccess ||
-                hipMemcpyAsync(st.data(), h->tw_status, sizeof(int) * cnt, hipMemcpyDeviceToHost, stream) != hipSuccess ||
+            if (temperature && h->tail_mass > 0.0) return GR_EUNSUPPORTED;       // the nucleus cut is defined on probabilities
+            const size_t at_n = sizeof(long long) * cnt, at_d = at_n + sizeof(int) * cnt, at_u = at_d + sizeof(int) * cnt * most,
+                         at_t = at_u + sizeof(float) * cnt, in_bytes = at_t + sizeof(float) * cnt;
+            long long* const idx = reinterpret_cast<long long*>(h->tw_host);
+            int* const ns = reinterpret_cast<int*>(h->tw_host + at_n); int* const drafts = reinterpret_cast<int*>(h->tw_host + at_d);
+            float* const us = reinterpret_cast<float*>(h->tw_host + at_u); float* const ts = reinterpret_cast<float*>(h->tw_host + at_t);
+            for (int j = 0; j < cnt; ++j) {
+                const int s = seqs[j];
+                idx[j] = ((static_cast<long long>(s) * K + __builtin_ctz(active[s])) * L + l) * V;
+                ns[j] = __builtin_popcount(active[s]);
+                int* d = drafts + static_cast<size_t>(j) * most;
+                for (int a = 0; a < K; ++a) if (active[s] >> a & 1u) *d++ = paths[(static_cast<size_t>(s) * K + a) * L + l];
+                for (; d < drafts + static_cast<size_t>(j + 1) * most; ++d) *d = 0;
+                us[j] = uniforms[static_cast<size_t>(s) * L + l];
+                ts[j] = temperature ? temperature[s] : 1.f;
+            }
+            if (hipMemcpyAsync(h->tw_in, h->tw_host, in_bytes, hipMemcpyHostToDevice, stream) != hipSuccess) return GR_EHIP;
+            const long long* const d_at = reinterpret_cast<const long long*>(h->tw_in);
+            const int* const d_n = reinterpret_cast<const int*>(h->tw_in + at_n); const int* const d_drafts = reinterpret_cast<const int*>(h->tw_in + at_d);
+            const float* const d_u = reinterpret_cast<const float*>(h->tw_in + at_u);
+            const float* const d_temp = temperature ? reinterpret_cast<const float*>(h->tw_in + at_t) : nullptr;
+            int* const o_tok = reinterpret_cast<int*>(h->tw_out); int* const o_st = o_tok + cnt;
+            float* const o_acc = reinterpret_cast<float*>(o_st + cnt); unsigned char* const o_ok = reinterpret_cast<unsigned char*>(o_acc + cnt);
+            int rc;
+            if (in_lds) {
+                rc = solve_in_lds(h, p, q, d_temp, nullptr, most, k_eff, tol, cnt, V, o_acc, o_st, stream, d_drafts, d_u, o_tok, o_ok, d_at, d_n);
+                if (rc == GR_OK) mark_no_verify(h, stream);
+            } else {
+                hipLaunchKernelGGL(gather_rows_kernel, dim3(cnt), dim3(kThreads), 0, stream, p, q, d_at, h->tw_p, h->tw_q, V);
+                if (hipGetLastError() != hipSuccess) return GR_EHIP;
+                rc = solve_entry(h, h->tw_p, h->tw_q, d_temp, nullptr, group, k, tol, cnt, V, d_drafts, d_u, o_acc, o_st, o_tok, o_ok, stream);
+            }
+            if (rc != GR_OK) { (void)hipStreamSynchronize(stream); return rc; }        // the copy reads the staging that the next call writes
+            unsigned char* const back = h->tw_host + rows * kIn;
+            if (hipMemcpyAsync(back, h->tw_out, kOut * cnt, hipMemcpyDeviceToHost, stream) != hipSuccess ||
                 hipStreamSynchronize(stream) != hipSuccess) return GR_EHIP;
+            const int* const tok = reinterpret_cast<const int*>(back); const int* const st = tok + cnt;
+            const unsigned char* const okv = back + 3 * sizeof(int) * cnt;
             for (int j = 0; j < cnt; ++j) {
                 const int s = seqs[j];
                 out_tokens[static_cast<size_t>(s) * L + l] = tok[j];

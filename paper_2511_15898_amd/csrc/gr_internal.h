@@ -60,6 +60,10 @@ struct SolveParams {
     // the sums of p over pieces of 256 tokens that the select pass left, as in PolicyView
     const int* v_drafts; const float* v_uniforms; int* v_token; unsigned char* v_accepted;
     const double* piece_psum; int piece_stride; const float* piece_pref;
+    int v_stride;                     // drafts of a row to the next
+    // rows of a gathered batch: where they begin in p and q (elements; nullptr: one after the other), their own draft counts [B]
+    // (at most n; nullptr: n for all)
+    const long long* row_at; const int* row_n;
 };
 
 // Workspace and arguments of the full-vocabulary path (no top-k).  Per-token arrays are row-major with
@@ -91,10 +95,11 @@ struct FullSweep;
 void launch_full_sweep(const FullParams& fp, const FullSweep& fs, hipStream_t stream);
 void launch_select(const float* p, const float* q, int B, int V, int k, int splits, int slice_len,
                    unsigned long long* cand, int* cand_count, double* psum, double* qsum, int* bad,
-                   double* piece_psum, int piece_stride, hipStream_t stream);
+                   double* piece_psum, int piece_stride, const long long* row_at, hipStream_t stream);
 void launch_select_logits(const float* target_logits, const float* draft_logits, const float* temperature, int B, int V, int k,
                           int splits, int slice_len, unsigned long long* cand, int* cand_count, double* psum, double* qsum,
-                          int* bad, float* part_pref, double* piece_psum, float* piece_pref, int piece_stride, hipStream_t stream);
+                          int* bad, float* part_pref, double* piece_psum, float* piece_pref, int piece_stride, const long long* row_at,
+                          hipStream_t stream);
 hipError_t launch_solve(const SolveParams& sp, hipStream_t stream);
 // The policy object as the verify and slice kernels read it.  Top-k policies: arrays [B, stride] with
 // stride = kMaxSupport, rank_of = rho_id = nullptr.  Full-vocabulary policies: stride = V + 2, plus the

@@ -27,7 +27,8 @@ __global__ __launch_bounds__(kThreads, 8) void select_kernel(
     unsigned long long* __restrict__ cand, int* __restrict__ cand_count,
     double* __restrict__ part_psum, double* __restrict__ part_qsum, int* __restrict__ part_bad,
     double* __restrict__ piece_psum, int piece_stride,
-    const float* __restrict__ temperature, float* __restrict__ part_pref, float* __restrict__ piece_pref) {
+    const float* __restrict__ temperature, float* __restrict__ part_pref, float* __restrict__ piece_pref,
+    const long long* __restrict__ row_at) {
     __shared__ unsigned long long keys[kSelCap];
     __shared__ int hist[256];
     __shared__ int pick[4];
@@ -40,8 +41,10 @@ __global__ __launch_bounds__(kThreads, 8) void select_kernel(
     const int s = blockIdx.x, b = blockIdx.y, splits = gridDim.x;
     const int v0 = s * slice_len;
     const int v1 = min(V, v0 + slice_len);
-    const float* qr = q + static_cast<size_t>(b) * V;
-    const float* pr = p + static_cast<size_t>(b) * V;
+    // row_at: where the rows begin, in elements (multiples of V); nullptr: one after the other
+    const size_t row0 = row_at ? static_cast<size_t>(row_at[b]) : static_cast<size_t>(b) * V;
+    const float* qr = q + row0;
+    const float* pr = p + row0;
     // float4 loads need 16-byte aligned rows: V % 4 == 0 (slice_len is a multiple of 4).
     const bool vec = (V & 3) == 0 && ((reinterpret_cast<uintptr_t>(p) | reinterpret_cast<uintptr_t>(q)) & 15) == 0;
 
@@ -232,18 +235,19 @@ __global__ __launch_bounds__(kThreads, 8) void select_kernel(
 
 void launch_select(const float* p, const float* q, int B, int V, int k, int splits, int slice_len,
                    unsigned long long* cand, int* cand_count, double* psum, double* qsum, int* bad,
-                   double* piece_psum, int piece_stride, hipStream_t stream) {
+                   double* piece_psum, int piece_stride, const long long* row_at, hipStream_t stream) {
     dim3 grid(splits, B);
     hipLaunchKernelGGL(select_kernel<false>, grid, dim3(kThreads), 0, stream, p, q, V, k, slice_len, cand,
-                       cand_count, psum, qsum, bad, piece_psum, piece_stride, nullptr, nullptr, nullptr);
+                       cand_count, psum, qsum, bad, piece_psum, piece_stride, nullptr, nullptr, nullptr, row_at);
 }
 
 void launch_select_logits(const float* target_logits, const float* draft_logits, const float* temperature, int B, int V, int k,
                           int splits, int slice_len, unsigned long long* cand, int* cand_count, double* psum, double* qsum,
-                          int* bad, float* part_pref, double* piece_psum, float* piece_pref, int piece_stride, hipStream_t stream) {
+                          int* bad, float* part_pref, double* piece_psum, float* piece_pref, int piece_stride, const long long* row_at,
+                          hipStream_t stream) {
     dim3 grid(splits, B);
     hipLaunchKernelGGL(select_kernel<true>, grid, dim3(kThreads), 0, stream, target_logits, draft_logits, V, k, slice_len, cand,
-                       cand_count, psum, qsum, bad, piece_psum, piece_stride, temperature, part_pref, piece_pref);
+                       cand_count, psum, qsum, bad, piece_psum, piece_stride, temperature, part_pref, piece_pref, row_at);
 }
 
 }  // namespace gr

@@ -1572,7 +1572,8 @@ __global__ __launch_bounds__(kThreadsOf<D>) void solve_kernel(SolveParams sp) {
     Lds<D>& L = *reinterpret_cast<Lds<D>*>(gr_lds_raw);
     const int tid = threadIdx.x;
     const int row = blockIdx.x;
-    const int n = sp.n, V = sp.V;
+    const int n = sp.row_n ? sp.row_n[row] : sp.n, V = sp.V;
+    const float* const prow = sp.p + (sp.row_at ? static_cast<size_t>(sp.row_at[row]) : static_cast<size_t>(row) * V);
     RowInfo info;
     info.support = 0; info.h = 0; info.status = GR_ROW_OK; info.iterations = 0;
     info.alpha_star = 0.0; info.res_total = 0.0; info.p_total = 0.0; info.q_total = 0.0; info.node_tokens = 0.0; info.p_ref = 0.0; info.inv_temp = 0.0; info.q_ref = 0.0;
@@ -1680,12 +1681,12 @@ __global__ __launch_bounds__(kThreadsOf<D>) void solve_kernel(SolveParams sp) {
         const double d = tid < kk ? L.accb[tid] : -1e300;
         const double dmax = block_max<kSW>(d, L.redn);
         if (tid < kk) {
-            const double t = static_cast<double>(sp.p[static_cast<size_t>(row) * V + L.ids[tid]]);
+            const double t = static_cast<double>(prow[L.ids[tid]]);
             L.G0[tid] = exp((t - p_ref) * inv_temp);
             L.dlt[tid] = logit_ratio_key(d, t, inv_temp_q, inv_temp); L.dval[tid] = d;
             L.accb[tid] = exp((d - dmax) * inv_temp_q);
         }
-    } else if (tid < kk) L.G0[tid] = static_cast<double>(sp.p[static_cast<size_t>(row) * V + L.ids[tid]]);
+    } else if (tid < kk) L.G0[tid] = static_cast<double>(prow[L.ids[tid]]);
     if (tid < kk) { L.cnt0[tid] = 0; L.cnt1[tid] = 0; }
     __syncthreads();
     GR_CLK(L, 0);
@@ -1935,8 +1936,8 @@ __global__ __launch_bounds__(kThreadsOf<D>) void solve_kernel(SolveParams sp) {
         rp.pieces = sp.piece_psum ? sp.piece_psum + static_cast<size_t>(row) * sp.piece_stride : nullptr;
         rp.prefs = sp.piece_pref ? sp.piece_pref + static_cast<size_t>(row) * sp.piece_stride : nullptr;
         static_assert(sizeof(VerifyLds) <= sizeof(Lds<D>), "the verification reuses the solve's LDS");
-        verify_row(*reinterpret_cast<VerifyLds*>(gr_lds_raw), sp.p + static_cast<size_t>(row) * sp.V, sp.V, sp.n, rp, info,
-                   sp.v_drafts + static_cast<size_t>(row) * sp.n, sp.v_uniforms[row], sp.v_token + row, sp.v_accepted + row);
+        verify_row(*reinterpret_cast<VerifyLds*>(gr_lds_raw), prow, V, n, rp, info,
+                   sp.v_drafts + static_cast<size_t>(row) * sp.v_stride, sp.v_uniforms[row], sp.v_token + row, sp.v_accepted + row);
     }
 }
 
