@@ -106,7 +106,7 @@ PolicyView policy_view(gr_handle h) {
 }
 
 constexpr size_t kFullPad = 256;
-size_t full_ws_bytes(size_t rows, size_t vs) { return rows * vs * kFullBytesPerToken + 40 * kFullPad + rows * 3 * sizeof(int); }
+size_t full_ws_bytes(size_t rows, size_t vs) { return rows * vs * kFullBytesPerToken + 40 * kFullPad + rows * 4 * sizeof(int); }
 
 // Carve the workspace of the full-vocabulary path (allocated once by gr_create) for a batch of B rows of V tokens.
 int prepare_full(gr_handle h, int B, int V) {
@@ -118,13 +118,13 @@ int prepare_full(gr_handle h, int B, int V) {
     FullParams& f = h->full;
     const size_t cnt = rows * vs;
     f.key0 = static_cast<unsigned long long*>(take(cnt * 8)); f.key1 = static_cast<unsigned long long*>(take(cnt * 8));
-    f.val0 = static_cast<int*>(take(cnt * 4)); f.val1 = static_cast<int*>(take(cnt * 4));
+    f.val0 = static_cast<int*>(take(cnt * 4));
     f.order = static_cast<int*>(take(cnt * 4)); f.byq = static_cast<int*>(take(cnt * 4));
-    double** dbl[] = {&f.pn, &f.qn, &f.P, &f.Q, &f.F, &f.rho, &f.tgt, &f.weight, &f.rho_id};
+    double** dbl[] = {&f.pn, &f.qn, &f.P, &f.Q, &f.rho, &f.weight, &f.rho_id};
     for (double** d : dbl) *d = static_cast<double*>(take(cnt * 8));
-    int** ints[] = {&f.flag, &f.blk, &f.blo, &f.inT, &f.bcount, &f.rank_of};
+    int** ints[] = {&f.flag, &f.blk, &f.blo, &f.bcount, &f.rank_of};
     for (int** d : ints) *d = static_cast<int*>(take(cnt * 4));
-    f.nblk = static_cast<int*>(take(rows * 4)); f.tcount = static_cast<int*>(take(rows * 8));
+    f.nblk = static_cast<int*>(take(rows * 4)); f.tcount = static_cast<int*>(take(rows * 12));
     return GR_OK;
 }
 
@@ -189,7 +189,7 @@ int solve_in_hbm(gr_handle h, const float* p, const float* q, const float* tempe
     if (rc != GR_OK) return rc;
     FullParams& f = h->full;
     f.p = p; f.q = q; f.B = B; f.V = V; f.n = n; f.k = k_eff; f.max_T = h->max_T; f.max_iter = h->max_iter;
-    f.tau = static_cast<double>(tol); f.rel_tol = h->rel_tol; f.tail_mass = h->tail_mass;
+    f.tau = static_cast<double>(tol); f.rel_tol = h->rel_tol; f.tail_mass = h->tail_mass; f.dense = 1;
     f.logits = temperature ? 1 : 0; f.temperature = temperature; f.draft_temperature = draft_temperature;
     f.info = h->info; f.accept_prob = accept_prob; f.status = status; f.newton_ws = h->newton_ws;
     mark(h, 0, stream);
@@ -273,7 +273,7 @@ extern "C" int gr_create(gr_handle* out, int max_B, int max_V, int max_k, int ma
          dev_alloc(&h->part_pref, rows * kMaxSplits);
     ok = ok && dev_alloc(&h->newton_ws, rows * kMaxT * (kMaxT + 1));
     if (ok && k_cap > kMaxSupport) {
-        // supports above GR_MAX_SUPPORT live in HBM: 128 bytes per token of max_V and row, held until gr_destroy
+        // supports above GR_MAX_SUPPORT live in HBM: 104 bytes per token of max_V and row, held until gr_destroy
         const size_t need = full_ws_bytes(rows, static_cast<size_t>(max_V) + 2);
         ok = hipMalloc(&h->full_ws, need) == hipSuccess && dev_alloc(&h->sweep_mass, rows * kSweepMaxK);
         if (ok) h->full_ws_bytes = need;
@@ -386,7 +386,7 @@ extern "C" int gr_accept_sweep(gr_handle h, const float* p, const float* q, cons
             if (rc != GR_OK) return rc;
             FullParams& f = h->full;
             f.p = p; f.q = q; f.B = B; f.V = V; f.n = 1; f.k = kmax; f.max_T = h->max_T; f.max_iter = h->max_iter;
-            f.tau = 0.0; f.rel_tol = h->rel_tol; f.tail_mass = 0.0; f.logits = 0; f.temperature = nullptr; f.draft_temperature = nullptr;
+            f.tau = 0.0; f.rel_tol = h->rel_tol; f.tail_mass = 0.0; f.dense = 0; f.logits = 0; f.temperature = nullptr; f.draft_temperature = nullptr;
             f.info = h->info; f.accept_prob = accept_prob; f.status = status; f.newton_ws = h->newton_ws;
             fs.mass = h->sweep_mass; fs.accept_prob = accept_prob; fs.status = status;
             launch_full_sweep(f, fs, stream);

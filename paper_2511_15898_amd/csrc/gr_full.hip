@@ -14,131 +14,8 @@ namespace gr {
 namespace {
 
 constexpr int kSortItems = 4;                      // keys per thread and tile
-constexpr int kSortWaves = kSortItems * kWaves;    // 64-key groups of one tile, in index order
-
-struct SortLds {
-    int hist[8][256];                              // digit histograms of all eight passes
-    int base[2][256];                              // first output slot of each digit for the current tile
-    unsigned short wcnt[2][kSortWaves][256];       // per 64-key group: keys with this digit, then their offset within the tile
-    int skip[8];
-};
-
-// Stable least-significant-digit radix sort of `count` (key, value) pairs of one row, ascending in the
-// 64-bit key, 8 bits per pass, between the buffer pairs (k0, v0) and (k1, v1).  Returns 0 or 1: the pair
-// that holds the result.  The histograms of all passes come from one read of the keys (they do not depend
-// on the order); passes whose digit is the same for every key are skipped.  A pass moves tiles of 1024
-// keys, four per thread, with two barriers per tile: the per-group counters and the digit bases are
-// double-buffered, and thread d carries the running base of digit d in a register.  All threads call.
-__device__ int block_radix_sort(unsigned long long* k0, int* v0, unsigned long long* k1, int* v1, int count,
-                                SortLds& S) {
-    constexpr int kTile = kThreads * kSortItems;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    for (int j = 0; j < 8; ++j) S.hist[j][tid] = 0;
-    if (tid < 8) S.skip[tid] = 0;
-    __syncthreads();
-    for (int i0 = 0; i0 < count; i0 += kThreads) {
-        const int i = i0 + tid;
-        const bool valid = i < count;
-        const unsigned long long key = valid ? k0[i] : 0ull;
-        const unsigned long long vm = __ballot(valid);
-        if (vm == 0ull) continue;                               // wave-uniform; lane 0 is valid otherwise
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int d = static_cast<int>((key >> (8 * j)) & 255ull);
-            const int d0 = __builtin_amdgcn_readfirstlane(d);
-            if (__ballot(valid && d == d0) == vm) {             // one digit in the whole wave: one update
-                if (lane == 0) atomicAdd(&S.hist[j][d0], __popcll(vm));
-            } else if (valid) {
-                atomicAdd(&S.hist[j][d], 1);
-            }
-        }
-    }
-    __syncthreads();
-    for (int j = 0; j < 8; ++j) if (S.hist[j][tid] == count) S.skip[j] = 1;
-    __syncthreads();
-
-    int cur = 0;
-    for (int pass = 0; pass < 8; ++pass) {
-        if (S.skip[pass]) continue;
-        const int shift = 8 * pass;
-        const unsigned long long* ks = cur ? k1 : k0; const int* vs = cur ? v1 : v0;
-        unsigned long long* kd = cur ? k0 : k1; int* vd = cur ? v0 : v1;
-        if (wv == 0) {
-            // exclusive scan of the histogram: lane l owns digits 4l .. 4l+3; the result goes to base[1]
-            // (unused until the second tile) and from there to the owners' registers
-            int c[4]; int tot = 0;
-            for (int j = 0; j < 4; ++j) { c[j] = S.hist[pass][4 * lane + j]; tot += c[j]; }
-            int incl = tot;
-            for (int o = 1; o < 64; o <<= 1) { const int up = __shfl_up(incl, o); if (lane >= o) incl += up; }
-            int run = incl - tot;
-            for (int j = 0; j < 4; ++j) { S.base[1][4 * lane + j] = run; run += c[j]; }
-        }
-        for (int w = 0; w < kSortWaves; ++w) { S.wcnt[0][w][tid] = 0; S.wcnt[1][w][tid] = 0; }
-        __syncthreads();
-        int mybase = S.base[1][tid];                            // running first slot of digit `tid`
-        __syncthreads();
-        unsigned long long kn[kSortItems]; int vn[kSortItems];
-#pragma unroll
-        for (int j = 0; j < kSortItems; ++j) {
-            const int i = j * kThreads + tid;
-            kn[j] = 0ull; vn[j] = 0;
-            if (i < count) { kn[j] = ks[i]; vn[j] = vs[i]; }
-        }
-        int buf = 0;
-        for (int t0 = 0; t0 < count; t0 += kTile, buf ^= 1) {
-            unsigned long long key[kSortItems]; int val[kSortItems]; int dig[kSortItems]; int rank[kSortItems];
-#pragma unroll
-            for (int j = 0; j < kSortItems; ++j) { key[j] = kn[j]; val[j] = vn[j]; }
-#pragma unroll
-            for (int j = 0; j < kSortItems; ++j) {
-                const int i = t0 + kTile + j * kThreads + tid;
-                if (i < count) { kn[j] = ks[i]; vn[j] = vs[i]; }
-            }
-#pragma unroll
-            for (int j = 0; j < kSortItems; ++j) {
-                const bool valid = t0 + j * kThreads + tid < count;
-                const int d = static_cast<int>((key[j] >> shift) & 255ull);
-                // lanes of this wave that hold the same digit
-                unsigned long long peers = __ballot(valid);
-#pragma unroll
-                for (int b = 0; b < 8; ++b) {
-                    const bool bit = (d >> b) & 1;
-                    const unsigned long long m = __ballot(valid && bit);
-                    peers &= bit ? m : ~m;
-                }
-                dig[j] = d;
-                rank[j] = __popcll(peers & ((1ull << lane) - 1ull));
-                if (valid && rank[j] == 0) S.wcnt[buf][j * kWaves + wv][d] = static_cast<unsigned short>(__popcll(peers));
-            }
-            __syncthreads();
-            {
-                // digit `tid`: counts of the groups -> offsets within the tile; clear the other buffer for the next tile
-                S.base[buf][tid] = mybase;
-                int run = 0;
-#pragma unroll
-                for (int w = 0; w < kSortWaves; ++w) {
-                    const int c = S.wcnt[buf][w][tid];
-                    S.wcnt[buf][w][tid] = static_cast<unsigned short>(run);
-                    run += c;
-                    S.wcnt[buf ^ 1][w][tid] = 0;
-                }
-                mybase += run;
-            }
-            __syncthreads();
-#pragma unroll
-            for (int j = 0; j < kSortItems; ++j) {
-                if (t0 + j * kThreads + tid < count) {
-                    const int off = S.base[buf][dig[j]] + S.wcnt[buf][j * kWaves + wv][dig[j]] + rank[j];
-                    kd[off] = key[j]; vd[off] = val[j];
-                }
-            }
-        }
-        cur ^= 1;
-        __syncthreads();
-    }
-    return cur;
-}
-
+constexpr int kScanThreads = 512;                  // of the kernel that takes the prefix sums
+constexpr int kDenseRanks = 4096;                  // ranks per workgroup of the kernel that writes the dense arrays
 // The sort of the large supports: elements of 8 bytes, the key in the high bits and the token id in the low ones.
 template <int NT>
 struct Sort32Lds {
@@ -282,41 +159,6 @@ __device__ __forceinline__ unsigned long long pack32(unsigned key, int id) {
 }
 __device__ __forceinline__ int packed_id(unsigned long long e) { return static_cast<int>(static_cast<unsigned>(e)); }
 
-// Exclusive suffix minimum over the 256 threads: min of v over the threads after this one (1e300 for
-// the last); *total = min over all.  buf0, buf1: LDS double[256].
-__device__ double block_suffix_min_excl(double v, double* buf0, double* buf1, double* total) {
-    const int tid = threadIdx.x;
-    double* src = buf0; double* dst = buf1;
-    src[tid] = v;
-    __syncthreads();
-    for (int o = 1; o < kThreads; o <<= 1) {
-        dst[tid] = (tid + o < kThreads) ? fmin(src[tid], src[tid + o]) : src[tid];
-        __syncthreads();
-        double* t = src; src = dst; dst = t;
-    }
-    const double excl = (tid + 1 < kThreads) ? src[tid + 1] : 1e300;
-    *total = src[0];
-    __syncthreads();
-    return excl;
-}
-
-// Exclusive prefix sum over the 256 threads; *total = sum over all.  buf0, buf1: LDS int[256].
-__device__ int block_prefix_sum_excl(int v, int* buf0, int* buf1, int* total) {
-    const int tid = threadIdx.x;
-    int* src = buf0; int* dst = buf1;
-    src[tid] = v;
-    __syncthreads();
-    for (int o = 1; o < kThreads; o <<= 1) {
-        dst[tid] = (tid >= o) ? src[tid] + src[tid - o] : src[tid];
-        __syncthreads();
-        int* t = src; src = dst; dst = t;
-    }
-    const int excl = src[tid] - v;
-    *total = src[kThreads - 1];
-    __syncthreads();
-    return excl;
-}
-
 // wtot: LDS, the counts of the workgroup's 4 NW groups of 64 tokens in token order (NW <= 16: one per lane).  offs[j] = the
 // count before this wave's group of round j; returns the count of all groups.  (A loop over the groups in every thread
 // cost a row of 8193 tokens cut to 9 36 of its 100 us in a workgroup of 16 waves.)
@@ -376,6 +218,25 @@ __device__ void mark_bad(const FullParams& fp, int row, double ptot, double qtot
     fp.info[row] = info;
     fp.accept_prob[row] = __uint_as_float(0x7fc00000u);
     fp.status[row] = GR_ROW_BAD;
+}
+
+// What adding a run of terms one after the other does to a running sum, from its rounding alone.  While the sum stays in one
+// binade it is a whole number of units u, and acc + x rounds to acc + r u with r depending on x and, where x lies halfway between
+// two units, on whether acc / u is even.  So a run of terms is two sums (exact, both whole numbers of u) and the parity they
+// leave, one for an even start and one for an odd one, and runs compose: sequential sums, bit for bit, by a scan.
+struct RunSum { double d[2]; int par; };                       // par: bit s = the parity that a start of parity s ends with
+__device__ __forceinline__ RunSum compose(const RunSum& a, const RunSum& b) {
+    RunSum r;
+    r.d[0] = a.d[0] + ((a.par & 1) ? b.d[1] : b.d[0]);
+    r.d[1] = a.d[1] + ((a.par & 2) ? b.d[1] : b.d[0]);
+    r.par = ((b.par >> (a.par & 1)) & 1) | (((b.par >> ((a.par >> 1) & 1)) & 1) << 1);
+    return r;
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ void scan_step(RunSum& v) {
+    RunSum a;                                                  // a lane without a source: the empty run
+    a.d[0] = dpp_shift<CTRL, ROWS>(v.d[0], 0.0); a.d[1] = dpp_shift<CTRL, ROWS>(v.d[1], 0.0); a.par = dpp_shift<CTRL, ROWS>(v.par, 2);
+    v = compose(a, v);
 }
 
 }  // namespace
@@ -614,7 +475,8 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
     // read them in the order of the ratios: one line of memory per token and not two (full_scan_kernel, 1024 rows of
     // 128256 tokens: 10.92 -> 9.57 ms, 256 rows: 3.45 -> 3.06 ms; full_sweep_rank_kernel, 256 rows: 3.54 -> 3.12 ms;
     // writing the pairs: 0.03-0.24 ms)
-    float2* pq = reinterpret_cast<float2*>(fp.rho_id + row * vs);   // the programs kernel writes the residuals there later
+    float2* pq = reinterpret_cast<float2*>(fp.rho_id + row * vs);   // the dense kernel writes the residuals there later
+    double* rho_id = fp.rho_id + row * vs; int* rank_of = fp.rank_of + row * vs;
     int kk = 0, close = 0;                                       // close: twice the sampled pairs of tokens that are near
     auto near = [&](unsigned long long x, unsigned long long y) { return (x >> lo) == (y >> lo) && (x >> id_bits) != (y >> id_bits); };
     for (int t0 = 0; t0 < V; t0 += 4 * kThreads) {               // 4 NT tokens per round
@@ -649,6 +511,11 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
                 const int off = kk + offs[j] + __popcll(mask[j] & ((1ull << lane) - 1ull));
                 k0[off] = e[j];
                 pq[t0 + j * kThreads + tid] = make_float2(pv[j], qv[j]);
+            } else if (fp.dense && t0 + j * kThreads + tid < V) {
+                // a token outside the support keeps all of p as residual
+                const double x = static_cast<double>(pv[j]);
+                rank_of[t0 + j * kThreads + tid] = -1;
+                rho_id[t0 + j * kThreads + tid] = (lg ? exp((x - p_ref) * inv_temp) : x) / ptot;
             }
         }
         kk += run;
@@ -738,187 +605,209 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
 }
 
 // ---- kernel 2: prefix sums in the order, F, H*, alpha*, suffix minima, residuals, records, blocks.
-__global__ __launch_bounds__(kThreads) void full_scan_kernel(FullParams fp) {
-    constexpr int kTile = 1024;
-    __shared__ double xin[2][kTile];
-    __shared__ double xout[2][kTile + 1];
-    __shared__ double red[kWaves];
-    __shared__ double dbuf[2][kThreads];
-    __shared__ int ibuf[2][kThreads];
-    const int tid = threadIdx.x, wv = tid >> 6, row = blockIdx.x;
+//
+// Ascending, in tiles of 2048 ranks: the pairs (p, q) by rank and every token's rank, and the sequential sums P (waves 0-3) and
+// Q (waves 4-7), eight terms per lane (RunSum).  A sum that leaves its binade inside the tile is right up to the lane where it
+// does; the lanes behind it go again with the new unit (a row's sums double some 40 times, mostly in its first tile).
+// Descending: F, its suffix minima G, residuals, records (F(m) <= G(m + 1); m = kk always) and the number of records behind
+// every rank, in one pass: below H* the suffix minimum is F(h) throughout, so residuals and records there come out 0 and none,
+// and h is the first record.
+// Bound: memory (84 bytes per token, of which a line for the gathered pair and one for the scattered rank).
+// One wave adding for each sum from LDS, and P, Q, F, the targets and the records' flags as arrays of their own: 9.5 ms for
+// 1024 rows of 128256 tokens, 3.06 for 256.
+__global__ __launch_bounds__(kScanThreads, 4) void full_scan_kernel(FullParams fp) {
+    constexpr int NT = kScanThreads, NW = NT / 64, CW = NW / 2, E = 8, kTile = 64 * CW * E, PER = kTile / NT;
+    static_assert(CW == 4 && PER == 4, "four waves per sum, four ranks per thread");
+    __shared__ double xs[2][kTile + kTile / E];                // a lane's eight terms, then its sums; one word of padding per lane
+    __shared__ RunSum run[NW];
+    __shared__ double upto[NW];
+    __shared__ int stop[NW];
+    __shared__ double wmin[2][NW];
+    __shared__ int wcnt[2][NW];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, row = blockIdx.x;
     const int V = fp.V, n = fp.n;
     const size_t vs = static_cast<size_t>(V) + 2;
     RowInfo info = fp.info[row];
     if (info.status == GR_ROW_BAD) return;
     const int kk = info.support;
-    const double inv_temp_q = fp.logits ? 1.0 / static_cast<double>(fp.draft_temperature ? fp.draft_temperature[row] : fp.temperature[row]) : 0.0;
+    const RowValues val(fp, info, row);
     const float2* pq = reinterpret_cast<const float2*>(fp.rho_id + row * vs);   // by token id
-    const int* order = fp.order + row * vs;
-    double* pn = fp.pn + row * vs; double* qn = fp.qn + row * vs;
-    double* P = fp.P + row * vs; double* Q = fp.Q + row * vs; double* F = fp.F + row * vs;
-    double* rho = fp.rho + row * vs; double* tgt = fp.tgt + row * vs;
-    int* flag = fp.flag + row * vs; int* blk = fp.blk + row * vs; int* blo = fp.blo + row * vs;
-    int* inT = fp.inT + row * vs; int* bcount = fp.bcount + row * vs;
+    float2* by_rank = reinterpret_cast<float2*>(fp.pn + row * vs);
+    const int* order = fp.order + row * vs; int* rank_of = fp.rank_of + row * vs;
+    double* P = fp.P + row * vs; double* Q = fp.Q + row * vs; double* rho = fp.rho + row * vs;
+    int* blk = fp.blk + row * vs; int* blo = fp.blo + row * vs; int* bcount = fp.bcount + row * vs; int* behind = fp.val0 + row * vs;
+    auto pad = [](int i) { return i + (i >> 3); };
 
-    for (int r0 = tid; r0 < kk; r0 += 4 * kThreads) {           // four independent gathers per thread in flight
-        int id[4]; float pv[4], qv[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) { const int r = r0 + j * kThreads; id[j] = r < kk ? order[r] : 0; }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const float2 x = r0 + j * kThreads < kk ? pq[id[j]] : make_float2(0.f, 0.f);
-            pv[j] = x.x; qv[j] = x.y;
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int r = r0 + j * kThreads;
-            if (r < kk) {
-                if (fp.logits) {
-                    pn[r] = exp((static_cast<double>(pv[j]) - info.p_ref) * info.inv_temp) / info.p_total;
-                    qn[r] = exp((static_cast<double>(qv[j]) - info.q_ref) * inv_temp_q);
-                } else {
-                    pn[r] = static_cast<double>(pv[j]) / info.p_total;
-                    qn[r] = static_cast<double>(qv[j]);          // raw q for now
-                }
-                inT[r] = 0;
-            }
-        }
-    }
+    const int chain = wv / CW, cw = wv % CW;
+    double acc = 0.0;                                          // the running sum of this wave's chain
     if (tid == 0) { P[0] = 0.0; Q[0] = 0.0; }
-    __syncthreads();
-    // sequential prefix sums, a tile at a time through LDS (wave 0: p, wave 1: q); the next tile is
-    // loaded into registers while the two waves scan
-    double carry_p = 0.0, carry_q = 0.0;
-    double np_[4], nq_[4];
+    int id[PER]; float2 x2[PER];                               // the next tile's pairs are on their way while this one is added up
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int i = j * kThreads + tid;
-        np_[j] = i < kk ? pn[i] : 0.0; nq_[j] = i < kk ? qn[i] : 0.0;
-    }
+    for (int j = 0; j < PER; ++j) { const int r = j * NT + tid; id[j] = r < kk ? order[r] : 0; }
+#pragma unroll
+    for (int j = 0; j < PER; ++j) x2[j] = j * NT + tid < kk ? pq[id[j]] : make_float2(0.f, 0.f);
     for (int t0 = 0; t0 < kk; t0 += kTile) {
-        const int cnt = min(kTile, kk - t0);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) { xin[0][j * kThreads + tid] = np_[j]; xin[1][j * kThreads + tid] = nq_[j]; }   // zeros beyond cnt
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int i = t0 + kTile + j * kThreads + tid;
-            np_[j] = i < kk ? pn[i] : 0.0; nq_[j] = i < kk ? qn[i] : 0.0;
+        for (int j = 0; j < PER; ++j) {
+            const int i = j * NT + tid, r = t0 + i;
+            const bool in = r < kk;
+            xs[0][pad(i)] = in ? val.p(x2[j].x) : 0.0; xs[1][pad(i)] = in ? val.q(x2[j].y) : 0.0;
+            if (in) { by_rank[r] = x2[j]; rank_of[id[j]] = r; }
         }
-        // 64 sums in registers: the chain of additions bounds this, and 16 at a time (71 registers for 171) lengthened it more
-        // than the further workgroups per compute unit gave: one row of 8192 tokens 143 -> 159 us, 256 of 128256 3.06 -> 3.33
-        // ms, 1024 9.57 -> 9.68 ms
-        if (wv == 0) wave_sequential_scan_padded(xin[0], xout[0], cnt, carry_p);
-        if (wv == 1) wave_sequential_scan_padded(xin[1], xout[1], cnt, carry_q);
+#pragma unroll
+        for (int j = 0; j < PER; ++j) { const int r = t0 + kTile + j * NT + tid; id[j] = r < kk ? order[r] : 0; }
         __syncthreads();
-        for (int i = tid; i < cnt; i += kThreads) { P[t0 + i + 1] = xout[0][i + 1]; Q[t0 + i + 1] = xout[1][i + 1]; }
-        carry_p = xout[0][cnt]; carry_q = xout[1][cnt];
-        // the next tile's scan, which overwrites xout, starts behind the next barrier
-    }
-    __syncthreads();                                            // P and Q are read back below by other threads than wrote them
-    const double stot = carry_q;
-    double fmin_local = 1e300, hcand = 1e18;                    // this thread's smallest F and the first rank that has it
-    {
+#pragma unroll
+        for (int j = 0; j < PER; ++j) x2[j] = t0 + kTile + j * NT + tid < kk ? pq[id[j]] : make_float2(0.f, 0.f);
+        double x[E], sum[E];
+        const int mine = (cw * 64 + lane) * (E + 1);
+#pragma unroll
+        for (int e = 0; e < E; ++e) { x[e] = xs[chain][mine + e]; sum[e] = 0.0; }
+        {
 #pragma clang fp contract(off)
-        for (int m0 = tid; m0 <= kk; m0 += 4 * kThreads) {
-            double Qv[4], Pv[4], qv[4];
+            for (int pos = 0;;) {                              // the lanes of the chain from `pos` on
+                const long long bits = __double_as_longlong(acc);
+                const double unit = __longlong_as_double(bits & 0x7FF0000000000000ll), odd = __longlong_as_double((bits & 0x7FF0000000000000ll) | 1ll);
+                const bool none = acc < 1e-290;                // nothing to speak of yet: the first term starts the sum
+                const bool act = cw * 64 + lane >= pos;
+                double a0 = unit, a1 = odd;
+                if (act) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int m = m0 + j * kThreads;
-                Qv[j] = m <= kk ? Q[m] : 0.0; Pv[j] = m <= kk ? P[m] : 0.0; qv[j] = m < kk ? qn[m] : 0.0;
-            }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int m = m0 + j * kThreads;
-                if (m <= kk) {
-                    const double Qm = Qv[j] / stot;
-                    Q[m] = Qm;
-                    const double Fm = (m == 0) ? 0.0 : Pv[j] - ipow(Qm, n);
-                    F[m] = Fm;
-                    if (Fm < fmin_local) { fmin_local = Fm; hcand = static_cast<double>(m); }   // ranks rise within a thread
-                    if (m < kk) qn[m] = qv[j] / stot;
+                    for (int e = 0; e < E; ++e) { a0 = a0 + x[e]; a1 = a1 + x[e]; }
                 }
-            }
-        }
-    }
-    __syncthreads();
-    // H*: the smallest minimising prefix
-    const double Fmin = block_min(fmin_local, red);
-    const int h = static_cast<int>(block_min(fmin_local == Fmin ? hcand : 1e18, red));
-    // G = suffix minima of F over m = 0..kk, tiles of 1024 from the top down (4 consecutive entries per
-    // thread); G is only needed here, so residuals, targets and records (F(m) <= G(m+1) for m >= h;
-    // m = kk always) are taken in the same sweep and G is never stored
-    {
-        double later = 1e300;                                   // min of F over the tiles above
-        const int ntile = (kk + 1 + kTile - 1) / kTile;
-        for (int t = ntile - 1; t >= 0; --t) {
-            const int m0 = t * kTile + tid * 4;
-            double a[4], pv[4];
+                RunSum v;
+                v.d[0] = a0 - unit; v.d[1] = a1 - odd;
+                v.par = static_cast<int>(__double_as_longlong(a0) & 1ll) | (static_cast<int>(__double_as_longlong(a1) & 1ll) << 1);
+                scan_step<0x111, 0xF>(v); scan_step<0x112, 0xF>(v); scan_step<0x114, 0xF>(v); scan_step<0x118, 0xF>(v);
+                scan_step<0x142, 0xA>(v); scan_step<0x143, 0xC>(v);
+                if (lane == 63) run[wv] = v;
+                RunSum before;                                 // the lanes before this one
+                before.d[0] = __shfl_up(v.d[0], 1); before.d[1] = __shfl_up(v.d[1], 1); before.par = __shfl_up(v.par, 1);
+                if (lane == 0) { before.d[0] = 0.0; before.d[1] = 0.0; before.par = 2; }
+                __syncthreads();
+                double delta = 0.0;
+                int s = static_cast<int>(bits & 1ll);
+                for (int w = 0; w < cw; ++w) { const RunSum c = run[chain * CW + w]; delta = delta + (s ? c.d[1] : c.d[0]); s = (c.par >> s) & 1; }
+                delta = delta + (s ? before.d[1] : before.d[0]);
+                double t = none ? acc : acc + delta;
+                const double start = t;
+                if (act) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) { a[j] = (m0 + j <= kk) ? F[m0 + j] : 1e300; pv[j] = (m0 + j < kk) ? pn[m0 + j] : 0.0; }
-            double s[4];
-            s[3] = a[3]; s[2] = fmin(a[2], s[3]); s[1] = fmin(a[1], s[2]); s[0] = fmin(a[0], s[1]);
-            double total;
-            const double after = fmin(block_suffix_min_excl(s[0], dbuf[0], dbuf[1], &total), later);   // G(m0 + 4)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int m = m0 + j;
-                if (m <= kk) {
-                    const double g = fmin(s[j], after);                                  // G(m)
-                    const double gn = (j < 3) ? fmin(s[j + 1], after) : after;           // G(m + 1), unused at m = kk
-                    flag[m] = (m >= h && (m == kk || a[j] <= gn)) ? 1 : 0;
-                    if (m < kk) {
-                        const double r = (m >= h) ? gn - g : 0.0;
-                        rho[m] = r; tgt[m] = pv[j] - r;
+                    for (int e = 0; e < E; ++e) { t = t + x[e]; sum[e] = t; }
+                }
+                const unsigned long long out = __ballot(act && (none ? t != start : !(t < 2.0 * unit)));
+                const int last = out ? __ffsll(static_cast<long long>(out)) - 1 : 63;
+                const double end = read_lane(t, last);
+                if (lane == 0) { upto[wv] = end; stop[wv] = out ? cw * 64 + last + 1 : 0; }
+                __syncthreads();
+                int next[2];
+                for (int c = 0; c < 2; ++c) {
+                    next[c] = 64 * CW;
+                    for (int w = 0; w < CW; ++w) {
+                        if (c == chain) acc = upto[c * CW + w];
+                        if (stop[c * CW + w]) { next[c] = stop[c * CW + w]; break; }
                     }
                 }
+                pos = next[chain];
+                if (next[0] == 64 * CW && next[1] == 64 * CW) break;
             }
-            later = fmin(later, total);
         }
+#pragma unroll
+        for (int e = 0; e < E; ++e) xs[chain][mine + e] = sum[e];
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const int i = j * NT + tid, r = t0 + i;
+            if (r < kk) { P[r + 1] = xs[0][pad(i)]; Q[r + 1] = xs[1][pad(i)]; }
+        }
+        __syncthreads();                                       // the next tile's terms take the place of these sums
     }
     __syncthreads();
-    // inclusive count of records -> block of each token outside H*, record positions
-    int nrec = 0;
-    {
-        const int ntile = (kk + 1 + kTile - 1) / kTile;
-        for (int t = 0; t < ntile; ++t) {
-            const int m0 = t * kTile + tid * 4;
-            int f[4];
+    const double stot = Q[kk];
+    // thread t holds four ranks, the last threads the first ones: what lies behind a rank is a scan over the threads
+    double later = 1e300;                                      // min of F over the tiles above
+    int nrec = 0;                                              // records in the tiles above
+    const int ntile = kk / kTile + 1;
+    double Pn[PER], Qn[PER];
+    auto fetch = [&](int t) {
+        const int m0 = t * kTile + (NT - 1 - tid) * PER;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) f[j] = (m0 + j <= kk) ? flag[m0 + j] : 0;
-            int total;
-            int run = nrec + block_prefix_sum_excl(f[0] + f[1] + f[2] + f[3], ibuf[0], ibuf[1], &total);
+        for (int j = 0; j < PER; ++j) { const bool in = t >= 0 && m0 + j <= kk; Pn[j] = in ? P[m0 + j] : 0.0; Qn[j] = in ? Q[m0 + j] : 0.0; }
+    };
+    fetch(ntile - 1);
+    for (int t = ntile - 1, b = 0; t >= 0; --t, b ^= 1) {
+#pragma clang fp contract(off)
+        const int m0 = t * kTile + (NT - 1 - tid) * PER;
+        double a[PER], s[PER];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int m = m0 + j;
-                if (m <= kk) {
-                    run += f[j];
-                    if (f[j]) blo[run] = m;                     // record number `run` (1-based) sits at rank m
-                    if (m < kk) blk[m] = (m >= h) ? run : 0;    // token m lies after record `run`
-                }
-            }
-            nrec += total;
+        for (int j = 0; j < PER; ++j) {
+            a[j] = 1e300;
+            if (m0 + j <= kk) a[j] = m0 + j == 0 ? 0.0 : Pn[j] - ipow(Qn[j] / stot, n);
         }
+        fetch(t - 1);
+        s[3] = a[3]; s[2] = fmin(a[2], s[3]); s[1] = fmin(a[1], s[2]); s[0] = fmin(a[0], s[1]);
+        const double incl = wave_scan_min(s[0]);
+        double after = __shfl_up(incl, 1);
+        if (lane == 0) after = 1e300;
+        if (lane == 63) wmin[b][wv] = incl;
+        __syncthreads();
+        double total = 1e300;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) { const double x = wmin[b][w]; total = fmin(total, x); if (w < wv) after = fmin(after, x); }
+        after = fmin(after, later);                            // G(m0 + 4)
+        int rec[PER], cnt = 0;
+#pragma unroll
+        for (int j = PER - 1; j >= 0; --j) {
+            const int m = m0 + j;
+            const double g = fmin(s[j], after), gn = j < PER - 1 ? fmin(s[j < PER - 1 ? j + 1 : j], after) : after;   // G(m), G(m + 1)
+            rec[j] = m <= kk && (m == kk || a[j] <= gn) ? 1 : 0;
+            cnt += rec[j];
+            if (m < kk) rho[m] = gn - g;
+        }
+        const int ci = wave_scan_i(cnt);
+        if (lane == 63) wcnt[b][wv] = ci;
+        __syncthreads();
+        int c = nrec + ci - cnt;                               // records behind this thread's ranks
+#pragma unroll
+        for (int w = 0; w < NW; ++w) { const int x = wcnt[b][w]; if (w < wv) c += x; nrec += x; }
+#pragma unroll
+        for (int j = PER - 1; j >= 0; --j) {
+            const int m = m0 + j;
+            if (m < kk) blk[m] = c;                            // for now the records behind token m
+            if (rec[j]) { behind[c] = m; ++c; }
+        }
+        later = fmin(later, total);
     }
     __syncthreads();
-    for (int b = tid; b <= nrec; b += kThreads) bcount[b] = 0;
+    // records in rising order, and every token's block: the records up to its rank
+    for (int m = tid; m < kk; m += NT) blk[m] = nrec - blk[m];
+    for (int i = tid; i <= nrec; i += NT) { bcount[i] = 0; if (i > 0) blo[i] = behind[nrec - i]; }
     if (tid == 0) {
+#pragma clang fp contract(off)
+        const int h = behind[nrec - 1];
+        const double Fh = h == 0 ? 0.0 : P[h] - ipow(Q[h] / stot, n);
         info.h = h;
-        info.alpha_star = 1.0 + F[h];
-        info.res_total = -F[h];
+        info.alpha_star = 1.0 + Fh;
+        info.res_total = -Fh;
         fp.info[row] = info;
         fp.nblk[row] = nrec - 1;
-        fp.accept_prob[row] = static_cast<float>(1.0 + F[h]);
+        fp.accept_prob[row] = static_cast<float>(1.0 + Fh);
     }
 }
 
 // ---- kernel 3: truncation sets (Alg. 1: fewest tokens by decreasing q with gamma_T <= tau inside H*,
 // epsilon_T <= tau outside), size of every program, row status.
-__global__ __launch_bounds__(kThreads) void full_trunc_kernel(FullParams fp) {
-    __shared__ SortLds S;
+//
+// Bound: the pass over q (twice, 4 bytes a token) and, where many tokens stay, their sort.  A workgroup of 256 threads that read
+// q in ratio order as float64 and sorted by eight passes of 12 bytes took 7.2 ms for 1024 rows of 128256 tokens.
+template <int NT>
+__global__ __launch_bounds__(NT) void full_trunc_kernel(FullParams fp) {
+    constexpr int kWaves = NT / 64;
+    __shared__ Sort32Lds<NT> S;
     __shared__ int cnt_in, cnt_out, act_in, capped, bsel;
-    __shared__ int wtot[8 * kWaves];
-    __shared__ double dscan[kThreads];
+    __shared__ int wtot[4 * kWaves];
+    __shared__ double dscan[gr::kThreads];
+    __shared__ double red[kWaves];
     __shared__ double wx[2][64];
     __shared__ double wo[2][65];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, row = blockIdx.x;
@@ -927,15 +816,26 @@ __global__ __launch_bounds__(kThreads) void full_trunc_kernel(FullParams fp) {
     const RowInfo info = fp.info[row];
     if (info.status == GR_ROW_BAD) return;
     const int kk = info.support, h = info.h;
+    const RowValues val(fp, info, row);
+    const bool lg = val.lg;
     const float* qr = fp.q + static_cast<size_t>(row) * V;
-    const int* order = fp.order + row * vs;
+    const int* order = fp.order + row * vs; const int* rank_of = fp.rank_of + row * vs;
+    const float2* by_rank = reinterpret_cast<const float2*>(fp.pn + row * vs);
     unsigned long long* k0 = fp.key0 + row * vs; unsigned long long* k1 = fp.key1 + row * vs;
-    int* v0 = fp.val0 + row * vs; int* v1 = fp.val1 + row * vs;
     int* byq = fp.byq + row * vs;
-    const double* qn = fp.qn + row * vs; const double* Q = fp.Q + row * vs; const double* tgt = fp.tgt + row * vs;
+    const double* Q = fp.Q + row * vs; const double* rho = fp.rho + row * vs;
     const int* blk = fp.blk + row * vs; const int* blo = fp.blo + row * vs;
-    int* inT = fp.inT + row * vs; int* bcount = fp.bcount + row * vs;
+    int* bcount = fp.bcount + row * vs;
+    const double stot = Q[kk];
+    auto qn = [&](int r) { return val.q(by_rank[r].y) / stot; };
+    auto target = [&](int r) { return val.p(by_rank[r].x) - rho[r]; };
 
+    // A large support is gone through in token order (its ties go to the lower id, and q is read as it lies), a small one by its ranks.
+    const bool ids = kk > V / 8;
+    const int count = ids ? V : kk;
+    auto member = [&](int i) { return i < count && (!ids || kk == V || rank_of[i] >= 0); };
+    auto raw = [&](int i) { return ids ? qr[i] : by_rank[i].y; };
+    auto cls = [&](float q) { return static_cast<int>(__float_as_uint(lg ? static_cast<float>(val.q(q)) : q) >> 19); };
     // A token joins a truncation set only while the mass before it leaves more than tau.  The lowest-q tokens whose
     // normalised masses sum to at most tau / n can therefore never join: before any of them lies everything else of
     // its side, so what is left is at most Q^n - (Q - tau/n)^n <= tau.  They are left out of the sort (found, safely,
@@ -943,91 +843,102 @@ __global__ __launch_bounds__(kThreads) void full_trunc_kernel(FullParams fp) {
     // the same arithmetic as before.
     int bstar = 0;
     if (fp.tau > 0.0) {
-        int* chist = reinterpret_cast<int*>(&S.wcnt[0][0][0]);
-        for (int c = tid; c < 4096; c += kThreads) chist[c] = 0;
+        int* chist = reinterpret_cast<int*>(&S);
+        static_assert(sizeof(S) >= 4096 * sizeof(int), "the class histogram borrows the sort's LDS");
+        for (int c = tid; c < 4096; c += NT) chist[c] = 0;
         __syncthreads();
-        for (int r = tid; r < kk; r += kThreads) {
-            const float qf = static_cast<float>(qn[r]);
-            if (qf > 0.f) atomicAdd(&chist[__float_as_uint(qf) >> 19], 1);
+        for (int i0 = tid; i0 < count; i0 += 4 * NT) {
+            float qv[4]; bool in[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) { const int i = i0 + j * NT; in[j] = member(i); qv[j] = i < count ? raw(i) : 0.f; }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) { const int c = in[j] ? cls(qv[j]) : 0; if (c > 0) atomicAdd(&chist[c], 1); }
         }
         __syncthreads();
-        bstar = class_threshold(chist, (fp.tau / static_cast<double>(n)) * (1.0 - 1e-6), dscan, &bsel);   // the margin covers the rounding of q to float
+        bstar = class_threshold(chist, (fp.tau / static_cast<double>(n)) * (1.0 - 1e-6) * stot, dscan, &bsel);   // the margin covers the rounding of q to float
     }
-    // ranks by (inside H* first, decreasing q, token id) of the tokens that stay, compacted in rank order
-    int kept = 0, kept_in = 0;
-    for (int t0 = 0; t0 < kk; t0 += 4 * kThreads) {               // 1024 ranks per round
-        int id[4]; float qv[4]; bool take[4]; unsigned long long mask[4];
+    // the tokens that stay: inside H* first, decreasing q (the leading 32 or 33 bits of an element), token id
+    int kept = 0, kin = 0;
+    for (int t0 = 0; t0 < count; t0 += 4 * NT) {
+        float qv[4]; bool take[4]; unsigned long long mask[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { const int i = t0 + j * NT + tid; take[j] = member(i); qv[j] = i < count ? raw(i) : 0.f; }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int r = t0 + j * kThreads + tid;
-            const float qf = r < kk ? static_cast<float>(qn[r]) : 0.f;
-            id[j] = 0; qv[j] = 0.f;
-            take[j] = r < kk && (bstar == 0 || static_cast<int>(__float_as_uint(qf) >> 19) >= bstar);
+            take[j] = take[j] && (bstar == 0 || cls(qv[j]) >= bstar);
             mask[j] = __ballot(take[j]);
-            const unsigned long long in_mask = __ballot(take[j] && r < h);
-            // a gather costs a whole line: only the tokens that stay read their id and q (all of them: 7.96 ms for 1024
-            // rows of 128256 tokens; these: 6.57 ms)
-            if (take[j]) { id[j] = order[r]; qv[j] = qr[id[j]]; }
-            if (lane == 0) { wtot[j * kWaves + wv] = __popcll(mask[j]); wtot[4 * kWaves + j * kWaves + wv] = __popcll(in_mask); }
+            if (lane == 0) wtot[j * kWaves + wv] = __popcll(mask[j]);
         }
         __syncthreads();
-        int run = 0, run_in = 0, offs[4] = {0, 0, 0, 0};
-#pragma unroll
-        for (int g = 0; g < 4 * kWaves; ++g) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) if (g == j * kWaves + wv) offs[j] = run;
-            run += wtot[g]; run_in += wtot[4 * kWaves + g];
-        }
+        int offs[4];
+        const int run = group_offsets<kWaves>(wtot, offs);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int r = t0 + j * kThreads + tid;
+            const int i = t0 + j * NT + tid;
             if (take[j]) {
-                const int off = kept + offs[j] + __popcll(mask[j] & ((1ull << lane) - 1ull));
-                // q < 2, so bit 31 of ~bits(q) is always set: it carries the class instead (seven digits, not eight)
-                // rows given as logits: decreasing q is decreasing draft logit, whose pattern needs all 32 bits; the class moves up
-                const unsigned long long qb = fp.logits
-                    ? (static_cast<unsigned long long>(~mono32(qv[j])) | (r < h ? 0ull : 0x100000000ull))
-                    : static_cast<unsigned long long>((~__float_as_uint(qv[j]) & 0x7FFFFFFFu) | (r < h ? 0u : 0x80000000u));
-                k0[off] = (qb << 24) | static_cast<unsigned long long>(id[j]);
-                v0[off] = r;
+                const int id = ids ? i : order[i], r = ids ? rank_of[i] : i;
+                const bool in = r < h;
+                kin += in;
+                // q < 2, so bit 31 of ~bits(q) is always set: it carries the class instead; a draft logit's pattern needs all 32 bits
+                k0[kept + offs[j] + __popcll(mask[j] & ((1ull << lane) - 1ull))] =
+                    lg ? (static_cast<unsigned long long>(~mono32(qv[j])) << 31) | (in ? 0ull : 0x8000000000000000ull) | static_cast<unsigned>(id)
+                       : pack32((~__float_as_uint(qv[j]) & 0x7FFFFFFFu) | (in ? 0u : 0x80000000u), id);
             }
         }
-        kept += run; kept_in += run_in;
+        kept += run;
         __syncthreads();
     }
+    const int kept_in = block_sum_i<kWaves>(kin, red);
     if (tid == 0) { cnt_in = 0; cnt_out = 0; act_in = 0; capped = 0; }
-    __syncthreads();
-    const int* sorted = v0;
-    if (kept > 0) {
-        const int res = block_radix_sort(k0, v0, k1, v1, kept, S);
-        sorted = res ? v1 : v0;
+    const int id_shift = lg ? 31 : 32;
+    auto id_of = [&](unsigned long long e) { return static_cast<int>(e & ((1ull << id_shift) - 1ull)); };
+    if (kept <= NT) {
+        // few of them, the common case: every thread counts what comes before its own
+        const unsigned long long mine = tid < kept ? k0[tid] : ~0ull;
+        S.tile[tid] = mine;
+        __syncthreads();
+        if (tid < kept) {
+            int at = 0;
+#pragma unroll 8
+            for (int o = 0; o < kept; ++o) at += S.tile[o] < mine;
+            byq[at] = rank_of[id_of(mine)];
+        }
+    } else {
+        unsigned long long* e = k0;
+        auto other = [&]() { return e == k0 ? k1 : k0; };
+        if (!ids) e = block_sort32<NT>(e, other(), kept, S, 0, 3);   // ids below 2^24
+        e = block_sort32<NT>(e, other(), kept, S, id_shift);
+        if (lg) e = block_sort32<NT>(e, other(), kept, S, 63, 1);
+        for (int i = tid; i < kept; i += NT) byq[i] = rank_of[id_of(e[i])];
     }
-    for (int i = tid; i < kept; i += kThreads) byq[i] = sorted[i];
     __syncthreads();
-    const double Qh = Q[h];
+    const double Qh = Q[h] / stot;
     // wave 0 walks H* by decreasing q, wave 1 the other tokens: a token joins T while the mass before
     // it leaves more than tau (running sums added one after the other, as a sequential loop would).
-    // The walk only counts; the ranks and masses of the next two rounds are already on their way.
+    // The walk only counts; the ranks and masses of the next two rounds are already on their way.  Inside H* it ends, the row
+    // capped, with more active tokens than a program may have.
     if (wv < 2) {
 #pragma clang fp contract(off)
         const int first = wv == 0 ? 0 : kept_in;                 // the tokens of H* that stayed come first
         const int len = wv == 0 ? kept_in : kept - kept_in;
         const double bound = wv == 0 ? ipow(Qh, n) : 1.0;
         double acc = wv == 0 ? 0.0 : Qh;
-        int taken = 0;
+        int taken = 0, active = 0;
         bool done = false;
         int r1 = (lane < len) ? byq[first + lane] : 0;                        // ranks of round 0
         int r2 = (64 + lane < len) ? byq[first + 64 + lane] : 0;              // ranks of round 1
-        double m1 = (lane < len) ? qn[r1] : 0.0;                              // masses of round 0
+        double m1 = (lane < len) ? qn(r1) : 0.0;                              // masses of round 0
         for (int base = 0; base < len && !done; base += 64) {
             const bool valid = base + lane < len;
             const double mine = m1;
-            m1 = (base + 64 + lane < len) ? qn[r2] : 0.0;
+            const bool act = wv == 0 && valid && target(r1) > 0.0;
+            m1 = (base + 64 + lane < len) ? qn(r2) : 0.0;
+            r1 = r2;
             r2 = (base + 128 + lane < len) ? byq[first + base + 128 + lane] : 0;
             // running sums through a wave-private LDS strip (broadcast reads; see the padded scan)
             wx[wv][lane] = mine;
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); __builtin_amdgcn_wave_barrier();
-            wave_sequential_scan_padded(wx[wv], wo[wv], 64, acc);
+            wave_sequential_scan_padded<32>(wx[wv], wo[wv], 64, acc);
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); __builtin_amdgcn_wave_barrier();
             const double before = wo[wv][lane];
             acc = wo[wv][64];
@@ -1038,34 +949,23 @@ __global__ __launch_bounds__(kThreads) void full_trunc_kernel(FullParams fp) {
             int upto = 64;                                       // lanes below `upto` join T
             if (out_mask) { upto = __ffsll(static_cast<long long>(out_mask)) - 1; done = true; }
             taken += __popcll(__ballot(valid && lane < upto));
+            active += __popcll(__ballot(act && lane < upto));
+            done = done || active > fp.max_T;
         }
-        if (lane == 0) { if (wv == 0) cnt_in = taken; else cnt_out = taken; }
+        if (lane == 0) { if (wv == 0) { cnt_in = taken; act_in = active; } else cnt_out = taken; }
     }
     __syncthreads();
-    // mark the members of both sets; count the active ones per program
+    // count the active tokens of every program outside H*
     {
-        const int nin = cnt_in, nout = cnt_out;
-        int act = 0;
-        for (int i0 = tid; i0 < nin; i0 += 4 * kThreads) {
-            int r[4]; double t[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) { const int i = i0 + j * kThreads; r[j] = i < nin ? byq[i] : -1; }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) t[j] = r[j] >= 0 ? tgt[r[j]] : 0.0;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) if (r[j] >= 0) { inT[r[j]] = 1; act += t[j] > 0.0; }
-        }
-        if (act) atomicAdd(&act_in, act);
-        for (int i0 = tid; i0 < nout; i0 += 4 * kThreads) {
+        const int nout = cnt_out;
+        for (int i0 = tid; i0 < nout; i0 += 4 * NT) {
             int r[4]; double t[4]; int bl[4];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) { const int i = i0 + j * kThreads; r[j] = i < nout ? byq[kept_in + i] : -1; }
+            for (int j = 0; j < 4; ++j) { const int i = i0 + j * NT; r[j] = i < nout ? byq[kept_in + i] : -1; }
 #pragma unroll
-            for (int j = 0; j < 4; ++j) { t[j] = r[j] >= 0 ? tgt[r[j]] : 0.0; bl[j] = r[j] >= 0 ? blk[r[j]] : 0; }
+            for (int j = 0; j < 4; ++j) { t[j] = r[j] >= 0 ? target(r[j]) : 0.0; bl[j] = r[j] >= 0 ? blk[r[j]] : 0; }
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                if (r[j] < 0) continue;
-                inT[r[j]] = 1;
                 if (t[j] > 0.0 && blo[bl[j] + 1] - blo[bl[j]] >= 2) {
                     const int old = atomicAdd(&bcount[bl[j]], 1);
                     if (old + 1 > fp.max_T) capped = 1;
@@ -1076,11 +976,54 @@ __global__ __launch_bounds__(kThreads) void full_trunc_kernel(FullParams fp) {
     __syncthreads();
     if (tid == 0) {
         const int status = (act_in > fp.max_T || capped) ? GR_ROW_TRUNC_CAP : GR_ROW_OK;
-        fp.tcount[2 * row] = cnt_in; fp.tcount[2 * row + 1] = cnt_out;
+        fp.tcount[3 * row] = cnt_in; fp.tcount[3 * row + 1] = cnt_out; fp.tcount[3 * row + 2] = kept_in;
         RowInfo out = info;
         out.status = status;
         fp.info[row] = out;
         fp.status[row] = status;
+    }
+}
+
+// ---- kernel 4: the dense per-token arrays that the verify and slice kernels read, of the rows within the cap: start weights by
+// rank (target / Pr[token drawn within its system], inner ones in the slack's gauge) and the residuals by token id.
+// grid = (4096 ranks, B).  Bound: memory.  Inside the programs kernel, one workgroup of 512 threads to a compute unit, these arrays were
+// most of the 4.8 ms for 1024 rows of 128256 tokens.
+__global__ __launch_bounds__(kThreads) void full_dense_kernel(FullParams fp) {
+    const int row = blockIdx.y, V = fp.V, n = fp.n;
+    const size_t vs = static_cast<size_t>(V) + 2;
+    const RowInfo info = fp.info[row];
+    const int kk = info.support, h = info.h;
+    if (info.status != GR_ROW_OK || static_cast<int>(blockIdx.x) * kDenseRanks >= kk) return;
+    const RowValues val(fp, info, row);
+    const float2* by_rank = reinterpret_cast<const float2*>(fp.pn + row * vs);
+    const int* order = fp.order + row * vs; const int* blk = fp.blk + row * vs; const int* blo = fp.blo + row * vs;
+    const double* Q = fp.Q + row * vs; const double* rho = fp.rho + row * vs;
+    double* weight = fp.weight + row * vs; double* rho_id = fp.rho_id + row * vs;
+    const double stot = Q[kk];
+    const int end = min(kk, (static_cast<int>(blockIdx.x) + 1) * kDenseRanks);
+    for (int r0 = blockIdx.x * kDenseRanks + threadIdx.x; r0 < end; r0 += 4 * kThreads) {   // four independent chains of gathers per thread in flight
+        int hi[4], id[4]; double top[4], rv[4]; float2 x[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int r = r0 + j * kThreads;
+            const bool ok = r < end;
+            hi[j] = ok && r >= h ? blk[r] : 0;
+            x[j] = ok ? by_rank[r] : make_float2(0.f, 0.f); rv[j] = ok ? rho[r] : 0.0; id[j] = ok ? order[r] : 0;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { const int r = r0 + j * kThreads; hi[j] = (r < h || r >= end) ? h : blo[hi[j] + 1]; }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) top[j] = Q[hi[j]] / stot;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int r = r0 + j * kThreads;
+            if (r < end) {
+                const double t = val.p(x[j].x) - rv[j];
+                const double gauge = (r < h) ? ipow(top[j], n) / info.res_total : 1.0;
+                weight[r] = (t > 0.0) ? gauge * t / pow_diff(top[j], val.q(x[j].y) / stot, n) : 0.0;
+                rho_id[id[j]] = rv[j];
+            }
+        }
     }
 }
 
@@ -1281,8 +1224,10 @@ void launch_full_sweep(const FullParams& fp, const FullSweep& fs, hipStream_t st
 
 void launch_full_prologue(const FullParams& fp, hipStream_t stream) {
     launch_full_order(fp, stream);
-    hipLaunchKernelGGL(full_scan_kernel, dim3(fp.B), dim3(kThreads), 0, stream, fp);
-    hipLaunchKernelGGL(full_trunc_kernel, dim3(fp.B), dim3(kThreads), 0, stream, fp);
+    hipLaunchKernelGGL(full_scan_kernel, dim3(fp.B), dim3(kScanThreads), 0, stream, fp);
+    if (fp.V > 8192) hipLaunchKernelGGL(full_trunc_kernel<1024>, dim3(fp.B), dim3(1024), 0, stream, fp);
+    else hipLaunchKernelGGL(full_trunc_kernel<kThreads>, dim3(fp.B), dim3(kThreads), 0, stream, fp);
+    hipLaunchKernelGGL(full_dense_kernel, dim3((fp.V + kDenseRanks - 1) / kDenseRanks, fp.B), dim3(kThreads), 0, stream, fp);
 }
 
 }  // namespace gr

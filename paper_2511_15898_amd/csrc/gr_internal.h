@@ -67,7 +67,7 @@ struct SolveParams {
 };
 
 // Workspace and arguments of the full-vocabulary path (no top-k).  Per-token arrays are row-major with
-// stride V + 2; P, Q, F, G hold kk + 1 entries per row (prefix index 0..kk), blo the record positions.
+// stride V + 2; P and Q hold kk + 1 entries per row (prefix index 0..kk), blo the record positions.
 struct FullParams {
     const float* p; const float* q;
     int B, V, n, max_T, max_iter;
@@ -76,19 +76,21 @@ struct FullParams {
     double tail_mass;  // nucleus cut of the draft: share of the draw mass that may be left out (0: none)
     int logits; const float* temperature;   // rows given as logits (p = target logits, q = draft logits), one temperature per row
     const float* draft_temperature;         // [B] the draft's own temperature, or nullptr
-    unsigned long long* key0; unsigned long long* key1; int* val0; int* val1;   // sort buffers
+    unsigned long long* key0; unsigned long long* key1; int* val0;   // sort buffers
     int* order;        // token ids by decreasing q/p
     int* byq;          // ranks by (inside H* first, decreasing q, token id)
-    double* pn; double* qn; double* P; double* Q; double* F; double* rho; double* tgt; double* weight;
-    int* flag; int* blk; int* blo; int* inT; int* bcount;
+    double* pn; double* qn;   // solves: pn holds the raw pair (p, q) of every rank; sweeps: p / sum p and q by rank
+    double* P; double* Q; double* rho; double* weight;   // prefix sums (Q of the raw q: divide by Q[kk]), residuals and weights by rank
+    int* flag; int* blk; int* blo; int* bcount;
+    int dense;         // 1: a solve, whose policy needs what follows for every token
     int* rank_of;      // [B, V + 2] rank of each token id, -1 outside the support
-    double* rho_id;    // [B, V + 2] residual p(i) - p_i by token id (0 inside H*); before the programs kernel: the pair (p, q) of every token of the support
+    double* rho_id;    // [B, V + 2] residual p(i) - p_i by token id (0 inside H*); before the dense kernel: the pair (p, q) of every token of the support
     int* nblk;         // [B] number of outer blocks
-    int* tcount;       // [B, 2] sizes of the two truncation sets
+    int* tcount;       // [B, 3] sizes of the two truncation sets, place of the second in byq
     RowInfo* info; float* accept_prob; int* status;
     double* newton_ws; // [B, kMaxT * (kMaxT + 1)] Jacobian scratch of the Newton fallback
 };
-constexpr size_t kFullBytesPerToken = 2 * 8 + 2 * 4 + 2 * 4 + 8 * 8 + 5 * 4 + 4 + 8;
+constexpr size_t kFullBytesPerToken = 2 * 8 + 4 + 2 * 4 + 6 * 8 + 4 * 4 + 4 + 8;
 
 void launch_full_prologue(const FullParams& fp, hipStream_t stream);
 struct FullSweep;
@@ -234,6 +236,23 @@ __device__ __forceinline__ double wave_scan_min(double v) {
     v = fmin(v, dpp_shift<0x143, 0xC>(v, 1e300));
     return v;
 }
+
+// A row's values as the kernels behind the order take them: p / sum p and the raw draft weight, in float64.
+struct RowValues {
+    bool lg;
+    double ptot, p_ref, inv_temp, q_ref, inv_temp_q;
+    __device__ RowValues(const FullParams& fp, const RowInfo& info, int row)
+        : lg(fp.logits != 0), ptot(info.p_total), p_ref(info.p_ref), inv_temp(info.inv_temp), q_ref(info.q_ref),
+          inv_temp_q(fp.logits ? 1.0 / static_cast<double>(fp.draft_temperature ? fp.draft_temperature[row] : fp.temperature[row]) : 0.0) {}
+    __device__ __forceinline__ double p(float v) const {
+        const double x = static_cast<double>(v);
+        return (lg ? exp((x - p_ref) * inv_temp) : x) / ptot;
+    }
+    __device__ __forceinline__ double q(float v) const {
+        const double x = static_cast<double>(v);
+        return lg ? exp((x - q_ref) * inv_temp_q) : x;
+    }
+};
 
 // Workgroup reductions over NW waves.  `red` is an LDS array of at least NW doubles; both barriers are inside, so `red` may be reused right after the call.
 template <int NW = kWaves>

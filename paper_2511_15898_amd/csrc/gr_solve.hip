@@ -97,7 +97,7 @@ struct Lds {
     double aR0, alc;                      // ... the slack mass and, with slack, log(slack mass / its target)
     double ared[2][3];                    // ... and the first two waves' sum of R, max and min of log(target / R)
     double apd[kMaxT];              // Pr[token drawn within the program] = atot^n - (atot - q)^n
-    double aw[kMaxT]; double af[kMaxT]; int adeg[kMaxT];   // staging of the HBM-path programs kernel
+    double af[kMaxT];
     // Newton fallback (its Jacobian lives in a per-row HBM scratch)
     double nR[kMaxT]; double nstep[kMaxT]; double nsave[kMaxT]; int nused[kMaxT]; int ncolof[kMaxT];
     // scans and counters of the prologue (dead once the first program starts) share their bytes with the
@@ -1941,8 +1941,7 @@ __global__ __launch_bounds__(kThreadsOf<D>) void solve_kernel(SolveParams sp) {
     }
 }
 
-// ---- full-vocabulary policies: the convex programs of a row whose steps 1-2 were done in HBM.
-// Start weights of every support token, the dense per-token arrays the verify kernel reads, then the
+// ---- full-vocabulary policies: the convex programs of a row whose steps 1-2 were done in HBM: the
 // inner program over T inside H* and one outer program per block that holds two or more active
 // tokens of T -- the same programs, in the same arithmetic, as the LDS-resident path.
 template <int D>
@@ -1954,71 +1953,39 @@ __global__ __launch_bounds__(kThreadsOf<D>) void full_programs_kernel(FullParams
     const size_t vs = static_cast<size_t>(V) + 2;
     RowInfo info = fp.info[row];
     if (info.status == GR_ROW_BAD) return;
+    if (info.status != GR_ROW_OK) return;                  // above the cap on |T|: sampled from p
     const int kk = info.support, h = info.h;
-    const float* pr = fp.p + static_cast<size_t>(row) * V;
-    const int* order = fp.order + row * vs; const int* byq = fp.byq + row * vs;
-    const double* qn = fp.qn + row * vs; const double* Q = fp.Q + row * vs; const double* F = fp.F + row * vs;
-    const double* rho = fp.rho + row * vs; const double* tgt = fp.tgt + row * vs;
-    const int* blk = fp.blk + row * vs; const int* blo = fp.blo + row * vs; const int* inT = fp.inT + row * vs;
-    const int* bcount = fp.bcount + row * vs;
-    double* weight = fp.weight + row * vs; double* rho_id = fp.rho_id + row * vs; int* rank_of = fp.rank_of + row * vs;
-    const double Fh = F[h];
-
-    // a row that exceeded the cap on |T| is sampled from p (no dense arrays, no weights are read for it)
-    if (info.status != GR_ROW_OK) return;
-    // tokens outside the support keep all of p as residual; then the support by rank
-    if (fp.logits) {
-        for (int i = tid; i < V; i += kST) { rank_of[i] = -1; rho_id[i] = exp((static_cast<double>(pr[i]) - info.p_ref) * info.inv_temp) / info.p_total; }
-    } else {
-        for (int i = tid; i < V; i += kST) { rank_of[i] = -1; rho_id[i] = static_cast<double>(pr[i]) / info.p_total; }
-    }
-    __syncthreads();
-    for (int r0 = tid; r0 < kk; r0 += 4 * kST) {             // four independent chains of gathers per thread in flight
-        int bl[4], hi[4], id[4]; double top[4], t[4], qv[4], rv[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int r = r0 + j * kST;
-            const bool ok = r < kk;
-            bl[j] = (ok && r >= h) ? blk[r] : 0;
-            t[j] = ok ? tgt[r] : 0.0; qv[j] = ok ? qn[r] : 0.0; rv[j] = ok ? rho[r] : 0.0; id[j] = ok ? order[r] : 0;
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) { const int r = r0 + j * kST; hi[j] = (r < h || r >= kk) ? h : blo[bl[j] + 1]; }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) top[j] = Q[hi[j]];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int r = r0 + j * kST;
-            if (r < kk) {
-                const double gauge = (r < h) ? ipow(top[j], n) / (-Fh) : 1.0;
-                weight[r] = (t[j] > 0.0) ? gauge * t[j] / pow_diff(top[j], qv[j], n) : 0.0;
-                rank_of[id[j]] = r; rho_id[id[j]] = rv[j];
-            }
-        }
-    }
-    if (info.status != GR_ROW_OK) return;
+    const RowValues val(fp, info, row);
+    const int* byq = fp.byq + row * vs;
+    const float2* by_rank = reinterpret_cast<const float2*>(fp.pn + row * vs);
+    const double* Q = fp.Q + row * vs; const double* rho = fp.rho + row * vs;
+    const int* blo = fp.blo + row * vs; const int* bcount = fp.bcount + row * vs;
+    double* weight = fp.weight + row * vs;
+    const double Fh = -info.res_total, stot = Q[kk];
+    auto qn = [&](int r) { return val.q(by_rank[r].y) / stot; };
+    auto target = [&](int r) { return val.p(by_rank[r].x) - rho[r]; };
     if (tid == 0) L.work = 0.0;
     __syncthreads();
 
     int status = GR_ROW_OK, evals = 0, par = 0;
     // ---- inner program: T inside H* is the first tcount[0] entries of byq, already by decreasing q
     if (h > 0) {
-        const int c_in = fp.tcount[2 * row];
+        const int c_in = fp.tcount[3 * row];
         int m = 0;
         double ctx_part = 0.0;
         for (int base = 0; base < c_in; base += kST) {
             const int i = base + tid;
             const int r = i < c_in ? byq[i] : -1;
-            const double t = r >= 0 ? tgt[r] : 0.0;
+            const double t = r >= 0 ? target(r) : 0.0;
             const bool on = r >= 0 && t > 0.0;
-            if (r >= 0 && !on) ctx_part += qn[r];
+            if (r >= 0 && !on) ctx_part += qn(r);
             const unsigned long long mask = __ballot(on);
             if (lane == 0) L.hist[wv] = __popcll(mask);
             __syncthreads();
             int slot = m + __popcll(mask & ((1ull << lane) - 1ull));
             int tile_total = 0;
             for (int w = 0; w < kSW; ++w) { if (w < wv) slot += L.hist[w]; tile_total += L.hist[w]; }
-            if (on && slot < kMaxT) { L.apos[slot] = r; L.aq[slot] = qn[r]; L.at[slot] = t; L.aal[slot] = log(weight[r]); }
+            if (on && slot < kMaxT) { L.apos[slot] = r; L.aq[slot] = qn(r); L.at[slot] = t; L.aal[slot] = log(weight[r]); }
             m += tile_total;
             __syncthreads();
         }
@@ -2039,7 +2006,7 @@ __global__ __launch_bounds__(kThreadsOf<D>) void full_programs_kernel(FullParams
         }
     }
     // ---- outer programs: those blocks with two or more active tokens of T
-    const int nblk = fp.nblk[row];
+    const int nblk = fp.nblk[row], c_out = fp.tcount[3 * row + 1], at_out = fp.tcount[3 * row + 2];
     for (int b0 = 1; b0 <= nblk; b0 += KS) {               // windows of KS blocks: L.flag lists the window's programs
         const int bme = b0 + tid;
         const bool need = tid < KS && bme <= nblk && bcount[bme] >= 2;
@@ -2054,33 +2021,26 @@ __global__ __launch_bounds__(kThreadsOf<D>) void full_programs_kernel(FullParams
         for (int pi = 0; pi < nprog; ++pi) {
             const int b = L.flag[pi];
             const int lo = blo[b], hi = blo[b + 1];
-            // active tokens of the block, by rank
+            // its active tokens, by decreasing q as T lists them
             int m = 0;
-            for (int base = lo; base < hi; base += kST) {
-                const int r = base + tid;
-                const bool on = r < hi && inT[r] && tgt[r] > 0.0;
+            for (int base = 0; base < c_out; base += kST) {
+                const int i = base + tid, r = i < c_out ? byq[at_out + i] : -1;
+                const double t = r >= lo && r < hi ? target(r) : 0.0;
+                const bool on = t > 0.0;
                 const unsigned long long mask = __ballot(on);
                 if (lane == 0) L.hist[wv] = __popcll(mask);
                 __syncthreads();
                 int slot = m + __popcll(mask & ((1ull << lane) - 1ull));
                 int tile_total = 0;
                 for (int w = 0; w < kSW; ++w) { if (w < wv) slot += L.hist[w]; tile_total += L.hist[w]; }
-                if (on && slot < kMaxT) { L.adeg[slot] = r; L.af[slot] = qn[r]; L.aR[slot] = tgt[r]; L.aw[slot] = log(weight[r]); }
+                if (on && slot < kMaxT) { L.apos[slot] = r; L.aq[slot] = qn(r); L.at[slot] = t; L.aal[slot] = log(weight[r]); }
                 m += tile_total;
                 __syncthreads();
             }
             if (m < 2 || m > kMaxT) continue;               // cannot happen for a row with status OK
-            // by decreasing q (the evaluator takes its heavy tokens first), ties by rank
-            if (tid < m) {
-                const double qa = L.af[tid];
-                int pos = 0;
-                for (int j = 0; j < m; ++j) pos += (L.af[j] > qa) || (L.af[j] == qa && j < tid);
-                L.apos[pos] = L.adeg[tid]; L.aq[pos] = qa; L.at[pos] = L.aR[tid]; L.aal[pos] = L.aw[tid];
-            }
-            __syncthreads();
             const double qa = block_sum<kSW>(tid < m ? L.aq[tid] : 0.0, L.redn);
             const double ta = block_sum<kSW>(tid < m ? L.at[tid] : 0.0, L.redn);
-            const double ctx = Q[lo];
+            const double ctx = Q[lo] / stot;
             const double scale = pow_diff(ctx + qa, qa, n) / ta;
             const double w0sum = block_sum<kSW>(tid < m ? exp(L.aal[tid]) : 0.0, L.redn);
             if (tid < m) L.at[tid] *= scale;
