@@ -83,7 +83,7 @@ typedef struct {
  * up to max_n drafts (1..GR_MAX_N).  cfg may be NULL.
  * Device memory held by the handle until gr_destroy: about 150 KB per row (candidate keys, the policy
  * object of GR_MAX_SUPPORT entries, the Jacobian scratch of the solver's Newton fallback) plus 8 bytes per
- * 256 tokens and row; when max_k exceeds GR_MAX_SUPPORT, also 104 bytes per token of max_V and row (supports
+ * 256 tokens and row; when max_k exceeds GR_MAX_SUPPORT, also 96 bytes per token of max_V and row (supports
  * that large are ordered, scanned and kept in HBM; max_V must then stay below 2^24, otherwise
  * GR_EUNSUPPORTED).  GR_ENOMEM if it cannot be allocated. */
 int gr_create(gr_handle* out, int max_B, int max_V, int max_k, int max_n, const gr_config* cfg);

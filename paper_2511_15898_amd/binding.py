@@ -93,7 +93,7 @@ def _stream(stream) -> int:
 def gr_create(max_B: int, max_V: int, max_k: int = GR_MAX_SUPPORT, max_n: int = GR_MAX_N, max_iter: int = 0, max_T: int = 0,
               rel_tol: float = 0.0, flags: int = 0, tail_mass: float = 0.0) -> int:
     """max_k: largest top-k support the handle will serve (<= 0: whole rows; above GR_MAX_SUPPORT the handle
-    holds an HBM workspace of 104 bytes per token and row).  tail_mass: nucleus cut of the draft on that path."""
+    holds an HBM workspace of 96 bytes per token and row).  tail_mass: nucleus cut of the draft on that path."""
     cfg = GrConfig(max_iter, max_T, rel_tol, flags, tail_mass)
     h = ctypes.c_void_p()
     rc = load_library().gr_create(ctypes.byref(h), max_B, max_V, max_k, max_n, ctypes.byref(cfg))

@@ -120,7 +120,8 @@ int prepare_full(gr_handle h, int B, int V) {
     f.key0 = static_cast<unsigned long long*>(take(cnt * 8)); f.key1 = static_cast<unsigned long long*>(take(cnt * 8));
     f.val0 = static_cast<int*>(take(cnt * 4));
     f.order = static_cast<int*>(take(cnt * 4)); f.byq = static_cast<int*>(take(cnt * 4));
-    double** dbl[] = {&f.pn, &f.qn, &f.P, &f.Q, &f.rho, &f.weight, &f.rho_id};
+    f.pairs = static_cast<float2*>(take(cnt * 8));
+    double** dbl[] = {&f.P, &f.Q, &f.rho, &f.weight, &f.rho_id};
     for (double** d : dbl) *d = static_cast<double*>(take(cnt * 8));
     int** ints[] = {&f.flag, &f.blk, &f.blo, &f.bcount, &f.rank_of};
     for (int** d : ints) *d = static_cast<int*>(take(cnt * 4));
@@ -259,7 +260,7 @@ extern "C" int gr_create(gr_handle* out, int max_B, int max_V, int max_k, int ma
         h->tail_mass = cfg->tail_mass;
     }
     if (hipGetDevice(&h->device) != hipSuccess) { delete h; return GR_EHIP; }
-    if (solve_kernel_setup() != hipSuccess) { delete h; return GR_EHIP; }
+    if (solve_kernel_setup() != hipSuccess || full_kernel_setup() != hipSuccess) { delete h; return GR_EHIP; }
     { unsigned char* na = nullptr; (void)scratch_address(&na); }      // so that gr_accept_sweep_noalloc finds its array later
     const size_t rows = static_cast<size_t>(max_B);
     bool ok = dev_alloc(&h->cand, rows * kMaxSplits * kMaxSupport) && dev_alloc(&h->cand_count, rows * kMaxSplits) &&
@@ -273,7 +274,7 @@ extern "C" int gr_create(gr_handle* out, int max_B, int max_V, int max_k, int ma
          dev_alloc(&h->part_pref, rows * kMaxSplits);
     ok = ok && dev_alloc(&h->newton_ws, rows * kMaxT * (kMaxT + 1));
     if (ok && k_cap > kMaxSupport) {
-        // supports above GR_MAX_SUPPORT live in HBM: 104 bytes per token of max_V and row, held until gr_destroy
+        // supports above GR_MAX_SUPPORT live in HBM: 96 bytes per token of max_V and row, held until gr_destroy
         const size_t need = full_ws_bytes(rows, static_cast<size_t>(max_V) + 2);
         ok = hipMalloc(&h->full_ws, need) == hipSuccess && dev_alloc(&h->sweep_mass, rows * kSweepMaxK);
         if (ok) h->full_ws_bytes = need;

@@ -15,7 +15,9 @@ namespace {
 
 constexpr int kSortItems = 4;                      // keys per thread and tile
 constexpr int kScanThreads = 512;                  // of the kernel that takes the prefix sums
-constexpr int kDenseRanks = 4096;                  // ranks per workgroup of the kernel that writes the dense arrays
+constexpr int kChunkRanks = 4096;                  // ranks per workgroup of the kernels that gather and scatter by token id ...
+constexpr int kChunkLds = 40 * 1024;               // ... and the LDS that a workgroup of 256 threads reserves, for four of them to a compute unit (see full_gather_kernel)
+constexpr int kGatherThreads = 512, kGatherLds = 80 * 1024;
 // The sort of the large supports: elements of 8 bytes, the key in the high bits and the token id in the low ones.
 template <int NT>
 struct Sort32Lds {
@@ -210,6 +212,37 @@ __device__ int class_threshold(const int* chist, double budget, double* dscan, i
     return b == 4096 ? 0 : b;
 }
 
+// The lowest class c (4096: none) with enough(mass of the classes below it), the mass bounded from below: count x lower edge.
+template <class F>
+__device__ int definite_class(const int* chist, F enough, double* dscan, int* bsel) {
+    const int tid = threadIdx.x;
+    auto least = [&](int c) { return static_cast<double>(chist[c]) * static_cast<double>(__uint_as_float(static_cast<unsigned>(c) << 19)); };
+    if (tid < kThreads) {
+        double local = 0.0;
+        for (int c = 16 * tid; c < 16 * tid + 16; ++c) local += least(c);
+        dscan[tid] = local;
+    }
+    if (tid == 0) *bsel = 4096;
+    __syncthreads();
+    if (tid == 0) {
+        double run = 0.0;
+#pragma unroll 32
+        for (int t = 0; t < kThreads; ++t) { const double v = dscan[t]; dscan[t] = run; run += v; }
+    }
+    __syncthreads();
+    if (tid < kThreads) {
+        double run = dscan[tid];
+        for (int c = 16 * tid; c < 16 * tid + 16; ++c) {
+            if (enough(run)) { atomicMin(bsel, c); break; }
+            run += least(c);
+        }
+    }
+    __syncthreads();
+    const int b = *bsel;
+    __syncthreads();
+    return b;
+}
+
 __device__ void mark_bad(const FullParams& fp, int row, double ptot, double qtot) {
     RowInfo info;
     info.support = 0; info.h = 0; info.status = GR_ROW_BAD; info.iterations = 0;
@@ -218,6 +251,17 @@ __device__ void mark_bad(const FullParams& fp, int row, double ptot, double qtot
     fp.info[row] = info;
     fp.accept_prob[row] = __uint_as_float(0x7fc00000u);
     fp.status[row] = GR_ROW_BAD;
+}
+
+// Workgroups of a kernel that goes through all rows in chunks of kChunkRanks ranks: a launch of chunk_grid() workgroups of one dimension.  A chunk
+// reads or writes by token id, anywhere in its row's arrays, so the chunks of a row should share an L2: with eight rows or more to each XCD
+// (workgroups go round the XCDs) a row's chunks stay on one.
+__host__ __device__ inline bool rows_to_xcds(int B) { return B >= 64; }
+inline unsigned chunk_grid(int B, int chunks) { return static_cast<unsigned>(rows_to_xcds(B) ? (B + 7) / 8 * 8 : B) * static_cast<unsigned>(chunks); }
+__device__ __forceinline__ void chunk_of(int B, int chunks, int& row, int& chunk) {
+    const unsigned g = blockIdx.x;
+    if (rows_to_xcds(B)) { row = static_cast<int>((g >> 3) / chunks * 8 + (g & 7u)); chunk = static_cast<int>((g >> 3) % chunks); }
+    else { row = static_cast<int>(g / chunks); chunk = static_cast<int>(g % chunks); }
 }
 
 // What adding a run of terms one after the other does to a running sum, from its rounding alone.  While the sum stays in one
@@ -604,15 +648,44 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
     }
 }
 
-// ---- kernel 2: prefix sums in the order, F, H*, alpha*, suffix minima, residuals, records, blocks.
+// ---- kernel 2: the pairs (p, q) of the support by rank, and (solves) every token's rank.
+// Bound: memory, as long as a row's pairs and ranks (1.5 MB at V = 128256) stay in the L2 of the workgroups that share the row, which is why
+// few of them are resident: they reserve LDS (1024 rows: 2.6 ms with ten workgroups of 256 threads to a compute unit, 2.4 with four, 1.85 with
+// two, 1.97 with one).  Gathered and scattered by the scan kernel, a row to a workgroup, they took 5 of its 8.4 ms.
+__global__ __launch_bounds__(kGatherThreads) void full_gather_kernel(FullParams fp, int chunks) {
+    constexpr int NT = kGatherThreads;
+    int row, chunk;
+    chunk_of(fp.B, chunks, row, chunk);
+    if (row >= fp.B) return;
+    const size_t vs = static_cast<size_t>(fp.V) + 2;
+    const RowInfo info = fp.info[row];
+    if (info.status == GR_ROW_BAD) return;
+    const float2* pq = reinterpret_cast<const float2*>(fp.rho_id + row * vs);   // by token id
+    float2* by_rank = fp.pairs + row * vs;
+    const int* order = fp.order + row * vs; int* rank_of = fp.rank_of + row * vs;
+    const int end = min(info.support, (chunk + 1) * kChunkRanks);
+    for (int r0 = chunk * kChunkRanks + static_cast<int>(threadIdx.x); r0 < end; r0 += 8 * NT) {
+        int id[8]; float2 x[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) { const int r = r0 + j * NT; id[j] = r < end ? order[r] : 0; }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) if (r0 + j * NT < end) x[j] = pq[id[j]];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int r = r0 + j * NT;
+            if (r < end) { by_rank[r] = x[j]; if (fp.dense) rank_of[id[j]] = r; }
+        }
+    }
+}
+
+// ---- kernel 3: prefix sums in the order, F, H*, alpha*, suffix minima, residuals, records, blocks.
 //
-// Ascending, in tiles of 2048 ranks: the pairs (p, q) by rank and every token's rank, and the sequential sums P (waves 0-3) and
-// Q (waves 4-7), eight terms per lane (RunSum).  A sum that leaves its binade inside the tile is right up to the lane where it
+// Ascending, in tiles of 2048 ranks: the sequential sums P (waves 0-3) and Q (waves 4-7), eight terms per lane (RunSum).  A sum that leaves its binade inside the tile is right up to the lane where it
 // does; the lanes behind it go again with the new unit (a row's sums double some 40 times, mostly in its first tile).
 // Descending: F, its suffix minima G, residuals, records (F(m) <= G(m + 1); m = kk always) and the number of records behind
 // every rank, in one pass: below H* the suffix minimum is F(h) throughout, so residuals and records there come out 0 and none,
 // and h is the first record.
-// Bound: memory (84 bytes per token, of which a line for the gathered pair and one for the scattered rank).
+// Bound: memory (52 bytes per token) and the two passes' barriers.
 // One wave adding for each sum from LDS, and P, Q, F, the targets and the records' flags as arrays of their own: 9.5 ms for
 // 1024 rows of 128256 tokens, 3.06 for 256.
 __global__ __launch_bounds__(kScanThreads, 4) void full_scan_kernel(FullParams fp) {
@@ -631,9 +704,7 @@ __global__ __launch_bounds__(kScanThreads, 4) void full_scan_kernel(FullParams f
     if (info.status == GR_ROW_BAD) return;
     const int kk = info.support;
     const RowValues val(fp, info, row);
-    const float2* pq = reinterpret_cast<const float2*>(fp.rho_id + row * vs);   // by token id
-    float2* by_rank = reinterpret_cast<float2*>(fp.pn + row * vs);
-    const int* order = fp.order + row * vs; int* rank_of = fp.rank_of + row * vs;
+    const float2* by_rank = fp.pairs + row * vs;
     double* P = fp.P + row * vs; double* Q = fp.Q + row * vs; double* rho = fp.rho + row * vs;
     int* blk = fp.blk + row * vs; int* blo = fp.blo + row * vs; int* bcount = fp.bcount + row * vs; int* behind = fp.val0 + row * vs;
     auto pad = [](int i) { return i + (i >> 3); };
@@ -641,24 +712,19 @@ __global__ __launch_bounds__(kScanThreads, 4) void full_scan_kernel(FullParams f
     const int chain = wv / CW, cw = wv % CW;
     double acc = 0.0;                                          // the running sum of this wave's chain
     if (tid == 0) { P[0] = 0.0; Q[0] = 0.0; }
-    int id[PER]; float2 x2[PER];                               // the next tile's pairs are on their way while this one is added up
+    float2 x2[PER];                                            // the next tile's pairs are on their way while this one is added up
 #pragma unroll
-    for (int j = 0; j < PER; ++j) { const int r = j * NT + tid; id[j] = r < kk ? order[r] : 0; }
-#pragma unroll
-    for (int j = 0; j < PER; ++j) x2[j] = j * NT + tid < kk ? pq[id[j]] : make_float2(0.f, 0.f);
+    for (int j = 0; j < PER; ++j) x2[j] = j * NT + tid < kk ? by_rank[j * NT + tid] : make_float2(0.f, 0.f);
     for (int t0 = 0; t0 < kk; t0 += kTile) {
 #pragma unroll
         for (int j = 0; j < PER; ++j) {
             const int i = j * NT + tid, r = t0 + i;
             const bool in = r < kk;
             xs[0][pad(i)] = in ? val.p(x2[j].x) : 0.0; xs[1][pad(i)] = in ? val.q(x2[j].y) : 0.0;
-            if (in) { by_rank[r] = x2[j]; rank_of[id[j]] = r; }
         }
 #pragma unroll
-        for (int j = 0; j < PER; ++j) { const int r = t0 + kTile + j * NT + tid; id[j] = r < kk ? order[r] : 0; }
+        for (int j = 0; j < PER; ++j) { const int r = t0 + kTile + j * NT + tid; x2[j] = r < kk ? by_rank[r] : make_float2(0.f, 0.f); }
         __syncthreads();
-#pragma unroll
-        for (int j = 0; j < PER; ++j) x2[j] = t0 + kTile + j * NT + tid < kk ? pq[id[j]] : make_float2(0.f, 0.f);
         double x[E], sum[E];
         const int mine = (cw * 64 + lane) * (E + 1);
 #pragma unroll
@@ -795,11 +861,12 @@ __global__ __launch_bounds__(kScanThreads, 4) void full_scan_kernel(FullParams f
     }
 }
 
-// ---- kernel 3: truncation sets (Alg. 1: fewest tokens by decreasing q with gamma_T <= tau inside H*,
+// ---- kernel 4: truncation sets (Alg. 1: fewest tokens by decreasing q with gamma_T <= tau inside H*,
 // epsilon_T <= tau outside), size of every program, row status.
 //
 // Bound: the pass over q (twice, 4 bytes a token) and, where many tokens stay, their sort.  A workgroup of 256 threads that read
-// q in ratio order as float64 and sorted by eight passes of 12 bytes took 7.2 ms for 1024 rows of 128256 tokens.
+// q in ratio order as float64 and sorted by eight passes of 12 bytes took 7.2 ms for 1024 rows of 128256 tokens; this without the
+// rows that are known to end above the cap before their sort, 4.5.
 template <int NT>
 __global__ __launch_bounds__(NT) void full_trunc_kernel(FullParams fp) {
     constexpr int kWaves = NT / 64;
@@ -820,7 +887,7 @@ __global__ __launch_bounds__(NT) void full_trunc_kernel(FullParams fp) {
     const bool lg = val.lg;
     const float* qr = fp.q + static_cast<size_t>(row) * V;
     const int* order = fp.order + row * vs; const int* rank_of = fp.rank_of + row * vs;
-    const float2* by_rank = reinterpret_cast<const float2*>(fp.pn + row * vs);
+    const float2* by_rank = fp.pairs + row * vs;
     unsigned long long* k0 = fp.key0 + row * vs; unsigned long long* k1 = fp.key1 + row * vs;
     int* byq = fp.byq + row * vs;
     const double* Q = fp.Q + row * vs; const double* rho = fp.rho + row * vs;
@@ -890,6 +957,62 @@ __global__ __launch_bounds__(NT) void full_trunc_kernel(FullParams fp) {
     }
     const int kept_in = block_sum_i<kWaves>(kin, red);
     if (tid == 0) { cnt_in = 0; cnt_out = 0; act_in = 0; capped = 0; }
+    __syncthreads();
+    // Many tokens that stay are a sort of their own, and most such rows end above the cap.  A token whose class leaves more than tau
+    // in the classes below it joins its set whatever the order within the classes, so where those alone exceed the cap, the row does.
+    if constexpr (NT >= 1024) {
+        if (kept > NT) {
+            int* chist = reinterpret_cast<int*>(&S);
+            static_assert(sizeof(S) >= 2 * 4096 * sizeof(int), "one histogram for each side");
+            for (int c = tid; c < 2 * 4096; c += NT) chist[c] = 0;
+            __syncthreads();
+            for (int r0 = tid; r0 < kk; r0 += 4 * NT) {
+                float qv[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) { const int r = r0 + j * NT; qv[j] = r < kk ? by_rank[r].y : 0.f; }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) { const int r = r0 + j * NT; if (r < kk) atomicAdd(&chist[(r < h ? 0 : 4096) + cls(qv[j])], 1); }
+            }
+            __syncthreads();
+            const double more = fp.tau * (1.0 + 1e-6) + 1e-12, Qh = Q[h] / stot;
+            const int c_in = definite_class(chist, [&](double m) { return ipow(Qh, n) - ipow(fmax(Qh - m / stot, 0.0), n) > more; }, dscan, &bsel);
+            const int c_out = definite_class(chist + 4096, [&](double m) { return 1.0 - ipow(1.0 - m / stot, n) > more; }, dscan, &bsel);
+            for (int r0 = 0; r0 < kk; r0 += 4 * NT) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int r = r0 + j * NT + tid;
+                    const float2 x = r < kk ? by_rank[r] : make_float2(0.f, 0.f);
+                    const bool in = r < kk && cls(x.y) >= (r < h ? c_in : c_out) && val.p(x.x) - rho[min(r, kk - 1)] > 0.0;
+                    if (in && r < h) { atomicAdd(&act_in, 1); }
+                    else if (in) {
+                        const int bl = blk[r];
+                        if (blo[bl + 1] - blo[bl] >= 2) {
+                            const int lead = __builtin_amdgcn_readfirstlane(bl);
+                            const unsigned long long same = __ballot(bl == lead);
+                            if (bl == lead) { if (lane == __ffsll(static_cast<long long>(same)) - 1 && atomicAdd(&bcount[bl], __popcll(same)) + __popcll(same) > fp.max_T) capped = 1; }
+                            else if (atomicAdd(&bcount[bl], 1) + 1 > fp.max_T) capped = 1;
+                        }
+                    }
+                }
+                __syncthreads();
+                const bool over = act_in > fp.max_T || capped != 0;
+                __syncthreads();
+                if (over) {
+                    if (tid == 0) {
+                        fp.tcount[3 * row] = 0; fp.tcount[3 * row + 1] = 0; fp.tcount[3 * row + 2] = 0;
+                        RowInfo out = info;
+                        out.status = GR_ROW_TRUNC_CAP;
+                        fp.info[row] = out;
+                        fp.status[row] = GR_ROW_TRUNC_CAP;
+                    }
+                    return;
+                }
+            }
+            for (int b = tid; b <= fp.nblk[row] + 1; b += NT) bcount[b] = 0;   // the walk counts again
+            if (tid == 0) act_in = 0;
+            __syncthreads();
+        }
+    }
     const int id_shift = lg ? 31 : 32;
     auto id_of = [&](unsigned long long e) { return static_cast<int>(e & ((1ull << id_shift) - 1ull)); };
     if (kept <= NT) {
@@ -984,24 +1107,27 @@ __global__ __launch_bounds__(NT) void full_trunc_kernel(FullParams fp) {
     }
 }
 
-// ---- kernel 4: the dense per-token arrays that the verify and slice kernels read, of the rows within the cap: start weights by
+// ---- kernel 5: the dense per-token arrays that the verify and slice kernels read, of the rows within the cap: start weights by
 // rank (target / Pr[token drawn within its system], inner ones in the slack's gauge) and the residuals by token id.
-// grid = (4096 ranks, B).  Bound: memory.  Inside the programs kernel, one workgroup of 512 threads to a compute unit, these arrays were
+// Bound: memory.  Inside the programs kernel, one workgroup of 512 threads to a compute unit, these arrays were
 // most of the 4.8 ms for 1024 rows of 128256 tokens.
-__global__ __launch_bounds__(kThreads) void full_dense_kernel(FullParams fp) {
-    const int row = blockIdx.y, V = fp.V, n = fp.n;
-    const size_t vs = static_cast<size_t>(V) + 2;
+__global__ __launch_bounds__(kThreads) void full_dense_kernel(FullParams fp, int chunks) {
+    int row, chunk;
+    chunk_of(fp.B, chunks, row, chunk);
+    if (row >= fp.B) return;
+    const int n = fp.n;
+    const size_t vs = static_cast<size_t>(fp.V) + 2;
     const RowInfo info = fp.info[row];
     const int kk = info.support, h = info.h;
-    if (info.status != GR_ROW_OK || static_cast<int>(blockIdx.x) * kDenseRanks >= kk) return;
+    if (info.status != GR_ROW_OK || chunk * kChunkRanks >= kk) return;
     const RowValues val(fp, info, row);
-    const float2* by_rank = reinterpret_cast<const float2*>(fp.pn + row * vs);
+    const float2* by_rank = fp.pairs + row * vs;
     const int* order = fp.order + row * vs; const int* blk = fp.blk + row * vs; const int* blo = fp.blo + row * vs;
     const double* Q = fp.Q + row * vs; const double* rho = fp.rho + row * vs;
     double* weight = fp.weight + row * vs; double* rho_id = fp.rho_id + row * vs;
     const double stot = Q[kk];
-    const int end = min(kk, (static_cast<int>(blockIdx.x) + 1) * kDenseRanks);
-    for (int r0 = blockIdx.x * kDenseRanks + threadIdx.x; r0 < end; r0 += 4 * kThreads) {   // four independent chains of gathers per thread in flight
+    const int end = min(kk, (chunk + 1) * kChunkRanks);
+    for (int r0 = chunk * kChunkRanks + static_cast<int>(threadIdx.x); r0 < end; r0 += 4 * kThreads) {   // four independent chains of gathers per thread in flight
         int hi[4], id[4]; double top[4], rv[4]; float2 x[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -1047,30 +1173,10 @@ __global__ __launch_bounds__(NT) void full_sweep_rank_kernel(FullParams fp, Full
     const RowInfo info = fp.info[row];
     if (info.status == GR_ROW_BAD) return;
     const int kk = info.support;
-    const float2* pq = reinterpret_cast<const float2*>(fp.rho_id + row * vs);   // by token id
     const float* qr = fp.q + static_cast<size_t>(row) * V;
     const int* order = fp.order + row * vs;
     unsigned long long* k0 = fp.key0 + row * vs; unsigned long long* k1 = fp.key1 + row * vs;
-    double* pn = fp.pn + row * vs; double* qn = fp.qn + row * vs;
     int* qrank = fp.blk + row * vs;                              // by ratio rank: the token's rank by decreasing q
-    for (int r0 = tid; r0 < kk; r0 += 4 * kThreads) {
-        int id[4]; float qv[4], pv[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) { const int r = r0 + j * kThreads; id[j] = r < kk ? order[r] : 0; }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const float2 x = r0 + j * kThreads < kk ? pq[id[j]] : make_float2(0.f, 0.f);
-            pv[j] = x.x; qv[j] = x.y;
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int r = r0 + j * kThreads;
-            if (r < kk) {
-                pn[r] = static_cast<double>(pv[j]) / info.p_total;
-                qn[r] = static_cast<double>(qv[j]);
-            }
-        }
-    }
     // the ranks by decreasing q, ties by id, and the q mass of the first k of them for every k of the grid
     double part[kSweepMaxK];
 #pragma unroll
@@ -1093,23 +1199,54 @@ __global__ __launch_bounds__(NT) void full_sweep_rank_kernel(FullParams fp, Full
             __syncthreads();
         }
     }
-    int* by_id = fp.blo + row * vs;                              // whole: q rank of every token id
-    for (int j = tid; j < kk; j += NT) {                         // the support is the first kk of the vocabulary by q
-        const int x = packed_id(sorted[j]);
-        double qv;
-        if (whole) { by_id[x] = j; qv = static_cast<double>(qr[x]); }
-        else { qrank[x] = j; qv = qn[x]; }
+    if (tid == 0) fp.tcount[3 * row] = whole ? (sorted == k0 ? 1 : 2) : 0;   // where full_qrank_kernel finds the tokens by q
+    for (int j0 = tid; j0 < kk; j0 += 4 * NT) {                  // the support is the first kk of the vocabulary by q
+        unsigned long long e[4];
 #pragma unroll
-        for (int a = 0; a < kSweepMaxK; ++a) if (a < fs.nk && j < fs.ks[a]) part[a] += qv;
-    }
-    if (whole) {
-        __syncthreads();
-        for (int r = tid; r < kk; r += NT) qrank[r] = by_id[order[r]];
+        for (int u = 0; u < 4; ++u) { const int j = j0 + u * NT; e[u] = j < kk ? sorted[j] : ~0ull; }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int j = j0 + u * NT;
+            if (j < kk && !whole) qrank[packed_id(e[u])] = j;
+            const double qv = static_cast<double>(__uint_as_float(~static_cast<unsigned>(e[u] >> 32)));   // 0 beyond kk
+#pragma unroll
+            for (int a = 0; a < kSweepMaxK; ++a) if (a < fs.nk && j < fs.ks[a]) part[a] += qv;
+        }
     }
 #pragma unroll
     for (int a = 0; a < kSweepMaxK; ++a) {
         const double t = block_sum<kWaves>(part[a], red);
         if (tid == 0 && a < fs.nk) fs.mass[row * kSweepMaxK + a] = t;
+    }
+}
+
+// Where the rank kernel sorted the whole vocabulary: the q rank of every token id (ids), then of every ratio rank.  Scattered and gathered
+// chunk by chunk from a row that stays in L2; one workgroup per row took 1.6 of the rank kernel's 3.1 ms for 256 rows of 128256 tokens.
+template <bool IDS>
+__global__ __launch_bounds__(kGatherThreads) void full_qrank_kernel(FullParams fp, int chunks) {
+    constexpr int NT = kGatherThreads;
+    int row, chunk;
+    chunk_of(fp.B, chunks, row, chunk);
+    if (row >= fp.B) return;
+    const size_t vs = static_cast<size_t>(fp.V) + 2;
+    const RowInfo info = fp.info[row];
+    if (info.status == GR_ROW_BAD) return;
+    const int where = fp.tcount[3 * row];
+    if (where == 0) return;
+    const unsigned long long* sorted = (where == 1 ? fp.key0 : fp.key1) + row * vs;
+    const int* order = fp.order + row * vs;
+    int* by_id = fp.blo + row * vs; int* qrank = fp.blk + row * vs;
+    const int end = min(info.support, (chunk + 1) * kChunkRanks);
+    for (int r0 = chunk * kChunkRanks + static_cast<int>(threadIdx.x); r0 < end; r0 += 8 * NT) {
+        int id[8], x[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) { const int r = r0 + j * NT; id[j] = r < end ? (IDS ? packed_id(sorted[r]) : order[r]) : 0; }
+        if (!IDS) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) x[j] = r0 + j * NT < end ? by_id[id[j]] : 0;
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) { const int r = r0 + j * NT; if (r < end) { if (IDS) by_id[id[j]] = r; else qrank[r] = x[j]; } }
     }
 }
 
@@ -1135,8 +1272,9 @@ __global__ __launch_bounds__(NT) void full_sweep_scan_kernel(FullParams fp, Full
         return;
     }
     const int kk = info.support;
-    const double* pn = fp.pn + row * vs; const double* qn = fp.qn + row * vs;
+    const float2* by_rank = fp.pairs + row * vs;
     const int* qrank = fp.blk + row * vs;
+    const double invp = 1.0 / info.p_total;
     const int ka = fs.ks[a];
     const double inv = 1.0 / fs.mass[row * kSweepMaxK + a];
     double best[kSweepMaxN];                                     // F(0) = 0: the empty prefix
@@ -1153,7 +1291,8 @@ __global__ __launch_bounds__(NT) void full_sweep_scan_kernel(FullParams fp, Full
             const int r = t0 + 4 * tid + j;
             const bool on = r < kk && qrank[r] < ka;
             any |= on;
-            accp += on ? pn[r] : 0.0; accs += on ? qn[r] : 0.0;
+            const float2 y = on ? by_rank[r] : make_float2(0.f, 0.f);
+            accp += static_cast<double>(y.x); accs += static_cast<double>(y.y);
             lp[j] = accp; ls[j] = accs;
         }
         const bool wave_on = __ballot(any) != 0ull;
@@ -1176,7 +1315,7 @@ __global__ __launch_bounds__(NT) void full_sweep_scan_kernel(FullParams fp, Full
         if (!wave_on) continue;                                  // uniform over the wave; no barrier below
         double x[4], pw[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) { lp[j] += bp; x[j] = (bs + ls[j]) * inv; pw[j] = x[j]; }
+        for (int j = 0; j < 4; ++j) { lp[j] = (lp[j] + bp) * invp; x[j] = (bs + ls[j]) * inv; pw[j] = x[j]; }
         int e = 1;
 #pragma unroll
         for (int b = 0; b < kSweepMaxN; ++b) {
@@ -1215,19 +1354,37 @@ static void launch_full_order(const FullParams& fp, hipStream_t stream) {
 
 void launch_full_sweep(const FullParams& fp, const FullSweep& fs, hipStream_t stream) {
     launch_full_order(fp, stream);
+    const int chunks = (fp.V + kChunkRanks - 1) / kChunkRanks;
+    const dim3 grid(chunk_grid(fp.B, chunks));
+    hipLaunchKernelGGL(full_gather_kernel, grid, dim3(kGatherThreads), kGatherLds, stream, fp, chunks);
     if (fp.V > 8192) hipLaunchKernelGGL(full_sweep_rank_kernel<1024>, dim3(fp.B), dim3(1024), 0, stream, fp, fs);
     else hipLaunchKernelGGL(full_sweep_rank_kernel<kThreads>, dim3(fp.B), dim3(kThreads), 0, stream, fp, fs);
+    hipLaunchKernelGGL(full_qrank_kernel<true>, grid, dim3(kGatherThreads), kGatherLds, stream, fp, chunks);
+    hipLaunchKernelGGL(full_qrank_kernel<false>, grid, dim3(kGatherThreads), kGatherLds, stream, fp, chunks);
     // a round of a 1024-thread workgroup is 4096 ranks: rows that fill fewer than two rounds take the small workgroup
     if (fp.V > 8192) hipLaunchKernelGGL(full_sweep_scan_kernel<1024>, dim3(fp.B, fs.nk), dim3(1024), 0, stream, fp, fs);
     else hipLaunchKernelGGL(full_sweep_scan_kernel<kThreads>, dim3(fp.B, fs.nk), dim3(kThreads), 0, stream, fp, fs);
 }
 
+// The reserved LDS of the chunk kernels lies above the default limit.
+hipError_t full_kernel_setup() {
+    const void* kernels[3] = {reinterpret_cast<const void*>(full_gather_kernel), reinterpret_cast<const void*>(full_qrank_kernel<true>),
+                              reinterpret_cast<const void*>(full_qrank_kernel<false>)};
+    for (const void* k : kernels) {
+        const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kGatherLds);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 void launch_full_prologue(const FullParams& fp, hipStream_t stream) {
     launch_full_order(fp, stream);
+    const int chunks = (fp.V + kChunkRanks - 1) / kChunkRanks;
+    hipLaunchKernelGGL(full_gather_kernel, dim3(chunk_grid(fp.B, chunks)), dim3(kGatherThreads), kGatherLds, stream, fp, chunks);
     hipLaunchKernelGGL(full_scan_kernel, dim3(fp.B), dim3(kScanThreads), 0, stream, fp);
     if (fp.V > 8192) hipLaunchKernelGGL(full_trunc_kernel<1024>, dim3(fp.B), dim3(1024), 0, stream, fp);
     else hipLaunchKernelGGL(full_trunc_kernel<kThreads>, dim3(fp.B), dim3(kThreads), 0, stream, fp);
-    hipLaunchKernelGGL(full_dense_kernel, dim3((fp.V + kDenseRanks - 1) / kDenseRanks, fp.B), dim3(kThreads), 0, stream, fp);
+    hipLaunchKernelGGL(full_dense_kernel, dim3(chunk_grid(fp.B, chunks)), dim3(kThreads), kChunkLds, stream, fp, chunks);
 }
 
 }  // namespace gr

@@ -79,7 +79,7 @@ struct FullParams {
     unsigned long long* key0; unsigned long long* key1; int* val0;   // sort buffers
     int* order;        // token ids by decreasing q/p
     int* byq;          // ranks by (inside H* first, decreasing q, token id)
-    double* pn; double* qn;   // solves: pn holds the raw pair (p, q) of every rank; sweeps: p / sum p and q by rank
+    float2* pairs;     // the raw pair (p, q) of every rank
     double* P; double* Q; double* rho; double* weight;   // prefix sums (Q of the raw q: divide by Q[kk]), residuals and weights by rank
     int* flag; int* blk; int* blo; int* bcount;
     int dense;         // 1: a solve, whose policy needs what follows for every token
@@ -90,7 +90,7 @@ struct FullParams {
     RowInfo* info; float* accept_prob; int* status;
     double* newton_ws; // [B, kMaxT * (kMaxT + 1)] Jacobian scratch of the Newton fallback
 };
-constexpr size_t kFullBytesPerToken = 2 * 8 + 4 + 2 * 4 + 6 * 8 + 4 * 4 + 4 + 8;
+constexpr size_t kFullBytesPerToken = 2 * 8 + 4 + 2 * 4 + 5 * 8 + 4 * 4 + 4 + 8;
 
 void launch_full_prologue(const FullParams& fp, hipStream_t stream);
 struct FullSweep;
@@ -144,6 +144,7 @@ struct FullSweep {
     int* status;                  // [B]
 };
 hipError_t solve_kernel_setup();
+hipError_t full_kernel_setup();
 
 // ---------------------------------------------------------------- device helpers
 // Wave reductions on the data-parallel-primitive path (no LDS round trip): a butterfly inside each

@@ -1957,7 +1957,7 @@ __global__ __launch_bounds__(kThreadsOf<D>) void full_programs_kernel(FullParams
     const int kk = info.support, h = info.h;
     const RowValues val(fp, info, row);
     const int* byq = fp.byq + row * vs;
-    const float2* by_rank = reinterpret_cast<const float2*>(fp.pn + row * vs);
+    const float2* by_rank = fp.pairs + row * vs;
     const double* Q = fp.Q + row * vs; const double* rho = fp.rho + row * vs;
     const int* blo = fp.blo + row * vs; const int* bcount = fp.bcount + row * vs;
     double* weight = fp.weight + row * vs;
