@@ -47,20 +47,26 @@ __device__ unsigned long long* block_sort32(unsigned long long* a, unsigned long
     for (int c = tid; c < 4 * 256; c += NT) (&S.hist[0][0])[c] = 0;
     if (tid < 4) S.skip[tid] = 0;
     __syncthreads();
-    for (int i0 = 0; i0 < count; i0 += NT) {
-        const int i = i0 + tid;
-        const bool valid = i < count;
-        const unsigned key = valid ? static_cast<unsigned>(a[i] >> lo) : 0u;
-        const unsigned long long vm = __ballot(valid);
-        if (vm == 0ull) continue;                               // wave-uniform; lane 0 is valid otherwise
+    for (int i0 = 0; i0 < count; i0 += 4 * NT) {
+        unsigned keys[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int d = static_cast<int>((key >> (8 * j)) & 255u);
-            const int d0 = __builtin_amdgcn_readfirstlane(d);
-            if (__ballot(valid && d == d0) == vm) {             // one digit in the whole wave: one update
-                if (lane == 0) atomicAdd(&S.hist[j][d0], __popcll(vm));
-            } else if (valid) {
-                atomicAdd(&S.hist[j][d], 1);
+        for (int u = 0; u < 4; ++u) { const int i = i0 + u * NT + tid; keys[u] = i < count ? static_cast<unsigned>(a[i] >> lo) : 0u; }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const bool valid = i0 + u * NT + tid < count;
+            const unsigned key = keys[u];
+            const unsigned long long vm = __ballot(valid);
+            if (vm == 0ull) continue;                           // wave-uniform; lane 0 is valid otherwise
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (j >= passes) break;
+                const int d = static_cast<int>((key >> (8 * j)) & 255u);
+                const int d0 = __builtin_amdgcn_readfirstlane(d);
+                if (__ballot(valid && d == d0) == vm) {         // one digit in the whole wave: one update
+                    if (lane == 0) atomicAdd(&S.hist[j][d0], __popcll(vm));
+                } else if (valid) {
+                    atomicAdd(&S.hist[j][d], 1);
+                }
             }
         }
     }
@@ -76,8 +82,7 @@ __device__ unsigned long long* block_sort32(unsigned long long* a, unsigned long
             int tot = 0;
 #pragma unroll
             for (int j = 0; j < 4; ++j) { next[j] = tot; tot += S.hist[pass][4 * lane + j]; }
-            int incl = tot;
-            for (int o = 1; o < 64; o <<= 1) { const int up = __shfl_up(incl, o); if (lane >= o) incl += up; }
+            const int incl = wave_scan_i(tot);
 #pragma unroll
             for (int j = 0; j < 4; ++j) next[j] += incl - tot;
         }
@@ -126,9 +131,7 @@ __device__ unsigned long long* block_sort32(unsigned long long* a, unsigned long
                 int c[4]; int tot = 0;
 #pragma unroll
                 for (int j = 0; j < 4; ++j) { c[j] = static_cast<int>((run >> (16 * j)) & 0xFFFFull); tot += c[j]; }
-                int incl = tot;
-                for (int o = 1; o < 64; o <<= 1) { const int up = __shfl_up(incl, o); if (lane >= o) incl += up; }
-                int at = incl - tot;
+                int at = wave_scan_i(tot) - tot;
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     S.start[4 * lane + j] = at; S.dest[4 * lane + j] = next[j] - at;
@@ -169,12 +172,10 @@ __device__ __forceinline__ int group_offsets(const int* wtot, int (&offs)[4]) {
     static_assert(4 * NW <= 64, "one group per lane");
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int v = lane < 4 * NW ? wtot[lane] : 0;
-    int incl = v;
-#pragma unroll
-    for (int o = 1; o < 4 * NW; o <<= 1) { const int up = __shfl_up(incl, o); if (lane >= o) incl += up; }
+    const int incl = wave_scan_i(v);
 #pragma unroll
     for (int j = 0; j < 4; ++j) offs[j] = __shfl(incl - v, j * NW + wv);
-    return __shfl(incl, 4 * NW - 1);
+    return __builtin_amdgcn_readlane(incl, 4 * NW - 1);
 }
 
 // chist[4096]: members per magnitude class of a positive float (its bit pattern >> 19: exponent and four mantissa
@@ -310,6 +311,9 @@ __device__ __forceinline__ void scan_step(RunSum& v) {
 // Bound: as the sort.  One workgroup of 256 threads per row and eight passes
 // over 12 bytes took 15.45 ms for 1024 rows of 128256 tokens and 4.47 ms for 256 of them; four passes over 8 bytes and
 // 1024 threads 6.03 and 1.42 ms.  (Two workgroups per compute unit, at half the registers, spilled and were slower.)
+// With four loads in flight in the passes over the row and in the histogram, which counts only the digits that are sorted by, and scans over
+// the lanes without LDS: 1024 rows 6295 -> 6059 us, 256 rows 1434 -> 1382 us, 64 rows cut by a nucleus 119 -> 105 us.  (24 leading bits first
+// where the sample shows no near pairs, and the runs that remain put in order from LDS: 256 rows 1360 us, but 1024 rows 7000-7740 us.)
 template <int NT>
 __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
     constexpr int kWaves = NT / 64;                              // this workgroup's waves
@@ -356,10 +360,12 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
         const float T = fp.temperature[row];
         const float Td = fp.draft_temperature ? fp.draft_temperature[row] : T;
         float tm = -__builtin_inff(), dm = -__builtin_inff(); int bad = !(T > 0.f) || !(T <= 3.0e38f) || !(Td > 0.f) || !(Td <= 3.0e38f);
-        for (int i = tid; i < V; i += kThreads) {
-            const float pv = pr[i], qv = qr[i];
-            bad |= !(pv + qv < 3.0e38f);
-            tm = fmaxf(tm, pv); dm = fmaxf(dm, qv);
+        for (int i0 = tid; i0 < V; i0 += 4 * kThreads) {
+            float pv[4], qv[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) { const int i = i0 + j * kThreads; pv[j] = i < V ? pr[i] : -__builtin_inff(); qv[j] = i < V ? qr[i] : -__builtin_inff(); }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) { bad |= !(pv[j] + qv[j] < 3.0e38f); tm = fmaxf(tm, pv[j]); dm = fmaxf(dm, qv[j]); }
         }
         p_ref = block_max<kWaves>(static_cast<double>(tm), red);
         q_ref = block_max<kWaves>(static_cast<double>(dm), red);
@@ -368,10 +374,15 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
         inv_temp_q = anybad ? 0.0 : 1.0 / static_cast<double>(Td);
         double ps = 0.0;
         if (!anybad && p_ref > -3.0e38 && q_ref > -3.0e38)
-            for (int i = tid; i < V; i += kThreads) {
-                const float pv = pr[i], qv = qr[i];
-                ps += exp((static_cast<double>(pv) - p_ref) * inv_temp);
-                if (early && qv > -3.0e38f) bounds(qv, pv);
+            for (int i0 = tid; i0 < V; i0 += 4 * kThreads) {
+                float pv[4], qv[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) { const int i = i0 + j * kThreads; pv[j] = i < V ? pr[i] : -__builtin_inff(); qv[j] = i < V ? qr[i] : -__builtin_inff(); }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    ps += exp((static_cast<double>(pv[j]) - p_ref) * inv_temp);
+                    if (early && qv[j] > -3.0e38f) bounds(qv[j], pv[j]);
+                }
             }
         ptot = block_sum<kWaves>(ps, red); qtot = 1.0;
         if (anybad || !(ptot >= 1.0) || !(ptot < 1e300)) {
@@ -380,11 +391,16 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
         }
     } else {
         double ps = 0.0, qs = 0.0; int bad = 0;
-        for (int i = tid; i < V; i += kThreads) {
-            const float pv = pr[i], qv = qr[i];
-            bad |= !(qv >= 0.f) | !(pv >= 0.f);
-            ps += static_cast<double>(pv); qs += static_cast<double>(qv);
-            if (early && qv > 0.f) bounds(qv, pv);
+        for (int i0 = tid; i0 < V; i0 += 4 * kThreads) {           // four tokens in flight
+            float pv[4], qv[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) { const int i = i0 + j * kThreads; pv[j] = i < V ? pr[i] : 0.f; qv[j] = i < V ? qr[i] : 0.f; }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                bad |= !(qv[j] >= 0.f) | !(pv[j] >= 0.f);
+                ps += static_cast<double>(pv[j]); qs += static_cast<double>(qv[j]);
+                if (early && qv[j] > 0.f) bounds(qv[j], pv[j]);
+            }
         }
         ptot = block_sum<kWaves>(ps, red);
         qtot = block_sum<kWaves>(qs, red);
@@ -414,9 +430,12 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
             __syncthreads();
             const double budget = fp.tail_mass * qtot;
             qmin = 0.5 * budget / static_cast<double>(V);
-            for (int i = tid; i < V; i += kThreads) {
-                const float qv = qr[i];
-                if (static_cast<double>(qv) >= qmin && qv > 0.f) atomicAdd(&chist[__float_as_uint(qv) >> 19], 1);
+            for (int i0 = tid; i0 < V; i0 += 4 * kThreads) {
+                float qv[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) { const int i = i0 + j * kThreads; qv[j] = i < V ? qr[i] : 0.f; }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) if (static_cast<double>(qv[j]) >= qmin && qv[j] > 0.f) atomicAdd(&chist[__float_as_uint(qv[j]) >> 19], 1);
             }
             __syncthreads();
             bstar = class_threshold(chist, 0.5 * budget, dscan, &bsel);
