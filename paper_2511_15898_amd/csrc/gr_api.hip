@@ -80,14 +80,18 @@ void free_all(gr_handle h) {
                 if (e) (void)hipEventDestroy(e);
 }
 
-// Number of workgroups that share a row in the select kernel: enough groups to keep every CU's
-// memory pipeline busy (about 8 per CU), slices no shorter than 4 tiles.
-int choose_splits(int B, int V) {
-    int s = 2048 / (B > 0 ? B : 1);
-    if (s < 1) s = 1;
-    if (s > kMaxSplits) s = kMaxSplits;
-    while (s > 1 && V / s < 4 * kSelTile) --s;
-    return s;
+// How the select kernel shares a row of V tokens among workgroups: about 8 of them for every CU, each with a slice of
+// whole tiles, kMinTiles at least, and the k keys that each may keep fit the row's candidates together.
+// At least 4 tiles / 2 / 1: one row of 32000 tokens, k = 64, selection and solve 10.3 + 40.8 / 8.6 + 41.6 / 6.4 + 43.6 us, a tree's
+// level of 32 to 128 rows 14.0 + 84.2 / 10.6 + 84.3 / 8.5 + 88.7 us (the solve merges the slices' candidates).
+struct Slices { int count, len; };
+Slices choose_slices(int B, int V, int k) {
+    constexpr int kMinTiles = 2;
+    const int tiles = (V + kSelTile - 1) / kSelTile;
+    int s = 2048 / B;
+    s = std::min(std::min(s, kMaxSplits), std::min(kSelCap / k, tiles / kMinTiles));
+    const int each = (tiles + std::max(s, 1) - 1) / std::max(s, 1);
+    return Slices{(tiles + each - 1) / each, each * kSelTile};
 }
 
 PolicyView policy_view(gr_handle h) {
@@ -135,8 +139,8 @@ int prepare_full(gr_handle h, int B, int V) {
 namespace {
 
 constexpr size_t kNoAllocRows = GR_NOALLOC_MAX_B;
-constexpr size_t kNaCand = 0;                                                                  // u64 [rows, kMaxSplits, kMaxSupport]
-constexpr size_t kNaPsum = kNaCand + kNoAllocRows * kMaxSplits * kMaxSupport * sizeof(unsigned long long);   // f64 [rows, kMaxSplits]
+constexpr size_t kNaCand = 0;                                                                  // u64 [rows, kSelCap]
+constexpr size_t kNaPsum = kNaCand + kNoAllocRows * kSelCap * sizeof(unsigned long long);   // f64 [rows, kMaxSplits]
 constexpr size_t kNaQsum = kNaPsum + kNoAllocRows * kMaxSplits * sizeof(double);              // f64 [rows, kMaxSplits]
 constexpr size_t kNaCount = kNaQsum + kNoAllocRows * kMaxSplits * sizeof(double);             // i32 [rows, kMaxSplits]
 constexpr size_t kNaBad = kNaCount + kNoAllocRows * kMaxSplits * sizeof(int);                 // i32 [rows, kMaxSplits]
@@ -210,21 +214,19 @@ int solve_in_lds(gr_handle h, const float* p, const float* q, const float* tempe
                  float* accept_prob, int* status, hipStream_t stream, const int* drafts = nullptr, const float* uniforms = nullptr,
                  int* token = nullptr, unsigned char* accepted = nullptr, const long long* row_at = nullptr, const int* row_n = nullptr) {
     h->full_mode = false;
-    const int splits = choose_splits(B, V);
-    int slice_len = (V + splits - 1) / splits;
-    slice_len = (slice_len + kSelTile - 1) / kSelTile * kSelTile;
+    const Slices cut = choose_slices(B, V, k_eff);
     h->solved = false;
     mark(h, 0, stream);
     if (temperature)
-        launch_select_logits(p, q, temperature, B, V, k_eff, splits, slice_len, h->cand, h->cand_count, h->part_psum, h->part_qsum,
+        launch_select_logits(p, q, temperature, B, V, k_eff, cut.count, cut.len, h->cand, h->cand_count, h->part_psum, h->part_qsum,
                              h->part_bad, h->part_pref, h->piece_psum, h->piece_pref, h->piece_stride, row_at, stream);
     else
-        launch_select(p, q, B, V, k_eff, splits, slice_len, h->cand, h->cand_count, h->part_psum, h->part_qsum,
+        launch_select(p, q, B, V, k_eff, cut.count, cut.len, h->cand, h->cand_count, h->part_psum, h->part_qsum,
                       h->part_bad, h->piece_psum, h->piece_stride, row_at, stream);
     if (hipGetLastError() != hipSuccess) return GR_EHIP;
     mark(h, 1, stream);
     SolveParams sp;
-    sp.p = p; sp.q = q; sp.B = B; sp.V = V; sp.n = n; sp.k = k_eff; sp.splits = splits;
+    sp.p = p; sp.q = q; sp.B = B; sp.V = V; sp.n = n; sp.k = k_eff; sp.splits = cut.count;
     sp.tau = static_cast<double>(tol); sp.rel_tol = h->rel_tol; sp.max_iter = h->max_iter; sp.max_T = h->max_T;
     sp.tail_mass = temperature ? 0.0 : h->tail_mass;
     sp.cand = h->cand; sp.cand_count = h->cand_count; sp.part_psum = h->part_psum; sp.part_qsum = h->part_qsum;
@@ -263,7 +265,7 @@ extern "C" int gr_create(gr_handle* out, int max_B, int max_V, int max_k, int ma
     if (solve_kernel_setup() != hipSuccess || full_kernel_setup() != hipSuccess) { delete h; return GR_EHIP; }
     { unsigned char* na = nullptr; (void)scratch_address(&na); }      // so that gr_accept_sweep_noalloc finds its array later
     const size_t rows = static_cast<size_t>(max_B);
-    bool ok = dev_alloc(&h->cand, rows * kMaxSplits * kMaxSupport) && dev_alloc(&h->cand_count, rows * kMaxSplits) &&
+    bool ok = dev_alloc(&h->cand, rows * kSelCap) && dev_alloc(&h->cand_count, rows * kMaxSplits) &&
               dev_alloc(&h->part_psum, rows * kMaxSplits) && dev_alloc(&h->part_qsum, rows * kMaxSplits) &&
               dev_alloc(&h->part_bad, rows * kMaxSplits) && dev_alloc(&h->order, rows * kMaxSupport) &&
               dev_alloc(&h->block, rows * kMaxSupport) && dev_alloc(&h->weight, rows * kMaxSupport) &&
@@ -398,14 +400,12 @@ extern "C" int gr_accept_sweep(gr_handle h, const float* p, const float* q, cons
     SweepParams sw;
     const int rcf = fill_sweep(sw, ks, nk, ns, nn, V);
     if (rcf != GR_OK) return rcf;
-    const int splits = choose_splits(B, V);
-    int slice_len = (V + splits - 1) / splits;
-    slice_len = (slice_len + kSelTile - 1) / kSelTile * kSelTile;
+    const Slices cut = choose_slices(B, V, sw.kmax);
     h->solved = false;                                   // the selection scratch of the handle is overwritten
-    launch_select(p, q, B, V, sw.kmax, splits, slice_len, h->cand, h->cand_count, h->part_psum, h->part_qsum,
+    launch_select(p, q, B, V, sw.kmax, cut.count, cut.len, h->cand, h->cand_count, h->part_psum, h->part_qsum,
                   h->part_bad, h->piece_psum, h->piece_stride, nullptr, stream);
     if (hipGetLastError() != hipSuccess) return GR_EHIP;
-    sw.p = p; sw.splits = splits;
+    sw.p = p; sw.splits = cut.count;
     sw.cand = h->cand; sw.cand_count = h->cand_count; sw.part_psum = h->part_psum; sw.part_qsum = h->part_qsum;
     sw.part_bad = h->part_bad; sw.accept_prob = accept_prob; sw.status = status;
     if (launch_sweep(sw, B, stream) != hipSuccess) return GR_EHIP;
@@ -428,12 +428,10 @@ extern "C" int gr_accept_sweep_noalloc(const float* p, const float* q, const int
     int* count = reinterpret_cast<int*>(base + kNaCount);
     int* bad = reinterpret_cast<int*>(base + kNaBad);
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    const int splits = choose_splits(B, V);
-    int slice_len = (V + splits - 1) / splits;
-    slice_len = (slice_len + kSelTile - 1) / kSelTile * kSelTile;
-    launch_select(p, q, B, V, sw.kmax, splits, slice_len, cand, count, psum, qsum, bad, nullptr, 0, nullptr, stream);
+    const Slices cut = choose_slices(B, V, sw.kmax);
+    launch_select(p, q, B, V, sw.kmax, cut.count, cut.len, cand, count, psum, qsum, bad, nullptr, 0, nullptr, stream);
     if (hipGetLastError() != hipSuccess) return GR_EHIP;
-    sw.p = p; sw.splits = splits;
+    sw.p = p; sw.splits = cut.count;
     sw.cand = cand; sw.cand_count = count; sw.part_psum = psum; sw.part_qsum = qsum; sw.part_bad = bad;
     sw.accept_prob = accept_prob; sw.status = status;
     if (launch_sweep(sw, B, stream) != hipSuccess) return GR_EHIP;

@@ -13,7 +13,7 @@ constexpr int kMaxSupport = GR_MAX_SUPPORT;
 constexpr int kMaxT = GR_MAX_T;
 constexpr int kSelTile = kThreads * 4;    // tokens per streaming tile (one float4 per thread)
 constexpr int kSelCap = 2048;             // candidate keys held in LDS (>= kMaxSupport + kSelTile)
-constexpr int kMaxSplits = 8;             // workgroups that share one row in the select kernel
+constexpr int kMaxSplits = 32;            // workgroups that share one row in the select kernel (kSelCap / k of them at most)
 
 // Per-row result of the solve kernel (one per row, in HBM).
 struct RowInfo {
@@ -43,7 +43,7 @@ struct SolveParams {
     double tail_mass;   // nucleus cut of the draft (0: none)
     int max_iter, max_T;
     // select kernel output
-    const unsigned long long* cand;   // [B, splits, kMaxSupport] keys
+    const unsigned long long* cand;   // [B, kSelCap] keys: kSelCap / splits of each slice
     const int* cand_count;            // [B, splits]
     const double* part_psum;          // [B, splits]
     const double* part_qsum;          // [B, splits]
@@ -336,6 +336,52 @@ __device__ __forceinline__ void wave_sequential_scan_padded(const double* x, dou
     }
 }
 #pragma clang fp contract(fast)
+
+// What the slices of a row found, in every thread: the number of candidates and the float64 sums of p and q, added in the order of the
+// slices.  LOGITS: the sums of p brought to the row's largest reference, which `ref` returns, and no sum of q.  A lane reads the records of
+// one slice (a loop over the slices waits for memory once per slice).
+struct SliceTotals { int total, bad; double ptot, qtot; float ref; int count, before; };   // count, before: of lane s, its slice's candidates and those before them
+template <bool LOGITS>
+__device__ __forceinline__ SliceTotals slice_totals(const int* cand_count, const int* part_bad, const double* part_psum, const double* part_qsum,
+                                                    const float* part_pref, int row, int splits, double inv_temp) {
+    static_assert(kMaxSplits <= 64, "a lane to a slice");
+    const int lane = threadIdx.x & 63, at = row * splits + lane;
+    const bool mine = lane < splits;
+    SliceTotals t;
+    t.count = mine ? cand_count[at] : 0;
+    const int bad = mine ? part_bad[at] : 0;
+    double ps = mine ? part_psum[at] : 0.0, qs = 0.0;
+    t.ref = 0.f;
+    if (LOGITS) {
+        const float r = mine ? part_pref[at] : -__builtin_inff();
+        t.ref = static_cast<float>(wave_max(static_cast<double>(r)));
+        ps = r > -3.0e38f ? ps * exp((static_cast<double>(r) - static_cast<double>(t.ref)) * inv_temp) : 0.0;
+    } else if (mine) qs = part_qsum[at];
+    const int upto = wave_scan_i(t.count);
+    t.before = upto - t.count;
+    t.total = __builtin_amdgcn_readlane(upto, 63);
+    t.bad = __ballot(bad != 0) != 0ull;
+    t.ptot = 0.0; t.qtot = 0.0;
+    for (int s = 0; s < splits; ++s) {
+        t.ptot += read_lane(ps, s);
+        if (!LOGITS) t.qtot += read_lane(qs, s);
+    }
+    return t;
+}
+// The candidates of a row, one slice after the other, into LDS: a wave to a slice.  (A thread to a key, which looks for its slice in the
+// lanes' counts, cost 1.5 us more on one slice and no less on eight.)
+template <int NT>
+__device__ __forceinline__ void gather_keys(unsigned long long* keys, const unsigned long long* row_cand, const SliceTotals& t, int splits) {
+    const int lane = threadIdx.x & 63, room = kSelCap / splits;
+    for (int s = threadIdx.x >> 6; s < splits; s += NT / 64) {
+        const int count = __builtin_amdgcn_readlane(t.count, s), before = __builtin_amdgcn_readlane(t.before, s);
+        unsigned long long key[kMaxSupport / 64];
+#pragma unroll
+        for (int u = 0; u < kMaxSupport / 64; ++u) if (u * 64 + lane < count) key[u] = row_cand[s * room + u * 64 + lane];
+#pragma unroll
+        for (int u = 0; u < kMaxSupport / 64; ++u) if (u * 64 + lane < count) keys[before + u * 64 + lane] = key[u];
+    }
+}
 
 // e^{-y} for y >= 0 with a 32-entry table: y = k ln2/32 + r, |r| <= ln2/64, e^{-y} =
 // 2^-(k>>5) * tab[k&31] * e^{-r} with tab[j] = 2^(-j/32) and a degree-5 polynomial (error < 3e-15 + 1.2e-16 y:

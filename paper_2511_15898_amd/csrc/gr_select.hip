@@ -198,14 +198,15 @@ __global__ __launch_bounds__(kThreads, 8) void select_kernel(
         theta = 0ull;
     }
     // emit the keys >= theta (at most k of them)
-    unsigned long long* out = cand + (static_cast<size_t>(b) * splits + s) * kMaxSupport;
+    const int room = kSelCap / splits;                         // >= k
+    unsigned long long* out = cand + static_cast<size_t>(b) * kSelCap + s * room;
     if (tid == 0) pick[0] = 0;
     __syncthreads();
     for (int i = tid; i < c; i += kThreads) {
         const unsigned long long key = keys[i];
         if (key >= theta) {
             const int slot = atomicAdd(&pick[0], 1);
-            if (slot < kMaxSupport) out[slot] = key;
+            if (slot < room) out[slot] = key;
         }
     }
     __syncthreads();
@@ -225,7 +226,7 @@ __global__ __launch_bounds__(kThreads, 8) void select_kernel(
     }
     const int anybad = block_sum_i(bad, red);
     if (tid == 0) {
-        cand_count[b * splits + s] = min(pick[0], kMaxSupport);
+        cand_count[b * splits + s] = min(pick[0], room);
         part_psum[b * splits + s] = pt;
         part_qsum[b * splits + s] = qt;
         part_bad[b * splits + s] = anybad;

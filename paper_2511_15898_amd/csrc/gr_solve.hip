@@ -1579,8 +1579,8 @@ __global__ __launch_bounds__(kThreadsOf<D>) void solve_kernel(SolveParams sp) {
     info.alpha_star = 0.0; info.res_total = 0.0; info.p_total = 0.0; info.q_total = 0.0; info.node_tokens = 0.0; info.p_ref = 0.0; info.inv_temp = 0.0; info.q_ref = 0.0;
 
     // ---- merge the slices
-    int total = 0, bad = 0;
-    double ptot = 0.0, qtot = 0.0;
+    SliceTotals found;
+    int bad = 0;
     double p_ref = 0.0, inv_temp = 0.0, inv_temp_q = 0.0;
     if (sp.logits) {
         // rows given as logits: the slices' softmax sums are brought to the row's largest reference; q needs no
@@ -1590,26 +1590,16 @@ __global__ __launch_bounds__(kThreadsOf<D>) void solve_kernel(SolveParams sp) {
         const float Td = sp.draft_temperature ? sp.draft_temperature[row] : T;
         inv_temp_q = 1.0 / static_cast<double>(Td);
         if (!(Td > 0.f) || !(Td <= 3.0e38f)) bad = 1;
-        float m = -__builtin_inff();
-        for (int s = 0; s < sp.splits; ++s) m = fmaxf(m, sp.part_pref[row * sp.splits + s]);
-        p_ref = static_cast<double>(m);
-        for (int s = 0; s < sp.splits; ++s) {
-            total += sp.cand_count[row * sp.splits + s];
-            bad |= sp.part_bad[row * sp.splits + s];
-            const float r = sp.part_pref[row * sp.splits + s];
-            if (r > -3.0e38f) ptot += sp.part_psum[row * sp.splits + s] * exp((static_cast<double>(r) - p_ref) * inv_temp);
-        }
-        qtot = 1.0;
-        if (!(ptot > 0.0) || !(ptot < 1e300) || !(m > -3.0e38f)) bad = 1;
+        found = slice_totals<true>(sp.cand_count, sp.part_bad, sp.part_psum, sp.part_qsum, sp.part_pref, row, sp.splits, inv_temp);
+        p_ref = static_cast<double>(found.ref); found.qtot = 1.0;
+        if (!(found.ptot > 0.0) || !(found.ptot < 1e300) || !(found.ref > -3.0e38f)) bad = 1;
     } else {
-        for (int s = 0; s < sp.splits; ++s) {
-            total += sp.cand_count[row * sp.splits + s];
-            bad |= sp.part_bad[row * sp.splits + s];
-            ptot += sp.part_psum[row * sp.splits + s];
-            qtot += sp.part_qsum[row * sp.splits + s];
-        }
-        if (!(fabs(ptot - 1.0) <= 1e-3) || !(fabs(qtot - 1.0) <= 1e-3)) bad = 1;
+        found = slice_totals<false>(sp.cand_count, sp.part_bad, sp.part_psum, sp.part_qsum, nullptr, row, sp.splits, 0.0);
+        if (!(fabs(found.ptot - 1.0) <= 1e-3) || !(fabs(found.qtot - 1.0) <= 1e-3)) bad = 1;
     }
+    bad |= found.bad;
+    const int total = found.total;
+    const double ptot = found.ptot, qtot = found.qtot;
     info.p_total = ptot; info.q_total = qtot; info.p_ref = p_ref; info.inv_temp = sp.logits ? inv_temp : 0.0;
     if (bad || total <= 0 || total > kSelCap) {
         if (tid == 0) {
@@ -1622,15 +1612,7 @@ __global__ __launch_bounds__(kThreadsOf<D>) void solve_kernel(SolveParams sp) {
         }
         return;
     }
-    {
-        int off = 0;
-        for (int s = 0; s < sp.splits; ++s) {
-            const int c = sp.cand_count[row * sp.splits + s];
-            const unsigned long long* src = sp.cand + (static_cast<size_t>(row) * sp.splits + s) * kMaxSupport;
-            for (int i = tid; i < c; i += kST) L.keys[off + i] = src[i];
-            off += c;
-        }
-    }
+    gather_keys<kST>(L.keys, sp.cand + static_cast<size_t>(row) * kSelCap, found, sp.splits);
     if (tid == 0) { L.count = 0; L.work = 0.0; }
 #ifdef GR_PHASE_CLOCKS
     if (tid == 0) { for (int i = 0; i < 24; ++i) L.clk[i] = 0; L.clk_last = clock64(); }

@@ -4,9 +4,13 @@
 // the support is the first k tokens by decreasing q (App. "Top-k Sampling for the Relaxed OTLP") and
 // its ratio order is the sub-sequence of the largest support's order, so one ordering serves the grid.
 //
-// One 256-thread workgroup per row, everything in LDS; thread m owns rank m of the ratio order.
+// One workgroup per row, everything in LDS, its 1024 threads in groups of 256: thread m of a group owns rank m of the
+// ratio order; the groups share the comparisons of the ranks and take the top-k sizes in turn.
 // Only the minimum of F(m) = P_m - Q_m^n is reported, to 1e-5, so the prefix sums here are parallel
 // scans in float64 (no integer decision hangs on their rounding).
+// Bound: latency, a row's chain of LDS reads, scans and barriers; 256 threads to a row left most of a compute unit idle
+// (256 rows, six sizes up to 256, ten draft counts: 44 us, now 25.7; with the selection, V = 32000, 1 / 512 / 1024 / 2048
+// rows 53.0 / 78.5 / 116.2 / 216.0 -> 35.7 / 67.4 / 111.5 / 215.1 us, so no batch is better served by fewer threads).
 #include <hip/hip_runtime.h>
 
 #include "gr_internal.h"
@@ -15,6 +19,9 @@ namespace gr {
 
 namespace {
 
+constexpr int kSweepThreads = 1024, kGroups = kSweepThreads / kThreads;
+static_assert(kThreads == kMaxSupport, "a thread of a group to a rank");
+
 struct SweepLds {
     unsigned long long keys[kSelCap];     // merged slice candidates
     unsigned long long ckey[kMaxSupport]; // the kmax largest, unordered
@@ -22,64 +29,61 @@ struct SweepLds {
     double rp[kMaxSupport]; double rq[kMaxSupport];   // by ratio rank: p / sum p, raw q
     int rqr[kMaxSupport];                 // by ratio rank: the token's rank by decreasing q
     int ids[kMaxSupport];
-    double wtot[2][kWaves];
-    double cell[kSweepMaxN][kWaves];      // per draft count: the waves' minima of F
+    int rank[2][kMaxSupport];             // by slot: the ranks by decreasing q and by decreasing q/p
+    double wtot[kGroups][2][kWaves];            // per group
+    double cell[kGroups][kSweepMaxN][kWaves];   // per group and draft count: the waves' minima of F
     int hist[256]; int pick[4]; int count;
 };
 
-// Inclusive sums of a and b over the 256 threads (thread order); *atot, *btot = the totals.
-__device__ __forceinline__ void block_scan2(double& a, double& b, double (*wtot)[kWaves], double* atot, double* btot) {
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    for (int o = 1; o < 64; o <<= 1) {
-        const double ua = __shfl_up(a, o), ub = __shfl_up(b, o);
-        if (lane >= o) { a += ua; b += ub; }
-    }
-    if (lane == 63) { wtot[0][wv] = a; wtot[1][wv] = b; }
+// Inclusive sums of a over the lanes of a wave.
+__device__ __forceinline__ double wave_scan(double a) {
+    a += dpp_shift<0x111, 0xF>(a, 0.0);
+    a += dpp_shift<0x112, 0xF>(a, 0.0);
+    a += dpp_shift<0x114, 0xF>(a, 0.0);
+    a += dpp_shift<0x118, 0xF>(a, 0.0);
+    a += dpp_shift<0x142, 0xA>(a, 0.0);
+    a += dpp_shift<0x143, 0xC>(a, 0.0);
+    return a;
+}
+// Inclusive sums of a and b over the 256 threads of a group (thread order); *btot = the total of b.
+__device__ __forceinline__ void group_scan2(double& a, double& b, double (*wtot)[kWaves], double* btot) {
+    const int wv = (threadIdx.x >> 6) & (kWaves - 1);
+    a = wave_scan(a); b = wave_scan(b);
+    if ((threadIdx.x & 63) == 63) { wtot[0][wv] = a; wtot[1][wv] = b; }
     __syncthreads();
-    double pa = 0.0, pb = 0.0, ta = 0.0, tb = 0.0;
+    double pa = 0.0, pb = 0.0, tb = 0.0;
+#pragma unroll
     for (int w = 0; w < kWaves; ++w) {
         if (w < wv) { pa += wtot[0][w]; pb += wtot[1][w]; }
-        ta += wtot[0][w]; tb += wtot[1][w];
+        tb += wtot[1][w];
     }
-    a += pa; b += pb; *atot = ta; *btot = tb;
-    __syncthreads();
+    a += pa; b += pb; *btot = tb;
 }
 
-__global__ __launch_bounds__(kThreads) void sweep_kernel(SweepParams sw) {
+__global__ __launch_bounds__(kSweepThreads) void sweep_kernel(SweepParams sw) {
+    constexpr int NT = kSweepThreads;
     __shared__ SweepLds L;
-    const int tid = threadIdx.x, row = blockIdx.x;
+    const int tid = threadIdx.x, row = blockIdx.x, m = tid & (kThreads - 1), group = tid / kThreads;
     const int cells = sw.nk * sw.nn;
     float* out = sw.accept_prob + static_cast<size_t>(row) * cells;
 
     // ---- merge the slices (same per-slice records as the solve kernel reads)
-    int total = 0, bad = 0;
-    double ptot = 0.0, qtot = 0.0;
-    for (int s = 0; s < sw.splits; ++s) {
-        total += sw.cand_count[row * sw.splits + s];
-        bad |= sw.part_bad[row * sw.splits + s];
-        ptot += sw.part_psum[row * sw.splits + s];
-        qtot += sw.part_qsum[row * sw.splits + s];
-    }
-    if (bad || !(fabs(ptot - 1.0) <= 1e-3) || !(fabs(qtot - 1.0) <= 1e-3) || total <= 0 || total > kSelCap) {
-        for (int c = tid; c < cells; c += kThreads) out[c] = __uint_as_float(0x7fc00000u);
+    const SliceTotals found = slice_totals<false>(sw.cand_count, sw.part_bad, sw.part_psum, sw.part_qsum, nullptr, row, sw.splits, 0.0);
+    const int total = found.total;
+    const double ptot = found.ptot, qtot = found.qtot;
+    if (found.bad || !(fabs(ptot - 1.0) <= 1e-3) || !(fabs(qtot - 1.0) <= 1e-3) || total <= 0 || total > kSelCap) {
+        for (int c = tid; c < cells; c += NT) out[c] = __uint_as_float(0x7fc00000u);
         if (tid == 0) sw.status[row] = GR_ROW_BAD;
         return;
     }
-    {
-        int off = 0;
-        for (int s = 0; s < sw.splits; ++s) {
-            const int c = sw.cand_count[row * sw.splits + s];
-            const unsigned long long* src = sw.cand + (static_cast<size_t>(row) * sw.splits + s) * kMaxSupport;
-            for (int i = tid; i < c; i += kThreads) L.keys[off + i] = src[i];
-            off += c;
-        }
-    }
+    gather_keys<NT>(L.keys, sw.cand + static_cast<size_t>(row) * kSelCap, found, sw.splits);
     if (tid == 0) L.count = 0;
+    if (tid < kMaxSupport) { L.rank[0][tid] = 0; L.rank[1][tid] = 0; }
     __syncthreads();
     unsigned long long theta = 0ull;
-    if (total > sw.kmax) theta = block_kth_largest<kThreads>(L.keys, total, sw.kmax, L.hist, L.pick);
+    if (total > sw.kmax) theta = block_kth_largest<NT>(L.keys, total, sw.kmax, L.hist, L.pick);
     const int kk = min(total, sw.kmax);                       // <= kMaxSupport = kThreads
-    for (int i = tid; i < total; i += kThreads) {
+    for (int i = tid; i < total; i += NT) {
         const unsigned long long key = L.keys[i];
         if (key >= theta) {
             const int slot = atomicAdd(&L.count, 1);
@@ -87,51 +91,65 @@ __global__ __launch_bounds__(kThreads) void sweep_kernel(SweepParams sw) {
         }
     }
     __syncthreads();
-    // ---- per slot: token id, q, p; rank by decreasing q (keys are distinct: ties go to the lower id)
-    int qrank = 0, id = 0;
-    if (tid < kk) {
-        const unsigned long long mine = L.ckey[tid];
-        id = key_id(mine);
-        L.ids[tid] = id;
-        L.qv[tid] = static_cast<double>(key_q(mine));
-        L.pv[tid] = static_cast<double>(sw.p[static_cast<size_t>(row) * sw.V + id]);
-        for (int j = 0; j < kk; ++j) qrank += static_cast<int>(L.ckey[j] > mine);
+    // ---- per slot: token id, q, p; rank by decreasing q (keys are distinct: ties go to the lower id).  A group compares
+    // with its share of the slots.
+    const int each = (kk + kGroups - 1) / kGroups, j0 = group * each, j1 = min(kk, j0 + each);
+    if (m < kk) {
+        const unsigned long long mine = L.ckey[m];
+        if (group == 0) {
+            const int id = key_id(mine);
+            L.ids[m] = id;
+            L.qv[m] = static_cast<double>(key_q(mine));
+            L.pv[m] = static_cast<double>(sw.p[static_cast<size_t>(row) * sw.V + id]);
+        }
+        int before = 0;
+#pragma unroll 8
+        for (int j = j0; j < j1; ++j) before += static_cast<int>(L.ckey[j] > mine);
+        atomicAdd(&L.rank[0][m], before);
     }
     __syncthreads();
     // ---- rank by decreasing q/p: exact cross products (float x float fits a double), ties by id
-    if (tid < kk) {
-        const double qa = L.qv[tid], pa = L.pv[tid];
-        int rank = 0;
-        for (int j = 0; j < kk; ++j) {
+    if (m < kk) {
+        const double qa = L.qv[m], pa = L.pv[m];
+        const int id = L.ids[m];
+        int before = 0;
+#pragma unroll 8
+        for (int j = j0; j < j1; ++j) {
             const double lhs = L.qv[j] * pa, rhs = qa * L.pv[j];              // j before me?
-            rank += static_cast<int>(lhs > rhs) | (static_cast<int>(lhs == rhs) & static_cast<int>(L.ids[j] < id));
+            before += static_cast<int>(lhs > rhs) | (static_cast<int>(lhs == rhs) & static_cast<int>(L.ids[j] < id));
         }
-        L.rp[rank] = pa / ptot; L.rq[rank] = qa; L.rqr[rank] = qrank;
+        atomicAdd(&L.rank[1][m], before);
+    }
+    __syncthreads();
+    if (tid < kk) {
+        const int rank = L.rank[1][tid];
+        L.rp[rank] = L.pv[tid] / ptot; L.rq[rank] = L.qv[tid]; L.rqr[rank] = L.rank[0][tid];
     }
     __syncthreads();
     // ---- the grid: for each k the masked prefix sums along the order, for each n the best prefix
-    const bool have = tid < kk;
-    const double myp = have ? L.rp[tid] : 0.0, myq = have ? L.rq[tid] : 0.0;
-    const int myqr = have ? L.rqr[tid] : 0x7fffffff;
-    for (int a = 0; a < sw.nk; ++a) {
-        const bool on = myqr < sw.ks[a];
-        double P = on ? myp : 0.0, S = on ? myq : 0.0, Ptot, Stot;
-        block_scan2(P, S, L.wtot, &Ptot, &Stot);
-        const double Q = S / Stot;                            // Stot > 0: the largest q is positive
+    const bool have = m < kk;
+    const double myp = have ? L.rp[m] : 0.0, myq = have ? L.rq[m] : 0.0;
+    const int myqr = have ? L.rqr[m] : 0x7fffffff;
+    for (int a0 = 0; a0 < sw.nk; a0 += kGroups) {
+        const int a = a0 + group;
+        const bool on = a < sw.nk && myqr < sw.ks[min(a, kSweepMaxK - 1)];
+        double P = on ? myp : 0.0, S = on ? myq : 0.0, Stot;
+        group_scan2(P, S, L.wtot[group], &Stot);
+        const double Q = S / Stot;                            // a < nk: Stot > 0, the largest q is positive
         // a rank outside this support repeats the prefix before it (or the empty prefix, F = 0);
         // the minima of all draft counts meet in LDS behind one barrier
         for (int b = 0; b < sw.nn; ++b) {
             const double F = have ? P - ipow(Q, sw.ns[b]) : 0.0;
-            const double m = wave_min(fmin(F, 0.0));
-            if ((tid & 63) == 0) L.cell[b][tid >> 6] = m;
+            const double least = wave_min(fmin(F, 0.0));
+            if ((tid & 63) == 0) L.cell[group][b][(tid >> 6) & (kWaves - 1)] = least;
         }
         __syncthreads();
-        if (tid < sw.nn) {
-            double t = L.cell[tid][0];
-            for (int w = 1; w < kWaves; ++w) t = fmin(t, L.cell[tid][w]);
-            out[a * sw.nn + tid] = static_cast<float>(1.0 + t);
+        if (m < sw.nn && a < sw.nk) {
+            double t = L.cell[group][m][0];
+            for (int w = 1; w < kWaves; ++w) t = fmin(t, L.cell[group][m][w]);
+            out[a * sw.nn + m] = static_cast<float>(1.0 + t);
         }
-        // L.cell is written again only behind the two barriers of the next scan
+        // L.wtot was read before the barrier; L.cell is written again only behind the barrier of the next scan
     }
     if (tid == 0) sw.status[row] = GR_ROW_OK;
 }
@@ -139,7 +157,7 @@ __global__ __launch_bounds__(kThreads) void sweep_kernel(SweepParams sw) {
 }  // namespace
 
 hipError_t launch_sweep(const SweepParams& sw, int B, hipStream_t stream) {
-    hipLaunchKernelGGL(sweep_kernel, dim3(B), dim3(kThreads), 0, stream, sw);
+    hipLaunchKernelGGL(sweep_kernel, dim3(B), dim3(kSweepThreads), 0, stream, sw);
     return hipGetLastError();
 }
 
