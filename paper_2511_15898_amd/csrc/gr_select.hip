@@ -18,7 +18,8 @@ namespace gr {
 // (App. A: temperature only changes how p and q come from the logits).  The k largest q are the k largest
 // draft logits, so the keys carry the draft logit (as a monotone 32-bit pattern); the draft needs no
 // normaliser, because q is renormalised over the support anyway.  The target's normaliser is an online
-// softmax: every wave keeps a reference r (the largest target logit it has seen, raised tile by tile) and
+// softmax: every wave keeps a reference r (the largest target logit that it, and up to the tile before any wave of the
+// workgroup, has seen: with its own alone more terms were near it, 84 -> 78 us for 256 rows of 128256 tokens) and
 // its lanes the float64 sums of exp((t - r) / T); part_psum / part_pref get the
 // slice's sum and reference, piece_psum / piece_pref those of every 256 tokens.
 template <bool LOGITS>
@@ -63,6 +64,7 @@ __global__ __launch_bounds__(kThreads, 8) void select_kernel(
     if (LOGITS) {
         const float T = temperature[b];
         if (!(T > 0.f) || !(T <= 3.0e38f)) bad = 1; else { inv_temp = 1.0 / static_cast<double>(T); scale2 = 1.44269504088896341f / T; }
+        if (tid < kWaves) wref[tid] = -__builtin_inff();
         if (tid < 32) e2tab[tid] = exp2(-static_cast<double>(tid) / 32.0);
         __syncthreads();
     }
@@ -100,6 +102,7 @@ __global__ __launch_bounds__(kThreads, 8) void select_kernel(
                 for (int o = 1; o < 64; o <<= 1) m4 = fmaxf(m4, __shfl_xor(m4, o));
                 ps = (ref > -3.0e38f) ? ps * exp_neg((static_cast<double>(m4) - static_cast<double>(ref)) * inv_temp, e2tab) : 0.0;
                 ref = m4;
+                if ((tid & 63) == 0) wref[tid >> 6] = ref;
             }
             // Terms more than 25 temperatures below the reference (each below 1.4e-11 of it) take the hardware's
             // float32 exponential: their relative error of 1e-7 moves the sum by at most 1.4e-18 V of the reference's
@@ -169,6 +172,13 @@ __global__ __launch_bounds__(kThreads, 8) void select_kernel(
         }
         __syncthreads();
         const int c = count;
+        if (LOGITS) {                                              // the largest reference of the workgroup is everyone's
+            const float m = fmaxf(fmaxf(wref[0], wref[1]), fmaxf(wref[2], wref[3]));
+            if (m > ref) {                                         // uniform over the wave
+                ps = (ref > -3.0e38f) ? ps * exp_neg((static_cast<double>(m) - static_cast<double>(ref)) * inv_temp, e2tab) : 0.0;
+                ref = m;
+            }
+        }
         __syncthreads();
         if (c + kSelTile > kSelCap && c > k) {
             theta = block_kth_largest(keys, c, k, hist, pick);
