@@ -156,9 +156,9 @@ int gr_accept_sweep(gr_handle h, const float* p, const float* q, const int* ks, 
  * gr_accept_sweep for callers that cannot allocate device memory or create a handle: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, outputs and arithmetic as
  * gr_accept_sweep, without the handle, for top-k sizes of 1..GR_MAX_SUPPORT (GR_EINVAL beyond: the HBM-resident
- * ordering lives in a handle's workspace); the selection scratch (candidate keys and partial sums, 16.2 KB per row)
+ * ordering lives in a handle's workspace); the selection scratch (candidate keys and partial sums, 17.2 KB per row)
  * is a fixed array in the library's device image, so B is limited to GR_NOALLOC_MAX_B rows (GR_ECAPACITY
- * beyond; 4.2 MB per GPU, held until the process ends).  The call allocates nothing, frees nothing and does
+ * beyond; 4.4 MB per GPU, held until the process ends).  The call allocates nothing, frees nothing and does
  * not synchronise.  The array's address on the current device is looked up on the first call on that device
  * (and by any gr_create on it): make that first call outside a graph capture.  Every call on a GPU uses
  * that GPU's one array: calls that overlap in time on one GPU race, whatever their streams.  Nothing in the

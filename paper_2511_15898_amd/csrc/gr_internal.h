@@ -143,7 +143,7 @@ struct FullSweep {
     float* accept_prob;           // [B, nk, nn]
     int* status;                  // [B]
 };
-hipError_t solve_kernel_setup();
+hipError_t solve_kernel_setup(int max_n, bool hbm);
 hipError_t full_kernel_setup();
 
 // ---------------------------------------------------------------- device helpers

@@ -1,4 +1,4 @@
-// Per-row solve: one 256-thread workgroup per decode position, everything after the streaming
+// Per-row solve: one workgroup per decode position, everything after the streaming
 // selection lives in LDS.
 //
 //   merge the slices' candidates -> top-k support V_0       (App. "Top-k Sampling ...")
@@ -2056,14 +2056,17 @@ hipError_t launch_full_programs(const FullParams& fp, hipStream_t stream) {
 static_assert(sizeof(Lds<16>) + 20 * 1024 <= 160 * 1024,
               "the solve workgroup's state and one streaming workgroup of the next batch must fit the CU's LDS together");
 
-hipError_t solve_kernel_setup() {
+// The kernels that a handle of up to max_n drafts can launch; hbm: those of supports above kMaxSupport too.  (A handle for one row,
+// its inputs and its drafts: 353 us with these eight kernels, 407 with those of full_kernel_setup as well, in every gr_create.)
+hipError_t solve_kernel_setup(int max_n, bool hbm) {
     const void* kernels[8] = {reinterpret_cast<const void*>(solve_kernel<2>), reinterpret_cast<const void*>(solve_kernel<4>),
                               reinterpret_cast<const void*>(solve_kernel<8>), reinterpret_cast<const void*>(solve_kernel<16>),
                               reinterpret_cast<const void*>(full_programs_kernel<2>), reinterpret_cast<const void*>(full_programs_kernel<4>),
                               reinterpret_cast<const void*>(full_programs_kernel<8>), reinterpret_cast<const void*>(full_programs_kernel<16>)};
     const size_t sizes[8] = {sizeof(Lds<2>), sizeof(Lds<4>), sizeof(Lds<8>), sizeof(Lds<16>),
                              sizeof(Lds<2>), sizeof(Lds<4>), sizeof(Lds<8>), sizeof(Lds<16>)};
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < (hbm ? 8 : 4); ++i) {
+        if ((1 << (i & 3)) >= max_n && (i & 3) > 0) continue;              // series degree 2 << (i & 3); half of it serves max_n
         const hipError_t e = hipFuncSetAttribute(kernels[i], hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(sizes[i]));
         if (e != hipSuccess) return e;
     }
