@@ -1,0 +1,30 @@
+"""Supports above 256 tokens at the edges of the scan's tiles (2048 ranks) and of the chunks that gather and scatter, with row
+counts that leave some of the chunk kernels' workgroups without a row: alpha* on every row, everything else on sampled rows."""
+import numpy as np
+import pytest
+
+from paper_2511_15898_amd import workloads as W
+from parity_util import check_alpha_all_rows, compare_rows, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B", [5, 66])
+@pytest.mark.parametrize("V", [257, 2047, 2048, 2049, 4097])
+def test_rows_at_tile_edges(B, V):
+    wl = W.llm_shaped(B=B, V=V, n=3, k=0, seed_sub=1300 + V)
+    rows = sorted({0, B // 2, B - 1})
+    out = run_gpu(wl, 1e-3, export_rows=rows)
+    check_alpha_all_rows(wl, out)
+    stats = compare_rows(wl, out, rows, 1e-3)
+    assert stats["rows"] == len(rows)
+
+
+@pytest.mark.parametrize("V", [2048, 2049, 9001])
+def test_flat_rows_end_above_the_cap(V):
+    """Dirichlet rows whose truncation sets hold thousands of tokens: the count alone ends them."""
+    wl = W.tiny(B=4, V=V, n=2)
+    out = run_gpu(wl, 1e-4, export_rows=range(wl.B))
+    check_alpha_all_rows(wl, out)
+    compare_rows(wl, out, range(wl.B), 1e-4)
+    assert np.all(out["status"] != 0)
