@@ -13,16 +13,16 @@ namespace gr {
 
 namespace {
 
-constexpr int kSortItems = 4;                      // keys per thread and tile
 constexpr int kScanThreads = 512;                  // of the kernel that takes the prefix sums
 constexpr int kChunkRanks = 4096;                  // ranks per workgroup of the kernels that gather and scatter by token id ...
 constexpr int kChunkLds = 40 * 1024;               // ... and the LDS that a workgroup of 256 threads reserves, for four of them to a compute unit (see full_gather_kernel)
 constexpr int kGatherThreads = 512, kGatherLds = 80 * 1024;
 // The sort of the large supports: elements of 8 bytes, the key in the high bits and the token id in the low ones.
-template <int NT>
+template <int NT, int R = 4>
 struct Sort32Lds {
     static constexpr int kWavesNT = NT / 64;
-    static constexpr int kTile = NT * kSortItems;
+    static constexpr int kItems = R;               // elements per thread and tile
+    static constexpr int kTile = NT * kItems;
     unsigned long long tile[kTile];                // the tile in digit order
     unsigned long long wcnt[kWavesNT][64];         // per wave: 256 counters of 16 bits, four to a word
     int hist[4][256];
@@ -32,17 +32,18 @@ struct Sort32Lds {
 };
 
 // Stable least-significant-digit radix sort of one row's `count` elements by their bits from `lo` on, 8 bits per pass and
-// at most four passes, between a and b; returns the buffer that holds the result.  A pass moves tiles of 4 NT elements: every wave ranks 256
-// consecutive ones among themselves (ballots, and counters that are its own, so no barrier lies between its four
+// at most four passes, between a and b; returns the buffer that holds the result.  A pass moves tiles of kTile elements: every wave ranks 64 kItems
+// consecutive ones among themselves (ballots, and counters that are its own, so no barrier lies between its
 // rounds), wave 0 turns the counters into places, and the tile goes through LDS into digit order, so that the
-// elements of one digit leave as one run (128 bytes on average for NT = 1024) and not one by one.  Three barriers per tile.
+// elements of one digit leave as one run and not one by one.  Three barriers per tile.
+// A run is 128 bytes on average with four elements per thread and 1024 threads, 256 bytes with eight (see kLongRow).
 // Bound: 16 bytes of traffic per element and pass, and the latency of a tile's three barriers (order kernel, 1024 rows of 128256
 // tokens: 18 GB in 6.0 ms, 3.0 TB/s where a device copy reaches 5.1).  All threads call.
-template <int NT>
-__device__ unsigned long long* block_sort32(unsigned long long* a, unsigned long long* b, int count, Sort32Lds<NT>& S, int lo = 32,
+template <int NT, int R>
+__device__ unsigned long long* block_sort32(unsigned long long* a, unsigned long long* b, int count, Sort32Lds<NT, R>& S, int lo = 32,
                                            int passes = 4) {
-    constexpr int kTile = Sort32Lds<NT>::kTile;
-    constexpr int NW = NT / 64;
+    constexpr int kTile = Sort32Lds<NT, R>::kTile;
+    constexpr int kSortItems = R, NW = NT / 64;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     for (int c = tid; c < 4 * 256; c += NT) (&S.hist[0][0])[c] = 0;
     if (tid < 4) S.skip[tid] = 0;
@@ -124,7 +125,7 @@ __device__ unsigned long long* block_sort32(unsigned long long* a, unsigned long
             }
             __syncthreads();
             if (wv == 0) {
-                // four digits per lane: the waves' counts become offsets (16-bit fields: a tile holds at most 4096)
+                // four digits per lane: the waves' counts become offsets (16-bit fields: a tile holds at most 8192)
                 unsigned long long run = 0ull;
 #pragma unroll 4
                 for (int w = 0; w < NW; ++w) { const unsigned long long c = S.wcnt[w][lane]; S.wcnt[w][lane] = run; run += c; }
@@ -314,12 +315,12 @@ __device__ __forceinline__ void scan_step(RunSum& v) {
 // With four loads in flight in the passes over the row and in the histogram, which counts only the digits that are sorted by, and scans over
 // the lanes without LDS: 1024 rows 6295 -> 6059 us, 256 rows 1434 -> 1382 us, 64 rows cut by a nucleus 119 -> 105 us.  (24 leading bits first
 // where the sample shows no near pairs, and the runs that remain put in order from LDS: 256 rows 1360 us, but 1024 rows 7000-7740 us.)
-template <int NT>
+template <int NT, int R = 4>
 __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
     constexpr int kWaves = NT / 64;                              // this workgroup's waves
     constexpr int kThreads = NT;
     constexpr int kMaxRun = 16, kClose = 4;                      // kClose: twice the near pairs that the sample may hold
-    __shared__ Sort32Lds<NT> S;
+    __shared__ Sort32Lds<NT, R> S;
     __shared__ double red[kWaves];
     __shared__ unsigned long long kred[2][kWaves];
     __shared__ int wtot[4 * kWaves];
@@ -469,7 +470,7 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
         const unsigned long long* sorted = k0;
         int keep = cnt;
         if (cnt > fp.k || (cut && cnt > 0)) {
-            sorted = block_sort32<NT>(k0, k1, cnt, S);
+            sorted = block_sort32(k0, k1, cnt, S);
             if (cut) {
                 // the exact walk: running sums of q in the sorted order, added one after the other (wave 0), until
                 // they reach (1 - tail_mass) qtot; the first rank that does is the last token of the support
@@ -604,7 +605,7 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
     int step = block_sum_i<kWaves>(close, red) >= kClose && lo > id_bits ? 1 : 0;
     for (;;) {
         const int from = step == 1 ? id_bits : (step >= 3 ? 32 : lo);
-        elems = block_sort32<NT>(elems, elems == k0 ? k1 : k0, kk, S, from, step == 1 ? (lo - id_bits + 7) >> 3 : 4);
+        elems = block_sort32(elems, elems == k0 ? k1 : k0, kk, S, from, step == 1 ? (lo - id_bits + 7) >> 3 : 4);
         if (step == 1) { step = 2; continue; }
         if (step == 0 || step == 2) {
             const int same = step == 0 ? lo : id_bits;           // tokens equal from this bit on may still be out of order
@@ -1048,9 +1049,9 @@ __global__ __launch_bounds__(NT) void full_trunc_kernel(FullParams fp) {
     } else {
         unsigned long long* e = k0;
         auto other = [&]() { return e == k0 ? k1 : k0; };
-        if (!ids) e = block_sort32<NT>(e, other(), kept, S, 0, 3);   // ids below 2^24
-        e = block_sort32<NT>(e, other(), kept, S, id_shift);
-        if (lg) e = block_sort32<NT>(e, other(), kept, S, 63, 1);
+        if (!ids) e = block_sort32(e, other(), kept, S, 0, 3);   // ids below 2^24
+        e = block_sort32(e, other(), kept, S, id_shift);
+        if (lg) e = block_sort32(e, other(), kept, S, 63, 1);
         for (int i = tid; i < kept; i += NT) byq[i] = rank_of[id_of(e[i])];
     }
     __syncthreads();
@@ -1181,10 +1182,10 @@ __global__ __launch_bounds__(kThreads) void full_dense_kernel(FullParams fp, int
 //
 // The whole vocabulary is ranked by one sort of the tokens in token order (their order is the tie-break: 32-bit keys, four
 // passes); a support below half of it by its own tokens alone, first by id and then by q.
-template <int NT>
+template <int NT, int R = 4>
 __global__ __launch_bounds__(NT) void full_sweep_rank_kernel(FullParams fp, FullSweep fs) {
     constexpr int kThreads = NT, kWaves = NT / 64;
-    __shared__ Sort32Lds<NT> S;
+    __shared__ Sort32Lds<NT, R> S;
     __shared__ double red[kWaves];
     const int tid = threadIdx.x, row = blockIdx.x;
     const int V = fp.V;
@@ -1209,7 +1210,7 @@ __global__ __launch_bounds__(NT) void full_sweep_rank_kernel(FullParams fp, Full
     __syncthreads();
     unsigned long long* sorted = k0;
     for (int round = whole ? 1 : 0; round < 2; ++round) {
-        sorted = block_sort32<NT>(sorted, sorted == k0 ? k1 : k0, count, S);
+        sorted = block_sort32(sorted, sorted == k0 ? k1 : k0, count, S);
         if (round == 0) {                                        // by token id so far: now by decreasing q
             for (int j = tid; j < kk; j += NT) {
                 const int r = packed_id(sorted[j]);
@@ -1365,9 +1366,14 @@ __global__ __launch_bounds__(NT) void full_sweep_scan_kernel(FullParams fp, Full
 // idle.  One of them fills a compute unit, so where rows wait for one (more of them than compute units) and a nucleus cut
 // leaves little to sort, the row must be longer (cut of 1e-3; 1024 against 256 threads, the call): 1024 rows of
 // 8193 tokens 795 and 707 us, of 12289 840 and 779, of 16384 959 and 950, of 24000 968 and 1010, of 50021 1504 and 1725.
+// Rows of more than kLongRow tokens are sorted in tiles of eight elements per thread: half the barriers, twice the run; a shorter row loses more to
+// its last tile.  The call, four / eight: 1024 rows of 128256 tokens 12993 / 12654 us, of 50021 4768 / 4759, of 24000 2416 / 2419, of 9000
+// 1317 / 1381; acceptance grid to V, 256 rows of 128256, 4031 / 3868.
+constexpr int kLongRow = 65536;
 static void launch_full_order(const FullParams& fp, hipStream_t stream) {
     const bool crowded = fp.tail_mass > 0.0 && fp.B > 256 && fp.V <= 16384;
-    if (fp.V > 8192 && !crowded) hipLaunchKernelGGL(full_order_kernel<1024>, dim3(fp.B), dim3(1024), 0, stream, fp);
+    if (fp.V > kLongRow) hipLaunchKernelGGL((full_order_kernel<1024, 8>), dim3(fp.B), dim3(1024), 0, stream, fp);
+    else if (fp.V > 8192 && !crowded) hipLaunchKernelGGL(full_order_kernel<1024>, dim3(fp.B), dim3(1024), 0, stream, fp);
     else hipLaunchKernelGGL(full_order_kernel<kThreads>, dim3(fp.B), dim3(kThreads), 0, stream, fp);
 }
 
@@ -1376,7 +1382,8 @@ void launch_full_sweep(const FullParams& fp, const FullSweep& fs, hipStream_t st
     const int chunks = (fp.V + kChunkRanks - 1) / kChunkRanks;
     const dim3 grid(chunk_grid(fp.B, chunks));
     hipLaunchKernelGGL(full_gather_kernel, grid, dim3(kGatherThreads), kGatherLds, stream, fp, chunks);
-    if (fp.V > 8192) hipLaunchKernelGGL(full_sweep_rank_kernel<1024>, dim3(fp.B), dim3(1024), 0, stream, fp, fs);
+    if (fp.V > kLongRow) hipLaunchKernelGGL((full_sweep_rank_kernel<1024, 8>), dim3(fp.B), dim3(1024), 0, stream, fp, fs);
+    else if (fp.V > 8192) hipLaunchKernelGGL(full_sweep_rank_kernel<1024>, dim3(fp.B), dim3(1024), 0, stream, fp, fs);
     else hipLaunchKernelGGL(full_sweep_rank_kernel<kThreads>, dim3(fp.B), dim3(kThreads), 0, stream, fp, fs);
     hipLaunchKernelGGL(full_qrank_kernel<true>, grid, dim3(kGatherThreads), kGatherLds, stream, fp, chunks);
     hipLaunchKernelGGL(full_qrank_kernel<false>, grid, dim3(kGatherThreads), kGatherLds, stream, fp, chunks);

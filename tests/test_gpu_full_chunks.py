@@ -28,3 +28,12 @@ def test_flat_rows_end_above_the_cap(V):
     check_alpha_all_rows(wl, out)
     compare_rows(wl, out, range(wl.B), 1e-4)
     assert np.all(out["status"] != 0)
+
+
+@pytest.mark.parametrize("V", [65536, 65537, 73729])
+def test_rows_on_both_sort_tiles(V):
+    """Rows up to and above the length that takes the sort's longer tiles, with a last tile of one token."""
+    wl = W.llm_shaped(B=2, V=V, n=2, k=0, seed_sub=1400 + V)
+    out = run_gpu(wl, 1e-3, export_rows=range(wl.B))
+    check_alpha_all_rows(wl, out)
+    compare_rows(wl, out, range(wl.B), 1e-3)
