@@ -1331,7 +1331,8 @@ __device__ __attribute__((noinline)) StepState newton_step(StepState st, int m, 
             }
         }
         double longest = wave_max(fmax(fabs(f[0]), fabs(f[1])));
-        if (st.since >= kStall || !(longest < 1e300)) {     // the fixed-point step, which lowers the objective whatever the point
+        const bool broken = __any(!(fabs(f[0]) < 1e300) || !(fabs(f[1]) < 1e300));   // fmax drops a NaN, so `longest` does not show one
+        if (st.since >= kStall || broken) {                 // the fixed-point step, which lowers the objective whatever the point
 #pragma unroll
             for (int u = 0; u < 2; ++u) f[u] = on[u] ? g[u] + lc : 0.0;
             longest = err; st.since = 0; st.havePrev = 0;
