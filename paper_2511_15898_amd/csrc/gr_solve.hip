@@ -1150,7 +1150,7 @@ __device__ int newton_program(Lds<D>& L, int& par, double* J, int m, int n, doub
 // of 1024, n = 4, k = 32: 122 -> 80; 256 rows of 128256, n = 8, k = 128: 272 -> 217.
 // Compiled as a function of its own (not inlined) so that its values do not compete for registers with the evaluator's series.
 // The uniform solver state travels in StepState; per-token values live in LDS (see solve_program).
-struct StepState { int since, retreats, havePrev; double best_err; };
+struct StepState { int since, retreats, havePrev, held; double best_err; };   // held: the token of largest target, one of the first kStar
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 template <int D>
 __device__ __attribute__((noinline)) StepState newton_step(StepState st, int m, int n, int slack, double ctx, double slack_target, double tsum,
@@ -1262,6 +1262,7 @@ __device__ __attribute__((noinline)) StepState newton_step(StepState st, int m, 
         GR_CLK(L, 17);
         // lane i < 10 holds row i of the remaining vertices: their own edges and what the light tokens left
         float dl[kNodes];
+        const int held = __builtin_amdgcn_readfirstlane(st.held);
         {
             const int i = min(lane, kNodes - 1);
             float a[kNodes], r1 = L.Am[kNodes][i];
@@ -1275,6 +1276,18 @@ __device__ __attribute__((noinline)) StepState newton_step(StepState st, int m, 
 #pragma unroll
                 for (int k = 0; k < kStar; ++k) a[k] += L.W[k][kStar];
                 r1 += static_cast<float>(rhs0);
+            }
+            // The held token takes the place of vertex 0.  With a light one held the others' sum, which its equation hides, is rounding
+            // over its own edges (six tokens, two drafts, the first one's target 1e-35: 68 evaluations).
+            if (held != 0) {
+                const int swapped = lane == 0 ? held : (lane == held ? 0 : lane);
+                float other = 0.f;
+#pragma unroll
+                for (int k = 1; k < kStar; ++k) { other = k == held ? a[k] : other; a[k] = k == held ? a[0] : a[k]; }
+                a[0] = other;
+#pragma unroll
+                for (int k = 0; k < kNodes; ++k) a[k] = __shfl(a[k], swapped);
+                r1 = __shfl(r1, swapped);
             }
             float e[kNodes][kNodes], c[kNodes];
 #pragma unroll
@@ -1296,6 +1309,10 @@ __device__ __attribute__((noinline)) StepState newton_step(StepState st, int m, 
 #pragma unroll
                 for (int x = 1; x < k; ++x) v = fmaf(e[k][x], dl[x], v);
                 dl[k] = v;
+            }
+            if (held != 0) {
+#pragma unroll
+                for (int k = 1; k < kStar; ++k) { dl[0] = k == held ? dl[k] : dl[0]; dl[k] = k == held ? 0.f : dl[k]; }
             }
         }
         GR_CLK(L, 20);
@@ -1470,8 +1487,10 @@ __device__ __forceinline__ int solve_program(Lds<D>& L, int& par, double* newton
     // Wave-0 state: uniform scalars in registers, per-token values in LDS (L.aal, L.at, the best point and the last one, each with
     // its step).
     StepState st;
-    st.since = 0; st.retreats = 0; st.havePrev = 0; st.best_err = 1e300;
+    st.since = 0; st.retreats = 0; st.havePrev = 0; st.held = 0; st.best_err = 1e300;
     if (wvi == 0) {
+        // up to kStar tokens stand in decreasing q, and heavy ones before the others: the largest target is not always the first
+        st.held = (kStar - 1) - static_cast<int>(wave_max_u(lane < min(m, kStar) ? (__float_as_uint(static_cast<float>(L.at[lane])) & ~(kStar - 1u)) | (kStar - 1u - lane) : 0u) & (kStar - 1u));
         const int tk[2] = {lane, lane + 64};
         const bool on[2] = {tk[0] < m, tk[1] < m};
         double ws = 0.0, wm = 1e300, amax = -1e300;
