@@ -67,6 +67,8 @@ constexpr int kRetreats = 30;        // returns to the best point, each with hal
 constexpr int kStarBudget = 60;      // the iteration gets kStarBudget + m evaluations before the fallback takes over
 constexpr int kRowW = 12;            // floats of a token's row of couplings: kStar couplings, slack, hub, right-hand side, 1 / sum
 constexpr int kNodes = kStar + 2;    // the reduced system's vertices: kStar tokens, slack, hub
+constexpr float kLightest = 0x1p-100f;   // a row whose edges sum to less of the program's mass takes no part in the reduced system:
+                                     // its reciprocal overflows below 2^-127, and from 2^-102 on its right-hand side lacks the digits for 1e-8
 constexpr int kMaxHeavy = 3;         // tokens that keep their exact factor (only with more than 8 drafts)
 constexpr double kHeavyShare = 0.3;  // ... those above this share of the program's draw mass
 
@@ -1229,7 +1231,7 @@ __device__ __attribute__((noinline)) StepState newton_step(StepState st, int m, 
                 if (tk[u] >= kStar) {
                     wr[u][9] = fmaxf(static_cast<float>((R[u] - S[u]) * inv) - known, 0.f);
                     const float d = known + wr[u][9];
-                    wr[u][11] = d > 0.f ? __builtin_amdgcn_rcpf(d) : 0.f;
+                    wr[u][11] = d >= kLightest ? __builtin_amdgcn_rcpf(d) : 0.f;
                 }
             }
             if (tk[u] < max(m, kStar)) {
@@ -1262,6 +1264,7 @@ __device__ __attribute__((noinline)) StepState newton_step(StepState st, int m, 
         GR_CLK(L, 17);
         // lane i < 10 holds row i of the remaining vertices: their own edges and what the light tokens left
         float dl[kNodes];
+        bool alone[2] = {false, false};                        // tokens whose rows are left out: they take the fixed-point step
         const int held = __builtin_amdgcn_readfirstlane(st.held);
         {
             const int i = min(lane, kNodes - 1);
@@ -1279,8 +1282,8 @@ __device__ __attribute__((noinline)) StepState newton_step(StepState st, int m, 
             }
             // The held token takes the place of vertex 0.  With a light one held the others' sum, which its equation hides, is rounding
             // over its own edges (six tokens, two drafts, the first one's target 1e-35: 68 evaluations).
+            const int swapped = lane == 0 ? held : (lane == held ? 0 : lane);
             if (held != 0) {
-                const int swapped = lane == 0 ? held : (lane == held ? 0 : lane);
                 float other = 0.f;
 #pragma unroll
                 for (int k = 1; k < kStar; ++k) { other = k == held ? a[k] : other; a[k] = k == held ? a[0] : a[k]; }
@@ -1290,13 +1293,16 @@ __device__ __attribute__((noinline)) StepState newton_step(StepState st, int m, 
                 r1 = __shfl(r1, swapped);
             }
             float e[kNodes][kNodes], c[kNodes];
+            unsigned lost = 0u;
 #pragma unroll
             for (int k = kNodes - 1; k >= 1; --k) {
                 float ak[kNodes], s = 0.f;
 #pragma unroll
                 for (int x = 0; x < k; ++x) { ak[x] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(a[x]), k)); s += ak[x]; }
                 const float rk = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(r1), k));
-                const float is = s > 0.f ? __builtin_amdgcn_rcpf(s) : 0.f, fac = a[k] * is;
+                const bool light = !(s >= kLightest);
+                const float is = light ? 0.f : __builtin_amdgcn_rcpf(s), fac = a[k] * is;
+                lost |= light ? 1u << k : 0u;
                 c[k] = rk * is;
                 r1 = fmaf(fac, rk, r1);
 #pragma unroll
@@ -1314,6 +1320,7 @@ __device__ __attribute__((noinline)) StepState newton_step(StepState st, int m, 
 #pragma unroll
                 for (int k = 1; k < kStar; ++k) { dl[0] = k == held ? dl[k] : dl[0]; dl[k] = k == held ? 0.f : dl[k]; }
             }
+            alone[0] = lane < kStar && (lost >> swapped & 1u) != 0u;
         }
         GR_CLK(L, 20);
         const float base = slack ? dl[kStar] : 0.f;
@@ -1323,11 +1330,12 @@ __device__ __attribute__((noinline)) StepState newton_step(StepState st, int m, 
 #pragma unroll
             for (int c = 0; c < kNodes; ++c) v = fmaf(wr[u][c], dl[c], v);
             v *= wr[u][11];
+            if (tk[u] >= kStar) alone[u] = wr[u][11] == 0.f;
             if (u == 0) {
 #pragma unroll
                 for (int c = 0; c < kStar; ++c) v = lane == c ? dl[c] : v;
             }
-            f[u] = static_cast<double>(v - base);
+            f[u] = alone[u] ? g[u] + lc : static_cast<double>(v - base);
         }
         // A few programs are left with a linear rate by what the hub stands for: near the end a step is combined with the one
         // before it (one secant pair).

@@ -73,3 +73,18 @@ def test_a_light_token_that_comes_first_does_not_steer_the_step(V, k, n):
     out = run_gpu(wl, 1e-5)
     _check_weights(wl, out, 1e-5, wl.meta["token"])
     assert out["iterations"].max() <= 24, out["iterations"]
+
+
+@pytest.mark.parametrize("V, k, n", [(64, 0, 2), (64, 0, 9), (512, 64, 4), (300, 100, 8), (40, 6, 2), (40, 6, 16)])
+def test_a_token_too_light_for_the_step_s_float32(V, k, n):
+    """Target gaps up to the last float32 probability and, as logits, beyond it (a token banned by its logit): the reciprocal of such
+    a token's row overflowed, and the step of every token with it.  60 to 480 evaluations."""
+    from test_gpu_logits import _compare, _drafts_from_logits, _run_logits
+    wl = _favoured(V, k, n, [84, 88, 92, 98, 103, 106, 110, 200])
+    out = run_gpu(wl, 1e-5)
+    _check_weights(wl, out, 1e-5, wl.meta["token"])
+    assert out["iterations"].max() <= 24, out["iterations"]
+    drafts = _drafts_from_logits(wl, range(wl.B), 3)
+    out = _run_logits(wl, 1e-5, drafts)
+    _compare(wl, out, range(wl.B), 1e-5, drafts)
+    assert np.all(out["status"] == 0) and out["iterations"].max() <= 24, out["iterations"]
