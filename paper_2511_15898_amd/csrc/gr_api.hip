@@ -475,6 +475,8 @@ extern "C" int gr_tree_walk(gr_handle h, const float* p, const float* q, const f
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const int k_eff = (k <= 0 || k >= V) ? V : k;
     const bool in_lds = k_eff <= kMaxSupport;
+    if (!in_lds && k_eff > h->k_cap) return GR_EINVAL;
+    if (temperature && h->tail_mass > 0.0) return GR_EUNSUPPORTED;               // the nucleus cut is defined on probabilities
     // Per row in: where it begins, its draft count, its drafts, uniform, temperature; out: token, status, acceptance, flag.
     constexpr size_t kIn = sizeof(long long) + sizeof(int) * (1 + GR_MAX_N) + 2 * sizeof(float), kOut = 2 * sizeof(int) + sizeof(float) + 1;
     const size_t rows = static_cast<size_t>(h->max_B), cols = static_cast<size_t>(h->max_V);
@@ -482,6 +484,9 @@ extern "C" int gr_tree_walk(gr_handle h, const float* p, const float* q, const f
                         (h->tw_host || hipHostMalloc(reinterpret_cast<void**>(&h->tw_host), rows * (kIn + kOut), hipHostMallocDefault) == hipSuccess) &&
                         (in_lds || ((h->tw_p || dev_alloc(&h->tw_p, rows * cols)) && (h->tw_q || dev_alloc(&h->tw_q, rows * cols))));
     if (!staged) { (void)hipGetLastError(); return GR_ENOMEM; }          // what was allocated stays for the next call
+    // A batch leaves no policy of the caller's rows in the handle, and the copies use the staging that the next call writes: no return
+    // leaves either behind.
+    auto fail = [&](int rc) { h->solved = false; (void)hipStreamSynchronize(stream); return rc; };
     try {
     // the state of every sequence lives on the host: the paths that still agree with the tokens emitted so far
     std::vector<unsigned> active(S, K >= 32 ? 0xFFFFFFFFu : ((1u << K) - 1u));
@@ -504,7 +509,6 @@ extern "C" int gr_tree_walk(gr_handle h, const float* p, const float* q, const f
             }
             const int cnt = static_cast<int>(seqs.size());
             if (cnt == 0) continue;
-            if (temperature && h->tail_mass > 0.0) return GR_EUNSUPPORTED;       // the nucleus cut is defined on probabilities
             const size_t at_n = sizeof(long long) * cnt, at_d = at_n + sizeof(int) * cnt, at_u = at_d + sizeof(int) * cnt * most,
                          at_t = at_u + sizeof(float) * cnt, in_bytes = at_t + sizeof(float) * cnt;
             long long* const idx = reinterpret_cast<long long*>(h->tw_host);
@@ -520,7 +524,7 @@ extern "C" int gr_tree_walk(gr_handle h, const float* p, const float* q, const f
                 us[j] = uniforms[static_cast<size_t>(s) * L + l];
                 ts[j] = temperature ? temperature[s] : 1.f;
             }
-            if (hipMemcpyAsync(h->tw_in, h->tw_host, in_bytes, hipMemcpyHostToDevice, stream) != hipSuccess) return GR_EHIP;
+            if (hipMemcpyAsync(h->tw_in, h->tw_host, in_bytes, hipMemcpyHostToDevice, stream) != hipSuccess) return fail(GR_EHIP);
             const long long* const d_at = reinterpret_cast<const long long*>(h->tw_in);
             const int* const d_n = reinterpret_cast<const int*>(h->tw_in + at_n); const int* const d_drafts = reinterpret_cast<const int*>(h->tw_in + at_d);
             const float* const d_u = reinterpret_cast<const float*>(h->tw_in + at_u);
@@ -533,13 +537,13 @@ extern "C" int gr_tree_walk(gr_handle h, const float* p, const float* q, const f
                 if (rc == GR_OK) mark_no_verify(h, stream);
             } else {
                 hipLaunchKernelGGL(gather_rows_kernel, dim3(cnt), dim3(kThreads), 0, stream, p, q, d_at, h->tw_p, h->tw_q, V);
-                if (hipGetLastError() != hipSuccess) return GR_EHIP;
+                if (hipGetLastError() != hipSuccess) return fail(GR_EHIP);
                 rc = solve_entry(h, h->tw_p, h->tw_q, d_temp, nullptr, group, k, tol, cnt, V, d_drafts, d_u, o_acc, o_st, o_tok, o_ok, stream);
             }
-            if (rc != GR_OK) { (void)hipStreamSynchronize(stream); return rc; }        // the copy reads the staging that the next call writes
+            if (rc != GR_OK) return fail(rc);
             unsigned char* const back = h->tw_host + rows * kIn;
             if (hipMemcpyAsync(back, h->tw_out, kOut * cnt, hipMemcpyDeviceToHost, stream) != hipSuccess ||
-                hipStreamSynchronize(stream) != hipSuccess) return GR_EHIP;
+                hipStreamSynchronize(stream) != hipSuccess) return fail(GR_EHIP);
             const int* const tok = reinterpret_cast<const int*>(back); const int* const st = tok + cnt;
             const unsigned char* const okv = back + 3 * sizeof(int) * cnt;
             for (int j = 0; j < cnt; ++j) {

@@ -1,0 +1,90 @@
+"""The library's host code without a GPU, on a HIP runtime that only records (recorded_hip.c): what a call leaves behind when one of
+its HIP calls fails, and what it launches."""
+import json
+import os
+import subprocess
+import sys
+
+import pytest
+
+from paper_2511_15898_amd.build import LIB_PATH, build_library
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+# Runs in a process of its own: its HIP symbols must come before those of any runtime that is loaded already.
+PROGRAM = r'''
+import ctypes as C, json, sys
+hip = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)
+hip.recorded_log.restype = C.c_char_p
+lib = C.CDLL(sys.argv[2])
+
+def create(B, V, k, n):
+    h = C.c_void_p()
+    assert lib.gr_create(C.byref(h), B, V, k, n, None) == 0
+    return h
+def log():
+    return hip.recorded_log().decode().split("\n")[:-1]
+def buffer(n):
+    return (C.c_double * n)()
+
+def walk(h, S, K, L, V, k):
+    rows = buffer(S * K * L * V // 2 + 1)
+    ints = [(C.c_int * (S * L))() for _ in range(4)]
+    return lib.gr_tree_walk(h, rows, rows, None, (C.c_int * (S * K * L))(), (C.c_float * (S * L))(), S, K, L, V, k, C.c_float(1e-4), *ints, None)
+def solve(h, B, V, n, k):
+    rows, out = buffer(B * V // 2 + 1), buffer(B)
+    return lib.gr_solve(h, rows, rows, n, k, C.c_float(1e-4), B, V, out, out, None)
+def verify(h, B):
+    return lib.gr_verify(h, buffer(64 * B), buffer(B), buffer(B), buffer(B), None)
+def sweep(h, B, V, ks, ns):
+    rows, out = buffer(B * V // 2 + 1), buffer(B * 128)
+    return lib.gr_accept_sweep(h, rows, rows, (C.c_int * len(ks))(*ks), len(ks), (C.c_int * len(ns))(*ns), len(ns), B, V, out, out, None)
+
+result = {}
+exec(sys.argv[3])
+print(json.dumps(result))
+'''
+
+
+@pytest.fixture(scope="module")
+def recorded(tmp_path_factory):
+    if not os.path.exists(LIB_PATH):
+        build_library()
+    so = str(tmp_path_factory.mktemp("recorded") / "librecorded_hip.so")
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-o", so, os.path.join(HERE, "recorded_hip.c")], check=True)
+
+    def run(body):
+        r = subprocess.run([sys.executable, "-c", PROGRAM, so, LIB_PATH, body], capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0, r.stdout + r.stderr
+        return json.loads(r.stdout)
+    return run
+
+
+@pytest.mark.parametrize("V, k", [(1024, 32), (1024, 300)])
+@pytest.mark.parametrize("call, after", [("to_host", 0), ("synchronize", 0), ("to_device", 0)])
+def test_a_walk_that_fails_leaves_no_policy_and_nothing_in_flight(recorded, V, k, call, after):
+    """A batch of a walk is read through row offsets, so what it leaves in the handle is no policy of the caller's rows; and the
+    staging that its copies use belongs to the next call."""
+    r = recorded(f"""
+h = create(4, {V}, {k}, 3)
+result["whole"] = walk(h, 4, 3, 2, {V}, {k})
+hip.recorded_clear()
+hip.recorded_fail(b"{call}", {after})
+result["rc"] = walk(h, 4, 3, 2, {V}, {k})
+result["log"] = log()
+result["verify"] = verify(h, 4)
+""")
+    EHIP, ESTATE = -4, -3
+    assert r["whole"] == 0 and r["rc"] == EHIP
+    assert r["verify"] == ESTATE
+    assert r["log"][-1].startswith("synchronize"), r["log"]
+
+
+def test_a_refused_walk_leaves_the_policy_of_the_last_solve(recorded):
+    r = recorded("""
+h = create(4, 1024, 32, 3)
+result["solve"] = solve(h, 4, 1024, 3, 32)
+result["walk"] = walk(h, 4, 3, 2, 1024, 0)          # no workspace for a support this large
+result["verify"] = verify(h, 4)
+""")
+    assert r == {"solve": 0, "walk": -1, "verify": 0}
