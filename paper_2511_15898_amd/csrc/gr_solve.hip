@@ -67,6 +67,8 @@ constexpr int kRetreats = 30;        // returns to the best point, each with hal
 constexpr int kStarBudget = 60;      // the iteration gets kStarBudget + m evaluations before the fallback takes over
 constexpr int kRowW = 12;            // floats of a token's row of couplings: kStar couplings, slack, hub, right-hand side, 1 / sum
 constexpr int kNodes = kStar + 2;    // the reduced system's vertices: kStar tokens, slack, hub
+constexpr double kMostCoupled = 1e30;   // a larger weight of a coupling is that of nodes where only tokens too light for the step are left,
+                                     // and would overflow
 constexpr float kLightest = 0x1p-100f;   // a row whose edges sum to less of the program's mass takes no part in the reduced system:
                                      // its reciprocal overflows below 2^-127, and from 2^-102 on its right-hand side lacks the digits for 1e-8
 constexpr int kMaxHeavy = 3;         // tokens that keep their exact factor (only with more than 8 drafts)
@@ -486,7 +488,7 @@ __device__ __forceinline__ void star_series(const float (&Tr)[D], const double* 
     cum_g_from<1, M>(fmaf(-x, x, x), fmaf(-2.f, x, 1.f), g);
 #pragma unroll
     for (int b = 1; b <= M; ++b) phi[b - 1] = x * g[b - 1] * static_cast<float>(e[b - 1]);
-    float cw = static_cast<float>(qw2 * fmin(tw, 1000.0));    // beyond that x = 0
+    float cw = static_cast<float>(fmin(qw2 * fmin(tw, 1000.0), kMostCoupled));   // beyond 1000 x = 0
     float u[Lds<D>::kSer];
 #pragma unroll
     for (int k = 1; k <= Lds<D>::kSer; ++k) {
@@ -565,7 +567,7 @@ __device__ __forceinline__ void star_series_exact(const double (&T)[D + 1], cons
 #pragma unroll
     for (int d = 0; d < D; ++d) B[d] = T[d];
     divide_factor<D>(B, x, e);
-    const double cx = qw2 * fmin(tw, 1000.0) * x;
+    const double cx = fmin(qw2 * fmin(tw, 1000.0), kMostCoupled) * x;
     V[0] = 0.0;
 #pragma unroll
     for (int d = 1; d < D; ++d) {
