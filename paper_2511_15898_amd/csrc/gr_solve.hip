@@ -1154,7 +1154,7 @@ __device__ int newton_program(Lds<D>& L, int& par, double* J, int m, int n, doub
 // of 1024, n = 4, k = 32: 122 -> 80; 256 rows of 128256, n = 8, k = 128: 272 -> 217.
 // Compiled as a function of its own (not inlined) so that its values do not compete for registers with the evaluator's series.
 // The uniform solver state travels in StepState; per-token values live in LDS (see solve_program).
-struct StepState { int since, retreats, havePrev, held; double best_err; };   // held: the token of largest target, one of the first kStar
+struct StepState { int since, retreats, havePrev, held; double best_err; };   // held: the token of largest target, 0 up to eight drafts
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 template <int D>
 __device__ __attribute__((noinline)) StepState newton_step(StepState st, int m, int n, int slack, double ctx, double slack_target, double tsum,
@@ -1217,6 +1217,7 @@ __device__ __attribute__((noinline)) StepState newton_step(StepState st, int m, 
         rhs0 = (rhs0 - lack * R0) * inv;
         // the tokens' rows: couplings to the kStar (in place), to the slack, what is left (light tokens), right-hand side, 1 / sum
         float wr[2][kRowW];
+        bool alone[2] = {false, false};                        // tokens too light for the reduced system: they take the fixed-point step
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             if (u == 1 && !two) continue;
@@ -1230,11 +1231,9 @@ __device__ __attribute__((noinline)) StepState newton_step(StepState st, int m, 
                 wr[u][8] = L.W[tk[u]][8];
                 const float known = ((c0.x + c0.y) + (c0.z + c0.w)) + ((c1.x + c1.y) + (c1.z + c1.w)) + wr[u][8];
                 wr[u][10] = static_cast<float>(rhs[u]);
-                if (tk[u] >= kStar) {
-                    wr[u][9] = fmaxf(static_cast<float>((R[u] - S[u]) * inv) - known, 0.f);
-                    const float d = known + wr[u][9];
-                    wr[u][11] = d >= kLightest ? __builtin_amdgcn_rcpf(d) : 0.f;
-                }
+                const float rest = fmaxf(static_cast<float>((R[u] - S[u]) * inv) - known, 0.f), d = known + rest;
+                alone[u] = !(d >= kLightest);
+                if (tk[u] >= kStar) { wr[u][9] = rest; wr[u][11] = alone[u] ? 0.f : __builtin_amdgcn_rcpf(d); }
             }
             if (tk[u] < max(m, kStar)) {
 #pragma unroll
@@ -1266,8 +1265,7 @@ __device__ __attribute__((noinline)) StepState newton_step(StepState st, int m, 
         GR_CLK(L, 17);
         // lane i < 10 holds row i of the remaining vertices: their own edges and what the light tokens left
         float dl[kNodes];
-        bool alone[2] = {false, false};                        // tokens whose rows are left out: they take the fixed-point step
-        const int held = __builtin_amdgcn_readfirstlane(st.held);
+        const int held = D > 8 ? __builtin_amdgcn_readfirstlane(st.held) : 0;
         {
             const int i = min(lane, kNodes - 1);
             float a[kNodes], r1 = L.Am[kNodes][i];
@@ -1282,10 +1280,10 @@ __device__ __attribute__((noinline)) StepState newton_step(StepState st, int m, 
                 for (int k = 0; k < kStar; ++k) a[k] += L.W[k][kStar];
                 r1 += static_cast<float>(rhs0);
             }
-            // The held token takes the place of vertex 0.  With a light one held the others' sum, which its equation hides, is rounding
+            // Where heavy tokens stand first, the held one takes the place of vertex 0.  With a light one held the others' sum, which its equation hides, is rounding
             // over its own edges (six tokens, two drafts, the first one's target 1e-35: 68 evaluations).
-            const int swapped = lane == 0 ? held : (lane == held ? 0 : lane);
-            if (held != 0) {
+            if (D > 8 && held != 0) {
+                const int swapped = lane == 0 ? held : (lane == held ? 0 : lane);
                 float other = 0.f;
 #pragma unroll
                 for (int k = 1; k < kStar; ++k) { other = k == held ? a[k] : other; a[k] = k == held ? a[0] : a[k]; }
@@ -1295,16 +1293,13 @@ __device__ __attribute__((noinline)) StepState newton_step(StepState st, int m, 
                 r1 = __shfl(r1, swapped);
             }
             float e[kNodes][kNodes], c[kNodes];
-            unsigned lost = 0u;
 #pragma unroll
             for (int k = kNodes - 1; k >= 1; --k) {
                 float ak[kNodes], s = 0.f;
 #pragma unroll
                 for (int x = 0; x < k; ++x) { ak[x] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(a[x]), k)); s += ak[x]; }
                 const float rk = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(r1), k));
-                const bool light = !(s >= kLightest);
-                const float is = light ? 0.f : __builtin_amdgcn_rcpf(s), fac = a[k] * is;
-                lost |= light ? 1u << k : 0u;
+                const float is = s >= kLightest ? __builtin_amdgcn_rcpf(s) : 0.f, fac = a[k] * is;
                 c[k] = rk * is;
                 r1 = fmaf(fac, rk, r1);
 #pragma unroll
@@ -1318,11 +1313,10 @@ __device__ __attribute__((noinline)) StepState newton_step(StepState st, int m, 
                 for (int x = 1; x < k; ++x) v = fmaf(e[k][x], dl[x], v);
                 dl[k] = v;
             }
-            if (held != 0) {
+            if (D > 8 && held != 0) {
 #pragma unroll
                 for (int k = 1; k < kStar; ++k) { dl[0] = k == held ? dl[k] : dl[0]; dl[k] = k == held ? 0.f : dl[k]; }
             }
-            alone[0] = lane < kStar && (lost >> swapped & 1u) != 0u;
         }
         GR_CLK(L, 20);
         const float base = slack ? dl[kStar] : 0.f;
@@ -1332,7 +1326,6 @@ __device__ __attribute__((noinline)) StepState newton_step(StepState st, int m, 
 #pragma unroll
             for (int c = 0; c < kNodes; ++c) v = fmaf(wr[u][c], dl[c], v);
             v *= wr[u][11];
-            if (tk[u] >= kStar) alone[u] = wr[u][11] == 0.f;
             if (u == 0) {
 #pragma unroll
                 for (int c = 0; c < kStar; ++c) v = lane == c ? dl[c] : v;
@@ -1453,6 +1446,15 @@ __device__ __forceinline__ int solve_program(Lds<D>& L, int& par, double* newton
             L.aq[me] = q; L.at[me] = t; L.aal[me] = al; L.apos[me] = pos;
         }
     }
+    else if (D <= 8 && wvi == 0) {
+        // the token of largest target to the front, where the step holds it; with more drafts heavy tokens may stand there
+        const double t = tid < m ? L.at[tid] : 0.0, al = tid < m ? L.aal[tid] : 0.0;
+        const int pos = tid < m ? L.apos[tid] : 0;
+        const int big = (kStar - 1) - static_cast<int>(wave_max_u(tid < m ? (__float_as_uint(static_cast<float>(t)) & ~(kStar - 1u)) | (kStar - 1u - tid) : 0u) & (kStar - 1u));
+        me = tid == 0 ? big : (tid == big ? 0 : tid);
+        wave_lds_sync();
+        if (tid < m) { L.aq[me] = q; L.at[me] = t; L.aal[me] = al; L.apos[me] = pos; }
+    }
     int full = 0;
     if (tid < m) {
         // per-token series of e^{zq}: q^k / k! for k <= n (terms beyond z^n never reach the z^n coefficient)
@@ -1499,8 +1501,7 @@ __device__ __forceinline__ int solve_program(Lds<D>& L, int& par, double* newton
     StepState st;
     st.since = 0; st.retreats = 0; st.havePrev = 0; st.held = 0; st.best_err = 1e300;
     if (wvi == 0) {
-        // up to kStar tokens stand in decreasing q, and heavy ones before the others: the largest target is not always the first
-        st.held = (kStar - 1) - static_cast<int>(wave_max_u(lane < min(m, kStar) ? (__float_as_uint(static_cast<float>(L.at[lane])) & ~(kStar - 1u)) | (kStar - 1u - lane) : 0u) & (kStar - 1u));
+        if (D > 8) st.held = (kStar - 1) - static_cast<int>(wave_max_u(lane < min(m, kStar) ? (__float_as_uint(static_cast<float>(L.at[lane])) & ~(kStar - 1u)) | (kStar - 1u - lane) : 0u) & (kStar - 1u));
         const int tk[2] = {lane, lane + 64};
         const bool on[2] = {tk[0] < m, tk[1] < m};
         double ws = 0.0, wm = 1e300, amax = -1e300;
