@@ -1197,6 +1197,7 @@ __global__ __launch_bounds__(NT) void full_sweep_rank_kernel(FullParams fp, Full
     const int* order = fp.order + row * vs;
     unsigned long long* k0 = fp.key0 + row * vs; unsigned long long* k1 = fp.key1 + row * vs;
     int* qrank = fp.blk + row * vs;                              // by ratio rank: the token's rank by decreasing q
+    int* by_id = fp.blo + row * vs;                              // ... by token id, where the whole vocabulary is sorted and the row is short
     // the ranks by decreasing q, ties by id, and the q mass of the first k of them for every k of the grid
     double part[kSweepMaxK];
 #pragma unroll
@@ -1228,6 +1229,7 @@ __global__ __launch_bounds__(NT) void full_sweep_rank_kernel(FullParams fp, Full
         for (int u = 0; u < 4; ++u) {
             const int j = j0 + u * NT;
             if (j < kk && !whole) qrank[packed_id(e[u])] = j;
+            else if (j < kk && NT == gr::kThreads) by_id[packed_id(e[u])] = j;
             const double qv = static_cast<double>(__uint_as_float(~static_cast<unsigned>(e[u] >> 32)));   // 0 beyond kk
 #pragma unroll
             for (int a = 0; a < kSweepMaxK; ++a) if (a < fs.nk && j < fs.ks[a]) part[a] += qv;
@@ -1277,9 +1279,11 @@ __global__ __launch_bounds__(kGatherThreads) void full_qrank_kernel(FullParams f
 // before it: it computes nothing.  Bound: arithmetic, 2 float64 operations per token, size and draft count plus the
 // chain.  (One workgroup per row for all sizes, a wave reduction per cell and round, and a chain per draft count:
 // 4576 us for 256 rows of 128256 tokens, 6 sizes and 10 draft counts; now 1388 us, at 3.1 GB.)
+// The small workgroup's rows are short (kShortRow): it reads the pairs and the q ranks through the order, and no kernel gathers them for it.
 template <int NT>
 __global__ __launch_bounds__(NT) void full_sweep_scan_kernel(FullParams fp, FullSweep fs) {
     constexpr int NW = NT / 64;
+    constexpr bool OWN = NT == kThreads;
     __shared__ double wtot[2][2][NW];                            // two rounds in turn: one barrier a round
     __shared__ double cell[kSweepMaxN][NW];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, row = blockIdx.x, a = blockIdx.y;
@@ -1294,6 +1298,9 @@ __global__ __launch_bounds__(NT) void full_sweep_scan_kernel(FullParams fp, Full
     const int kk = info.support;
     const float2* by_rank = fp.pairs + row * vs;
     const int* qrank = fp.blk + row * vs;
+    const float2* pq = reinterpret_cast<const float2*>(fp.rho_id + row * vs);
+    const int* order = fp.order + row * vs; const int* by_id = fp.blo + row * vs;
+    const bool ranked = !OWN || fp.tcount[3 * row] == 0;
     const double invp = 1.0 / info.p_total;
     const int ka = fs.ks[a];
     const double inv = 1.0 / fs.mass[row * kSweepMaxK + a];
@@ -1309,9 +1316,10 @@ __global__ __launch_bounds__(NT) void full_sweep_scan_kernel(FullParams fp, Full
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int r = t0 + 4 * tid + j;
-            const bool on = r < kk && qrank[r] < ka;
+            const int id = OWN && r < kk ? order[r] : 0;
+            const bool on = r < kk && (ranked ? qrank[r] : by_id[id]) < ka;
             any |= on;
-            const float2 y = on ? by_rank[r] : make_float2(0.f, 0.f);
+            const float2 y = on ? (OWN ? pq[id] : by_rank[r]) : make_float2(0.f, 0.f);
             accp += static_cast<double>(y.x); accs += static_cast<double>(y.y);
             lp[j] = accp; ls[j] = accs;
         }
@@ -1377,19 +1385,30 @@ static void launch_full_order(const FullParams& fp, hipStream_t stream) {
     else hipLaunchKernelGGL(full_order_kernel<kThreads>, dim3(fp.B), dim3(kThreads), 0, stream, fp);
 }
 
+// Rows up to kShortRow take the small workgroup in a grid (a round of a 1024-thread workgroup is 4096 ranks: they would fill fewer than two
+// rounds) and three launches: the rank kernel leaves the q ranks by token id, and the scan reads them and the pairs through the order, once per
+// top-k size.  Three / six launches, the call with eight sizes and eight draft counts: 1 row of 300 tokens 57.1 / 61.9 us, 256 rows of 3000
+// 152.8 / 165.5, of 8192 375.1 / 379.5; 256 rows of 12000 456.3 / 430.7, of 24000 949 / 780.
+constexpr int kShortRow = 8192;
+
 void launch_full_sweep(const FullParams& fp, const FullSweep& fs, hipStream_t stream) {
     launch_full_order(fp, stream);
+    const dim3 cells(fp.B, fs.nk);
+    if (fp.V <= kShortRow) {
+        hipLaunchKernelGGL(full_sweep_rank_kernel<kThreads>, dim3(fp.B), dim3(kThreads), 0, stream, fp, fs);
+        hipLaunchKernelGGL(full_sweep_scan_kernel<kThreads>, cells, dim3(kThreads), 0, stream, fp, fs);
+        return;
+    }
     const int chunks = (fp.V + kChunkRanks - 1) / kChunkRanks;
     const dim3 grid(chunk_grid(fp.B, chunks));
     hipLaunchKernelGGL(full_gather_kernel, grid, dim3(kGatherThreads), kGatherLds, stream, fp, chunks);
     if (fp.V > kLongRow) hipLaunchKernelGGL((full_sweep_rank_kernel<1024, 8>), dim3(fp.B), dim3(1024), 0, stream, fp, fs);
-    else if (fp.V > 8192) hipLaunchKernelGGL(full_sweep_rank_kernel<1024>, dim3(fp.B), dim3(1024), 0, stream, fp, fs);
-    else hipLaunchKernelGGL(full_sweep_rank_kernel<kThreads>, dim3(fp.B), dim3(kThreads), 0, stream, fp, fs);
-    hipLaunchKernelGGL(full_qrank_kernel<true>, grid, dim3(kGatherThreads), kGatherLds, stream, fp, chunks);
-    hipLaunchKernelGGL(full_qrank_kernel<false>, grid, dim3(kGatherThreads), kGatherLds, stream, fp, chunks);
-    // a round of a 1024-thread workgroup is 4096 ranks: rows that fill fewer than two rounds take the small workgroup
-    if (fp.V > 8192) hipLaunchKernelGGL(full_sweep_scan_kernel<1024>, dim3(fp.B, fs.nk), dim3(1024), 0, stream, fp, fs);
-    else hipLaunchKernelGGL(full_sweep_scan_kernel<kThreads>, dim3(fp.B, fs.nk), dim3(kThreads), 0, stream, fp, fs);
+    else hipLaunchKernelGGL(full_sweep_rank_kernel<1024>, dim3(fp.B), dim3(1024), 0, stream, fp, fs);
+    if (fp.k > fp.V / 2) {                                       // a smaller support is never ranked by token id
+        hipLaunchKernelGGL(full_qrank_kernel<true>, grid, dim3(kGatherThreads), kGatherLds, stream, fp, chunks);
+        hipLaunchKernelGGL(full_qrank_kernel<false>, grid, dim3(kGatherThreads), kGatherLds, stream, fp, chunks);
+    }
+    hipLaunchKernelGGL(full_sweep_scan_kernel<1024>, cells, dim3(1024), 0, stream, fp, fs);
 }
 
 // The reserved LDS of the chunk kernels lies above the default limit.

@@ -37,3 +37,30 @@ def test_rows_on_both_sort_tiles(V):
     out = run_gpu(wl, 1e-3, export_rows=range(wl.B))
     check_alpha_all_rows(wl, out)
     compare_rows(wl, out, range(wl.B), 1e-3)
+
+
+@pytest.mark.parametrize("B, V, top", [(3, 301, 290), (2, 1025, 513), (2, 8192, 300), (2, 8192, 0), (63, 8193, 0), (64, 8193, 4097), (66, 8193, 4096),
+                                       (2, 12289, 0), (1, 65537, 0)])
+def test_grids_on_both_sides_of_the_short_rows(B, V, top):
+    """Rows that gather for themselves and rows that have it done, supports above and up to half of the vocabulary, row counts on both
+    sides of the one from which a row's chunks share an XCD, and draft masses that tie at the ends of the supports."""
+    import torch
+    from oracle import gr_oracle as G
+    from paper_2511_15898_amd import binding as gr
+    rng = np.random.default_rng(B * V + top)
+    wl = W.llm_shaped(B=B, V=V, n=2, k=0, seed_sub=1600 + V)
+    p, q = wl.p, wl.q.copy()
+    q[:, rng.permutation(V)[: V // 3]] = np.float32(0.5 / V)          # many equal entries: ties go to the lower id
+    q = (q / q.sum(1, keepdims=True, dtype=np.float64)).astype(np.float32)
+    ks, ns = [5, 200, 257, top], [1, 3, 7]
+    dev = torch.device("cuda:0")
+    h = gr.gr_create(B, V, max_k=top)
+    try:
+        acc, st = gr.gr_accept_sweep(h, torch.from_numpy(p).to(dev), torch.from_numpy(q).to(dev), ks, ns)
+        torch.cuda.synchronize()
+        acc, st = acc.cpu().numpy(), st.cpu().numpy()
+    finally:
+        gr.gr_destroy(h)
+    assert np.all(st == 0)
+    for b in sorted({0, B // 2, B - 1}):
+        assert np.abs(acc[b] - G.acceptance_sweep(p[b], q[b], ks, ns)).max() < 1e-5, b
