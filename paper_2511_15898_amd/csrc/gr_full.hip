@@ -701,7 +701,10 @@ __global__ __launch_bounds__(kGatherThreads) void full_gather_kernel(FullParams 
 // ---- kernel 3: prefix sums in the order, F, H*, alpha*, suffix minima, residuals, records, blocks.
 //
 // Ascending, in tiles of 2048 ranks: the sequential sums P (waves 0-3) and Q (waves 4-7), eight terms per lane (RunSum).  A sum that leaves its binade inside the tile is right up to the lane where it
-// does; the lanes behind it go again with the new unit (a row's sums double some 40 times, mostly in its first tile).
+// does; the lanes behind it go again with the new unit (a row's sums double some 40 times, mostly in its first tile).  So one wave adds the
+// first ranks of a row, where most of that happens: all of a row of up to 1024 ranks, 256 of a longer one.  No ranks / 256 / 512 / 1024 so, the
+// call: 1 row of 300 tokens 128 / 119 / 114 / 114 us, 256 rows of 700 278 / 271 / 269 / 257, 1 row of 1500 157 / 154 / 156 / 161, 256 rows of 8192
+// 502 / 493 / 499 / 504.
 // Descending: F, its suffix minima G, residuals, records (F(m) <= G(m + 1); m = kk always) and the number of records behind
 // every rank, in one pass: below H* the suffix minimum is F(h) throughout, so residuals and records there come out 0 and none,
 // and h is the first record.
@@ -711,6 +714,8 @@ __global__ __launch_bounds__(kGatherThreads) void full_gather_kernel(FullParams 
 __global__ __launch_bounds__(kScanThreads, 4) void full_scan_kernel(FullParams fp) {
     constexpr int NT = kScanThreads, NW = NT / 64, CW = NW / 2, E = 8, kTile = 64 * CW * E, PER = kTile / NT;
     static_assert(CW == 4 && PER == 4, "four waves per sum, four ranks per thread");
+    constexpr int kRound = 32, kHead = 256, kWhole = 1024;     // ranks that one wave adds at the start of a row, and of a row that it adds alone
+    static_assert(kHead % (kRound * E) == 0 && kWhole <= kTile, "rounds of the first tile, whole lanes");
     __shared__ double xs[2][kTile + kTile / E];                // a lane's eight terms, then its sums; one word of padding per lane
     __shared__ RunSum run[NW];
     __shared__ double upto[NW];
@@ -745,13 +750,33 @@ __global__ __launch_bounds__(kScanThreads, 4) void full_scan_kernel(FullParams f
 #pragma unroll
         for (int j = 0; j < PER; ++j) { const int r = t0 + kTile + j * NT + tid; x2[j] = r < kk ? by_rank[r] : make_float2(0.f, 0.f); }
         __syncthreads();
+        const int head = t0 > 0 ? 0 : (kk <= kWhole ? kWhole : kHead);   // ranks whose sums take the place of their terms here
+        if (head) {
+#pragma clang fp contract(off)
+            if (cw == 0) {
+                for (int i0 = 0; i0 < min(head, kk); i0 += kRound) {
+                    double v[kRound];
+#pragma unroll
+                    for (int i = 0; i < kRound; ++i) v[i] = xs[chain][pad(i0 + i)];
+#pragma unroll
+                    for (int i = 0; i < kRound; ++i) { acc = acc + v[i]; v[i] = acc; }
+                    if (lane == 0) {
+#pragma unroll
+                        for (int i = 0; i < kRound; ++i) xs[chain][pad(i0 + i)] = v[i];
+                    }
+                }
+                if (lane == 0) upto[wv] = acc;
+            }
+            __syncthreads();
+            acc = upto[chain * CW];
+        }
         double x[E], sum[E];
         const int mine = (cw * 64 + lane) * (E + 1);
 #pragma unroll
-        for (int e = 0; e < E; ++e) { x[e] = xs[chain][mine + e]; sum[e] = 0.0; }
-        {
+        for (int e = 0; e < E; ++e) { x[e] = xs[chain][mine + e]; sum[e] = x[e]; }
+        if (t0 + head < kk) {
 #pragma clang fp contract(off)
-            for (int pos = 0;;) {                              // the lanes of the chain from `pos` on
+            for (int pos = head / E;;) {                       // the lanes of the chain from `pos` on
                 const long long bits = __double_as_longlong(acc);
                 const double unit = __longlong_as_double(bits & 0x7FF0000000000000ll), odd = __longlong_as_double((bits & 0x7FF0000000000000ll) | 1ll);
                 const bool none = acc < 1e-290;                // nothing to speak of yet: the first term starts the sum

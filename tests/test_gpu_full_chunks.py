@@ -39,6 +39,15 @@ def test_rows_on_both_sort_tiles(V):
     compare_rows(wl, out, range(wl.B), 1e-3)
 
 
+@pytest.mark.parametrize("V", [1000, 1023, 1024, 1025, 1033])
+def test_sums_of_the_ranks_that_one_wave_adds(V):
+    """Rows up to the length that one wave adds alone, and above it: supports that end in and behind its last lane."""
+    wl = W.llm_shaped(B=3, V=V, n=3, k=0, seed_sub=1500 + V)
+    out = run_gpu(wl, 1e-3, export_rows=range(wl.B))
+    check_alpha_all_rows(wl, out)
+    compare_rows(wl, out, range(wl.B), 1e-3)
+
+
 @pytest.mark.parametrize("B, V, top", [(3, 301, 290), (2, 1025, 513), (2, 8192, 300), (2, 8192, 0), (63, 8193, 0), (64, 8193, 4097), (66, 8193, 4096),
                                        (2, 12289, 0), (1, 65537, 0)])
 def test_grids_on_both_sides_of_the_short_rows(B, V, top):
