@@ -208,3 +208,28 @@ def test_logits_on_both_workgroup_sizes_of_the_order_kernel(V, n, k, tol):
     out = _run_logits(wl, tol, drafts, export_rows=range(wl.B))
     st = _compare(wl, out, range(wl.B), tol, drafts)
     assert st["rows"] == wl.B and st["fragile"] < wl.B
+
+
+@pytest.mark.parametrize("T", [1.0, 1.3])
+def test_row_sum_of_a_plateau_below_the_largest_logit(T):
+    """100000 targets 25 to 28 temperatures below one: together 1e-8 to 1e-6 of the row's sum, the same term for all of them, so their errors
+    add up.  Eight equal draft logits, two drafts: the largest target's residual is p_0 - 1 + (7/8)^2, in float64, exact but for
+    the sum.  Tolerance: the lane that holds the largest term adds to it once for every 1024 tokens, half a unit of 2.2e-16 each
+    time.  (Float32 exponentials from 25 temperatures on: 3e-14 to 9e-14.)"""
+    import torch
+    from paper_2511_15898_amd import binding as gr
+    gaps = np.float32(T) * np.linspace(25.02, 27.9, 16, dtype=np.float32)
+    B, V = len(gaps), 100000
+    t = np.repeat(-gaps[:, None], V, axis=1); t[:, 77] = 0.0
+    d = np.full((B, V), -50.0, np.float32); d[:, 77 + 1000 * np.arange(8)] = 0.0
+    dev = torch.device("cuda:0")
+    h = gr.gr_create(B, V, max_k=8, max_n=2)
+    try:
+        acc, st = gr.gr_solve_logits(h, torch.from_numpy(t).to(dev), torch.from_numpy(d).to(dev), torch.full((B,), T, device=dev), 2, 8, 1e-4)
+        out = {k: v.cpu().numpy() for k, v in gr.gr_policy_export(h, B, dev).items()}
+    finally:
+        gr.gr_destroy(h)
+    term = np.exp(-gaps.astype(np.longdouble) / np.longdouble(np.float32(T)))
+    want = 1 / (1 + (V - 1) * term) - 1 + np.longdouble(49) / 64
+    assert np.all(out["h_size"] == 7) and np.all(out["order"][:, 7] == 77)
+    assert np.abs(out["rho"][:, 7] - want).max() < V / 1024 * 1.1e-16, out["rho"][:, 7] - want
