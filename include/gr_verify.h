@@ -206,8 +206,9 @@ int gr_solve_logits_verify(gr_handle h, const float* target_logits, const float*
  * Multi-step verification over a tree of draft paths (App. "Multi-Step Experiments": K i.i.d. paths of length L
  * are drafted autoregressively from the draft model; the verifier advances from the root with n = the number of
  * drafted continuations of the current node until it lands off the tree; a row whose solve fails is sampled from p).
- * For each of S sequences and each level, sequences are grouped by n; every group is gathered, solved with
- * gr_solve(n) and sampled with gr_verify, and the paths that drew the emitted token go on to the next level.
+ * Every level is one batch: the current node of each of the S sequences, read where its row lies, solved with gr_solve at the node's
+ * own n and sampled with gr_verify; the paths that drew the emitted token go on to the next level.  With a support above
+ * GR_MAX_SUPPORT the sequences of a level are grouped by n, and every group is gathered and is a batch of its own.
  *
  * p, q       DEVICE [S, K, L, V] float32: the target / draft distribution after the first l tokens of path a of
  *            sequence s (paths with equal prefixes must carry equal rows; level 0 is the same row for all paths).
@@ -219,9 +220,9 @@ int gr_solve_logits_verify(gr_handle h, const float* target_logits, const float*
  * out_tokens HOST [S, L] int32: the tokens emitted, -1 beyond the last.  out_len [S]: how many (the walk emits one
  *            token per level visited; no bonus token after a fully accepted tree).  out_accepted [S]: how many of
  *            them were drafts.  out_fallbacks [S] or NULL: levels whose row had a status other than GR_ROW_OK.
- * The first call allocates staging for max_B rows of max_V tokens (8 max_V bytes per row; GR_ENOMEM); every call
- * synchronises the stream once per level and group, and leaves the handle without a policy (GR_ESTATE for a
- * gr_verify that follows).
+ * The first call allocates staging (97 bytes per row on the device and in pinned host memory; the first call with a support above
+ * GR_MAX_SUPPORT also 8 max_V bytes per row on the device; GR_ENOMEM); every call synchronises the stream once per batch, and one that
+ * has enqueued a batch leaves the handle without a policy (GR_ESTATE for a gr_verify that follows), also where it fails.
  */
 int gr_tree_walk(gr_handle h, const float* p, const float* q, const float* temperature, const int* paths,
                  const float* uniforms, int S, int K, int L, int V, int k, float tol,
@@ -251,8 +252,8 @@ int gr_policy_export_row(gr_handle h, int row, int count, int* order, int* block
                          double* rho, void* hip_stream);
 
 /* Work done by the last gr_solve, per row ([B] device arrays, either may be NULL):
- * evaluations = calls of the routed-mass evaluator (one per fixed-point or Newton step, plus
- * the finite-difference columns of a Newton Jacobian); node_tokens = sum over those calls of
+ * evaluations = calls of the routed-mass evaluator (one per step, plus
+ * the finite-difference columns of the fallback's Jacobian); node_tokens = sum over those calls of
  * (quadrature nodes x active tokens of the program), the unit in which the arithmetic of the
  * generating-function evaluator of Sec. 6.3's objectives is counted: one call costs about
  * 4 n^2 floating-point operations per (node, token) pair. */

@@ -38,7 +38,7 @@ struct Sort32Lds {
 // elements of one digit leave as one run and not one by one.  Three barriers per tile.
 // A run is 128 bytes on average with four elements per thread and 1024 threads, 256 bytes with eight (see kLongRow).
 // Bound: 16 bytes of traffic per element and pass, and the latency of a tile's three barriers (order kernel, 1024 rows of 128256
-// tokens: 18 GB in 6.0 ms, 3.0 TB/s where a device copy reaches 5.1).  All threads call.
+// tokens: 18 GB in 5.3 ms, 3.4 TB/s where a device copy reaches 5.2).  All threads call.
 template <int NT, int R>
 __device__ unsigned long long* block_sort32(unsigned long long* a, unsigned long long* b, int count, Sort32Lds<NT, R>& S, int lo = 32,
                                            int passes = 4) {
@@ -535,10 +535,9 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
         lo = id_bits + max(0, bits((range >> shift) + base) - 32);
     }
     auto code = [&](unsigned long long key) -> unsigned long long { return key >= kmin ? ((key - kmin) >> shift) + base : (key >> 63) << under; };
-    // the support in token order, with its codes; p and q of a token side by side for the kernels behind this one, which
-    // read them in the order of the ratios: one line of memory per token and not two (full_scan_kernel, 1024 rows of
-    // 128256 tokens: 10.92 -> 9.57 ms, 256 rows: 3.45 -> 3.06 ms; full_sweep_rank_kernel, 256 rows: 3.54 -> 3.12 ms;
-    // writing the pairs: 0.03-0.24 ms)
+    // the support in token order, with its codes; p and q of a token side by side for the kernel that gathers them in the
+    // order of the ratios: one line of memory per token and not two (1024 rows of 128256 tokens, when a row's workgroup gathered for
+    // itself: 10.92 -> 9.57 ms; writing the pairs: 0.03-0.24 ms)
     float2* pq = reinterpret_cast<float2*>(fp.rho_id + row * vs);   // the dense kernel writes the residuals there later
     double* rho_id = fp.rho_id + row * vs; int* rank_of = fp.rank_of + row * vs;
     int kk = 0, close = 0;                                       // close: twice the sampled pairs of tokens that are near
@@ -1005,6 +1004,7 @@ __global__ __launch_bounds__(NT) void full_trunc_kernel(FullParams fp) {
     __syncthreads();
     // Many tokens that stay are a sort of their own, and most such rows end above the cap.  A token whose class leaves more than tau
     // in the classes below it joins its set whatever the order within the classes, so where those alone exceed the cap, the row does.
+    // The large workgroup only: the small one's LDS holds one histogram of the two, and its rows have at most 8192 tokens to sort.
     if constexpr (NT >= 1024) {
         if (kept > NT) {
             int* chist = reinterpret_cast<int*>(&S);
@@ -1303,7 +1303,7 @@ __global__ __launch_bounds__(kGatherThreads) void full_qrank_kernel(FullParams f
 // ipow takes for each of them apart.  A wave none of whose 256 tokens belongs to the support repeats the prefix
 // before it: it computes nothing.  Bound: arithmetic, 2 float64 operations per token, size and draft count plus the
 // chain.  (One workgroup per row for all sizes, a wave reduction per cell and round, and a chain per draft count:
-// 4576 us for 256 rows of 128256 tokens, 6 sizes and 10 draft counts; now 1388 us, at 3.1 GB.)
+// 4576 us for 256 rows of 128256 tokens, 6 sizes and 10 draft counts; now 1012 us, at 3.1 GB.)
 // The small workgroup's rows are short (kShortRow): it reads the pairs and the q ranks through the order, and no kernel gathers them for it.
 template <int NT>
 __global__ __launch_bounds__(NT) void full_sweep_scan_kernel(FullParams fp, FullSweep fs) {

@@ -20,7 +20,7 @@ struct RowInfo {
     int support;        // k' = |V_0|
     int h;              // |H*|
     int status;         // GR_ROW_*
-    int iterations;     // fixed-point evaluations summed over the row's programs
+    int iterations;     // evaluations of the routed masses, summed over the row's programs
     double alpha_star;  // 1 + psi(H*)
     double res_total;   // sum of residuals p(i) - p_i over tokens outside H* (= 1 - alpha*)
     double p_total;     // float64 row sum of p

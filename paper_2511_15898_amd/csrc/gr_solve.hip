@@ -651,7 +651,7 @@ __device__ __forceinline__ void star_phase(Lds<D>& L, int lane, int wv, int m, d
 //
 // Tokens are held in decreasing q: first the (at most three, only with more than 8 drafts) heavy ones that keep
 // their exact factor, then up to L.nfull tokens with all D cumulants, then the tokens that need four.  A chunk
-// of up to 64 quadrature nodes is dealt to the waves (wave w owns nodes w, w + NW, ...), and a wave takes
+// of up to 64 quadrature nodes is dealt to the waves (wave w owns the pairs of nodes w, w + NW, ...), and a wave takes
 // its nodes through all three phases without a workgroup barrier:
 //   phase 1  lane = (node, token subset): the cumulant sums of its tokens at its node, then a butterfly over
 //            the subsets;
@@ -1146,12 +1146,14 @@ __device__ int newton_program(Lds<D>& L, int& par, double* J, int m, int n, doub
 // are eliminated one by one, sum over i of W_i W_i^T / d_i on the matrix cores, and ten vertices remain.  Those are eliminated
 // with every diagonal taken as the sum of its row's edges, so nothing is subtracted and float32 gives the step to 1e-5
 // relative whatever the edges' sizes; the token of largest target is held, so its equation, the one whose rounding would
-// hide the slack's, is the one left out.  In the solver's emulation (1134 programs, n = 2..16) this takes 5.2, 4.5, 4.3 and 4.2
-// evaluations for n = 2, 3-4, 5-8 and 9-16, 17 at most; the fixed-point iteration with Anderson mixing that stood here took
-// 8.9, 7.4, 6.4 and 5.7, and 33 at most.
-// Bound: the serial chain of the stepping wave (about 9 k cycles for up to 64 tokens) between two evaluations.  A call of 256 rows of
-// 32000 tokens, n = 4, k = 64: 242 -> 126 us (and 2424 -> 132 where a row of the batch had reached the finite differences); 64 rows
-// of 1024, n = 4, k = 32: 122 -> 80; 256 rows of 128256, n = 8, k = 128: 272 -> 217.
+// hide the slack's, is the one left out; a token whose row is too light for float32 takes the fixed-point step, which is exact to first
+// order there.  Rows of 40 to 512 tokens with one to three tokens that the draft favours and the target excludes by up to e^-800 (7577
+// rows, n = 2..16) take 5.7 evaluations on average and 31 at most; the fixed-point iteration with Anderson mixing that stood here
+// 10.1 and 90.
+// Bound: the serial chain of the stepping wave (about 9 k cycles for up to 64 tokens) between two evaluations.  Against that iteration, both
+// timed in turn, a call of 256 rows of 32000 tokens, n = 4, k = 64: 251 -> 150 us (its slowest row decides: 1.4 to 1.9 times on other
+// rows); 64 rows of 1024, n = 4, k = 32: 119 -> 77; 256 rows of 128256, n = 8, k = 128: 264 -> 221.  Single rows: 1.25 times on average over 60,
+// three of them slower (0.80 to 0.97), where both take the same three to five evaluations and a series of degree 16 makes the couplings dear.
 // Compiled as a function of its own (not inlined) so that its values do not compete for registers with the evaluator's series.
 // The uniform solver state travels in StepState; per-token values live in LDS (see solve_program).
 struct StepState { int since, retreats, havePrev, held; double best_err; };   // held: the token of largest target, 0 up to eight drafts

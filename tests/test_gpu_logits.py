@@ -233,3 +233,26 @@ def test_row_sum_of_a_plateau_below_the_largest_logit(T):
     want = 1 / (1 + (V - 1) * term) - 1 + np.longdouble(49) / 64
     assert np.all(out["h_size"] == 7) and np.all(out["order"][:, 7] == 77)
     assert np.abs(out["rho"][:, 7] - want).max() < V / 1024 * 1.1e-16, out["rho"][:, 7] - want
+
+
+@pytest.mark.parametrize("V, finite, status", [(700, 40, 0), (2500, 60, 0), (9000, 60, 0), (9001, 100, 0), (2500, 2500, 1), (9001, 9001, 1)])
+def test_truncation_sets_of_hundreds_and_thousands_of_tokens(V, finite, status):
+    """Flat drafts of either sign, no top-k: sets that are sorted as elements of 33 bits (a draft logit's pattern and its side of H*), in
+    rows of the small and of the large workgroup.  All but `finite` targets are masked, so the sets stay within the cap; with all of
+    them finite a row ends above it, where it is long by the classes alone."""
+    import dataclasses
+    rng = np.random.default_rng(V + finite)
+    t = (4.0 * rng.gumbel(size=(3, V))).astype(np.float32)
+    d = rng.normal(size=(3, V)).astype(np.float32)
+    for b in range(3):
+        t[b, rng.permutation(V)[finite:]] = -np.inf
+        d[b] += np.float32([-3.0, 0.0, 3.0][b])
+        d[b, np.isfinite(t[b])] += np.float32(1.0)
+        if status:
+            t[b] = 0.5 * d[b] + rng.normal(size=V).astype(np.float32) * 0.3
+    z = np.where(np.isfinite(t), t, -1e4).astype(np.float64)
+    wl = W._finish("flat", W._softmax32(z), W._softmax32(d.astype(np.float64)), 3, 0, rng, {"target_logits": t, "draft_logits": d, "temps": np.array([0.8, 1.0, 1.3])})
+    drafts = _drafts_from_logits(wl, range(3), 23)
+    out = _run_logits(wl, 1e-4, drafts, export_rows=range(3))
+    st = _compare(wl, out, range(3), 1e-4, drafts)
+    assert st["rows"] == 3 and np.all(out["status"] == status), out["status"]

@@ -26,3 +26,24 @@ def test_evaluations_of_the_step(n, most, mean_most):
     assert np.mean(out["status"] == 0) > 0.99
     ev = out["iterations"][out["status"] == 0]
     assert ev.max() <= most and ev.mean() <= mean_most, (int(ev.max()), float(ev.mean()))
+
+
+@pytest.mark.parametrize("n", [2, 4, 8, 9, 16])
+def test_the_finite_differences_stay_at_the_solution(n):
+    """A tolerance that no evaluation meets: the step's budget of 60 + m evaluations ends, and the damped Newton iteration with a
+    finite-difference Jacobian goes on from its best point to the iteration cap, on the evaluator and the order of tokens that the
+    step uses.  The rows end at the cap; their weights must be those of rows solved to 1e-12 (a target's saturation amplifies that
+    at most a thousandfold on these rows)."""
+    wl = W.small(B=6, V=64, n=n, k=12, seed_sub=n + 12)
+    solved = run_gpu(wl, 1e-5, rel_tol=1e-12)
+    out = run_gpu(wl, 1e-5, rel_tol=1e-17, max_iter=200)
+    assert np.all(solved["status"] == 0) and solved["iterations"].max() < 60          # the step alone
+    ran = solved["iterations"] > 0                         # rows with a program
+    assert ran.sum() >= 4 and np.all(out["status"][ran] == 2) and np.all(out["iterations"][ran] >= 200), out["iterations"]
+    assert np.array_equal(out["order"], solved["order"]) and np.array_equal(out["block"], solved["block"])
+    w, want = out["weight"][ran], solved["weight"][ran]
+    kk = out["support"][ran]
+    for b in range(len(kk)):
+        some = want[b, : kk[b]] > 0
+        assert np.array_equal(w[b, : kk[b]] > 0, some)
+        assert np.abs(w[b, : kk[b]][some] / want[b, : kk[b]][some] - 1.0).max() < 1e-9, b
