@@ -58,13 +58,15 @@ constexpr double kQuadEnd[5] = {1.01966774875832561, -0.714299827412849101, 0.20
 constexpr double kQuadPair = 1.198;  // weight of the first node of every other one for t^2: 1 + 1 / (e^{4 step} - 1)
 constexpr double kQuadHi = 25.0;     // t_hi * (slowest decay rate)
 constexpr int kStar = 8;             // tokens of a program whose couplings to every token are computed (the others meet in a hub)
-constexpr double kClip = 3.0;        // longest step in log weight
+constexpr double kClip = 3.0;        // longest step of a token in log weight.  Each token's own: one that saturates asks for steps without a bound, and with
+                                     // all steps scaled to the longest it held up the others for good (rows at the cap after 1000 evaluations)
 constexpr double kOddsFrom = 0.5;    // a target above this share of Pr[token drawn] aims at its log odds while its mass falls short
-constexpr double kSecantBelow = 1e-2;   // stopping measure from which on a step is combined with the one before it
+constexpr double kSecantBelow = 1e-2;   // stopping measure from which on a step is combined with the one before it ...
+constexpr int kSecantAfter = 5;      // ... as it is after this many evaluations, which only a program with a slow mode needs
 constexpr double kKeepBelow = 1e-3;  // stopping measure from which on the couplings stay as they are
 constexpr int kStall = 4;            // steps without a better point before fixed-point steps are mixed in
 constexpr int kRetreats = 30;        // returns to the best point, each with half the step, before the program is left to the fallback
-constexpr int kStarBudget = 60;      // the iteration gets kStarBudget + m evaluations before the fallback takes over
+constexpr int kStarBudget = 120;     // the iteration gets kStarBudget + m evaluations before the fallback takes over
 constexpr int kRowW = 12;            // floats of a token's row of couplings: kStar couplings, slack, hub, right-hand side, 1 / sum
 constexpr int kNodes = kStar + 2;    // the reduced system's vertices: kStar tokens, slack, hub
 constexpr double kMostCoupled = 1e30;   // a larger weight of a coupling is that of nodes where only tokens too light for the step are left,
@@ -1160,7 +1162,7 @@ struct StepState { int since, retreats, havePrev, held; double best_err; };   //
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 template <int D>
 __device__ __attribute__((noinline)) StepState newton_step(StepState st, int m, int n, int slack, double ctx, double slack_target, double tsum,
-                                                           double rel_tol, int evals) {
+                                                           double rel_tol, int evals, int evals0) {
     Lds<D>& L = *reinterpret_cast<Lds<D>*>(gr_lds_raw);
     const int tid = threadIdx.x, lane = tid & 63;
     const bool two = m > 64;                               // uniform: lane l holds tokens l and l + 64
@@ -1334,9 +1336,10 @@ __device__ __attribute__((noinline)) StepState newton_step(StepState st, int m, 
             }
             f[u] = alone[u] ? g[u] + lc : static_cast<double>(v - base);
         }
+        const double plain[2] = {f[0], f[1]};                  // what the best point keeps: half of a secant step gone astray would still be one
         // A few programs are left with a linear rate by what the hub stands for: near the end a step is combined with the one
         // before it (one secant pair).
-        if (err < kSecantBelow) {
+        if (err < kSecantBelow || evals - evals0 > kSecantAfter) {
             if (st.havePrev) {
                 double df[2] = {0.0, 0.0}, da[2] = {0.0, 0.0};
 #pragma unroll
@@ -1352,18 +1355,17 @@ __device__ __attribute__((noinline)) StepState newton_step(StepState st, int m, 
                 st.havePrev = 1;
             }
         }
-        double longest = wave_max(fmax(fabs(f[0]), fabs(f[1])));
-        const bool broken = __any(!(fabs(f[0]) < 1e300) || !(fabs(f[1]) < 1e300));   // fmax drops a NaN, so `longest` does not show one
-        if (st.since >= kStall || broken) {                 // the fixed-point step, which lowers the objective whatever the point
+        const bool broken = __any(!(fabs(f[0]) < 1e300) || !(fabs(f[1]) < 1e300));   // a clipped NaN would pass for a step
+        const bool fixed = st.since >= kStall || broken;
+        if (fixed) {                 // the fixed-point step, which lowers the objective whatever the point
 #pragma unroll
             for (int u = 0; u < 2; ++u) f[u] = on[u] ? g[u] + lc : 0.0;
-            longest = err; st.since = 0; st.havePrev = 0;
+            st.since = 0; st.havePrev = 0;
         }
-        const double cut = longest > kClip ? kClip * fast_rcp(longest) : 1.0;
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            f[u] *= cut;
-            if (better && on[u]) { L.aBest[tk[u]] = al[u]; L.fBest[tk[u]] = f[u]; }
+            f[u] = fmin(fmax(f[u], -kClip), kClip);
+            if (better && on[u]) { L.aBest[tk[u]] = al[u]; L.fBest[tk[u]] = fixed ? f[u] : fmin(fmax(plain[u], -kClip), kClip); }
         }
         if (better) st.best_err = err;
     }
@@ -1560,7 +1562,7 @@ __device__ __forceinline__ int solve_program(Lds<D>& L, int& par, double* newton
         }
         __syncthreads();
         if (wvi != 0) continue;
-        st = newton_step<D>(st, m, n, slack, ctx, slack_target, tsum, rel_tol, *evals);
+        st = newton_step<D>(st, m, n, slack, ctx, slack_target, tsum, rel_tol, *evals, evals0);
     }
     __syncthreads();
     int result = L.ctl_result;
