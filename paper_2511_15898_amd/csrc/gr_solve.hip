@@ -64,6 +64,7 @@ constexpr double kOddsFrom = 0.5;    // a target above this share of Pr[token dr
 constexpr double kSecantBelow = 1e-2;   // stopping measure from which on a step is combined with the one before it ...
 constexpr int kSecantAfter = 5;      // ... as it is after this many evaluations, which only a program with a slow mode needs
 constexpr double kKeepBelow = 1e-3;  // stopping measure from which on the couplings stay as they are
+constexpr int kTurn = 8;             // evaluations between two looks at whether the step should change (a power of two)
 constexpr int kStall = 4;            // steps without a better point before fixed-point steps are mixed in
 constexpr int kRetreats = 30;        // returns to the best point, each with half the step, before the program is left to the fallback
 constexpr int kStarBudget = 120;     // the iteration gets kStarBudget + m evaluations before the fallback takes over
@@ -129,7 +130,7 @@ struct Lds {
     double aBest[kMaxT]; double fBest[kMaxT]; double aPrev[kMaxT]; double fPrev[kMaxT];
     alignas(16) float W[kMaxT][kRowW];   // the tokens' rows of the reduced system
     alignas(16) float Am[16][20];        // the light tokens' share of it, as the matrix cores leave it
-    Grid ctl_grid; int ctl_go, ctl_result, ctl_bestok, ctl_couple;   // handed from the stepping wave to all waves
+    Grid ctl_grid; int ctl_go, ctl_result, ctl_bestok, ctl_couple; double turn_err;   // handed from the stepping wave to all waves
     double e2tab[32];               // 2^(-j/32)
     int nheavy;                     // leading tokens that keep their exact factor
     int nfull;                      // leading tokens (the heavy ones included) that need all D cumulants; the rest need four
@@ -1158,7 +1159,9 @@ __device__ int newton_program(Lds<D>& L, int& par, double* J, int m, int n, doub
 // three of them slower (0.80 to 0.97), where both take the same three to five evaluations and a series of degree 16 makes the couplings dear.
 // Compiled as a function of its own (not inlined) so that its values do not compete for registers with the evaluator's series.
 // The uniform solver state travels in StepState; per-token values live in LDS (see solve_program).
-struct StepState { int since, retreats, havePrev, held; double best_err; };   // held: the token of largest target, 0 up to eight drafts
+// held: the token of largest target (0 up to eight drafts), and kPlainly where the fixed-point step has its turn.
+struct StepState { int since, retreats, havePrev, held; double best_err; };
+constexpr int kPlainly = 16;
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 template <int D>
 __device__ __attribute__((noinline)) StepState newton_step(StepState st, int m, int n, int slack, double ctx, double slack_target, double tsum,
@@ -1269,7 +1272,7 @@ __device__ __attribute__((noinline)) StepState newton_step(StepState st, int m, 
         GR_CLK(L, 17);
         // lane i < 10 holds row i of the remaining vertices: their own edges and what the light tokens left
         float dl[kNodes];
-        const int held = D > 8 ? __builtin_amdgcn_readfirstlane(st.held) : 0;
+        const int held = D > 8 ? __builtin_amdgcn_readfirstlane(st.held) & (kStar - 1) : 0;
         {
             const int i = min(lane, kNodes - 1);
             float a[kNodes], r1 = L.Am[kNodes][i];
@@ -1335,6 +1338,17 @@ __device__ __attribute__((noinline)) StepState newton_step(StepState st, int m, 
                 for (int c = 0; c < kStar; ++c) v = lane == c ? dl[c] : v;
             }
             f[u] = alone[u] ? g[u] + lc : static_cast<double>(v - base);
+        }
+        // Where the couplings mislead (light tokens that meet only one another, tokens that saturate together, an acceptance near 0) the
+        // measure stands still: after kTurn evaluations that did not take it to a tenth the fixed-point step and Newton's change turns, each
+        // with its secant pair.  (Rows that ended at the cap: 31 to 52 evaluations; targets 1e-12 of the slack's 44 to 168: 17 to 33.)
+        if (((evals - evals0) & (kTurn - 1)) == 0) {
+            if (!(st.best_err < 0.1 * L.turn_err)) { st.held ^= kPlainly; st.havePrev = 0; }
+            if (lane == 0) L.turn_err = st.best_err;
+        }
+        if (st.held & kPlainly) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) f[u] = on[u] ? g[u] + lc : 0.0;
         }
         const double plain[2] = {f[0], f[1]};                  // what the best point keeps: half of a secant step gone astray would still be one
         // A few programs are left with a linear rate by what the hub stands for: near the end a step is combined with the one
@@ -1521,7 +1535,7 @@ __device__ __forceinline__ int solve_program(Lds<D>& L, int& par, double* newton
             L.aal[tk[u]] = al; L.trec[tk[u]].aw = w; ws += w; wm = fmin(wm, w);
         }
         ws = wave_sum(ws); wm = wave_min(wm);
-        if (lane == 0) { L.ctl_go = 1; L.ctl_result = 1; L.ctl_bestok = 0; L.ctl_couple = 1; L.ctl_grid = make_grid(slack, ctx, ws, wm); }
+        if (lane == 0) { L.turn_err = 1.0; L.ctl_go = 1; L.ctl_result = 1; L.ctl_bestok = 0; L.ctl_couple = 1; L.ctl_grid = make_grid(slack, ctx, ws, wm); }
     }
     const double inv_mass = fast_rcp(tsum + slack_target);
     for (int it = 1; it <= step_iters; ++it) {
