@@ -1151,7 +1151,7 @@ __device__ int newton_program(Lds<D>& L, int& par, double* J, int m, int n, doub
 // relative whatever the edges' sizes; the token of largest target is held, so its equation, the one whose rounding would
 // hide the slack's, is the one left out; a token whose row is too light for float32 takes the fixed-point step, which is exact to first
 // order there.  Rows of 40 to 512 tokens with one to three tokens that the draft favours and the target excludes by up to e^-800 (7577
-// rows, n = 2..16) take 5.7 evaluations on average and 31 at most; the fixed-point iteration with Anderson mixing that stood here
+// rows, n = 2..16) take 5.6 evaluations on average and 31 at most; the fixed-point iteration with Anderson mixing that stood here
 // 10.1 and 90.
 // Bound: the serial chain of the stepping wave (about 9 k cycles for up to 64 tokens) between two evaluations.  Against that iteration, both
 // timed in turn, a call of 256 rows of 32000 tokens, n = 4, k = 64: 251 -> 150 us (its slowest row decides: 1.4 to 1.9 times on other
