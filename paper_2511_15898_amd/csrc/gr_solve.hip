@@ -1044,7 +1044,7 @@ __device__ __forceinline__ Defect defect_eval(Lds<D>& L, int& par, int m, int n,
 }
 
 // Damped Newton iteration on routed(alpha) = target with a finite-difference Jacobian (the Hessian of
-// Theta_T / Phi_T in alpha), for programs on which the fixed-point iteration is slow (a target that
+// Theta_T / Phi_T in alpha), for programs on which the iteration of newton_step is slow (a target that
 // nearly exhausts the tuples containing its token).  One step costs one evaluation per variable, so
 // it only takes over when the iteration of newton_step has used up its budget.  Without slack the last weight
 // is pinned (the system is singular along the common shift).  Starts from L.aal.

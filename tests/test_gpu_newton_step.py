@@ -52,7 +52,7 @@ def test_the_finite_differences_stay_at_the_solution(n):
 def test_rows_that_held_the_step_up():
     """Rows found among fifteen million random ones (golden/stubborn_rows.json): a token that saturates, whose step without a bound kept
     all others from theirs; slow modes of blocks without slack, which a secant pair ends; a secant step gone astray, halved twenty
-    times; light tokens that meet only one another, and an acceptance near 0, where the fixed-point step is the better one.  Five of
+    times; light tokens that meet only one another, and an acceptance near 0, where the fixed-point step is the better one.  Four of
     them ended at the cap after 1000 evaluations, the others took 41 to 788; the mixed iteration that stood here 2 to 57."""
     import json
     import os
