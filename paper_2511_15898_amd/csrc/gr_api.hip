@@ -35,7 +35,6 @@ struct gr_handle_s {
     int prof_count = 0;
     // full-vocabulary path: workspace (allocated by gr_create when k_cap exceeds GR_MAX_SUPPORT) and the arguments of the last such solve
     void* full_ws = nullptr; size_t full_ws_bytes = 0;
-    double* sweep_mass = nullptr;  // [max_B, kSweepMaxK] q mass of each top-k support of a sweep that runs in the workspace
     FullParams full = {};
     bool full_mode = false;
     // staging of gr_tree_walk (allocated by its first call): what a batch takes and gives, packed, on both sides; rows gathered for the
@@ -69,7 +68,7 @@ bool dev_alloc(T** ptr, size_t count) {
 }
 
 void free_all(gr_handle h) {
-    void* ptrs[] = {h->cand, h->cand_count, h->part_psum, h->part_qsum, h->part_bad, h->piece_psum, h->piece_pref, h->part_pref, h->tw_p, h->tw_q, h->tw_in, h->tw_out, h->sweep_mass, h->newton_ws, h->order, h->block,
+    void* ptrs[] = {h->cand, h->cand_count, h->part_psum, h->part_qsum, h->part_bad, h->piece_psum, h->piece_pref, h->part_pref, h->tw_p, h->tw_q, h->tw_in, h->tw_out, h->newton_ws, h->order, h->block,
                     h->weight, h->rho, h->pnorm, h->info};
     for (void* ptr : ptrs) (void)hipFree(ptr);
     (void)hipFree(h->full_ws);
@@ -194,7 +193,7 @@ int solve_in_hbm(gr_handle h, const float* p, const float* q, const float* tempe
     if (rc != GR_OK) return rc;
     FullParams& f = h->full;
     f.p = p; f.q = q; f.B = B; f.V = V; f.n = n; f.k = k_eff; f.max_T = h->max_T; f.max_iter = h->max_iter;
-    f.tau = static_cast<double>(tol); f.rel_tol = h->rel_tol; f.tail_mass = h->tail_mass; f.dense = 1;
+    f.tau = static_cast<double>(tol); f.rel_tol = h->rel_tol; f.tail_mass = h->tail_mass;
     f.logits = temperature ? 1 : 0; f.temperature = temperature; f.draft_temperature = draft_temperature;
     f.info = h->info; f.accept_prob = accept_prob; f.status = status; f.newton_ws = h->newton_ws;
     mark(h, 0, stream);
@@ -262,7 +261,7 @@ extern "C" int gr_create(gr_handle* out, int max_B, int max_V, int max_k, int ma
         h->tail_mass = cfg->tail_mass;
     }
     if (hipGetDevice(&h->device) != hipSuccess) { delete h; return GR_EHIP; }
-    if (solve_kernel_setup(max_n, k_cap > kMaxSupport) != hipSuccess || (k_cap > kMaxSupport && full_kernel_setup() != hipSuccess)) { delete h; return GR_EHIP; }
+    if (solve_kernel_setup(max_n, k_cap > kMaxSupport) != hipSuccess || (k_cap > kMaxSupport && (full_kernel_setup() != hipSuccess || grid_kernel_setup() != hipSuccess))) { delete h; return GR_EHIP; }
     { unsigned char* na = nullptr; (void)scratch_address(&na); }      // so that gr_accept_sweep_noalloc finds its array later
     const size_t rows = static_cast<size_t>(max_B);
     bool ok = dev_alloc(&h->cand, rows * kSelCap) && dev_alloc(&h->cand_count, rows * kMaxSplits) &&
@@ -278,7 +277,7 @@ extern "C" int gr_create(gr_handle* out, int max_B, int max_V, int max_k, int ma
     if (ok && k_cap > kMaxSupport) {
         // supports above GR_MAX_SUPPORT live in HBM: 96 bytes per token of max_V and row, held until gr_destroy
         const size_t need = full_ws_bytes(rows, static_cast<size_t>(max_V) + 2);
-        ok = hipMalloc(&h->full_ws, need) == hipSuccess && dev_alloc(&h->sweep_mass, rows * kSweepMaxK);
+        ok = hipMalloc(&h->full_ws, need) == hipSuccess;
         if (ok) h->full_ws_bytes = need;
     }
     if (!ok) { free_all(h); delete h; (void)hipGetLastError(); return GR_ENOMEM; }
@@ -367,32 +366,27 @@ extern "C" int gr_accept_sweep(gr_handle h, const float* p, const float* q, cons
     if (B <= 0 || V <= 0 || B > h->max_B || V > h->max_V) return GR_EINVAL;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     {
-        // a top-k above GR_MAX_SUPPORT anywhere in the grid (k <= 0 or k >= V: no top-k): the whole grid runs on
-        // the HBM-resident ordering
+        // a top-k above GR_MAX_SUPPORT anywhere in the grid (k <= 0 or k >= V: no top-k): the whole grid by bins of the ratio
         int kmax = 0;
         if (nk < 1 || nk > kSweepMaxK || nn < 1 || nn > kSweepMaxN) return GR_EINVAL;
         for (int i = 0; i < nk; ++i) { const int ke = (ks[i] <= 0 || ks[i] >= V) ? V : ks[i]; if (ke > kmax) kmax = ke; }
         if (kmax > kMaxSupport) {
             if (kmax > h->k_cap) return GR_EINVAL;                   // the handle holds no workspace for such a support
             if (V >= (1 << 24)) return GR_EUNSUPPORTED;
-            FullSweep fs;
-            fs.nk = nk; fs.nn = nn;
-            for (int i = 0; i < kSweepMaxK; ++i) fs.ks[i] = i < nk ? ((ks[i] <= 0 || ks[i] >= V) ? V : ks[i]) : 0;
-            for (int i = 0; i < kSweepMaxN; ++i) {
-                if (i < nn && (ns[i] < 1 || ns[i] > kSweepMaxDrafts)) return GR_EINVAL;
-                fs.npos[i] = i;
-            }
-            std::stable_sort(fs.npos, fs.npos + nn, [ns](int x, int y) { return ns[x] < ns[y]; });
-            for (int i = 0; i < kSweepMaxN; ++i) fs.ns[i] = i < nn ? ns[fs.npos[i]] : 1;
-            h->solved = false;
-            const int rc = prepare_full(h, B, V);
-            if (rc != GR_OK) return rc;
-            FullParams& f = h->full;
-            f.p = p; f.q = q; f.B = B; f.V = V; f.n = 1; f.k = kmax; f.max_T = h->max_T; f.max_iter = h->max_iter;
-            f.tau = 0.0; f.rel_tol = h->rel_tol; f.tail_mass = 0.0; f.dense = 0; f.logits = 0; f.temperature = nullptr; f.draft_temperature = nullptr;
-            f.info = h->info; f.accept_prob = accept_prob; f.status = status; f.newton_ws = h->newton_ws;
-            fs.mass = h->sweep_mass; fs.accept_prob = accept_prob; fs.status = status;
-            launch_full_sweep(f, fs, stream);
+            GridParams gp;
+            gp.nk = nk; gp.nn = nn;
+            for (int i = 0; i < nn; ++i) if (ns[i] < 1 || ns[i] > kSweepMaxDrafts) return GR_EINVAL;
+            auto effective = [ks, V](int i) { return (ks[i] <= 0 || ks[i] >= V) ? V : ks[i]; };
+            for (int i = 0; i < kSweepMaxK; ++i) gp.kpos[i] = i;
+            for (int i = 0; i < kSweepMaxN; ++i) gp.npos[i] = i;
+            std::stable_sort(gp.kpos, gp.kpos + nk, [&](int x, int y) { return effective(x) < effective(y); });
+            std::stable_sort(gp.npos, gp.npos + nn, [ns](int x, int y) { return ns[x] < ns[y]; });
+            for (int i = 0; i < kSweepMaxK; ++i) gp.ks[i] = i < nk ? effective(gp.kpos[i]) : V;
+            for (int i = 0; i < kSweepMaxN; ++i) gp.ns[i] = i < nn ? ns[gp.npos[i]] : 1;
+            h->solved = false;                                       // the workspace holds the policy of an earlier solve
+            gp.p = p; gp.q = q; gp.V = V; gp.accept_prob = accept_prob; gp.status = status;
+            gp.work = static_cast<unsigned char*>(h->full_ws); gp.work_stride = (static_cast<size_t>(V) + 2) * kFullBytesPerToken;
+            launch_grid(gp, B, stream);
             if (hipGetLastError() != hipSuccess) return GR_EHIP;
             return GR_OK;
         }

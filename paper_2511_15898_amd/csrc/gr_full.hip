@@ -3,8 +3,7 @@
 // without top-k or with a top-k above GR_MAX_SUPPORT, where the support (up to V tokens) does not fit LDS.
 //
 // Every per-token array lives in a per-handle HBM workspace, row-major with stride V + 2; one
-// workgroup works through a row (256 threads; 1024 in the kernels that order and rank long rows; one
-// workgroup per row and top-k size in the acceptance grid's scan).  The arithmetic that decides integers (prefix sums, F,
+// workgroup works through a row (256 threads; 1024 in the kernels that order long rows).  The arithmetic that decides integers (prefix sums, F,
 // the running masses of the truncation sets) is the same sequential fp64 arithmetic as on the
 // LDS-resident path.
 #include "gr_internal.h"
@@ -574,7 +573,7 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
                 const int off = kk + offs[j] + __popcll(mask[j] & ((1ull << lane) - 1ull));
                 k0[off] = e[j];
                 pq[t0 + j * kThreads + tid] = make_float2(pv[j], qv[j]);
-            } else if (fp.dense && t0 + j * kThreads + tid < V) {
+            } else if (t0 + j * kThreads + tid < V) {
                 // a token outside the support keeps all of p as residual
                 const double x = static_cast<double>(pv[j]);
                 rank_of[t0 + j * kThreads + tid] = -1;
@@ -667,7 +666,7 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
     }
 }
 
-// ---- kernel 2: the pairs (p, q) of the support by rank, and (solves) every token's rank.
+// ---- kernel 2: the pairs (p, q) of the support by rank, and every token's rank.
 // Bound: memory, as long as a row's pairs and ranks (1.5 MB at V = 128256) stay in the L2 of the workgroups that share the row, which is why
 // few of them are resident: they reserve LDS (1024 rows: 2.6 ms with ten workgroups of 256 threads to a compute unit, 2.4 with four, 1.85 with
 // two, 1.97 with one).  Gathered and scattered by the scan kernel, a row to a workgroup, they took 5 of its 8.4 ms.
@@ -692,7 +691,7 @@ __global__ __launch_bounds__(kGatherThreads) void full_gather_kernel(FullParams 
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const int r = r0 + j * NT;
-            if (r < end) { by_rank[r] = x[j]; if (fp.dense) rank_of[id[j]] = r; }
+            if (r < end) { by_rank[r] = x[j]; rank_of[id[j]] = r; }
         }
     }
 }
@@ -1198,203 +1197,6 @@ __global__ __launch_bounds__(kThreads) void full_dense_kernel(FullParams fp, int
     }
 }
 
-// ---- acceptance sweep over supports that do not fit LDS (the first experiment of Sec. 7 runs the top-k size up to
-// the whole vocabulary).  Behind full_order_kernel with the grid's largest k: kernel A ranks the support by
-// decreasing q (ties by token id) and leaves, by ratio rank, p / sum p, q and the q rank of every token, plus the
-// q mass of each top-k support of the grid; kernel B takes the masked prefix sums along the ratio order and
-// the minimum of F(m) = P_m - Q_m^n for every cell (Thm 3.1, Sec. 5.1).  Only min F is reported, to 1e-5, so these
-// sums are parallel float64 scans like those of the LDS-resident sweep.
-//
-// The whole vocabulary is ranked by one sort of the tokens in token order (their order is the tie-break: 32-bit keys, four
-// passes); a support below half of it by its own tokens alone, first by id and then by q.
-template <int NT, int R = 4>
-__global__ __launch_bounds__(NT) void full_sweep_rank_kernel(FullParams fp, FullSweep fs) {
-    constexpr int kThreads = NT, kWaves = NT / 64;
-    __shared__ Sort32Lds<NT, R> S;
-    __shared__ double red[kWaves];
-    const int tid = threadIdx.x, row = blockIdx.x;
-    const int V = fp.V;
-    const size_t vs = static_cast<size_t>(V) + 2;
-    const RowInfo info = fp.info[row];
-    if (info.status == GR_ROW_BAD) return;
-    const int kk = info.support;
-    const float* qr = fp.q + static_cast<size_t>(row) * V;
-    const int* order = fp.order + row * vs;
-    unsigned long long* k0 = fp.key0 + row * vs; unsigned long long* k1 = fp.key1 + row * vs;
-    int* qrank = fp.blk + row * vs;                              // by ratio rank: the token's rank by decreasing q
-    int* by_id = fp.blo + row * vs;                              // ... by token id, where the whole vocabulary is sorted and the row is short
-    // the ranks by decreasing q, ties by id, and the q mass of the first k of them for every k of the grid
-    double part[kSweepMaxK];
-#pragma unroll
-    for (int a = 0; a < kSweepMaxK; ++a) part[a] = 0.0;
-    const bool whole = kk > V / 2;
-    const int count = whole ? V : kk;
-    for (int i = tid; i < count; i += NT) {
-        if (whole) { const float qv = qr[i]; k0[i] = pack32(qv > 0.f ? ~__float_as_uint(qv) : ~0u, i); }
-        else k0[i] = pack32(static_cast<unsigned>(order[i]), i);
-    }
-    __syncthreads();
-    unsigned long long* sorted = k0;
-    for (int round = whole ? 1 : 0; round < 2; ++round) {
-        sorted = block_sort32(sorted, sorted == k0 ? k1 : k0, count, S);
-        if (round == 0) {                                        // by token id so far: now by decreasing q
-            for (int j = tid; j < kk; j += NT) {
-                const int r = packed_id(sorted[j]);
-                sorted[j] = pack32(~__float_as_uint(qr[order[r]]), r);
-            }
-            __syncthreads();
-        }
-    }
-    if (tid == 0) fp.tcount[3 * row] = whole ? (sorted == k0 ? 1 : 2) : 0;   // where full_qrank_kernel finds the tokens by q
-    for (int j0 = tid; j0 < kk; j0 += 4 * NT) {                  // the support is the first kk of the vocabulary by q
-        unsigned long long e[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) { const int j = j0 + u * NT; e[u] = j < kk ? sorted[j] : ~0ull; }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int j = j0 + u * NT;
-            if (j < kk && !whole) qrank[packed_id(e[u])] = j;
-            else if (j < kk && NT == gr::kThreads) by_id[packed_id(e[u])] = j;
-            const double qv = static_cast<double>(__uint_as_float(~static_cast<unsigned>(e[u] >> 32)));   // 0 beyond kk
-#pragma unroll
-            for (int a = 0; a < kSweepMaxK; ++a) if (a < fs.nk && j < fs.ks[a]) part[a] += qv;
-        }
-    }
-#pragma unroll
-    for (int a = 0; a < kSweepMaxK; ++a) {
-        const double t = block_sum<kWaves>(part[a], red);
-        if (tid == 0 && a < fs.nk) fs.mass[row * kSweepMaxK + a] = t;
-    }
-}
-
-// Where the rank kernel sorted the whole vocabulary: the q rank of every token id (ids), then of every ratio rank.  Scattered and gathered
-// chunk by chunk from a row that stays in L2; one workgroup per row took 1.6 of the rank kernel's 3.1 ms for 256 rows of 128256 tokens.
-template <bool IDS>
-__global__ __launch_bounds__(kGatherThreads) void full_qrank_kernel(FullParams fp, int chunks) {
-    constexpr int NT = kGatherThreads;
-    int row, chunk;
-    chunk_of(fp.B, chunks, row, chunk);
-    if (row >= fp.B) return;
-    const size_t vs = static_cast<size_t>(fp.V) + 2;
-    const RowInfo info = fp.info[row];
-    if (info.status == GR_ROW_BAD) return;
-    const int where = fp.tcount[3 * row];
-    if (where == 0) return;
-    const unsigned long long* sorted = (where == 1 ? fp.key0 : fp.key1) + row * vs;
-    const int* order = fp.order + row * vs;
-    int* by_id = fp.blo + row * vs; int* qrank = fp.blk + row * vs;
-    const int end = min(info.support, (chunk + 1) * kChunkRanks);
-    for (int r0 = chunk * kChunkRanks + static_cast<int>(threadIdx.x); r0 < end; r0 += 8 * NT) {
-        int id[8], x[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) { const int r = r0 + j * NT; id[j] = r < end ? (IDS ? packed_id(sorted[r]) : order[r]) : 0; }
-        if (!IDS) {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) x[j] = r0 + j * NT < end ? by_id[id[j]] : 0;
-        }
-#pragma unroll
-        for (int j = 0; j < 8; ++j) { const int r = r0 + j * NT; if (r < end) { if (IDS) by_id[id[j]] = r; else qrank[r] = x[j]; } }
-    }
-}
-
-// One workgroup per (row, top-k size): the running minima of its draft counts stay in registers, and the sizes of a grid
-// are spread over the chip.  The draft counts come in rising order
-// (fs.ns; fs.npos is each one's place in the grid), so their powers are one chain of products, the same products that
-// ipow takes for each of them apart.  A wave none of whose 256 tokens belongs to the support repeats the prefix
-// before it: it computes nothing.  Bound: arithmetic, 2 float64 operations per token, size and draft count plus the
-// chain.  (One workgroup per row for all sizes, a wave reduction per cell and round, and a chain per draft count:
-// 4576 us for 256 rows of 128256 tokens, 6 sizes and 10 draft counts; now 1012 us, at 3.1 GB.)
-// The small workgroup's rows are short (kShortRow): it reads the pairs and the q ranks through the order, and no kernel gathers them for it.
-template <int NT>
-__global__ __launch_bounds__(NT) void full_sweep_scan_kernel(FullParams fp, FullSweep fs) {
-    constexpr int NW = NT / 64;
-    constexpr bool OWN = NT == kThreads;
-    __shared__ double wtot[2][2][NW];                            // two rounds in turn: one barrier a round
-    __shared__ double cell[kSweepMaxN][NW];
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, row = blockIdx.x, a = blockIdx.y;
-    const size_t vs = static_cast<size_t>(fp.V) + 2;
-    float* out = fs.accept_prob + (static_cast<size_t>(row) * fs.nk + a) * fs.nn;
-    const RowInfo info = fp.info[row];
-    if (info.status == GR_ROW_BAD) {
-        for (int c = tid; c < fs.nn; c += NT) out[c] = __uint_as_float(0x7fc00000u);
-        if (tid == 0 && a == 0) fs.status[row] = GR_ROW_BAD;
-        return;
-    }
-    const int kk = info.support;
-    const float2* by_rank = fp.pairs + row * vs;
-    const int* qrank = fp.blk + row * vs;
-    const float2* pq = reinterpret_cast<const float2*>(fp.rho_id + row * vs);
-    const int* order = fp.order + row * vs; const int* by_id = fp.blo + row * vs;
-    const bool ranked = !OWN || fp.tcount[3 * row] == 0;
-    const double invp = 1.0 / info.p_total;
-    const int ka = fs.ks[a];
-    const double inv = 1.0 / fs.mass[row * kSweepMaxK + a];
-    double best[kSweepMaxN];                                     // F(0) = 0: the empty prefix
-#pragma unroll
-    for (int b = 0; b < kSweepMaxN; ++b) best[b] = 0.0;
-    double carry_p = 0.0, carry_s = 0.0;
-    int buf = 0;
-    for (int t0 = 0; t0 < kk; t0 += 4 * NT, buf ^= 1) {          // four consecutive ranks per thread
-        double lp[4], ls[4];
-        double accp = 0.0, accs = 0.0;
-        bool any = false;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int r = t0 + 4 * tid + j;
-            const int id = OWN && r < kk ? order[r] : 0;
-            const bool on = r < kk && (ranked ? qrank[r] : by_id[id]) < ka;
-            any |= on;
-            const float2 y = on ? (OWN ? pq[id] : by_rank[r]) : make_float2(0.f, 0.f);
-            accp += static_cast<double>(y.x); accs += static_cast<double>(y.y);
-            lp[j] = accp; ls[j] = accs;
-        }
-        const bool wave_on = __ballot(any) != 0ull;
-        // exclusive prefix of the threads' sums over the workgroup
-        double ip = accp, is = accs;
-        if (wave_on)
-            for (int o = 1; o < 64; o <<= 1) {
-                const double up = __shfl_up(ip, o), us = __shfl_up(is, o);
-                if (lane >= o) { ip += up; is += us; }
-            }
-        if (lane == 63) { wtot[buf][0][wv] = ip; wtot[buf][1][wv] = is; }
-        __syncthreads();
-        double bp = carry_p + (ip - accp), bs = carry_s + (is - accs), tp = 0.0, ts = 0.0;
-#pragma unroll
-        for (int w = 0; w < NW; ++w) {
-            if (w < wv) { bp += wtot[buf][0][w]; bs += wtot[buf][1][w]; }
-            tp += wtot[buf][0][w]; ts += wtot[buf][1][w];
-        }
-        carry_p += tp; carry_s += ts;
-        if (!wave_on) continue;                                  // uniform over the wave; no barrier below
-        double x[4], pw[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) { lp[j] = (lp[j] + bp) * invp; x[j] = (bs + ls[j]) * inv; pw[j] = x[j]; }
-        int e = 1;
-#pragma unroll
-        for (int b = 0; b < kSweepMaxN; ++b) {
-            if (b >= fs.nn) break;
-            for (; e < fs.ns[b]; ++e) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) pw[j] = __dmul_rn(pw[j], x[j]);
-            }
-            // a rank outside this support repeats the prefix before it, so do the ranks beyond kk
-            best[b] = fmin(best[b], fmin(fmin(lp[0] - pw[0], lp[1] - pw[1]), fmin(lp[2] - pw[2], lp[3] - pw[3])));
-        }
-    }
-#pragma unroll
-    for (int b = 0; b < kSweepMaxN; ++b) {
-        const double m = wave_min(best[b]);
-        if (lane == 0) cell[b][wv] = m;
-    }
-    __syncthreads();
-    if (tid < fs.nn) {
-        double t = cell[tid][0];
-        for (int w = 1; w < NW; ++w) t = fmin(t, cell[tid][w]);
-        out[fs.npos[tid]] = static_cast<float>(1.0 + t);
-    }
-    if (tid == 0 && a == 0) fs.status[row] = GR_ROW_OK;
-}
-
 // Workgroups of 1024 threads take rows of more than two of their tiles of 4096 tokens; shorter rows would leave most of one
 // idle.  One of them fills a compute unit, so where rows wait for one (more of them than compute units) and a nucleus cut
 // leaves little to sort, the row must be longer (cut of 1e-3; 1024 against 256 threads, the call): 1024 rows of
@@ -1410,41 +1212,9 @@ static void launch_full_order(const FullParams& fp, hipStream_t stream) {
     else hipLaunchKernelGGL(full_order_kernel<kThreads>, dim3(fp.B), dim3(kThreads), 0, stream, fp);
 }
 
-// Rows up to kShortRow take the small workgroup in a grid (a round of a 1024-thread workgroup is 4096 ranks: they would fill fewer than two
-// rounds) and three launches: the rank kernel leaves the q ranks by token id, and the scan reads them and the pairs through the order, once per
-// top-k size.  Three / six launches, the call with eight sizes and eight draft counts: 1 row of 300 tokens 57.1 / 61.9 us, 256 rows of 3000
-// 152.8 / 165.5, of 8192 375.1 / 379.5; 256 rows of 12000 456.3 / 430.7, of 24000 949 / 780.
-constexpr int kShortRow = 8192;
-
-void launch_full_sweep(const FullParams& fp, const FullSweep& fs, hipStream_t stream) {
-    launch_full_order(fp, stream);
-    const dim3 cells(fp.B, fs.nk);
-    if (fp.V <= kShortRow) {
-        hipLaunchKernelGGL(full_sweep_rank_kernel<kThreads>, dim3(fp.B), dim3(kThreads), 0, stream, fp, fs);
-        hipLaunchKernelGGL(full_sweep_scan_kernel<kThreads>, cells, dim3(kThreads), 0, stream, fp, fs);
-        return;
-    }
-    const int chunks = (fp.V + kChunkRanks - 1) / kChunkRanks;
-    const dim3 grid(chunk_grid(fp.B, chunks));
-    hipLaunchKernelGGL(full_gather_kernel, grid, dim3(kGatherThreads), kGatherLds, stream, fp, chunks);
-    if (fp.V > kLongRow) hipLaunchKernelGGL((full_sweep_rank_kernel<1024, 8>), dim3(fp.B), dim3(1024), 0, stream, fp, fs);
-    else hipLaunchKernelGGL(full_sweep_rank_kernel<1024>, dim3(fp.B), dim3(1024), 0, stream, fp, fs);
-    if (fp.k > fp.V / 2) {                                       // a smaller support is never ranked by token id
-        hipLaunchKernelGGL(full_qrank_kernel<true>, grid, dim3(kGatherThreads), kGatherLds, stream, fp, chunks);
-        hipLaunchKernelGGL(full_qrank_kernel<false>, grid, dim3(kGatherThreads), kGatherLds, stream, fp, chunks);
-    }
-    hipLaunchKernelGGL(full_sweep_scan_kernel<1024>, cells, dim3(1024), 0, stream, fp, fs);
-}
-
 // The reserved LDS of the chunk kernels lies above the default limit.
 hipError_t full_kernel_setup() {
-    const void* kernels[3] = {reinterpret_cast<const void*>(full_gather_kernel), reinterpret_cast<const void*>(full_qrank_kernel<true>),
-                              reinterpret_cast<const void*>(full_qrank_kernel<false>)};
-    for (const void* k : kernels) {
-        const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kGatherLds);
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(full_gather_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kGatherLds);
 }
 
 void launch_full_prologue(const FullParams& fp, hipStream_t stream) {

@@ -82,7 +82,6 @@ struct FullParams {
     float2* pairs;     // the raw pair (p, q) of every rank
     double* P; double* Q; double* rho; double* weight;   // prefix sums (Q of the raw q: divide by Q[kk]), residuals and weights by rank
     int* flag; int* blk; int* blo; int* bcount;
-    int dense;         // 1: a solve, whose policy needs what follows for every token
     int* rank_of;      // [B, V + 2] rank of each token id, -1 outside the support
     double* rho_id;    // [B, V + 2] residual p(i) - p_i by token id (0 inside H*); before the dense kernel: the pair (p, q) of every token of the support
     int* nblk;         // [B] number of outer blocks
@@ -93,8 +92,6 @@ struct FullParams {
 constexpr size_t kFullBytesPerToken = 2 * 8 + 4 + 2 * 4 + 5 * 8 + 4 * 4 + 4 + 8;
 
 void launch_full_prologue(const FullParams& fp, hipStream_t stream);
-struct FullSweep;
-void launch_full_sweep(const FullParams& fp, const FullSweep& fs, hipStream_t stream);
 void launch_select(const float* p, const float* q, int B, int V, int k, int splits, int slice_len,
                    unsigned long long* cand, int* cand_count, double* psum, double* qsum, int* bad,
                    double* piece_psum, int piece_stride, const long long* row_at, hipStream_t stream);
@@ -134,15 +131,18 @@ struct SweepParams {
     int* status;                  // [B]
 };
 hipError_t launch_sweep(const SweepParams& sw, int B, hipStream_t stream);
-// The grid of a sweep whose largest support lives in the HBM workspace.
-struct FullSweep {
+// The grid of a sweep with a top-k above kMaxSupport: sizes and draft counts in rising order, with their places in the caller's lists.
+struct GridParams {
+    const float* p; const float* q; int V;
     int nk, nn;
-    int ks[kSweepMaxK]; int ns[kSweepMaxN];   // ks: V for "no top-k"; ns in rising order
-    int npos[kSweepMaxN];         // place of ns[i] in the caller's list
-    double* mass;                 // [B, kSweepMaxK] q mass of each top-k support
+    int ks[kSweepMaxK], kpos[kSweepMaxK];     // ks: V for "no top-k"
+    int ns[kSweepMaxN], npos[kSweepMaxN];
+    unsigned char* work; size_t work_stride;  // scratch of a row: 72 bytes per token at least
     float* accept_prob;           // [B, nk, nn]
     int* status;                  // [B]
 };
+hipError_t grid_kernel_setup();
+void launch_grid(const GridParams& gp, int B, hipStream_t stream);
 hipError_t solve_kernel_setup(int max_n, bool hbm);
 hipError_t full_kernel_setup();
 

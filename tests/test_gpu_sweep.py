@@ -202,3 +202,29 @@ def test_grids_that_end_below_half_the_vocabulary(V):
     acc, st = _sweep(p[2:3], q[2:3], [0, 300], [1, 2, 8], max_k=0)     # no top-k: the zeros leave a support below V / 2
     assert np.all(st == 0)
     _check(p[2:3], q[2:3], [0, 300], [1, 2, 8], [0], acc)
+
+
+@pytest.mark.parametrize("V", [257, 511, 4097, 12290, 20001])
+def test_rows_that_take_the_bins_to_their_ends(V):
+    """What the bins of the ratio have to resolve: a draft that is the target up to noise (one bin, cut again and again), equal rows, rows of
+    two ratios, flat drafts (the thresholds lie among equal q, more of them than one list holds), masked targets and ratios many
+    octaves apart, rows that begin anywhere (V odd).  F is found to 1e-13; the bound is that of a float32 result."""
+    from oracle import gr_oracle as G
+    rng = np.random.default_rng(V)
+    base = rng.dirichlet(np.full(V, 0.4)) + 1e-12
+    p = np.stack([base] * 7); q = p.copy()
+    q[0] *= np.exp(0.01 * rng.standard_normal(V))                       # draft close to the target
+    q[1] *= 1.0 + 1e-7 * rng.standard_normal(V)                         # the target up to the rounding of float32
+    q[3] = np.where(rng.random(V) < 0.5, 2.0, 0.7) * p[3]               # two ratios
+    q[4] = 1.0                                                          # flat: every threshold among equal q
+    p[5, rng.random(V) < 0.3] = 0.0; q[5, rng.random(V) < 0.3] = 0.0    # masked tokens on both sides
+    p[6] = np.exp(-60.0 * rng.random(V)); q[6] = np.exp(-60.0 * rng.random(V))
+    p = (p / p.sum(1, keepdims=True)).astype(np.float32); q = (q / q.sum(1, keepdims=True)).astype(np.float32)
+    ks, ns = [0, 1, 2, 255, V - 1, V // 2, 100, 100], [1, 2, 3, 16, 64]
+    acc, st = _sweep(p, q, ks, ns, max_k=0)
+    assert np.all(st == 0)
+    for b in range(len(p)):
+        want = G.acceptance_sweep(p[b], q[b], ks, ns)
+        assert np.abs(acc[b] - want).max() <= 2e-7, (b, acc[b], want)    # two roundings of a value up to 1 to float32
+    again, _ = _sweep(p, q, ks, ns, max_k=0)
+    assert np.array_equal(acc, again)
