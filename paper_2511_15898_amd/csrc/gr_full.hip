@@ -6,6 +6,9 @@
 // workgroup works through a row (256 threads; 1024 in the kernels that order long rows).  The arithmetic that decides integers (prefix sums, F,
 // the running masses of the truncation sets) is the same sequential fp64 arithmetic as on the
 // LDS-resident path.
+#include <algorithm>
+#include <type_traits>
+
 #include "gr_internal.h"
 
 namespace gr {
@@ -15,7 +18,6 @@ namespace {
 constexpr int kScanThreads = 512;                  // of the kernel that takes the prefix sums
 constexpr int kChunkRanks = 4096;                  // ranks per workgroup of the kernels that gather and scatter by token id ...
 constexpr int kChunkLds = 40 * 1024;               // ... and the LDS that a workgroup of 256 threads reserves, for four of them to a compute unit (see full_gather_kernel)
-constexpr int kGatherThreads = 512, kGatherLds = 80 * 1024;
 // The sort of the large supports: elements of 8 bytes, the key in the high bits and the token id in the low ones.
 template <int NT, int R = 4>
 struct Sort32Lds {
@@ -265,6 +267,76 @@ __device__ __forceinline__ void chunk_of(int B, int chunks, int& row, int& chunk
     else { row = static_cast<int>(g / chunks); chunk = static_cast<int>(g % chunks); }
 }
 
+// The order's key of a token: rising keys are falling ratios, ties go by the token id.  Rows given as probabilities: the correctly rounded quotient
+// (p = 0 gives an infinity: first); as logits: q/p is proportional to exp((d - t) / T), so d - t (exact in float64; a masked target gives +inf).
+struct RatioKey {
+    bool lg; double inv_temp, inv_temp_q;
+    __device__ __forceinline__ unsigned long long operator()(float qv, float pv) const {
+        const double ratio = lg ? logit_ratio_key(static_cast<double>(qv), static_cast<double>(pv), inv_temp_q, inv_temp)
+                                : static_cast<double>(qv) / static_cast<double>(pv);
+        return lg ? ~mono64(ratio) : ~static_cast<unsigned long long>(__double_as_longlong(ratio));
+    }
+};
+// Buckets of the order: kBucket tokens on average at most (while there are buckets enough), kBucketCap in the LDS of the workgroup that sorts one.
+// With kSamplesPerBucket samples to a bucket, one of twice the average comes up once in 1e6.
+constexpr int kBucket = 1024, kBucketCap = 2048, kSamplesPerBucket = 32, kLogBuckets = 11;
+__host__ __device__ inline int log_buckets(int tokens) {
+    int l = 0;
+    while (tokens > kBucketCap && l < kLogBuckets && (kBucket << l) < tokens) ++l;   // up to the cap one workgroup takes them whole
+    return l;
+}
+// What the order's kernels hand on about a row's buckets, in arrays that later kernels fill.
+constexpr int kMaxSlices = 32;
+struct SplitView {
+    unsigned long long* key; int* id;                            // the splitters
+    unsigned short* bucket;                                      // of a token
+    int* count;                                                  // [slices, buckets]
+    int* first;                                                  // the first rank of each bucket, and of the end
+    __device__ SplitView(const FullParams& fp, int row) {
+        const size_t at = row * (static_cast<size_t>(fp.V) + 2);
+        key = reinterpret_cast<unsigned long long*>(fp.rho + at); id = fp.blk + at;
+        bucket = reinterpret_cast<unsigned short*>(fp.blo + at);
+        count = reinterpret_cast<int*>(fp.weight + at); first = fp.val0 + at;
+    }
+};
+static_assert((kMaxSlices + 1) * 2 * sizeof(int) <= kBucket * sizeof(double), "the counts of a row's slices lie in its weights");
+template <int NT>
+struct SplitLds {
+    static constexpr int kLogBuckets = NT >= 1024 ? gr::kLogBuckets : 4;   // the small workgroup takes rows of up to 16384 tokens
+    static constexpr int kSamples = NT >= 1024 ? 4096 : kSamplesPerBucket << kLogBuckets;
+    unsigned long long key[kSamples];
+    int id[kSamples];
+};
+
+// Sorts `size` (a power of two, at least 64) keys with their ids in LDS, by key and then id.  All threads call; barriers at both ends.
+template <int NT>
+__device__ void block_bitonic(unsigned long long* key, int* id, int size) {
+    for (int k = 2; k <= size; k *= 2)
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            __syncthreads();
+            for (int t = threadIdx.x; t < size / 2; t += NT) {
+                const int i = 2 * t - (t & (j - 1)), o = i + j;
+                const unsigned long long a = key[i], b = key[o];
+                const int ia = id[i], ib = id[o];
+                const bool behind = a > b || (a == b && ia > ib);
+                if (behind == ((i & k) == 0)) { key[i] = b; key[o] = a; id[i] = ib; id[o] = ia; }
+            }
+        }
+    __syncthreads();
+}
+__device__ __forceinline__ unsigned long long wave_min_u64(unsigned long long v) {
+    auto least = [](unsigned long long a, int lo, int hi) { return min(a, (static_cast<unsigned long long>(static_cast<unsigned>(hi)) << 32) | static_cast<unsigned>(lo)); };
+    v = least(v, dpp_move<kDppXor1>(static_cast<int>(v)), dpp_move<kDppXor1>(static_cast<int>(v >> 32)));
+    v = least(v, dpp_move<kDppXor2>(static_cast<int>(v)), dpp_move<kDppXor2>(static_cast<int>(v >> 32)));
+    v = least(v, dpp_move<kDppHalfMirror>(static_cast<int>(v)), dpp_move<kDppHalfMirror>(static_cast<int>(v >> 32)));
+    v = least(v, dpp_move<kDppMirror>(static_cast<int>(v)), dpp_move<kDppMirror>(static_cast<int>(v >> 32)));
+    const int lo = static_cast<int>(v), hi = static_cast<int>(v >> 32);
+    unsigned long long r = ~0ull;
+#pragma unroll
+    for (int l = 0; l < 64; l += 16) r = least(r, __builtin_amdgcn_readlane(lo, l), __builtin_amdgcn_readlane(hi, l));
+    return r;
+}
+
 // What adding a run of terms one after the other does to a running sum, from its rounding alone.  While the sum stays in one
 // binade it is a whole number of units u, and acc + x rounds to acc + r u with r depending on x and, where x lies halfway between
 // two units, on whether acc / u is even.  So a run of terms is two sums (exact, both whole numbers of u) and the parity they
@@ -292,67 +364,33 @@ __device__ __forceinline__ void scan_step(RunSum& v) {
 // ratios differ by at least 2^-48 relative, so their quotients differ and keep their order, and equal
 // ratios give equal quotients -- the same order as the exact cross-product comparison (Sec. 5.1).
 //
-// An element of the sort is 64 bits: the token id in as many low bits as V needs, the token's code above it.  The code is
-// the quotient's pattern relative to the row's first one, without the low bits that there is no room for (15 at most for
-// V = 128256 and probabilities, whose patterns span at most 2^61).  A sort by the 32 leading bits of the codes orders all
-// but the few neighbours that share them; one thread per run of such neighbours puts those in order by the rest of their
-// codes, or by the whole pattern where the codes are equal.
-// A row of tight ratios beside one far away has many such neighbours: a draft that is the target up to rounding, beside a
-// token that the target all but excludes.  The pack loop compares a sample of pairs, nine partners of every token; from
-// two near pairs on the codes are sorted whole (6 passes at V = 128256, 7 at 8192), which costs what it costs to put about
-// one near neighbour per token in order.  Ordinary rows show two such pairs less than once in a million.  A run of more
-// than kMaxRun tokens, which one thread would work on for longer than the workgroup sorts, takes the row to the next sort:
-// by the whole codes, then by the low and the high half of the whole patterns.
-// Ratios that are not finite have codes of their own and don't widen the range.
-// 256 rows of 8192 and of 128256 tokens, us, with eight passes over 12 bytes; with one sort of 32 bits and two more
-// for every row with a long run; and now: ratios within 2^-13 and one masked target 258 and 4230; 633 and 5414; 168 and 1439.
-// Ratios within 2^-18 beside ratios 2^20 and 2^-20: 251 and 4134; 648 and 5378; 249 and 2114 (within 2^-15, 8192 tokens: 283
-// against 255 with eight passes).
-// Bound: as the sort.  One workgroup of 256 threads per row and eight passes
-// over 12 bytes took 15.45 ms for 1024 rows of 128256 tokens and 4.47 ms for 256 of them; four passes over 8 bytes and
-// 1024 threads 6.03 and 1.42 ms.  (Two workgroups per compute unit, at half the registers, spilled and were slower.)
-// With four loads in flight in the passes over the row and in the histogram, which counts only the digits that are sorted by, and scans over
-// the lanes without LDS: 1024 rows 6295 -> 6059 us, 256 rows 1434 -> 1382 us, 64 rows cut by a nucleus 119 -> 105 us.  (24 leading bits first
-// where the sample shows no near pairs, and the runs that remain put in order from LDS: 256 rows 1360 us, but 1024 rows 7000-7740 us.)
-template <int NT, int R = 4>
-__global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
+// This kernel splits the support into buckets of some kBucket tokens by splitters, keys with their token ids from a sorted sample of the row (so
+// that equal ratios can be split too); full_bucket_kernel puts each bucket in order.  The elements keep p and q beside the id: the
+// second kernel needs no gather.  Where the support is sparse or cut, its list is sampled and not the row.
+// Bound: memory, and the quotients.  1024 rows of 128256 tokens, n = 8: four sorting passes over elements of 8 bytes by one workgroup per row and a
+// gather of the pairs took 6.1 + 1.6 ms; support 0.44, count 0.72, scatter 0.78 and buckets 1.5 ms take their place.  One row 1587 -> 810 us the call,
+// 16 rows 2412 -> 1485, 64 rows cut by a nucleus of 32000 tokens 314 -> 274.
+template <int NT, bool CUT, int R = 4>
+__global__ __launch_bounds__(NT, CUT ? 1 : 8) void full_support_kernel(FullParams fp) {
     constexpr int kWaves = NT / 64;                              // this workgroup's waves
     constexpr int kThreads = NT;
-    constexpr int kMaxRun = 16, kClose = 4;                      // kClose: twice the near pairs that the sample may hold
-    __shared__ Sort32Lds<NT, R> S;
+    __shared__ union { std::conditional_t<CUT, Sort32Lds<NT, R>, char> sort; SplitLds<NT> split; } lds;
+    auto& S = lds.sort;
     __shared__ double red[kWaves];
-    __shared__ unsigned long long kred[2][kWaves];
     __shared__ int wtot[4 * kWaves];
     __shared__ double dscan[gr::kThreads];
-    __shared__ int bsel, nruns, again;
+    __shared__ int bsel;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, row = blockIdx.x;
     const int V = fp.V;
     const size_t vs = static_cast<size_t>(V) + 2;
     const float* pr = fp.p + static_cast<size_t>(row) * V;
     const float* qr = fp.q + static_cast<size_t>(row) * V;
     unsigned long long* k0 = fp.key0 + row * vs; unsigned long long* k1 = fp.key1 + row * vs;
-    int* runs = fp.val0 + row * vs;
     const bool lg = fp.logits != 0;
-    const bool cut = fp.tail_mass > 0.0;
-    // Where the support may be small, its first and last pattern are found when it is known: a division per token of the
-    // vocabulary is much of what such a row costs (one row of 128256 tokens cut to 9: 531 -> 459 us, with the pack loop
-    // leaving out the waves that hold none).  A top-k above V / 8 takes those of all tokens from the pass over the sums.
-    const bool early = !cut && fp.k > V / 8;
-
+    const bool cut = CUT && fp.tail_mass > 0.0;
+    int positive = 0;                                            // tokens that the draft may take
     double ptot, qtot;
     double p_ref = 0.0, q_ref = 0.0, inv_temp = 0.0, inv_temp_q = 0.0;
-    // the sort key of a token: ascending patterns are descending ratios.
-    // Rows given as logits: q/p is proportional to exp((d - t) / T), so the order is that of d - t (exact in
-    // float64 for float32 logits; a masked target gives +inf: first)
-    auto full_key = [&](float qv, float pv) -> unsigned long long {
-        const double ratio = lg ? logit_ratio_key(static_cast<double>(qv), static_cast<double>(pv), inv_temp_q, inv_temp)
-                                : static_cast<double>(qv) / static_cast<double>(pv);   // p = 0 gives +inf: first
-        return lg ? ~mono64(ratio) : ~static_cast<unsigned long long>(__double_as_longlong(ratio));
-    };
-    unsigned long long kmin = ~0ull, kmax = 0ull;               // of the support (early: of all tokens), where the ratio is finite
-    auto bounds = [&](float qv, float pv) {
-        if (pv > (lg ? -__builtin_inff() : 0.f)) { const unsigned long long key = full_key(qv, pv); kmin = min(kmin, key); kmax = max(kmax, key); }
-    };
     if (fp.logits) {
         // rows given as logits: the largest target and draft logit, then the target's softmax sum relative to it;
         // q needs no sum (it is renormalised over the support).  A NaN or +inf anywhere, or a temperature that is not
@@ -381,7 +419,7 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     ps += exp((static_cast<double>(pv[j]) - p_ref) * inv_temp);
-                    if (early && qv[j] > -3.0e38f) bounds(qv[j], pv[j]);
+                    positive += qv[j] > -3.0e38f;
                 }
             }
         ptot = block_sum<kWaves>(ps, red); qtot = 1.0;
@@ -399,7 +437,7 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
             for (int j = 0; j < 4; ++j) {
                 bad |= !(qv[j] >= 0.f) | !(pv[j] >= 0.f);
                 ps += static_cast<double>(pv[j]); qs += static_cast<double>(qv[j]);
-                if (early && qv[j] > 0.f) bounds(qv[j], pv[j]);
+                positive += qv[j] > 0.f;
             }
         }
         ptot = block_sum<kWaves>(ps, red);
@@ -415,7 +453,10 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
     // and flag the first k' of them; the support is then the flagged tokens.
     int* member = fp.flag + row * vs;                       // by token id here; reused by rank later
     bool by_flag = false;
-    if (fp.k < V || cut) {
+    positive = block_sum_i<kWaves>(positive, red);
+    int kk = positive;                                      // the support's size
+    const unsigned long long* sorted = nullptr;             // its tokens, where they are listed
+    if (CUT || positive < V / 4) {
         // Nucleus cut: tokens are taken by decreasing q until their running sum reaches (1 - tail_mass) qtot.
         // Candidates first, so that only they are sorted: half of the budget tail_mass qtot goes to the tokens
         // below qmin = budget / (2 V) (fewer than V of them: below budget / 2 together), the other half to the
@@ -423,7 +464,7 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
         // class's upper edge, so count x edge bounds the class's mass).  Everything dropped here lies in the
         // tail that the exact walk below would leave out anyway.
         double qmin = 0.0; int bstar = 0;
-        if (cut) {
+        if constexpr (CUT) if (cut) {
             int* chist = reinterpret_cast<int*>(&S);             // 4096 classes = 16 KB of the sort's LDS
             static_assert(sizeof(S) >= 4096 * sizeof(int), "the class histogram borrows the sort's LDS");
             for (int c = tid; c < 4096; c += kThreads) chist[c] = 0;
@@ -466,9 +507,9 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
             cnt += run;
             __syncthreads();
         }
-        const unsigned long long* sorted = k0;
+        sorted = k0;
         int keep = cnt;
-        if (cnt > fp.k || (cut && cnt > 0)) {
+        if constexpr (CUT) if (cnt > fp.k || (cut && cnt > 0)) {
             sorted = block_sort32(k0, k1, cnt, S);
             if (cut) {
                 // the exact walk: running sums of q in the sorted order, added one after the other (wave 0), until
@@ -499,162 +540,38 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
             by_flag = true;
         }
         __syncthreads();
-        if (!early) {
-            // a small support by its list (a gather costs whole lines), a large one in token order
-            const bool few = keep <= V / 8;
-            for (int r = tid; r < (few ? keep : V); r += kThreads) {
-                const int i = few ? packed_id(sorted[r]) : r;
-                if (few || (by_flag ? member[i] != 0 : (lg ? qr[i] > -3.0e38f : qr[i] > 0.f))) bounds(qr[i], pr[i]);
-            }
-            __syncthreads();
-        }
-    }
-    // A token's code: its finite ratio's pattern, relative to the row's first and without the `shift` bits that the element
-    // has no room for, behind the codes of the ratios that are not finite (a target of -0 gives -inf, which comes first,
-    // one of +0 or a masked target logit +inf).  `lo`: where the 32 leading bits of the row's codes begin; each kind of
-    // ratio that is not finite has leading bits of its own.
-    const int id_bits = V > 2 ? 32 - __clz(V - 1) : 1;
-    const unsigned id_mask = (1u << id_bits) - 1u;
-    int shift, under, lo;
-    unsigned long long base;
-    {
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            kmin = min(kmin, static_cast<unsigned long long>(__shfl_xor(kmin, o)));
-            kmax = max(kmax, static_cast<unsigned long long>(__shfl_xor(kmax, o)));
-        }
-        if (lane == 0) { kred[0][wv] = kmin; kred[1][wv] = kmax; }
-        __syncthreads();
-        for (int w = 0; w < kWaves; ++w) { kmin = min(kmin, kred[0][w]); kmax = max(kmax, kred[1][w]); }
-        auto bits = [](unsigned long long x) { return x ? 64 - __clzll(static_cast<long long>(x)) : 0; };
-        const unsigned long long range = kmax > kmin ? kmax - kmin : 0ull;
-        shift = max(0, bits(range) - (64 - id_bits) + 1);        // one bit less than there is room for: `base` may carry into it
-        under = max(0, bits(range >> shift) - 31);
-        base = 2ull << under;
-        lo = id_bits + max(0, bits((range >> shift) + base) - 32);
-    }
-    auto code = [&](unsigned long long key) -> unsigned long long { return key >= kmin ? ((key - kmin) >> shift) + base : (key >> 63) << under; };
-    // the support in token order, with its codes; p and q of a token side by side for the kernel that gathers them in the
-    // order of the ratios: one line of memory per token and not two (1024 rows of 128256 tokens, when a row's workgroup gathered for
-    // itself: 10.92 -> 9.57 ms; writing the pairs: 0.03-0.24 ms)
-    float2* pq = reinterpret_cast<float2*>(fp.rho_id + row * vs);   // the dense kernel writes the residuals there later
-    double* rho_id = fp.rho_id + row * vs; int* rank_of = fp.rank_of + row * vs;
-    int kk = 0, close = 0;                                       // close: twice the sampled pairs of tokens that are near
-    auto near = [&](unsigned long long x, unsigned long long y) { return (x >> lo) == (y >> lo) && (x >> id_bits) != (y >> id_bits); };
-    for (int t0 = 0; t0 < V; t0 += 4 * kThreads) {               // 4 NT tokens per round
-        float qv[4], pv[4]; bool in[4]; unsigned long long mask[4], e[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int i = t0 + j * kThreads + tid;
-            qv[j] = i < V ? qr[i] : (lg ? -__builtin_inff() : 0.f); pv[j] = i < V ? pr[i] : 1.f;
-            in[j] = by_flag ? (i < V && member[i] != 0) : (lg ? qv[j] > -3.0e38f : qv[j] > 0.f);
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            mask[j] = __ballot(in[j]);
-            if (lane == 0) wtot[j * kWaves + wv] = __popcll(mask[j]);
-            e[j] = 0ull;
-            if (mask[j] == 0ull) continue;                       // uniform over the wave
-            if (in[j]) e[j] = (code(full_key(qv[j], pv[j])) << id_bits) | static_cast<unsigned>(t0 + j * kThreads + tid);
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const unsigned long long x = __shfl_xor(e[j], o);
-                close += in[j] && (mask[j] >> (lane ^ o) & 1ull) && near(x, e[j]);
-            }
-#pragma unroll
-            for (int i = 0; i < j; ++i) close += in[j] && in[i] && near(e[i], e[j]) ? 2 : 0;
-        }
-        __syncthreads();
-        int offs[4];
-        const int run = group_offsets<kWaves>(wtot, offs);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            if (in[j]) {
-                const int off = kk + offs[j] + __popcll(mask[j] & ((1ull << lane) - 1ull));
-                k0[off] = e[j];
-                pq[t0 + j * kThreads + tid] = make_float2(pv[j], qv[j]);
-            } else if (t0 + j * kThreads + tid < V) {
-                // a token outside the support keeps all of p as residual
-                const double x = static_cast<double>(pv[j]);
-                rank_of[t0 + j * kThreads + tid] = -1;
-                rho_id[t0 + j * kThreads + tid] = (lg ? exp((x - p_ref) * inv_temp) : x) / ptot;
-            }
-        }
-        kk += run;
-        __syncthreads();
+        kk = keep;
     }
     if (kk == 0) {
         if (tid == 0) mark_bad(fp, row, ptot, qtot);
         return;
     }
+    const RatioKey key_of{lg, inv_temp, inv_temp_q};
+    SplitLds<NT>& L = lds.split;
+    const int log_nb = log_buckets(kk), nb = 1 << log_nb;
+    static_assert(SplitLds<NT>::kSamples >= kSamplesPerBucket << SplitLds<NT>::kLogBuckets || NT >= 1024, "samples for every bucket");
     __syncthreads();
-    int* order = fp.order + row * vs;
-    unsigned long long* elems = k0;
-    auto id_of = [&](unsigned long long e) { return static_cast<int>(static_cast<unsigned>(e) & id_mask); };
-    auto key_of = [&](unsigned long long e) { const float2 x = pq[id_of(e)]; return full_key(x.y, x.x); };
-    auto behind = [&](unsigned long long x, unsigned long long y) {   // the token of x comes after that of y (ids decide between equals)
-        if ((x >> id_bits) != (y >> id_bits) || shift == 0) return x > y;
-        const unsigned long long kx = key_of(x), ky = key_of(y);
-        return kx != ky ? kx > ky : x > y;
-    };
-    if (tid == 0) { again = 0; nruns = 0; }
-    // The sorts of a row, all stable: 0 by the codes' leading bits; 1 and 2 by the bits below them, then by the leading
-    // ones again; 3 and 4 by the low, then the high half of the whole patterns.
-    int step = block_sum_i<kWaves>(close, red) >= kClose && lo > id_bits ? 1 : 0;
-    for (;;) {
-        const int from = step == 1 ? id_bits : (step >= 3 ? 32 : lo);
-        elems = block_sort32(elems, elems == k0 ? k1 : k0, kk, S, from, step == 1 ? (lo - id_bits + 7) >> 3 : 4);
-        if (step == 1) { step = 2; continue; }
-        if (step == 0 || step == 2) {
-            const int same = step == 0 ? lo : id_bits;           // tokens equal from this bit on may still be out of order
-            for (int r = tid; r < kk; r += NT) order[r] = id_of(elems[r]);
-            if (shift == 0 && same == id_bits) break;
-            // The sorts were stable, so tokens of equal ratios already are in token order, and a run without a descent
-            // is in order.  The first descent of a run lists it (its first rank and its length).
-            for (int r = tid + 1; r < kk; r += NT) {
-                const unsigned long long e = elems[r], before = elems[r - 1];
-                if ((before >> same) != (e >> same) || !behind(before, e)) continue;
-                int first = r - 1, end = r + 1;
-                bool lists = true;
-                while (first > 0 && r - first <= kMaxRun && (elems[first - 1] >> same) == (e >> same)) {
-                    lists = lists && !behind(elems[first - 1], elems[first]);
-                    --first;
-                }
-                while (end < kk && end - first <= kMaxRun && (elems[end] >> same) == (e >> same)) ++end;
-                if (end - first > kMaxRun) { again = 1; break; }
-                if (lists) runs[atomicAdd(&nruns, 1)] = first | ((end - first - 1) << 24);     // V < 2^24; fewer runs than tokens
-            }
-            __syncthreads();
-            if (again == 0) {
-                // one thread per run: a token's place is the number of tokens that it comes after
-                for (int i = tid; i < nruns; i += NT) {
-                    const int first = runs[i] & 0xFFFFFF, end = first + (runs[i] >> 24) + 1;
-                    for (int r = first; r < end; ++r) {
-                        const unsigned long long e = elems[r];
-                        int at = first;
-                        for (int o = first; o < end; ++o) at += behind(e, elems[o]);
-                        order[at] = id_of(e);
-                    }
-                }
-                break;
-            }
-            __syncthreads();
-            if (tid == 0) { again = 0; nruns = 0; }
-            step = same > id_bits ? 1 : 3;
-        } else {
-            ++step;
+    if (nb > 1) {
+        // a token of every part of the support or the row, at a place that no pattern of the tokens follows
+        const int ns = min(SplitLds<NT>::kSamples, kSamplesPerBucket * nb), of = sorted ? kk : V;
+        int valid = 0;
+        for (int t = tid; t < ns; t += NT) {
+            const int lo = static_cast<int>(static_cast<long long>(t) * of / ns), hi = static_cast<int>(static_cast<long long>(t + 1) * of / ns);
+            unsigned x = static_cast<unsigned>(t) * 0x9E3779B9u + 0x7F4A7C15u;
+            x ^= x >> 15; x *= 0x85EBCA6Bu; x ^= x >> 13;
+            const int at = lo + static_cast<int>(__umulhi(x, static_cast<unsigned>(max(hi - lo, 1))));
+            const int id = sorted ? packed_id(sorted[at]) : at;
+            const float qv = qr[id], pv = pr[id];
+            const bool in = sorted || (lg ? qv > -3.0e38f : qv > 0.f);
+            L.key[t] = in ? key_of(qv, pv) : ~0ull; L.id[t] = in ? id : 0x7fffffff;
+            valid += in;
         }
-        if (step == 5) {
-            for (int r = tid; r < kk; r += NT) order[r] = packed_id(elems[r]);
-            break;
-        }
-        if (step >= 3) {
-            for (int r = tid; r < kk; r += NT) {
-                const int id = step == 3 ? id_of(elems[r]) : packed_id(elems[r]);
-                const unsigned long long key = full_key(pq[id].y, pq[id].x);
-                elems[r] = pack32(static_cast<unsigned>(step == 3 ? key : key >> 32), id);
-            }
-            __syncthreads();
+        valid = block_sum_i<kWaves>(valid, red);                 // barriers inside
+        block_bitonic<NT>(L.key, L.id, ns);                      // ns is a power of two
+        const SplitView split(fp, row);
+        for (int j = tid; j < nb - 1; j += NT) {
+            const int at = static_cast<int>(static_cast<long long>(j + 1) * valid >> log_nb);
+            split.key[j] = at < valid ? L.key[at] : ~0ull; split.id[j] = at < valid ? L.id[at] : 0x7fffffff;
         }
     }
     if (tid == 0) {
@@ -663,37 +580,309 @@ __global__ __launch_bounds__(NT) void full_order_kernel(FullParams fp) {
         info.alpha_star = 0.0; info.res_total = 0.0; info.p_total = ptot; info.q_total = qtot; info.node_tokens = 0.0;
         info.p_ref = p_ref; info.inv_temp = inv_temp; info.q_ref = q_ref;
         fp.info[row] = info;
+        fp.tcount[3 * row] = by_flag;                            // until the truncation kernel: how the next two know the support
     }
 }
 
-// ---- kernel 2: the pairs (p, q) of the support by rank, and every token's rank.
-// Bound: memory, as long as a row's pairs and ranks (1.5 MB at V = 128256) stay in the L2 of the workgroups that share the row, which is why
-// few of them are resident: they reserve LDS (1024 rows: 2.6 ms with ten workgroups of 256 threads to a compute unit, 2.4 with four, 1.85 with
-// two, 1.97 with one).  Gathered and scattered by the scan kernel, a row to a workgroup, they took 5 of its 8.4 ms.
-__global__ __launch_bounds__(kGatherThreads) void full_gather_kernel(FullParams fp, int chunks) {
-    constexpr int NT = kGatherThreads;
-    int row, chunk;
-    chunk_of(fp.B, chunks, row, chunk);
+// ---- kernels 2 and 3: the bucket of every token and the buckets' sizes, then the elements.  A row is shared by the workgroups of its slices of
+// `len` tokens; splitters and counters lie in LDS (`room` buckets).
+constexpr int kCountThreads = 512, kLogCells = 10;
+// Tokens from `from` on of a row, R to a thread: p, q, and whether the support has it.
+template <int NT, int R>
+struct Tokens {
+    float p[R], q[R]; bool in[R];
+    __device__ __forceinline__ void load(const FullParams& fp, int row, int from, int to, bool by_flag) {
+        const float* pr = fp.p + static_cast<size_t>(row) * fp.V;
+        const float* qr = fp.q + static_cast<size_t>(row) * fp.V;
+        const int* member = fp.flag + row * (static_cast<size_t>(fp.V) + 2);
+        int m[R];
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const int i = from + j * NT + static_cast<int>(threadIdx.x);
+            q[j] = i < to ? qr[i] : -__builtin_inff(); p[j] = i < to ? pr[i] : 0.f;
+            m[j] = by_flag && i < to ? member[i] : 0;
+        }
+#pragma unroll
+        for (int j = 0; j < R; ++j) in[j] = by_flag ? m[j] != 0 : (fp.logits ? q[j] > -3.0e38f : q[j] > 0.f);
+    }
+};
+
+// The search goes from the cell of a key, of 2^kLogCells equal ones over the splitters' range, whose splitters are counted: most cells hold one
+// or none.  Bound: arithmetic, the quotient and the search.
+__global__ __launch_bounds__(kCountThreads, 8) void full_count_kernel(FullParams fp, int slices, int len, int room) {
+    extern __shared__ __align__(16) unsigned char full_lds[];
+    constexpr int NT = kCountThreads, kCells = 1 << kLogCells;
+    unsigned long long* key = reinterpret_cast<unsigned long long*>(full_lds);
+    int* ids = reinterpret_cast<int*>(key + room); int* count = ids + room; int* below = count + room;   // below: kCells + 1 of them
+    int row, slice;
+    chunk_of(fp.B, slices, row, slice);
     if (row >= fp.B) return;
-    const size_t vs = static_cast<size_t>(fp.V) + 2;
     const RowInfo info = fp.info[row];
     if (info.status == GR_ROW_BAD) return;
-    const float2* pq = reinterpret_cast<const float2*>(fp.rho_id + row * vs);   // by token id
-    float2* by_rank = fp.pairs + row * vs;
-    const int* order = fp.order + row * vs; int* rank_of = fp.rank_of + row * vs;
-    const int end = min(info.support, (chunk + 1) * kChunkRanks);
-    for (int r0 = chunk * kChunkRanks + static_cast<int>(threadIdx.x); r0 < end; r0 += 8 * NT) {
-        int id[8]; float2 x[8];
+    const int tid = threadIdx.x;
+    const size_t vs = static_cast<size_t>(fp.V) + 2;
+    const int nb = 1 << log_buckets(info.support);
+    const bool by_flag = fp.tcount[3 * row] != 0;
+    const SplitView split(fp, row);
+    for (int b = tid; b < nb; b += NT) {
+        if (b < nb - 1) { key[b] = split.key[b]; ids[b] = split.id[b]; }
+        count[b] = 0;
+    }
+    __syncthreads();
+    unsigned long long base = 0ull;
+    int shift = 0;
+    if (nb > 1) {
+        base = key[0];
+        const unsigned long long range = key[nb - 2] - base;
+        shift = max(0, 64 - kLogCells - (range ? __clzll(static_cast<long long>(range)) : 64));
+        for (int c = tid; c <= kCells; c += NT) {
+            const unsigned long long ahead = static_cast<unsigned long long>(c) << shift, from = ahead > ~base ? ~0ull : base + ahead;
+            int b = 0;
+            for (int step = nb >> 1; step > 0; step >>= 1) if (key[b + step - 1] < from) b += step;
+            below[c] = c == 0 ? 0 : (c == kCells ? nb - 1 : b);
+        }
+        __syncthreads();
+    }
+    const RowValues val(fp, info, row);
+    const RatioKey key_of{val.lg, val.inv_temp, val.inv_temp_q};
+    double* rho_id = fp.rho_id + row * vs; int* rank_of = fp.rank_of + row * vs;
+    const int end = min(fp.V, slice * len + len);
+    for (int t0 = slice * len; t0 < end; t0 += 4 * NT) {
+        Tokens<NT, 4> x;
+        x.load(fp, row, t0, end, by_flag);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) { const int r = r0 + j * NT; id[j] = r < end ? order[r] : 0; }
-#pragma unroll
-        for (int j = 0; j < 8; ++j) if (r0 + j * NT < end) x[j] = pq[id[j]];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int r = r0 + j * NT;
-            if (r < end) { by_rank[r] = x[j]; rank_of[id[j]] = r; }
+        for (int j = 0; j < 4; ++j) {
+            const int i = t0 + j * NT + tid;
+            if (x.in[j]) {
+                int b = 0;                                       // the splitters that do not come after the token
+                if (nb > 1) {
+                    const unsigned long long k = key_of(x.q[j], x.p[j]);
+                    const int c = k <= base ? 0 : static_cast<int>(min((k - base) >> shift, static_cast<unsigned long long>(kCells - 1)));
+                    b = below[c];
+                    for (int up = below[c + 1]; b < up;) {
+                        const int mid = (b + up) >> 1;
+                        const unsigned long long o = key[mid];
+                        if (o < k || (o == k && ids[mid] <= i)) b = mid + 1; else up = mid;
+                    }
+                    split.bucket[i] = static_cast<unsigned short>(b);
+                }
+                atomicAdd(&count[b], 1);
+            } else if (i < end) {
+                // a token outside the support keeps all of p as residual
+                rank_of[i] = -1;
+                rho_id[i] = val.p(x.p[j]);
+            }
         }
     }
+    __syncthreads();
+    for (int b = tid; b < nb; b += NT) split.count[slice * nb + b] = count[b];
+}
+
+// A tile of 8 NT tokens goes through LDS into bucket order, so that the elements of a bucket leave as one run: stores of single elements were
+// spread over more lines than an L2 holds (1024 rows of 128256 tokens: 1840 us).
+template <int NT>
+__global__ __launch_bounds__(NT) void full_scatter_kernel(FullParams fp, int slices, int len, int room) {
+    extern __shared__ __align__(16) unsigned char full_lds[];
+    constexpr int R = 8, kTile = R * NT, NW = NT / 64;
+    Element* tile = reinterpret_cast<Element*>(full_lds);
+    // per bucket: tokens of the tile, its first place in the tile, the output slot of the tile's place 0, the next output slot
+    int* count = reinterpret_cast<int*>(tile + kTile); int* start = count + room; int* dest = start + room; int* next = dest + room;
+    unsigned short* where = reinterpret_cast<unsigned short*>(next + room);
+    __shared__ int held;
+    __shared__ int wsum[NW];
+    int row, slice;
+    chunk_of(fp.B, slices, row, slice);
+    if (row >= fp.B || fp.info[row].status == GR_ROW_BAD) return;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const size_t vs = static_cast<size_t>(fp.V) + 2;
+    const int kk = fp.info[row].support, nb = 1 << log_buckets(kk);
+    const bool by_flag = fp.tcount[3 * row] != 0;
+    const SplitView split(fp, row);
+    // exclusive sums over the buckets of what `of` gives for each, NT of them at a time; all threads call
+    auto prefix = [&](auto of, auto put) {
+        int run = 0;
+        for (int b0 = 0; b0 < nb; b0 += NT) {
+            const int b = b0 + tid, c = b < nb ? of(b) : 0, incl = wave_scan_i(c);
+            if (lane == 63) wsum[wv] = incl;
+            __syncthreads();
+            int at = run + incl - c;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) { const int x = wsum[w]; if (w < wv) at += x; run += x; }
+            if (b < nb) put(b, at, c);
+            if (b0 + NT < nb) __syncthreads();
+        }
+    };
+    prefix([&](int b) { int all = 0; for (int s = 0; s < slices; ++s) all += split.count[s * nb + b]; return all; },
+           [&](int b, int at, int) {
+               if (slice == 0) { split.first[b] = at; if (b == 0) split.first[nb] = kk; }
+               for (int s = 0; s < slice; ++s) at += split.count[s * nb + b];
+               next[b] = at; count[b] = 0;
+           });
+    __syncthreads();
+    Element* elems = fp.elements() + row * vs;
+    const int end = min(fp.V, slice * len + len);
+    int b[R];
+    Tokens<NT, R> x;
+    auto load = [&](int t0) {
+        x.load(fp, row, t0, end, by_flag);
+#pragma unroll
+        for (int j = 0; j < R; ++j) { const int i = t0 + j * NT + tid; b[j] = nb > 1 && i < end ? split.bucket[i] : 0; }
+    };
+    load(slice * len);
+    for (int t0 = slice * len; t0 < end; t0 += kTile) {
+        int at[R];
+#pragma unroll
+        for (int j = 0; j < R; ++j) if (x.in[j]) at[j] = atomicAdd(&count[b[j]], 1);
+        __syncthreads();
+        prefix([&](int d) { return count[d]; },
+               [&](int d, int from, int c) {
+                   start[d] = from; dest[d] = next[d] - from; next[d] += c; count[d] = 0;
+                   if (d == nb - 1) held = from + c;
+               });
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < R; ++j)
+            if (x.in[j]) {
+                const int o = start[b[j]] + at[j];
+                tile[o] = Element{x.p[j], x.q[j], t0 + j * NT + tid};
+                where[o] = static_cast<unsigned short>(b[j]);
+            }
+        load(t0 + kTile);
+        __syncthreads();
+        for (int i = tid; i < held; i += NT) elems[dest[where[i]] + i] = tile[i];
+    }
+}
+
+// ---- kernel 4: every bucket in order: token ids and pairs (p, q) by rank, and every token's rank.
+//
+// A token's place in its bucket is found through the key's place between the bucket's smallest and largest one: it goes to one of kCells cells,
+// half a token each on average, and is compared with the others of its cell.  Where the keys lie too unevenly for that (kCrowded in a
+// cell) the bucket is sorted; one above kBucketCap (the sample missed it) is ranked by comparison with all of its tokens, tile by
+// tile.  Buckets of a row share an XCD: the ranks go to 4 V bytes of it at random and stay in its L2 meanwhile.
+constexpr int kBucketThreads = 512, kCells = 2048, kCrowded = 48;
+__global__ __launch_bounds__(kBucketThreads, 8) void full_bucket_kernel(FullParams fp, int buckets) {
+    constexpr int NT = kBucketThreads, PER = kBucketCap / NT, kWaves = NT / 64;
+    __shared__ union { unsigned long long key[kBucketCap]; float2 pair[kBucketCap]; } A;
+    __shared__ int ids[kBucketCap];
+    __shared__ int cells[kCells];
+    __shared__ unsigned long long wred[2][kWaves];
+    __shared__ int wsum[kWaves], wmost[kWaves];
+    int row, b;
+    chunk_of(fp.B, buckets, row, b);
+    if (row >= fp.B) return;
+    const size_t vs = static_cast<size_t>(fp.V) + 2;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const SplitView split(fp, row);
+    const RowInfo info = fp.info[row];
+    const int at = split.first[b], count = split.first[b + 1] - at;
+    if (info.status == GR_ROW_BAD || b >> log_buckets(info.support) != 0) return;
+    const RowValues val(fp, info, row);
+    const RatioKey key_of{val.lg, val.inv_temp, val.inv_temp_q};
+    const Element* elems = fp.elements() + row * vs + at;
+    int* order = fp.order + row * vs + at; float2* pairs = fp.pairs + row * vs + at; int* rank_of = fp.rank_of + row * vs;
+    auto before = [](unsigned long long k0, int i0, unsigned long long k1, int i1) { return k0 < k1 || (k0 == k1 && i0 < i1); };
+    if (count > kBucketCap) {
+        for (int i0 = 0; i0 < count; i0 += NT) {
+            const bool mine = i0 + tid < count;
+            const Element e = elems[mine ? i0 + tid : 0];
+            const unsigned long long key = key_of(e.q, e.p);
+            int rank = 0;
+            for (int t0 = 0; t0 < count; t0 += kBucketCap) {
+                const int cnt = min(kBucketCap, count - t0);
+                __syncthreads();
+                for (int i = tid; i < cnt; i += NT) { const Element o = elems[t0 + i]; A.key[i] = key_of(o.q, o.p); ids[i] = o.id; }
+                __syncthreads();
+                for (int i = 0; i < cnt; ++i) rank += before(A.key[i], ids[i], key, e.id);
+            }
+            if (mine) { order[rank] = e.id; pairs[rank] = make_float2(e.p, e.q); rank_of[e.id] = at + rank; }
+        }
+        return;
+    }
+    Element e[PER]; unsigned long long key[PER];
+    unsigned long long kmin = ~0ull, kmax = 0ull;
+    for (int c = tid; c < kCells; c += NT) cells[c] = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) if (j * NT + tid < count) e[j] = elems[j * NT + tid];
+#pragma unroll
+    for (int j = 0; j < PER; ++j)
+        if (j * NT + tid < count) { key[j] = key_of(e[j].q, e[j].p); kmin = min(kmin, key[j]); kmax = max(kmax, key[j]); }
+    kmin = wave_min_u64(kmin); kmax = ~wave_min_u64(~kmax);
+    if (lane == 0) { wred[0][wv] = kmin; wred[1][wv] = kmax; }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) { kmin = min(kmin, wred[0][w]); kmax = max(kmax, wred[1][w]); }
+    // tokens of one ratio go by their ids
+    const bool one = kmin == kmax;
+    const unsigned long long range = one ? static_cast<unsigned long long>(fp.V) : kmax - kmin;
+    const int shift = max(0, 32 - __clzll(static_cast<long long>(range)));
+    // a ratio's pattern is even in its logarithm; the difference of two logits is the logarithm itself
+    const double x0 = val.lg ? unmono64(~kmin) : 0.0, spread = val.lg ? x0 - unmono64(~kmax) : 0.0;
+    const bool linear = val.lg && !one && spread > 1e-290 && spread < 1e300;
+    const double per = linear ? 4294967040.0 / spread : 0.0;
+    const unsigned top = linear ? 0xFFFFFFFFu : static_cast<unsigned>(range >> shift);
+    const unsigned scale = top < kCells ? 0u : static_cast<unsigned>(static_cast<double>(kCells) * 4294967296.0 / (static_cast<double>(top) + 1.0));
+    auto cell_of = [&](unsigned long long k, int id) {
+        const unsigned v = linear ? static_cast<unsigned>((x0 - unmono64(~k)) * per)
+                                  : static_cast<unsigned>((one ? static_cast<unsigned long long>(id) : k - kmin) >> shift);
+        return static_cast<int>(scale ? __umulhi(v, scale) : v);
+    };
+    int cell[PER], slot[PER];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) if (j * NT + tid < count) { cell[j] = cell_of(key[j], e[j].id); slot[j] = atomicAdd(&cells[cell[j]], 1); }
+    __syncthreads();
+    {
+        int c[kCells / NT], tot = 0, most = 0;
+#pragma unroll
+        for (int j = 0; j < kCells / NT; ++j) { c[j] = cells[kCells / NT * tid + j]; tot += c[j]; most = max(most, c[j]); }
+        const int incl = wave_scan_i(tot);
+        const bool crowded = __ballot(most > kCrowded) != 0ull;
+        if (lane == 63) { wsum[wv] = incl; wmost[wv] = crowded; }
+        __syncthreads();
+        int run = incl - tot;
+        for (int w = 0; w < wv; ++w) run += wsum[w];
+#pragma unroll
+        for (int j = 0; j < kCells / NT; ++j) { cells[kCells / NT * tid + j] = run; run += c[j]; }
+    }
+    bool crowded = false;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) crowded |= wmost[w] != 0;
+    __syncthreads();
+    int rank[PER];
+    if (!crowded) {
+#pragma unroll
+        for (int j = 0; j < PER; ++j) if (j * NT + tid < count) { const int o = cells[cell[j]] + slot[j]; A.key[o] = key[j]; ids[o] = e[j].id; }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < PER; ++j)
+            if (j * NT + tid < count) {
+                const int from = cells[cell[j]], to = cell[j] + 1 < kCells ? cells[cell[j] + 1] : count;
+                rank[j] = from;
+                for (int o = from; o < to; ++o) rank[j] += before(A.key[o], ids[o], key[j], e[j].id);
+            }
+        __syncthreads();
+    } else {
+        int size = 64;
+        while (size < count) size *= 2;
+        for (int i = tid; i < size; i += NT) { A.key[i] = ~0ull; ids[i] = 0x7fffffff; }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < PER; ++j) if (j * NT + tid < count) { A.key[j * NT + tid] = key[j]; ids[j * NT + tid] = e[j].id; }
+        __syncthreads();
+        block_bitonic<NT>(A.key, ids, size);
+#pragma unroll
+        for (int j = 0; j < PER; ++j)
+            if (j * NT + tid < count) {
+                int lo = 0;
+                for (int step = size >> 1; step > 0; step >>= 1) if (before(A.key[lo + step - 1], ids[lo + step - 1], key[j], e[j].id)) lo += step;
+                rank[j] = lo;
+            }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int j = 0; j < PER; ++j)
+        if (j * NT + tid < count) { A.pair[rank[j]] = make_float2(e[j].p, e[j].q); ids[rank[j]] = e[j].id; rank_of[e[j].id] = at + rank[j]; }
+    __syncthreads();
+    for (int i = tid; i < count; i += NT) { pairs[i] = A.pair[i]; order[i] = ids[i]; }
 }
 
 // ---- kernel 3: prefix sums in the order, F, H*, alpha*, suffix minima, residuals, records, blocks.
@@ -1205,22 +1394,34 @@ __global__ __launch_bounds__(kThreads) void full_dense_kernel(FullParams fp, int
 // its last tile.  The call, four / eight: 1024 rows of 128256 tokens 12993 / 12654 us, of 50021 4768 / 4759, of 24000 2416 / 2419, of 9000
 // 1317 / 1381; acceptance grid to V, 256 rows of 128256, 4031 / 3868.
 constexpr int kLongRow = 65536;
+constexpr int scatter_lds(int threads, int buckets) { return 8 * threads * static_cast<int>(sizeof(Element) + sizeof(unsigned short)) + buckets * 16; }
+// The LDS of the kernel that moves the elements lies above the default limit.
+hipError_t full_kernel_setup() {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(full_scatter_kernel<1024>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               scatter_lds(1024, 1 << kLogBuckets));
+}
 static void launch_full_order(const FullParams& fp, hipStream_t stream) {
     const bool crowded = fp.tail_mass > 0.0 && fp.B > 256 && fp.V <= 16384;
-    if (fp.V > kLongRow) hipLaunchKernelGGL((full_order_kernel<1024, 8>), dim3(fp.B), dim3(1024), 0, stream, fp);
-    else if (fp.V > 8192 && !crowded) hipLaunchKernelGGL(full_order_kernel<1024>, dim3(fp.B), dim3(1024), 0, stream, fp);
-    else hipLaunchKernelGGL(full_order_kernel<kThreads>, dim3(fp.B), dim3(kThreads), 0, stream, fp);
-}
-
-// The reserved LDS of the chunk kernels lies above the default limit.
-hipError_t full_kernel_setup() {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(full_gather_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kGatherLds);
+    const bool small = fp.V <= 8192 || crowded;
+    if (fp.k < fp.V || fp.tail_mass > 0.0) {
+        if (fp.V > kLongRow) hipLaunchKernelGGL((full_support_kernel<1024, true, 8>), dim3(fp.B), dim3(1024), 0, stream, fp);
+        else if (!small) hipLaunchKernelGGL((full_support_kernel<1024, true>), dim3(fp.B), dim3(1024), 0, stream, fp);
+        else hipLaunchKernelGGL((full_support_kernel<kThreads, true>), dim3(fp.B), dim3(kThreads), 0, stream, fp);
+    } else if (!small) hipLaunchKernelGGL((full_support_kernel<1024, false>), dim3(fp.B), dim3(1024), 0, stream, fp);
+    else hipLaunchKernelGGL((full_support_kernel<kThreads, false>), dim3(fp.B), dim3(kThreads), 0, stream, fp);
+    const int buckets = 1 << log_buckets(fp.V);
+    auto slices = [&](int groups, int least) { return std::max(1, std::min(std::min(kMaxSlices, groups / fp.B), fp.V / least)); };
+    const int count = small ? slices(2048, 1024) : slices(1024, 4096);
+    const int len = (fp.V + count - 1) / count;
+    hipLaunchKernelGGL(full_count_kernel, dim3(chunk_grid(fp.B, count)), dim3(kCountThreads), buckets * 16 + ((1 << kLogCells) + 1) * 4, stream, fp, count, len, buckets);
+    if (small) hipLaunchKernelGGL(full_scatter_kernel<kThreads>, dim3(chunk_grid(fp.B, count)), dim3(kThreads), scatter_lds(kThreads, buckets), stream, fp, count, len, buckets);
+    else hipLaunchKernelGGL(full_scatter_kernel<1024>, dim3(chunk_grid(fp.B, count)), dim3(1024), scatter_lds(1024, buckets), stream, fp, count, len, buckets);
+    hipLaunchKernelGGL(full_bucket_kernel, dim3(chunk_grid(fp.B, buckets)), dim3(kBucketThreads), 0, stream, fp, buckets);
 }
 
 void launch_full_prologue(const FullParams& fp, hipStream_t stream) {
     launch_full_order(fp, stream);
     const int chunks = (fp.V + kChunkRanks - 1) / kChunkRanks;
-    hipLaunchKernelGGL(full_gather_kernel, dim3(chunk_grid(fp.B, chunks)), dim3(kGatherThreads), kGatherLds, stream, fp, chunks);
     hipLaunchKernelGGL(full_scan_kernel, dim3(fp.B), dim3(kScanThreads), 0, stream, fp);
     if (fp.V > 8192) hipLaunchKernelGGL(full_trunc_kernel<1024>, dim3(fp.B), dim3(1024), 0, stream, fp);
     else hipLaunchKernelGGL(full_trunc_kernel<kThreads>, dim3(fp.B), dim3(kThreads), 0, stream, fp);

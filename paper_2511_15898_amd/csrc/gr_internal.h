@@ -66,6 +66,9 @@ struct SolveParams {
     const long long* row_at; const int* row_n;
 };
 
+// A token of the support on its way into the ratio order.
+struct Element { float p, q; int id; };
+
 // Workspace and arguments of the full-vocabulary path (no top-k).  Per-token arrays are row-major with
 // stride V + 2; P and Q hold kk + 1 entries per row (prefix index 0..kk), blo the record positions.
 struct FullParams {
@@ -83,12 +86,15 @@ struct FullParams {
     double* P; double* Q; double* rho; double* weight;   // prefix sums (Q of the raw q: divide by Q[kk]), residuals and weights by rank
     int* flag; int* blk; int* blo; int* bcount;
     int* rank_of;      // [B, V + 2] rank of each token id, -1 outside the support
-    double* rho_id;    // [B, V + 2] residual p(i) - p_i by token id (0 inside H*); before the dense kernel: the pair (p, q) of every token of the support
+    double* rho_id;    // [B, V + 2] residual p(i) - p_i by token id (0 inside H*)
     int* nblk;         // [B] number of outer blocks
     int* tcount;       // [B, 3] sizes of the two truncation sets, place of the second in byq
     RowInfo* info; float* accept_prob; int* status;
     double* newton_ws; // [B, kMaxT * (kMaxT + 1)] Jacobian scratch of the Newton fallback
+    // [B, V + 2] the support in the order's buckets, where P and Q (one after the other in the workspace) come later
+    __device__ __forceinline__ Element* elements() const { return reinterpret_cast<Element*>(P); }
 };
+static_assert(sizeof(Element) <= 2 * sizeof(double), "the elements lie where P and Q do");
 constexpr size_t kFullBytesPerToken = 2 * 8 + 4 + 2 * 4 + 5 * 8 + 4 * 4 + 4 + 8;
 
 void launch_full_prologue(const FullParams& fp, hipStream_t stream);
@@ -435,6 +441,9 @@ __device__ __forceinline__ unsigned long long make_key_logit(float d, int id) {
 __device__ __forceinline__ unsigned long long mono64(double x) {
     const unsigned long long b = static_cast<unsigned long long>(__double_as_longlong(x));
     return (b >> 63) ? ~b : (b | 0x8000000000000000ull);
+}
+__device__ __forceinline__ double unmono64(unsigned long long m) {
+    return __longlong_as_double(static_cast<long long>((m >> 63) ? m & 0x7FFFFFFFFFFFFFFFull : ~m));
 }
 __device__ __forceinline__ unsigned mono32(float x) {
     const unsigned b = __float_as_uint(x);

@@ -398,3 +398,35 @@ def test_nucleus_rows_across_the_workgroup_sizes():
     p, q = wl.p[at], wl.q[at]
     fewer = [(x[:, :8192].astype(np.float64) / x[:, :8192].sum(1, keepdims=True, dtype=np.float64)).astype(np.float32) for x in (p, q)]
     assert _solve_us(p, q, 1e-3) < 1.15 * _solve_us(*fewer, 1e-3)
+
+
+def _sampled_tokens(V, samples):
+    """The tokens that the order's splitters of a whole row are drawn from (the kernel's hash of the sample's number)."""
+    t = np.arange(samples, dtype=np.uint64)
+    x = (t * 0x9E3779B9 + 0x7F4A7C15) & 0xFFFFFFFF
+    x = ((x ^ (x >> 15)) * 0x85EBCA6B) & 0xFFFFFFFF
+    x ^= x >> 13
+    lo, hi = t * V // samples, (t + 1) * V // samples
+    return (lo + (x * np.maximum(hi - lo, 1) >> 32)).astype(np.int64)
+
+
+@pytest.mark.parametrize("V,buckets", [(2049, 4), (8192, 8), (20001, 32)])
+def test_ratio_order_of_rows_that_their_sample_does_not_show(V, buckets):
+    """Buckets of any size and any clustering of keys.  Row 0: the sampled tokens are spread over twenty octaves and all others lie within
+    2^-12 of one ratio: one bucket holds nearly the row.  Row 1: the same with equal ratios.  Row 2: three clusters.  Row 3: one token in
+    fifty may be drawn (the support is listed and not sampled from the row).  Row 4: none of the sampled tokens may be."""
+    rng = np.random.default_rng(V)
+    p = rng.dirichlet(np.full(V, 2.0), size=5) + 1e-7
+    picked = np.unique(_sampled_tokens(V, 32 * buckets))
+    ratio = np.empty((5, V))
+    ratio[0] = 1.0 + rng.uniform(0, 2.0 ** -12, V); ratio[1] = 1.0
+    ratio[:2, picked] = 2.0 ** rng.uniform(-10, 10, len(picked))
+    ratio[2] = rng.choice([1e-3, 1.0, 30.0], V) * (1.0 + 1e-5 * rng.standard_normal(V))
+    ratio[3] = np.where(rng.random(V) < 0.02, rng.lognormal(size=V), 0.0)
+    ratio[4] = rng.lognormal(size=V); ratio[4, picked] = 0.0
+    q = p * ratio
+    p = (p / p.sum(1, keepdims=True)).astype(np.float32); q = (q / q.sum(1, keepdims=True)).astype(np.float32)
+    got = _orders(p, q)
+    for b in range(5):
+        ids = np.flatnonzero(q[b] > 0)
+        assert np.array_equal(got[b], ids[np.argsort(-(q[b, ids].astype(np.float64) / p[b, ids].astype(np.float64)), kind="stable")]), b
