@@ -206,9 +206,10 @@ int gr_solve_logits_verify(gr_handle h, const float* target_logits, const float*
  * Multi-step verification over a tree of draft paths (App. "Multi-Step Experiments": K i.i.d. paths of length L
  * are drafted autoregressively from the draft model; the verifier advances from the root with n = the number of
  * drafted continuations of the current node until it lands off the tree; a row whose solve fails is sampled from p).
- * Every level is one batch: the current node of each of the S sequences, read where its row lies, solved with gr_solve at the node's
+ * A batch takes the current node of each of the S sequences and, while they are few, the nodes that the walk may reach at the next levels
+ * (a row that the walk does not reach decides nothing, whatever it holds); every node is read where its row lies, solved with gr_solve at its
  * own n and sampled with gr_verify; the paths that drew the emitted token go on to the next level.  With a support above
- * GR_MAX_SUPPORT the sequences of a level are grouped by n, and every group is gathered and is a batch of its own.
+ * GR_MAX_SUPPORT a level is a batch, its sequences are grouped by n, and every group is gathered and is a batch of its own.
  *
  * p, q       DEVICE [S, K, L, V] float32: the target / draft distribution after the first l tokens of path a of
  *            sequence s (paths with equal prefixes must carry equal rows; level 0 is the same row for all paths).
@@ -220,8 +221,9 @@ int gr_solve_logits_verify(gr_handle h, const float* target_logits, const float*
  * out_tokens HOST [S, L] int32: the tokens emitted, -1 beyond the last.  out_len [S]: how many (the walk emits one
  *            token per level visited; no bonus token after a fully accepted tree).  out_accepted [S]: how many of
  *            them were drafts.  out_fallbacks [S] or NULL: levels whose row had a status other than GR_ROW_OK.
- * The first call allocates staging (97 bytes per row on the device and in pinned host memory; the first call with a support above
- * GR_MAX_SUPPORT also 8 max_V bytes per row on the device; GR_ENOMEM); every call synchronises the stream once per batch, and one that
+ * The first call allocates staging (97 bytes per row, for 512 rows at least, on the device and in pinned host memory; the first call with a support above
+ * GR_MAX_SUPPORT also 8 max_V bytes per row on the device; GR_ENOMEM), and the first batch of more than max_B nodes the scratch of 512 rows (77 MB and
+ * 24 KB per 1000 tokens of max_V; without it the batches hold max_B nodes at most); every call synchronises the stream once per batch, and one that
  * has enqueued a batch leaves the handle without a policy (GR_ESTATE for a gr_verify that follows), also where it fails.
  */
 int gr_tree_walk(gr_handle h, const float* p, const float* q, const float* temperature, const int* paths,

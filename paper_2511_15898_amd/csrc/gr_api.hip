@@ -1,6 +1,8 @@
 // C ABI of the Global Resolution verifier: handle, argument checks, kernel launches.
 #include <algorithm>
 #include <new>
+#include <type_traits>
+#include <utility>
 #include <vector>
 
 #include "gr_internal.h"
@@ -9,7 +11,22 @@ using namespace gr;
 
 namespace { constexpr int kProfSlots = 512; }
 
-struct gr_handle_s {
+namespace {
+// What the select and solve kernels keep of every row.
+struct RowScratch {
+    // scratch of the select kernel
+    unsigned long long* cand = nullptr; int* cand_count = nullptr;
+    double* part_psum = nullptr; double* part_qsum = nullptr; int* part_bad = nullptr;
+    double* newton_ws = nullptr;   // [rows, kMaxT * (kMaxT + 1)] Jacobian scratch of the solver's Newton fallback
+    double* piece_psum = nullptr;  // float64 sums of p per 256 tokens, [rows, piece_stride]
+    float* piece_pref = nullptr; float* part_pref = nullptr;   // rows given as logits: the references of the piece sums and of the slices' sums
+    // policy object of the last solve
+    int* order = nullptr; int* block = nullptr; double* weight = nullptr; double* rho = nullptr; double* pnorm = nullptr;
+    RowInfo* info = nullptr;
+};
+}  // namespace
+
+struct gr_handle_s : RowScratch {
     int max_B = 0, max_V = 0;
     int k_cap = 0;                 // largest support (top-k, or max_V for whole rows) the handle was created for
     int max_n = GR_MAX_N;
@@ -17,15 +34,7 @@ struct gr_handle_s {
     double rel_tol = 1e-8;
     double tail_mass = 0.0;        // nucleus cut of the draft on the HBM-resident path
     int device = 0;
-    // scratch of the select kernel
-    unsigned long long* cand = nullptr; int* cand_count = nullptr;
-    double* part_psum = nullptr; double* part_qsum = nullptr; int* part_bad = nullptr;
-    double* newton_ws = nullptr;   // [max_B, kMaxT * (kMaxT + 1)] Jacobian scratch of the solver's Newton fallback
-    double* piece_psum = nullptr; int piece_stride = 0;   // float64 sums of p per 256 tokens, [max_B, piece_stride]
-    float* piece_pref = nullptr; float* part_pref = nullptr;   // rows given as logits: the references of the piece sums and of the slices' sums
-    // policy object of the last solve
-    int* order = nullptr; int* block = nullptr; double* weight = nullptr; double* rho = nullptr; double* pnorm = nullptr;
-    RowInfo* info = nullptr;
+    int piece_stride = 0;
     // optional per-kernel timing (gr_config.flags bit 0): events around every launch, read back
     // by gr_profile_read
     bool profile = false;
@@ -41,6 +50,8 @@ struct gr_handle_s {
     // HBM-resident path
     unsigned char* tw_in = nullptr; unsigned char* tw_out = nullptr; unsigned char* tw_host = nullptr;
     float* tw_p = nullptr; float* tw_q = nullptr;
+    // scratch of a walk's batches of more than max_B rows, in one allocation (made by the first of them)
+    RowScratch wide; void* wide_mem = nullptr; bool wide_asked = false;
     // last solve
     bool solved = false;
     const float* p = nullptr;
@@ -71,12 +82,45 @@ void free_all(gr_handle h) {
     void* ptrs[] = {h->cand, h->cand_count, h->part_psum, h->part_qsum, h->part_bad, h->piece_psum, h->piece_pref, h->part_pref, h->tw_p, h->tw_q, h->tw_in, h->tw_out, h->newton_ws, h->order, h->block,
                     h->weight, h->rho, h->pnorm, h->info};
     for (void* ptr : ptrs) (void)hipFree(ptr);
-    (void)hipFree(h->full_ws);
+    (void)hipFree(h->full_ws); (void)hipFree(h->wide_mem);
     if (h->tw_host) (void)hipHostFree(h->tw_host);
     if (h->profile)
         for (auto& slot : h->ev)
             for (auto& e : slot)
                 if (e) (void)hipEventDestroy(e);
+}
+
+// Rows of one batch of a walk, at most, and of one of its levels where it is taken in the same batch as the level before (see gr_tree_walk).
+// kWalkRows bounds the scratch (150 KB a row); beyond kWalkLevelRows a level fills the chip by itself: 512 sequences of 3 paths, 3 levels take as long
+// either way (590 and 611 us), and 256 sequences of 8 paths, 8 levels of 3000 tokens too (1417 and 1516).
+constexpr int kWalkRows = 512, kWalkLevelRows = 256;
+
+// The scratch of kWalkRows rows; false: there is no memory for it.
+bool wide_scratch(gr_handle h) {
+    if (h->wide_asked) return h->wide_mem != nullptr;
+    h->wide_asked = true;
+    RowScratch& w = h->wide;
+    unsigned char* base = nullptr;
+    size_t used = 0;
+    const size_t rows = kWalkRows, pieces = rows * static_cast<size_t>(h->piece_stride);
+    auto carve = [&](auto** ptr, size_t count) {
+        using T = std::remove_reference_t<decltype(**ptr)>;
+        *ptr = reinterpret_cast<T*>(base + used);
+        used += (count * sizeof(T) + 255) / 256 * 256;
+    };
+    auto all = [&]() {
+        used = 0;
+        carve(&w.cand, rows * kSelCap); carve(&w.cand_count, rows * kMaxSplits); carve(&w.part_psum, rows * kMaxSplits);
+        carve(&w.part_qsum, rows * kMaxSplits); carve(&w.part_bad, rows * kMaxSplits); carve(&w.part_pref, rows * kMaxSplits);
+        carve(&w.piece_psum, pieces); carve(&w.piece_pref, pieces); carve(&w.newton_ws, rows * kMaxT * (kMaxT + 1));
+        carve(&w.order, rows * kMaxSupport); carve(&w.block, rows * kMaxSupport); carve(&w.weight, rows * kMaxSupport);
+        carve(&w.rho, rows * kMaxSupport); carve(&w.pnorm, rows * kMaxSupport); carve(&w.info, rows);
+    };
+    all();
+    if (hipMalloc(&h->wide_mem, used) != hipSuccess) { (void)hipGetLastError(); h->wide_mem = nullptr; return false; }
+    base = static_cast<unsigned char*>(h->wide_mem);
+    all();
+    return true;
 }
 
 // How the select kernel shares a row of V tokens among workgroups: about 8 of them for every CU, each with a slice of
@@ -473,10 +517,10 @@ extern "C" int gr_tree_walk(gr_handle h, const float* p, const float* q, const f
     if (temperature && h->tail_mass > 0.0) return GR_EUNSUPPORTED;               // the nucleus cut is defined on probabilities
     // Per row in: where it begins, its draft count, its drafts, uniform, temperature; out: token, status, acceptance, flag.
     constexpr size_t kIn = sizeof(long long) + sizeof(int) * (1 + GR_MAX_N) + 2 * sizeof(float), kOut = 2 * sizeof(int) + sizeof(float) + 1;
-    const size_t rows = static_cast<size_t>(h->max_B), cols = static_cast<size_t>(h->max_V);
+    const size_t rows = static_cast<size_t>(std::max(h->max_B, kWalkRows)), cols = static_cast<size_t>(h->max_V);
     const bool staged = (h->tw_in || dev_alloc(&h->tw_in, rows * kIn)) && (h->tw_out || dev_alloc(&h->tw_out, rows * kOut)) &&
                         (h->tw_host || hipHostMalloc(reinterpret_cast<void**>(&h->tw_host), rows * (kIn + kOut), hipHostMallocDefault) == hipSuccess) &&
-                        (in_lds || ((h->tw_p || dev_alloc(&h->tw_p, rows * cols)) && (h->tw_q || dev_alloc(&h->tw_q, rows * cols))));
+                        (in_lds || ((h->tw_p || dev_alloc(&h->tw_p, static_cast<size_t>(h->max_B) * cols)) && (h->tw_q || dev_alloc(&h->tw_q, static_cast<size_t>(h->max_B) * cols))));
     if (!staged) { (void)hipGetLastError(); return GR_ENOMEM; }          // what was allocated stays for the next call
     // A batch leaves no policy of the caller's rows in the handle, and the copies use the staging that the next call writes: no return
     // leaves either behind.
@@ -487,36 +531,71 @@ extern "C" int gr_tree_walk(gr_handle h, const float* p, const float* q, const f
     std::vector<char> alive(S, 1);
     for (int s = 0; s < S; ++s) { out_len[s] = 0; out_accepted[s] = 0; if (out_fallbacks) out_fallbacks[s] = 0; }
     for (int i = 0; i < S * L; ++i) out_tokens[i] = -1;
-    std::vector<int> seqs;
-    for (int l = 0; l < L; ++l) {
+    // A batch: nodes of the tree (a sequence, the paths through the node, its level), each with a row of its own.  The children of node i are
+    // nodes child[i] .. child[i + 1] - 1, its row in the batch row_of[i].
+    struct Node { int s, l; unsigned paths; };
+    std::vector<Node> nodes;
+    std::vector<int> child, by_n, row_of;
+    const auto token_of = [&](const Node& x, int a) { return paths[(static_cast<size_t>(x.s) * K + a) * L + x.l]; };
+    for (int l = 0; l < L;) {
         // Every sequence still alive, whatever its draft count, in one batch: a level then takes as long as its slowest row, and
         // not as the slowest row of every count in turn (32 sequences of 4 paths, 5 levels, V = 32000: 17 batches took 3060 us).
+        // The nodes that a walk may reach at the next levels are known too, and their draft counts; while a level has no more of them than the chip has
+        // compute units, solving all beside the others costs less than the chain of another batch (the same walks: 560 us by levels, 165 in one
+        // batch; one sequence of 8 paths, 8 levels 685 and 113; 16 of 8 paths, 4 levels, V = 50000, k = 200: 508 and 231).
         // The HBM-resident kernels take one count per batch and rows one after the other.
+        int next_l = l + 1;
         for (int group = in_lds ? K : 1; group <= K; ++group) {
-            seqs.clear();
-            int most = 0;
-            for (int s = 0; s < S; ++s) {
-                const int n = __builtin_popcount(active[s]);
-                if (!alive[s] || (!in_lds && n != group)) continue;
-                seqs.push_back(s);
-                most = std::max(most, n);
+            nodes.clear(); child.clear();
+            for (int s = 0; s < S; ++s)
+                if (alive[s] && (in_lds || __builtin_popcount(active[s]) == group)) nodes.push_back(Node{s, l, active[s]});
+            if (nodes.empty()) continue;
+            const size_t roots = nodes.size();
+            if (in_lds) {
+                size_t from = 0;                                     // the first node of the last level taken
+                for (; next_l < L; ++next_l) {
+                    const size_t to = nodes.size(), least = to - from;   // a node has a child at least
+                    child.resize(from);
+                    if (least > static_cast<size_t>(kWalkLevelRows) || to + least > static_cast<size_t>(kWalkRows)) break;
+                    for (size_t i = from; i < to; ++i) {
+                        child.push_back(static_cast<int>(nodes.size()));
+                        const Node x = nodes[i];
+                        for (unsigned left = x.paths; left;) {
+                            unsigned same = 0u;
+                            const int t = token_of(x, __builtin_ctz(left));
+                            for (int a = 0; a < K; ++a) if ((left >> a & 1u) && token_of(x, a) == t) same |= 1u << a;
+                            nodes.push_back(Node{x.s, next_l, same});
+                            left &= ~same;
+                        }
+                    }
+                    const size_t more = nodes.size() - to;
+                    if (more > static_cast<size_t>(kWalkLevelRows) || nodes.size() > static_cast<size_t>(kWalkRows) ||
+                        (nodes.size() > static_cast<size_t>(h->max_B) && !wide_scratch(h))) { nodes.resize(to); child.resize(from); break; }
+                    from = to;
+                }
             }
-            const int cnt = static_cast<int>(seqs.size());
-            if (cnt == 0) continue;
+            const int cnt = static_cast<int>(nodes.size()), inner = static_cast<int>(child.size());   // nodes with children in the batch come first
+            child.push_back(cnt);
+            // long solves first: rows beyond the number of compute units wait for one to end
+            by_n.resize(cnt); row_of.resize(cnt);
+            int at[GR_MAX_N + 2] = {}, most = 0;                     // at[K - n]: the row of the next node of n paths
+            for (const Node& x : nodes) { const int n = __builtin_popcount(x.paths); most = std::max(most, n); ++at[K - n + 1]; }
+            for (int n = 1; n <= K; ++n) at[n] += at[n - 1];
+            for (int i = 0; i < cnt; ++i) { const int j = at[K - __builtin_popcount(nodes[i].paths)]++; row_of[i] = j; by_n[j] = i; }
             const size_t at_n = sizeof(long long) * cnt, at_d = at_n + sizeof(int) * cnt, at_u = at_d + sizeof(int) * cnt * most,
                          at_t = at_u + sizeof(float) * cnt, in_bytes = at_t + sizeof(float) * cnt;
             long long* const idx = reinterpret_cast<long long*>(h->tw_host);
             int* const ns = reinterpret_cast<int*>(h->tw_host + at_n); int* const drafts = reinterpret_cast<int*>(h->tw_host + at_d);
             float* const us = reinterpret_cast<float*>(h->tw_host + at_u); float* const ts = reinterpret_cast<float*>(h->tw_host + at_t);
             for (int j = 0; j < cnt; ++j) {
-                const int s = seqs[j];
-                idx[j] = ((static_cast<long long>(s) * K + __builtin_ctz(active[s])) * L + l) * V;
-                ns[j] = __builtin_popcount(active[s]);
+                const Node x = nodes[by_n[j]];
+                idx[j] = ((static_cast<long long>(x.s) * K + __builtin_ctz(x.paths)) * L + x.l) * V;
+                ns[j] = __builtin_popcount(x.paths);
                 int* d = drafts + static_cast<size_t>(j) * most;
-                for (int a = 0; a < K; ++a) if (active[s] >> a & 1u) *d++ = paths[(static_cast<size_t>(s) * K + a) * L + l];
+                for (int a = 0; a < K; ++a) if (x.paths >> a & 1u) *d++ = token_of(x, a);
                 for (; d < drafts + static_cast<size_t>(j + 1) * most; ++d) *d = 0;
-                us[j] = uniforms[static_cast<size_t>(s) * L + l];
-                ts[j] = temperature ? temperature[s] : 1.f;
+                us[j] = uniforms[static_cast<size_t>(x.s) * L + x.l];
+                ts[j] = temperature ? temperature[x.s] : 1.f;
             }
             if (hipMemcpyAsync(h->tw_in, h->tw_host, in_bytes, hipMemcpyHostToDevice, stream) != hipSuccess) return fail(GR_EHIP);
             const long long* const d_at = reinterpret_cast<const long long*>(h->tw_in);
@@ -527,7 +606,10 @@ extern "C" int gr_tree_walk(gr_handle h, const float* p, const float* q, const f
             float* const o_acc = reinterpret_cast<float*>(o_st + cnt); unsigned char* const o_ok = reinterpret_cast<unsigned char*>(o_acc + cnt);
             int rc;
             if (in_lds) {
+                const bool wide = cnt > h->max_B;
+                if (wide) std::swap(static_cast<RowScratch&>(*h), h->wide);
                 rc = solve_in_lds(h, p, q, d_temp, nullptr, most, k_eff, tol, cnt, V, o_acc, o_st, stream, d_drafts, d_u, o_tok, o_ok, d_at, d_n);
+                if (wide) std::swap(static_cast<RowScratch&>(*h), h->wide);
                 if (rc == GR_OK) mark_no_verify(h, stream);
             } else {
                 hipLaunchKernelGGL(gather_rows_kernel, dim3(cnt), dim3(kThreads), 0, stream, p, q, d_at, h->tw_p, h->tw_q, V);
@@ -540,20 +622,27 @@ extern "C" int gr_tree_walk(gr_handle h, const float* p, const float* q, const f
                 hipStreamSynchronize(stream) != hipSuccess) return fail(GR_EHIP);
             const int* const tok = reinterpret_cast<const int*>(back); const int* const st = tok + cnt;
             const unsigned char* const okv = back + 3 * sizeof(int) * cnt;
-            for (int j = 0; j < cnt; ++j) {
-                const int s = seqs[j];
-                out_tokens[static_cast<size_t>(s) * L + l] = tok[j];
-                out_len[s] = l + 1;
-                if (out_fallbacks && st[j] != GR_ROW_OK) ++out_fallbacks[s];
-                if (!okv[j] || tok[j] < 0) { alive[s] = 0; continue; }
-                ++out_accepted[s];
-                unsigned keep = 0u;
-                for (int a = 0; a < K; ++a)
-                    if ((active[s] >> a & 1u) && paths[(static_cast<size_t>(s) * K + a) * L + l] == tok[j]) keep |= 1u << a;
-                active[s] = keep;
-                if (!keep) alive[s] = 0;                         // cannot happen: an accepted token is one of the drafts
+            for (size_t root = 0; root < roots; ++root) {
+                const int s = nodes[root].s;
+                for (int i = static_cast<int>(root); i >= 0;) {      // down the tree
+                    const Node x = nodes[i];
+                    const int j = row_of[i];
+                    i = -1;
+                    out_tokens[static_cast<size_t>(s) * L + x.l] = tok[j];
+                    out_len[s] = x.l + 1;
+                    if (out_fallbacks && st[j] != GR_ROW_OK) ++out_fallbacks[s];
+                    if (!okv[j] || tok[j] < 0) { alive[s] = 0; break; }
+                    ++out_accepted[s];
+                    unsigned keep = 0u;
+                    for (int a = 0; a < K; ++a) if ((x.paths >> a & 1u) && token_of(x, a) == tok[j]) keep |= 1u << a;
+                    active[s] = keep;
+                    if (!keep) { alive[s] = 0; break; }              // cannot happen: an accepted token is one of the drafts
+                    const int self = by_n[j];
+                    if (self < inner) for (int c = child[self]; c < child[self + 1]; ++c) if (nodes[c].paths == keep) i = c;
+                }
             }
         }
+        l = next_l;
     }
     h->solved = false;                                           // the policy left in the handle belongs to a gathered batch
     return GR_OK;
