@@ -574,13 +574,19 @@ __global__ __launch_bounds__(NT, CUT ? 1 : 8) void full_support_kernel(FullParam
             split.key[j] = at < valid ? L.key[at] : ~0ull; split.id[j] = at < valid ? L.id[at] : 0x7fffffff;
         }
     }
+    if (nb == 1 && sorted) {                                     // one bucket of listed tokens: here it is
+        Element* elems = fp.elements() + row * vs;
+        for (int r = tid; r < kk; r += NT) { const int id = packed_id(sorted[r]); elems[r] = Element{pr[id], qr[id], id}; }
+        if (tid == 0) { const SplitView split(fp, row); split.first[0] = 0; split.first[1] = kk; }
+    }
     if (tid == 0) {
         RowInfo info;
         info.support = kk; info.h = 0; info.status = GR_ROW_OK; info.iterations = 0;
         info.alpha_star = 0.0; info.res_total = 0.0; info.p_total = ptot; info.q_total = qtot; info.node_tokens = 0.0;
         info.p_ref = p_ref; info.inv_temp = inv_temp; info.q_ref = q_ref;
         fp.info[row] = info;
-        fp.tcount[3 * row] = by_flag;                            // until the truncation kernel: how the next two know the support
+        // until the truncation kernel, for the next two: how to know the support, whether its elements are written
+        fp.tcount[3 * row] = by_flag; fp.tcount[3 * row + 1] = nb == 1 && sorted;
     }
 }
 
@@ -692,7 +698,7 @@ __global__ __launch_bounds__(NT) void full_scatter_kernel(FullParams fp, int sli
     __shared__ int wsum[NW];
     int row, slice;
     chunk_of(fp.B, slices, row, slice);
-    if (row >= fp.B || fp.info[row].status == GR_ROW_BAD) return;
+    if (row >= fp.B || fp.info[row].status == GR_ROW_BAD || fp.tcount[3 * row + 1] != 0) return;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const size_t vs = static_cast<size_t>(fp.V) + 2;
     const int kk = fp.info[row].support, nb = 1 << log_buckets(kk);
