@@ -422,11 +422,11 @@ extern "C" int gr_accept_sweep(gr_handle h, const float* p, const float* q, cons
             for (int i = 0; i < nn; ++i) if (ns[i] < 1 || ns[i] > kSweepMaxDrafts) return GR_EINVAL;
             auto effective = [ks, V](int i) { return (ks[i] <= 0 || ks[i] >= V) ? V : ks[i]; };
             for (int i = 0; i < kSweepMaxK; ++i) gp.kpos[i] = i;
-            for (int i = 0; i < kSweepMaxN; ++i) gp.npos[i] = i;
             std::stable_sort(gp.kpos, gp.kpos + nk, [&](int x, int y) { return effective(x) < effective(y); });
-            std::stable_sort(gp.npos, gp.npos + nn, [ns](int x, int y) { return ns[x] < ns[y]; });
             for (int i = 0; i < kSweepMaxK; ++i) gp.ks[i] = i < nk ? effective(gp.kpos[i]) : V;
-            for (int i = 0; i < kSweepMaxN; ++i) gp.ns[i] = i < nn ? ns[gp.npos[i]] : 1;
+            gp.nmask = 0;
+            for (int i = 0; i < nn; ++i) gp.nmask |= 1ull << (ns[i] - 1);
+            for (int i = 0; i < kSweepMaxN; ++i) gp.slot[i] = i < nn ? __builtin_popcountll(gp.nmask & ((1ull << (ns[i] - 1)) - 1ull)) : 0;
             h->solved = false;                                       // the workspace holds the policy of an earlier solve
             gp.p = p; gp.q = q; gp.V = V; gp.accept_prob = accept_prob; gp.status = status;
             gp.work = static_cast<unsigned char*>(h->full_ws); gp.work_stride = (static_cast<size_t>(V) + 2) * kFullBytesPerToken;

@@ -10,10 +10,11 @@
 //
 // Sums are whole numbers of 2^-62 (p and q sum to 1.001 at most): exact, so the result does not depend on the order of the additions.
 //
-// One workgroup per row.  Bound: three passes over the row (20 bytes a token; q alone in the second) and the LDS additions of the third.
-// Two radix sorts per row (by q/p and by q), gathers and masked prefix scans took 3856 us for 256 rows of 128256 tokens, six sizes and ten draft
-// counts; this takes 311 us.  256 rows whose drafts are almost the target 3630 -> 639, of 8192 tokens 324 -> 55, one row of 128256 tokens
-// 1758 -> 181, of 300 tokens and one size 38.8 -> 14.3 us (and as long as before, 42 us, with eight sizes and eight draft counts).
+// One workgroup per row.  Bound: instruction issue of the third of three passes over the row (class, ratio, bin and three LDS additions per token), which takes
+// half of the launch; the first runs at the memory's rate.  Two radix sorts per row (by q/p and by q), gathers and masked prefix scans took 3860 us for 256
+// rows of 128256 tokens, six sizes and ten draft counts; the first form of this 311 us (with a float64 quotient for every token, a pass over the row for
+// every second round and a wave reduction per bin and cell), this 246.  256 rows whose drafts are almost the target 3640 -> 649, of 8192 tokens 324 -> 52, one row
+// of 128256 tokens 1755 -> 135, of 300 tokens and one size 38.6 -> 20.5, with eight sizes and eight draft counts 41.8 -> 38.6 us.
 #include "gr_internal.h"
 
 namespace gr {
@@ -27,26 +28,34 @@ constexpr int kClasses = 2048;                     // of q: exponent and four bi
 constexpr int kList = 8192;                        // keys that the search for the top-k thresholds holds in LDS
 constexpr unsigned long long kInf = 0x7ff0000000000000ull;
 
+constexpr int kMaxHeavy = 2048;                   // so many tokens of the classes of largest q at most are kept at hand
+constexpr int kItems = kSweepMaxK * kBins / kNT;   // bins of a thread, one of every other top-k size
+
+// The place of a digit's counter: the lanes that look for a digit each own a run of them.
+__host__ __device__ constexpr int padded(int digit) { return digit + (digit >> 5); }
+
 // An interval of the order's keys that is still open: [lo, hi), and what lies before it of every top-k size.
-struct Interval { unsigned long long lo, hi, P[kSweepMaxK], Q[kSweepMaxK]; };
-static_assert(sizeof(Interval) == 144, "two tokens of the workspace's 96 bytes hold one");
+struct Interval { unsigned long long lo, hi, tokens; double P[kSweepMaxK], Q[kSweepMaxK]; };
+static_assert(sizeof(Interval) <= 2 * kFullBytesPerToken, "an interval holds two tokens at least: their bytes of the workspace hold it");
 
 struct GridLds {
     union {
-        struct { unsigned long long P[kSweepMaxK][kBins + 1], Q[kSweepMaxK][kBins + 1]; int count[kSweepMaxK][kBins]; };
-        struct { unsigned long long keys[kList]; int hist[kSweepMaxK][256]; int classes[kClasses]; };
+        // per top-k size and bin: sums in units of 2^-62, then P and Q at the bin's last place (rows padded: the sizes of a bin lie in different banks)
+        struct { union { unsigned long long sum[2][kSweepMaxK][kBins + 2]; double at[2][kSweepMaxK][kBins + 2]; }; int count[kSweepMaxK][kBins]; };
+        struct { unsigned long long keys[kList]; int hist[kSweepMaxK][padded(256)]; int classes[padded(kClasses)]; };   // classes: the wanted ones, once counted
     };
+    Element heavy[kMaxHeavy];
     Interval open[kMaxOpen];
     int shift[kMaxOpen];                           // bin of a key of open[i]: (key - lo) >> shift[i]
     unsigned long long prefix[kSweepMaxK];         // the search: the threshold's digits so far; then the thresholds
     int need[kSweepMaxK], bucket[kSweepMaxK];
-    double best[kSweepMaxK][kSweepMaxN];
-    double cell[kSweepMaxN][kNW];
-    double mass[kSweepMaxK];
+    double best[kSweepMaxK][kSweepMaxN], limit[kSweepMaxK][kSweepMaxN];   // limit: what a smaller F has to be below
+    double low[kSweepMaxN][kNW];
+    double mass[kSweepMaxK], inv_mass[kSweepMaxK];
     double red[kNW];
     int flag[kBins];
     int wcount[kNW];
-    int listed;
+    int listed, heavies, inside, heavy_class;
 };
 
 // The order's key of a token: rising keys are falling ratios; p = 0 gives +inf, which comes first.  The quotient is rounded correctly, so two
@@ -58,41 +67,52 @@ __device__ __forceinline__ unsigned long long ratio_key(float q, float p) {
 // v in units of 2^-62, v in [0, 2).
 __device__ __forceinline__ unsigned long long fixed62(float v) {
     const unsigned b = __float_as_uint(v);
-    const int e = static_cast<int>(b >> 23) & 255;
-    const unsigned long long m = (b & 0x7FFFFFu) | (e ? 0x800000u : 0u);
-    const int s = max(e, 1) - 88;                  // 2^(e - 150) to 2^-62
-    return s >= 0 ? m << s : m >> min(-s, 31);
+    const unsigned long long m = static_cast<unsigned long long>(((b & 0x7FFFFFu) | 0x800000u) << 7) << 32;   // 24 bits below bit 63
+    return m >> min(127u - (b >> 23), 63u);
 }
-// Bins of the first round, by the ratio's exponent e: 32 to an octave for -5 <= e < 5, where thresholds lie (a token is taken up to a ratio
-// of about 1 / n, in the support's own scale), 4 up to 21, one to four octaves beyond, and one for the ratios that are not finite.
+// Bins of the first round, by the ratio's place x in 32nds of an octave: 32 to an octave from 2^-5 to 2^5, where thresholds lie (a token is taken up to
+// a ratio of about 1 / n, in the support's own scale), two to an octave out to 2^-53 and 2^52, one for what lies beyond on either side, and one for
+// the ratios that are not finite.
+__device__ __forceinline__ int bin_of(int x) {
+    const int u = x < -160 ? max(0, 96 + ((x + 160) >> 4)) : (x < 160 ? 256 + x : min(510, 416 + ((x - 160) >> 4)));
+    return kBins - 1 - u;
+}
 __device__ __forceinline__ int first_bin(unsigned long long key) {
     const unsigned long long r = kInf - key;
-    const int e = static_cast<int>(r >> 52) - 1023;
-    const int top5 = static_cast<int>(r >> 47) & 31;
-    int u;
-    if (e >= -5 && e < 5) u = 96 + (e + 5) * 32 + top5;
-    else if (e < -21) u = max(0, 32 + ((e + 21) >> 2));
-    else if (e < -5) u = 32 + (e + 21) * 4 + (top5 >> 3);
-    else if (e < 21) u = 416 + (e - 5) * 4 + (top5 >> 3);
-    else u = e < 1024 ? min(510, 480 + ((e - 21) >> 2)) : 511;
-    return kBins - 1 - u;
+    return r == kInf ? 0 : bin_of(static_cast<int>(r >> 47) - (1023 << 5));
+}
+// The same from a float32 quotient of a few units in the last place, where that cannot lie on the other side of an edge; -1 where it might.
+__device__ __forceinline__ int quick_bin(float q, float p) {
+    const unsigned r = __float_as_uint(q * __builtin_amdgcn_rcpf(p));
+    const bool sure = min(__float_as_uint(p), __float_as_uint(q)) > 0x0d800000u && ((r + 8u) & 0x3FFFFu) > 16u;   // both above 2^-100
+    return sure ? bin_of(static_cast<int>(r >> 18) - (127 << 5)) : -1;
 }
 // The smallest pattern of a ratio in bin u (counted by rising ratios), 0..kBins.
 __device__ __forceinline__ unsigned long long first_edge(int u) {
-    auto at = [](int e, unsigned long long sub) { return (static_cast<unsigned long long>(e + 1023) << 52) | sub; };
     if (u <= 0) return 0ull;
-    if (u < 32) return at(-21 + 4 * (u - 32), 0ull);
-    if (u < 96) return at(-21 + (u - 32) / 4, static_cast<unsigned long long>((u - 32) & 3) << 50);
-    if (u < 416) return at(-5 + (u - 96) / 32, static_cast<unsigned long long>((u - 96) & 31) << 47);
-    if (u < 480) return at(5 + (u - 416) / 4, static_cast<unsigned long long>((u - 416) & 3) << 50);
-    if (u < 511) return at(21 + 4 * (u - 480), 0ull);
-    return u == 511 ? kInf : kInf + 1ull;
+    if (u >= 511) return u == 511 ? kInf : kInf + 1ull;
+    const int x = u < 96 ? 16 * (u - 96) - 160 : (u < 416 ? u - 256 : 16 * (u - 416) + 160);
+    return static_cast<unsigned long long>(x + (1023 << 5)) << 47;
 }
 
-// Every token of a row, four to a thread and step: f(p, q, id).
+// Every token of a row: f(p, q, id).  Long rows: four to a thread and step, two steps in flight where vectors can read them.  A short row takes
+// one copy of f for all of its tokens: it waits for instructions that no wave has fetched before more than for anything else (one row of 300 tokens,
+// eight sizes and eight draft counts 55 us with the long rows' loops, 42 with this one; 256 rows of 128256 tokens 313 us with this one).
+constexpr int kFewTokens = 16384;
 template <bool P, class F>
 __device__ __forceinline__ void each_token(const float* pr, const float* qr, int V, F f) {
     const int tid = threadIdx.x;
+    if (V <= kFewTokens) {
+        float p = 0.f, q = 0.f;
+        if (tid < V) { if (P) p = pr[tid]; q = qr[tid]; }
+#pragma unroll 1
+        for (int i = tid; i < V; i += kNT) {
+            const float pv = p, qv = q;
+            if (i + kNT < V) { if (P) p = pr[i + kNT]; q = qr[i + kNT]; }
+            f(pv, qv, i);
+        }
+        return;
+    }
     if (((reinterpret_cast<size_t>(pr) | reinterpret_cast<size_t>(qr)) & 15u) == 0) {
         const int whole = V & ~3;
         constexpr int U = 2;
@@ -130,17 +150,17 @@ template <int DIGITS>
 __device__ __forceinline__ int pick_digit(const int* hist, int& need, int& holds) {
     constexpr int PER = DIGITS / 64;
     const int lane = threadIdx.x & 63;
-    int tot = 0;                                   // lane l owns the digits from DIGITS - 1 - PER l downwards
-    for (int j = 0; j < PER; ++j) tot += hist[DIGITS - 1 - PER * lane - j];
+    int c[PER], tot = 0;                           // lane l owns the digits from DIGITS - 1 - PER l downwards
+#pragma unroll
+    for (int j = 0; j < PER; ++j) { c[j] = hist[padded(DIGITS - 1 - PER * lane - j)]; tot += c[j]; }
     const int incl = wave_scan_i(tot), excl = incl - tot;
     int digit = 0, left = 0, here = 0;
     if (excl < need && need <= incl) {
         int above = excl;
+#pragma unroll
         for (int j = 0; j < PER; ++j) {
-            digit = DIGITS - 1 - PER * lane - j;
-            here = hist[digit]; left = need - above;
-            if (left <= here) break;
-            above += here;
+            if (here == 0 && need <= above + c[j]) { digit = DIGITS - 1 - PER * lane - j; here = c[j]; left = need - above; }
+            above += c[j];
         }
     }
     const int src = __ffsll(static_cast<long long>(__ballot(here > 0))) - 1;
@@ -149,17 +169,25 @@ __device__ __forceinline__ int pick_digit(const int* hist, int& need, int& holds
     return __builtin_amdgcn_readlane(digit, src);
 }
 
-// x, x^2, ... to the grid's draft counts in rising order: g(b, x^ns[b]), the products that ipow takes.
-template <class G>
-__device__ __forceinline__ void powers(const GridParams& gp, double x, G g) {
-    double pw = x;
-    int e = 1;
+template <int CTRL, int ROWS>
+__device__ __forceinline__ void scan_step(unsigned long long& v) {
+    const int lo = dpp_shift<CTRL, ROWS>(static_cast<int>(v), 0), hi = dpp_shift<CTRL, ROWS>(static_cast<int>(v >> 32), 0);
+    v += (static_cast<unsigned long long>(static_cast<unsigned>(hi)) << 32) | static_cast<unsigned>(lo);
+}
+
+// x, x^2, ... up to the grid's largest draft count, the products that ipow takes, of every item: g(slot) at each draft count of the grid.
+template <int N, class G>
+__device__ __forceinline__ void powers(const GridParams& gp, const double (&x)[N], double (&pw)[N], G g) {
+    unsigned long long left = gp.nmask;            // bit n - 1: n is in the grid
 #pragma unroll
-    for (int b = 0; b < kSweepMaxN; ++b) {
-        if (b < gp.nn) {
-            for (; e < gp.ns[b]; ++e) pw = __dmul_rn(pw, x);
-            g(b, pw);
-        }
+    for (int i = 0; i < N; ++i) pw[i] = x[i];
+#pragma unroll 1
+    for (int slot = 0;;) {
+        if (left & 1ull) { g(slot); ++slot; }
+        left >>= 1;
+        if (left == 0ull) break;
+#pragma unroll
+        for (int i = 0; i < N; ++i) pw[i] = __dmul_rn(pw[i], x[i]);
     }
 }
 
@@ -169,21 +197,21 @@ __global__ __launch_bounds__(kNT) void grid_kernel(GridParams gp) {
     extern __shared__ __align__(16) unsigned char grid_lds[];
     GridLds& S = *reinterpret_cast<GridLds*>(grid_lds);
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, row = blockIdx.x;
-    const int V = gp.V, nk = gp.nk, nn = gp.nn;
+    const int V = gp.V, nk = gp.nk, nn = gp.nn, slots = __popcll(gp.nmask);
     const float* pr = gp.p + static_cast<size_t>(row) * V;
     const float* qr = gp.q + static_cast<size_t>(row) * V;
     Interval* stack = reinterpret_cast<Interval*>(gp.work + row * gp.work_stride);
 
     // sums, validity, positive entries of q by magnitude
-    for (int c = tid; c < kClasses; c += kNT) S.classes[c] = 0;
-    if (tid == 0) S.listed = 0;
+    for (int c = tid; c < padded(kClasses); c += kNT) S.classes[c] = 0;
+    if (tid == 0) { S.listed = 0; S.heavies = 0; }
     __syncthreads();
     double ps = 0.0, qs = 0.0;
     int bad = 0, positive = 0;
     each_token<true>(pr, qr, V, [&](float pv, float qv, int) {
         bad |= !(qv >= 0.f) | !(pv >= 0.f);
         ps += static_cast<double>(pv); qs += static_cast<double>(qv);
-        if (qv > 0.f) { ++positive; atomicAdd(&S.classes[min(__float_as_uint(qv) >> 19, kClasses - 1u)], 1); }
+        if (qv > 0.f) { ++positive; atomicAdd(&S.classes[padded(min(__float_as_uint(qv) >> 19, kClasses - 1u))], 1); }
     });
     const double ptot = block_sum<kNW>(ps, S.red), qtot = block_sum<kNW>(qs, S.red);
     bad = block_sum_i<kNW>(bad, S.red);
@@ -196,47 +224,46 @@ __global__ __launch_bounds__(kNT) void grid_kernel(GridParams gp) {
 
     // the smallest key (q, then the lower id) of each top-k size, by radix selection: the classes first, then eight bits at a time over the
     // keys of the classes that thresholds fall into, from LDS where they fit and from the row where not
-    if (wv < nk) {
-        int need = gp.ks[wv], holds = 0;
-        unsigned long long prefix = 0ull;
-        if (need < positive) prefix = static_cast<unsigned long long>(pick_digit<kClasses>(S.classes, need, holds)) << 51;
-        if (lane == 0) { S.prefix[wv] = prefix; S.need[wv] = need; S.bucket[wv] = gp.ks[wv] < positive ? holds : need; }
+    if (wv <= nk) {                                // the last of these waves: the classes of the kMaxHeavy largest q
+        const int rank = wv < nk ? gp.ks[wv] : kMaxHeavy + 1;
+        int need = rank, holds = rank, digit = 0;
+        if (rank < positive) digit = pick_digit<kClasses>(S.classes, need, holds);
+        if (lane == 0) {
+            if (wv < nk) { S.prefix[wv] = static_cast<unsigned long long>(digit) << 51; S.need[wv] = need; S.bucket[wv] = holds; }
+            else S.heavy_class = rank < positive ? digit + 1 : 0;
+        }
     }
     __syncthreads();
     unsigned open = 0u;                            // the sizes whose threshold is not found yet
     for (int a = 0; a < nk; ++a) if (S.bucket[a] != S.need[a]) open |= 1u << a;
     if (open) {
         int keys = 0;
-        for (int a = 0; a < nk; ++a) {
-            bool first = open >> a & 1u;
-            for (int o = 0; o < a; ++o) first = first && !((open >> o & 1u) && S.prefix[o] == S.prefix[a]);
-            if (first) keys += S.bucket[a];
-        }
+        unsigned long long last = ~0ull;               // sizes rise, so equal classes are neighbours
+        for (int a = 0; a < nk; ++a)
+            if (open >> a & 1u) { const unsigned long long c = S.prefix[a]; if (c != last) keys += S.bucket[a]; last = c; }
         const bool listed = keys <= kList;
         unsigned long long thr[kSweepMaxK];
         if (listed) {
-#pragma unroll
-            for (int a = 0; a < kSweepMaxK; ++a) thr[a] = a < nk && (open >> a & 1u) ? S.prefix[a] >> 51 : ~0ull;
+            for (int c = tid; c < padded(kClasses); c += kNT) S.classes[c] = 0;
+            __syncthreads();
+            if (tid < nk && (open >> tid & 1u)) S.classes[padded(static_cast<int>(S.prefix[tid] >> 51))] = 1;
+            __syncthreads();
             each_token<false>(pr, qr, V, [&](float, float qv, int id) {
-                const unsigned c = __float_as_uint(qv) >> 19;
-                bool in = false;
-#pragma unroll
-                for (int a = 0; a < kSweepMaxK; ++a) in |= c == static_cast<unsigned>(thr[a]);
-                if (in && qv > 0.f) S.keys[atomicAdd(&S.listed, 1)] = make_key(qv, id);
+                if (S.classes[padded(min(__float_as_uint(qv) >> 19, kClasses - 1u))] && qv > 0.f) S.keys[atomicAdd(&S.listed, 1)] = make_key(qv, id);
             });
             __syncthreads();
         }
         for (int shift = 51; open && shift > 0;) {
             const int width = min(8, shift), above = shift;
             shift -= width;
-            for (int c = tid; c < kSweepMaxK * 256; c += kNT) (&S.hist[0][0])[c] = 0;
+            for (int c = tid; c < kSweepMaxK * padded(256); c += kNT) (&S.hist[0][0])[c] = 0;
             __syncthreads();
 #pragma unroll
             for (int a = 0; a < kSweepMaxK; ++a) thr[a] = a < nk && (open >> a & 1u) ? S.prefix[a] >> above : ~0ull;
             auto add = [&](unsigned long long key) {
                 const int d = static_cast<int>(key >> shift) & 255 & ((1 << width) - 1);
 #pragma unroll
-                for (int a = 0; a < kSweepMaxK; ++a) if (key >> above == thr[a]) atomicAdd(&S.hist[a][d], 1);
+                for (int a = 0; a < kSweepMaxK; ++a) if (key >> above == thr[a]) atomicAdd(&S.hist[a][padded(d)], 1);
             };
             if (listed) { for (int i = tid; i < keys; i += kNT) add(S.keys[i]); }
             else each_token<false>(pr, qr, V, [&](float, float qv, int id) { if (qv > 0.f) add(make_key(qv, id)); });
@@ -251,81 +278,139 @@ __global__ __launch_bounds__(kNT) void grid_kernel(GridParams gp) {
             for (int a = 0; a < nk; ++a) if (S.bucket[a] != S.need[a]) open |= 1u << a;
         }
     }
-    unsigned long long thr[kSweepMaxK];
+    unsigned thr_q[kSweepMaxK], thr_id[kSweepMaxK];            // the same in every lane: scalar registers
 #pragma unroll
-    for (int a = 0; a < kSweepMaxK; ++a) thr[a] = a < nk ? S.prefix[a] : 0ull;
+    for (int a = 0; a < kSweepMaxK; ++a) {
+        const unsigned long long t = a < nk ? S.prefix[a] : 0ull;
+        thr_q[a] = __builtin_amdgcn_readfirstlane(static_cast<int>(t >> 32)); thr_id[a] = __builtin_amdgcn_readfirstlane(static_cast<int>(t));
+    }
+    // the smallest top-k size that holds a token; nk: none
+    auto class_of = [&](float qv, int id) {
+        const unsigned b = __float_as_uint(qv);
+        int cls = 0;
+        bool ties = false;
+#pragma unroll
+        for (int a = 0; a < kSweepMaxK; ++a) if (a < nk) { cls += b < thr_q[a]; ties |= b == thr_q[a]; }
+        if (ties) {
+            const unsigned low = 0xFFFFFFFFu - static_cast<unsigned>(id);
+#pragma unroll
+            for (int a = 0; a < kSweepMaxK; ++a) if (a < nk) cls += b == thr_q[a] && low < thr_id[a];
+        }
+        return qv > 0.f ? cls : nk;
+    };
+    auto add = [&](int cls, int bin, float pv, float qv) {
+        atomicAdd(&S.sum[0][cls][bin], fixed62(pv));
+        atomicAdd(&S.sum[1][cls][bin], fixed62(qv));
+        atomicAdd(&S.count[cls][bin], 1);
+    };
     for (int c = tid; c < kSweepMaxK * kSweepMaxN; c += kNT) (&S.best[0][0])[c] = 0.0;   // F(0) = 0: the empty prefix
     const double invp = 1.0 / ptot;
+    const int heavy_class = S.heavy_class;
     constexpr double kUnit = 1.0 / 4611686018427387904.0;      // 2^-62
 
     int waiting = 0;                               // intervals on the stack, the one of smallest keys on top
     for (int taken = 0;; ) {                       // intervals of this round; 0: the first, over all keys
         const int log_per = taken ? kBinsLog - (31 - __clz(2 * taken - 1)) : kBinsLog;
         __syncthreads();
-        for (int c = tid; c < nk * (kBins + 1); c += kNT) { (&S.P[0][0])[c] = 0ull; (&S.Q[0][0])[c] = 0ull; }
-        for (int c = tid; c < nk * kBins; c += kNT) (&S.count[0][0])[c] = 0;
+        static_assert((kBins + 2) % 2 == 0 && kBins % 4 == 0, "whole vectors");
+        for (int c = tid; c < nk * (kBins + 2) / 2; c += kNT) {
+            reinterpret_cast<ulonglong2*>(S.sum[0])[c] = make_ulonglong2(0ull, 0ull); reinterpret_cast<ulonglong2*>(S.sum[1])[c] = make_ulonglong2(0ull, 0ull);
+        }
+        for (int c = tid; c < nk * kBins / 4; c += kNT) reinterpret_cast<int4*>(S.count)[c] = make_int4(0, 0, 0, 0);
         if (tid < taken) {
             const unsigned long long width = S.open[tid].hi - S.open[tid].lo - 1ull;
             S.shift[tid] = max(0, (width ? 64 - __clzll(static_cast<long long>(width)) : 0) - log_per);
         }
         __syncthreads();
-        const unsigned long long from = taken ? S.open[0].lo : 0ull, to = taken ? S.open[taken - 1].hi : ~0ull;
-        each_token<true>(pr, qr, V, [&](float pv, float qv, int id) {
-            const unsigned long long qkey = make_key(qv, id);
-            if (!(qv > 0.f) || qkey < thr[nk - 1]) return;
-            const unsigned long long key = ratio_key(qv, pv);
-            int bin;
-            if (!taken) bin = first_bin(key);
-            else {
-                if (key < from || key >= to) return;
-                int i = 0;                         // the last interval that begins at the key or before it
+        if (!taken) {
+            each_token<true>(pr, qr, V, [&](float pv, float qv, int id) {
+                const int cls = class_of(qv, id);
+                if (cls >= nk) return;
+                int bin = quick_bin(qv, pv);
+                if (bin < 0) bin = first_bin(ratio_key(qv, pv));
+                add(cls, bin, pv, qv);
+                if (static_cast<int>(__float_as_uint(qv) >> 19) >= heavy_class) S.heavy[min(atomicAdd(&S.heavies, 1), kMaxHeavy - 1)] = Element{pv, qv, id};   // they fit
+            });
+        } else {
+            const unsigned long long from = S.open[0].lo, to = S.open[taken - 1].hi;
+            // the open interval of a token's key, -1: none
+            auto interval = [&](unsigned long long key) {
+                if (key < from || key >= to) return -1;
+                int i = 0;                         // the last one that begins at the key or before it
                 for (int step = kMaxOpen / 2; step > 0; step >>= 1) if (i + step < taken && S.open[i + step].lo <= key) i += step;
-                if (key >= S.open[i].hi) return;
-                bin = (i << log_per) + static_cast<int>((key - S.open[i].lo) >> S.shift[i]);
+                return key < S.open[i].hi ? i : -1;
+            };
+            auto put = [&](float pv, float qv, int id) {
+                const int cls = class_of(qv, id);
+                if (cls >= nk) return;
+                const unsigned long long key = ratio_key(qv, pv);
+                const int i = interval(key);
+                if (i >= 0) add(cls, (i << log_per) + static_cast<int>((key - S.open[i].lo) >> S.shift[i]), pv, qv);
+            };
+            // Far from the thresholds a bin is wide, and one or two tokens of a large mass leave it open: those are at hand.  (One row of 256 needs
+            // the round more often than not, and a pass over its row for it took a third of the launch again.)
+            const int heavies = S.heavies;
+            if (tid == 0) S.inside = 0;
+            __syncthreads();
+            for (int h = tid; h < heavies; h += kNT) {
+                const Element e = S.heavy[h];
+                if (class_of(e.q, e.id) < nk && interval(ratio_key(e.q, e.p)) >= 0) atomicAdd(&S.inside, 1);
             }
-            int cls = 0;
-#pragma unroll
-            for (int a = 0; a < kSweepMaxK; ++a) cls += a < nk && qkey < thr[a];
-            atomicAdd(&S.P[cls][bin], fixed62(pv));
-            atomicAdd(&S.Q[cls][bin], fixed62(qv));
-            atomicAdd(&S.count[cls][bin], 1);
-        });
-        __syncthreads();
-        // every top-k size holds the tokens of the smaller ones
-        if (tid < kBins) {
-            unsigned long long p = 0ull, q = 0ull; int c = 0;
-            for (int a = 0; a < nk; ++a) {
-                p += S.P[a][tid]; S.P[a][tid] = p;
-                q += S.Q[a][tid]; S.Q[a][tid] = q;
-                c += S.count[a][tid]; S.count[a][tid] = c;
-            }
-            S.flag[tid] = 0;
+            __syncthreads();
+            int tokens = 0;
+            for (int i = lane; i < taken; i += 64) tokens += static_cast<int>(S.open[i].tokens);
+            if (wave_sum_i(tokens) == S.inside) { for (int h = tid; h < heavies; h += kNT) { const Element e = S.heavy[h]; put(e.p, e.q, e.id); } }
+            else each_token<true>(pr, qr, V, put);
         }
         __syncthreads();
-        // prefix sums over the bins: a wave to a size and sum
+        // every top-k size holds the tokens of the smaller ones: a thread adds up one bin's p or q
+        {
+            const int which = tid / kBins, j = tid % kBins;
+            unsigned long long v[kSweepMaxK]; int c[kSweepMaxK];
+#pragma unroll
+            for (int a = 0; a < kSweepMaxK; ++a) { v[a] = a < nk ? S.sum[which][a][j] : 0ull; c[a] = which == 0 && a < nk ? S.count[a][j] : 0; }
+#pragma unroll
+            for (int a = 1; a < kSweepMaxK; ++a) {
+                v[a] += v[a - 1]; c[a] += c[a - 1];
+                if (a < nk) { S.sum[which][a][j] = v[a]; if (which == 0) S.count[a][j] = c[a]; }
+            }
+            if (which == 0) S.flag[j] = 0;
+        }
+        __syncthreads();
+        // P and Q at every bin's last place: sums over the bins, a wave to a size and sum, from where the bin's interval begins
         if (wv < 2 * nk) {
-            unsigned long long* x = (wv & 1) ? S.Q[wv >> 1] : S.P[wv >> 1];
-            constexpr int PER = kBins / 64;
-            unsigned long long v[PER], tot = 0ull;
-#pragma unroll
-            for (int j = 0; j < PER; ++j) { v[j] = x[PER * lane + j]; tot += v[j]; }
-            unsigned long long incl = tot;
-            for (int o = 1; o < 64; o <<= 1) { const unsigned long long up = __shfl_up(incl, o); if (lane >= o) incl += up; }
-            unsigned long long at = incl - tot;
-#pragma unroll
-            for (int j = 0; j < PER; ++j) { x[PER * lane + j] = at; at += v[j]; }
-            if (lane == 63) { x[kBins] = at; if (!taken && (wv & 1)) S.mass[wv >> 1] = static_cast<double>(at) * kUnit; }
+            const int a = wv >> 1, which = wv & 1;
+            unsigned long long carry = 0ull;
+#pragma unroll 1
+            for (int j = lane; j < kBins; j += 64) {
+                unsigned long long v = S.sum[which][a][j];
+                scan_step<0x111, 0xF>(v); scan_step<0x112, 0xF>(v); scan_step<0x114, 0xF>(v); scan_step<0x118, 0xF>(v);
+                scan_step<0x142, 0xA>(v); scan_step<0x143, 0xC>(v);
+                v += carry;
+                carry = (static_cast<unsigned long long>(static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(v >> 32), 63))) << 32) |
+                        static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(v), 63));
+                S.sum[which][a][j] = v;
+            }
+            if (!taken && which == 1) { const double m = static_cast<double>(carry) * kUnit; if (lane == 0) { S.mass[a] = m; S.inv_mass[a] = 1.0 / m; } }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); __builtin_amdgcn_wave_barrier();
+            const double scale = kUnit * (which == 0 ? invp : S.inv_mass[a]);
+#pragma unroll 1
+            for (int j = kBins - 64 + lane; j >= 0; j -= 64) {       // downwards: what lies before an interval is still a sum
+                const int o = j >> log_per, from = o << log_per;
+                unsigned long long v = S.sum[which][a][j];
+                if (from > 0) v -= S.sum[which][a][from - 1];
+                const double base = taken && o < taken ? (which == 0 ? S.open[o].P[a] : S.open[o].Q[a]) : 0.0;
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); __builtin_amdgcn_wave_barrier();
+                S.at[which][a][j] = base + static_cast<double>(v) * scale;
+            }
         }
         __syncthreads();
-        // A bin's ends: (Q, P) of its first and last place; false where it holds no token of size a.
-        auto ends = [&](int a, int j, double& p0, double& q0, double& p1, double& q1) {
-            if (S.count[a][j] == 0) return false;
-            unsigned long long bp = 0ull, bq = 0ull;
-            if (taken) { const int i = j >> log_per; bp = S.open[i].P[a] - S.P[a][i << log_per]; bq = S.open[i].Q[a] - S.Q[a][i << log_per]; }
-            const double inv = 1.0 / S.mass[a];
-            p0 = static_cast<double>(S.P[a][j] + bp) * kUnit * invp; q0 = static_cast<double>(S.Q[a][j] + bq) * kUnit * inv;
-            p1 = static_cast<double>(S.P[a][j + 1] + bp) * kUnit * invp; q1 = static_cast<double>(S.Q[a][j + 1] + bq) * kUnit * inv;
-            return true;
+        // (P, Q) at the first place of a bin
+        auto start = [&](int a, int j, double& p, double& q) {
+            const int o = j >> log_per;
+            if (j != o << log_per) { p = S.at[0][a][j - 1]; q = S.at[1][a][j - 1]; }
+            else if (taken) { p = S.open[o].P[a]; q = S.open[o].Q[a]; }
+            else { p = 0.0; q = 0.0; }
         };
         auto keys_of = [&](int j, unsigned long long& lo, unsigned long long& hi) {
             if (!taken) { const int u = kBins - 1 - j; lo = kInf + 1ull - first_edge(u + 1); hi = kInf + 1ull - first_edge(u); return; }
@@ -333,48 +418,62 @@ __global__ __launch_bounds__(kNT) void grid_kernel(GridParams gp) {
             lo = S.open[i].lo + (static_cast<unsigned long long>(j & ((1 << log_per) - 1)) << S.shift[i]);
             hi = min(S.open[i].hi, lo + (1ull << S.shift[i]));
         };
-        // F at the bins' last places: the eight waves of a size by turns
-        for (int a0 = 0; a0 < nk; a0 += kNT / kBins) {
-            const int a = a0 + tid / kBins, j = tid % kBins;
-            double f[kSweepMaxN];
+        // F at the bins' last places, two waves to a top-k size: their lanes take four bins each, so that few minima go over the lanes
+        if (wv < 2 * nk) {
+            constexpr int PER = kBins / 128;
+            double p[PER], x[PER], pw[PER];
 #pragma unroll
-            for (int b = 0; b < kSweepMaxN; ++b) f[b] = 0.0;
-            double p0, q0, p1, q1;
-            if (a < nk && ends(a, j, p0, q0, p1, q1)) powers(gp, q1, [&](int b, double pw) { f[b] = fmin(0.0, p1 - pw); });
+            for (int i = 0; i < PER; ++i) {
+                const int j = 128 * i + 64 * (wv & 1) + lane;
+                const bool in = (j >> log_per) < max(taken, 1);                // no interval behind the last one
+                p[i] = in ? S.at[0][wv >> 1][j] : 1e300; x[i] = in ? S.at[1][wv >> 1][j] : 0.0;
+            }
+            powers(gp, x, pw, [&](int slot) {
+                double m = p[0] - pw[0];
 #pragma unroll
-            for (int b = 0; b < kSweepMaxN; ++b) {
-                if (b < nn) {
-                    const double m = wave_min(f[b]);
-                    if (lane == 0) S.cell[b][wv] = m;
-                }
-            }
-            __syncthreads();
-            if (tid < kNT / kBins * kSweepMaxN) {
-                const int b = tid % kSweepMaxN, s = tid / kSweepMaxN;
-                if (b < nn && a0 + s < nk) {
-                    double m = S.best[a0 + s][b];
-                    for (int w = 0; w < kBins / 64; ++w) m = fmin(m, S.cell[b][s * (kBins / 64) + w]);
-                    S.best[a0 + s][b] = m;
-                }
-            }
-            __syncthreads();
+                for (int i = 1; i < PER; ++i) m = fmin(m, p[i] - pw[i]);
+                m = wave_min(m);
+                if (lane == 0) S.low[slot][wv] = m;
+            });
         }
-        // bins that may hold less.  What is not looked for is below 1e-13 of the acceptance.
-        for (int a0 = 0; a0 < nk; a0 += kNT / kBins) {
-            const int a = a0 + tid / kBins, j = tid % kBins;
-            double p0, q0, p1, q1;
-            if (a >= nk || S.count[a < nk ? a : 0][j] < 2 || !ends(a, j, p0, q0, p1, q1)) continue;
-            unsigned long long lo, hi;
-            keys_of(j, lo, hi);
-            if (hi - lo < 2ull) continue;
-            const double scale = S.mass[a] * invp, rmax = __longlong_as_double(static_cast<long long>(kInf - lo)),
-                         rmin = __longlong_as_double(static_cast<long long>(kInf + 1ull - hi));
-            const double s0 = scale / rmax, s1 = scale / rmin, dq = q1 - q0;
-            double x = s1 < 1e300 ? (s1 * dq - (p1 - p0)) / (s1 - s0) : dq;
-            x = fmin(fmax(x, 0.0), dq);
-            const double px = p0 + s0 * x;
+        __syncthreads();
+        if (tid < kSweepMaxK * kSweepMaxN) {
+            const int a = tid / kSweepMaxN, slot = tid % kSweepMaxN;
+            if (a < nk && slot < slots) {
+                const double m = fmin(S.best[a][slot], fmin(S.low[slot][2 * a], S.low[slot][2 * a + 1]));
+                S.best[a][slot] = m;
+                S.limit[a][slot] = m - (1e-13 * (1.0 + m) + 1e-16);   // what is not looked for is below 1e-13 of the acceptance
+            }
+        }
+        __syncthreads();
+        // bins that may hold less: a thread takes one bin of every other size
+        {
+            const int j = tid % kBins, odd = tid / kBins;
+            unsigned long long lo = 0ull, hi = 0ull;
+            if ((j >> log_per) < max(taken, 1)) keys_of(j, lo, hi);
+            const double r0 = 1.0 / __longlong_as_double(static_cast<long long>(kInf - lo)), r1 = 1.0 / __longlong_as_double(static_cast<long long>(kInf + 1ull - hi));
+            double px[kItems], qx[kItems], pw[kItems];
+            bool some = false;
+#pragma unroll
+            for (int i = 0; i < kItems; ++i) {
+                const int a = min(2 * i + odd, nk - 1);
+                px[i] = 1e300; qx[i] = 0.0;
+                if (hi - lo >= 2ull && S.count[a][j] >= 2) {
+                    double p0, q0;
+                    start(a, j, p0, q0);
+                    const double scale = S.mass[a] * invp, s0 = scale * r0, s1 = scale * r1, dq = S.at[1][a][j] - q0, dp = S.at[0][a][j] - p0;
+                    double x = s1 < 1e300 ? (s1 * dq - dp) / (s1 - s0) : dq;
+                    x = fmin(fmax(x, 0.0), dq);
+                    px[i] = p0 + s0 * x; qx[i] = q0 + x;
+                    some = true;
+                }
+            }
             bool less = false;
-            powers(gp, q0 + x, [&](int b, double pw) { const double m = S.best[a][b]; less |= px - pw < m - (1e-13 * (1.0 + m) + 1e-16); });
+            if (__any(some))
+                powers(gp, qx, pw, [&](int slot) {
+#pragma unroll
+                    for (int i = 0; i < kItems; ++i) less |= px[i] - pw[i] < S.limit[min(2 * i + odd, nk - 1)][slot];
+                });
             if (less) S.flag[j] = 1;
         }
         __syncthreads();
@@ -388,25 +487,23 @@ __global__ __launch_bounds__(kNT) void grid_kernel(GridParams gp) {
         if (push) {
             Interval& t = stack[waiting + all - 1 - (before + __popcll(mask & ((1ull << lane) - 1ull)))];
             keys_of(tid, t.lo, t.hi);
-            const int i = tid >> log_per;
-            for (int a = 0; a < nk; ++a) {
-                t.P[a] = S.P[a][tid] + (taken ? S.open[i].P[a] - S.P[a][i << log_per] : 0ull);
-                t.Q[a] = S.Q[a][tid] + (taken ? S.open[i].Q[a] - S.Q[a][i << log_per] : 0ull);
-            }
+            t.tokens = S.count[nk - 1][tid];
+            for (int a = 0; a < nk; ++a) start(a, tid, t.P[a], t.Q[a]);
         }
         waiting += all;
         __syncthreads();
         if (waiting == 0) break;
         taken = min(waiting, kMaxOpen);
-        for (int c = tid; c < taken * (2 + 2 * kSweepMaxK); c += kNT) {
-            const int i = c / (2 + 2 * kSweepMaxK), w = c % (2 + 2 * kSweepMaxK);
+        constexpr int kWords = sizeof(Interval) / 8;
+        for (int c = tid; c < taken * kWords; c += kNT) {
+            const int i = c / kWords, w = c % kWords;
             reinterpret_cast<unsigned long long*>(&S.open[i])[w] = reinterpret_cast<const unsigned long long*>(&stack[waiting - 1 - i])[w];
         }
         waiting -= taken;
     }
     for (int c = tid; c < nk * kSweepMaxN; c += kNT) {
         const int a = c / kSweepMaxN, b = c % kSweepMaxN;
-        if (b < nn) gp.accept_prob[(static_cast<size_t>(row) * nk + gp.kpos[a]) * nn + gp.npos[b]] = static_cast<float>(1.0 + S.best[a][b]);
+        if (b < nn) gp.accept_prob[(static_cast<size_t>(row) * nk + gp.kpos[a]) * nn + b] = static_cast<float>(1.0 + S.best[a][gp.slot[b]]);
     }
     if (tid == 0) gp.status[row] = GR_ROW_OK;
 }

@@ -127,6 +127,7 @@ hipError_t launch_full_programs(const FullParams& fp, hipStream_t stream);
 constexpr int kSweepMaxK = 8;     // top-k sizes per call
 constexpr int kSweepMaxN = 16;    // draft counts per call
 constexpr int kSweepMaxDrafts = 64;
+static_assert(kSweepMaxDrafts <= 64, "a bit to a draft count");
 struct SweepParams {
     const float* p; int V; int splits;
     const unsigned long long* cand; const int* cand_count;
@@ -137,13 +138,14 @@ struct SweepParams {
     int* status;                  // [B]
 };
 hipError_t launch_sweep(const SweepParams& sw, int B, hipStream_t stream);
-// The grid of a sweep with a top-k above kMaxSupport: sizes and draft counts in rising order, with their places in the caller's lists.
+// The grid of a sweep with a top-k above kMaxSupport.
 struct GridParams {
     const float* p; const float* q; int V;
     int nk, nn;
-    int ks[kSweepMaxK], kpos[kSweepMaxK];     // ks: V for "no top-k"
-    int ns[kSweepMaxN], npos[kSweepMaxN];
-    unsigned char* work; size_t work_stride;  // scratch of a row: 72 bytes per token at least
+    int ks[kSweepMaxK], kpos[kSweepMaxK];     // in rising order, V for "no top-k"; their places in the caller's list
+    unsigned long long nmask;                 // bit n - 1: n is among the draft counts (kSweepMaxDrafts at most)
+    int slot[kSweepMaxN];                     // the caller's draft counts: how many smaller ones there are
+    unsigned char* work; size_t work_stride;  // scratch of a row: 76 bytes per token at least
     float* accept_prob;           // [B, nk, nn]
     int* status;                  // [B]
 };
