@@ -117,7 +117,7 @@ bool wide_scratch(gr_handle h) {
         carve(&w.rho, rows * kMaxSupport); carve(&w.pnorm, rows * kMaxSupport); carve(&w.info, rows);
     };
     all();
-    if (hipMalloc(&h->wide_mem, used) != hipSuccess) { (void)hipGetLastError(); h->wide_mem = nullptr; return false; }
+    if (solve_kernel_setup(h->max_n, kWalkRows, false) != hipSuccess || hipMalloc(&h->wide_mem, used) != hipSuccess) { (void)hipGetLastError(); h->wide_mem = nullptr; return false; }
     base = static_cast<unsigned char*>(h->wide_mem);
     all();
     return true;
@@ -305,7 +305,7 @@ extern "C" int gr_create(gr_handle* out, int max_B, int max_V, int max_k, int ma
         h->tail_mass = cfg->tail_mass;
     }
     if (hipGetDevice(&h->device) != hipSuccess) { delete h; return GR_EHIP; }
-    if (solve_kernel_setup(max_n, k_cap > kMaxSupport) != hipSuccess || (k_cap > kMaxSupport && (full_kernel_setup() != hipSuccess || grid_kernel_setup() != hipSuccess))) { delete h; return GR_EHIP; }
+    if (solve_kernel_setup(max_n, max_B, k_cap > kMaxSupport) != hipSuccess || (k_cap > kMaxSupport && (full_kernel_setup() != hipSuccess || grid_kernel_setup() != hipSuccess))) { delete h; return GR_EHIP; }
     { unsigned char* na = nullptr; (void)scratch_address(&na); }      // so that gr_accept_sweep_noalloc finds its array later
     const size_t rows = static_cast<size_t>(max_B);
     bool ok = dev_alloc(&h->cand, rows * kSelCap) && dev_alloc(&h->cand_count, rows * kMaxSplits) &&

@@ -151,7 +151,7 @@ struct GridParams {
 };
 hipError_t grid_kernel_setup();
 void launch_grid(const GridParams& gp, int B, hipStream_t stream);
-hipError_t solve_kernel_setup(int max_n, bool hbm);
+hipError_t solve_kernel_setup(int max_n, int max_B, bool hbm);
 hipError_t full_kernel_setup();
 
 // ---------------------------------------------------------------- device helpers

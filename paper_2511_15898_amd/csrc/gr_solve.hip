@@ -46,6 +46,12 @@ __device__ __forceinline__ int padded(int count) { return (count + kScan - 1) / 
 // wave's dependent float64 chains and LDS waits are filled by the other; four waves (one per SIMD, all 512
 // registers) for the longer series of 9 to 16 drafts.
 template <int D> constexpr int kThreadsOf = D > 8 ? 256 : 512;
+template <int D> constexpr int kWavesOf = D > 8 ? 1 : 2;
+// With more rows than compute units, two workgroups of four waves share one up to 8 drafts: while one row's stepping wave or its prologue keeps the other waves
+// waiting, the other row evaluates.  The call, one workgroup and two: 257 rows of 32000 tokens, n = 4, k = 64 130 and 142 us, 300 192 and 165, 512 217 and 178;
+// 1024 rows of 1024, n = 4, k = 32 246 and 169, of 128256, n = 8, k = 128 611 and 507 (selection 210).  Rows beyond the compute units must wait for one of them
+// to end, which a handful can do behind the batch's slowest row: the line lies a little above their number.
+constexpr int kNarrow = 256, kChip = 264;
 constexpr double kQuadStep = 0.45;   // trapezoid step in log t (discretisation error 5.6e-9 relative at most)
 constexpr double kQuadLo = 0.1;      // t_lo * (slack + sum w)
 // The nodes below t_lo, t_lo e^{-step k}, are not evaluated: the integrand over t, a sum of e^{-s t} with s (slack + sum w)^-1
@@ -85,18 +91,18 @@ template <int D> struct alignas(16) NodeRec { double t, qw; double Tr[D]; };    
 struct Grid { double t_lo, tail; int N; };
 
 // D: the series degree of the kernel (>= n).
-template <int D>
+template <int D, int ST = kThreadsOf<D>>
 struct Lds {
-    static constexpr int kST = kThreadsOf<D>;
+    static constexpr int kST = ST;
     static constexpr int kSW = kST / 64;
     static constexpr int kNPW = D > 8 ? 16 : 4;               // quadrature nodes a wave owns within a chunk
     static constexpr int kChunk = kSW * kNPW;
     static constexpr int kSer = D < 4 ? 4 : D;                // floats of one series of hser ...
     static constexpr int kSerStride = kStar * kSer + 4;      // ... and of a node's kStar of them (padded: neighbouring nodes start four banks apart)
     // support, in ratio order
-    int tok[KS]; int blk[KS]; int inT[KS]; int ordq[KS]; int apos[kMaxT];
+    int blk[KS]; int inT[KS]; int ordq[KS]; int apos[kMaxT];
     int flag[KS + 2]; int blo[KS + 2]; int star[kStar];
-    double qn[KS]; double pn[KS]; double rho[KS]; double tgt[KS]; double wgt[KS];
+    double qn[KS]; double tgt[KS]; double wgt[KS];
     double Q[KS + 1]; double F[KS + 2];
     // one convex program (the kStar tokens of largest target first, then by decreasing q)
     double aq[kMaxT]; double at[kMaxT]; double aal[kMaxT]; double aR[kMaxT];
@@ -111,11 +117,15 @@ struct Lds {
     // evaluator's records and per-wave partial sums
     union {
         struct {
-            int cnt0[KS + 2]; int cnt1[KS + 2]; int ids[KS]; int byq[KS];
-            double qd[KS]; double accb[KS];
-            double dlt[KS]; double dval[KS];   // rows given as logits: draft minus target logit, draft logit
-            double P[KS + 2]; double S[KS + 2]; double G0[KS]; double G1[KS + 2]; double O0[KS]; double O1[KS + 2];
-            unsigned long long keys[kSelCap];   // unsorted candidates (select merge)
+            int cnt0[KS + 2]; int cnt1[KS + 2]; int ids[KS]; int byq[KS]; int tok[KS];
+            double qd[KS]; double accb[KS]; double pn[KS]; double rho[KS];
+            union {
+                unsigned long long keys[kSelCap];   // unsorted candidates (select merge), until ids and accb hold the support
+                struct {
+                    double dlt[KS]; double dval[KS];   // rows given as logits: draft minus target logit, draft logit
+                    double P[KS + 2]; double S[KS + 2]; double G0[KS]; double G1[KS + 2]; double O0[KS]; double O1[KS + 2];
+                };
+            };
         };
         struct {
             double hpair[kSW][4];       // per wave: the couplings of the heavy tokens 0-1, 0-2, 1-2 (only with more than 8 drafts)
@@ -612,9 +622,9 @@ __device__ __forceinline__ double heavy_pair(const double (&T)[D + 1], const dou
 // lane's node.  The sixteen tokens that come first (the kStar, then the largest q) take all orders, the others the first (the first
 // two with more than 8 drafts): with all orders for all of them the step is no better, as their q is small.
 // `more`: the wave has been through a chunk of nodes before.
-template <int D>
-__device__ __forceinline__ void star_phase(Lds<D>& L, int lane, int wv, int m, double t, bool more) {
-    constexpr int NPW = Lds<D>::kNPW, NS = 64 / NPW, CC = D > 8 ? 2 : 1;
+template <int D, int ST>
+__device__ __forceinline__ void star_phase(Lds<D, ST>& L, int lane, int wv, int m, double t, bool more) {
+    constexpr int NPW = Lds<D, ST>::kNPW, NS = 64 / NPW, CC = D > 8 ? 2 : 1;
     static_assert(NPW == 4 || NPW == 16, "the sums over a subset's node lanes below");
     const int j = lane & (NPW - 1), tsub = lane / NPW;
     const bool b0 = j & 1, b1 = j & 2, b2 = j & 4;
@@ -622,8 +632,8 @@ __device__ __forceinline__ void star_phase(Lds<D>& L, int lane, int wv, int m, d
     const double tm = dpp_move<NPW == 4 ? kDppXor1 : kDppMirror>(t);
     const double te = upper ? tm : t;                          // the pair's even node
     wave_lds_sync();
-    float U[4][Lds<D>::kSer];
-    star_load<D>(U, &L.hser[wv][(NPW == 4 ? j >> 1 : (upper ? 15 - j : j)) * Lds<D>::kSerStride], upper);
+    float U[4][Lds<D, ST>::kSer];
+    star_load<D>(U, &L.hser[wv][(NPW == 4 ? j >> 1 : (upper ? 15 - j : j)) * Lds<D, ST>::kSerStride], upper);
     float* out = &L.cpart[wv][tsub * kStar + (upper ? 4 : 0) + (NPW == 4 ? (b1 ? 2 : 0) : (b2 ? 2 : 0) + (b0 ? 1 : 0))];
     auto row = [&](int i, auto all) {
         const TokRec<D>& rec = L.trec[NS * i + tsub];          // records beyond the last token: x = 0
@@ -666,9 +676,9 @@ __device__ __forceinline__ void star_phase(Lds<D>& L, int lane, int wv, int m, d
 // In: L.trec[] (weights and series terms), L.apd / L.nheavy / L.nfull (set up by solve_program), the grid.
 // Out: every wave's partial sums in L.rpart / L.spart / L.r0part, and in L.cpart where `couple` is set.  All waves call it
 // behind a barrier that made the weights visible; it contains no workgroup barrier itself.
-template <int D>
-__device__ __forceinline__ void eval_core_nodes(Lds<D>& L, const Grid& gr, int m, int n, double ctx, int slack, bool couple) {
-    constexpr int kSW = Lds<D>::kSW, NPW = Lds<D>::kNPW, NS = 64 / NPW;
+template <int D, int ST>
+__device__ __forceinline__ void eval_core_nodes(Lds<D, ST>& L, const Grid& gr, int m, int n, double ctx, int slack, bool couple) {
+    constexpr int kSW = Lds<D, ST>::kSW, NPW = Lds<D, ST>::kNPW, NS = 64 / NPW;
     constexpr int CL = D < 4 ? D : 4;                          // cumulants of a light token
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int nheavy = (D > 8) ? L.nheavy : 0;
@@ -761,7 +771,7 @@ __device__ __forceinline__ void eval_core_nodes(Lds<D>& L, const Grid& gr, int m
             const double tm = dpp_move<kDppMirror>(t), qm = dpp_move<kDppMirror>(tq);       // not inside the selection: every lane must be active
             const double te = upper ? tm : t, qe = upper ? qm : tq;
             const double tw = te * L.trec[a].aw;
-            float* const out = &L.hser[wv][k * Lds<D>::kSerStride + a * Lds<D>::kSer];
+            float* const out = &L.hser[wv][k * Lds<D, ST>::kSerStride + a * Lds<D, ST>::kSer];
             if (a >= nheavy) star_series<D>(Tr, L.trec[a].e, tw, qe, __expf(-static_cast<float>(fmin(tw, 1000.0))), out);
             else star_series_exact<D>(T, L.trec[a].e, tw, qe, exp_neg(tw, L.e2tab), n, out);
             // the heavy tokens' couplings among themselves: one pair per token subset
@@ -809,9 +819,9 @@ __device__ __forceinline__ void eval_core_nodes(Lds<D>& L, const Grid& gr, int m
 // by as many waves as it has nodes for.  Eight nodes a wave and chunks of 64 left no wave out and took 217 us where this takes 210
 // for a call of 256 rows of 128256 tokens (n = 8, k = 128), 660 and 634 for 1024 of them; 77 and 78 for 64 rows of 1024 (n = 4).
 // The first row's lanes hold the factors of the first kStar tokens: lane (node, tsub) takes the series of token tsub.
-template <int D>
-__device__ __forceinline__ void eval_core_rows(Lds<D>& L, const Grid& gr, int m_, int n_, double ctx, int slack_, bool couple) {
-    constexpr int NPW = Lds<D>::kNPW, NS = 64 / NPW, NT = kMaxT / NS;
+template <int D, int ST>
+__device__ __forceinline__ void eval_core_rows(Lds<D, ST>& L, const Grid& gr, int m_, int n_, double ctx, int slack_, bool couple) {
+    constexpr int NPW = Lds<D, ST>::kNPW, NS = 64 / NPW, NT = kMaxT / NS;
     constexpr int CL = D < 4 ? D : 4;
     static_assert(D <= 8 && NPW == 4 && NS >= kStar, "four node lanes per subset; the first row holds the kStar");
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -830,8 +840,8 @@ __device__ __forceinline__ void eval_core_rows(Lds<D>& L, const Grid& gr, int m_
         for (int i = lane; i < m; i += 64) { L.rpart[wv][i] = 0.0; L.spart[wv][i] = 0.0; }
         if (couple) for (int i = lane; i < m * (kStar / 4); i += 64) *reinterpret_cast<float4*>(&L.cpart[wv][4 * i]) = make_float4(0.f, 0.f, 0.f, 0.f);
     }
-    for (int c0 = NPW * wv; c0 < N; c0 += Lds<D>::kChunk) {  // this wave's first node of the chunk
-        const bool more = c0 >= Lds<D>::kChunk;             // its sums go on
+    for (int c0 = NPW * wv; c0 < N; c0 += Lds<D, ST>::kChunk) {  // this wave's first node of the chunk
+        const bool more = c0 >= Lds<D, ST>::kChunk;             // its sums go on
         const int node = c0 + j;
         const double t = t_lo * exp(kQuadStep * static_cast<double>(node));
         const double es = node < N ? exp_neg(slack * t, L.e2tab) : 0.0, qw = node_weight(node, t, t_lo) * es;
@@ -890,7 +900,7 @@ __device__ __forceinline__ void eval_core_rows(Lds<D>& L, const Grid& gr, int m_
                 for (int k = 0; k < D; ++k) Tr[k] = static_cast<float>(rec.Tr[k]);
                 if (!odd && tsub < kStar)
                     star_series<D>(Tr, L.trec[tsub].e, t * L.trec[tsub].aw, 2.0 * kQuadStep * (node == 0 ? kQuadPair : 1.0) * t * es,
-                                   static_cast<float>(xs[0]), &L.hser[wv][(j >> 1) * Lds<D>::kSerStride + tsub * Lds<D>::kSer]);
+                                   static_cast<float>(xs[0]), &L.hser[wv][(j >> 1) * Lds<D, ST>::kSerStride + tsub * Lds<D, ST>::kSer]);
             }
             double invf = qw;
 #pragma unroll
@@ -932,17 +942,17 @@ __device__ __forceinline__ void eval_core_rows(Lds<D>& L, const Grid& gr, int m_
     if (tid == 0) L.work += static_cast<double>(N) * m;
 }
 
-template <int D>
-__device__ __forceinline__ void eval_core(Lds<D>& L, const Grid& gr, int m, int n, double ctx, int slack, bool couple) {
+template <int D, int ST>
+__device__ __forceinline__ void eval_core(Lds<D, ST>& L, const Grid& gr, int m, int n, double ctx, int slack, bool couple) {
     if constexpr (D <= 8) eval_core_rows<D>(L, gr, m, n, ctx, slack, couple); else eval_core_nodes<D>(L, gr, m, n, ctx, slack, couple);
 }
 
 // The routed mass R of token `tok`, its t-weighted companion S (the share that the token loses to itself) and, with slack,
 // its coupling to the slack vertex, from the waves' partial sums (behind the barrier that follows eval_core).
 struct TokenSums { double R, S, b; };
-template <int D>
-__device__ __forceinline__ TokenSums token_sums(const Lds<D>& L, const Grid& gr, int tok, double fact) {
-    constexpr int kSW = Lds<D>::kSW;
+template <int D, int ST>
+__device__ __forceinline__ TokenSums token_sums(const Lds<D, ST>& L, const Grid& gr, int tok, double fact) {
+    constexpr int kSW = Lds<D, ST>::kSW;
     const double rfact = fast_rcp(fact);
     double r = L.apd[tok] * gr.tail * rfact, sq = 0.0;           // the integrand of S is 0 at t = 0
 #pragma unroll
@@ -956,18 +966,18 @@ __device__ __forceinline__ TokenSums token_sums(const Lds<D>& L, const Grid& gr,
     o.S = o.b * w;
     return o;
 }
-template <int D>
-__device__ __forceinline__ double slack_mass(const Lds<D>& L, const Grid& gr, int n, double atot, double fact, int slack) {
-    constexpr int kSW = Lds<D>::kSW;
+template <int D, int ST>
+__device__ __forceinline__ double slack_mass(const Lds<D, ST>& L, const Grid& gr, int n, double atot, double fact, int slack) {
+    constexpr int kSW = Lds<D, ST>::kSW;
     double r0all = 0.0;
 #pragma unroll
     for (int w2 = 0; w2 < kSW; ++w2) r0all += L.r0part[w2];
     return (r0all * fact + ipow(atot, n) * gr.tail) * slack;
 }
 // The couplings of token `tok` to four of the kStar tokens (half: 0 or 1), times `scale`, into its row; none to itself.
-template <int D>
-__device__ __forceinline__ void token_couplings(Lds<D>& L, const Grid& gr, int tok, int half, double scale) {
-    constexpr int kSW = Lds<D>::kSW;
+template <int D, int ST>
+__device__ __forceinline__ void token_couplings(Lds<D, ST>& L, const Grid& gr, int tok, int half, double scale) {
+    constexpr int kSW = Lds<D, ST>::kSW;
     float c[4] = {0.f, 0.f, 0.f, 0.f};
     if (D > 8 && tok < L.nheavy) {
         // the other token's row, or the heavy pair's own sum
@@ -995,8 +1005,8 @@ __device__ __forceinline__ void token_couplings(Lds<D>& L, const Grid& gr, int t
 // Workgroup-wide evaluation (the Newton fallback's): every thread passes the log weight of its own token and gets
 // that token's routed mass back (also left in L.aR); returns the slack mass.  All threads call it.
 struct Routed { double R0, R, S; };
-template <int D>
-__device__ __forceinline__ Routed routed_eval(Lds<D>& L, int& par, int m, int n, double ctx, int slack, double qsum, double fact, double alpha) {
+template <int D, int ST>
+__device__ __forceinline__ Routed routed_eval(Lds<D, ST>& L, int& par, int m, int n, double ctx, int slack, double qsum, double fact, double alpha) {
     const int tid = threadIdx.x;
     double w = 0.0;
     if (tid < m) { w = exp(alpha); L.trec[tid].aw = w; }
@@ -1018,8 +1028,8 @@ __device__ __forceinline__ Routed routed_eval(Lds<D>& L, int& par, int m, int n,
 // (the latter is zero in exact arithmetic and removes the common quadrature error).  Per-token quantities are
 // those of the calling thread's token: alpha and target in, f = log(target / routed) - common term, R and S out.
 struct Defect { double err, f, R, S, rsum, R0; };
-template <int D>
-__device__ __forceinline__ Defect defect_eval(Lds<D>& L, int& par, int m, int n, double ctx, int slack, double slack_target, double qsum,
+template <int D, int ST>
+__device__ __forceinline__ Defect defect_eval(Lds<D, ST>& L, int& par, int m, int n, double ctx, int slack, double slack_target, double qsum,
                                               double tsum, double fact, double alpha, double target) {
     const int tid = threadIdx.x;
     Defect d;
@@ -1050,10 +1060,10 @@ __device__ __forceinline__ Defect defect_eval(Lds<D>& L, int& par, int m, int n,
 // is pinned (the system is singular along the common shift).  Starts from L.aal.
 // J: this row's scratch in HBM, kMaxT rows of kMaxT + 1 doubles (the last column is the right-hand side).
 // The cap counts the evaluations of this program only (`evals0` = the row's count when the program began).
-template <int D>
-__device__ int newton_program(Lds<D>& L, int& par, double* J, int m, int n, double ctx, int slack, double slack_target, double qsum,
+template <int D, int ST>
+__device__ int newton_program(Lds<D, ST>& L, int& par, double* J, int m, int n, double ctx, int slack, double slack_target, double qsum,
                               double tsum, double fact, double rel_tol, int max_evals, int* evals, int evals0) {
-    constexpr int kSW = Lds<D>::kSW;
+    constexpr int kSW = Lds<D, ST>::kSW;
     const int tid = threadIdx.x;
     const int nfree = slack ? m : m - 1;
     constexpr int LD = kMaxT + 1;
@@ -1163,10 +1173,10 @@ __device__ int newton_program(Lds<D>& L, int& par, double* J, int m, int n, doub
 struct StepState { int since, retreats, havePrev, held; double best_err; };
 constexpr int kPlainly = 16;
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-template <int D>
+template <int D, int ST>
 __device__ __attribute__((noinline)) StepState newton_step(StepState st, int m, int n, int slack, double ctx, double slack_target, double tsum,
                                                            double rel_tol, int evals, int evals0) {
-    Lds<D>& L = *reinterpret_cast<Lds<D>*>(gr_lds_raw);
+    Lds<D, ST>& L = *reinterpret_cast<Lds<D, ST>*>(gr_lds_raw);
     const int tid = threadIdx.x, lane = tid & 63;
     const bool two = m > 64;                               // uniform: lane l holds tokens l and l + 64
     const int tk[2] = {lane, lane + 64};
@@ -1407,10 +1417,10 @@ __device__ __attribute__((noinline)) StepState newton_step(StepState st, int m, 
 // written by the thread of their token; qsum = sum aq, tsum = sum at.
 // Out: L.aal, L.apos, in the program's own order of tokens.  `evals` counts evaluator calls (summed over the row's programs;
 // max_iter caps this program's).
-template <int D>
-__device__ __forceinline__ int solve_program(Lds<D>& L, int& par, double* newton_ws, int m, int n, double ctx, int slack, double slack_target,
+template <int D, int ST>
+__device__ __forceinline__ int solve_program(Lds<D, ST>& L, int& par, double* newton_ws, int m, int n, double ctx, int slack, double slack_target,
                              double qsum, double tsum, double rel_tol, int max_iter, int* evals) {
-    constexpr int kST = Lds<D>::kST;
+    constexpr int kST = Lds<D, ST>::kST;
     const int tid = threadIdx.x;
     const int evals0 = *evals;
     if (n == 1) {
@@ -1576,7 +1586,7 @@ __device__ __forceinline__ int solve_program(Lds<D>& L, int& par, double* newton
         }
         __syncthreads();
         if (wvi != 0) continue;
-        st = newton_step<D>(st, m, n, slack, ctx, slack_target, tsum, rel_tol, *evals, evals0);
+        st = newton_step<D, ST>(st, m, n, slack, ctx, slack_target, tsum, rel_tol, *evals, evals0);
     }
     __syncthreads();
     int result = L.ctl_result;
@@ -1615,10 +1625,10 @@ __device__ int compact_active(LdsT& L, int lo, int hi, int kk) {
 
 }  // namespace
 
-template <int D>
-__global__ __launch_bounds__(kThreadsOf<D>) void solve_kernel(SolveParams sp) {
-    constexpr int kST = Lds<D>::kST, kSW = Lds<D>::kSW;
-    Lds<D>& L = *reinterpret_cast<Lds<D>*>(gr_lds_raw);
+template <int D, int ST>
+__global__ __launch_bounds__(ST, kWavesOf<D>) void solve_kernel(SolveParams sp) {
+    constexpr int kST = Lds<D, ST>::kST, kSW = Lds<D, ST>::kSW;
+    Lds<D, ST>& L = *reinterpret_cast<Lds<D, ST>*>(gr_lds_raw);
     const int tid = threadIdx.x;
     const int row = blockIdx.x;
     const int n = sp.row_n ? sp.row_n[row] : sp.n, V = sp.V;
@@ -1892,6 +1902,14 @@ __global__ __launch_bounds__(kThreadsOf<D>) void solve_kernel(SolveParams sp) {
     __syncthreads();
 
     GR_CLK(L, 3);
+    // ---- policy object; the programs' records take the place of all this
+    int* o_order = sp.order + static_cast<size_t>(row) * KS;
+    int* o_block = sp.block + static_cast<size_t>(row) * KS;
+    double* o_w = sp.weight + static_cast<size_t>(row) * KS;
+    double* o_rho = sp.rho + static_cast<size_t>(row) * KS;
+    double* o_pn = sp.pnorm + static_cast<size_t>(row) * KS;
+    if (tid < kk) { o_order[tid] = L.tok[tid]; o_block[tid] = L.blk[tid]; o_rho[tid] = L.rho[tid]; o_pn[tid] = L.pn[tid]; }
+
     // ---- the convex programs: program 0 = inner system, then every outer block of two or more tokens
     int status = GR_ROW_OK, evals = 0, par = 0;
     for (int b = (h > 0 ? 0 : 1); b <= nblk && status != GR_ROW_TRUNC_CAP; ++b) {
@@ -1934,16 +1952,7 @@ __global__ __launch_bounds__(kThreadsOf<D>) void solve_kernel(SolveParams sp) {
         __syncthreads();
     }
 
-    // ---- policy object
-    int* o_order = sp.order + static_cast<size_t>(row) * KS;
-    int* o_block = sp.block + static_cast<size_t>(row) * KS;
-    double* o_w = sp.weight + static_cast<size_t>(row) * KS;
-    double* o_rho = sp.rho + static_cast<size_t>(row) * KS;
-    double* o_pn = sp.pnorm + static_cast<size_t>(row) * KS;
-    if (tid < kk) {
-        o_order[tid] = L.tok[tid]; o_block[tid] = L.blk[tid]; o_w[tid] = L.wgt[tid];
-        o_rho[tid] = L.rho[tid]; o_pn[tid] = L.pn[tid];
-    }
+    if (tid < kk) o_w[tid] = L.wgt[tid];
     info.support = kk; info.h = h; info.status = status; info.iterations = evals;
     info.alpha_star = 1.0 + L.F[h];
     info.res_total = -L.F[h];
@@ -1966,7 +1975,7 @@ __global__ __launch_bounds__(kThreadsOf<D>) void solve_kernel(SolveParams sp) {
         rp.o = o_order; rp.bl = o_block; rp.wt = o_w; rp.rh = o_rho; rp.rk = nullptr; rp.rid = nullptr;
         rp.pieces = sp.piece_psum ? sp.piece_psum + static_cast<size_t>(row) * sp.piece_stride : nullptr;
         rp.prefs = sp.piece_pref ? sp.piece_pref + static_cast<size_t>(row) * sp.piece_stride : nullptr;
-        static_assert(sizeof(VerifyLds) <= sizeof(Lds<D>), "the verification reuses the solve's LDS");
+        static_assert(sizeof(VerifyLds) <= sizeof(Lds<D, ST>), "the verification reuses the solve's LDS");
         verify_row(*reinterpret_cast<VerifyLds*>(gr_lds_raw), prow, V, n, rp, info,
                    sp.v_drafts + static_cast<size_t>(row) * sp.v_stride, sp.v_uniforms[row], sp.v_token + row, sp.v_accepted + row);
     }
@@ -1975,10 +1984,10 @@ __global__ __launch_bounds__(kThreadsOf<D>) void solve_kernel(SolveParams sp) {
 // ---- full-vocabulary policies: the convex programs of a row whose steps 1-2 were done in HBM: the
 // inner program over T inside H* and one outer program per block that holds two or more active
 // tokens of T -- the same programs, in the same arithmetic, as the LDS-resident path.
-template <int D>
-__global__ __launch_bounds__(kThreadsOf<D>) void full_programs_kernel(FullParams fp) {
-    constexpr int kST = Lds<D>::kST, kSW = Lds<D>::kSW;
-    Lds<D>& L = *reinterpret_cast<Lds<D>*>(gr_lds_raw);
+template <int D, int ST>
+__global__ __launch_bounds__(ST, kWavesOf<D>) void full_programs_kernel(FullParams fp) {
+    constexpr int kST = Lds<D, ST>::kST, kSW = Lds<D, ST>::kSW;
+    Lds<D, ST>& L = *reinterpret_cast<Lds<D, ST>*>(gr_lds_raw);
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, row = blockIdx.x;
     const int n = fp.n, V = fp.V;
     const size_t vs = static_cast<size_t>(V) + 2;
@@ -2093,43 +2102,48 @@ __global__ __launch_bounds__(kThreadsOf<D>) void full_programs_kernel(FullParams
     }
 }
 
+// The kernel of the series degree D >= n (2, 4, 8, 16), so that each keeps its series in registers, and of the workgroup that suits the batch.
+enum { kSolve, kPrograms };
+template <int D, int ST> const void* kernel_of(int which) {
+    return which == kSolve ? reinterpret_cast<const void*>(solve_kernel<D, ST>) : reinterpret_cast<const void*>(full_programs_kernel<D, ST>);
+}
+struct Chosen { const void* kernel; int threads, lds; };
+template <int D, int ST> Chosen chosen(int which) { return Chosen{kernel_of<D, ST>(which), ST, static_cast<int>(sizeof(Lds<D, ST>))}; }
+static Chosen choose(int which, int n, bool narrow) {
+    if (n <= 2) return narrow ? chosen<2, kNarrow>(which) : chosen<2, kThreadsOf<2>>(which);
+    if (n <= 4) return narrow ? chosen<4, kNarrow>(which) : chosen<4, kThreadsOf<4>>(which);
+    if (n <= 8) return narrow ? chosen<8, kNarrow>(which) : chosen<8, kThreadsOf<8>>(which);
+    return chosen<16, kThreadsOf<16>>(which);
+}
+
 hipError_t launch_full_programs(const FullParams& fp, hipStream_t stream) {
-    const dim3 grid(fp.B);
-    if (fp.n <= 2) hipLaunchKernelGGL(full_programs_kernel<2>, grid, dim3(kThreadsOf<2>), sizeof(Lds<2>), stream, fp);
-    else if (fp.n <= 4) hipLaunchKernelGGL(full_programs_kernel<4>, grid, dim3(kThreadsOf<4>), sizeof(Lds<4>), stream, fp);
-    else if (fp.n <= 8) hipLaunchKernelGGL(full_programs_kernel<8>, grid, dim3(kThreadsOf<8>), sizeof(Lds<8>), stream, fp);
-    else hipLaunchKernelGGL(full_programs_kernel<16>, grid, dim3(kThreadsOf<16>), sizeof(Lds<16>), stream, fp);
-    return hipGetLastError();
+    const Chosen c = choose(kPrograms, fp.n, fp.B > kChip);
+    void* args[] = {const_cast<FullParams*>(&fp)};
+    return hipLaunchKernel(c.kernel, dim3(fp.B), dim3(c.threads), args, c.lds, stream);
 }
 
 static_assert(sizeof(Lds<16>) + 20 * 1024 <= 160 * 1024,
               "the solve workgroup's state and one streaming workgroup of the next batch must fit the CU's LDS together");
+static_assert(sizeof(Lds<8, kNarrow>) <= 80 * 1024 && sizeof(Lds<4, kNarrow>) <= 80 * 1024 && sizeof(Lds<2, kNarrow>) <= 80 * 1024, "two to a compute unit");
 
-// The kernels that a handle of up to max_n drafts can launch; hbm: those of supports above kMaxSupport too.  (A handle for one row,
-// its inputs and its drafts: 353 us with these eight kernels, 407 with those of full_kernel_setup as well, in every gr_create.)
-hipError_t solve_kernel_setup(int max_n, bool hbm) {
-    const void* kernels[8] = {reinterpret_cast<const void*>(solve_kernel<2>), reinterpret_cast<const void*>(solve_kernel<4>),
-                              reinterpret_cast<const void*>(solve_kernel<8>), reinterpret_cast<const void*>(solve_kernel<16>),
-                              reinterpret_cast<const void*>(full_programs_kernel<2>), reinterpret_cast<const void*>(full_programs_kernel<4>),
-                              reinterpret_cast<const void*>(full_programs_kernel<8>), reinterpret_cast<const void*>(full_programs_kernel<16>)};
-    const size_t sizes[8] = {sizeof(Lds<2>), sizeof(Lds<4>), sizeof(Lds<8>), sizeof(Lds<16>),
-                             sizeof(Lds<2>), sizeof(Lds<4>), sizeof(Lds<8>), sizeof(Lds<16>)};
-    for (int i = 0; i < (hbm ? 8 : 4); ++i) {
-        if ((1 << (i & 3)) >= max_n && (i & 3) > 0) continue;              // series degree 2 << (i & 3); half of it serves max_n
-        const hipError_t e = hipFuncSetAttribute(kernels[i], hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(sizes[i]));
-        if (e != hipSuccess) return e;
-    }
+// The kernels that a handle of up to max_n drafts and max_B rows can launch; hbm: those of supports above kMaxSupport too.  (A handle for one row,
+// its inputs and its drafts: 353 us with eight kernels, 407 with two more, in every gr_create.)
+hipError_t solve_kernel_setup(int max_n, int max_B, bool hbm) {
+    for (int which = kSolve; which <= (hbm ? kPrograms : kSolve); ++which)
+        for (int narrow = 0; narrow <= (max_B > kChip ? 1 : 0); ++narrow)
+            for (int n = 2; n <= GR_MAX_N && n < 2 * max_n; n *= 2) {
+                if (narrow && n > 8) continue;
+                const Chosen c = choose(which, n, narrow != 0);
+                const hipError_t e = hipFuncSetAttribute(c.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, c.lds);
+                if (e != hipSuccess) return e;
+            }
     return hipSuccess;
 }
 
-// One kernel per series degree D >= n (2, 4, 8, 16), so that each keeps its series in registers.
 hipError_t launch_solve(const SolveParams& sp, hipStream_t stream) {
-    const dim3 grid(sp.B);
-    if (sp.n <= 2) hipLaunchKernelGGL(solve_kernel<2>, grid, dim3(kThreadsOf<2>), sizeof(Lds<2>), stream, sp);
-    else if (sp.n <= 4) hipLaunchKernelGGL(solve_kernel<4>, grid, dim3(kThreadsOf<4>), sizeof(Lds<4>), stream, sp);
-    else if (sp.n <= 8) hipLaunchKernelGGL(solve_kernel<8>, grid, dim3(kThreadsOf<8>), sizeof(Lds<8>), stream, sp);
-    else hipLaunchKernelGGL(solve_kernel<16>, grid, dim3(kThreadsOf<16>), sizeof(Lds<16>), stream, sp);
-    return hipGetLastError();
+    const Chosen c = choose(kSolve, sp.n, sp.B > kChip);
+    void* args[] = {const_cast<SolveParams*>(&sp)};
+    return hipLaunchKernel(c.kernel, dim3(sp.B), dim3(c.threads), args, c.lds, stream);
 }
 
 }  // namespace gr

@@ -108,3 +108,36 @@ def test_rows_given_as_logits():
         for name, a, b in zip(("accept_prob", "status", "token", "accepted"), two, one):
             assert torch.equal(a.view(torch.int32) if name == "accept_prob" else a, b.view(torch.int32) if name == "accept_prob" else b), name
         assert int((one[1] == 0).sum()) >= wl.B // 2 and int((one[2] >= 0).sum()) >= wl.B // 2
+
+
+@pytest.mark.parametrize("n,k,V,logits", [(1, 20, 300, False), (2, 256, 600, False), (3, 33, 1024, True), (4, 64, 1025, False), (5, 200, 700, False),
+                                          (8, 128, 2000, True), (8, 9, 333, False)])
+def test_batches_on_both_workgroup_sizes(n, k, V, logits):
+    """Batches of more rows than the chip has compute units run two smaller workgroups to a unit: the same rows in one batch of 270 and in
+    halves.  The routed masses are summed over other waves, so programs agree to their stopping measure (1e-8), far inside 1e-6."""
+    import torch
+    from paper_2511_15898_amd import binding as gr
+    B = 270
+    wl = W.llm_shaped(B=B, V=V, n=n, k=k, temperature=(0.5, 1.5), near_identical_frac=0.2, seed_sub=2000 + V)
+    dev = torch.device("cuda:0")
+    p, q = torch.from_numpy(wl.p).to(dev), torch.from_numpy(wl.q).to(dev)
+    drafts, u = torch.from_numpy(wl.drafts).to(dev), torch.from_numpy(wl.uniforms).to(dev)
+    temp = torch.ones(B, device=dev)
+    h = gr.gr_create(B, V, max_k=k, max_n=n)
+    def run(rows):
+        if logits:
+            gr.gr_solve_logits(h, p[rows].log().contiguous(), q[rows].log().contiguous(), temp[rows], n, k, 1e-4)
+        else:
+            gr.gr_solve(h, p[rows].contiguous(), q[rows].contiguous(), n, k, 1e-4)
+        pi, given = gr.gr_policy_slice(h, drafts[rows].contiguous(), V)
+        one = (gr.gr_solve_verify(h, p[rows].contiguous(), q[rows].contiguous(), n, k, 1e-4, drafts[rows].contiguous(), u[rows].contiguous()))
+        return (pi, given) + tuple(one)
+    try:
+        whole = [x.cpu().numpy() for x in run(slice(0, B))]
+        halves = [np.concatenate([a.cpu().numpy(), b.cpu().numpy()]) for a, b in zip(run(slice(0, 135)), run(slice(135, B)))]
+    finally:
+        gr.gr_destroy(h)
+    pi, given, acc, st, tok, ok = zip(whole, halves)
+    assert np.array_equal(*st) and np.array_equal(*acc)
+    assert np.abs(pi[0] - pi[1]).max() < 1e-6 and np.abs(given[0] - given[1]).max() < 1e-6
+    assert (tok[0] != tok[1]).sum() <= 1 and (ok[0] != ok[1]).sum() <= 1      # a uniform on an edge
