@@ -220,6 +220,8 @@ int fill_sweep(SweepParams& sw, const int* ks, int nk, const int* ns, int nn, in
         if (ns[i] < 1 || ns[i] > kSweepMaxDrafts) return GR_EINVAL;
         sw.ns[i] = ns[i];
     }
+    sw.nmask = 0;
+    for (int i = 0; i < nn; ++i) sw.nmask |= 1ull << (ns[i] - 1);
     if (sw.kmax > V) sw.kmax = V;                        // a top-k of V or more keeps every positive entry
     for (int i = nk; i < kSweepMaxK; ++i) sw.ks[i] = 0;
     for (int i = nn; i < kSweepMaxN; ++i) sw.ns[i] = 1;

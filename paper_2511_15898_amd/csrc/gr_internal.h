@@ -134,6 +134,7 @@ struct SweepParams {
     const double* part_psum; const double* part_qsum; const int* part_bad;
     int kmax, nk, nn;
     int ks[kSweepMaxK]; int ns[kSweepMaxN];
+    unsigned long long nmask;     // bit n - 1: n is among the draft counts
     float* accept_prob;           // [B, nk, nn]
     int* status;                  // [B]
 };
