@@ -90,16 +90,24 @@ template <int D> struct alignas(16) NodeRec { double t, qw; double Tr[D]; };    
 // The quadrature grid of one evaluation: nodes t_lo e^{kQuadStep j}, j = 0..N-1, and the weight of the integrand's value at 0.
 struct Grid { double t_lo, tail; int N; };
 
+// What the policy object holds of a rank beside its block and weight.  Where there is room it stays in LDS to the end of the row; two workgroups to a compute
+// unit write it out before the programs, whose first barrier then waits for these stores (0.4 % of a call of 256 rows).
+struct PolicyRows { int tok[KS]; double pn[KS]; double rho[KS]; };
+struct Nothing {};
+
 // D: the series degree of the kernel (>= n).
 template <int D, int ST = kThreadsOf<D>>
 struct Lds {
     static constexpr int kST = ST;
+    static constexpr bool kKeeps = !(D <= 8 && ST == kNarrow);
     static constexpr int kSW = kST / 64;
     static constexpr int kNPW = D > 8 ? 16 : 4;               // quadrature nodes a wave owns within a chunk
     static constexpr int kChunk = kSW * kNPW;
     static constexpr int kSer = D < 4 ? 4 : D;                // floats of one series of hser ...
     static constexpr int kSerStride = kStar * kSer + 4;      // ... and of a node's kStar of them (padded: neighbouring nodes start four banks apart)
     // support, in ratio order
+    std::conditional_t<kKeeps, PolicyRows, Nothing> kept;
+    __device__ PolicyRows& rows() { if constexpr (kKeeps) return kept; else return early; }
     int blk[KS]; int inT[KS]; int ordq[KS]; int apos[kMaxT];
     int flag[KS + 2]; int blo[KS + 2]; int star[kStar];
     double qn[KS]; double tgt[KS]; double wgt[KS];
@@ -117,8 +125,8 @@ struct Lds {
     // evaluator's records and per-wave partial sums
     union {
         struct {
-            int cnt0[KS + 2]; int cnt1[KS + 2]; int ids[KS]; int byq[KS]; int tok[KS];
-            double qd[KS]; double accb[KS]; double pn[KS]; double rho[KS];
+            int cnt0[KS + 2]; int cnt1[KS + 2]; int ids[KS]; int byq[KS];
+            double qd[KS]; double accb[KS]; std::conditional_t<kKeeps, Nothing, PolicyRows> early;
             union {
                 unsigned long long keys[kSelCap];   // unsorted candidates (select merge), until ids and accb hold the support
                 struct {
@@ -1768,16 +1776,16 @@ __global__ __launch_bounds__(ST, kWavesOf<D>) void solve_kernel(SolveParams sp) 
         __syncthreads();
         if (tid < kk) {
             const int rank = L.cnt0[tid];
-            L.tok[rank] = L.ids[tid]; L.qd[rank] = L.accb[tid]; L.pn[rank] = L.G0[tid] / ptot;
+            L.rows().tok[rank] = L.ids[tid]; L.qd[rank] = L.accb[tid]; L.rows().pn[rank] = L.G0[tid] / ptot;
             L.byq[L.cnt1[tid]] = rank;                    // the token of q rank j sits at ratio rank byq[j]
-        } else if (tid < padded(kk)) { L.pn[tid] = 0.0; L.qd[tid] = 0.0; }
+        } else if (tid < padded(kk)) { L.rows().pn[tid] = 0.0; L.qd[tid] = 0.0; }
         __syncthreads();
     }
     GR_CLK(L, 1);
     // ---- prefix sums in the order, sequentially (bit-reproducible), then F(m) = P_m - Q_m^n
     {
 #pragma clang fp contract(off)
-        if ((tid >> 6) == 0) wave_sequential_scan_padded<kScan>(L.pn, L.P, kk, 0.0);
+        if ((tid >> 6) == 0) wave_sequential_scan_padded<kScan>(L.rows().pn, L.P, kk, 0.0);
         if ((tid >> 6) == 1) wave_sequential_scan_padded<kScan>(L.qd, L.S, kk, 0.0);
         __syncthreads();
         const double stot = L.S[kk];
@@ -1826,7 +1834,7 @@ __global__ __launch_bounds__(ST, kWavesOf<D>) void solve_kernel(SolveParams sp) 
                 L.flag[m] = fl[e];
                 if (m < kk) {
                     const double r = (m >= hh) ? gn - g : 0.0;
-                    L.rho[m] = r; L.tgt[m] = L.pn[m] - r;
+                    L.rows().rho[m] = r; L.tgt[m] = L.rows().pn[m] - r;
                 }
             }
             run += fl[e]; cl[e] = run;
@@ -1902,13 +1910,12 @@ __global__ __launch_bounds__(ST, kWavesOf<D>) void solve_kernel(SolveParams sp) 
     __syncthreads();
 
     GR_CLK(L, 3);
-    // ---- policy object; the programs' records take the place of all this
-    int* o_order = sp.order + static_cast<size_t>(row) * KS;
-    int* o_block = sp.block + static_cast<size_t>(row) * KS;
-    double* o_w = sp.weight + static_cast<size_t>(row) * KS;
-    double* o_rho = sp.rho + static_cast<size_t>(row) * KS;
-    double* o_pn = sp.pnorm + static_cast<size_t>(row) * KS;
-    if (tid < kk) { o_order[tid] = L.tok[tid]; o_block[tid] = L.blk[tid]; o_rho[tid] = L.rho[tid]; o_pn[tid] = L.pn[tid]; }
+    // ---- policy object, but for the weights
+    auto write_rows = [&]() {
+        const size_t at = static_cast<size_t>(row) * KS + tid;
+        if (tid < kk) { sp.order[at] = L.rows().tok[tid]; sp.block[at] = L.blk[tid]; sp.rho[at] = L.rows().rho[tid]; sp.pnorm[at] = L.rows().pn[tid]; }
+    };
+    if constexpr (!Lds<D, ST>::kKeeps) write_rows();
 
     // ---- the convex programs: program 0 = inner system, then every outer block of two or more tokens
     int status = GR_ROW_OK, evals = 0, par = 0;
@@ -1952,7 +1959,8 @@ __global__ __launch_bounds__(ST, kWavesOf<D>) void solve_kernel(SolveParams sp) 
         __syncthreads();
     }
 
-    if (tid < kk) o_w[tid] = L.wgt[tid];
+    if constexpr (Lds<D, ST>::kKeeps) write_rows();
+    if (tid < kk) sp.weight[static_cast<size_t>(row) * KS + tid] = L.wgt[tid];
     info.support = kk; info.h = h; info.status = status; info.iterations = evals;
     info.alpha_star = 1.0 + L.F[h];
     info.res_total = -L.F[h];
@@ -1972,7 +1980,8 @@ __global__ __launch_bounds__(ST, kWavesOf<D>) void solve_kernel(SolveParams sp) 
         __syncthreads();
         if (tid >= kThreads) __builtin_amdgcn_endpgm();
         RowPolicy rp;
-        rp.o = o_order; rp.bl = o_block; rp.wt = o_w; rp.rh = o_rho; rp.rk = nullptr; rp.rid = nullptr;
+        const size_t at = static_cast<size_t>(row) * KS;
+        rp.o = sp.order + at; rp.bl = sp.block + at; rp.wt = sp.weight + at; rp.rh = sp.rho + at; rp.rk = nullptr; rp.rid = nullptr;
         rp.pieces = sp.piece_psum ? sp.piece_psum + static_cast<size_t>(row) * sp.piece_stride : nullptr;
         rp.prefs = sp.piece_pref ? sp.piece_pref + static_cast<size_t>(row) * sp.piece_stride : nullptr;
         static_assert(sizeof(VerifyLds) <= sizeof(Lds<D, ST>), "the verification reuses the solve's LDS");
