@@ -901,7 +901,8 @@ __global__ __launch_bounds__(kBucketThreads, 8) void full_bucket_kernel(FullPara
 // Descending: F, its suffix minima G, residuals, records (F(m) <= G(m + 1); m = kk always) and the number of records behind
 // every rank, in one pass: below H* the suffix minimum is F(h) throughout, so residuals and records there come out 0 and none,
 // and h is the first record.
-// Bound: memory (52 bytes per token) and the two passes' barriers.
+// Bound: memory (44 bytes per token: most tiles hold no record, and their ranks' blocks are written once, when the records are counted) and the two
+// passes' barriers.  1024 rows of 128256 tokens: 2110 us with every rank's block written twice, 1900 now.
 // One wave adding for each sum from LDS, and P, Q, F, the targets and the records' flags as arrays of their own: 9.5 ms for
 // 1024 rows of 128256 tokens, 3.06 for 256.
 __global__ __launch_bounds__(kScanThreads, 4) void full_scan_kernel(FullParams fp) {
@@ -925,6 +926,7 @@ __global__ __launch_bounds__(kScanThreads, 4) void full_scan_kernel(FullParams f
     const float2* by_rank = fp.pairs + row * vs;
     double* P = fp.P + row * vs; double* Q = fp.Q + row * vs; double* rho = fp.rho + row * vs;
     int* blk = fp.blk + row * vs; int* blo = fp.blo + row * vs; int* bcount = fp.bcount + row * vs; int* behind = fp.val0 + row * vs;
+    int* tile_rec = fp.flag + row * vs;                        // per tile: the records behind all of its ranks, -1 where it holds one itself
     auto pad = [](int i) { return i + (i >> 3); };
 
     const int chain = wv / CW, cw = wv % CW;
@@ -1071,20 +1073,27 @@ __global__ __launch_bounds__(kScanThreads, 4) void full_scan_kernel(FullParams f
         const int ci = wave_scan_i(cnt);
         if (lane == 63) wcnt[b][wv] = ci;
         __syncthreads();
-        int c = nrec + ci - cnt;                               // records behind this thread's ranks
+        int c = nrec + ci - cnt, here = 0;                     // records behind this thread's ranks, and in this tile
 #pragma unroll
-        for (int w = 0; w < NW; ++w) { const int x = wcnt[b][w]; if (w < wv) c += x; nrec += x; }
+        for (int w = 0; w < NW; ++w) { const int x = wcnt[b][w]; if (w < wv) c += x; here += x; }
+        if (tid == 0) tile_rec[t] = here ? -1 : nrec;
+        if (here)
 #pragma unroll
-        for (int j = PER - 1; j >= 0; --j) {
-            const int m = m0 + j;
-            if (m < kk) blk[m] = c;                            // for now the records behind token m
-            if (rec[j]) { behind[c] = m; ++c; }
-        }
+            for (int j = PER - 1; j >= 0; --j) {
+                const int m = m0 + j;
+                if (m < kk) blk[m] = c;                        // for now the records behind token m
+                if (rec[j]) { behind[c] = m; ++c; }
+            }
+        nrec += here;
         later = fmin(later, total);
     }
     __syncthreads();
     // records in rising order, and every token's block: the records up to its rank
-    for (int m = tid; m < kk; m += NT) blk[m] = nrec - blk[m];
+    for (int t = 0; t < ntile; ++t) {
+        const int c = tile_rec[t];
+#pragma unroll
+        for (int j = 0; j < PER; ++j) { const int m = t * kTile + j * NT + tid; if (m < kk) blk[m] = nrec - (c < 0 ? blk[m] : c); }
+    }
     for (int i = tid; i <= nrec; i += NT) { bcount[i] = 0; if (i > 0) blo[i] = behind[nrec - i]; }
     if (tid == 0) {
 #pragma clang fp contract(off)
