@@ -2140,7 +2140,7 @@ static_assert(sizeof(Lds<8, kNarrow>) <= 80 * 1024 && sizeof(Lds<4, kNarrow>) <=
 hipError_t solve_kernel_setup(int max_n, int max_B, bool hbm) {
     for (int which = kSolve; which <= (hbm ? kPrograms : kSolve); ++which)
         for (int narrow = 0; narrow <= (max_B > kChip ? 1 : 0); ++narrow)
-            for (int n = 2; n <= GR_MAX_N && n < 2 * max_n; n *= 2) {
+            for (int n = 2; n <= GR_MAX_N && (n == 2 || n < 2 * max_n); n *= 2) {   // n: the series degrees that serve up to max_n
                 if (narrow && n > 8) continue;
                 const Chosen c = choose(which, n, narrow != 0);
                 const hipError_t e = hipFuncSetAttribute(c.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, c.lds);

@@ -10,6 +10,8 @@ enum { kFunctions = 256, kLog = 1 << 16 };
 static const void* functions[kFunctions];
 static const char* names[kFunctions];
 static int function_count;
+static size_t allowed[kFunctions];                     /* dynamic LDS, as hipFuncSetAttribute set it */
+static int over;                                       /* launches with more than 64 KB and more than was set */
 static char log_[kLog];
 static size_t log_used;
 static char fail_name[64];
@@ -47,13 +49,19 @@ int __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, void** strea
     return 0;
 }
 int hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, size_t lds, void* stream) {
-    (void)grid; (void)block; (void)args; (void)lds; (void)stream;
-    for (int i = 0; i < function_count; ++i) if (functions[i] == f) return note("launch", names[i]);
+    (void)grid; (void)block; (void)args; (void)stream;
+    for (int i = 0; i < function_count; ++i)
+        if (functions[i] == f) { over += lds > 65536 && lds > allowed[i]; return note("launch", names[i]); }
     return note("launch", "?");
 }
 int hipGetLastError(void) { return 0; }
 int hipGetDevice(int* device) { *device = 0; return 0; }
-int hipFuncSetAttribute(const void* f, int attribute, int value) { (void)f; (void)attribute; (void)value; return 0; }
+int recorded_over(void) { return over; }
+int hipFuncSetAttribute(const void* f, int attribute, int value) {
+    (void)attribute;
+    for (int i = 0; i < function_count; ++i) if (functions[i] == f) allowed[i] = (size_t)value;
+    return 0;
+}
 int hipGetSymbolAddress(void** p, const void* symbol) { (void)symbol; *p = log_; return 0; }
 int hipMalloc(void** p, size_t size) { *p = calloc(1, size); return *p ? note("malloc", "") : 2; }
 int hipFree(void* p) { free(p); return 0; }

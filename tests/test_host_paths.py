@@ -102,3 +102,23 @@ result["log"] = log()
 """)
     assert r["rc"] == 0 and all(line.startswith("launch ") for line in r["log"]), r
     assert len(r["log"]) == launches, r["log"]
+
+
+@pytest.mark.parametrize("max_n", [1, 2, 3, 5, 16])
+@pytest.mark.parametrize("B", [1, 264, 265])
+def test_a_handle_sets_up_the_kernels_that_its_calls_launch(recorded, max_n, B):
+    """A kernel with more than 64 KB of dynamic LDS needs its limit raised on the device: for every draft count of the handle, batches on
+    both workgroup sizes, supports in LDS and in HBM, grids, and walks whose batches hold more rows than the handle."""
+    r = recorded(f"""
+h = create({B}, 600, 0, {max_n})
+for n in range(1, {max_n} + 1):
+    for k in (20, 300):
+        assert solve(h, {B}, 600, n, k) == 0 and verify(h, {B}) == 0
+assert sweep(h, {B}, 600, [10, 0], [1, 2]) == 0
+if {B} == 264:
+    paths = (C.c_int * (264 * {max_n} * 2))(*[i % 7 for i in range(264 * {max_n} * 2)])
+    rows, ints = buffer(264 * {max_n} * 600 + 1), [(C.c_int * 528)() for _ in range(4)]
+    assert lib.gr_tree_walk(h, rows, rows, None, paths, (C.c_float * 528)(), 240, {max_n}, 2, 600, 20, C.c_float(1e-4), *ints, None) == 0
+result["over"] = hip.recorded_over()
+""")
+    assert r["over"] == 0
