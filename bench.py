@@ -125,7 +125,7 @@ def bench_sweep(args):
         "config": {"workload": f"sweep on {wl.name}: B={wl.B} rows x V={wl.V} vocab, top-k in {ks}, drafts in {ns}",
                    "B": wl.B, "V": wl.V, "ks": ks, "ns": ns, "cells_per_row": len(ks) * len(ns)},
         "status_histogram": [int(x) for x in np.bincount(st.cpu().numpy(), minlength=4)],
-        "roofline": {"bound": "hbm", "kernel": ("full_order + full_sweep_rank + full_sweep_scan kernels" if args.sweep_to_v else "select_kernel + sweep_kernel") + " (one gr_accept_sweep call)", "achieved": achieved,
+        "roofline": {"bound": "hbm", "kernel": ("grid_kernel" if args.sweep_to_v else "select_kernel + sweep_kernel") + " (one gr_accept_sweep call)", "achieved": achieved,
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "traffic": None,
                      "call_ms": call_ms},
         "cpu_baseline": cpu,
@@ -308,7 +308,7 @@ def main():
     if prof and prof["steps"]:
         k_eff = wl.V if (wl.k <= 0 or wl.k >= wl.V) else wl.k
         hbm_path = k_eff > 256                         # support kept in HBM: other kernels behind the same three events
-        first, second = (("full_order+full_scan+full_trunc kernels", "full_programs_kernel") if hbm_path
+        first, second = (("full_support+count+scatter+bucket+scan+trunc+dense kernels", "full_programs_kernel") if hbm_path
                          else ("select_kernel", "solve_kernel"))
         kernels = {first: prof["select_ms"], second: prof["solve_ms"]}
         if not (fused and not hbm_path):               # one launch solves and verifies: no verify kernel of its own

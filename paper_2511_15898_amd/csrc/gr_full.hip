@@ -3,8 +3,8 @@
 // without top-k or with a top-k above GR_MAX_SUPPORT, where the support (up to V tokens) does not fit LDS.
 //
 // Every per-token array lives in a per-handle HBM workspace, row-major with stride V + 2; one
-// workgroup works through a row (256 threads; 1024 in the kernels that order long rows).  The arithmetic that decides integers (prefix sums, F,
-// the running masses of the truncation sets) is the same sequential fp64 arithmetic as on the
+// workgroup works through a row (256 threads; 512 or 1024 on long rows), but where a row's slices, buckets or chunks are shared out.  The
+// arithmetic that decides integers (prefix sums, F, the running masses of the truncation sets) is the same sequential fp64 arithmetic as on the
 // LDS-resident path.
 #include <algorithm>
 #include <type_traits>
@@ -16,9 +16,10 @@ namespace gr {
 namespace {
 
 constexpr int kScanThreads = 512;                  // of the kernel that takes the prefix sums
-constexpr int kChunkRanks = 4096;                  // ranks per workgroup of the kernels that gather and scatter by token id ...
-constexpr int kChunkLds = 40 * 1024;               // ... and the LDS that a workgroup of 256 threads reserves, for four of them to a compute unit (see full_gather_kernel)
-// The sort of the large supports: elements of 8 bytes, the key in the high bits and the token id in the low ones.
+constexpr int kChunkRanks = 4096;                  // ranks per workgroup of the kernel that scatters by token id ...
+constexpr int kChunkLds = 40 * 1024;               // ... and the LDS that a workgroup of 256 threads reserves, for four of them to a compute unit: the rows that are in
+                                                   // work at a time then stay in their XCD's L2
+// The sort by q of a support's candidates and of the truncation sets: elements of 8 bytes, the key in the high bits and the token id in the low ones.
 template <int NT, int R = 4>
 struct Sort32Lds {
     static constexpr int kWavesNT = NT / 64;
@@ -38,8 +39,8 @@ struct Sort32Lds {
 // rounds), wave 0 turns the counters into places, and the tile goes through LDS into digit order, so that the
 // elements of one digit leave as one run and not one by one.  Three barriers per tile.
 // A run is 128 bytes on average with four elements per thread and 1024 threads, 256 bytes with eight (see kLongRow).
-// Bound: 16 bytes of traffic per element and pass, and the latency of a tile's three barriers (order kernel, 1024 rows of 128256
-// tokens: 18 GB in 5.3 ms, 3.4 TB/s where a device copy reaches 5.2).  All threads call.
+// Bound: 16 bytes of traffic per element and pass, and the latency of a tile's three barriers (1024 rows of 128256
+// tokens, four passes: 18 GB in 5.3 ms, 3.4 TB/s where a device copy reaches 5.2).  All threads call.
 template <int NT, int R>
 __device__ unsigned long long* block_sort32(unsigned long long* a, unsigned long long* b, int count, Sort32Lds<NT, R>& S, int lo = 32,
                                            int passes = 4) {
@@ -359,14 +360,14 @@ __device__ __forceinline__ void scan_step(RunSum& v) {
 }  // namespace
 
 // ---- kernel 1: row sums and validity, the support (all positive entries of q, or the k largest) in
-// token order, sort by decreasing q/p (ties by id).
-// The sort key is the correctly rounded float64 quotient q/p: for float32 inputs two different
+// token order where it is cut, the splitters of its order by decreasing q/p (ties by id).
+// The key of the order is the correctly rounded float64 quotient q/p: for float32 inputs two different
 // ratios differ by at least 2^-48 relative, so their quotients differ and keep their order, and equal
 // ratios give equal quotients -- the same order as the exact cross-product comparison (Sec. 5.1).
 //
 // This kernel splits the support into buckets of some kBucket tokens by splitters, keys with their token ids from a sorted sample of the row (so
-// that equal ratios can be split too); full_bucket_kernel puts each bucket in order.  The elements keep p and q beside the id: the
-// second kernel needs no gather.  Where the support is sparse or cut, its list is sampled and not the row.
+// that equal ratios can be split too); the next two kernels move the tokens there, and full_bucket_kernel puts each bucket in order.  The elements keep p and q
+// beside the id: no kernel gathers them.  Where the support is sparse or cut, its list is sampled and not the row.
 // Bound: memory, and the quotients.  1024 rows of 128256 tokens, n = 8: four sorting passes over elements of 8 bytes by one workgroup per row and a
 // gather of the pairs took 6.1 + 1.6 ms; support 0.44, count 0.72, scatter 0.78 and buckets 1.5 ms take their place.  One row 1587 -> 810 us the call,
 // 16 rows 2412 -> 1485, 64 rows cut by a nucleus of 32000 tokens 314 -> 274.
@@ -891,7 +892,7 @@ __global__ __launch_bounds__(kBucketThreads, 8) void full_bucket_kernel(FullPara
     for (int i = tid; i < count; i += NT) { pairs[i] = A.pair[i]; order[i] = ids[i]; }
 }
 
-// ---- kernel 3: prefix sums in the order, F, H*, alpha*, suffix minima, residuals, records, blocks.
+// ---- kernel 5: prefix sums in the order, F, H*, alpha*, suffix minima, residuals, records, blocks.
 //
 // Ascending, in tiles of 2048 ranks: the sequential sums P (waves 0-3) and Q (waves 4-7), eight terms per lane (RunSum).  A sum that leaves its binade inside the tile is right up to the lane where it
 // does; the lanes behind it go again with the new unit (a row's sums double some 40 times, mostly in its first tile).  So one wave adds the
@@ -1108,7 +1109,7 @@ __global__ __launch_bounds__(kScanThreads, 4) void full_scan_kernel(FullParams f
     }
 }
 
-// ---- kernel 4: truncation sets (Alg. 1: fewest tokens by decreasing q with gamma_T <= tau inside H*,
+// ---- kernel 6: truncation sets (Alg. 1: fewest tokens by decreasing q with gamma_T <= tau inside H*,
 // epsilon_T <= tau outside), size of every program, row status.
 //
 // Bound: the pass over q (twice, 4 bytes a token) and, where many tokens stay, their sort.  A workgroup of 256 threads that read
@@ -1355,7 +1356,7 @@ __global__ __launch_bounds__(NT) void full_trunc_kernel(FullParams fp) {
     }
 }
 
-// ---- kernel 5: the dense per-token arrays that the verify and slice kernels read, of the rows within the cap: start weights by
+// ---- kernel 7: the dense per-token arrays that the verify and slice kernels read, of the rows within the cap: start weights by
 // rank (target / Pr[token drawn within its system], inner ones in the slack's gauge) and the residuals by token id.
 // Bound: memory.  Inside the programs kernel, one workgroup of 512 threads to a compute unit, these arrays were
 // most of the 4.8 ms for 1024 rows of 128256 tokens.
@@ -1401,13 +1402,12 @@ __global__ __launch_bounds__(kThreads) void full_dense_kernel(FullParams fp, int
     }
 }
 
-// Workgroups of 1024 threads take rows of more than two of their tiles of 4096 tokens; shorter rows would leave most of one
+// Workgroups of 1024 threads take rows of more than two of the sort's tiles of 4096 tokens; shorter rows would leave most of one
 // idle.  One of them fills a compute unit, so where rows wait for one (more of them than compute units) and a nucleus cut
-// leaves little to sort, the row must be longer (cut of 1e-3; 1024 against 256 threads, the call): 1024 rows of
+// leaves little to sort, the row must be longer (cut of 1e-3; 1024 against 256 threads, the call when one kernel ordered the whole row): 1024 rows of
 // 8193 tokens 795 and 707 us, of 12289 840 and 779, of 16384 959 and 950, of 24000 968 and 1010, of 50021 1504 and 1725.
-// Rows of more than kLongRow tokens are sorted in tiles of eight elements per thread: half the barriers, twice the run; a shorter row loses more to
-// its last tile.  The call, four / eight: 1024 rows of 128256 tokens 12993 / 12654 us, of 50021 4768 / 4759, of 24000 2416 / 2419, of 9000
-// 1317 / 1381; acceptance grid to V, 256 rows of 128256, 4031 / 3868.
+// Rows of more than kLongRow tokens sort their candidates in tiles of eight elements per thread: half the barriers, twice the run; a shorter row loses more to
+// its last tile.  The call, four / eight: 1024 rows of 128256 tokens with a nucleus cut of 1e-8 11602 / 11359 us, 256 of them with a top-k of 1000 1493 / 1342.
 constexpr int kLongRow = 65536;
 constexpr int scatter_lds(int threads, int buckets) { return 8 * threads * static_cast<int>(sizeof(Element) + sizeof(unsigned short)) + buckets * 16; }
 // The LDS of the kernel that moves the elements lies above the default limit.

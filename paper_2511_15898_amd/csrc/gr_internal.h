@@ -84,7 +84,7 @@ struct FullParams {
     int* byq;          // ranks by (inside H* first, decreasing q, token id)
     float2* pairs;     // the raw pair (p, q) of every rank
     double* P; double* Q; double* rho; double* weight;   // prefix sums (Q of the raw q: divide by Q[kk]), residuals and weights by rank
-    int* flag; int* blk; int* blo; int* bcount;
+    int* flag; int* blk; int* blo; int* bcount;   // flag: by token id, whether a cut support has it; from the scan kernel on, by tile of ranks
     int* rank_of;      // [B, V + 2] rank of each token id, -1 outside the support
     double* rho_id;    // [B, V + 2] residual p(i) - p_i by token id (0 inside H*)
     int* nblk;         // [B] number of outer blocks

@@ -4,13 +4,11 @@
 // the support is the first k tokens by decreasing q (App. "Top-k Sampling for the Relaxed OTLP") and
 // its ratio order is the sub-sequence of the largest support's order, so one ordering serves the grid.
 //
-// One workgroup per row, everything in LDS, its 1024 threads in groups of 256: thread m of a group owns rank m of the
-// ratio order; the groups share the comparisons of the ranks and take the top-k sizes in turn.
+// One workgroup per row, everything in LDS: its 1024 threads share the comparisons of the ranks, then a wave takes each top-k size.
 // Only the minimum of F(m) = P_m - Q_m^n is reported, to 1e-5, so the prefix sums here are parallel
 // scans in float64 (no integer decision hangs on their rounding).
 // Bound: latency, a row's chain of LDS reads, scans and barriers; 256 threads to a row left most of a compute unit idle
-// (256 rows, six sizes up to 256, ten draft counts: 44 us, now 25.7; with the selection, V = 32000, 1 / 512 / 1024 / 2048
-// rows 53.0 / 78.5 / 116.2 / 216.0 -> 35.7 / 67.4 / 111.5 / 215.1 us, so no batch is better served by fewer threads).
+// (256 rows, six sizes up to 256, ten draft counts: 44 us; 1024 threads 25.7, and 16.9 with a wave to a size).
 #include <hip/hip_runtime.h>
 
 #include "gr_internal.h"
