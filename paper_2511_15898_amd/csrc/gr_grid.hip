@@ -144,6 +144,13 @@ __device__ __forceinline__ void each_token(const float* pr, const float* qr, int
     }
 }
 
+// One more at a counter in LDS, for the lanes that are here: by one of them where all name the same (flat drafts).
+__device__ __forceinline__ void count_one(int* counters, int at) {
+    const unsigned long long here = __ballot(true);
+    if (__ballot(at == __builtin_amdgcn_readfirstlane(at)) != here) atomicAdd(&counters[at], 1);
+    else if ((threadIdx.x & 63) == __ffsll(static_cast<long long>(here)) - 1) atomicAdd(&counters[at], __popcll(here));
+}
+
 // One wave: the digit of `hist` (DIGITS of them) that holds the need-th largest key; returns it, with the keys still needed from it and
 // how many it holds.
 template <int DIGITS>
@@ -211,7 +218,7 @@ __global__ __launch_bounds__(kNT) void grid_kernel(GridParams gp) {
     each_token<true>(pr, qr, V, [&](float pv, float qv, int) {
         bad |= !(qv >= 0.f) | !(pv >= 0.f);
         ps += static_cast<double>(pv); qs += static_cast<double>(qv);
-        if (qv > 0.f) { ++positive; atomicAdd(&S.classes[padded(min(__float_as_uint(qv) >> 19, kClasses - 1u))], 1); }
+        if (qv > 0.f) { ++positive; count_one(S.classes, padded(min(__float_as_uint(qv) >> 19, kClasses - 1u))); }
     });
     const double ptot = block_sum<kNW>(ps, S.red), qtot = block_sum<kNW>(qs, S.red);
     bad = block_sum_i<kNW>(bad, S.red);
@@ -258,19 +265,29 @@ __global__ __launch_bounds__(kNT) void grid_kernel(GridParams gp) {
             shift -= width;
             for (int c = tid; c < kSweepMaxK * padded(256); c += kNT) (&S.hist[0][0])[c] = 0;
             __syncthreads();
+            // sizes whose thresholds agree so far (neighbours, as the sizes rise) share the counters of the first of them
+            int lead = 0, my_lead = 0;
+            unsigned long long last = ~0ull;
 #pragma unroll
-            for (int a = 0; a < kSweepMaxK; ++a) thr[a] = a < nk && (open >> a & 1u) ? S.prefix[a] >> above : ~0ull;
+            for (int a = 0; a < kSweepMaxK; ++a) {
+                thr[a] = ~0ull;
+                if (a < nk && (open >> a & 1u)) {
+                    const unsigned long long t = S.prefix[a] >> above;
+                    if (t != last) { thr[a] = t; lead = a; last = t; }
+                    if (a == wv) my_lead = lead;
+                }
+            }
             auto add = [&](unsigned long long key) {
                 const int d = static_cast<int>(key >> shift) & 255 & ((1 << width) - 1);
 #pragma unroll
-                for (int a = 0; a < kSweepMaxK; ++a) if (key >> above == thr[a]) atomicAdd(&S.hist[a][padded(d)], 1);
+                for (int a = 0; a < kSweepMaxK; ++a) if (key >> above == thr[a]) count_one(S.hist[a], padded(d));
             };
             if (listed) { for (int i = tid; i < keys; i += kNT) add(S.keys[i]); }
             else each_token<false>(pr, qr, V, [&](float, float qv, int id) { if (qv > 0.f) add(make_key(qv, id)); });
             __syncthreads();
             if (wv < nk && (open >> wv & 1u)) {
                 int need = S.need[wv], holds = 0;
-                const int d = pick_digit<256>(S.hist[wv], need, holds);
+                const int d = pick_digit<256>(S.hist[my_lead], need, holds);
                 if (lane == 0) { S.prefix[wv] |= static_cast<unsigned long long>(d) << shift; S.need[wv] = need; S.bucket[wv] = holds; }
             }
             __syncthreads();
