@@ -231,13 +231,14 @@ __global__ __launch_bounds__(kNT) void grid_kernel(GridParams gp) {
 
     // the smallest key (q, then the lower id) of each top-k size, by radix selection: the classes first, then eight bits at a time over the
     // keys of the classes that thresholds fall into, from LDS where they fit and from the row where not
-    if (wv <= nk) {                                // the last of these waves: the classes of the kMaxHeavy largest q
+    if (wv <= nk) {                                // the last of these waves: the classes above that of the first key that has no place at hand
         const int rank = wv < nk ? gp.ks[wv] : kMaxHeavy + 1;
+        const bool there = wv < nk ? rank < positive : rank <= positive;   // a size of every token has no threshold
         int need = rank, holds = rank, digit = 0;
-        if (rank < positive) digit = pick_digit<kClasses>(S.classes, need, holds);
+        if (there) digit = pick_digit<kClasses>(S.classes, need, holds);
         if (lane == 0) {
             if (wv < nk) { S.prefix[wv] = static_cast<unsigned long long>(digit) << 51; S.need[wv] = need; S.bucket[wv] = holds; }
-            else S.heavy_class = rank < positive ? digit + 1 : 0;
+            else S.heavy_class = there ? digit + 1 : 0;
         }
     }
     __syncthreads();

@@ -228,3 +228,24 @@ def test_rows_that_take_the_bins_to_their_ends(V):
         assert np.abs(acc[b] - want).max() <= 2e-7, (b, acc[b], want)    # two roundings of a value up to 1 to float32
     again, _ = _sweep(p, q, ks, ns, max_k=0)
     assert np.array_equal(acc, again)
+
+
+@pytest.mark.parametrize("V,positive", [(2047, 2047), (2048, 2048), (2049, 2049), (2050, 2050), (6000, 2049), (20001, 2049)])
+def test_rows_with_about_as_many_tokens_as_are_kept_at_hand(V, positive):
+    """Supports on both sides of the 2048 tokens that the later rounds find at hand, drafts close enough to the target that there are
+    such rounds; zeros among the tokens or none.  Bound: two roundings of a value up to 1 to float32."""
+    from oracle import gr_oracle as G
+    rng = np.random.default_rng(V + positive)
+    base = rng.dirichlet(np.full(V, 2.0), size=6) + 1e-9
+    p, q = base.copy(), base.copy()
+    for b, near in enumerate([1e-2, 1e-4, 1e-6, 0.0, 0.3, 1.0]):
+        q[b] *= np.exp(near * rng.standard_normal(V))
+        q[b, rng.permutation(V)[positive:]] = 0.0
+    p = (p / p.sum(1, keepdims=True)).astype(np.float32); q = (q / q.sum(1, keepdims=True)).astype(np.float32)
+    assert np.all((q > 0).sum(1) == positive)
+    ks, ns = [0, positive, positive - 1, 300, 20], [1, 2, 5, 16]
+    acc, st = _sweep(p, q, ks, ns, max_k=0)
+    assert np.all(st == 0)
+    for b in range(len(p)):
+        want = G.acceptance_sweep(p[b], q[b], ks, ns)
+        assert np.abs(acc[b] - want).max() <= 2e-7, (b, acc[b], want)
