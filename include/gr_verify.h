@@ -139,7 +139,8 @@ int gr_solve_logits(gr_handle h, const float* target_logits, const float* draft_
  *             k is at most GR_MAX_SUPPORT the grid is served from one streaming pass; otherwise (the study runs k
  *             up to the whole vocabulary) the handle must have been created with max_k at least the largest
  *             (GR_EINVAL otherwise) and the whole grid comes from the sums of p and q over bins of the ratio q/p,
- *             cut finer where the minimum may lie inside one, to 1e-13 of the acceptance.
+ *             cut finer where the minimum may lie inside one, to 1e-13 of the acceptance and the float64 rounding of
+ *             its difference from 1 (some n 1e-16 for n drafts).
  * ns          HOST array of nn draft counts, 1 <= nn <= GR_SWEEP_MAX_N, each 1..GR_SWEEP_MAX_DRAFTS.
  * accept_prob [B, nk, nn] float32 device out (NaN for a bad row).   status [B] int32 device out:
  *             GR_ROW_OK or GR_ROW_BAD.

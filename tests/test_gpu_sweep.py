@@ -249,3 +249,30 @@ def test_rows_with_about_as_many_tokens_as_are_kept_at_hand(V, positive):
     for b in range(len(p)):
         want = G.acceptance_sweep(p[b], q[b], ks, ns)
         assert np.abs(acc[b] - want).max() <= 2e-7, (b, acc[b], want)
+
+
+@pytest.mark.parametrize("V,gap", [(128256, 16), (128256, 20), (131077, 24)])
+def test_small_acceptances_of_targets_and_drafts_apart(V, gap):
+    """Half of the tokens for the target, half for the draft, `gap` nats apart: acceptances of 1e-6 to 1e-11, which hang on the sums of many
+    tokens too small to be whole in the kernel's units.  Bound: the acceptance's rounding to float32 and, in float64, four roundings for each of n
+    factors Q and of the difference from 1."""
+    rng = np.random.default_rng(gap)
+    wide = np.longdouble
+    p, q = np.empty((3, V), np.float32), np.empty((3, V), np.float32)
+    for b in range(3):
+        t, d, half = rng.gumbel(size=V), rng.gumbel(size=V), rng.random(V) < 0.5
+        t[half] -= gap; d[~half] -= gap
+        p[b], q[b] = np.exp(t) / np.exp(t).sum(), np.exp(d) / np.exp(d).sum()
+    ks, ns = [0, V // 2, 5000], [1, 3, 8]
+    acc, st = _sweep(p, q, ks, ns, max_k=0)
+    assert np.all(st == 0)
+    for b in range(3):
+        total = p[b].sum(dtype=wide)
+        for a, k in enumerate(ks):
+            ids = np.argsort(-q[b], kind="stable")[:k or V]
+            order = ids[np.argsort(-q[b, ids].astype(np.float64) / p[b, ids].astype(np.float64), kind="stable")]
+            P = np.cumsum(p[b, order].astype(wide)) / total
+            Q = np.cumsum(q[b, order].astype(wide)); Q /= Q[-1]
+            for c, n in enumerate(ns):
+                want = 1.0 + min(wide(0.0), (P - Q ** n).min())
+                assert abs(acc[b, a, c] - want) <= 2.0 ** -24 * want + (4 * n + 8) * 2.0 ** -53, (b, k, n, acc[b, a, c], want)
