@@ -73,6 +73,12 @@ void mark_no_verify(gr_handle h, hipStream_t stream) {
     h->prof_now = false;
 }
 
+// The runtime keeps the error of a call until it is asked for: left there, the next valid call of the thread would find it behind its launches.
+int hip_failed() {
+    (void)hipGetLastError();
+    return GR_EHIP;
+}
+
 template <typename T>
 bool dev_alloc(T** ptr, size_t count) {
     return hipMalloc(reinterpret_cast<void**>(ptr), count * sizeof(T)) == hipSuccess;
@@ -197,10 +203,10 @@ void* g_scratch_ptr[kMaxDevices] = {};       // device address of `scratch` on e
 // The address of this device's copy of `scratch` (host code must never pass the array's name to a kernel).
 int scratch_address(unsigned char** out) {
     int dev = -1;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return GR_EHIP;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return hip_failed();
     void* ptr = __atomic_load_n(&g_scratch_ptr[dev], __ATOMIC_ACQUIRE);
     if (!ptr) {
-        if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess || !ptr) { (void)hipGetLastError(); return GR_EHIP; }
+        if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess || !ptr) return hip_failed();
         __atomic_store_n(&g_scratch_ptr[dev], ptr, __ATOMIC_RELEASE);      // every thread finds the same address
     }
     *out = static_cast<unsigned char*>(ptr);
@@ -306,8 +312,8 @@ extern "C" int gr_create(gr_handle* out, int max_B, int max_V, int max_k, int ma
         if (!(cfg->tail_mass >= 0.0) || !(cfg->tail_mass < 1.0)) { delete h; return GR_EINVAL; }
         h->tail_mass = cfg->tail_mass;
     }
-    if (hipGetDevice(&h->device) != hipSuccess) { delete h; return GR_EHIP; }
-    if (solve_kernel_setup(max_n, max_B, k_cap > kMaxSupport) != hipSuccess || (k_cap > kMaxSupport && (full_kernel_setup() != hipSuccess || grid_kernel_setup() != hipSuccess))) { delete h; return GR_EHIP; }
+    if (hipGetDevice(&h->device) != hipSuccess) { delete h; return hip_failed(); }
+    if (solve_kernel_setup(max_n, max_B, k_cap > kMaxSupport) != hipSuccess || (k_cap > kMaxSupport && (full_kernel_setup() != hipSuccess || grid_kernel_setup() != hipSuccess))) { delete h; return hip_failed(); }
     { unsigned char* na = nullptr; (void)scratch_address(&na); }      // so that gr_accept_sweep_noalloc finds its array later
     const size_t rows = static_cast<size_t>(max_B);
     bool ok = dev_alloc(&h->cand, rows * kSelCap) && dev_alloc(&h->cand_count, rows * kMaxSplits) &&
@@ -331,7 +337,7 @@ extern "C" int gr_create(gr_handle* out, int max_B, int max_V, int max_k, int ma
         h->profile = true;
         for (auto& slot : h->ev)
             for (auto& e : slot)
-                if (hipEventCreate(&e) != hipSuccess) { free_all(h); delete h; return GR_EHIP; }
+                if (hipEventCreate(&e) != hipSuccess) { free_all(h); delete h; return hip_failed(); }
     }
     *out = h;
     return GR_OK;
@@ -526,7 +532,7 @@ extern "C" int gr_tree_walk(gr_handle h, const float* p, const float* q, const f
     if (!staged) { (void)hipGetLastError(); return GR_ENOMEM; }          // what was allocated stays for the next call
     // A batch leaves no policy of the caller's rows in the handle, and the copies use the staging that the next call writes: no return
     // leaves either behind.
-    auto fail = [&](int rc) { h->solved = false; (void)hipStreamSynchronize(stream); return rc; };
+    auto fail = [&](int rc) { h->solved = false; (void)hipStreamSynchronize(stream); (void)hipGetLastError(); return rc; };
     try {
     // the state of every sequence lives on the host: the paths that still agree with the tokens emitted so far
     std::vector<unsigned> active(S, K >= 32 ? 0xFFFFFFFFu : ((1u << K) - 1u));
@@ -666,11 +672,11 @@ extern "C" int gr_profile_read(gr_handle h, double* select_ms, double* solve_ms,
     if (!h->profile) return GR_ESTATE;
     double acc[3] = {0.0, 0.0, 0.0};
     for (int s = 0; s < h->prof_count; ++s) {
-        if (hipEventSynchronize(h->ev[s][4]) != hipSuccess) return GR_EHIP;
+        if (hipEventSynchronize(h->ev[s][4]) != hipSuccess) return hip_failed();
         const int pairs[3][2] = {{0, 1}, {1, 2}, {3, 4}};
         for (int j = 0; j < 3; ++j) {
             float ms = 0.f;
-            if (hipEventElapsedTime(&ms, h->ev[s][pairs[j][0]], h->ev[s][pairs[j][1]]) != hipSuccess) return GR_EHIP;
+            if (hipEventElapsedTime(&ms, h->ev[s][pairs[j][0]], h->ev[s][pairs[j][1]]) != hipSuccess) return hip_failed();
             acc[j] += ms;
         }
     }
@@ -721,7 +727,7 @@ extern "C" int gr_policy_export(gr_handle h, int* order, int* block, double* wei
     if (block && e == hipSuccess) e = hipMemcpyAsync(block, h->block, cnt * sizeof(int), hipMemcpyDeviceToDevice, stream);
     if (weight && e == hipSuccess) e = hipMemcpyAsync(weight, h->weight, cnt * sizeof(double), hipMemcpyDeviceToDevice, stream);
     if (rho && e == hipSuccess) e = hipMemcpyAsync(rho, h->rho, cnt * sizeof(double), hipMemcpyDeviceToDevice, stream);
-    if (e != hipSuccess) return GR_EHIP;
+    if (e != hipSuccess) return hip_failed();
     if (support || h_size || iterations) {
         hipLaunchKernelGGL(export_kernel, dim3((h->B + 255) / 256), dim3(256), 0, stream, h->info, h->B, support,
                            h_size, iterations);
@@ -749,7 +755,7 @@ extern "C" int gr_policy_export_row(gr_handle h, int row, int count, int* order,
     if (block && e == hipSuccess) e = hipMemcpyAsync(block, s_block + off, n * sizeof(int), hipMemcpyDeviceToDevice, stream);
     if (weight && e == hipSuccess) e = hipMemcpyAsync(weight, s_weight + off, n * sizeof(double), hipMemcpyDeviceToDevice, stream);
     if (rho && e == hipSuccess) e = hipMemcpyAsync(rho, s_rho + off, n * sizeof(double), hipMemcpyDeviceToDevice, stream);
-    return e == hipSuccess ? GR_OK : GR_EHIP;
+    return e == hipSuccess ? GR_OK : hip_failed();
 }
 
 extern "C" int gr_solve_stats(gr_handle h, int* evaluations, double* node_tokens, void* hip_stream) {

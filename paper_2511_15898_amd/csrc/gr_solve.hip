@@ -2128,7 +2128,8 @@ static Chosen choose(int which, int n, bool narrow) {
 hipError_t launch_full_programs(const FullParams& fp, hipStream_t stream) {
     const Chosen c = choose(kPrograms, fp.n, fp.B > kChip);
     void* args[] = {const_cast<FullParams*>(&fp)};
-    return hipLaunchKernel(c.kernel, dim3(fp.B), dim3(c.threads), args, c.lds, stream);
+    (void)hipLaunchKernel(c.kernel, dim3(fp.B), dim3(c.threads), args, c.lds, stream);
+    return hipGetLastError();                                    // which clears it: the next call asks again
 }
 
 static_assert(sizeof(Lds<16>) + 20 * 1024 <= 160 * 1024,
@@ -2152,7 +2153,8 @@ hipError_t solve_kernel_setup(int max_n, int max_B, bool hbm) {
 hipError_t launch_solve(const SolveParams& sp, hipStream_t stream) {
     const Chosen c = choose(kSolve, sp.n, sp.B > kChip);
     void* args[] = {const_cast<SolveParams*>(&sp)};
-    return hipLaunchKernel(c.kernel, dim3(sp.B), dim3(c.threads), args, c.lds, stream);
+    (void)hipLaunchKernel(c.kernel, dim3(sp.B), dim3(c.threads), args, c.lds, stream);
+    return hipGetLastError();                                    // which clears it: the next call asks again
 }
 
 }  // namespace gr

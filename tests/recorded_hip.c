@@ -16,6 +16,7 @@ static char log_[kLog];
 static size_t log_used;
 static char fail_name[64];
 static int fail_in;
+static int last_error;                                 /* kept until hipGetLastError */
 
 /* The fail_after-th next call of `name` (0: the next one) returns an error. */
 void recorded_fail(const char* name, int fail_after) { snprintf(fail_name, sizeof fail_name, "%s", name); fail_in = fail_after + 1; }
@@ -25,7 +26,7 @@ void recorded_clear(void) { log_used = 0; log_[0] = 0; fail_name[0] = 0; }
 static int note(const char* name, const char* what) {
     const int n = snprintf(log_ + log_used, kLog - log_used, "%s %s\n", name, what);
     if (n > 0 && log_used + (size_t)n < kLog) log_used += (size_t)n;
-    if (strcmp(name, fail_name) == 0 && --fail_in == 0) { fail_name[0] = 0; return 999; }
+    if (strcmp(name, fail_name) == 0 && --fail_in == 0) { fail_name[0] = 0; return last_error = 999; }
     return 0;
 }
 
@@ -54,7 +55,7 @@ int hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, size_t ld
         if (functions[i] == f) { over += lds > 65536 && lds > allowed[i]; return note("launch", names[i]); }
     return note("launch", "?");
 }
-int hipGetLastError(void) { return 0; }
+int hipGetLastError(void) { const int e = last_error; last_error = 0; return e; }
 int hipGetDevice(int* device) { *device = 0; return 0; }
 int recorded_over(void) { return over; }
 int hipFuncSetAttribute(const void* f, int attribute, int value) {

@@ -80,6 +80,33 @@ result["verify"] = verify(h, 4)
     assert r["log"][-1].startswith("synchronize"), r["log"]
 
 
+@pytest.mark.parametrize("k", [32, 300])
+@pytest.mark.parametrize("call", ["solve(h, 4, 1024, 3, {k})", "walk(h, 4, 3, 2, 1024, {k})", "sweep(h, 4, 1024, [10, {k}], [1, 2])", "verify(h, 4)"])
+def test_a_failed_call_leaves_no_error_to_the_next(recorded, k, call):
+    """Whichever of a call's launches, copies and waits fails: that call reports it, and a valid one after it does not."""
+    call = call.format(k=k)
+    r = recorded(f"""
+h = create(4, 1024, 300, 3)
+assert solve(h, 4, 1024, 3, {k}) == 0
+hip.recorded_clear()
+assert {call} == 0
+steps, result["seen"] = log(), []
+for i, line in enumerate(steps):
+    name = line.split()[0]
+    if name not in ("launch", "to_device", "to_host", "synchronize"):
+        continue
+    assert solve(h, 4, 1024, 3, {k}) == 0
+    hip.recorded_clear()
+    hip.recorded_fail(name.encode(), sum(x.split()[0] == name for x in steps[:i]))
+    rc = {call}
+    hip.recorded_clear()
+    result["seen"].append([line, rc, solve(h, 4, 1024, 3, {k}), verify(h, 4)])
+""")
+    assert len(r["seen"]) >= 1
+    for line, failed, solved, verified in r["seen"]:
+        assert failed == -4 and solved == 0 and verified == 0, (line, failed, solved, verified)
+
+
 def test_a_refused_walk_leaves_the_policy_of_the_last_solve(recorded):
     r = recorded("""
 h = create(4, 1024, 32, 3)
