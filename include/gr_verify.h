@@ -223,8 +223,9 @@ int gr_solve_logits_verify(gr_handle h, const float* target_logits, const float*
  *            token per level visited; no bonus token after a fully accepted tree).  out_accepted [S]: how many of
  *            them were drafts.  out_fallbacks [S] or NULL: levels whose row had a status other than GR_ROW_OK.
  * The first call allocates staging (97 bytes per row, for 512 rows at least, on the device and in pinned host memory; the first call with a support above
- * GR_MAX_SUPPORT also 8 max_V bytes per row on the device; GR_ENOMEM), and the first batch of more than max_B nodes the scratch of 512 rows (77 MB and
- * 24 KB per 1000 tokens of max_V; without it the batches hold max_B nodes at most); every call synchronises the stream once per batch, and one that
+ * GR_MAX_SUPPORT also 8 max_V bytes per row on the device; GR_ENOMEM), and the first batch of more than max_B nodes, or of more than the largest such
+ * batch before, scratch for the nodes that the walk may take at once (64 to 512, a power of two: 150 KB and 47 bytes per 1000 tokens of max_V each; in a
+ * walk that finds no memory for it the batches hold max_B nodes at most); every call synchronises the stream once per batch, and one that
  * has enqueued a batch leaves the handle without a policy (GR_ESTATE for a gr_verify that follows), also where it fails.
  */
 int gr_tree_walk(gr_handle h, const float* p, const float* q, const float* temperature, const int* paths,

@@ -50,8 +50,8 @@ struct gr_handle_s : RowScratch {
     // HBM-resident path
     unsigned char* tw_in = nullptr; unsigned char* tw_out = nullptr; unsigned char* tw_host = nullptr;
     float* tw_p = nullptr; float* tw_q = nullptr;
-    // scratch of a walk's batches of more than max_B rows, in one allocation (made by the first of them)
-    RowScratch wide; void* wide_mem = nullptr; bool wide_asked = false;
+    // scratch of a walk's batches of more than max_B rows, in one allocation (made by the first of them, again by the first that needs more)
+    RowScratch wide; void* wide_mem = nullptr; int wide_rows = 0;
     // last solve
     bool solved = false;
     const float* p = nullptr;
@@ -101,14 +101,18 @@ void free_all(gr_handle h) {
 // either way (590 and 611 us), and 256 sequences of 8 paths, 8 levels of 3000 tokens too (1417 and 1516).
 constexpr int kWalkRows = 512, kWalkLevelRows = 256;
 
-// The scratch of kWalkRows rows; false: there is no memory for it.
-bool wide_scratch(gr_handle h) {
-    if (h->wide_asked) return h->wide_mem != nullptr;
-    h->wide_asked = true;
+// Scratch for batches of `need` rows (for a power of two of them, 64 at least: 150 KB a row); false: there is no memory for it.  No batch is in work
+// here: the walk waits for each.
+bool wide_scratch(gr_handle h, int need) {
+    if (need <= h->wide_rows) return true;
+    (void)hipFree(h->wide_mem);
+    h->wide_mem = nullptr; h->wide_rows = 0;
     RowScratch& w = h->wide;
     unsigned char* base = nullptr;
     size_t used = 0;
-    const size_t rows = kWalkRows, pieces = rows * static_cast<size_t>(h->piece_stride);
+    size_t rows = 64;
+    while (rows < static_cast<size_t>(need)) rows *= 2;
+    const size_t pieces = rows * static_cast<size_t>(h->piece_stride);
     auto carve = [&](auto** ptr, size_t count) {
         using T = std::remove_reference_t<decltype(**ptr)>;
         *ptr = reinterpret_cast<T*>(base + used);
@@ -123,9 +127,10 @@ bool wide_scratch(gr_handle h) {
         carve(&w.rho, rows * kMaxSupport); carve(&w.pnorm, rows * kMaxSupport); carve(&w.info, rows);
     };
     all();
-    if (solve_kernel_setup(h->max_n, kWalkRows, false) != hipSuccess || hipMalloc(&h->wide_mem, used) != hipSuccess) { (void)hipGetLastError(); h->wide_mem = nullptr; return false; }
+    if (solve_kernel_setup(h->max_n, static_cast<int>(rows), false) != hipSuccess || hipMalloc(&h->wide_mem, used) != hipSuccess) { (void)hipGetLastError(); h->wide_mem = nullptr; return false; }
     base = static_cast<unsigned char*>(h->wide_mem);
     all();
+    h->wide_rows = static_cast<int>(rows);
     return true;
 }
 
@@ -544,6 +549,7 @@ extern "C" int gr_tree_walk(gr_handle h, const float* p, const float* q, const f
     struct Node { int s, l; unsigned paths; };
     std::vector<Node> nodes;
     std::vector<int> child, by_n, row_of;
+    bool no_room = false;                                        // for a larger batch, in this walk
     const auto token_of = [&](const Node& x, int a) { return paths[(static_cast<size_t>(x.s) * K + a) * L + x.l]; };
     for (int l = 0; l < L;) {
         // Every sequence still alive, whatever its draft count, in one batch: a level then takes as long as its slowest row, and
@@ -560,6 +566,9 @@ extern "C" int gr_tree_walk(gr_handle h, const float* p, const float* q, const f
             if (nodes.empty()) continue;
             const size_t roots = nodes.size();
             if (in_lds) {
+                int bound = 0;                                       // nodes of the levels left: their paths each, at most
+                for (const Node& x : nodes) bound += __builtin_popcount(x.paths);
+                bound = std::min(kWalkRows, bound * (L - l));
                 size_t from = 0;                                     // the first node of the last level taken
                 for (; next_l < L; ++next_l) {
                     const size_t to = nodes.size(), least = to - from;   // a node has a child at least
@@ -578,7 +587,7 @@ extern "C" int gr_tree_walk(gr_handle h, const float* p, const float* q, const f
                     }
                     const size_t more = nodes.size() - to;
                     if (more > static_cast<size_t>(kWalkLevelRows) || nodes.size() > static_cast<size_t>(kWalkRows) ||
-                        (nodes.size() > static_cast<size_t>(h->max_B) && !wide_scratch(h))) { nodes.resize(to); child.resize(from); break; }
+                        (nodes.size() > static_cast<size_t>(h->max_B) && (no_room || (no_room = !wide_scratch(h, bound))))) { nodes.resize(to); child.resize(from); break; }
                     from = to;
                 }
             }

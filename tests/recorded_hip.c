@@ -50,9 +50,14 @@ int __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, void** strea
     return 0;
 }
 int hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, size_t lds, void* stream) {
-    (void)grid; (void)block; (void)args; (void)stream;
+    (void)block; (void)args; (void)stream;
     for (int i = 0; i < function_count; ++i)
-        if (functions[i] == f) { over += lds > 65536 && lds > allowed[i]; return note("launch", names[i]); }
+        if (functions[i] == f) {
+            char what[256];
+            over += lds > 65536 && lds > allowed[i];
+            snprintf(what, sizeof what, "%.200s %u", names[i], grid.x);
+            return note("launch", what);
+        }
     return note("launch", "?");
 }
 int hipGetLastError(void) { const int e = last_error; last_error = 0; return e; }

@@ -107,6 +107,24 @@ for i, line in enumerate(steps):
         assert failed == -4 and solved == 0 and verified == 0, (line, failed, solved, verified)
 
 
+def test_a_walk_without_memory_for_its_batch_goes_by_levels_and_the_next_one_asks_again(recorded):
+    """Sequences of two paths, all of them the same: 4 nodes to a level, where the handle has 4 rows.  A walk of more nodes than the scratch
+    holds asks for more, a smaller one for nothing."""
+    r = recorded("""
+h = create(4, 1024, 32, 2)
+assert walk(h, 1, 1, 1, 1024, 32) == 0              # one node: staging only
+def batch(S, L, fail=False):
+    hip.recorded_clear()
+    if fail:
+        hip.recorded_fail(b"malloc", 0)
+    assert walk(h, S, 2, L, 1024, 32) == 0
+    rows = [int(x.split()[2]) for x in log() if x.startswith("launch") and "solve_kernel" in x]
+    return rows[0], sum(x.startswith("malloc") for x in log())
+result["got"] = [batch(4, 3, True), batch(4, 3), batch(4, 3), batch(4, 9), batch(4, 3)]
+""")
+    assert r["got"] == [[4, 1], [12, 1], [12, 0], [36, 1], [12, 0]], r
+
+
 def test_a_refused_walk_leaves_the_policy_of_the_last_solve(recorded):
     r = recorded("""
 h = create(4, 1024, 32, 3)
