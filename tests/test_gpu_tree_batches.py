@@ -30,10 +30,11 @@ def test_walks_with_mixed_draft_counts(K, L, V, k):
     assert compared >= S - 2
 
 
-@pytest.mark.parametrize("S,K,L,V,k", [(90, 4, 4, 300, 24), (257, 2, 3, 261, 12), (40, 16, 3, 300, 16)])
+@pytest.mark.parametrize("S,K,L,V,k", [(90, 4, 4, 300, 24), (257, 2, 3, 261, 12), (40, 16, 3, 300, 16), (70, 4, 3, 300, 24), (60, 7, 3, 301, 20)])
 def test_walks_of_several_levels_to_a_batch(S, K, L, V, k):
-    """Trees on both sides of what one batch takes (512 nodes, 256 of a later level): the same walks taken node by node, every step a tree of one
-    level with the paths that are left.  A token may differ where the uniform falls on an edge of the distribution."""
+    """Trees on both sides of what one batch takes (512 nodes, 256 of a later level), some in batches of more rows than the handle has and than
+    the chip has compute units (390 nodes of 3 or 4 paths at most, of 5 to 7 too): the same walks taken node by node, every step a tree of one level with the
+    paths that are left.  A token may differ where the uniform falls on an edge of the distribution."""
     import torch
     from paper_2511_15898_amd import binding as gr
     rng = np.random.default_rng(S)

@@ -161,9 +161,14 @@ for n in range(1, {max_n} + 1):
         assert solve(h, {B}, 600, n, k) == 0 and verify(h, {B}) == 0
 assert sweep(h, {B}, 600, [10, 0], [1, 2]) == 0
 if {B} == 264:
-    paths = (C.c_int * (264 * {max_n} * 2))(*[i % 7 for i in range(264 * {max_n} * 2)])
-    rows, ints = buffer(264 * {max_n} * 600 + 1), [(C.c_int * 528)() for _ in range(4)]
-    assert lib.gr_tree_walk(h, rows, rows, None, paths, (C.c_float * 528)(), 240, {max_n}, 2, 600, 20, C.c_float(1e-4), *ints, None) == 0
+    paths = (C.c_int * (240 * {max_n} * 2))(*[i % 2 * (i // 2 % 7) for i in range(240 * {max_n} * 2)])   # one token at level 0, so two nodes a sequence
+    rows, ints = buffer(240 * {max_n} * 600 + 1), [(C.c_int * 480)() for _ in range(4)]
+    hip.recorded_clear()
+    assert lib.gr_tree_walk(h, rows, rows, None, paths, (C.c_float * 480)(), 240, {max_n}, 2, 600, 20, C.c_float(1e-4), *ints, None) == 0
+    result["batch"] = [x.split()[1:] for x in log() if "solve_kernel" in x]
 result["over"] = hip.recorded_over()
 """)
     assert r["over"] == 0
+    if B == 264:
+        (kernel, rows), = r["batch"]
+        assert rows == "480" and ("Li256E" in kernel), kernel     # more rows than the handle and the chip: the small workgroup (of all with more than 8 drafts)
