@@ -279,7 +279,10 @@ struct RatioKey {
     }
 };
 // Buckets of the order: kBucket tokens on average at most (while there are buckets enough), kBucketCap in the LDS of the workgroup that sorts one.
-// With kSamplesPerBucket samples to a bucket, one of twice the average comes up once in 1e6.
+// With kSamplesPerBucket samples to a bucket, one of twice the average comes up once in 1e6.  Rows of more than 131072 tokens have 4096 samples for all their
+// buckets, so that more of these end above the cap: one in 2000 at 262144 tokens, one in 25 at a million, and from 4 million tokens on, with 2048 buckets
+// for all, most.  Those go by sorted stretches (one row of 2^18 / 2^20 / 2^22 / 2^24 - 1 tokens, the call: 1463 us, 4.1, 16.0 and 67 ms; with the tokens of
+// a bucket compared all with all 2117 us, 5.4, 28 and 294 ms).
 constexpr int kBucket = 1024, kBucketCap = 2048, kSamplesPerBucket = 32, kLogBuckets = 11;
 __host__ __device__ inline int log_buckets(int tokens) {
     int l = 0;
@@ -764,8 +767,8 @@ __global__ __launch_bounds__(NT) void full_scatter_kernel(FullParams fp, int sli
 //
 // A token's place in its bucket is found through the key's place between the bucket's smallest and largest one: it goes to one of kCells cells,
 // half a token each on average, and is compared with the others of its cell.  Where the keys lie too unevenly for that (kCrowded in a
-// cell) the bucket is sorted; one above kBucketCap (the sample missed it) is ranked by comparison with all of its tokens, tile by
-// tile.  Buckets of a row share an XCD: the ranks go to 4 V bytes of it at random and stay in its L2 meanwhile.
+// cell) the bucket is sorted; one above kBucketCap (the sample missed it, or the row has more than kBucket tokens to each of all buckets) goes by sorted
+// stretches.  Buckets of a row share an XCD: the ranks go to 4 V bytes of it at random and stay in its L2 meanwhile.
 constexpr int kBucketThreads = 512, kCells = 2048, kCrowded = 48;
 __global__ __launch_bounds__(kBucketThreads, 8) void full_bucket_kernel(FullParams fp, int buckets) {
     constexpr int NT = kBucketThreads, PER = kBucketCap / NT, kWaves = NT / 64;
@@ -789,19 +792,29 @@ __global__ __launch_bounds__(kBucketThreads, 8) void full_bucket_kernel(FullPara
     int* order = fp.order + row * vs + at; float2* pairs = fp.pairs + row * vs + at; int* rank_of = fp.rank_of + row * vs;
     auto before = [](unsigned long long k0, int i0, unsigned long long k1, int i1) { return k0 < k1 || (k0 == k1 && i0 < i1); };
     if (count > kBucketCap) {
-        for (int i0 = 0; i0 < count; i0 += NT) {
-            const bool mine = i0 + tid < count;
-            const Element e = elems[mine ? i0 + tid : 0];
-            const unsigned long long key = key_of(e.q, e.p);
-            int rank = 0;
-            for (int t0 = 0; t0 < count; t0 += kBucketCap) {
-                const int cnt = min(kBucketCap, count - t0);
-                __syncthreads();
-                for (int i = tid; i < cnt; i += NT) { const Element o = elems[t0 + i]; A.key[i] = key_of(o.q, o.p); ids[i] = o.id; }
-                __syncthreads();
-                for (int i = 0; i < cnt; ++i) rank += before(A.key[i], ids[i], key, e.id);
+        // stretches of kBucketCap tokens, each put in order in LDS; every token of the bucket finds how many of it come before itself
+        unsigned long long* key = fp.key0 + row * vs + at; int* rank = fp.byq + row * vs + at;   // later kernels fill them
+        for (int i = tid; i < count; i += NT) { const Element e = elems[i]; key[i] = key_of(e.q, e.p); rank[i] = 0; }
+        for (int t0 = 0; t0 < count; t0 += kBucketCap) {
+            __syncthreads();
+            for (int i = tid; i < kBucketCap; i += NT) {
+                const bool in = t0 + i < count;
+                A.key[i] = in ? key[t0 + i] : ~0ull; ids[i] = in ? elems[t0 + i].id : 0x7fffffff;
             }
-            if (mine) { order[rank] = e.id; pairs[rank] = make_float2(e.p, e.q); rank_of[e.id] = at + rank; }
+            block_bitonic<NT>(A.key, ids, kBucketCap);
+            for (int i = tid; i < count; i += NT) {
+                const unsigned long long k = key[i];
+                const int id = elems[i].id;
+                int lo = 0;
+#pragma unroll
+                for (int step = kBucketCap / 2; step > 0; step >>= 1) if (before(A.key[lo + step - 1], ids[lo + step - 1], k, id)) lo += step;
+                rank[i] += lo + before(A.key[lo], ids[lo], k, id);
+            }
+        }
+        for (int i = tid; i < count; i += NT) {
+            const Element e = elems[i];
+            const int r = rank[i];
+            order[r] = e.id; pairs[r] = make_float2(e.p, e.q); rank_of[e.id] = at + r;
         }
         return;
     }

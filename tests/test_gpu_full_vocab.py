@@ -430,3 +430,27 @@ def test_ratio_order_of_rows_that_their_sample_does_not_show(V, buckets):
     for b in range(5):
         ids = np.flatnonzero(q[b] > 0)
         assert np.array_equal(got[b], ids[np.argsort(-(q[b, ids].astype(np.float64) / p[b, ids].astype(np.float64)), kind="stable")]), b
+
+
+@pytest.mark.parametrize("V", [262147, 1 << 20, (1 << 22) + 3])
+def test_ratio_order_of_rows_with_buckets_above_the_cap(V):
+    """Rows so long that the sample is thin and the buckets are few: some of their buckets, and at last most, hold more tokens than a workgroup
+    keeps in LDS."""
+    rng = np.random.default_rng(V)
+    t = rng.gumbel(size=(1, V))
+    p = np.exp(2.0 * t); q = np.exp(1.5 * t + rng.standard_normal((1, V)))
+    p = (p / p.sum()).astype(np.float32); q = (q / q.sum()).astype(np.float32)
+    assert (q > 0).all()
+    got, = _orders(p, q)
+    assert np.array_equal(got, np.argsort(-(q[0].astype(np.float64) / p[0].astype(np.float64)), kind="stable"))
+
+
+def test_the_longest_rows_take_their_share_of_time():
+    """Four times the tokens, with buckets four times as full: the call grows in proportion (4.2 times), not with the square of the buckets
+    (9 times)."""
+    rng = np.random.default_rng(5)
+    def us(V):
+        t = rng.standard_normal((1, V), dtype=np.float32)
+        p = np.exp(3.0 * t); q = np.exp(2.0 * t + rng.standard_normal((1, V), dtype=np.float32))
+        return _solve_us(p / p.sum(dtype=np.float64).astype(np.float32), q / q.sum(dtype=np.float64).astype(np.float32))
+    assert us((1 << 24) - 1) < 6.5 * us(1 << 22)
