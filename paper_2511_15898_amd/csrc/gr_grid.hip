@@ -53,7 +53,7 @@ struct GridLds {
     unsigned long long prefix[kSweepMaxK];         // the search: the threshold's digits so far; then the thresholds
     int need[kSweepMaxK], bucket[kSweepMaxK];
     double best[kSweepMaxK][kSweepMaxN], limit[kSweepMaxK][kSweepMaxN];   // limit: what a smaller F has to be below
-    double low[kSweepMaxN][kNW];
+    double low[kSweepMaxN][kNW][16];               // of a wave's groups of four lanes
     double mass[kSweepMaxK], inv_mass[kSweepMaxK];
     double red[kNW];
     int flag[kBins];
@@ -67,14 +67,13 @@ __device__ __forceinline__ unsigned long long ratio_key(float q, float p) {
     const double r = p > 0.f ? static_cast<double>(q) / static_cast<double>(p) : __builtin_inf();
     return kInf - static_cast<unsigned long long>(__double_as_longlong(r));
 }
-// Whether what a token's values have below a unit counts as one: even over the tokens, the same for a token at every look; below 2^31.
-__device__ __forceinline__ unsigned odds_of(int id) { return static_cast<unsigned>(id) * 0x9E3779B1u >> 1; }
+// Whether what a token's values have below a unit counts as one: even over the tokens, the same for a token at every look.
+__device__ __forceinline__ float odds_of(int id) { return static_cast<float>(static_cast<unsigned>(id) * 0x9E3779B1u) * 0x1p-32f; }
 // v in units of 2^-62, v in [0, 2).  Values of 2^-39 and more are whole; the fraction that a smaller one leaves counts as a unit with that probability,
 // so that a sum of many small values errs by half a unit times the root of their number, and not by half a unit each.
-__device__ __forceinline__ unsigned long long fixed62(float v, unsigned odds) {
-    const unsigned b = __float_as_uint(v), down = 127u - (b >> 23), s = min(down, 63u);
-    const unsigned m = (((b & 0x7FFFFFu) | 0x800000u) << 7) >> min(down - s, 31u);     // 24 bits below bit 31, fewer and none below 2^-64
-    return static_cast<unsigned long long>(m + (odds >> min(63u - s, 31u))) << 32 >> s;
+__device__ __forceinline__ unsigned long long fixed62(float v, float odds) {
+    const float a = v * 0x1p30f, t = __builtin_amdgcn_fractf(a) * 0x1p32f;            // both exact
+    return (static_cast<unsigned long long>(static_cast<unsigned>(a)) << 32) + static_cast<unsigned>(t) + (__builtin_amdgcn_fractf(t) > odds);
 }
 // Bins of the first round, by the ratio's place x in 32nds of an octave: 32 to an octave from 2^-5 to 2^5, where thresholds lie (a token is taken up to
 // a ratio of about 1 / n, in the support's own scale), two to an octave out to 2^-53 and 2^52, one for what lies beyond on either side, and one for
@@ -195,10 +194,10 @@ __device__ __forceinline__ void powers(const GridParams& gp, const double (&x)[N
 #pragma unroll
     for (int i = 0; i < N; ++i) pw[i] = x[i];
 #pragma unroll 1
-    for (int slot = 0;;) {
+    for (int slot = 0, more = 63 - __builtin_clzll(left);; --more) {
         if (left & 1ull) { g(slot); ++slot; }
+        if (more == 0) break;
         left >>= 1;
-        if (left == 0ull) break;
 #pragma unroll
         for (int i = 0; i < N; ++i) pw[i] = __dmul_rn(pw[i], x[i]);
     }
@@ -314,8 +313,13 @@ __global__ __launch_bounds__(kNT) void grid_kernel(GridParams gp) {
         const unsigned b = __float_as_uint(qv);
         int cls = 0;
         bool ties = false;
+        auto compare = [&](int from, int to) {
 #pragma unroll
-        for (int a = 0; a < kSweepMaxK; ++a) { cls += b < thr_q[a]; ties |= b == thr_q[a]; }
+            for (int a = from; a < to; ++a) { cls += b < thr_q[a]; ties |= b == thr_q[a]; }
+        };
+        compare(0, 2);
+        if (nk > 2) compare(2, 4);
+        if (nk > 4) compare(4, kSweepMaxK);
         if (ties) {
             const unsigned low = 0xFFFFFFFFu - static_cast<unsigned>(id);
 #pragma unroll
@@ -324,7 +328,7 @@ __global__ __launch_bounds__(kNT) void grid_kernel(GridParams gp) {
         return qv > 0.f ? cls : nk;
     };
     auto add = [&](int cls, int bin, float pv, float qv, int id) {
-        const unsigned odds = odds_of(id);
+        const float odds = odds_of(id);
         atomicAdd(&S.sum[0][cls][bin], fixed62(pv, odds));
         atomicAdd(&S.sum[1][cls][bin], fixed62(qv, odds));
         atomicAdd(&S.count[cls][bin], 1);
@@ -444,7 +448,9 @@ __global__ __launch_bounds__(kNT) void grid_kernel(GridParams gp) {
             lo = S.open[i].lo + (static_cast<unsigned long long>(j & ((1 << log_per) - 1)) << S.shift[i]);
             hi = min(S.open[i].hi, lo + (1ull << S.shift[i]));
         };
-        // F at the bins' last places, two waves to a top-k size: their lanes take four bins each, so that few minima go over the lanes
+        // F at the bins' last places, two waves to a top-k size: their lanes take four bins each, and a draft count's minimum goes over four lanes; all
+        // others wait until the last count, as the loops over the counts are chains of one instruction's latency after the other (minima over the wave
+        // and their limits read from LDS at every count: 1024 rows of 300 tokens, eight sizes and 16 counts 155 us, so 143; one row 39 and 37).
         if (wv < 2 * nk) {
             constexpr int PER = kBins / 128;
             double p[PER], x[PER], pw[PER];
@@ -458,15 +464,22 @@ __global__ __launch_bounds__(kNT) void grid_kernel(GridParams gp) {
                 double m = p[0] - pw[0];
 #pragma unroll
                 for (int i = 1; i < PER; ++i) m = fmin(m, p[i] - pw[i]);
-                m = wave_min(m);
-                if (lane == 0) S.low[slot][wv] = m;
+                m = fmin(m, dpp_move<kDppXor1>(m));
+                m = fmin(m, dpp_move<kDppXor2>(m));
+                if ((lane & 3) == 0) S.low[slot][wv][lane >> 2] = m;
             });
         }
         __syncthreads();
-        if (tid < kSweepMaxK * kSweepMaxN) {
-            const int a = tid / kSweepMaxN, slot = tid % kSweepMaxN;
-            if (a < nk && slot < slots) {
-                const double m = fmin(S.best[a][slot], fmin(S.low[slot][2 * a], S.low[slot][2 * a + 1]));
+        {
+            static_assert(kNT == 8 * kSweepMaxK * kSweepMaxN, "eight lanes to a size and draft count, four minima of the two waves' 32 to a lane");
+            const int a = tid / (8 * kSweepMaxN), slot = tid / 8 % kSweepMaxN, part = tid % 8;
+            const double* low = &S.low[slot][2 * a][0] + 4 * part;
+            double m = fmin(fmin(low[0], low[1]), fmin(low[2], low[3]));
+            m = fmin(m, dpp_move<kDppXor1>(m));
+            m = fmin(m, dpp_move<kDppXor2>(m));
+            m = fmin(m, dpp_move<kDppHalfMirror>(m));
+            if (part == 0 && a < nk && slot < slots) {
+                m = fmin(m, S.best[a][slot]);
                 S.best[a][slot] = m;
                 S.limit[a][slot] = m - (1e-13 * (1.0 + m) + 1e-16);   // what is not looked for is below 1e-13 of the acceptance
             }
@@ -494,11 +507,13 @@ __global__ __launch_bounds__(kNT) void grid_kernel(GridParams gp) {
                     some = true;
                 }
             }
+            static_assert(kItems * kSweepMaxN == 64, "a wave's limits, one to a lane");
+            const double limit = S.limit[min(2 * (lane / kSweepMaxN) + odd, nk - 1)][lane % kSweepMaxN];
             bool less = false;
             if (__any(some))
                 powers(gp, qx, pw, [&](int slot) {
 #pragma unroll
-                    for (int i = 0; i < kItems; ++i) less |= px[i] - pw[i] < S.limit[min(2 * i + odd, nk - 1)][slot];
+                    for (int i = 0; i < kItems; ++i) less |= px[i] - pw[i] < read_lane(limit, i * kSweepMaxN + slot);
                 });
             if (less) S.flag[j] = 1;
         }
