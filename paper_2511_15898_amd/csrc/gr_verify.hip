@@ -6,7 +6,7 @@
 //                     residuals p(i) - p_i (the residual lift of Eq. (3));
 //   otherwise       : all mass stays on the drafted tokens of the block that holds the lowest-ratio
 //                     draft, softmax of that block's weights.
-// Rows whose solve failed use pi = p.  One 256-thread workgroup per row.
+// Rows whose solve failed use pi = p.  One 256-thread workgroup per row, registers for four of them to a compute unit: 1024 rows are all in work at once.
 #include <algorithm>
 
 #include "gr_internal.h"
@@ -53,7 +53,7 @@ __device__ void tile_weights(double* w, const Slice& S, const RowInfo& info, con
 
 }  // namespace
 
-__global__ __launch_bounds__(kThreads) void verify_kernel(
+__global__ __launch_bounds__(kThreads, 4) void verify_kernel(
     const float* __restrict__ p, int V, int n, PolicyView pv, const RowInfo* __restrict__ infos,
     const int* __restrict__ drafts, const float* __restrict__ uniforms, int* __restrict__ token,
     unsigned char* __restrict__ accepted) {

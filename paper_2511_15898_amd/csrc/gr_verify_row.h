@@ -216,11 +216,12 @@ __device__ inline void verify_row(VerifyLds& vl, const float* prow, int V, int n
                 if (lane == 0) seg[pc] = f * sa;
             }
         } else if (dense) {
-            // four pieces of a wave and eight loads of each in flight (one piece and sixteen loads at a time: 64 rows of 32000
-            // tokens 29.6 and 16.8 us, 1024 of 128256 150 and 84)
-            constexpr int G = 4;
+            // Two pieces of a wave and eight loads of each in flight, in registers for four workgroups to a compute unit.  The call, 1024 rows of 257 / 8192 /
+            // 128256 tokens 14.8 / 21 / 97 us, 64 of 32000 22.8; four pieces, three workgroups 17.9 / 24 / 106, 23.0; one piece, sixteen loads one after the
+            // other 14.5 / 22 / 188, 22.8.
+            constexpr int G = 2;
             for (int pc = wvv; pc < np; pc += G * kWaves) {
-                double sum[G] = {0.0, 0.0, 0.0, 0.0};
+                double sum[G] = {0.0, 0.0};
                 for (int t0 = 0; t0 < cs; t0 += 8 * 64) {
                     double x[G][8];
 #pragma unroll
