@@ -48,10 +48,12 @@ __device__ __forceinline__ int padded(int count) { return (count + kScan - 1) / 
 template <int D> constexpr int kThreadsOf = D > 8 ? 256 : 512;
 template <int D> constexpr int kWavesOf = D > 8 ? 1 : 2;
 // With more rows than compute units, two workgroups of four waves share one up to 8 drafts: while one row's stepping wave or its prologue keeps the other waves
-// waiting, the other row evaluates.  The call, one workgroup and two: 257 rows of 32000 tokens, n = 4, k = 64 130 and 142 us, 300 192 and 165, 512 217 and 178;
-// 1024 rows of 1024, n = 4, k = 32 246 and 169, of 128256, n = 8, k = 128 611 and 507 (selection 210).  Rows beyond the compute units must wait for one of them
-// to end, which a handful can do behind the batch's slowest row: the line lies a little above their number.
-constexpr int kNarrow = 256, kChip = 264;
+// waiting, the other row evaluates.  The call, one workgroup and two: 300 rows of 32000 tokens, n = 4, k = 64 192 and 165 us, 512 217 and 178;
+// 1024 rows of 1024, n = 4, k = 32 246 and 169, of 128256, n = 8, k = 128 611 and 507 (selection 210).  A row by itself is slower on four waves, up to 0.76 times
+// where its program takes the fallback, and a handful of rows beyond the compute units begins behind the rows that end first, before the slowest one has: 12
+// kinds of rows (n 1 to 8, k 16 to 256, V 400 to 50000), three seeds, one workgroup's time over two's, in the mean and the calls that lose more than 2 %:
+// 264 rows 1.00 and 19 of 36, 288 1.05 and 14, 304 1.09 and 8, 320 1.11 and 7, 384 1.16 and 3, 512 1.28 and 1.
+constexpr int kNarrow = 256, kOne = 304;   // kOne: rows of a batch that have a compute unit each, or wait for one
 constexpr double kQuadStep = 0.45;   // trapezoid step in log t (discretisation error 5.6e-9 relative at most)
 constexpr double kQuadLo = 0.1;      // t_lo * (slack + sum w)
 // The nodes below t_lo, t_lo e^{-step k}, are not evaluated: the integrand over t, a sum of e^{-s t} with s (slack + sum w)^-1
@@ -2126,7 +2128,7 @@ static Chosen choose(int which, int n, bool narrow) {
 }
 
 hipError_t launch_full_programs(const FullParams& fp, hipStream_t stream) {
-    const Chosen c = choose(kPrograms, fp.n, fp.B > kChip);
+    const Chosen c = choose(kPrograms, fp.n, fp.B > kOne);
     void* args[] = {const_cast<FullParams*>(&fp)};
     (void)hipLaunchKernel(c.kernel, dim3(fp.B), dim3(c.threads), args, c.lds, stream);
     return hipGetLastError();                                    // which clears it: the next call asks again
@@ -2140,7 +2142,7 @@ static_assert(sizeof(Lds<8, kNarrow>) <= 80 * 1024 && sizeof(Lds<4, kNarrow>) <=
 // its inputs and its drafts: 353 us with eight kernels, 407 with two more, in every gr_create.)
 hipError_t solve_kernel_setup(int max_n, int max_B, bool hbm) {
     for (int which = kSolve; which <= (hbm ? kPrograms : kSolve); ++which)
-        for (int narrow = 0; narrow <= (max_B > kChip ? 1 : 0); ++narrow)
+        for (int narrow = 0; narrow <= (max_B > kOne ? 1 : 0); ++narrow)
             for (int n = 2; n <= GR_MAX_N && (n == 2 || n < 2 * max_n); n *= 2) {   // n: the series degrees that serve up to max_n
                 if (narrow && n > 8) continue;
                 const Chosen c = choose(which, n, narrow != 0);
@@ -2151,7 +2153,7 @@ hipError_t solve_kernel_setup(int max_n, int max_B, bool hbm) {
 }
 
 hipError_t launch_solve(const SolveParams& sp, hipStream_t stream) {
-    const Chosen c = choose(kSolve, sp.n, sp.B > kChip);
+    const Chosen c = choose(kSolve, sp.n, sp.B > kOne);
     void* args[] = {const_cast<SolveParams*>(&sp)};
     (void)hipLaunchKernel(c.kernel, dim3(sp.B), dim3(c.threads), args, c.lds, stream);
     return hipGetLastError();                                    // which clears it: the next call asks again
