@@ -546,9 +546,10 @@ extern "C" int gr_tree_walk(gr_handle h, const float* p, const float* q, const f
     for (int i = 0; i < S * L; ++i) out_tokens[i] = -1;
     // A batch: nodes of the tree (a sequence, the paths through the node, its level), each with a row of its own.  The children of node i are
     // nodes child[i] .. child[i + 1] - 1, its row in the batch row_of[i].
-    struct Node { int s, l; unsigned paths; };
+    struct Node { int s, l; unsigned paths; int n; };            // n: how many paths
     std::vector<Node> nodes;
     std::vector<int> child, by_n, row_of;
+    nodes.reserve(static_cast<size_t>(S) + kWalkRows); child.reserve(kWalkRows);
     bool no_room = false;                                        // for a larger batch, in this walk
     const auto token_of = [&](const Node& x, int a) { return paths[(static_cast<size_t>(x.s) * K + a) * L + x.l]; };
     for (int l = 0; l < L;) {
@@ -562,26 +563,27 @@ extern "C" int gr_tree_walk(gr_handle h, const float* p, const float* q, const f
         for (int group = in_lds ? K : 1; group <= K; ++group) {
             nodes.clear(); child.clear();
             for (int s = 0; s < S; ++s)
-                if (alive[s] && (in_lds || __builtin_popcount(active[s]) == group)) nodes.push_back(Node{s, l, active[s]});
+                if (alive[s]) { const int n = __builtin_popcount(active[s]); if (in_lds || n == group) nodes.push_back(Node{s, l, active[s], n}); }
             if (nodes.empty()) continue;
             const size_t roots = nodes.size();
             if (in_lds) {
                 int bound = 0;                                       // nodes of the levels left: their paths each, at most
-                for (const Node& x : nodes) bound += __builtin_popcount(x.paths);
+                for (const Node& x : nodes) bound += x.n;
                 bound = std::min(kWalkRows, bound * (L - l));
                 size_t from = 0;                                     // the first node of the last level taken
                 for (; next_l < L; ++next_l) {
                     const size_t to = nodes.size(), least = to - from;   // a node has a child at least
                     child.resize(from);
                     if (least > static_cast<size_t>(kWalkLevelRows) || to + least > static_cast<size_t>(kWalkRows)) break;
-                    for (size_t i = from; i < to; ++i) {
+                    for (size_t i = from; i < to && nodes.size() - to <= static_cast<size_t>(kWalkLevelRows); ++i) {   // no further than what is taken
                         child.push_back(static_cast<int>(nodes.size()));
                         const Node x = nodes[i];
                         for (unsigned left = x.paths; left;) {
                             unsigned same = 0u;
+                            int n = 0;
                             const int t = token_of(x, __builtin_ctz(left));
-                            for (int a = 0; a < K; ++a) if ((left >> a & 1u) && token_of(x, a) == t) same |= 1u << a;
-                            nodes.push_back(Node{x.s, next_l, same});
+                            for (int a = __builtin_ctz(left); a < K; ++a) if ((left >> a & 1u) && token_of(x, a) == t) { same |= 1u << a; ++n; }
+                            nodes.push_back(Node{x.s, next_l, same, n});
                             left &= ~same;
                         }
                     }
@@ -596,9 +598,9 @@ extern "C" int gr_tree_walk(gr_handle h, const float* p, const float* q, const f
             // long solves first: rows beyond the number of compute units wait for one to end
             by_n.resize(cnt); row_of.resize(cnt);
             int at[GR_MAX_N + 2] = {}, most = 0;                     // at[K - n]: the row of the next node of n paths
-            for (const Node& x : nodes) { const int n = __builtin_popcount(x.paths); most = std::max(most, n); ++at[K - n + 1]; }
+            for (const Node& x : nodes) { most = std::max(most, x.n); ++at[K - x.n + 1]; }
             for (int n = 1; n <= K; ++n) at[n] += at[n - 1];
-            for (int i = 0; i < cnt; ++i) { const int j = at[K - __builtin_popcount(nodes[i].paths)]++; row_of[i] = j; by_n[j] = i; }
+            for (int i = 0; i < cnt; ++i) { const int j = at[K - nodes[i].n]++; row_of[i] = j; by_n[j] = i; }
             const size_t at_n = sizeof(long long) * cnt, at_d = at_n + sizeof(int) * cnt, at_u = at_d + sizeof(int) * cnt * most,
                          at_t = at_u + sizeof(float) * cnt, in_bytes = at_t + sizeof(float) * cnt;
             long long* const idx = reinterpret_cast<long long*>(h->tw_host);
@@ -607,7 +609,7 @@ extern "C" int gr_tree_walk(gr_handle h, const float* p, const float* q, const f
             for (int j = 0; j < cnt; ++j) {
                 const Node x = nodes[by_n[j]];
                 idx[j] = ((static_cast<long long>(x.s) * K + __builtin_ctz(x.paths)) * L + x.l) * V;
-                ns[j] = __builtin_popcount(x.paths);
+                ns[j] = x.n;
                 int* d = drafts + static_cast<size_t>(j) * most;
                 for (int a = 0; a < K; ++a) if (x.paths >> a & 1u) *d++ = token_of(x, a);
                 for (; d < drafts + static_cast<size_t>(j + 1) * most; ++d) *d = 0;
