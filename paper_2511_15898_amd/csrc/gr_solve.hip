@@ -49,11 +49,18 @@ template <int D> constexpr int kThreadsOf = D > 8 ? 256 : 512;
 template <int D> constexpr int kWavesOf = D > 8 ? 1 : 2;
 // With more rows than compute units, two workgroups of four waves share one up to 8 drafts: while one row's stepping wave or its prologue keeps the other waves
 // waiting, the other row evaluates.  The call, one workgroup and two: 300 rows of 32000 tokens, n = 4, k = 64 192 and 165 us, 512 217 and 178;
-// 1024 rows of 1024, n = 4, k = 32 246 and 169, of 128256, n = 8, k = 128 611 and 507 (selection 210).  A row by itself is slower on four waves, up to 0.76 times
-// where its program takes the fallback, and a handful of rows beyond the compute units begins behind the rows that end first, before the slowest one has: 12
+// 1024 rows of 1024, n = 4, k = 32 246 and 169, of 128256, n = 8, k = 128 611 and 507 (selection 210).  A row by itself is slower on four waves, and a handful of rows
+// beyond the compute units begins behind the rows that end first, before the slowest one has: 12
 // kinds of rows (n 1 to 8, k 16 to 256, V 400 to 50000), three seeds, one workgroup's time over two's, in the mean and the calls that lose more than 2 %:
 // 264 rows 1.00 and 19 of 36, 288 1.05 and 14, 304 1.09 and 8, 320 1.11 and 7, 384 1.16 and 3, 512 1.28 and 1.
 constexpr int kNarrow = 256, kOne = 304;   // kOne: rows of a batch that have a compute unit each, or wait for one
+// A program that asks for more than kPatience evaluations there, or for the fallback, leaves its row to a second launch, of one workgroup to a compute unit, in
+// which it goes on from its best weights and the workgroups of all other rows end at once (2 us): of 43000 rows of 14 kinds one took 1005 evaluations, one 68 and
+// all others 19 at most, and where there is such a row it is the call (1024 rows of 1000 tokens, n = 4, k = 32, 1005 evaluations: 9.9 ms in workgroups of eight
+// waves, 13.1 of four, 9.6 so; of 50000, n = 2, k = 256, 68 of them: 0.80, 0.84 and 0.87).
+constexpr int kPatience = 24;
+template <int D, int ST> constexpr bool kDefers = D <= 8 && ST == kNarrow;
+constexpr int kDeferred = -1;        // of a program; RowInfo::status of its row between the launches: -1 - the program's number
 constexpr double kQuadStep = 0.45;   // trapezoid step in log t (discretisation error 5.6e-9 relative at most)
 constexpr double kQuadLo = 0.1;      // t_lo * (slack + sum w)
 // The nodes below t_lo, t_lo e^{-step k}, are not evaluated: the integrand over t, a sum of e^{-s t} with s (slack + sum w)^-1
@@ -101,7 +108,7 @@ struct Nothing {};
 template <int D, int ST = kThreadsOf<D>>
 struct Lds {
     static constexpr int kST = ST;
-    static constexpr bool kKeeps = !(D <= 8 && ST == kNarrow);
+    static constexpr bool kKeeps = !kDefers<D, ST>;
     static constexpr int kSW = kST / 64;
     static constexpr int kNPW = D > 8 ? 16 : 4;               // quadrature nodes a wave owns within a chunk
     static constexpr int kChunk = kSW * kNPW;
@@ -1425,7 +1432,7 @@ __device__ __attribute__((noinline)) StepState newton_step(StepState st, int m, 
 // Solve one program by Newton's iteration with a reduced Hessian (newton_step).  Returns 0 when converged.
 // In: L.aq (decreasing), L.at (targets, already scaled to the tuple mass), L.aal (start log weights) and L.apos, the first three
 // written by the thread of their token; qsum = sum aq, tsum = sum at.
-// Out: L.aal, L.apos, in the program's own order of tokens.  `evals` counts evaluator calls (summed over the row's programs;
+// Out: L.aal, L.apos, in the program's own order of tokens.  Returns 0, 1 (not converged) or kDeferred.  `evals` counts evaluator calls (summed over the row's programs;
 // max_iter caps this program's).
 template <int D, int ST>
 __device__ __forceinline__ int solve_program(Lds<D, ST>& L, int& par, double* newton_ws, int m, int n, double ctx, int slack, double slack_target,
@@ -1529,7 +1536,8 @@ __device__ __forceinline__ int solve_program(Lds<D, ST>& L, int& par, double* ne
     GR_CLK(L, 5);
     double fact = 1.0;
     for (int i = 2; i <= n; ++i) fact *= i;
-    const int step_iters = (max_iter > kStarBudget + m) ? kStarBudget + m : max_iter;
+    const int full_iters = (max_iter > kStarBudget + m) ? kStarBudget + m : max_iter;
+    const int step_iters = kDefers<D, ST> ? min(full_iters, kPatience) : full_iters;
     // The iteration is steered by wave 0 alone (lane l holds tokens l and l + 64, so every reduction over the
     // tokens is a wave reduction and the step needs no workgroup exchange); all waves evaluate.  Per
     // iteration: barrier, evaluation by all waves, barrier, the waves' sums, barrier, the step by wave 0 (the others wait at the next
@@ -1602,6 +1610,11 @@ __device__ __forceinline__ int solve_program(Lds<D, ST>& L, int& par, double* ne
     int result = L.ctl_result;
     const bool bestok = L.ctl_bestok != 0;
     GR_CLK(L, 12);
+    if constexpr (kDefers<D, ST>) {
+        if (result == 0 || !((L.ctl_go && step_iters < full_iters) || (full_iters < max_iter && bestok))) return result;
+        if (bestok && tid < m) L.aal[tid] = L.aBest[tid];
+        return kDeferred;
+    }
     if (result != 0 && step_iters < max_iter && bestok) {
         if (tid < m) L.aal[tid] = L.aBest[tid];
         __syncthreads();
@@ -1641,6 +1654,8 @@ __global__ __launch_bounds__(ST, kWavesOf<D>) void solve_kernel(SolveParams sp) 
     Lds<D, ST>& L = *reinterpret_cast<Lds<D, ST>*>(gr_lds_raw);
     const int tid = threadIdx.x;
     const int row = blockIdx.x;
+    const bool again = !kDefers<D, ST> && sp.deferred;      // uniform: the rows that the launch before has left
+    if (again && sp.info[row].status >= 0) return;
     const int n = sp.row_n ? sp.row_n[row] : sp.n, V = sp.V;
     const float* const prow = sp.p + (sp.row_at ? static_cast<size_t>(sp.row_at[row]) : static_cast<size_t>(row) * V);
     RowInfo info;
@@ -1682,7 +1697,7 @@ __global__ __launch_bounds__(ST, kWavesOf<D>) void solve_kernel(SolveParams sp) 
         return;
     }
     gather_keys<kST>(L.keys, sp.cand + static_cast<size_t>(row) * kSelCap, found, sp.splits);
-    if (tid == 0) { L.count = 0; L.work = 0.0; }
+    if (tid == 0) { L.count = 0; L.work = again ? sp.info[row].node_tokens : 0.0; }
 #ifdef GR_PHASE_CLOCKS
     if (tid == 0) { for (int i = 0; i < 24; ++i) L.clk[i] = 0; L.clk_last = clock64(); }
 #endif
@@ -1907,7 +1922,7 @@ __global__ __launch_bounds__(ST, kWavesOf<D>) void solve_kernel(SolveParams sp) 
         const double top = L.Q[hi];
         const double gauge = (tid < h) ? ipow(top, n) / (-L.F[h]) : 1.0;
         const double t = L.tgt[tid];
-        L.wgt[tid] = (t > 0.0) ? gauge * t / pow_diff(top, L.qn[tid], n) : 0.0;
+        L.wgt[tid] = again ? sp.weight[static_cast<size_t>(row) * KS + tid] : ((t > 0.0) ? gauge * t / pow_diff(top, L.qn[tid], n) : 0.0);
     }
     __syncthreads();
 
@@ -1920,7 +1935,8 @@ __global__ __launch_bounds__(ST, kWavesOf<D>) void solve_kernel(SolveParams sp) 
     if constexpr (!Lds<D, ST>::kKeeps) write_rows();
 
     // ---- the convex programs: program 0 = inner system, then every outer block of two or more tokens
-    int status = GR_ROW_OK, evals = 0, par = 0;
+    int status = GR_ROW_OK, evals = again ? sp.info[row].iterations : 0, par = 0;
+    const int half_done = again ? -1 - sp.info[row].status : -1;
     for (int b = (h > 0 ? 0 : 1); b <= nblk && status != GR_ROW_TRUNC_CAP; ++b) {
         const int lo = (b == 0) ? 0 : L.blo[b];
         const int hi = (b == 0) ? h : L.blo[b + 1];
@@ -1953,12 +1969,17 @@ __global__ __launch_bounds__(ST, kWavesOf<D>) void solve_kernel(SolveParams sp) 
         if (tid < m) L.at[tid] = t0 * scale;
         GR_CLK(L, 4);
         const int rc = solve_program<D>(L, par, sp.newton_ws + static_cast<size_t>(row) * kMaxT * (kMaxT + 1), m, n, ctx, b == 0, slack_target,
-                                        qa, ta * scale, sp.rel_tol, sp.max_iter, &evals);
-        if (rc != 0 && status == GR_ROW_OK) status = GR_ROW_ITER_CAP;
+                                        qa, ta * scale, sp.rel_tol, sp.max_iter - (b == half_done ? kPatience : 0), &evals);
+        if (rc > 0 && status == GR_ROW_OK) status = GR_ROW_ITER_CAP;
         const double wv = (tid < m) ? exp(L.aal[tid]) : 0.0;
         const double wsum = (b == 0) ? 1.0 : wg_sum(L, par, wv);
-        if (tid < m) L.wgt[L.apos[tid]] = (b == 0) ? wv : wv * (w0sum / wsum);
+        if (tid < m && (rc >= 0 || L.ctl_bestok)) L.wgt[L.apos[tid]] = (b == 0) ? wv : wv * (w0sum / wsum);
         __syncthreads();
+        if (kDefers<D, ST> && rc < 0) {
+            if (tid < kk) sp.weight[static_cast<size_t>(row) * KS + tid] = L.wgt[tid];
+            if (tid == 0) { RowInfo& left = sp.info[row]; left.status = -1 - b; left.iterations = evals; left.node_tokens = L.work; }
+            return;
+        }
     }
 
     if constexpr (Lds<D, ST>::kKeeps) write_rows();
@@ -2003,8 +2024,10 @@ __global__ __launch_bounds__(ST, kWavesOf<D>) void full_programs_kernel(FullPara
     const int n = fp.n, V = fp.V;
     const size_t vs = static_cast<size_t>(V) + 2;
     RowInfo info = fp.info[row];
-    if (info.status == GR_ROW_BAD) return;
-    if (info.status != GR_ROW_OK) return;                  // above the cap on |T|: sampled from p
+    const bool again = !kDefers<D, ST> && fp.deferred;      // uniform: the rows that the launch before has left
+    if (again ? info.status >= 0 : info.status != GR_ROW_OK) return;   // bad, or above the cap on |T|: sampled from p
+    const int half_done = again ? -1 - info.status : -1;
+    auto leave = [&](int b, int evals) { if (tid == 0) { RowInfo& left = fp.info[row]; left.status = -1 - b; left.iterations = evals; left.node_tokens = L.work; } };
     const int kk = info.support, h = info.h;
     const RowValues val(fp, info, row);
     const int* byq = fp.byq + row * vs;
@@ -2015,10 +2038,10 @@ __global__ __launch_bounds__(ST, kWavesOf<D>) void full_programs_kernel(FullPara
     const double Fh = -info.res_total, stot = Q[kk];
     auto qn = [&](int r) { return val.q(by_rank[r].y) / stot; };
     auto target = [&](int r) { return val.p(by_rank[r].x) - rho[r]; };
-    if (tid == 0) L.work = 0.0;
+    if (tid == 0) L.work = info.node_tokens;                // 0 but for the rows left
     __syncthreads();
 
-    int status = GR_ROW_OK, evals = 0, par = 0;
+    int status = GR_ROW_OK, evals = info.iterations, par = 0;
     // ---- inner program: T inside H* is the first tcount[0] entries of byq, already by decreasing q
     if (h > 0) {
         const int c_in = fp.tcount[3 * row];
@@ -2050,9 +2073,10 @@ __global__ __launch_bounds__(ST, kWavesOf<D>) void full_programs_kernel(FullPara
             if (tid < m) L.at[tid] *= scale;
             __syncthreads();
             const int rc = solve_program<D>(L, par, fp.newton_ws + static_cast<size_t>(row) * kMaxT * (kMaxT + 1), m, n, ctx, 1, slack_target,
-                                            qa, ta * scale, fp.rel_tol, fp.max_iter, &evals);
-            if (rc != 0) status = GR_ROW_ITER_CAP;
-            if (tid < m) weight[L.apos[tid]] = exp(L.aal[tid]);
+                                            qa, ta * scale, fp.rel_tol, fp.max_iter - (half_done == 0 ? kPatience : 0), &evals);
+            if (rc > 0) status = GR_ROW_ITER_CAP;
+            if (tid < m && (rc >= 0 || L.ctl_bestok)) weight[L.apos[tid]] = exp(L.aal[tid]);
+            if (kDefers<D, ST> && rc < 0) { leave(0, evals); return; }
             __syncthreads();
         }
     }
@@ -2097,11 +2121,12 @@ __global__ __launch_bounds__(ST, kWavesOf<D>) void full_programs_kernel(FullPara
             if (tid < m) L.at[tid] *= scale;
             __syncthreads();
             const int rc = solve_program<D>(L, par, fp.newton_ws + static_cast<size_t>(row) * kMaxT * (kMaxT + 1), m, n, ctx, 0, 0.0,
-                                            qa, ta * scale, fp.rel_tol, fp.max_iter, &evals);
-            if (rc != 0 && status == GR_ROW_OK) status = GR_ROW_ITER_CAP;
+                                            qa, ta * scale, fp.rel_tol, fp.max_iter - (half_done == b ? kPatience : 0), &evals);
+            if (rc > 0 && status == GR_ROW_OK) status = GR_ROW_ITER_CAP;
             const double wvv = (tid < m) ? exp(L.aal[tid]) : 0.0;
             const double wsum = block_sum<kSW>(wvv, L.redn);
-            if (tid < m) weight[L.apos[tid]] = wvv * (w0sum / wsum);
+            if (tid < m && (rc >= 0 || L.ctl_bestok)) weight[L.apos[tid]] = wvv * (w0sum / wsum);
+            if (kDefers<D, ST> && rc < 0) { leave(b, evals); return; }
             __syncthreads();
         }
         __syncthreads();
@@ -2127,12 +2152,21 @@ static Chosen choose(int which, int n, bool narrow) {
     return chosen<16, kThreadsOf<16>>(which);
 }
 
-hipError_t launch_full_programs(const FullParams& fp, hipStream_t stream) {
-    const Chosen c = choose(kPrograms, fp.n, fp.B > kOne);
-    void* args[] = {const_cast<FullParams*>(&fp)};
-    (void)hipLaunchKernel(c.kernel, dim3(fp.B), dim3(c.threads), args, c.lds, stream);
-    return hipGetLastError();                                    // which clears it: the next call asks again
+// A batch on the workgroups that suit it; the rows that the small ones leave, on the large ones.
+template <class Params>
+static hipError_t launch_rows(int which, Params params, hipStream_t stream) {
+    const bool narrow = params.B > kOne && params.n <= 8;
+    void* args[] = {&params};
+    for (params.deferred = 0; params.deferred <= (narrow ? 1 : 0); ++params.deferred) {
+        const Chosen c = choose(which, params.n, narrow && !params.deferred);
+        (void)hipLaunchKernel(c.kernel, dim3(params.B), dim3(c.threads), args, c.lds, stream);
+        const hipError_t e = hipGetLastError();                  // which clears it: the next call asks again
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
+
+hipError_t launch_full_programs(const FullParams& fp, hipStream_t stream) { return launch_rows(kPrograms, fp, stream); }
 
 static_assert(sizeof(Lds<16>) + 20 * 1024 <= 160 * 1024,
               "the solve workgroup's state and one streaming workgroup of the next batch must fit the CU's LDS together");
@@ -2152,11 +2186,6 @@ hipError_t solve_kernel_setup(int max_n, int max_B, bool hbm) {
     return hipSuccess;
 }
 
-hipError_t launch_solve(const SolveParams& sp, hipStream_t stream) {
-    const Chosen c = choose(kSolve, sp.n, sp.B > kOne);
-    void* args[] = {const_cast<SolveParams*>(&sp)};
-    (void)hipLaunchKernel(c.kernel, dim3(sp.B), dim3(c.threads), args, c.lds, stream);
-    return hipGetLastError();                                    // which clears it: the next call asks again
-}
+hipError_t launch_solve(const SolveParams& sp, hipStream_t stream) { return launch_rows(kSolve, sp, stream); }
 
 }  // namespace gr

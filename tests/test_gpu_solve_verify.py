@@ -141,3 +141,42 @@ def test_batches_on_both_workgroup_sizes(n, k, V, logits):
     assert np.array_equal(*st) and np.array_equal(*acc)
     assert np.abs(pi[0] - pi[1]).max() < 1e-6 and np.abs(given[0] - given[1]).max() < 1e-6
     assert (tok[0] != tok[1]).sum() <= 1 and (ok[0] != ok[1]).sum() <= 1      # a uniform on an edge
+
+
+@pytest.mark.parametrize("n,k,V", [(2, 12, 64), (3, 12, 64), (4, 12, 64), (8, 12, 64), (4, 0, 300)])
+def test_programs_that_take_long_in_large_batches(n, k, V):
+    """A tolerance that no evaluation meets: every row with a program of a batch of 310 is left to the second launch, with large workgroups, which goes on
+    from its best weights through the step's budget and the finite differences to the cap.  Its weights must be those of rows solved to 1e-12 in
+    batches of 155.  Bound: w answers to its target R as R / (P - R) does, P the token's draw probability: 1 + w times the measure, summed over the
+    tokens that move with it, for which a thousandfold is allowed at the least.  A cap of 12 evaluations is reached in the first launch."""
+    from dataclasses import replace
+    from parity_util import run_gpu
+    B = 310
+    wl = W.small(B=B, V=V, n=n, k=k, seed_sub=n + 12)
+    part = lambda rows: replace(wl, B=155, p=wl.p[rows], q=wl.q[rows], drafts=wl.drafts[rows], uniforms=wl.uniforms[rows])
+    def run(w, **how):
+        out = run_gpu(w, 1e-5 if k else 0.05, want_slice=False, export_rows=range(w.B), **how)   # a whole row's programs would end above the cap
+        if "rows" in out:
+            for name in ("order", "block", "weight"):
+                out[name] = np.zeros((w.B, V))
+                for b, r in out["rows"].items():
+                    out[name][b, : len(r[name])] = r[name]
+            del out["rows"]
+        return out
+    def both(**how):
+        first, second = run(part(slice(0, 155)), **how), run(part(slice(155, B)), **how)
+        return {name: np.concatenate([first[name], second[name]]) for name in first}
+    solved, out = both(rel_tol=1e-12), run(wl, rel_tol=1e-17, max_iter=200)
+    fine = solved["status"] == 0
+    ran = fine & (solved["iterations"] > 0)
+    assert ran.sum() >= B // 2
+    long = ran & (out["status"] == 2)                          # the measure of a small program can come out 0 exactly
+    assert long.sum() >= 0.9 * ran.sum() and np.all(out["status"][fine & ~long] == 0) and np.all(out["iterations"][long] >= 200)
+    assert np.array_equal(out["accept_prob"], solved["accept_prob"]) and np.array_equal(out["support"], solved["support"])
+    for b in np.flatnonzero(ran):
+        kk = out["support"][b]
+        assert np.array_equal(out["order"][b, :kk], solved["order"][b, :kk]) and np.array_equal(out["block"][b, :kk], solved["block"][b, :kk])
+        w, want = out["weight"][b, :kk], solved["weight"][b, :kk]
+        assert np.array_equal(w > 0, want > 0) and np.abs(w[want > 0] / want[want > 0] - 1.0).max() < 1e-12 * max(1e3, 1.0 + want.max()), b
+    short, halves = run(wl, rel_tol=1e-17, max_iter=12), both(rel_tol=1e-17, max_iter=12)
+    assert np.mean((short["status"] == halves["status"]) & (short["iterations"] == halves["iterations"])) >= 0.9      # a measure of exactly 0 again

@@ -170,5 +170,7 @@ result["over"] = hip.recorded_over()
 """)
     assert r["over"] == 0
     if B == 304:
-        (kernel, rows), = r["batch"]
-        assert rows == "480" and ("Li256E" in kernel), kernel     # more rows than the handle and the chip: the small workgroup (of all with more than 8 drafts)
+        # more rows than the handle, and than have a compute unit each: the small workgroup, then the large one for the rows that it leaves (of all with
+        # more than 8 drafts there is one kernel)
+        sizes = [512 if "Li512E" in kernel else 256 for kernel, rows in r["batch"]]
+        assert sizes == ([256, 512] if max_n <= 8 else [256]) and all(rows == "480" for _, rows in r["batch"]), r["batch"]
