@@ -64,7 +64,6 @@ struct SolveParams {
     // rows of a gathered batch: where they begin in p and q (elements; nullptr: one after the other), their own draft counts [B]
     // (at most n; nullptr: n for all)
     const long long* row_at; const int* row_n;
-    int deferred;                     // 1: only the rows that the launch before has left
 };
 
 // A token of the support on its way into the ratio order.
@@ -92,7 +91,6 @@ struct FullParams {
     int* tcount;       // [B, 3] sizes of the two truncation sets, place of the second in byq
     RowInfo* info; float* accept_prob; int* status;
     double* newton_ws; // [B, kMaxT * (kMaxT + 1)] Jacobian scratch of the Newton fallback
-    int deferred;      // of the programs' launches, as in SolveParams
     // [B, V + 2] the support in the order's buckets, where P and Q (one after the other in the workspace) come later
     __device__ __forceinline__ Element* elements() const { return reinterpret_cast<Element*>(P); }
 };

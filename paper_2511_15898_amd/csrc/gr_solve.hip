@@ -1648,14 +1648,14 @@ __device__ int compact_active(LdsT& L, int lo, int hi, int kk) {
 
 }  // namespace
 
-template <int D, int ST>
+// AGAIN: the launch for the rows that the one before has left (kernels of their own: the others stay as short as they were).
+template <int D, int ST, bool AGAIN>
 __global__ __launch_bounds__(ST, kWavesOf<D>) void solve_kernel(SolveParams sp) {
     constexpr int kST = Lds<D, ST>::kST, kSW = Lds<D, ST>::kSW;
     Lds<D, ST>& L = *reinterpret_cast<Lds<D, ST>*>(gr_lds_raw);
     const int tid = threadIdx.x;
     const int row = blockIdx.x;
-    const bool again = !kDefers<D, ST> && sp.deferred;      // uniform: the rows that the launch before has left
-    if (again && sp.info[row].status >= 0) return;
+    if (AGAIN && sp.info[row].status >= 0) return;
     const int n = sp.row_n ? sp.row_n[row] : sp.n, V = sp.V;
     const float* const prow = sp.p + (sp.row_at ? static_cast<size_t>(sp.row_at[row]) : static_cast<size_t>(row) * V);
     RowInfo info;
@@ -1697,7 +1697,7 @@ __global__ __launch_bounds__(ST, kWavesOf<D>) void solve_kernel(SolveParams sp) 
         return;
     }
     gather_keys<kST>(L.keys, sp.cand + static_cast<size_t>(row) * kSelCap, found, sp.splits);
-    if (tid == 0) { L.count = 0; L.work = again ? sp.info[row].node_tokens : 0.0; }
+    if (tid == 0) { L.count = 0; L.work = AGAIN ? sp.info[row].node_tokens : 0.0; }
 #ifdef GR_PHASE_CLOCKS
     if (tid == 0) { for (int i = 0; i < 24; ++i) L.clk[i] = 0; L.clk_last = clock64(); }
 #endif
@@ -1922,7 +1922,7 @@ __global__ __launch_bounds__(ST, kWavesOf<D>) void solve_kernel(SolveParams sp) 
         const double top = L.Q[hi];
         const double gauge = (tid < h) ? ipow(top, n) / (-L.F[h]) : 1.0;
         const double t = L.tgt[tid];
-        L.wgt[tid] = again ? sp.weight[static_cast<size_t>(row) * KS + tid] : ((t > 0.0) ? gauge * t / pow_diff(top, L.qn[tid], n) : 0.0);
+        L.wgt[tid] = AGAIN ? sp.weight[static_cast<size_t>(row) * KS + tid] : ((t > 0.0) ? gauge * t / pow_diff(top, L.qn[tid], n) : 0.0);
     }
     __syncthreads();
 
@@ -1935,8 +1935,7 @@ __global__ __launch_bounds__(ST, kWavesOf<D>) void solve_kernel(SolveParams sp) 
     if constexpr (!Lds<D, ST>::kKeeps) write_rows();
 
     // ---- the convex programs: program 0 = inner system, then every outer block of two or more tokens
-    int status = GR_ROW_OK, evals = again ? sp.info[row].iterations : 0, par = 0;
-    const int half_done = again ? -1 - sp.info[row].status : -1;
+    int status = GR_ROW_OK, evals = AGAIN ? sp.info[row].iterations : 0, par = 0;
     for (int b = (h > 0 ? 0 : 1); b <= nblk && status != GR_ROW_TRUNC_CAP; ++b) {
         const int lo = (b == 0) ? 0 : L.blo[b];
         const int hi = (b == 0) ? h : L.blo[b + 1];
@@ -1969,11 +1968,11 @@ __global__ __launch_bounds__(ST, kWavesOf<D>) void solve_kernel(SolveParams sp) 
         if (tid < m) L.at[tid] = t0 * scale;
         GR_CLK(L, 4);
         const int rc = solve_program<D>(L, par, sp.newton_ws + static_cast<size_t>(row) * kMaxT * (kMaxT + 1), m, n, ctx, b == 0, slack_target,
-                                        qa, ta * scale, sp.rel_tol, sp.max_iter - (b == half_done ? kPatience : 0), &evals);
-        if (rc > 0 && status == GR_ROW_OK) status = GR_ROW_ITER_CAP;
+                                        qa, ta * scale, sp.rel_tol, sp.max_iter - (AGAIN && sp.info[row].status == -1 - b ? kPatience : 0), &evals);
+        if (rc != 0 && status == GR_ROW_OK) status = GR_ROW_ITER_CAP;
         const double wv = (tid < m) ? exp(L.aal[tid]) : 0.0;
         const double wsum = (b == 0) ? 1.0 : wg_sum(L, par, wv);
-        if (tid < m && (rc >= 0 || L.ctl_bestok)) L.wgt[L.apos[tid]] = (b == 0) ? wv : wv * (w0sum / wsum);
+        if (tid < m && (!kDefers<D, ST> || rc >= 0 || L.ctl_bestok)) L.wgt[L.apos[tid]] = (b == 0) ? wv : wv * (w0sum / wsum);
         __syncthreads();
         if (kDefers<D, ST> && rc < 0) {
             if (tid < kk) sp.weight[static_cast<size_t>(row) * KS + tid] = L.wgt[tid];
@@ -2016,7 +2015,7 @@ __global__ __launch_bounds__(ST, kWavesOf<D>) void solve_kernel(SolveParams sp) 
 // ---- full-vocabulary policies: the convex programs of a row whose steps 1-2 were done in HBM: the
 // inner program over T inside H* and one outer program per block that holds two or more active
 // tokens of T -- the same programs, in the same arithmetic, as the LDS-resident path.
-template <int D, int ST>
+template <int D, int ST, bool AGAIN>
 __global__ __launch_bounds__(ST, kWavesOf<D>) void full_programs_kernel(FullParams fp) {
     constexpr int kST = Lds<D, ST>::kST, kSW = Lds<D, ST>::kSW;
     Lds<D, ST>& L = *reinterpret_cast<Lds<D, ST>*>(gr_lds_raw);
@@ -2024,9 +2023,7 @@ __global__ __launch_bounds__(ST, kWavesOf<D>) void full_programs_kernel(FullPara
     const int n = fp.n, V = fp.V;
     const size_t vs = static_cast<size_t>(V) + 2;
     RowInfo info = fp.info[row];
-    const bool again = !kDefers<D, ST> && fp.deferred;      // uniform: the rows that the launch before has left
-    if (again ? info.status >= 0 : info.status != GR_ROW_OK) return;   // bad, or above the cap on |T|: sampled from p
-    const int half_done = again ? -1 - info.status : -1;
+    if (AGAIN ? info.status >= 0 : info.status != GR_ROW_OK) return;   // bad, or above the cap on |T|: sampled from p
     auto leave = [&](int b, int evals) { if (tid == 0) { RowInfo& left = fp.info[row]; left.status = -1 - b; left.iterations = evals; left.node_tokens = L.work; } };
     const int kk = info.support, h = info.h;
     const RowValues val(fp, info, row);
@@ -2038,10 +2035,10 @@ __global__ __launch_bounds__(ST, kWavesOf<D>) void full_programs_kernel(FullPara
     const double Fh = -info.res_total, stot = Q[kk];
     auto qn = [&](int r) { return val.q(by_rank[r].y) / stot; };
     auto target = [&](int r) { return val.p(by_rank[r].x) - rho[r]; };
-    if (tid == 0) L.work = info.node_tokens;                // 0 but for the rows left
+    if (tid == 0) L.work = AGAIN ? info.node_tokens : 0.0;
     __syncthreads();
 
-    int status = GR_ROW_OK, evals = info.iterations, par = 0;
+    int status = GR_ROW_OK, evals = AGAIN ? info.iterations : 0, par = 0;
     // ---- inner program: T inside H* is the first tcount[0] entries of byq, already by decreasing q
     if (h > 0) {
         const int c_in = fp.tcount[3 * row];
@@ -2073,9 +2070,9 @@ __global__ __launch_bounds__(ST, kWavesOf<D>) void full_programs_kernel(FullPara
             if (tid < m) L.at[tid] *= scale;
             __syncthreads();
             const int rc = solve_program<D>(L, par, fp.newton_ws + static_cast<size_t>(row) * kMaxT * (kMaxT + 1), m, n, ctx, 1, slack_target,
-                                            qa, ta * scale, fp.rel_tol, fp.max_iter - (half_done == 0 ? kPatience : 0), &evals);
-            if (rc > 0) status = GR_ROW_ITER_CAP;
-            if (tid < m && (rc >= 0 || L.ctl_bestok)) weight[L.apos[tid]] = exp(L.aal[tid]);
+                                            qa, ta * scale, fp.rel_tol, fp.max_iter - (AGAIN && fp.info[row].status == -1 ? kPatience : 0), &evals);
+            if (rc != 0) status = GR_ROW_ITER_CAP;
+            if (tid < m && (!kDefers<D, ST> || rc >= 0 || L.ctl_bestok)) weight[L.apos[tid]] = exp(L.aal[tid]);
             if (kDefers<D, ST> && rc < 0) { leave(0, evals); return; }
             __syncthreads();
         }
@@ -2121,11 +2118,11 @@ __global__ __launch_bounds__(ST, kWavesOf<D>) void full_programs_kernel(FullPara
             if (tid < m) L.at[tid] *= scale;
             __syncthreads();
             const int rc = solve_program<D>(L, par, fp.newton_ws + static_cast<size_t>(row) * kMaxT * (kMaxT + 1), m, n, ctx, 0, 0.0,
-                                            qa, ta * scale, fp.rel_tol, fp.max_iter - (half_done == b ? kPatience : 0), &evals);
-            if (rc > 0 && status == GR_ROW_OK) status = GR_ROW_ITER_CAP;
+                                            qa, ta * scale, fp.rel_tol, fp.max_iter - (AGAIN && fp.info[row].status == -1 - b ? kPatience : 0), &evals);
+            if (rc != 0 && status == GR_ROW_OK) status = GR_ROW_ITER_CAP;
             const double wvv = (tid < m) ? exp(L.aal[tid]) : 0.0;
             const double wsum = block_sum<kSW>(wvv, L.redn);
-            if (tid < m && (rc >= 0 || L.ctl_bestok)) weight[L.apos[tid]] = wvv * (w0sum / wsum);
+            if (tid < m && (!kDefers<D, ST> || rc >= 0 || L.ctl_bestok)) weight[L.apos[tid]] = wvv * (w0sum / wsum);
             if (kDefers<D, ST> && rc < 0) { leave(b, evals); return; }
             __syncthreads();
         }
@@ -2140,30 +2137,33 @@ __global__ __launch_bounds__(ST, kWavesOf<D>) void full_programs_kernel(FullPara
 
 // The kernel of the series degree D >= n (2, 4, 8, 16), so that each keeps its series in registers, and of the workgroup that suits the batch.
 enum { kSolve, kPrograms };
-template <int D, int ST> const void* kernel_of(int which) {
-    return which == kSolve ? reinterpret_cast<const void*>(solve_kernel<D, ST>) : reinterpret_cast<const void*>(full_programs_kernel<D, ST>);
-}
+enum { kWide, kSmall, kAgain };      // a workgroup to a compute unit, two, and one for the rows that those leave
 struct Chosen { const void* kernel; int threads, lds; };
-template <int D, int ST> Chosen chosen(int which) { return Chosen{kernel_of<D, ST>(which), ST, static_cast<int>(sizeof(Lds<D, ST>))}; }
-static Chosen choose(int which, int n, bool narrow) {
-    if (n <= 2) return narrow ? chosen<2, kNarrow>(which) : chosen<2, kThreadsOf<2>>(which);
-    if (n <= 4) return narrow ? chosen<4, kNarrow>(which) : chosen<4, kThreadsOf<4>>(which);
-    if (n <= 8) return narrow ? chosen<8, kNarrow>(which) : chosen<8, kThreadsOf<8>>(which);
+template <int D, int ST, bool AGAIN = false> Chosen chosen(int which) {
+    return Chosen{which == kSolve ? reinterpret_cast<const void*>(solve_kernel<D, ST, AGAIN>) : reinterpret_cast<const void*>(full_programs_kernel<D, ST, AGAIN>),
+                  ST, static_cast<int>(sizeof(Lds<D, ST>))};
+}
+template <int D> Chosen chosen_of(int which, int how) {
+    return how == kSmall ? chosen<D, kNarrow>(which) : (how == kAgain ? chosen<D, kThreadsOf<D>, true>(which) : chosen<D, kThreadsOf<D>>(which));
+}
+static Chosen choose(int which, int n, int how) {
+    if (n <= 2) return chosen_of<2>(which, how);
+    if (n <= 4) return chosen_of<4>(which, how);
+    if (n <= 8) return chosen_of<8>(which, how);
     return chosen<16, kThreadsOf<16>>(which);
 }
 
-// A batch on the workgroups that suit it; the rows that the small ones leave, on the large ones.
+// A batch on the workgroups that suit it.
 template <class Params>
 static hipError_t launch_rows(int which, Params params, hipStream_t stream) {
-    const bool narrow = params.B > kOne && params.n <= 8;
+    const bool small = params.B > kOne && params.n <= 8;
     void* args[] = {&params};
-    for (params.deferred = 0; params.deferred <= (narrow ? 1 : 0); ++params.deferred) {
-        const Chosen c = choose(which, params.n, narrow && !params.deferred);
+    for (int how = small ? kSmall : kWide;; how = kAgain) {
+        const Chosen c = choose(which, params.n, how);
         (void)hipLaunchKernel(c.kernel, dim3(params.B), dim3(c.threads), args, c.lds, stream);
         const hipError_t e = hipGetLastError();                  // which clears it: the next call asks again
-        if (e != hipSuccess) return e;
+        if (e != hipSuccess || how != kSmall) return e;
     }
-    return hipSuccess;
 }
 
 hipError_t launch_full_programs(const FullParams& fp, hipStream_t stream) { return launch_rows(kPrograms, fp, stream); }
@@ -2176,10 +2176,10 @@ static_assert(sizeof(Lds<8, kNarrow>) <= 80 * 1024 && sizeof(Lds<4, kNarrow>) <=
 // its inputs and its drafts: 353 us with eight kernels, 407 with two more, in every gr_create.)
 hipError_t solve_kernel_setup(int max_n, int max_B, bool hbm) {
     for (int which = kSolve; which <= (hbm ? kPrograms : kSolve); ++which)
-        for (int narrow = 0; narrow <= (max_B > kOne ? 1 : 0); ++narrow)
+        for (int how = kWide; how <= (max_B > kOne ? kAgain : kWide); ++how)
             for (int n = 2; n <= GR_MAX_N && (n == 2 || n < 2 * max_n); n *= 2) {   // n: the series degrees that serve up to max_n
-                if (narrow && n > 8) continue;
-                const Chosen c = choose(which, n, narrow != 0);
+                if (how != kWide && n > 8) continue;
+                const Chosen c = choose(which, n, how);
                 const hipError_t e = hipFuncSetAttribute(c.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, c.lds);
                 if (e != hipSuccess) return e;
             }
