@@ -279,10 +279,10 @@ struct RatioKey {
     }
 };
 // Buckets of the order: kBucket tokens on average at most (while there are buckets enough), kBucketCap in the LDS of the workgroup that sorts one.
-// With kSamplesPerBucket samples to a bucket, one of twice the average comes up once in 1e6.  Rows of more than 131072 tokens have 4096 samples for all their
-// buckets, so that more of these end above the cap: one in 2000 at 262144 tokens, one in 25 at a million, and from 4 million tokens on, with 2048 buckets
-// for all, most.  Those go by sorted stretches (one row of 2^18 / 2^20 / 2^22 / 2^24 - 1 tokens, the call: 1463 us, 4.1, 16.0 and 67 ms; with the tokens of
-// a bucket compared all with all 2117 us, 5.4, 28 and 294 ms).
+// With kSamplesPerBucket samples to a bucket, four in a million are of twice the average.  Rows of more than 131072 tokens have 4096 samples for all their
+// buckets, so that more of these end above the cap: one in 1500 at 262144 tokens, one in 24 at a million; at 4 million, with 2048 buckets for all, two of
+// five, and beyond that most.  Those go by sorted stretches (one row of 2^18 / 2^20 / 2^22 / 2^24 - 1 tokens, the call: 1463 us, 4.1, 16.0 and 67 ms; with the
+// tokens of a bucket compared all with all 2117 us, 5.4, 28 and 294 ms).
 constexpr int kBucket = 1024, kBucketCap = 2048, kSamplesPerBucket = 32, kLogBuckets = 11;
 __host__ __device__ inline int log_buckets(int tokens) {
     int l = 0;
@@ -372,8 +372,9 @@ __device__ __forceinline__ void scan_step(RunSum& v) {
 // that equal ratios can be split too); the next two kernels move the tokens there, and full_bucket_kernel puts each bucket in order.  The elements keep p and q
 // beside the id: no kernel gathers them.  Where the support is sparse or cut, its list is sampled and not the row.
 // Bound: memory, and the quotients.  1024 rows of 128256 tokens, n = 8: four sorting passes over elements of 8 bytes by one workgroup per row and a
-// gather of the pairs took 6.1 + 1.6 ms; support 0.44, count 0.72, scatter 0.78 and buckets 1.5 ms take their place.  One row 1587 -> 810 us the call,
-// 16 rows 2412 -> 1485, 64 rows cut by a nucleus of 32000 tokens 314 -> 274.
+// gather of the pairs took 6.1 + 1.6 ms; support 0.44, count 0.72, scatter 0.78 and buckets 1.5 ms take their place.  One row 1555 -> 748 us the call,
+// 16 rows 2412 -> 1485, 64 rows cut by a nucleus of 32000 tokens 314 -> 274; 64 rows whose draft logits are the target's but for noise of 1e-2 / 1e-4 / 1e-6
+// 1902 / 1899 / 2112 -> 1053 / 1145 / 1330 (ratios that are few or close crowd in their buckets' cells and go by the bitonic sort).
 template <int NT, bool CUT, int R = 4>
 __global__ __launch_bounds__(NT, CUT ? 1 : 8) void full_support_kernel(FullParams fp) {
     constexpr int kWaves = NT / 64;                              // this workgroup's waves

@@ -14,10 +14,11 @@
 // off below the unit up to 6e-14.
 //
 // One workgroup per row.  Bound: instruction issue of the third of three passes over the row (class, ratio, bin and three LDS additions per token), which takes
-// half of the launch; the first runs at the memory's rate.  Two radix sorts per row (by q/p and by q), gathers and masked prefix scans took 3860 us for 256
-// rows of 128256 tokens, six sizes and ten draft counts; the first form of this 311 us (with a float64 quotient for every token, a pass over the row for
-// every second round and a wave reduction per bin and cell), this 246.  256 rows whose drafts are almost the target 3640 -> 649, of 8192 tokens 324 -> 52, one row
-// of 128256 tokens 1755 -> 135, of 300 tokens and one size 38.6 -> 20.5, with eight sizes and eight draft counts 41.8 -> 38.6 us.
+// half of the launch; the first runs at the memory's rate.  Two radix sorts per row (by q/p and by q), gathers and masked prefix scans took 3877 us for 256
+// rows of 128256 tokens, six sizes and ten draft counts, this 258 of a kernel trace, 210 to 266 the call on different cards.  The call with sorts and now: 256
+// rows whose drafts are almost the target 4082 and 516 us, of 8192 tokens 336 and 90, one row of 128256 tokens 1773 and 156, of 300 tokens and one size 46 and 22, with
+// eight sizes and eight draft counts 50 and 35.  Slower than the sorts where many cells meet few tokens: that row with twelve counts and a draft that is almost
+// the target 51 and 53, 1024 rows of 300 tokens with eight sizes and 16 counts 134 and 143 (eight counts 129 and 127).
 #include "gr_internal.h"
 
 namespace gr {

@@ -2022,8 +2022,9 @@ __global__ __launch_bounds__(ST, kWavesOf<D>) void full_programs_kernel(FullPara
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, row = blockIdx.x;
     const int n = fp.n, V = fp.V;
     const size_t vs = static_cast<size_t>(V) + 2;
+    if (AGAIN && fp.info[row].status >= 0) return;
     RowInfo info = fp.info[row];
-    if (AGAIN ? info.status >= 0 : info.status != GR_ROW_OK) return;   // bad, or above the cap on |T|: sampled from p
+    if (!AGAIN && info.status != GR_ROW_OK) return;   // bad, or above the cap on |T|: sampled from p
     auto leave = [&](int b, int evals) { if (tid == 0) { RowInfo& left = fp.info[row]; left.status = -1 - b; left.iterations = evals; left.node_tokens = L.work; } };
     const int kk = info.support, h = info.h;
     const RowValues val(fp, info, row);
