@@ -101,7 +101,8 @@ int gr_destroy(gr_handle h);
  * accept_prob [B] float32 out: alpha* (Thm 3.1).       status [B] int32 out: GR_ROW_*.
  * The per-row policy stays inside the handle until the next gr_solve.
  * alpha*, the order, H*, the blocks and the truncation sets of a row do not depend on the rows beside it.  Its weights answer their targets to rel_tol in any
- * batch, but not to the last digit the same in all: up to 8 drafts, batches of more than 304 rows run smaller workgroups, whose partial sums are others.
+ * batch, but not to the last digit the same in all: up to 8 drafts, batches of more than 256 (one draft), 448 (two, three) or 320 rows run
+ * smaller workgroups, whose partial sums are others.
  */
 int gr_solve(gr_handle h, const float* p, const float* q, int n, int k, float tol,
              int B, int V, float* accept_prob, int* status, void* hip_stream);

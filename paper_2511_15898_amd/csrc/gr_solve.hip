@@ -48,12 +48,14 @@ __device__ __forceinline__ int padded(int count) { return (count + kScan - 1) / 
 template <int D> constexpr int kThreadsOf = D > 8 ? 256 : 512;
 template <int D> constexpr int kWavesOf = D > 8 ? 1 : 2;
 // With more rows than compute units, two workgroups of four waves share one up to 8 drafts: while one row's stepping wave or its prologue keeps the other waves
-// waiting, the other row evaluates.  The call, one workgroup and two: 300 rows of 32000 tokens, n = 4, k = 64 192 and 165 us, 512 217 and 178;
-// 1024 rows of 1024, n = 4, k = 32 246 and 169, of 128256, n = 8, k = 128 611 and 507 (selection 210).  A row by itself is slower on four waves, and a handful of rows
-// beyond the compute units begins behind the rows that end first, before the slowest one has: 12
-// kinds of rows (n 1 to 8, k 16 to 256, V 400 to 50000), three seeds, one workgroup's time over two's, in the mean and the calls that lose more than 2 %:
-// 264 rows 1.00 and 19 of 36, 288 1.05 and 14, 304 1.09 and 8, 320 1.11 and 7, 384 1.16 and 3, 512 1.28 and 1.
-constexpr int kNarrow = 256, kOne = 304;   // kOne: rows of a batch that have a compute unit each, or wait for one
+// waiting, the other row evaluates.  The call, one workgroup and two: 512 rows of 32000 tokens, n = 4, k = 64 217 and 178 us,
+// 1024 rows of 1024, n = 4, k = 32 246 and 169, of 128256, n = 8, k = 128 611 and 507 (selection 210).  A row by itself is slower on four waves, and a handful of
+// rows beyond the compute units begins behind the rows that end first, before the slowest one has.  So the line lies above their number, and higher for two and
+// three drafts, whose rows take up to 19 evaluations among many of 4; with one there are none.  16 kinds of rows (k 32 to 256, V 400 to 60000), four seeds, one
+// workgroup's time over two's, in the mean and the calls that lose more than 2 %: n = 2 and 3 304 rows 0.96 and 20 of 32, 400 1.01 and 11, 448 1.04 and 8, 512 1.11
+// and 5; n = 4 to 8 264 rows 1.00 and half, 304 1.09 and 9 of 32, 352 1.13 and 3, 400 1.14 and 1, 512 1.23 and none; n = 1 264 rows 1.30 and none.
+constexpr int kNarrow = 256;
+static int most_rows(int n) { return n == 1 ? 256 : (n < 4 ? 448 : 320); }   // of a batch that have a compute unit each, or wait for one
 // A program that asks for more than kPatience evaluations there, or for the fallback, leaves its row to a second launch, of one workgroup to a compute unit, in
 // which it goes on from its best weights and the workgroups of all other rows end at once (2 us): of 43000 rows of 14 kinds one took 1005 evaluations, one 68 and
 // all others 19 at most, and where there is such a row it is the call (1024 rows of 1000 tokens, n = 4, k = 32, 1005 evaluations: 9.9 ms in workgroups of eight
@@ -2157,7 +2159,7 @@ static Chosen choose(int which, int n, int how) {
 // A batch on the workgroups that suit it.
 template <class Params>
 static hipError_t launch_rows(int which, Params params, hipStream_t stream) {
-    const bool small = params.B > kOne && params.n <= 8;
+    const bool small = params.n <= 8 && params.B > most_rows(params.n);
     void* args[] = {&params};
     for (int how = small ? kSmall : kWide;; how = kAgain) {
         const Chosen c = choose(which, params.n, how);
@@ -2177,9 +2179,9 @@ static_assert(sizeof(Lds<8, kNarrow>) <= 80 * 1024 && sizeof(Lds<4, kNarrow>) <=
 // its inputs and its drafts: 353 us with eight kernels, 407 with two more, in every gr_create.)
 hipError_t solve_kernel_setup(int max_n, int max_B, bool hbm) {
     for (int which = kSolve; which <= (hbm ? kPrograms : kSolve); ++which)
-        for (int how = kWide; how <= (max_B > kOne ? kAgain : kWide); ++how)
+        for (int how = kWide; how <= kAgain; ++how)
             for (int n = 2; n <= GR_MAX_N && (n == 2 || n < 2 * max_n); n *= 2) {   // n: the series degrees that serve up to max_n
-                if (how != kWide && n > 8) continue;
+                if (how != kWide && (n > 8 || max_B <= most_rows(n == 2 ? 1 : n))) continue;   // the lowest line of the draft counts that it serves
                 const Chosen c = choose(which, n, how);
                 const hipError_t e = hipFuncSetAttribute(c.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, c.lds);
                 if (e != hipSuccess) return e;

@@ -113,11 +113,11 @@ def test_rows_given_as_logits():
 @pytest.mark.parametrize("n,k,V,logits", [(1, 20, 300, False), (2, 256, 600, False), (3, 33, 1024, True), (4, 64, 1025, False), (5, 200, 700, False),
                                           (8, 128, 2000, True), (8, 9, 333, False)])
 def test_batches_on_both_workgroup_sizes(n, k, V, logits):
-    """Batches of more than 304 rows run two smaller workgroups to a compute unit: the same rows in one batch of 310 and in
-    halves.  The routed masses are summed over other waves, so programs agree to their stopping measure (1e-8), far inside 1e-6."""
+    """Batches of more than 256, 320 or 448 rows, by the draft count, run two smaller workgroups to a compute unit: the same rows in one batch of
+    460 and in halves.  The routed masses are summed over other waves, so programs agree to their stopping measure (1e-8), far inside 1e-6."""
     import torch
     from paper_2511_15898_amd import binding as gr
-    B = 310
+    B = 460
     wl = W.llm_shaped(B=B, V=V, n=n, k=k, temperature=(0.5, 1.5), near_identical_frac=0.2, seed_sub=2000 + V)
     dev = torch.device("cuda:0")
     p, q = torch.from_numpy(wl.p).to(dev), torch.from_numpy(wl.q).to(dev)
@@ -134,7 +134,7 @@ def test_batches_on_both_workgroup_sizes(n, k, V, logits):
         return (pi, given) + tuple(one)
     try:
         whole = [x.cpu().numpy() for x in run(slice(0, B))]
-        halves = [np.concatenate([a.cpu().numpy(), b.cpu().numpy()]) for a, b in zip(run(slice(0, 155)), run(slice(155, B)))]
+        halves = [np.concatenate([a.cpu().numpy(), b.cpu().numpy()]) for a, b in zip(run(slice(0, 230)), run(slice(230, B)))]
     finally:
         gr.gr_destroy(h)
     pi, given, acc, st, tok, ok = zip(whole, halves)
@@ -145,15 +145,15 @@ def test_batches_on_both_workgroup_sizes(n, k, V, logits):
 
 @pytest.mark.parametrize("n,k,V", [(2, 12, 64), (3, 12, 64), (4, 12, 64), (8, 12, 64), (4, 0, 300)])
 def test_programs_that_take_long_in_large_batches(n, k, V):
-    """A tolerance that no evaluation meets: every row with a program of a batch of 310 is left to the second launch, with large workgroups, which goes on
+    """A tolerance that no evaluation meets: every row with a program of a batch of 460 is left to the second launch, with large workgroups, which goes on
     from its best weights through the step's budget and the finite differences to the cap.  Its weights must be those of rows solved to 1e-12 in
-    batches of 155.  Bound: w answers to its target R as R / (P - R) does, P the token's draw probability: 1 + w times the measure, summed over the
+    batches of 230.  Bound: w answers to its target R as R / (P - R) does, P the token's draw probability: 1 + w times the measure, summed over the
     tokens that move with it, for which a thousandfold is allowed at the least.  A cap of 12 evaluations is reached in the first launch."""
     from dataclasses import replace
     from parity_util import run_gpu
-    B = 310
+    B = 460
     wl = W.small(B=B, V=V, n=n, k=k, seed_sub=n + 12)
-    part = lambda rows: replace(wl, B=155, p=wl.p[rows], q=wl.q[rows], drafts=wl.drafts[rows], uniforms=wl.uniforms[rows])
+    part = lambda rows: replace(wl, B=230, p=wl.p[rows], q=wl.q[rows], drafts=wl.drafts[rows], uniforms=wl.uniforms[rows])
     def run(w, **how):
         out = run_gpu(w, 1e-5 if k else 0.05, want_slice=False, export_rows=range(w.B), **how)   # a whole row's programs would end above the cap
         if "rows" in out:
@@ -164,7 +164,7 @@ def test_programs_that_take_long_in_large_batches(n, k, V):
             del out["rows"]
         return out
     def both(**how):
-        first, second = run(part(slice(0, 155)), **how), run(part(slice(155, B)), **how)
+        first, second = run(part(slice(0, 230)), **how), run(part(slice(230, B)), **how)
         return {name: np.concatenate([first[name], second[name]]) for name in first}
     solved, out = both(rel_tol=1e-12), run(wl, rel_tol=1e-17, max_iter=200)
     fine = solved["status"] == 0
