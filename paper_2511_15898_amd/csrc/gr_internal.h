@@ -19,7 +19,7 @@ constexpr int kMaxSplits = 32;            // workgroups that share one row in th
 struct RowInfo {
     int support;        // k' = |V_0|
     int h;              // |H*|
-    int status;         // GR_ROW_*
+    int status;         // GR_ROW_*; below 0 between the two launches of a batch: a row left to the second
     int iterations;     // evaluations of the routed masses, summed over the row's programs
     double alpha_star;  // 1 + psi(H*)
     double res_total;   // sum of residuals p(i) - p_i over tokens outside H* (= 1 - alpha*)
